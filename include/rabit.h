@@ -248,9 +248,8 @@ int rb_couple(const float *W, const uint16_t *g, const uint16_t *h, int K, int o
 /*
  * Effective-weight gradient (Eq. RaBiT-grad-wfp), the straight-through gradient
  * of the shared weight: G = (dL/dY) X^T.  Delta fp16 [N][out], X fp16 [N][in],
- * G fp32 [out][in]; fp32 accumulation over the samples in order.  A plain
- * kernel (one thread per element): for large N a dense GEMM library is faster
- * and G may come from there.  out <= 65535.
+ * G fp32 [out][in]; exact products, fp32 accumulation on the matrix units in an
+ * order that depends on N alone (results repeat bit for bit).  out <= 65535.
  */
 int rb_weight_grad(const uint16_t *Delta, const uint16_t *X, int N, int out, int in, float *G, void *stream);
 

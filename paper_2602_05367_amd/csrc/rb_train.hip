@@ -13,8 +13,8 @@
 //         grad h_i[c] = sum_r B_i[r][c] g_i[r] G[r][c]       (columns: the transposed product)
 //     so one pass over G per direction gives them for every path, whatever the batch size.
 //
-// All three are bound by HBM (4 bytes per weight read); none needs matrix cores.  Every sum runs in
-// a fixed order, so results do not depend on scheduling.
+// The first and the last are bound by HBM (4 bytes per weight read); the weight gradient is a dense
+// contraction on the matrix cores.  Every sum runs in a fixed order, so results do not depend on scheduling.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
@@ -105,15 +105,140 @@ __global__ __launch_bounds__(256) void couple_kernel(const float *__restrict__ W
 }
 
 // --------------------------------------------------------------- gradients ---
-// G[r][c] = sum_n Delta[n][r] X[n][c]: one thread per element, the sum over samples in order.
-__global__ __launch_bounds__(256) void weight_grad_kernel(const __half *__restrict__ Delta, const __half *__restrict__ X,
-                                                          int N, int out, int in, float *__restrict__ G)
+// G = Delta^T X (Eq. RaBiT-grad-wfp) on the matrix cores: fp16 operands, exact products, fp32 sums.
+//
+// Bound by the store of G (4 bytes per weight) up to a few hundred samples and by the matrix units
+// beyond: one tile of WG_ROWS x WG_COLS outputs per workgroup, a wavefront owns 64 x 128 of it (2 x 4
+// accumulators of 32 x 32), two workgroups share a compute unit so that one stores while the other
+// multiplies.  Both operands lie in memory with the samples outermost while the matrix instruction
+// wants eight consecutive samples per lane, so a thread loads a block of samples x 4 columns (8 bytes per
+// sample, whole rows of a tile coalesced), transposes it in registers (one byte permute per dword)
+// and writes one group of consecutive samples per column to LDS.  LDS holds [group of 8 samples][slot][8 samples]
+// with the columns of a wavefront de-interleaved (slot 32 i + q holds column 4 q + i), so that
+//   * a write covers consecutive slots (no bank conflicts), and so does an operand read;
+//   * the four column accumulators of a lane are four consecutive columns of G: 16-byte stores.
+// 4096 x 11008, 512 samples: 0.090 ms (0.51 PFLOP/s, 2.0 TB/s of G stored), against 13.8 ms with one
+// thread per element and a scalar loop over the samples.
+constexpr int WG_ROWS = 128, WG_COLS = 256, WG_N = 32;      // tile of G, samples per step
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+// four columns of one sample (zero past the end of the samples or the columns); VEC: 8-byte loads
+template <bool VEC>
+__device__ __forceinline__ uint2 load_cols(const __half *p, int n, int N, int c, int width)
 {
-    const int c = blockIdx.x * 256 + threadIdx.x, r = blockIdx.y;
-    if (c >= in) return;
-    float s = 0.f;
-    for (int n = 0; n < N; ++n) s = __builtin_fmaf(__half2float(Delta[(size_t)n * out + r]), __half2float(X[(size_t)n * in + c]), s);
-    G[(size_t)r * in + c] = s;
+    uint2 v = make_uint2(0u, 0u);
+    if (n >= N) return v;
+    const unsigned short *row = reinterpret_cast<const unsigned short *>(p) + (size_t)n * width;
+    if (VEC) {
+        if (c < width) v = *reinterpret_cast<const uint2 *>(row + c);
+    } else {
+        if (c < width) v.x = row[c];
+        if (c + 1 < width) v.x |= (uint32_t)row[c + 1] << 16;
+        if (c + 2 < width) v.y = row[c + 2];
+        if (c + 3 < width) v.y |= (uint32_t)row[c + 3] << 16;
+    }
+    return v;
+}
+__device__ __forceinline__ uint32_t low_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
+__device__ __forceinline__ uint32_t high_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+
+template <bool VEC>
+__global__ __launch_bounds__(256, 2) void weight_grad_kernel(const __half *__restrict__ Delta, const __half *__restrict__ X,
+                                                             int N, int out, int in, float *__restrict__ G)
+{
+    constexpr int A_BYTES = WG_ROWS * WG_N * 2, B_BYTES = WG_COLS * WG_N * 2;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2][A_BYTES + B_BYTES];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wave >> 1, wc = wave & 1;
+    // workgroups go round the eight XCDs: each takes a run of tiles, row tiles fastest, so that one
+    // block of columns of X and all of Delta (N x out) are what its L2 sees
+    const int tiles_r = (out + WG_ROWS - 1) / WG_ROWS, tiles = tiles_r * ((in + WG_COLS - 1) / WG_COLS);
+    const int per = (tiles + 7) / 8, tile = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || tile >= tiles) return;
+    const int r0 = tile % tiles_r * WG_ROWS, c0 = tile / tiles_r * WG_COLS;
+
+    // this thread's part of a step: 4 samples x 4 columns of Delta, 8 samples x 4 columns of X
+    const int qa = tid & 31, na = tid >> 5, qb = tid & 63, nb = tid >> 6;
+    const int slot_a = (qa >> 4) * 64 + (qa & 15), slot_b = (qb >> 5) * 128 + (qb & 31);
+    uint2 da[4], xb[8];
+    auto request = [&](int n0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) da[j] = load_cols<VEC>(Delta, n0 + 4 * na + j, N, r0 + 4 * qa, out);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) xb[j] = load_cols<VEC>(X, n0 + 8 * nb + j, N, c0 + 4 * qb, in);
+    };
+    auto put = [&](uint8_t *buf) {
+        uint8_t *const a = buf + (na >> 1) * (WG_ROWS * 16) + slot_a * 16 + (na & 1) * 8;
+        *reinterpret_cast<uint2 *>(a) = make_uint2(low_halves(da[0].x, da[1].x), low_halves(da[2].x, da[3].x));
+        *reinterpret_cast<uint2 *>(a + 16 * 16) = make_uint2(high_halves(da[0].x, da[1].x), high_halves(da[2].x, da[3].x));
+        *reinterpret_cast<uint2 *>(a + 32 * 16) = make_uint2(low_halves(da[0].y, da[1].y), low_halves(da[2].y, da[3].y));
+        *reinterpret_cast<uint2 *>(a + 48 * 16) = make_uint2(high_halves(da[0].y, da[1].y), high_halves(da[2].y, da[3].y));
+        uint8_t *const b = buf + A_BYTES + nb * (WG_COLS * 16) + slot_b * 16;
+        uint4 v[4];
+        uint32_t *const w = reinterpret_cast<uint32_t *>(v);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            w[j] = low_halves(xb[2 * j].x, xb[2 * j + 1].x);
+            w[4 + j] = high_halves(xb[2 * j].x, xb[2 * j + 1].x);
+            w[8 + j] = low_halves(xb[2 * j].y, xb[2 * j + 1].y);
+            w[12 + j] = high_halves(xb[2 * j].y, xb[2 * j + 1].y);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4 *>(b + i * 32 * 16) = v[i];
+    };
+
+    v16f acc[2][4];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[m][i][e] = 0.f;
+
+    request(0);
+    put(lds[0]);
+    int cur = 0;
+    for (int n0 = 0; n0 < N; n0 += WG_N, cur ^= 1) {
+        const bool more = n0 + WG_N < N;
+        if (more) request(n0 + WG_N);
+        __syncthreads();                                   // this step's tile is complete, the other one free
+        const uint8_t *const a = lds[cur] + (wr * 64 + (lane & 31)) * 16, *const b = lds[cur] + A_BYTES + (wc * 128 + (lane & 31)) * 16;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            const int group = 2 * kk + (lane >> 5);
+            v8h av[2], bv[4];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) av[m] = *reinterpret_cast<const v8h *>(a + group * (WG_ROWS * 16) + m * 32 * 16);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) bv[i] = *reinterpret_cast<const v8h *>(b + group * (WG_COLS * 16) + i * 32 * 16);
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[m][i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[m], bv[i], acc[m][i], 0, 0, 0);
+        }
+        if (more) put(lds[cur ^ 1]);
+    }
+
+    // accumulator element e of a lane: matrix row rho = 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32;
+    // row block m holds row 4 (rho % 16) + 2 m + rho / 16 of the wavefront's 64
+    const int c = c0 + wc * 128 + 4 * (lane & 31);
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int rho = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+            const int r = r0 + wr * 64 + 4 * (rho & 15) + 2 * m + (rho >> 4);
+            if (r >= out) continue;
+            float *const dst = G + (size_t)r * in + c;
+            if (VEC) {
+                if (c < in) *reinterpret_cast<float4 *>(dst) = make_float4(acc[m][0][e], acc[m][1][e], acc[m][2][e], acc[m][3][e]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (c + i < in) dst[i] = acc[m][i][e];
+            }
+        }
 }
 
 // Both scale gradients from one pass over G.  A wavefront takes a slab of ROW_SLICE rows by 256
@@ -242,9 +367,15 @@ extern "C" int rb_weight_grad(const uint16_t *Delta, const uint16_t *X, int N, i
 {
     if (!Delta || !X || !G) return RB_ERR_NULL;
     if (N < 1 || out < 1 || in < 1 || out > 65535) return RB_ERR_SHAPE;
-    hipLaunchKernelGGL(weight_grad_kernel, dim3((unsigned)((in + 255) / 256), (unsigned)out), dim3(256), 0,
-                       static_cast<hipStream_t>(stream_), reinterpret_cast<const __half *>(Delta),
-                       reinterpret_cast<const __half *>(X), N, out, in, G);
+    const int tiles = (out + WG_ROWS - 1) / WG_ROWS * ((in + WG_COLS - 1) / WG_COLS);
+    const dim3 grid((unsigned)((tiles + 7) / 8 * 8));
+    const bool vec = out % 4 == 0 && in % 4 == 0 && (((uintptr_t)Delta | (uintptr_t)X) & 7) == 0 && ((uintptr_t)G & 15) == 0;
+    const __half *d = reinterpret_cast<const __half *>(Delta), *x = reinterpret_cast<const __half *>(X);
+    hipStream_t stream = static_cast<hipStream_t>(stream_);
+    if (vec)
+        hipLaunchKernelGGL(weight_grad_kernel<true>, grid, dim3(256), 0, stream, d, x, N, out, in, G);
+    else                                                       // rows that do not start at multiples of 8 bytes
+        hipLaunchKernelGGL(weight_grad_kernel<false>, grid, dim3(256), 0, stream, d, x, N, out, in, G);
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;
 }
 

@@ -81,6 +81,35 @@ def test_scale_gradients_against_the_oracle(K, out, inn, N):
         assert err.max() <= 1e-5, err
 
 
+@pytest.mark.parametrize("N,out,inn,shift", [
+    (1, 128, 256, 0), (31, 124, 252, 0), (33, 132, 260, 0), (64, 129, 255, 0),      # around one tile of G and one step of samples
+    (65, 300, 1056, 1), (40, 4, 32, 0), (7, 1, 1, 0), (100, 64, 2052, 3)])           # pointers at odd elements, tiny and wide
+def test_weight_gradient_tiles_and_tails(N, out, inn, shift):
+    """Every element of G against fp64.  Bound: products of two fp16 values are exact in fp32, so only
+    the N additions round: |error| <= N 2^-23 sum_n |Delta| |X| (twice the half-ulp bound, for an
+    accumulator that truncates).  One sample in four has Delta in the fp16 subnormals.  Nothing
+    outside G is written."""
+    rng = synth.child_rng(5, 603, N, out, inn)
+    X = synth.outlier_activations(rng, N, inn)
+    D = rng.standard_normal((N, out)) * 0.1
+    D[::4] *= 1e-4
+    D = D.astype(np.float16)
+
+    def at(a, shift):                                          # `a` in device memory, `shift` elements past an aligned address
+        flat = torch.zeros(a.size + shift, dtype=torch.float16, device="cuda")
+        flat[shift:].copy_(torch.from_numpy(a).flatten())
+        return flat
+    Dd, Xd = at(D, shift), at(X, shift)
+    G = torch.full((out * inn + 64,), float("nan"), dtype=torch.float32, device="cuda")
+    print(f"weight gradient {out}x{inn} N={N} shift={shift}", flush=True)
+    assert rb.lib.rb_weight_grad(Dd.data_ptr() + 2 * shift, Xd.data_ptr() + 2 * shift, N, out, inn, G.data_ptr(), None) == rb.RB_OK
+    torch.cuda.synchronize()
+    assert torch.isnan(G[out * inn:]).all()
+    D64, X64 = D.astype(np.float64), X.astype(np.float64)
+    err = np.abs(G[:out * inn].cpu().numpy().reshape(out, inn) - D64.T @ X64)
+    assert np.all(err <= N * 2.0 ** -23 * (np.abs(D64).T @ np.abs(X64)))
+
+
 def test_training_entry_points_reject_bad_arguments():
     W = torch.zeros((4, 32), dtype=torch.float32, device="cuda")
     g = torch.zeros((2, 4), dtype=torch.float16, device="cuda")
