@@ -45,9 +45,9 @@ extern "C" {
 
 /* K = 2 is the 2-bit layer every kernel here is built for.  K = 3 (the 3-bit variant of the
  * paper's packing appendix): stacks run on the matrix cores (one token on the fused decode kernel,
- * 2..16 tokens on the small-batch kernel), single calls of 6 tokens or more too (the small-batch
- * kernel up to 12 fp16 tokens, the many-token kernel otherwise), shorter single calls on the
- * generic sign-XOR + add kernel, which also runs K = 1. */
+ * 2..16 tokens on the few-token kernel), single calls of 6 tokens or more too (the few-token kernel
+ * up to 64 tokens, the many-token kernel beyond), shorter single calls on the generic sign-XOR + add
+ * kernel, which also runs K = 1. */
 #define RB_MAX_K 3
 
 /* element types for rb_linear_gemm */
@@ -103,8 +103,9 @@ int rb_linear_gemv(const rb_layer *L, const uint16_t *x, uint16_t *y,
 /*
  * Batched form, T tokens: Y[t] = layer(X[t]).  X device [T][in] of act_dtype
  * (RB_F16 or RB_BF16), Y device [T][out] of out_dtype (RB_F16, RB_BF16, RB_F32).
- * Small T streams the weights once for all tokens; large T runs as a dense
- * contraction on the matrix cores: beyond 32 tokens as Y = W_hat X with the
+ * Up to 64 tokens the weights are streamed once for all tokens and every product of
+ * scale and activation is exact; larger T runs as a dense
+ * contraction on the matrix cores, Y = W_hat X with the
  * effective weight W_hat = sum_k g_k (.) B_k (.) h_k (the form Alg. 2 gives for
  * batched inputs), which the kernel builds in fp16 registers from the packed
  * signs (two roundings per weight, a few 1e-4 relative on the output; fp32
@@ -120,11 +121,9 @@ int rb_linear_gemm(const rb_layer *L, const void *X, void *Y, int T,
  * status codes as rb_linear_gemm without the workspace pair; the scratch memory of the many-token
  * kernel is a device array inside the library (RB_NOALLOC_SCRATCH_BYTES per GPU that uses the
  * library, held until the process ends).  The call allocates nothing on host or device.  It returns
- * RB_ERR_WORKSPACE when rb_workspace_bytes(L, 1, 1, T) of the many-token kernel exceeds
- * RB_NOALLOC_SCRATCH_BYTES (roughly T_padded * in above 4 M elements; a three-path layer at up to
- * 32 tokens takes the generic kernel then, which needs no scratch memory, and where the variant
- * with a workspace takes the small-batch kernel this one takes the many-token kernel: same result
- * to the tolerance, not bit for bit).  Every call on one GPU
+ * RB_ERR_WORKSPACE when rb_workspace_bytes(L, 1, 1, T) of the many-token kernel (more than 64
+ * tokens) exceeds RB_NOALLOC_SCRATCH_BYTES (T_padded * in above 16 M elements; a three-path layer
+ * that wide takes the generic kernel at up to 32 tokens).  Every call on one GPU
  * shares that GPU's array: calls that may overlap in time on one GPU (different streams or
  * threads) race and must be ordered by the caller; calls on one stream are ordered already.
  * rb_noalloc_scratch_bytes returns RB_NOALLOC_SCRATCH_BYTES.
@@ -140,9 +139,8 @@ size_t rb_noalloc_scratch_bytes(void);
  * layers[ops[n].layer] to bufs[ops[n].src] and writes bufs[ops[n].dst]; every
  * buffer is device fp16 [T][width].  The result of each op equals
  * rb_linear_gemm on the same input (bit for bit for T <= 2 and T > 16; for
- * 3 <= T <= 16 a stack runs on the fused decode kernel or the small-batch
- * kernel while a single call takes the many-token kernel, and they agree to the
- * accuracy all are held to).  An op may read any buffer written by an
+ * 3 <= T <= 16 a stack may run on another kernel or with another order of its
+ * sums, and they agree to the accuracy all are held to).  An op may read any buffer written by an
  * earlier op (or never written: stack inputs); dst buffers must be distinct
  * from the op's src.  layers, ops and bufs are host arrays; bufs holds n_bufs
  * device pointers.  Activations are expected to be finite: an infinity or NaN
@@ -165,11 +163,10 @@ int rb_layer_stack(const rb_layer *layers, int n_layers,
  * between runs the caller must not write to the workspace nor change layers,
  * buffers addresses or T; rb_stack_forget drops the library's host-side record
  * of a workspace (call it before the memory is reused for something else).
- * Two paths: T <= 4 runs as one launch; 5 <= T <= 7 as one launch per group
- * of four consecutive tokens (every layer's out a multiple of 8, at least two
- * ops); 8 <= T <= 16 on the small-batch kernel (one pass over the weights for all
+ * Two paths: T <= 4 runs as one launch; 5 <= T <= 16 on the few-token kernel (at
+ * least two ops; one pass over the weights for all
  * tokens, one launch per group of independent ops).  Three paths in every
- * layer: T = 1 as one launch, 2 <= T <= 16 on the small-batch kernel, which
+ * layer: T = 1 as one launch, 2 <= T <= 16 on the few-token kernel, which
  * also takes stacks that mix two- and three-path layers.
  * rb_stack_prepare returns RB_ERR_UNSUPPORTED for stacks that only
  * rb_layer_stack's general path can run (K = 1, T > 16, an output read by more
@@ -288,11 +285,13 @@ int rb_stream_read_groups(void);
 
 /* Which kernel family the most recent compute call of this thread enqueued:
  * RB_PATH_NONE, RB_PATH_SIGNADD (generic sign-XOR + add kernel, one launch per
- * op), RB_PATH_GEMM (many-token matrix-core GEMM, one launch per op),
+ * op), RB_PATH_GEMM (matrix-core GEMM of a single call: the few-token or the many-token kernel, one
+ * launch per op),
  * RB_PATH_MX (matrix-core decode kernels: one layer and token in one launch,
- * or all ops of a stack in one persistent launch) or RB_PATH_BATCH (small-batch
+ * or all ops of a stack in one persistent launch) or RB_PATH_BATCH (few-token
  * kernel of a stack: one pass over the weights for up to 16 tokens, two or
- * three paths, one launch per group of independent ops).  For tests and
+ * three paths, one launch per group of independent ops; also a single three-path
+ * call of 6 to 12 fp16 tokens).  For tests and
  * benchmarks that must know what they measured. */
 #define RB_PATH_NONE    0
 #define RB_PATH_SIGNADD 1

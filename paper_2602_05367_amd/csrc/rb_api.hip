@@ -58,14 +58,9 @@ extern "C" int rb_stack_prepare(const rb_layer *layers, int n_layers, const rb_s
     const int rc = check_stack(layers, n_layers, ops, n_ops, bufs, n_bufs, T, workspace, workspace_bytes);
     if (rc != RB_OK) return rc;
     if (!workspace) return RB_ERR_WORKSPACE;
-    rb::forget_pairs(workspace);
     rb::batch::forget_plan(workspace);
     if (n_ops > 1 && rb::batch_applies(layers, n_layers, T))
-        return rb::batch::prepare_plan(layers, ops, n_ops, bufs, T, workspace, workspace_bytes,
-                                       static_cast<hipStream_t>(stream));
-    if (T > 4)
-        return rb::prepare_pairs(layers, n_layers, ops, n_ops, bufs, n_bufs, T, workspace, workspace_bytes,
-                                 static_cast<hipStream_t>(stream));
+        return rb::batch::prepare_plan(layers, ops, n_ops, bufs, T, workspace, workspace_bytes);
     for (int n = 0; n < n_ops; ++n)
         if (!rb::mx::layer_supported(&layers[ops[n].layer], T)) return RB_ERR_UNSUPPORTED;
     return rb::mx::prepare_plan(layers, ops, n_ops, bufs, T, workspace, workspace_bytes,
@@ -80,9 +75,7 @@ extern "C" int rb_stack_run(void *workspace, size_t workspace_bytes, void *strea
         if (rc == RB_OK) rb::set_last_path(RB_PATH_BATCH);
         return rc;
     }
-    rc = rb::run_pairs(workspace, workspace_bytes, static_cast<hipStream_t>(stream));
-    if (rc == RB_ERR_UNSUPPORTED)
-        rc = rb::mx::launch_plan(workspace, workspace_bytes, static_cast<hipStream_t>(stream));
+    rc = rb::mx::launch_plan(workspace, workspace_bytes, static_cast<hipStream_t>(stream));
     if (rc == RB_OK) rb::set_last_path(RB_PATH_MX);
     return rc;
 }
@@ -92,8 +85,6 @@ extern "C" int rb_stack_status(const void *workspace, void *stream)
     if (!workspace) return RB_ERR_NULL;
     if (rb::batch::has_plan(workspace))      // no hand-over inside a launch: nothing a run could give up
         return hipStreamSynchronize(static_cast<hipStream_t>(stream)) == hipSuccess ? RB_OK : RB_ERR_HIP;
-    const int rc = rb::pairs_status(workspace, static_cast<hipStream_t>(stream));
-    if (rc != RB_ERR_UNSUPPORTED) return rc;
     return rb::mx::plan_status(workspace, static_cast<hipStream_t>(stream));
 }
 
@@ -102,8 +93,6 @@ extern "C" int rb_stack_waited(const void *workspace, void *stream, unsigned lon
     if (!workspace || !tiles) return RB_ERR_NULL;
     *tiles = 0;
     if (rb::batch::has_plan(workspace)) return RB_OK;
-    const int rc = rb::pairs_status(workspace, static_cast<hipStream_t>(stream), tiles);
-    if (rc != RB_ERR_UNSUPPORTED) return rc;
     return rb::mx::plan_status(workspace, static_cast<hipStream_t>(stream), tiles);
 }
 
@@ -112,10 +101,8 @@ extern "C" int rb_stack_gave_up(const void *workspace, void *stream, int *reason
     if (!workspace || !reason) return RB_ERR_NULL;
     *reason = 0;
     if (rb::batch::has_plan(workspace)) return RB_OK;
-    const int rc = rb::pairs_status(workspace, static_cast<hipStream_t>(stream), nullptr, reason);
-    if (rc != RB_ERR_UNSUPPORTED) return rc == RB_ERR_HANDOVER ? RB_OK : rc;
-    const int rc2 = rb::mx::plan_status(workspace, static_cast<hipStream_t>(stream), nullptr, reason);
-    return rc2 == RB_ERR_HANDOVER ? RB_OK : rc2;
+    const int rc = rb::mx::plan_status(workspace, static_cast<hipStream_t>(stream), nullptr, reason);
+    return rc == RB_ERR_HANDOVER ? RB_OK : rc;
 }
 
 extern "C" int rb_stack_set_option(int option, int value)
@@ -130,7 +117,6 @@ extern "C" int rb_stack_set_option(int option, int value)
 extern "C" int rb_stack_forget(const void *workspace)
 {
     if (!workspace) return RB_ERR_NULL;
-    rb::forget_pairs(workspace);
     rb::mx::forget_plan(workspace);
     rb::batch::forget_plan(workspace);
     return RB_OK;

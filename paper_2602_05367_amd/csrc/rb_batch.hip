@@ -1,597 +1,459 @@
-// Small-batch path of the residual-binary layer (3 to 16 tokens, and any batch up to 16 for three
-// paths): every op of a stack streams its packed weights ONCE for all tokens.
+// Few-token kernel of the residual-binary layer: single calls and stacks of a handful to a few dozen
+// tokens, two or three paths.  Every op streams its packed weights ONCE for all tokens.
 //
-// Section 4.1: Y[t] = sum_k g_k (.) (B_k (h_k (.) X[t])).  The arithmetic is the one of the decode
-// kernels (rb_mx.h): signs as fp4 +-1 left operands of v_mfma_scale_f32_16x16x128_f8f6f4, the
-// scaled input u_k = h_k (.) x as a sum of four bf8 terms in the right operand.  What differs is
-// the shape of the work:
-//   * the 16 columns of a right operand are 4 tokens x 4 terms of ONE path, so a sign tile costs
-//     K * ceil(T / 4) * 2 matrix instructions and its sign expansion is done once for all tokens;
-//   * the right operands of a column tile (4 KB per path and group of four tokens) are staged in
-//     LDS and shared by the sixteen wavefronts of a workgroup; the staging of the next column
-//     tile overlaps the matrix instructions of the present one;
-//   * a workgroup owns R row tiles (16 rows each) and all columns: wavefront (r, s) takes row tile
-//     r and every S-th of the 2 K (128-column half, path) pieces of a sign tile, R * S = 16.  The
-//     partial sums of the S wavefronts of a row tile meet in LDS, where the workgroup adds them in
-//     a fixed order, rounds to fp16, stores Y and writes the expanded input of the ops that read
-//     Y.  Nothing is exchanged between workgroups, so a launch needs no counters, no scratch
-//     memory and no device-scope traffic; an op of 4096 rows is 64 workgroups, which at these
-//     sizes (a few hundred KB per workgroup) is bound by launch and memory latency, not by the
-//     number of compute units it covers;
-//   * the ops of a stack that do not depend on each other (q/k/v, gate/up of a transformer block)
-//     run in one launch; ops that depend on each other are ordered by the stream.
+// Section 4.1: Y[t] = sum_k g_k (.) (B_k (h_k (.) X[t])), here with the input scale on the side of the
+// signs: the left operand of v_mfma_f32_16x16x32_f16 is +-h_k[j] (the stored fp16 scale with the sign
+// bit of the weight put in), the right operand is the fp16 activation itself.  Both are exact, so are
+// their products, and only fp32 sums round; the activation is shared by the paths, nothing about the
+// input is prepared, and an op is one launch.  What bounds it:
+//   * a launch of a 4096-wide op moves 4 MB of signs, half a microsecond of HBM time, so it is a
+//     chain of latencies (launch, one trip to memory, the matrix instructions, the sum over the
+//     wavefronts): the compute units are filled and every wavefront asks for all it needs at once;
+//   * beyond that, vector instructions: three per two weights and path (a byte permute that brings
+//     two sign bits to bits 15 and 31, one three-input logic operation that puts them on the scales,
+//     and a share of the shifts), 0.7 to 0.9 k clocks per 16 x 256 tile and SIMD, where the matrix
+//     instructions of 16 tokens take 0.26 k.
+// Shape: a workgroup owns P row tiles (16 rows) and all columns; its up to sixteen wavefronts share out the
+// column tiles, each takes all P row tiles of its columns, so an activation is read from memory by
+// one wavefront of the workgroup.  The partial outputs of the wavefronts meet in LDS and are added in
+// a fixed order.  Nothing is exchanged between workgroups: no counters, no scratch memory, results do
+// not depend on scheduling.  The ops of a stack that do not depend on each other (q/k/v, gate/up of
+// a transformer block) run in one launch; dependent ones are ordered by the stream.
+//
+// Measured (start: bf8 term expansions staged in LDS with a ring of copies, a set-up launch per input,
+// four launches for a single call): 7B-shaped dependent chain, 128 launches, 2.51 -> 1.42 ms at 8
+// tokens and 3.09 -> 1.61 ms at 16; a launch takes 7.5 us (4096 x 4096, one row tile per workgroup) to 17 us
+// (2 x 11008 x 4096, six), of which a dependent launch by itself is 4.7.  Single calls: 4096 x 11008
+// with three paths at 16 tokens 107 -> 17 us, 10999 x 4128 with two at 7 tokens 42 -> 13 us.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
 #include <atomic>
-#include <cstring>
 #include <map>
 #include <memory>
 #include <mutex>
 #include <vector>
 
 #include "rabit.h"
+#include "rb_device.h"
 #include "rb_internal.h"
 #include "rb_layout.h"
-#include "rb_mx_device.h"
 
 namespace rb {
 namespace batch {
 
-using mx::v4f;
-using mx::v4i;
-using mx::v8i;
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
-constexpr int MAX_T = 16;
-constexpr int MAX_CONS = 3;            // ops that read one op's output inside a stack
-constexpr int WAVES = 16;              // wavefronts of a workgroup
-constexpr int THREADS = WAVES * 64;
+constexpr int STACK_MAX_T = 16;        // tokens of a stack
 constexpr int MAX_STAGE_OPS = 8;       // independent ops that share a launch
-// S wavefronts share P row tiles, each taking every S-th piece (128-column half x path) of their
-// sign tiles; a workgroup owns R = 16 / S * P row tiles.  Few row tiles per workgroup make many
-// workgroups out of a small op; many row tiles share the staged right operands among more rows,
-// which is what counts when a launch has workgroups enough anyway (at 16 tokens the operands of a
-// column tile are 32 KB, a sign tile 1 KB).  With P = 2 a wavefront reads an operand from LDS once
-// for two matrix instructions: at 16 tokens the reads of the operands, 2 KB per instruction, are
-// what a compute unit spends most of a column tile on.  The form is chosen per launch (see
-// prepare_plan): two paths (S, P) = (2, 2), (4, 2) or (4, 1), i.e. 16, 8 or 4 row tiles per
-// workgroup; three paths (2, 1) (two row tiles of three paths would need 96 accumulator registers
-// at 16 tokens).
-struct Form { int S, P; };
-__host__ __device__ constexpr int n_forms(int K) { return K == 2 ? 3 : 1; }
-__host__ __device__ constexpr Form form_of(int K, int i)     // by falling row tiles per workgroup
-{
-    return K == 2 ? (i == 0 ? Form{2, 2} : i == 1 ? Form{4, 2} : Form{4, 1}) : Form{2, 1};
-}
-__host__ __device__ constexpr int block_tiles(int S, int P) { return WAVES / S * P; }      // row tiles of a workgroup
-constexpr int WANT_GROUPS = 256;       // workgroups a launch should have before it takes larger row blocks
-constexpr size_t MAX_EXPAND = 1024;
 
-#define RB_LDS(p) ((__attribute__((address_space(3))) void *)(p))
-// Pointers read from the op table are generic; dereferencing them as such makes FLAT instructions,
-// which may touch LDS as far as the hardware and the compiler know: every one of them would wait
-// for all copies into LDS that are still in flight.
-#define RB_GLOBAL(T, p) ((__attribute__((address_space(1))) T *)(p))
+// Wavefronts of a workgroup at most, and row tiles per workgroup: accumulators take 4 P K G
+// registers and the activations of a column tile up to 32 G, of 128 with sixteen wavefronts per compute unit
+// and 256 with eight
+__host__ __device__ constexpr int max_waves(int G) { return G <= 2 ? 16 : 8; }
+__host__ __device__ constexpr bool p_available(int K, int G, int P) { return P == 1 || P * K <= (G == 1 ? 12 : 6); }
 
-__host__ __device__ constexpr int groups_of(int T) { return (T + 3) / 4; }
-// bytes of the right operands of one column tile: [128-column block][path][token group] x 2 KB,
-// each the register image the matrix instruction wants: [half j of the contraction][lane col + 16 q][16 bytes]
-__host__ __device__ constexpr size_t tile_operand_bytes(int K, int G) { return (size_t)2 * K * G * 2048; }
-__host__ __device__ inline size_t operand_bytes(int in, int K, int G) { return (size_t)col_tiles(in) * tile_operand_bytes(K, G); }
-// byte offset of the 16-byte group (16 consecutive input columns starting at j0, path k, token
-// group g, operand column c = 4 * (token % 4) + term)
-__host__ __device__ inline size_t operand_group_offset(int K, int G, int j0, int k, int g, int c)
-{
-    const int b = j0 >> 7, jj = j0 & 127, q = (jj & 63) >> 4, j = jj >> 6;
-    return ((size_t)(b * K + k) * G + g) * 2048 + (size_t)j * 1024 + (size_t)(q * 16 + c) * 16;
-}
-
-struct Reader {
-    uint8_t *up;              // expanded input of the reading op
-    const uint16_t *h;        // its input scales, fp16 [K][in]
-    float sc[RB_MAX_K];       // its power-of-two input scaling per path
-    int in, K;
-};
 struct Op {
     const uint32_t *bits;     // native sign tiles
     const uint16_t *g;        // fp16 [K][out]
     const uint16_t *h;        // fp16 [K][in]
-    const uint16_t *x;        // fp16 [T][in]: the input buffer (read by the expansion kernel only)
-    uint16_t *y;              // fp16 [T][out]
-    uint8_t *up;              // expanded input of this op
-    int out, in, K;
-    int RT, CT;               // row tiles, column tiles
+    const void *x;            // [T][in]
+    void *y;                  // [T][out]
+    int out, in;
     int wg0;                  // first workgroup of this op inside its launch
-    int n_cons;
-    float sc[RB_MAX_K];       // power-of-two input scaling per path (max |h_k| * sc in [1/4, 1/2))
-    float inv_sc[RB_MAX_K];
-    Reader cons[MAX_CONS];
+    int h_even;               // h starts at a multiple of four bytes
 };
-
-// ------------------------------------------------------------- set-up kernels ---
-// PREP_SPLIT workgroups per op share the zero fill of its expanded input (padding columns and
-// tokens read as zero; 1.4 MB for 11008 columns at 16 tokens); the first also works out the input
-// scaling of each path, copied to the ops that read from it later by link_kernel.
-constexpr int PREP_SPLIT = 8;
-__global__ __launch_bounds__(256) void prep_kernel(Op *ops, int T)
-{
-    Op &op = ops[blockIdx.x];
-    __shared__ float red[256];
-    for (int p = 0; p < op.K && blockIdx.y == 0; ++p) {
-        float m = 0.f;
-        for (int j = threadIdx.x; j < op.in; j += 256)
-            m = fmaxf(m, fabsf(__half2float(reinterpret_cast<const __half *>(op.h)[(size_t)p * op.in + j])));
-        red[threadIdx.x] = m;
-        __syncthreads();
-        for (int s = 128; s > 0; s >>= 1) {
-            if ((int)threadIdx.x < s) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + s]);
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            const float sc = mx::input_scale(red[0]);
-            op.sc[p] = sc;
-            op.inv_sc[p] = 1.f / sc;
-        }
-        __syncthreads();
-    }
-    const size_t n16 = operand_bytes(op.in, op.K, groups_of(T)) / 16;
-    uint4 *up = reinterpret_cast<uint4 *>(op.up);
-    for (size_t i = blockIdx.y * 256 + threadIdx.x; i < n16; i += 256 * PREP_SPLIT) up[i] = make_uint4(0, 0, 0, 0);
-}
-
-// second pass (needs every op's scaling): what a producer must know about its readers
-__global__ void link_kernel(Op *ops, const int *cons_index, int n_ops)
-{
-    const int o = blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= n_ops) return;
-    Op &op = ops[o];
-    for (int c = 0; c < op.n_cons; ++c) {
-        const Op &m = ops[cons_index[o * MAX_CONS + c]];
-        Reader r;
-        r.up = m.up; r.h = m.h; r.in = m.in; r.K = m.K;
-        for (int p = 0; p < RB_MAX_K; ++p) r.sc[p] = p < m.K ? m.sc[p] : 1.f;
-        op.cons[c] = r;
-    }
-}
-
-// Input scaling u_k = h_k (.) x (Section 4.1) for ops whose input comes from outside the stack,
-// as four bf8 terms in operand order.  A thread takes 16 consecutive columns of one token and path
-// (in % 32 == 0): 32 bytes of x and of h in, one 16-byte group per term out.
-__global__ __launch_bounds__(256) void expand_kernel(const Op *ops, const int *which, int T)
-{
-    const Op &op = ops[which[blockIdx.z]];
-    const int tok = blockIdx.y;
-    const int nblk = op.in / 16;
-    const int id = blockIdx.x * 256 + threadIdx.x;
-    if (id >= nblk * op.K) return;
-    const int p = id / nblk, j0 = (id - p * nblk) * 16;
-    const int G = groups_of(T);
-    const uint4 *xs = reinterpret_cast<const uint4 *>(reinterpret_cast<const __half *>(op.x) + (size_t)tok * op.in + j0);
-    const uint4 xq[2] = {xs[0], xs[1]};
-    const uint32_t xw[8] = {xq[0].x, xq[0].y, xq[0].z, xq[0].w, xq[1].x, xq[1].y, xq[1].z, xq[1].w};
-    uint32_t hw[8];
-    const uint16_t *hp = op.h + (size_t)p * op.in + j0;
-    if (((uintptr_t)hp & 15) == 0) {                          // the scales need only be 2-byte aligned
-        const uint4 h0 = reinterpret_cast<const uint4 *>(hp)[0], h1 = reinterpret_cast<const uint4 *>(hp)[1];
-        hw[0] = h0.x; hw[1] = h0.y; hw[2] = h0.z; hw[3] = h0.w; hw[4] = h1.x; hw[5] = h1.y; hw[6] = h1.z; hw[7] = h1.w;
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) hw[e] = (uint32_t)hp[2 * e] | ((uint32_t)hp[2 * e + 1] << 16);
-    }
-    uint32_t out[4][4] = {};                                  // [term][word of the group]
-    const float sc = op.sc[p];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const float x = __half2float(__ushort_as_half((unsigned short)(xw[e >> 1] >> (16 * (e & 1)))));
-        const float h = __half2float(__ushort_as_half((unsigned short)(hw[e >> 1] >> (16 * (e & 1)))));
-        const uint32_t terms = mx::expand4(h * x * sc);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) out[t][e >> 2] |= ((terms >> (8 * t)) & 0xffu) << (8 * (e & 3));
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-        *reinterpret_cast<uint4 *>(op.up + operand_group_offset(op.K, G, j0, p, tok >> 2, 4 * (tok & 3) + t)) =
-            make_uint4(out[t][0], out[t][1], out[t][2], out[t][3]);
-}
+// everything a launch needs, passed by value: no table in memory to fetch before the work starts
+struct Args {
+    Op op[MAX_STAGE_OPS];
+    int nops, T, out_dtype;
+};
 
 // ------------------------------------------------------------------- kernel ---
-// LDS ring of column tiles: a slot holds the tile's right operands and the sign tiles of the
-// workgroup's row tiles; as many slots as fit (at most 16)
-__host__ __device__ constexpr int slot_bytes(int K, int G, int S, int P)
+// lane N of each row of 16 lanes, in all 16
+template <int N> __device__ __forceinline__ uint32_t row_lane(uint32_t v)
 {
-    return (int)tile_operand_bytes(K, G) + block_tiles(S, P) * tile_words(K) * 4;
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + N, 0xf, 0xf, true);
 }
-__host__ __device__ constexpr int ring_depth(int K, int G, int S, int P)
+__device__ __forceinline__ uint32_t row_lane(uint32_t v, int n)      // n: constant once the loop around the call is unrolled
 {
-    return (144 * 1024) / slot_bytes(K, G, S, P) < 16 ? (144 * 1024) / slot_bytes(K, G, S, P) : 16;
-}
-
-// "at most rem * LPI vector-memory loads outstanding" for a run-time rem in 0 .. R.  (KERNEL only
-// makes the helpers of each kernel instantiation their own.)
-template <int KERNEL, int LPI, int R> struct WaitTiles {
-    static __device__ __forceinline__ void run(int rem)
-    {
-        if (rem >= R) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(R * LPI) : "memory");
-        else WaitTiles<KERNEL, LPI, R - 1>::run(rem);
+    switch (n) {
+    case 0: return row_lane<0>(v);
+    case 1: return row_lane<1>(v);
+    case 2: return row_lane<2>(v);
+    case 3: return row_lane<3>(v);
+    case 4: return row_lane<4>(v);
+    case 5: return row_lane<5>(v);
+    case 6: return row_lane<6>(v);
+    case 7: return row_lane<7>(v);
+    case 8: return row_lane<8>(v);
+    case 9: return row_lane<9>(v);
+    case 10: return row_lane<10>(v);
+    case 11: return row_lane<11>(v);
+    case 12: return row_lane<12>(v);
+    case 13: return row_lane<13>(v);
+    case 14: return row_lane<14>(v);
+    default: return row_lane<15>(v);
     }
-};
-template <int KERNEL, int LPI> struct WaitTiles<KERNEL, LPI, 0> {
-    static __device__ __forceinline__ void run(int) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-};
+}
 
-// the copies one wavefront makes per column tile: where from (advancing by `step` bytes per column
-// tile), where to inside the slot, and whether the bytes are read once (sign tiles: non-temporal)
-template <int KERNEL, int LPI> struct Copies {
-    const uint8_t *src[LPI];
-    int dst[LPI], step[LPI];
-    bool once[LPI];
-    __device__ __forceinline__ void request(uint8_t *slot, int ct) const
-    {
+// two bf16 activations as a pair of fp16 values, halved: a bf16 value up to 1.3e5 stays finite, and the
+// result is doubled again in fp32
+__device__ __forceinline__ uint32_t half_of_bf16_pair(uint32_t v)
+{
+    const _Float16 lo = (_Float16)(0.5f * __uint_as_float(v << 16)), hi = (_Float16)(0.5f * __uint_as_float(v & 0xffff0000u));
+    return (uint32_t)__builtin_bit_cast(unsigned short, lo) | ((uint32_t)__builtin_bit_cast(unsigned short, hi) << 16);
+}
+
+// the 2 K words (word c * K + k: path k, columns 128 c + 32 (lane / 16) ..) of one lane of a sign tile
+template <int K> struct Words { uint32_t w[2 * K]; };
+template <int K> __device__ __forceinline__ Words<K> load_words(const uint32_t *p)
+{
+    Words<K> r;
+    if constexpr (K == 2) {
+        const v4u v = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(p));
+        r.w[0] = v.x; r.w[1] = v.y; r.w[2] = v.z; r.w[3] = v.w;
+    } else {
 #pragma unroll
-        for (int i = 0; i < LPI; ++i) {
-            if (once[i])
-                __builtin_amdgcn_global_load_lds(src[i] + (size_t)ct * step[i], RB_LDS(slot + dst[i]), 16, 0, 2);
-            else
-                __builtin_amdgcn_global_load_lds(src[i] + (size_t)ct * step[i], RB_LDS(slot + dst[i]), 16, 0, 0);
+        for (int i = 0; i < K; ++i) {
+            const v2u v = __builtin_nontemporal_load(reinterpret_cast<const v2u *>(p) + i);
+            r.w[2 * i] = v.x; r.w[2 * i + 1] = v.y;
         }
     }
-};
+    return r;
+}
 
-template <int K, int G, int S, int P>
-__global__ __launch_bounds__(THREADS, 1) void batch_kernel(const Op *__restrict__ ops, int op0, int nops, int T)
+// K paths, G groups of 16 tokens, P row tiles per workgroup, BF16: the activations are bfloat16
+template <int K, int G, int P, bool BF16>
+__global__ __launch_bounds__(max_waves(G) * 64, 1) void batch_kernel(const Args args)
 {
-    constexpr int R = block_tiles(S, P), NP = 2 * K / S;     // NP: pieces per wavefront and tile
-    static_assert(2 * K % S == 0 && WAVES % S == 0, "pieces and wavefronts go round");
-    constexpr int OPB = (int)tile_operand_bytes(K, G);
-    constexpr int TB = tile_words(K) * 4;                    // bytes of a sign tile
-    constexpr int SLOT = slot_bytes(K, G, S, P);              // [operands OPB][sign tiles R x TB]
-    constexpr int COPIES = SLOT / 1024;                      // 1 KB per wavefront instruction
-    constexpr int LPI = (COPIES + WAVES - 1) / WAVES;        // copies per wavefront and tile
-    constexpr int D = ring_depth(K, G, S, P);                 // slots in LDS; D - 1 tiles are requested ahead
-    constexpr int PART = G * 4 * TILE_ROWS;                  // floats of one wavefront's partial outputs: [token][row]
-    static_assert(SLOT % 1024 == 0 && D >= 2 && (D - 1) * LPI < 64, "the in-order wait counts on this");
-    static_assert(WAVES * P * PART * 4 <= D * SLOT, "the partial outputs reuse the ring");
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];   // D slots
-
-    const int tid = threadIdx.x, lane = tid & 63;
+    constexpr bool AHEAD = P * K <= (G == 1 ? 6 : 4) && G <= 2;       // registers for the sign words of the next column tile
+    constexpr int XC = G == 1 && P * K <= 9 ? 2 : 1;                 // column halves whose activations are held at once
+    extern __shared__ __attribute__((aligned(16))) float part[];     // [wavefront][row tile][token][row]
+    const int tid = threadIdx.x, lane = tid & 63, nw = (int)blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r = wave / S, sp = wave % S;
-    // which op of the launch, which block of R row tiles
-    int o = op0, wg = (int)blockIdx.x;
-    while (o + 1 < op0 + nops && wg >= ops[o + 1].wg0) ++o;
-    const Op &op = ops[o];
-    wg -= op.wg0;
-    const int CT = op.CT, RT = op.RT, out = op.out;
-    const int rt = wg * R + r * P;                           // this wavefront's first row tile (of P)
-    const bool live = rt < RT;
-    const int col = lane & 15, qd = lane >> 4;
-    const int scale_b = mx::term_scale(col);
-    uint32_t c22;
-    asm volatile("v_mov_b32 %0, 0x22222222" : "=v"(c22));
+    const int r = lane & 15, q = lane >> 4;
+    int o = 0;
+    while (o + 1 < args.nops && (int)blockIdx.x >= args.op[o + 1].wg0) ++o;
+    const Op &op = args.op[o];
+    const int out = op.out, in = op.in, T = args.T;
+    const int RT = row_tiles(out), CT = col_tiles(in);
+    const int rt0 = ((int)blockIdx.x - op.wg0) * P;
 
-    // ---- one column tile's copies of this wavefront, always LPI of them (the waits count them):
-    // the slot's bytes, 1 KB per instruction, are dealt round-robin; where the pieces do not go
-    // round, a wavefront repeats a copy another one makes.  The right operands of a column tile
-    // are OPB consecutive bytes; the sign tiles of the R row tiles (every one read once: non-
-    // temporal) follow in the slot as they are in memory, so that lane l finds its 2 K words
-    // (word c * K + k = path k, columns 128 c + 32 (l / 16) ..) at 8 K l.  A row tile past the
-    // end of the matrix copies the last one (nobody reads it).
-    Copies<64 * K + 8 * G + S + 128 * P, LPI> copies;
+    // the row tiles of this workgroup; one past the end of the matrix reads the last one (not stored)
+    const uint32_t *bits[P];
 #pragma unroll
-    for (int i = 0; i < LPI; ++i) {
-        const int piece = (wave + WAVES * i) % COPIES;
-        copies.dst[i] = piece * 1024;
-        copies.once[i] = piece * 1024 >= OPB;
-        if (!copies.once[i]) {
-            copies.src[i] = op.up + (size_t)piece * 1024 + lane * 16;
-            copies.step[i] = OPB;
-        } else {
-            const int b = piece * 1024 - OPB + lane * 16;
-            const int rr = min(wg * R + b / TB, RT - 1);
-            copies.src[i] = reinterpret_cast<const uint8_t *>(op.bits) + (size_t)rr * CT * TB + b % TB;
-            copies.step[i] = TB;
-        }
-    }
+    for (int p = 0; p < P; ++p) bits[p] = op.bits + (size_t)min(rt0 + p, RT - 1) * CT * tile_words(K) + lane * 2 * K;
 
-    v4f acc[P][NP][G];
+    Words<K> w[P];
+    if (wave < CT)
+#pragma unroll
+        for (int p = 0; p < P; ++p) w[p] = load_words<K>(bits[p] + (size_t)wave * tile_words(K));
+    v4f acc[P][K][G];
 #pragma unroll
     for (int p = 0; p < P; ++p)
 #pragma unroll
-        for (int j = 0; j < NP; ++j)
+        for (int k = 0; k < K; ++k)
 #pragma unroll
-            for (int g = 0; g < G; ++g) acc[p][j][g] = (v4f){0.f, 0.f, 0.f, 0.f};
+            for (int g = 0; g < G; ++g) acc[p][k][g] = (v4f){0.f, 0.f, 0.f, 0.f};
 
+    // columns of this lane: 32 consecutive ones per half of a column tile, all of them inside the
+    // matrix or none (in % 32 == 0); lane r of a row of 16 feeds token r
+    const uint16_t *xrow[G];
 #pragma unroll
-    for (int d = 0; d < D - 1; ++d)
-        if (d < CT) copies.request(lds + d * SLOT, d);
-    const uint32_t lds_base = (uint32_t)(size_t)RB_LDS(lds);
-    const uint32_t lds_lane = lds_base + (uint32_t)lane * 16u;
-    const uint32_t lds_sign = lds_base + (uint32_t)(OPB + r * P * TB + lane * 8 * K + 4 * sp);
-    int slot = 0;
-    for (int ct = 0; ct < CT; ++ct) {
-        // Copies complete in order and every tile costs this wavefront LPI of them: when at most
-        // LPI times the number of younger tiles already requested are outstanding, tile ct is
-        // here.  After the barrier it is here for every wavefront, and every wavefront is
-        // through with the slot of tile ct - 1, which the next request overwrites.
-        WaitTiles<64 * K + 8 * G + S + 128 * P, LPI, D - 2>::run(min(CT - 1 - ct, D - 2));
-        asm volatile("s_barrier" ::: "memory");               // the barrier alone: a fence would wait for every copy in flight
-        if (ct + D - 1 < CT) copies.request(lds + (slot == 0 ? D - 1 : slot - 1) * SLOT, ct + D - 1);
-        if (live) {
+    for (int g = 0; g < G; ++g)
+        xrow[g] = static_cast<const uint16_t *>(op.x) + (size_t)min(16 * g + r, T - 1) * in + 32 * q;
+
+    for (int ct = wave; ct < CT; ct += nw) {
+        const int j0 = ct * TILE_COLS;
+        // scales: lane r of a row of 16 holds the pair of columns 2 r, 2 r + 1 of the row's 32
+        uint32_t hw[2][K];
 #pragma unroll
-            for (int j = 0; j < NP; ++j) {
-                // Reads of the ring are written as instructions: a read the compiler can see would
-                // wait for every copy still in flight.
-                v8i a[P];
+        for (int c = 0; c < 2; ++c) {
+            const bool real = j0 + 128 * c + 32 * q < in;
 #pragma unroll
-                for (int p = 0; p < P; ++p) {
-                    uint32_t sw;
-                    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)"
-                                 : "=v"(sw) : "v"(lds_sign + (uint32_t)(slot * SLOT + p * TB + 4 * j * S)) : "memory");
-                    a[p][0] = (int)(((sw << 3) & 0x88888888u) | c22);
-                    a[p][1] = (int)(((sw << 2) & 0x88888888u) | c22);
-                    a[p][2] = (int)(((sw << 1) & 0x88888888u) | c22);
-                    a[p][3] = (int)((sw & 0x88888888u) | c22);
-                    a[p][4] = 0; a[p][5] = 0; a[p][6] = 0; a[p][7] = 0;
-                }
+            for (int k = 0; k < K; ++k) {
+                const uint16_t *hp = op.h + (size_t)k * in + (real ? j0 + 128 * c + 32 * q + 2 * r : 0);
+                uint32_t v;
+                if (op.h_even) v = *reinterpret_cast<const uint32_t *>(hp);
+                else v = (uint32_t)hp[0] | ((uint32_t)hp[1] << 16);      // the scales need only be 2-byte aligned
+                hw[c][k] = real ? v : 0u;
+            }
+        }
+        uint4 x[XC][4][G];
+        auto load_x = [&](int c) {
+            const bool real = j0 + 128 * c + 32 * q < in;
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
 #pragma unroll
                 for (int g = 0; g < G; ++g) {
-                    // the operand of piece c * K + k, token group g: read once for the P row tiles
-                    const uint32_t addr = lds_lane + (uint32_t)(slot * SLOT + ((sp + j * S) * G + g) * 2048);
-                    v4i lo, hi;
-                    asm volatile("ds_read_b128 %0, %2\n\t"
-                                 "ds_read_b128 %1, %2 offset:1024\n\t"
-                                 "s_waitcnt lgkmcnt(0)"
-                                 : "=&v"(lo), "=&v"(hi)
-                                 : "v"(addr)
-                                 : "memory");
-                    v8i b;
-                    b[0] = lo[0]; b[1] = lo[1]; b[2] = lo[2]; b[3] = lo[3];
-                    b[4] = hi[0]; b[5] = hi[1]; b[6] = hi[2]; b[7] = hi[3];
-                    // A: fp4 (cbsz = 4), B: bf8 (blgp = 1); scale bytes are E8M0 exponents
+                    x[c % XC][s][g] = make_uint4(0u, 0u, 0u, 0u);
+                    if (real) x[c % XC][s][g] = *reinterpret_cast<const uint4 *>(xrow[g] + j0 + 128 * c + 8 * s);
+                }
+        };
+        load_x(0);
+        if constexpr (XC == 2) load_x(1);
+        Words<K> next[P];
+        if (AHEAD && ct + nw < CT)
 #pragma unroll
-                    for (int p = 0; p < P; ++p)
-                        acc[p][j][g] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a[p], b, acc[p][j][g], 4, 1, 0, 0x7f7f7f7f, 0, scale_b);
+            for (int p = 0; p < P; ++p) next[p] = load_words<K>(bits[p] + (size_t)(ct + nw) * tile_words(K));
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            if (XC == 1 && c == 1) load_x(1);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                v8h b[G];
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    uint4 v = x[c % XC][s][g];
+                    if constexpr (BF16) v = make_uint4(half_of_bf16_pair(v.x), half_of_bf16_pair(v.y), half_of_bf16_pair(v.z), half_of_bf16_pair(v.w));
+                    b[g] = __builtin_bit_cast(v8h, v);
+                }
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    uint32_t hp[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) hp[j] = row_lane(hw[c][k], 4 * s + j);
+#pragma unroll
+                    for (int p = 0; p < P; ++p) {
+                        // element e of the lane's eight is column 8 s + e: native bit 4 e + s.  Shifted by
+                        // 7 - s (3 - s) bit 8 j + s (8 j + 4 + s), of element 2 j (2 j + 1), is the
+                        // top of byte j; a permute brings the two bytes to the tops of the halves
+                        const uint32_t even = w[p].w[c * K + k] << (7 - s), odd = w[p].w[c * K + k] << (3 - s);
+                        uint4 a;
+                        uint32_t *const av = reinterpret_cast<uint32_t *>(&a);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            av[j] = hp[j] ^ (__builtin_amdgcn_perm(odd, even, (uint32_t)((4 + j) << 24 | j << 8)) & 0x80008000u);
+                        const v8h av8 = __builtin_bit_cast(v8h, a);
+#pragma unroll
+                        for (int g = 0; g < G; ++g) acc[p][k][g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av8, b[g], acc[p][k][g], 0, 0, 0);
+                    }
                 }
             }
         }
-        slot = slot + 1 == D ? 0 : slot + 1;
+        if (AHEAD) {
+#pragma unroll
+            for (int p = 0; p < P; ++p) w[p] = next[p];
+        } else if (ct + nw < CT) {
+#pragma unroll
+            for (int p = 0; p < P; ++p) w[p] = load_words<K>(bits[p] + (size_t)(ct + nw) * tile_words(K));
+        }
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();                                          // every wavefront is through with the operand ring
 
-    // ---- partial outputs of this wavefront's pieces, scaled by the output scales of their paths
-    // (Section 4.1: y = sum_k g_k (.) (B_k u_k)).  Lane (col, q) holds rows 4q .. 4q+3 of operand
-    // column col = 4 * (token % 4) + term; the four lanes of a quad hold the four terms.
-    float *const part = reinterpret_cast<float *>(lds);       // [wavefront][row tile of the wavefront][token][row]
-    if (live) {
+    // ---- partial outputs of this wavefront: path sum with the output scales (Section 4.1).  Lane
+    // (r, q) holds token r, rows 4 q .. 4 q + 3 of the row tile.
 #pragma unroll
-        for (int p = 0; p < P; ++p) {
-            float gq[NP][4];
+    for (int p = 0; p < P; ++p) {
+        float gq[K][4];
 #pragma unroll
-            for (int j = 0; j < NP; ++j) {
-                const int k = (sp + j * S) % K;
+        for (int k = 0; k < K; ++k)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int row = (rt + p) * TILE_ROWS + 4 * qd + i;
-                    gq[j][i] = row < out ? (float)RB_GLOBAL(const _Float16, op.g)[(size_t)k * out + row] * op.inv_sc[k] : 0.f;
-                }
+            for (int i = 0; i < 4; ++i) {
+                const int row = min((rt0 + p) * TILE_ROWS + 4 * q + i, out - 1);
+                gq[k][i] = __half2float(__ushort_as_half(op.g[(size_t)k * out + row])) * (BF16 ? 2.f : 1.f);
             }
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                v4f v = {0.f, 0.f, 0.f, 0.f};
+        for (int g = 0; g < G; ++g) {
+            v4f v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int j = 0; j < NP; ++j)
+            for (int k = 0; k < K; ++k)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) v[i] = __builtin_fmaf(gq[j][i], mx::quad_sum(acc[p][j][g][i]), v[i]);
-                if ((col & 3) == 0)
-                    *reinterpret_cast<v4f *>(part + (wave * P + p) * PART + (4 * g + (col >> 2)) * TILE_ROWS + 4 * qd) = v;
-            }
+                for (int i = 0; i < 4; ++i) v[i] = __builtin_fmaf(gq[k][i], acc[p][k][g][i], v[i]);
+            *reinterpret_cast<v4f *>(part + ((wave * P + p) * G + g) * 256 + r * 16 + 4 * q) = v;
         }
     }
     __syncthreads();
-
-    // ---- finish the R row tiles: add the S partial outputs of a row in wavefront order, round,
-    // store, and write the input scaling of the ops that read y
-    const int n_cons = op.n_cons;
-    for (int idx = tid; idx < R * T * TILE_ROWS; idx += THREADS) {
-        const int rr = idx / (T * TILE_ROWS), tok = (idx / TILE_ROWS) % T, i = idx % TILE_ROWS;
-        const int row = (wg * R + rr) * TILE_ROWS + i;
-        if (row >= out) continue;
-        float sum = 0.f;
-#pragma unroll
-        for (int q = 0; q < S; ++q) sum += part[(((rr / P) * S + q) * P + rr % P) * PART + tok * TILE_ROWS + i];
-        const _Float16 y16 = (_Float16)sum;                   // round to nearest even
-        RB_GLOBAL(_Float16, op.y)[(size_t)tok * out + row] = y16;
-        const float yf = (float)y16;
-        // input scaling of the ops that read y (Section 4.1), as four bf8 terms in operand order
-        for (int c = 0; c < n_cons; ++c) {
-            const Reader &rd = op.cons[c];
-            for (int p = 0; p < rd.K; ++p) {
-                const float h = (float)RB_GLOBAL(const _Float16, rd.h)[(size_t)p * rd.in + row];
-                const uint32_t terms = mx::expand4(h * yf * rd.sc[p]);
-                auto *dst = RB_GLOBAL(uint8_t, rd.up) + operand_group_offset(rd.K, G, row & ~15, p, tok >> 2, 4 * (tok & 3)) + (row & 15);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) dst[t * 16] = (uint8_t)(terms >> (8 * t));
-            }
-        }
+    // ---- add the wavefronts in order, round, store
+    for (int idx = tid; idx < P * G * 256; idx += (int)blockDim.x) {
+        const int p = idx / (G * 256), t = idx / 16 % (G * 16), row = (rt0 + p) * TILE_ROWS + idx % 16;
+        float s = 0.f;
+        for (int v = 0; v < nw; ++v) s += part[v * (P * G * 256) + idx];
+        if (t < T && row < out) store_out(op.y, args.out_dtype, (size_t)t * out + row, s);
     }
 }
 
 // ------------------------------------------------------------------ host ---
-struct Launch { int op0, nops, groups, K, S, P; };
-struct Layout { size_t ops, cons, which, up, total; };
+constexpr int ROW_TILES_PER_WG[] = {1, 2, 3, 4, 6};
 
-static Layout make_layout(int n_ops, size_t up_total)
+// Row tiles per workgroup: the device runs the workgroups in rounds of one per compute unit; a
+// round takes as long as its row tiles plus what every workgroup pays once (reading the
+// activations, the latencies, the sum), about one and a half row tiles' worth
+static int row_tiles_per_wg(const int *RT, int nops, int K, int G)
 {
-    Layout L;
-    size_t o = 0;
-    L.ops = o; o += mx::align_up(sizeof(Op) * (size_t)n_ops, 256);
-    L.cons = o; o += mx::align_up(sizeof(int) * MAX_CONS * (size_t)n_ops, 256);
-    L.which = o; o += mx::align_up(sizeof(int) * MAX_EXPAND, 256);
-    L.up = o; o += up_total;
-    L.total = mx::align_up(o, 256);
-    return L;
+    const int cus = std::max(1, mx::device_groups());
+    int best = 1;
+    double best_cost = 0.0;
+    for (int P : ROW_TILES_PER_WG) {
+        if (!p_available(K, G, P)) continue;
+        int groups = 0;
+        for (int i = 0; i < nops; ++i) groups += (RT[i] + P - 1) / P;
+        const double cost = (double)((groups + cus - 1) / cus) * (P + 1.5);
+        if (P == 1 || cost < best_cost) { best = P; best_cost = cost; }
+    }
+    return best;
+}
+
+template <int K, int G, int P, bool BF16>
+static int launch_form(const Args &args, int groups, int nw, hipStream_t stream)
+{
+    constexpr int lds_max = max_waves(G) * P * G * 1024;
+    if (lds_max > 64 * 1024) {
+        static std::atomic<bool> allowed[64];
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return RB_ERR_HIP;
+        if (!allowed[dev].load()) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(batch_kernel<K, G, P, BF16>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    lds_max) != hipSuccess)
+                return RB_ERR_HIP;
+            allowed[dev].store(true);
+        }
+    }
+    hipLaunchKernelGGL((batch_kernel<K, G, P, BF16>), dim3((unsigned)groups), dim3((unsigned)(nw * 64)), nw * P * G * 1024, stream, args);
+    return RB_OK;
+}
+
+template <int K, int G, bool BF16>
+static int launch_p(const Args &args, int P, int groups, int nw, hipStream_t stream)
+{
+    switch (P) {
+    case 1: return launch_form<K, G, 1, BF16>(args, groups, nw, stream);
+    case 2: if constexpr (p_available(K, G, 2)) return launch_form<K, G, 2, BF16>(args, groups, nw, stream); break;
+    case 3: if constexpr (p_available(K, G, 3)) return launch_form<K, G, 3, BF16>(args, groups, nw, stream); break;
+    case 4: if constexpr (p_available(K, G, 4)) return launch_form<K, G, 4, BF16>(args, groups, nw, stream); break;
+    default: if constexpr (p_available(K, G, 6)) return launch_form<K, G, 6, BF16>(args, groups, nw, stream); break;
+    }
+    return RB_ERR_UNSUPPORTED;
+}
+
+static int token_groups(int T) { return T <= 16 ? 1 : T <= 32 ? 2 : 4; }
+
+// one launch: the ops of `args` (wg0 is filled in here), all of K paths
+struct Shape { int K, P, groups, nw; };
+static Shape shape_of(Args &args, int K)
+{
+    int RT[MAX_STAGE_OPS], CT = 1;
+    for (int i = 0; i < args.nops; ++i) {
+        RT[i] = row_tiles(args.op[i].out);
+        CT = std::max(CT, col_tiles(args.op[i].in));
+        args.op[i].h_even = ((uintptr_t)args.op[i].h & 3) == 0;
+    }
+    Shape s;
+    s.K = K;
+    const int G = token_groups(args.T);
+    s.P = row_tiles_per_wg(RT, args.nops, K, G);
+    s.groups = 0;
+    for (int i = 0; i < args.nops; ++i) {
+        args.op[i].wg0 = s.groups;
+        s.groups += (RT[i] + s.P - 1) / s.P;
+    }
+    s.nw = std::min(CT, max_waves(G));      // a wavefront takes whole column tiles
+    return s;
+}
+
+template <bool BF16> static int launch_shape(const Args &args, const Shape &s, hipStream_t stream)
+{
+    const int G = token_groups(args.T);
+    if (s.K == 2)
+        return G == 1 ? launch_p<2, 1, BF16>(args, s.P, s.groups, s.nw, stream)
+             : G == 2 ? launch_p<2, 2, BF16>(args, s.P, s.groups, s.nw, stream)
+                      : launch_p<2, 4, BF16>(args, s.P, s.groups, s.nw, stream);
+    return G == 1 ? launch_p<3, 1, BF16>(args, s.P, s.groups, s.nw, stream)
+         : G == 2 ? launch_p<3, 2, BF16>(args, s.P, s.groups, s.nw, stream)
+                  : launch_p<3, 4, BF16>(args, s.P, s.groups, s.nw, stream);
+}
+
+static Op make_op(const rb_layer &L, const void *x, void *y)
+{
+    Op o;
+    o.bits = static_cast<const uint32_t *>(L.bits);
+    o.g = L.g; o.h = L.h;
+    o.x = x; o.y = y;
+    o.out = L.out; o.in = L.in;
+    o.wg0 = 0; o.h_even = 0;
+    return o;
+}
+
+bool call_supported(const rb_layer *L, int T) { return (L->K == 2 || L->K == 3) && T >= 1 && T <= CALL_MAX_T && L->in % 32 == 0; }
+
+int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, hipStream_t stream)
+{
+    Args args;
+    args.nops = 1; args.T = T; args.out_dtype = out_dtype;
+    args.op[0] = make_op(*L, X, Y);
+    const Shape s = shape_of(args, L->K);
+    const int rc = act_dtype == RB_BF16 ? launch_shape<true>(args, s, stream) : launch_shape<false>(args, s, stream);
+    if (rc != RB_OK) return rc;
+    return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;
 }
 
 bool layer_supported(const rb_layer *L, int T)
 {
-    return (L->K == 2 || L->K == 3) && T >= 1 && T <= MAX_T && L->in % 32 == 0;
+    return (L->K == 2 || L->K == 3) && T >= 1 && T <= STACK_MAX_T && L->in % 32 == 0;
 }
 
-size_t plan_workspace_bytes(const rb_layer *layers, int n_layers, int n_ops, int T)
-{
-    const int G = groups_of(T);
-    size_t up_max = 0;
-    for (int l = 0; l < n_layers; ++l)
-        up_max = std::max(up_max, mx::align_up(operand_bytes(layers[l].in, layers[l].K, G), 256));
-    return make_layout(n_ops, up_max * (size_t)n_ops).total;
-}
+// A plan lives on the host: the kernel needs nothing in device memory besides the buffers.  The
+// workspace is the name it is run by.
+size_t plan_workspace_bytes() { return 256; }
 
-struct Prepared {
-    Layout lay;
-    int n_ops = 0, T = 0, n_expand = 0, max_expand_in = 0;
-    std::vector<Launch> launches;
-    std::shared_ptr<std::vector<uint8_t>> blob;      // host copies of the tables: pageable, must outlive the queued copies
-};
+struct Prepared { std::vector<std::pair<Args, Shape>> launches; };
 static std::mutex g_mutex;
-static std::map<const void *, Prepared> g_prepared;
+static std::map<const void *, std::shared_ptr<const Prepared>> g_prepared;
 
 int prepare_plan(const rb_layer *layers, const rb_stack_op *sops, int n_ops, uint16_t *const *bufs, int T,
-                 void *workspace, size_t workspace_bytes_, hipStream_t stream)
+                 void *workspace, size_t workspace_bytes_)
 {
-    if (T < 1 || T > MAX_T) return RB_ERR_UNSUPPORTED;
-    const int G = groups_of(T);
-    std::vector<Op> ops((size_t)n_ops);
-    std::vector<int> cons((size_t)n_ops * MAX_CONS, 0), expand_list;
-    std::vector<size_t> up_off((size_t)n_ops);
-    size_t up_total = 0;
+    if (T < 1 || T > STACK_MAX_T) return RB_ERR_UNSUPPORTED;
+    if (!workspace || workspace_bytes_ < plan_workspace_bytes()) return RB_ERR_WORKSPACE;
+    // an op that reads another one's output reads all of it
+    std::map<int, int> width;
     for (int n = 0; n < n_ops; ++n) {
         const rb_layer &L = layers[sops[n].layer];
         if (!layer_supported(&L, T)) return RB_ERR_UNSUPPORTED;
-        Op &o = ops[(size_t)n];
-        std::memset(&o, 0, sizeof(Op));
-        o.bits = static_cast<const uint32_t *>(L.bits);
-        o.g = L.g; o.h = L.h;
-        o.x = bufs[sops[n].src];
-        o.y = bufs[sops[n].dst];
-        o.out = L.out; o.in = L.in; o.K = L.K;
-        o.RT = row_tiles(L.out); o.CT = col_tiles(L.in);
-        up_off[(size_t)n] = up_total;
-        up_total += mx::align_up(operand_bytes(L.in, L.K, G), 256);
-        int producer = -1;
-        for (int m = n - 1; m >= 0; --m)
-            if (sops[m].dst == sops[n].src) { producer = m; break; }
-        if (producer < 0) {
-            expand_list.push_back(n);
-        } else {
-            Op &pr = ops[(size_t)producer];
-            if (pr.n_cons >= MAX_CONS) return RB_ERR_UNSUPPORTED;
-            if (pr.out != o.in) return RB_ERR_SHAPE;
-            cons[(size_t)producer * MAX_CONS + pr.n_cons++] = n;
-        }
+        const auto it = width.find(sops[n].src);
+        if (it != width.end() && it->second != L.in) return RB_ERR_SHAPE;
+        width[sops[n].dst] = L.out;
     }
-    if (expand_list.size() > MAX_EXPAND) return RB_ERR_UNSUPPORTED;
-
-    // ---- launches: runs of consecutive ops of one K that neither read nor overwrite each other
-    Prepared pr;
-    pr.n_ops = n_ops; pr.T = T;
+    // launches: runs of consecutive ops of one K that neither read nor overwrite each other
+    auto pr = std::make_shared<Prepared>();
     for (int op0 = 0; op0 < n_ops;) {
-        int nops = 0;
-        const int K = ops[(size_t)op0].K;
-        for (int n = op0; n < n_ops && nops < MAX_STAGE_OPS; ++n) {
-            bool conflict = ops[(size_t)n].K != K;
+        Args args;
+        args.nops = 0; args.T = T; args.out_dtype = RB_F16;
+        const int K = layers[sops[op0].layer].K;
+        for (int n = op0; n < n_ops && args.nops < MAX_STAGE_OPS; ++n) {
+            const rb_layer &L = layers[sops[n].layer];
+            bool conflict = L.K != K;
             for (int m = op0; m < n; ++m)
                 if (sops[m].dst == sops[n].src || sops[m].dst == sops[n].dst || sops[m].src == sops[n].dst) conflict = true;
             if (conflict) break;
-            ++nops;
+            args.op[args.nops++] = make_op(L, bufs[sops[n].src], bufs[sops[n].dst]);
         }
-        // the largest row blocks that still give the launch WANT_GROUPS workgroups, else the smallest
-        Form f = form_of(K, n_forms(K) - 1);
-        int groups = 0;
-        for (int i = 0; i < n_forms(K); ++i) {
-            f = form_of(K, i);
-            groups = 0;
-            for (int n = op0; n < op0 + nops; ++n) groups += (ops[(size_t)n].RT + block_tiles(f.S, f.P) - 1) / block_tiles(f.S, f.P);
-            if (groups >= WANT_GROUPS) break;
-        }
-        groups = 0;
-        for (int n = op0; n < op0 + nops; ++n) {
-            ops[(size_t)n].wg0 = groups;
-            groups += (ops[(size_t)n].RT + block_tiles(f.S, f.P) - 1) / block_tiles(f.S, f.P);
-        }
-        pr.launches.push_back(Launch{op0, nops, groups, K, f.S, f.P});
-        op0 += nops;
+        const Shape s = shape_of(args, K);
+        pr->launches.emplace_back(args, s);
+        op0 += args.nops;
     }
-    pr.n_expand = (int)expand_list.size();
-    for (int n : expand_list) pr.max_expand_in = std::max(pr.max_expand_in, ops[(size_t)n].in);
-    pr.lay = make_layout(n_ops, up_total);
-    const Layout &lay = pr.lay;
-    if (!workspace || workspace_bytes_ < lay.total) return RB_ERR_WORKSPACE;
-    uint8_t *ws = static_cast<uint8_t *>(workspace);
-    for (int n = 0; n < n_ops; ++n) ops[(size_t)n].up = ws + lay.up + up_off[(size_t)n];
-
-    pr.blob = std::make_shared<std::vector<uint8_t>>(lay.up, (uint8_t)0);
-    std::vector<uint8_t> &blob = *pr.blob;
-    std::memcpy(blob.data() + lay.ops, ops.data(), sizeof(Op) * (size_t)n_ops);
-    std::memcpy(blob.data() + lay.cons, cons.data(), sizeof(int) * cons.size());
-    if (!expand_list.empty()) std::memcpy(blob.data() + lay.which, expand_list.data(), sizeof(int) * expand_list.size());
-    if (hipMemcpyAsync(ws, blob.data(), lay.up, hipMemcpyHostToDevice, stream) != hipSuccess) return RB_ERR_HIP;
-    hipLaunchKernelGGL(prep_kernel, dim3(n_ops, PREP_SPLIT), dim3(256), 0, stream, reinterpret_cast<Op *>(ws + lay.ops), T);
-    hipLaunchKernelGGL(link_kernel, dim3((n_ops + 63) / 64), dim3(64), 0, stream, reinterpret_cast<Op *>(ws + lay.ops),
-                       reinterpret_cast<const int *>(ws + lay.cons), n_ops);
-    if (hipGetLastError() != hipSuccess) return RB_ERR_HIP;
     std::lock_guard<std::mutex> lock(g_mutex);
     g_prepared[workspace] = std::move(pr);
     return RB_OK;
 }
 
-template <int K, int G, int S, int P>
-static int launch_one(const Op *d_ops, const Launch &l, int T, hipStream_t stream)
-{
-    const int lds_bytes = ring_depth(K, G, S, P) * slot_bytes(K, G, S, P);
-    static std::atomic<bool> configured{false};
-    if (!configured.load()) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(batch_kernel<K, G, S, P>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                lds_bytes) != hipSuccess)
-            return RB_ERR_HIP;
-        configured.store(true);
-    }
-    hipLaunchKernelGGL((batch_kernel<K, G, S, P>), dim3((unsigned)l.groups), dim3(THREADS), lds_bytes, stream, d_ops, l.op0, l.nops, T);
-    return RB_OK;
-}
-
-template <int K, int S, int P>
-static int launch_groups(const Op *d_ops, const Launch &l, int T, hipStream_t stream)
-{
-    switch (groups_of(T)) {
-    case 1: return launch_one<K, 1, S, P>(d_ops, l, T, stream);
-    case 2: return launch_one<K, 2, S, P>(d_ops, l, T, stream);
-    case 3: return launch_one<K, 3, S, P>(d_ops, l, T, stream);
-    default: return launch_one<K, 4, S, P>(d_ops, l, T, stream);
-    }
-}
-
 // RB_ERR_UNSUPPORTED: the workspace holds no plan of this kind
 int launch_plan(void *workspace, size_t workspace_bytes_, hipStream_t stream)
 {
-    std::unique_lock<std::mutex> lock(g_mutex);
-    const auto it = g_prepared.find(workspace);
-    if (it == g_prepared.end()) return RB_ERR_UNSUPPORTED;
-    const Prepared &pr = it->second;
-    if (workspace_bytes_ < pr.lay.total) return RB_ERR_WORKSPACE;
-    uint8_t *ws = static_cast<uint8_t *>(workspace);
-    const Op *d_ops = reinterpret_cast<const Op *>(ws + pr.lay.ops);
-    const int T = pr.T;
-    if (pr.n_expand > 0)
-        hipLaunchKernelGGL(expand_kernel, dim3((pr.max_expand_in / 16 * RB_MAX_K + 255) / 256, T, (unsigned)pr.n_expand), dim3(256), 0,
-                           stream, d_ops, reinterpret_cast<const int *>(ws + pr.lay.which), T);
-    for (const Launch &l : pr.launches) {
-        int rc = RB_ERR_UNSUPPORTED;
-        if (l.K == 2) rc = l.S == 2 ? launch_groups<2, 2, 2>(d_ops, l, T, stream) : l.P == 2 ? launch_groups<2, 4, 2>(d_ops, l, T, stream)
-                                    : launch_groups<2, 4, 1>(d_ops, l, T, stream);
-        else if (l.K == 3) rc = launch_groups<3, 2, 1>(d_ops, l, T, stream);
+    std::shared_ptr<const Prepared> pr;
+    {
+        std::lock_guard<std::mutex> lock(g_mutex);
+        const auto it = g_prepared.find(workspace);
+        if (it == g_prepared.end()) return RB_ERR_UNSUPPORTED;
+        pr = it->second;
+    }
+    if (workspace_bytes_ < plan_workspace_bytes()) return RB_ERR_WORKSPACE;
+    for (const auto &l : pr->launches) {
+        const int rc = launch_shape<false>(l.first, l.second, stream);
         if (rc != RB_OK) return rc;
     }
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;

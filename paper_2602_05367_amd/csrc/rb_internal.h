@@ -17,7 +17,9 @@ int launch_signadd(const rb_layer *L, const void *X, void *Y, int T, int act_dty
 size_t workspace_bytes(const rb_layer *layers, int n_layers, int n_ops, int T);
 // stacks that run on the small-batch kernel (see rb_dispatch.hip)
 bool batch_applies(const rb_layer *layers, int n_layers, int T);
-// a single call of T tokens on this layer takes the many-token kernel (given the scratch memory it needs)
+// a single call takes the few-token kernel; of T tokens on this layer, the many-token kernel (given
+// the scratch memory it needs)
+bool single_few_applies(const rb_layer *L, int T, int act_dtype, int out_dtype);
 bool single_gemm_applies(const rb_layer *L, int T);
 
 int dispatch_linear(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype,
@@ -27,16 +29,8 @@ int dispatch_stack(const rb_layer *layers, int n_layers, const rb_stack_op *ops,
                    uint16_t *const *bufs, int n_bufs, int T, void *workspace, size_t workspace_bytes,
                    hipStream_t stream);
 
-// stacks of 5..7 tokens as passes of the fused kernel over groups of four tokens: one plan per pass
-// in consecutive parts of the workspace (RB_ERR_UNSUPPORTED where that does not apply)
-int prepare_pairs(const rb_layer *layers, int n_layers, const rb_stack_op *ops, int n_ops, uint16_t *const *bufs,
-                  int n_bufs, int T, void *workspace, size_t workspace_bytes, hipStream_t stream);
-int run_pairs(void *workspace, size_t workspace_bytes, hipStream_t stream);
-void forget_pairs(const void *workspace);
-int pairs_status(const void *workspace, hipStream_t stream, unsigned long long *waited = nullptr, int *reason = nullptr);     // RB_ERR_UNSUPPORTED: no plans of this kind
-
 namespace gemm {
-// many-token matrix-core GEMM (K = 2): workspace holds the scaled input of both paths
+// many-token matrix-core GEMM (K = 2 or 3): workspace holds the input in contraction order
 bool supported(const rb_layer *L, int T);
 size_t workspace_bytes(const rb_layer *L, int T);
 int launch(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
@@ -51,12 +45,16 @@ int launch(const rb_layer *L, const void *x, void *y, hipStream_t stream);
 }  // namespace gemv1
 
 namespace batch {
-// small-batch path (K = 2 or 3, up to 16 tokens): every op streams its weights once for all
-// tokens; independent ops share a launch, dependent ones are ordered by the stream
+// few-token path (K = 2 or 3): the weights are read once for all tokens; independent ops of a
+// stack share a launch, dependent ones are ordered by the stream.  Single calls of any element type
+// take up to CALL_MAX_T tokens, stacks up to 16.
+constexpr int CALL_MAX_T = 64;
+bool call_supported(const rb_layer *L, int T);
+int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, hipStream_t stream);
 bool layer_supported(const rb_layer *L, int T);
-size_t plan_workspace_bytes(const rb_layer *layers, int n_layers, int n_ops, int T);
+size_t plan_workspace_bytes();
 int prepare_plan(const rb_layer *layers, const rb_stack_op *ops, int n_ops, uint16_t *const *bufs, int T,
-                 void *workspace, size_t workspace_bytes, hipStream_t stream);
+                 void *workspace, size_t workspace_bytes);
 int launch_plan(void *workspace, size_t workspace_bytes, hipStream_t stream);      // RB_ERR_UNSUPPORTED: no plan of this kind
 bool has_plan(const void *workspace);
 void forget_plan(const void *workspace);

@@ -1,5 +1,5 @@
 // rb_linear_gemm for callers that cannot provide a workspace and must not allocate: the scratch
-// memory of the many-token kernel (the scaled input of both paths and the partial sums of a split
+// memory of the many-token kernel (the input in contraction order and the partial sums of a split
 // contraction) lives in a device array of this library instead of a caller's buffer.
 #include <hip/hip_runtime.h>
 
@@ -54,10 +54,15 @@ extern "C" int rb_linear_gemm_noalloc(const rb_layer *L, const void *X, void *Y,
         rb::set_last_path(RB_PATH_MX);
         return rb::gemv1::launch(L, X, Y, stream);
     }
-    // three paths at up to 32 tokens: the generic kernel, which needs no scratch memory, serves
-    // whatever the many-token kernel's scratch would not fit
+    // three paths at up to 32 tokens: the generic kernel serves whatever the many-token kernel's
+    // scratch would not fit
     const bool generic_instead = L->K == 3 && T <= 32 && rb::gemm::workspace_bytes(L, T) > SCRATCH_BYTES;
-    if (rb::single_gemm_applies(L, T) && !generic_instead) {
+    // the few-token kernel needs no scratch memory
+    if (rb::single_few_applies(L, T, act_dtype, out_dtype) && !generic_instead) {
+        rb::set_last_path(RB_PATH_GEMM);
+        return rb::batch::launch_call(L, X, Y, T, act_dtype, out_dtype, stream);
+    }
+    if (rb::single_gemm_applies(L, T)) {
         // the only kernels here that need scratch memory: every byte of it that they read in a
         // call they have written earlier in the same call, so nothing has to be cleared
         if (rb::gemm::workspace_bytes(L, T) > SCRATCH_BYTES) return RB_ERR_WORKSPACE;

@@ -262,3 +262,35 @@ def test_three_path_decode_kernel_early_reads_and_degenerate_scales():
             _check_stack(layers, [(0, 0, 1), (1, 1, 2), (2, 2, 3)], widths, x, 1, f"three paths, pause {pause}", True)
         finally:
             rb.rb_stack_set_option(rb.RB_OPT_HANDOVER_PAUSE, -1)
+
+
+@pytest.mark.parametrize("K,out,inn,T,bf16", [
+    (2, 20, 32, 3, False), (2, 4112, 288, 16, False), (2, 8200, 288, 5, True), (2, 12304, 160, 16, False), (2, 16390, 288, 7, False),
+    (3, 4112, 288, 6, False), (3, 8208, 160, 16, True), (3, 12300, 288, 9, False),       # 1, 2, 3, 4 and 6 row tiles per workgroup
+    (2, 300, 4384, 17, False), (2, 4112, 288, 32, True), (2, 8200, 96, 31, False), (3, 4100, 288, 18, False),
+    (2, 300, 8256, 33, True), (2, 4112, 288, 64, False), (2, 8200, 96, 49, False), (3, 4100, 160, 64, False)])
+def test_few_token_calls_element_by_element(K, out, inn, T, bf16):
+    """Every form of the few-token kernel (token groups of 16, row tiles per workgroup, both element
+    types) against fp64, fp32 results.  Products of a scale and an activation are exact, so only the
+    additions of the K in terms, the output scale and the path sum round: |error| <= (K in + 8)
+    2^-23 sum |g h x| (twice the half-ulp bound).  One h in eight is an fp16 subnormal, scales have
+    either sign; bf16 activations are representable in fp16 after halving."""
+    rng = synth.child_rng(3, 510, K, out, inn, T)
+    signs, g, h = random_layer(rng, K, out, inn)
+    g = g.copy(); h = h.copy()
+    g[0, ::5] *= -1; h[1, 1::3] *= -1
+    h[:, ::8] = (h[:, ::8].astype(np.float64) * 1e-3).astype(np.float16)
+    X = synth.outlier_activations(rng, T, inn)
+    Xd = torch.from_numpy(X).cuda()
+    if bf16:
+        Xd = Xd.to(torch.bfloat16)
+        X = Xd.float().cpu().numpy()
+    print(f"few-token call K={K} {out}x{inn} T={T} bf16={bf16}", flush=True)
+    Y = rb.rb_linear_gemm(to_device_layer(signs, g, h), Xd, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    ref = oracle.forward(signs, g, h, X.astype(np.float64))
+    size = np.zeros((T, out))
+    for k in range(K):
+        size += (np.abs(X.astype(np.float64)) @ np.abs(h[k].astype(np.float64)))[:, None] * np.abs(g[k].astype(np.float64))[None, :]
+    err = np.abs(Y.cpu().numpy().astype(np.float64) - ref)
+    assert np.all(err <= (K * inn + 8) * 2.0 ** -23 * size), float((err / size).max())
