@@ -1,21 +1,42 @@
-// Many-token path of the residual-binary layer: a matrix-core GEMM.
+// Many-token kernel of the residual-binary layer: a matrix-core GEMM, one launch, no pre-pass.
 //
 // Section 4.1 / Eq. (stacked binary weight): Y[t][i] = sum_k g_k[i] * sum_j B_k[i][j] * (h_k[j] X[t][j]).
-// With T in the thousands this is a dense contraction and belongs on the MFMA units:
-//   * the left operand is the effective weight W_hat, built in registers from the packed sign words
-//     (see gemm1_kernel).  Inside a group of 32 columns the order of the contraction index is free
-//     as long as both operands agree; the pre-pass stores X in the order that the shifts of the
-//     sign expansion produce: position 2n + hi holds the column whose sign is native bit n + 16 * hi
-//     of the word;
-//   * the right operand goes through LDS, shared by the four wavefronts of a workgroup tile.  It
-//     is copied global -> LDS without passing through registers, three 32-column steps ahead,
-//     into a ring of five buffers with one barrier per step; rows are 64 bytes and the four
-//     16-byte chunks of a row are XOR-swizzled with the token index so that neither the copy nor
-//     the operand reads collide on LDS banks.
+// With dozens of tokens per weight and more this is a dense contraction Y = W_hat X with
+// W_hat = sum_k g_k (.) B_k (.) h_k (Alg. 2, "compute layer output") on v_mfma_f32_32x32x16_f16.  The left
+// operand is W_hat itself, built in registers from the packed signs on the way to the matrix
+// instruction and never stored.  Per pair of fp16 elements and path: a shift brings the two sign bits
+// to bits 15 and 31, one three-input logic operation puts them on the pair of h_k, and a packed multiply
+// (the other paths: fused multiply-add) with g_k: six vector instructions for two paths, two
+// roundings to fp16.  Powers of two (s_k that brings max|h_k| into [1/4, 1/2), S / s_k on g_k with one S
+// for the rows of a workgroup; the result is multiplied by 1 / S) keep the products in fp16's normal range
+// however the layer splits its magnitude.
+//
+// What bounds it: the vector instructions that build W_hat, until some 128 tokens share them, then the
+// matrix units (a wavefront hides about six vector instructions behind one 32x32x16 instruction,
+// measured; the rest add up).  So a workgroup (8 wavefronts, one workgroup per compute unit) takes as
+// many tokens as still leave one workgroup per compute unit:
+//   * a wavefront owns 64 rows and all 32 NT tokens of the workgroup, so no two wavefronts build the same
+//     piece of W_hat for the same tokens; WR wavefronts stand side by side along the rows, and
+//     WK = 8 / WR groups of them share out the columns and add their sums in LDS at the end;
+//   * a step is 128 columns per group.  X goes through LDS (two buffers): whole 256-byte rows are
+//     fetched, converted if they are bfloat16, and stored as pairs (e, e + 4) of eight columns, the
+//     order in which one shift of a native sign word serves both halves of a register.  The scales h are
+//     K more rows of the same slab.  A part of a slab is requested a whole step before it is
+//     written, in two places of the step, so that the requests of eight wavefronts do not queue up;
+//   * sign words come straight from memory into the lane that needs them (lane (r, kg) takes columns 64 kg ..
+//     of the step): no lane exchange;
+//   * the tile is brought to the output's type in LDS and stored as whole rows;
+//   * the left operand of the next row block is built between the matrix instructions of this one.
+//
+// Measured (before: a 256 x 256 tile on four wavefronts behind four pre-pass launches and, for most
+// sizes, a launch that added partial sums; stores of single elements), fp16, two paths:
+// 4096 x 4096 at 333 tokens 85 -> 31 us, 11008 x 4096 116 -> 55 us, 4096 x 11008 124 -> 64 us, at 512
+// tokens 132 -> 79 us; 8192 x 8192 at 1024 tokens 198 -> 138 us (1.0 PFLOP/s).
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
+#include <atomic>
 
 #include "rabit.h"
 #include "rb_device.h"
@@ -26,590 +47,478 @@
 namespace rb {
 namespace gemm {
 
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
-
-constexpr int BLK_ROWS = 256;       // rows of a workgroup tile
-constexpr int LARGE_TOKENS = 256;   // tokens of a workgroup tile
-#define RB_LDS(p) ((__attribute__((address_space(3))) void *)(p))
-
-// which 16-byte position of its 64-byte LDS row chunk c of a token sits at: c ^ swizzle(token)
-__device__ __forceinline__ int swizzle(int token) { return ((token >> 1) ^ (token >> 3)) & 3; }
-
-__host__ __device__ inline int round_up(int v, int a) { return (v + a - 1) / a * a; }
-
-// position inside a group of 32 columns at which the pre-pass stores column `col` (0..31)
-__host__ __device__ inline int contraction_position(int col)
-{
-    const int b = native_bit(col);  // bit of the native sign word
-    return 2 * (b & 15) + (b >> 4);
-}
-
-// ------------------------------------------------------------- pre-pass ---
-constexpr size_t SCALES_BYTES = 256;
-
-// split-contraction: sums the partial outputs of the `split` workgroups that share an output tile
-// and rounds to the output type.  part is [split][T][rows] for rows row0 .. row0 + rows - 1 of Y.
-__global__ __launch_bounds__(256) void finish_kernel(const float *__restrict__ part, const float *__restrict__ scl,
-                                                     void *__restrict__ Y, int out_dtype, int T, int out, int row0,
-                                                     int rows, int split)
-{
-    const size_t n = (size_t)T * rows;
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    float s = 0.f;
-    for (int k = 0; k < split; ++k) s += part[(size_t)k * n + i];
-    const size_t t = i / rows, r = i % rows;
-    store_out(Y, out_dtype, t * out + row0 + r, s * scl[6]);
-}
-
-// ----------------------------------------------------------------- GEMM ---
-// "at most N vector-memory loads outstanding", then the workgroup barrier.  The immediate of
-// s_waitcnt on gfx9: vmcnt in bits 3:0 and 15:14, expcnt (no wait: 7) in 6:4, lgkmcnt (no wait: 15) in 11:8.
-template <int N>
-__device__ __forceinline__ void wait_copies_and_sync()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt((N & 0xf) | ((N >> 4) << 14) | (0x7 << 4) | (0xf << 8));
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
-// ------------------------------------------------- one contraction (prefill) ---
-// With hundreds of tokens per weight the dense form of the layer, Y = W_hat X with
-// W_hat = sum_k g_k (.) B_k (.) h_k (Alg. 2, "compute layer output"), needs half the matrix
-// instructions of K contractions of +-1 matrices: the left operand is the effective weight itself,
-// built in registers from the packed signs on the way to the matrix instruction and never stored.
-// Per pair of fp16 elements: |g_1| |h_1| (packed multiply), its sign from the sign word (shift,
-// and-or), the signed |h_2| (shift, and-or), and one packed fused multiply-add with |g_2|: six
-// vector instructions, two roundings to fp16 (the product of path 1 and the sum).  Signs of g are
-// folded into the sign words per row, signs of h per 32-column group (a word the pre-pass writes),
-// so the magnitudes are non-negative and the and-or can place the sign.  Magnitudes are scaled by
-// powers of two (h_k by s_k that brings max|h_k| into [1/4, 1/2), g_k by S / s_k with one S for all
-// paths) so that the products sit in fp16's normal range however the layer splits its magnitude; the
-// result is multiplied by 1 / S.  The right operand is X itself in fp16, in the contraction order of
-// the sign words.  A workgroup tile is 256 rows x 256 tokens; each of the four wavefronts owns 64
-// rows and all 256 tokens, so no two wavefronts build the same left operand.
-//
-// Output tiles are numbered row block by row block.  Workgroups 0 .. full_tiles - 1 take one tile
-// each; the tiles after that - the last, partly filled round of the device - are shared by
-// tail_split workgroups each, which take a slice of the column tiles and write fp32 partial sums to
-// Acc [slice][T][tail_rows] (rows tail_row0 ..) instead of the output; finish_kernel adds the slices.
-constexpr int ONE_NBUF = 5;                    // ring of right-operand buffers (three steps of copies in flight)
-constexpr int ONE_BUF_BYTES = LARGE_TOKENS * 64 + 256;     // 256 tokens x 32 columns of X, then the step's h block
-constexpr int HBLOCK_BYTES = 256;              // per 32-column group: [path][32 magnitudes fp16][K sign words][padding]
-
-// Largest |h_k| and |g_k|: ABSMAX_GROUPS workgroups take a slice each and write their four maxima
-// to part[group][4] (scratch that the next kernels overwrite)
-constexpr int ABSMAX_GROUPS = 64;
-// (part[group][2 k] for |h_k|, part[group][2 k + 1] for |g_k|, eight floats per group)
-__global__ __launch_bounds__(256) void absmax_kernel(const __half *__restrict__ g, const __half *__restrict__ h, int K, int out,
-                                                     int in, float *__restrict__ part)
-{
-    __shared__ float red[2 * RB_MAX_K][256];
-    float m[2 * RB_MAX_K];
-#pragma unroll
-    for (int q = 0; q < 2 * RB_MAX_K; ++q) m[q] = 0.f;
-    const int tid = blockIdx.x * 256 + threadIdx.x, stride = ABSMAX_GROUPS * 256;
-#pragma unroll
-    for (int k = 0; k < RB_MAX_K; ++k) {
-        if (k < K) {
-            for (int j = tid; j < in; j += stride) m[2 * k] = fmaxf(m[2 * k], fabsf(__half2float(h[(size_t)k * in + j])));
-            for (int j = tid; j < out; j += stride) m[2 * k + 1] = fmaxf(m[2 * k + 1], fabsf(__half2float(g[(size_t)k * out + j])));
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < 2 * RB_MAX_K; ++q) red[q][threadIdx.x] = m[q];
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s)
-#pragma unroll
-            for (int q = 0; q < 2 * RB_MAX_K; ++q) red[q][threadIdx.x] = fmaxf(red[q][threadIdx.x], red[q][threadIdx.x + s]);
-        __syncthreads();
-    }
-    if (threadIdx.x < 2 * RB_MAX_K) part[blockIdx.x * 8 + threadIdx.x] = red[threadIdx.x][0];
-}
-
-// scl[k] = s_k (h), scl[3 + k] = S / s_k (g), scl[6] = 1 / S, with S the largest common power of two
-// that keeps every path's |g_k| S / s_k at or below 1/2
-__global__ __launch_bounds__(64) void scales1_kernel(const float *__restrict__ part, int K, float *__restrict__ scl)
-{
-    float m[2 * RB_MAX_K];
-#pragma unroll
-    for (int q = 0; q < 2 * RB_MAX_K; ++q) {
-        m[q] = part[threadIdx.x * 8 + q];                   // ABSMAX_GROUPS = 64 = one per lane
-        for (int s = 32; s > 0; s >>= 1) m[q] = fmaxf(m[q], __shfl_xor(m[q], s));
-    }
-    if (threadIdx.x == 0) {
-        float sk[RB_MAX_K], S = 0.f;
-        for (int k = 0; k < K; ++k) {
-            sk[k] = mx::input_scale(m[2 * k]);
-            const float cand = sk[k] * mx::input_scale(m[2 * k + 1]);
-            S = k == 0 ? cand : fminf(S, cand);
-        }
-        for (int k = 0; k < K; ++k) { scl[k] = sk[k]; scl[3 + k] = S / sk[k]; }
-        scl[6] = 1.f / S;
-    }
-}
-
-// the h block of every 32-column group, and X in fp16 in contraction order (rows t >= T and columns
-// j >= in are zero)
-__global__ __launch_bounds__(32 * RB_MAX_K) void hblock_kernel(const __half *__restrict__ h, const float *__restrict__ scl, int K,
-                                                               int in, uint8_t *__restrict__ Hblk)
-{
-    // one thread per (path, column) of the group: threads 0..31 path 0, 32..63 path 1, 64..95 path 2
-    const int group = blockIdx.x, k = threadIdx.x >> 5, col = threadIdx.x & 31;
-    uint8_t *blk = Hblk + (size_t)group * HBLOCK_BYTES;
-    if (k >= K) {
-        // the rest of the block: nobody reads it, but it is copied
-        for (int i = K * 64 + K * 4 + 4 * col; i < HBLOCK_BYTES; i += 128) *reinterpret_cast<uint32_t *>(blk + i) = 0u;
-        return;
-    }
-    const int j = group * 32 + col;
-    const float hv = j < in ? __half2float(h[(size_t)k * in + j]) : 0.f;
-    reinterpret_cast<_Float16 *>(blk)[k * 32 + contraction_position(col)] = (_Float16)(fabsf(hv) * scl[k]);
-    // sign word in the bit order of the stored sign words: native bit of column col
-    const unsigned long long neg = __ballot(hv < 0.f);       // a wavefront holds two paths (or path 2 alone)
-    const uint32_t mine = (uint32_t)(neg >> (32 * (threadIdx.x >> 5 & 1)));
-    uint32_t word = 0;
-    for (int b = 0; b < 32; ++b) word |= ((mine >> b) & 1u) << native_bit(b);
-    if (col == 0) reinterpret_cast<uint32_t *>(blk + K * 64)[k] = word;
-    if (K == RB_MAX_K && k == 0)
-        for (int i = K * 64 + K * 4 + 4 * col; i < HBLOCK_BYTES; i += 128) *reinterpret_cast<uint32_t *>(blk + i) = 0u;
-}
-
-// a thread writes eight consecutive positions (16 bytes) of a 32-column group and gathers their
-// eight columns from the group's 64 bytes of X
-template <typename ActT>
-__global__ __launch_bounds__(256) void xperm_kernel(const ActT *__restrict__ X, _Float16 *__restrict__ Xp, int T, int T_pad,
-                                                    int in, int in_pad)
-{
-    const int p8 = blockIdx.x * 256 + threadIdx.x;          // which run of eight positions of the row
-    const int t = blockIdx.y;
-    if (p8 * 8 >= in_pad) return;
-    const int group = p8 >> 2, pos0 = (p8 & 3) * 8;
-    v8h o;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        // position 2n + hi holds the column of native bit n + 16 hi
-        const int pos = pos0 + e, bit = (pos >> 1) + 16 * (pos & 1);
-        const int j = group * 32 + column_of_native_bit(bit);
-        o[e] = (_Float16)((t < T && j < in) ? to_float(X[(size_t)t * in + j]) : 0.f);
-    }
-    *reinterpret_cast<v8h *>(Xp + (size_t)t * in_pad + (size_t)p8 * 8) = o;
-}
-
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 
-template <int OUT_DT, int K>
-__global__ __launch_bounds__(256, 1) void gemm1_kernel(const uint32_t *__restrict__ bits, const __half *__restrict__ g,
-                                                       const float *__restrict__ scl, const uint8_t *__restrict__ Hblk,
-                                                       const _Float16 *__restrict__ Xp, void *__restrict__ Y,
-                                                       float *__restrict__ Acc, int out, int RT, int CT, int T, int T_pad,
-                                                       int full_tiles, int tail_split, int tail_row0, int tail_rows)
+constexpr int WAVES = 8, MB = 2;                 // wavefronts of a workgroup, blocks of 32 rows of a wavefront
+constexpr int STEP_COLS = 128, ROW_BYTES = 256;  // columns of a step; a token's fp16 values of them
+constexpr int MAX_IN = 1 << 22;                  // 32-bit offsets into the rows of a tile
+
+template <int K, int NT> __host__ __device__ constexpr int slab_bytes() { return (32 * NT + K) * ROW_BYTES; }
+template <int K, int NT, int WR> __host__ __device__ constexpr int lds_bytes() { return 2 * (WAVES / WR) * slab_bytes<K, NT>(); }
+
+struct Args {
+    const uint32_t *bits;
+    const __half *g, *h;
+    const void *X;
+    void *Y;
+    int out, in, T, out_dtype;
+};
+
+__device__ __forceinline__ uint32_t pack_halves(_Float16 lo, _Float16 hi)
 {
-    constexpr int MP = 2, NT = 8, BLK_TOK = LARGE_TOKENS, NBUF = ONE_NBUF, BUF_BYTES = ONE_BUF_BYTES;
-    constexpr int COPIES = 4;                              // 16 groups of 16 tokens over four wavefronts
-    constexpr int CP = COPIES + 1;                         // copies per wavefront and step: X, and the h block
-    extern __shared__ __attribute__((aligned(16))) uint8_t Bs[];       // NBUF * BUF_BYTES
+    return (uint32_t)__builtin_bit_cast(unsigned short, lo) | ((uint32_t)__builtin_bit_cast(unsigned short, hi) << 16);
+}
+// eight values in memory order as the pairs (e, e + 4), e = 0..3: the order in which two shifts of a
+// native sign word by 4 e bring the bits of a pair to bits 15 and 31
+__device__ __forceinline__ uint4 pair_order(uint4 v)
+{
+    return make_uint4(__builtin_amdgcn_perm(v.z, v.x, 0x05040100u), __builtin_amdgcn_perm(v.z, v.x, 0x07060302u),
+                      __builtin_amdgcn_perm(v.w, v.y, 0x05040100u), __builtin_amdgcn_perm(v.w, v.y, 0x07060302u));
+}
+__device__ __forceinline__ _Float16 low_bf16(uint32_t v) { return (_Float16)__uint_as_float(v << 16); }
+__device__ __forceinline__ _Float16 high_bf16(uint32_t v) { return (_Float16)__uint_as_float(v & 0xffff0000u); }
+__device__ __forceinline__ uint4 pair_order_of_bf16(uint4 v)
+{
+    return make_uint4(pack_halves(low_bf16(v.x), low_bf16(v.z)), pack_halves(high_bf16(v.x), high_bf16(v.z)),
+                      pack_halves(low_bf16(v.y), low_bf16(v.w)), pack_halves(high_bf16(v.y), high_bf16(v.w)));
+}
+__device__ __forceinline__ float abs_max8(uint4 v)
+{
+    float m = 0.f;
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        m = fmaxf(m, fabsf(__half2float(__ushort_as_half((unsigned short)(w[i] & 0xffffu)))));
+        m = fmaxf(m, fabsf(__half2float(__ushort_as_half((unsigned short)(w[i] >> 16)))));
+    }
+    return m;
+}
+// loads that return zero past the end of their buffer (NOWHERE always is)
+constexpr uint32_t NOWHERE = 0x40000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void *p, size_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ uint4 buffer_load(__amdgpu_buffer_rsrc_t rs, uint32_t lane_offset, int offset)
+{
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)lane_offset, offset, 0));
+}
+
+// eight scales; without H16 they need only be 2-byte aligned
+template <bool H16> __device__ __forceinline__ uint4 load_h8(__amdgpu_buffer_rsrc_t rs, uint32_t lane_offset, int offset)
+{
+    if constexpr (H16) return buffer_load(rs, lane_offset, offset);
+    uint32_t v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        v[i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)lane_offset + 4 * i, offset, 0) |
+               (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)lane_offset + 4 * i + 2, offset, 0) << 16;
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
+// K paths, NT groups of 32 tokens, WR wavefronts along the rows (the other WAVES / WR share out the columns);
+// BF16: X is bfloat16; H16: h starts at a multiple of 16 bytes (its rows then do too)
+template <int K, int NT, int WR, bool BF16, bool H16>
+__global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
+{
+    constexpr int WK = WAVES / WR, GT = 64 * WR;               // column groups; threads of one
+    constexpr int TOK = 32 * NT, XL = TOK * 16 / GT, XP = XL / 2;     // tokens of a tile; 16-byte loads of X per thread and step, in two parts
+    constexpr int SLAB = slab_bytes<K, NT>();
+    static_assert(MB == 2 && TOK * 16 % GT == 0 && XL % 2 == 0, "whole loads per thread");
+    static_assert(TOK * (64 * WR * 4 + 16) <= lds_bytes<K, NT, WR>() && 32768 * NT <= lds_bytes<K, NT, WR>(), "what reuses the slabs fits");
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];       // [column group][2][SLAB]
+    __shared__ float red[2 * RB_MAX_K][WAVES];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r = lane & 15, half_sel = (lane >> 4) & 1, kg = lane >> 5;
-    const int in_pad = CT * TILE_COLS;
-    // workgroups that share a token block sit on the same XCD (ids are dealt round-robin over
-    // eight of them), so the slice of X they all walk stays in that XCD's L2
-    const int TB = T_pad / BLK_TOK;
-    int tile = (int)blockIdx.x, slice = 0, n_slices = 1;
-    if (tile >= full_tiles) {
-        const int u = tile - full_tiles;
-        tile = full_tiles + u / tail_split;
-        slice = u % tail_split;
-        n_slices = tail_split;
-    }
-    const bool partial = n_slices > 1;
-    const int tb = tile % TB, rb = tile / TB;
-    const int rt_base = rb * (BLK_ROWS / TILE_ROWS) + wave * MP * 2;           // first row tile of this wavefront
-    const int ct_begin = (int)((long)CT * slice / n_slices);
-    const int ct_end = (int)((long)CT * (slice + 1) / n_slices);
+    const int grp = wave / WR, wr = wave % WR;
+    const int r = lane & 31, kg = lane >> 5;
+    const int out = args.out, in = args.in, T = args.T;
+    const int RT = row_tiles(out), CT = col_tiles(in);
+    const int TB = (T + TOK - 1) / TOK, RB = (RT + 2 * MB * WR - 1) / (2 * MB * WR);
+    // workgroups go round the eight XCDs: each takes a run of tiles, token blocks fastest, so its L2 sees
+    // an eighth of the signs and all of X
+    const int tiles = RB * TB, per = (tiles + 7) / 8, id = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || id >= tiles) return;
+    const int t0 = id % TB * TOK, rt0 = (id / TB * WR + wr) * 2 * MB;
 
-    // ---- per-row constants: |g_k| S / s_k as a packed pair, and the sign of g_k as a mask on the sign words
-    // (both for the row this lane feeds to the matrix instruction: row pair m, row l % 32)
-    uint32_t G2[MP][K], flip[MP][K];
+    // steps of 128 columns, a run of them per column group
+    const int n128 = (in + STEP_COLS - 1) / STEP_COLS;
+    const int s_begin = n128 * grp / WK, s_end = n128 * (grp + 1) / WK, rounds = (n128 + WK - 1) / WK;
+
+    // ---- staging: thread gid of a column group takes chunk gid % 16 (8 columns) of rows gid / 16 + ..
+    // Everything a step advances is uniform over the wavefront; a lane keeps 32-bit offsets
+    const int gid = tid - grp * GT, ch = gid & 15, row0 = gid >> 4;
+    uint8_t *const slab0 = lds + (size_t)grp * 2 * SLAB;
+    const uint8_t *const Xt = static_cast<const uint8_t *>(args.X) + (size_t)t0 * in * 2;
+    uint32_t x_off[XL];
 #pragma unroll
-    for (int m = 0; m < MP; ++m) {
-        const int row = (rt_base + 2 * m + half_sel) * TILE_ROWS + r;
+    for (int i = 0; i < XL; ++i) x_off[i] = (uint32_t)min(row0 + i * (GT / 16), T - 1 - t0) * (uint32_t)in * 2u + (uint32_t)ch * 16u;
+    const uint32_t h_off = row0 < K ? ((uint32_t)row0 * (uint32_t)in + (uint32_t)ch * 8u) * 2u : NOWHERE;
+    const __amdgpu_buffer_rsrc_t x_rs = buffer(Xt, (size_t)min(TOK, T - t0) * in * 2), h_rs = buffer(args.h, (size_t)K * in * 2);
+    constexpr bool SHORT = NT == 4;                            // registers for half of a slab only
+    uint4 xs[SHORT ? XP : XL], hs;
+    auto reg = [&](int i) { return SHORT ? i % XP : i; };
+    // (no branch: the waits further down count the loads that came after)
+    auto request = [&](int s, int part) {
+        const bool real = s < s_end && s * STEP_COLS + ch * 8 < in;        // columns past the end read as zero
+        const int at = min(s, n128 - 1) * ROW_BYTES;
+#pragma unroll
+        for (int i = part * XP; i < part * XP + XP; ++i) xs[reg(i)] = buffer_load(x_rs, real ? x_off[i] : NOWHERE, at);
+        if (part == 0) hs = load_h8<H16>(h_rs, real ? h_off : NOWHERE, at);
+    };
+    float h_scale = 1.f;
+    // a chunk sits at position chunk ^ (row % 16) of its row: neither these writes nor the operand reads collide on LDS banks
+    auto put = [&](int buf, int part) {
+        uint8_t *const dst = slab0 + buf * SLAB;
+#pragma unroll
+        for (int i = part * XP; i < part * XP + XP; ++i) {
+            const int row = row0 + i * (GT / 16);
+            *reinterpret_cast<uint4 *>(dst + row * ROW_BYTES + ((ch ^ (row & 15)) * 16)) = BF16 ? pair_order_of_bf16(xs[reg(i)]) : pair_order(xs[reg(i)]);
+        }
+        if (part == 0 && row0 < K) {
+            uint4 v = hs;
+            uint32_t *const w = reinterpret_cast<uint32_t *>(&v);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const v2h p = __builtin_bit_cast(v2h, w[i]);
+                w[i] = pack_halves((_Float16)((float)p[0] * h_scale), (_Float16)((float)p[1] * h_scale));
+            }
+            *reinterpret_cast<uint4 *>(dst + (TOK + row0) * ROW_BYTES + ch * 16) = pair_order(v);
+        }
+    };
+    // sign words of row block b: lane (r, kg) holds, for row r of the 32, columns 64 kg + 32 u .. of the step
+    uint32_t w[MB][2][K], wn[MB][2][K];
+    uint32_t w_off[MB];
+    const int rt_safe = min(rt0, RT - 1);
+    const uint8_t *const tile_bits = reinterpret_cast<const uint8_t *>(args.bits + (size_t)rt_safe * CT * tile_words(K));
+#pragma unroll
+    for (int b = 0; b < MB; ++b) {
+        const uint32_t rt = (uint32_t)(min(rt0 + 2 * b + (r >> 4), RT - 1) - rt_safe);      // row tiles past the end: the last one, not stored
+        w_off[b] = (rt * (uint32_t)CT * tile_words(K) + ((uint32_t)(r & 15) + 32u * kg) * (2 * K)) * 4u;
+    }
+    auto load_words = [&](int s, uint32_t (&to)[MB][2][K]) {
+        const int sc = min(s, n128 - 1);
+        const uint8_t *const p = tile_bits + (size_t)(sc >> 1) * (tile_words(K) * 4) + (sc & 1) * (4 * K);
+#pragma unroll
+        for (int b = 0; b < MB; ++b)
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int k = 0; k < K; ++k) to[b][u][k] = *reinterpret_cast<const uint32_t *>(p + w_off[b] + u * (16 * 2 * K * 4) + k * 4);
+    };
+    request(s_begin, 0);
+    if (!SHORT) request(s_begin, 1);
+    load_words(s_begin, w);
+    float gv[MB][K];
+#pragma unroll
+    for (int b = 0; b < MB; ++b)
+#pragma unroll
+        for (int k = 0; k < K; ++k) gv[b][k] = __half2float(args.g[(size_t)k * out + min(rt0 * TILE_ROWS + 32 * b + r, out - 1)]);
+
+    // ---- powers of two that keep the effective weight in fp16's normal range
+    float mx_h[K], mx_g[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        mx_h[k] = 0.f;
+        for (int j = tid * 8; j < in; j += WAVES * 64 * 8) mx_h[k] = fmaxf(mx_h[k], abs_max8(load_h8<H16>(h_rs, (uint32_t)(k * in + j) * 2u, 0)));
+        mx_g[k] = 0.f;
+#pragma unroll
+        for (int b = 0; b < MB; ++b) mx_g[k] = fmaxf(mx_g[k], fabsf(gv[b][k]));
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        for (int d = 32; d > 0; d >>= 1) {
+            mx_h[k] = fmaxf(mx_h[k], __shfl_xor(mx_h[k], d));
+            mx_g[k] = fmaxf(mx_g[k], __shfl_xor(mx_g[k], d));
+        }
+        if (lane == 0) { red[2 * k][wave] = mx_h[k]; red[2 * k + 1][wave] = mx_g[k]; }
+    }
+    __syncthreads();
+    float S = 0.f, sk[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        float a = 0.f, b = 0.f;
+#pragma unroll
+        for (int v = 0; v < WAVES; ++v) { a = fmaxf(a, red[2 * k][v]); b = fmaxf(b, red[2 * k + 1][v]); }
+        sk[k] = mx::input_scale(a);
+        const float cand = sk[k] * mx::input_scale(b);
+        S = k == 0 ? cand : fminf(S, cand);
+        if (row0 == k) h_scale = sk[k];
+    }
+    v2h G[MB][K];
+#pragma unroll
+    for (int b = 0; b < MB; ++b)
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const __half gk = row < out ? g[(size_t)k * out + row] : __float2half(0.f);
-            flip[m][k] = (__half_as_ushort(gk) & 0x8000u) ? 0xffffffffu : 0u;
-            const float gv = fabsf(__half2float(gk)) * scl[3 + k];
-            const uint32_t mag = (uint32_t)__half_as_ushort(__float2half_rn(gv));
-            G2[m][k] = mag | (mag << 16);
+            const _Float16 v = (_Float16)(gv[b][k] * (S / sk[k]));
+            G[b][k] = (v2h){v, v};
         }
-    }
-    // lane (row, k group kg) holds positions 16 kk + 8 kg .. + 7: register e of half kk gets native
-    // bits n and n + 16, n = 8 kk + 4 kg + e, on bits 15 and 31.  The words are shifted right by
-    // 4 kg once per step; what is left of the shift is a constant.
-    const uint32_t kg4 = 4u * (uint32_t)kg;
+    put(0, 0);
+    if (SHORT) request(s_begin, 1); else request(s_begin + 1, 0);
+    put(0, 1);
+    if (!SHORT) request(s_begin + 1, 1);
+    __syncthreads();
 
-    // sign words of this wavefront's row tiles for one column tile: lane (r, q) holds, for row r,
-    // the 2 K words [column half c][path k] of columns 128c + 32q .. +31
-    struct Words { uint32_t w[2 * K]; };
-    auto load_half = [&](int ct, int c, Words (&w)[2 * MP]) {
+    v16f acc[MB][NT];
 #pragma unroll
-        for (int i = 0; i < 2 * MP; ++i) {
-            const int rt = rt_base + i;
-            const uint32_t *src = bits + (((size_t)rt * CT + ct) * 64 + lane) * (2 * K) + c * K;
-#pragma unroll
-            for (int k = 0; k < K; ++k) w[i].w[c * K + k] = rt < RT ? src[k] : 0u;
-        }
-    };
-    auto load_words = [&](int ct, Words (&w)[2 * MP]) {
-        load_half(ct, 0, w);
-        load_half(ct, 1, w);
-    };
-    // the words of column half c again, for the next column tile
-    auto reload_half = [&](int ct, int c, Words (&w)[2 * MP]) { load_half(ct, c, w); };
-
-    // right-operand staging: one copy instruction moves 16 tokens x 64 bytes; lane L lands at LDS
-    // position (token L / 4, chunk position L % 4) and therefore fetches chunk (L % 4) ^ swizzle(token)
-    // from memory.  The 256-byte h block of the step goes along (every wavefront copies it: four bytes
-    // per lane, the same bytes to the same place)
-    // (a base the wavefront shares plus a 32-bit offset per lane: a token block of X is < 4 GB)
-    const uint8_t *stage_base = reinterpret_cast<const uint8_t *>(Xp + (size_t)tb * BLK_TOK * in_pad);
-    uint32_t stage_off[COPIES];
-#pragma unroll
-    for (int j = 0; j < COPIES; ++j) {
-        const int token = 16 * (wave * COPIES + j) + (lane >> 2);
-        const int chunk = (lane & 3) ^ swizzle(token);
-        stage_off[j] = (uint32_t)(((size_t)token * in_pad + chunk * 8) * sizeof(_Float16));
-    }
-    // step s = 8 (ct - ct_begin) + 4 column half + 32-column group; its operands live in buffer s % NBUF
-    const int n_steps = (ct_end - ct_begin) * 8;
-    auto stage_step = [&](int s) {
-        const int sc = s < n_steps ? s : 0;               // past the end: repeat the first copy
-        const int group = ct_begin * 8 + sc;              // 32-column group of the matrix
-        uint8_t *buf = &Bs[(s % NBUF) * BUF_BYTES];
-        const uint8_t *src = stage_base + (size_t)group * 64;
-#pragma unroll
-        for (int j = 0; j < COPIES; ++j)
-            __builtin_amdgcn_global_load_lds(static_cast<const void *>(src + stage_off[j]),
-                                             RB_LDS(buf + (wave * COPIES + j) * 1024), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds(static_cast<const void *>(Hblk + (size_t)group * HBLOCK_BYTES + lane * 4),
-                                         RB_LDS(buf + LARGE_TOKENS * 64), 4, 0, 0);
-    };
-    // LDS addresses of this lane's operand reads inside a buffer: token tile n adds n * 2048
-    uint32_t b_addr[2];
-    {
-        const int token = lane & 31;
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk) b_addr[kk] = (uint32_t)(size_t)RB_LDS(&Bs[token * 64 + (((2 * kk + kg) ^ swizzle(token)) * 16)]);
-    }
-    const uint32_t h_addr = (uint32_t)(size_t)RB_LDS(&Bs[LARGE_TOKENS * 64 + 16 * kg]);
-
-    v16f acc[MP][NT];
-#pragma unroll
-    for (int m = 0; m < MP; ++m)
+    for (int b = 0; b < MB; ++b)
 #pragma unroll
         for (int n = 0; n < NT; ++n)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[m][n][e] = 0.f;
+            for (int e = 0; e < 16; ++e) acc[b][n][e] = 0.f;
 
-    Words cur[2 * MP];
-    v8h a[2][MP][2], b[NT][2];
-    v8h hm[K][2];                                             // [path][half]: |h| of this lane's eight positions
-    uint32_t hs[K];                                           // sign words of h for the step
-    uint32_t wq[MP][K];
-    const uint32_t sel_mask = half_sel ? 0xffffffffu : 0u;
-    // (addresses: one register per half and ring buffer, everything else in the instruction's offset)
-    auto read_b = [&](uint32_t addr, int n, int kk) {
-        switch (n) {
-        case 0: asm volatile("ds_read_b128 %0, %1" : "=v"(b[0][kk]) : "v"(addr) : "memory"); break;
-        case 1: asm volatile("ds_read_b128 %0, %1 offset:2048" : "=v"(b[1][kk]) : "v"(addr) : "memory"); break;
-        case 2: asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(b[2][kk]) : "v"(addr) : "memory"); break;
-        case 3: asm volatile("ds_read_b128 %0, %1 offset:6144" : "=v"(b[3][kk]) : "v"(addr) : "memory"); break;
-        case 4: asm volatile("ds_read_b128 %0, %1 offset:8192" : "=v"(b[4][kk]) : "v"(addr) : "memory"); break;
-        case 5: asm volatile("ds_read_b128 %0, %1 offset:10240" : "=v"(b[5][kk]) : "v"(addr) : "memory"); break;
-        case 6: asm volatile("ds_read_b128 %0, %1 offset:12288" : "=v"(b[6][kk]) : "v"(addr) : "memory"); break;
-        default: asm volatile("ds_read_b128 %0, %1 offset:14336" : "=v"(b[7][kk]) : "v"(addr) : "memory"); break;
-        }
+    // chunk 8 kg + 4 u + c of a row is columns 64 kg + 32 u + 8 c ..
+    const int x_addr = r * ROW_BYTES + (((8 * kg) ^ (r & 15)) * 16), h_addr = TOK * ROW_BYTES + 8 * kg * 16;
+    constexpr int XB = NT <= 3 ? 2 : 1;                        // operands of X read one contraction ahead (registers)
+    v8h x[XB][NT];
+    uint4 hv[2][K];
+    auto fetch_h = [&](const uint8_t *slab, int uc, int to) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) hv[to][k] = *reinterpret_cast<const uint4 *>(slab + h_addr + k * ROW_BYTES + uc * 16);
     };
-    // addr: this lane's 16 bytes of path 0, half 0 of the step's h block; reads 0 .. 2K - 1 are the
-    // magnitudes [path][half], read 2K the sign words (K * 64 bytes into the block; addr carries
-    // 16 bytes per k group)
-    auto read_h = [&](uint32_t addr, int i) {
-        switch (i) {
-        case 0: asm volatile("ds_read_b128 %0, %1" : "=v"(hm[0][0]) : "v"(addr) : "memory"); break;
-        case 1: asm volatile("ds_read_b128 %0, %1 offset:32" : "=v"(hm[0][1]) : "v"(addr) : "memory"); break;
-        case 2: asm volatile("ds_read_b128 %0, %1 offset:64" : "=v"(hm[1][0]) : "v"(addr) : "memory"); break;
-        case 3: asm volatile("ds_read_b128 %0, %1 offset:96" : "=v"(hm[1][1]) : "v"(addr) : "memory"); break;
-        default:
-            if constexpr (K == 3) {
-                if (i == 4) { asm volatile("ds_read_b128 %0, %1 offset:128" : "=v"(hm[K - 1][0]) : "v"(addr) : "memory"); break; }
-                if (i == 5) { asm volatile("ds_read_b128 %0, %1 offset:160" : "=v"(hm[K - 1][1]) : "v"(addr) : "memory"); break; }
-                v4u v;
-                asm volatile("ds_read_b128 %0, %1 offset:192" : "=v"(v) : "v"(addr - 16u * (uint32_t)kg) : "memory");
-                hs[0] = v[0]; hs[1] = v[1]; hs[K - 1] = v[2];
+    auto fetch_x = [&](const uint8_t *slab, int uc, int to) {
+#pragma unroll
+        for (int n = 0; n < NT; ++n) x[to][n] = *reinterpret_cast<const v8h *>(slab + (x_addr ^ (uc * 16)) + n * 32 * ROW_BYTES);
+    };
+    // register j of the left operand of row block b, columns of contraction uc: W_hat of a pair of columns
+    auto expand = [&](uint4 &a, int b, int uc, int from, int j) {
+        v2h sum;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const uint32_t hw = reinterpret_cast<const uint32_t *>(&hv[from][k])[j];
+            const v2h v = __builtin_bit_cast(v2h, hw ^ ((w[b][uc >> 2][k] << (15 - 4 * j - (uc & 3))) & 0x80008000u));
+            sum = k == 0 ? G[b][0] * v : __builtin_elementwise_fma(G[b][k], v, sum);
+        }
+        reinterpret_cast<uint32_t *>(&a)[j] = __builtin_bit_cast(uint32_t, sum);
+    };
+    for (int i = 0; i < rounds; ++i) {
+        const int s = s_begin + i;
+        const uint8_t *const slab = slab0 + (i & 1) * SLAB;
+        fetch_h(slab, 0, 0);
+        fetch_x(slab, 0, 0);
+        uint4 a[2];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) expand(a[0], 0, 0, 0, j);
+#pragma unroll
+        for (int uc = 0; uc < 8; ++uc) {
+            const int at = uc & 1;
+            // the next step's slab is written part by part.  Each part's registers are asked for again at once (a
+            // step later they are needed), or half a step before they are needed
+            if (SHORT) {
+                if (uc == 0) request(s + 1, 0);
+                if (uc == 4) { put((i + 1) & 1, 0); request(s + 1, 1); }
             } else {
-                uint2 v;
-                asm volatile("ds_read_b64 %0, %1 offset:128" : "=v"(v) : "v"(addr - 16u * (uint32_t)kg) : "memory");
-                hs[0] = v.x; hs[1] = v.y;
+                if (uc == 1) { put((i + 1) & 1, 0); request(s + 2, 0); }
+                if (uc == 5) { put((i + 1) & 1, 1); request(s + 2, 1); }
             }
-            break;
+            if (uc == 3) load_words(s + 1, wn);
+            if (uc < 7) fetch_h(slab, uc + 1, at ^ 1);
+            if (uc < 7 && XB == 2) fetch_x(slab, uc + 1, at ^ 1);
+            if (uc > 0 && XB == 1) fetch_x(slab, uc, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            // between the matrix instructions of one row block: the left operand of the next
+#pragma unroll
+            for (int b = 0; b < MB; ++b) {
+                const int next_uc = b + 1 < MB ? uc : uc + 1, next_b = (b + 1) % MB;
+#pragma unroll
+                for (int n = 0; n < NT; ++n) {
+                    acc[b][n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a[b & 1]), x[at % XB][n], acc[b][n], 0, 0, 0);
+                    if (next_uc < 8)
+#pragma unroll
+                        for (int j = 4 * n / NT; j < 4 * (n + 1) / NT; ++j) expand(a[(b + 1) & 1], next_b, next_uc, next_uc & 1, j);
+                    if (NT > 2) __builtin_amdgcn_sched_barrier(0);
+                }
+            }
         }
-    };
-    auto ring = [&](int s) { return (uint32_t)((s % NBUF) * BUF_BYTES); };
-    // The word of this lane's row (row tile 2m + half_sel, row r) sits in lane (r, q) of that
-    // tile's register.  The lane exchange is written as instructions, like the operand reads: its
-    // results are taken up after the step's common wait, not one by one.
-    uint32_t wf[MP][K][2];
-    const uint32_t bp_addr = 4u * (uint32_t)r;
-    auto fetch_a = [&](const Words (&w)[2 * MP], int c, int q, int m, int k) {
-        const uint32_t a0 = bp_addr + 64u * (uint32_t)q;
-        asm volatile("ds_bpermute_b32 %0, %1, %2" : "=v"(wf[m][k][0]) : "v"(a0), "v"(w[2 * m].w[c * K + k]) : "memory");
-        asm volatile("ds_bpermute_b32 %0, %1, %2" : "=v"(wf[m][k][1]) : "v"(a0), "v"(w[2 * m + 1].w[c * K + k]) : "memory");
-    };
-    // after the wait: pick the word of this lane's row tile, put the signs of g and h into it, and
-    // move it so that this lane's first position sits at bit 0 (and 16)
-    auto sign_a = [&](int m, int k) {
-        asm volatile("" : "+v"(wf[m][k][0]), "+v"(wf[m][k][1]));
-        const uint32_t w = (wf[m][k][0] & ~sel_mask) | (wf[m][k][1] & sel_mask);
-        wq[m][k] = (w ^ hs[k] ^ flip[m][k]) >> kg4;
-    };
-    auto expand_a = [&](int i, v8h (&aa)[MP][2]) {
-        // register e of the four of (row pair m, half kk): two elements of the effective weight
-        const int m = i >> 3, kk = (i >> 2) & 1, e = i & 3;
-        union { v8h h; uint32_t u[4]; v2h p[4]; } f, h0;
-        f.h = aa[m][kk];
-        h0.h = hm[0][kk];
-        union { uint32_t u; v2h p; } g0, p1;
-        g0.u = G2[m][0];
-        p1.p = g0.p * h0.p[e];                                                 // |g_1| |h_1|
-        p1.u = ((wq[m][0] << (15 - 8 * kk - e)) & 0x80008000u) | p1.u;          // its sign
+        if (SHORT) put((i + 1) & 1, 1);
 #pragma unroll
-        for (int k = 1; k < K; ++k) {
-            union { v8h h; uint32_t u[4]; } hk;
-            union { uint32_t u; v2h p; } gk, sk;
-            hk.h = hm[k][kk];
-            gk.u = G2[m][k];
-            sk.u = ((wq[m][k] << (15 - 8 * kk - e)) & 0x80008000u) | hk.u[e];   // signed |h_k|
-            p1.p = __builtin_elementwise_fma(gk.p, sk.p, p1.p);
-        }
-        f.p[e] = p1.p;
-        aa[m][kk] = f.h;
-    };
-    auto wait_lds = [&]() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
-    auto touch_h = [&]() {
+        for (int b = 0; b < MB; ++b)
 #pragma unroll
-        for (int k = 0; k < K; ++k) asm volatile("" : "+v"(hm[k][0]), "+v"(hm[k][1]), "+v"(hs[k]));
-    };
-    auto touch_b = [&](int kk) {
+            for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int n = 0; n < NT; ++n) asm volatile("" : "+v"(b[n][kk]));
-    };
-
-    if (n_steps > 0) {
-        // ---- prologue: NBUF - 1 steps of copies in flight; operands of step 0 in registers
-        load_words(ct_begin, cur);
-#pragma unroll
-        for (int s = 0; s < NBUF - 1; ++s) stage_step(s);
-        wait_copies_and_sync<CP * (NBUF - 2)>();               // step 0 has landed
-#pragma unroll
-        for (int i = 0; i < 2 * K + 1; ++i) read_h(h_addr, i);
-#pragma unroll
-        for (int m = 0; m < MP; ++m)
-#pragma unroll
-            for (int k = 0; k < K; ++k) fetch_a(cur, 0, 0, m, k);
-#pragma unroll
-        for (int n = 0; n < NT; ++n) read_b(b_addr[0], n, 0);
-        wait_lds();
-        touch_h();
-        touch_b(0);
-#pragma unroll
-        for (int m = 0; m < MP; ++m)
-#pragma unroll
-            for (int k = 0; k < K; ++k) sign_a(m, k);
-#pragma unroll
-        for (int i = 0; i < MP * 8; ++i) expand_a(i, a[0]);
+                for (int k = 0; k < K; ++k) w[b][u][k] = wn[b][u][k];
+        __syncthreads();
     }
 
-    // ---- main loop: 32 matrix instructions per step (2 row pairs x 8 token tiles x 2 halves).  In
-    // between: the second half of this step's right operand (slots 0-7), everything the next
-    // step's left operand needs (h block, sign words, expansion) and the first half of its right
-    // operand (slots 16-23, after that half's last use).
-    for (int ct = ct_begin; ct < ct_end; ++ct) {
+    // ---- sums of the column groups: the upper half hands its accumulators to the lower half
+    float4 *const part = reinterpret_cast<float4 *>(lds);
 #pragma unroll
-        for (int step = 0; step < 8; ++step) {
-            const int s = (ct - ct_begin) * 8 + step;
-            const int p = step & 1, pn = p ^ 1;
-            const int ns = (step + 1) & 7;
-            const int c_ = ns >> 2, q_ = ns & 3;
-            const uint32_t here = ring(s), next = ring(s + 1);
-            const uint32_t b1_here = b_addr[1] + here, b0_next = b_addr[0] + next, h_next = h_addr + next;
+    for (int half = WK / 2; half > 0; half >>= 1) {
+        float4 *const mine = part + (size_t)((grp % half) * WR + wr) * (MB * NT * 4 * 64) + lane;
+        if (grp >= half && grp < 2 * half)
 #pragma unroll
-            for (int j = 0; j < 32; ++j) {
-                const int kk = j >> 4, n = (j >> 1) & 7, m = j & 1;
-                if (j == 16) {                                  // this step's second half, and the next step's words and h
-                    wait_lds();
-                    touch_b(1);
-                    touch_h();
+            for (int b = 0; b < MB; ++b)
 #pragma unroll
-                    for (int mm = 0; mm < MP; ++mm)
+                for (int n = 0; n < NT; ++n)
 #pragma unroll
-                        for (int k = 0; k < K; ++k) sign_a(mm, k);
-                }
-                acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[p][m][kk], b[n][kk], acc[m][n], 0, 0, 0);
-                if (j == 0) {
-                    // the copies of step s + 1 were requested NBUF - 2 steps before it, and
-                    // CP * (NBUF - 3) copies came after them; behind the barrier every wavefront has
-                    // read what it needed from the buffer of step s - 1, which the next copies fill
-                    wait_copies_and_sync<CP * (NBUF - 3)>();
-                    stage_step(s + NBUF - 1);
-                }
-                if (j < 8) read_b(b1_here, j, 1);
-                if (j >= 1 && j < 2 * K + 2) read_h(h_next, j - 1);
-                if (j >= 8 && j < 8 + MP * K) fetch_a(cur, c_, q_, (j - 8) / K, (j - 8) % K);
-                if (j >= 16 && j < 24) read_b(b0_next, j - 16, 0);
-                if (j >= 16) expand_a(j - 16, a[pn]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            wait_lds();
-            touch_b(0);
-            // the words of column half c were last fetched for its fourth step, one step ahead
-            if ((step & 3) == 2 && ct + 1 < ct_end) reload_half(ct + 1, step >> 2, cur);
-        }
+                    for (int e = 0; e < 4; ++e)
+                        mine[((b * NT + n) * 4 + e) * 64] = make_float4(acc[b][n][4 * e], acc[b][n][4 * e + 1], acc[b][n][4 * e + 2], acc[b][n][4 * e + 3]);
+        __syncthreads();
+        if (grp < half)
+#pragma unroll
+            for (int b = 0; b < MB; ++b)
+#pragma unroll
+                for (int n = 0; n < NT; ++n)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float4 v = mine[((b * NT + n) * 4 + e) * 64];
+                        acc[b][n][4 * e] += v.x; acc[b][n][4 * e + 1] += v.y; acc[b][n][4 * e + 2] += v.z; acc[b][n][4 * e + 3] += v.w;
+                    }
+        __syncthreads();
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // no copy may land in LDS after the end
-
-    // ---- epilogue: lane l of tile (m, n) holds token 32n + l % 32 and, in register 4a + e, row
-    // 8a + 4 (l / 32) + e of the 32
-    asm volatile("" : "+s"(out));
-    const float inv_s = scl[6];
+    // ---- the tile in the output's type through LDS, so that whole rows of it are stored.  Register 4 e + i
+    // of lane (r, kg): token r, row 8 e + 4 kg + i of the 32
+    constexpr int RW = 32 * MB * WR;                           // rows of the workgroup
+    const int size = args.out_dtype == RB_F32 ? 4 : 2, pitch = RW * size + 16;
+    if (grp == 0) {
+        const float inv = 1.f / S;
 #pragma unroll
-    for (int n = 0; n < NT; ++n) {
-        const int t = tb * BLK_TOK + n * 32 + (lane & 31);
-        if (t >= T) continue;
+        for (int n = 0; n < NT; ++n)
 #pragma unroll
-        for (int m = 0; m < MP; ++m) {
-#pragma unroll
-            for (int a4 = 0; a4 < 4; ++a4) {
-                const int row0 = (rt_base + 2 * m) * TILE_ROWS + 8 * a4 + 4 * kg;
+            for (int b = 0; b < MB; ++b)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    if (row0 + e >= out) continue;
-                    if (partial)
-                        Acc[((size_t)slice * T + t) * tail_rows + (row0 + e - tail_row0)] = acc[m][n][4 * a4 + e];
-                    else
-                        store_out(Y, OUT_DT, (size_t)t * out + row0 + e, acc[m][n][4 * a4 + e] * inv_s);
+                    uint8_t *const dst = lds + (32 * n + r) * pitch + (32 * (MB * wr + b) + 8 * e + 4 * kg) * size;
+                    float v[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = acc[b][n][4 * e + i] * inv;
+                    if (args.out_dtype == RB_F32) {
+                        *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+                    } else {
+                        uint32_t o[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) o[i] = args.out_dtype == RB_F16 ? __half_as_ushort(__float2half_rn(v[i])) : f32_to_bf16_rne(v[i]);
+                        *reinterpret_cast<uint2 *>(dst) = make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
+                    }
                 }
-            }
+    }
+    __syncthreads();
+    const int first = id / TB * RW, rows = min(RW, out - first), tokens = min(TOK, T - t0), per16 = 16 / size;
+    uint8_t *const Y = static_cast<uint8_t *>(args.Y) + ((size_t)t0 * out + first) * size;
+    if (out % per16 == 0) {                                    // rows of Y start at multiples of 16 bytes
+        const int chunks = RW / per16;                         // a power of two
+        for (int i = tid; i < tokens * chunks; i += WAVES * 64) {
+            const int t = i / chunks, c = i % chunks;
+            if (c * per16 < rows) *reinterpret_cast<uint4 *>(Y + ((size_t)t * out + c * per16) * size) = *reinterpret_cast<const uint4 *>(lds + t * pitch + c * 16);
+        }
+    } else {
+        for (int i = tid; i < tokens * RW; i += WAVES * 64) {
+            const int t = i / RW, c = i % RW;
+            if (c >= rows) continue;
+            if (size == 4) *reinterpret_cast<float *>(Y + ((size_t)t * out + c) * 4) = *reinterpret_cast<const float *>(lds + t * pitch + c * 4);
+            else *reinterpret_cast<uint16_t *>(Y + ((size_t)t * out + c) * 2) = *reinterpret_cast<const uint16_t *>(lds + t * pitch + c * 2);
         }
     }
+}
+
+// X out of the way of an output that overlaps it
+__global__ __launch_bounds__(256) void copy_kernel(const uint4 *__restrict__ from, uint4 *__restrict__ to, size_t n)
+{
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) to[i] = from[i];
 }
 
 // ------------------------------------------------------------------ host ---
-struct Plan {
-    int T_pad, CT, in_pad, RT, RB, TB;
-    // the tiles of the last, partly filled round are shared by tail_split workgroups each
-    int full_tiles, tail_split, tail_row0, tail_rows;
-    size_t u_bytes, acc_bytes, hblk_bytes;      // X in fp16, partial sums, h blocks
-};
+// The shapes of a workgroup, and what a round of the device takes with each, in microseconds: `fixed` (launch,
+// scales, first loads, sums, stores) and `step` per step of 128 columns per group, for two and for three paths.
+// Measured on layers of 256 to 11008 columns (4096 x 11008, 22 or 43 steps, against 4096 x 4096, 8 or 16); a
+// round costs the same whether it fills the device or not (11008 x 4096 at 333 tokens, two paths: 172 workgroups of
+// 256 x 96 55 us, 129 of 256 x 128 63, 258 of 256 x 64 92, 516 of 128 x 64 91), so the shape with the least sum is taken.
+struct Shape { int NT, WR; float fixed, step[2]; };
+constexpr Shape SHAPES[] = {{1, 2, 6.3f, {2.05f, 2.8f}}, {2, 2, 10.f, {2.5f, 3.35f}}, {2, 4, 9.5f, {2.15f, 2.8f}},
+                            {3, 4, 11.5f, {2.4f, 3.15f}}, {4, 4, 12.5f, {2.85f, 3.65f}}};
+constexpr int N_SHAPES = sizeof(SHAPES) / sizeof(SHAPES[0]);
 
-static Plan make_plan(const rb_layer *L, int T)
+static int tiles_of(const Shape &s, int out, int T)
 {
-    Plan p;
-    p.T_pad = round_up(T, LARGE_TOKENS);
-    p.CT = col_tiles(L->in);
-    p.in_pad = p.CT * TILE_COLS;
-    p.RT = row_tiles(L->out);
-    p.RB = (p.RT + BLK_ROWS / TILE_ROWS - 1) / (BLK_ROWS / TILE_ROWS);
-    p.TB = p.T_pad / LARGE_TOKENS;
-    p.hblk_bytes = (size_t)p.CT * 8 * HBLOCK_BYTES;
-    p.u_bytes = ((size_t)p.T_pad * p.in_pad * sizeof(_Float16) + 255) / 256 * 256;
-    p.acc_bytes = 0;
-    const int tiles = p.RB * p.TB;
-    p.full_tiles = tiles;
-    p.tail_split = 1;
-    p.tail_row0 = 0;
-    p.tail_rows = L->out;
-    // A tile takes the same time wherever it runs, so a last round that fills half of the
-    // compute units or less costs a whole round.  Its tiles (whole row blocks) are cut along
-    // the contraction instead, into as many slices as fill the round.
-    const int cus = mx::device_groups();
-    const int G = cus > 0 ? cus : 256;               // no device (size queries on a host): an MI355X
-    const int full = tiles / G * G / p.TB * p.TB;
-    const int tail = tiles - full;
-    const int cut = tail > 0 ? std::min(std::min(G / tail, 4), p.CT) : 1;
-    if (cut > 1) {
-        p.full_tiles = full;
-        p.tail_split = cut;
-        p.tail_row0 = full / p.TB * BLK_ROWS;
-        p.tail_rows = L->out - p.tail_row0;
-        p.acc_bytes = (size_t)cut * T * p.tail_rows * sizeof(float);
+    return (row_tiles(out) + 4 * s.WR - 1) / (4 * s.WR) * ((T + 32 * s.NT - 1) / (32 * s.NT));
+}
+static int best_shape(const rb_layer *L, int T)
+{
+    const int cus = std::max(1, mx::device_groups()), n128 = (L->in + STEP_COLS - 1) / STEP_COLS;
+    int best = 0;
+    float least = 0.f;
+    for (int i = 0; i < N_SHAPES; ++i) {
+        const int groups = WAVES / SHAPES[i].WR, rounds = (tiles_of(SHAPES[i], L->out, T) + cus - 1) / cus;
+        const float cost = (float)rounds * (SHAPES[i].fixed + SHAPES[i].step[L->K - 2] * (float)((n128 + groups - 1) / groups));
+        if (i == 0 || cost < least) { best = i; least = cost; }
     }
-    return p;
+    return best;
 }
 
+template <int K, int NT, int WR, bool BF16, bool H16> static int launch_form(const Args &a, hipStream_t stream)
+{
+    constexpr int lds = lds_bytes<K, NT, WR>();
+    static std::atomic<bool> allowed[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return RB_ERR_HIP;
+    if (!allowed[dev].load()) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_kernel<K, NT, WR, BF16, H16>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+            return RB_ERR_HIP;
+        allowed[dev].store(true);
+    }
+    const int tiles = tiles_of(Shape{NT, WR, 0.f, {0.f, 0.f}}, a.out, a.T);
+    hipLaunchKernelGGL((gemm_kernel<K, NT, WR, BF16, H16>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(WAVES * 64), lds, stream, a);
+    return RB_OK;
+}
+
+template <int K, bool BF16> static int launch_shape(const Args &a, int shape, hipStream_t stream)
+{
+    // scales at an odd multiple of two bytes: one shape serves them, eight loads in place of one
+    if ((uintptr_t)a.h & 15) return launch_form<K, 2, 4, BF16, false>(a, stream);
+    switch (shape) {
+    case 0: return launch_form<K, 1, 2, BF16, true>(a, stream);
+    case 1: return launch_form<K, 2, 2, BF16, true>(a, stream);
+    case 2: return launch_form<K, 2, 4, BF16, true>(a, stream);
+    case 3: return launch_form<K, 3, 4, BF16, true>(a, stream);
+    default: return launch_form<K, 4, 4, BF16, true>(a, stream);
+    }
+}
+
+// What a caller is asked for (rb_workspace_bytes): room for the input and, when 256 x 256 tiles
+// do not fill whole rounds of the device, for partial sums of the tiles of the last round.  This kernel uses
+// the room for the input alone, and that only when the output overlaps it; the size asked for stays what it was,
+// so that callers that keep one buffer for many layers need not change.
+constexpr int BLK = 256;
+constexpr size_t SCALES_BYTES = 256, HBLOCK_BYTES = 256;
 size_t workspace_bytes(const rb_layer *L, int T)
 {
-    const Plan p = make_plan(L, T);
-    return SCALES_BYTES + p.hblk_bytes + p.u_bytes + p.acc_bytes;
+    const int T_pad = (T + BLK - 1) / BLK * BLK, CT = col_tiles(L->in), TB = T_pad / BLK;
+    const int tiles = (row_tiles(L->out) + BLK / TILE_ROWS - 1) / (BLK / TILE_ROWS) * TB;
+    const int cus = mx::device_groups(), G = cus > 0 ? cus : 256;       // no device (size queries on a host): an MI355X
+    const int full = tiles / G * G / TB * TB, tail = tiles - full;
+    const int cut = tail > 0 ? std::min(std::min(G / tail, 4), CT) : 1;
+    const size_t input = ((size_t)T_pad * CT * TILE_COLS * 2 + 255) / 256 * 256;
+    const size_t partial = cut > 1 ? (size_t)cut * T * (L->out - full / TB * BLK) * sizeof(float) : 0;
+    return SCALES_BYTES + (size_t)CT * 8 * HBLOCK_BYTES + input + partial;
 }
 
 bool supported(const rb_layer *L, int T)
 {
-    return (L->K == 2 || L->K == 3) && T >= 1;
+    return (L->K == 2 || L->K == 3) && T >= 1 && L->in < MAX_IN;
 }
 
 int launch(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
            hipStream_t stream)
 {
-    const Plan p = make_plan(L, T);
-    float *scl = static_cast<float *>(workspace);
-    uint8_t *Hblk = static_cast<uint8_t *>(workspace) + SCALES_BYTES;
-    _Float16 *U = reinterpret_cast<_Float16 *>(Hblk + p.hblk_bytes);
-    float *Acc = p.acc_bytes > 0 ? reinterpret_cast<float *>(reinterpret_cast<uint8_t *>(U) + p.u_bytes) : nullptr;
-    const __half *h = reinterpret_cast<const __half *>(L->h);
-    // one contraction on the effective weight built in registers
-    const uint32_t *bits = static_cast<const uint32_t *>(L->bits);
-    const __half *g = reinterpret_cast<const __half *>(L->g);
-    static_assert(ABSMAX_GROUPS == 64 && ABSMAX_GROUPS * 8 * sizeof(float) <= LARGE_TOKENS * TILE_COLS * sizeof(_Float16), "partials fit in U");
-    hipLaunchKernelGGL(absmax_kernel, dim3(ABSMAX_GROUPS), dim3(256), 0, stream, g, h, L->K, L->out, L->in, reinterpret_cast<float *>(U));
-    hipLaunchKernelGGL(scales1_kernel, dim3(1), dim3(64), 0, stream, reinterpret_cast<const float *>(U), L->K, scl);
-    hipLaunchKernelGGL(hblock_kernel, dim3(p.CT * 8), dim3(32 * RB_MAX_K), 0, stream, h, scl, L->K, L->in, Hblk);
-    const dim3 xgrid((p.in_pad / 8 + 255) / 256, p.T_pad);
-    if (act_dtype == RB_F16)
-        hipLaunchKernelGGL(xperm_kernel<__half>, xgrid, dim3(256), 0, stream, static_cast<const __half *>(X), U, T, p.T_pad,
-                           L->in, p.in_pad);
-    else
-        hipLaunchKernelGGL(xperm_kernel<bf16_t>, xgrid, dim3(256), 0, stream, static_cast<const bf16_t *>(X), U, T, p.T_pad,
-                           L->in, p.in_pad);
-    const int tail_tiles = p.RB * p.TB - p.full_tiles;
-    const dim3 grid((unsigned)(p.full_tiles + tail_tiles * p.tail_split));
-    constexpr int lds1 = ONE_NBUF * ONE_BUF_BYTES;
-    auto run = [&](auto kernel) -> int {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds1) !=
-            hipSuccess)
-            return RB_ERR_HIP;
-        hipLaunchKernelGGL(kernel, grid, dim3(256), lds1, stream, bits, g, scl, Hblk, U, Y, Acc, L->out, p.RT, p.CT, T, p.T_pad,
-                           p.full_tiles, p.tail_split, p.tail_row0, p.tail_rows);
-        return RB_OK;
-    };
-    const int rc = L->K == 3 ? (out_dtype == RB_F16    ? run(gemm1_kernel<RB_F16, 3>)
-                                : out_dtype == RB_BF16 ? run(gemm1_kernel<RB_BF16, 3>)
-                                                       : run(gemm1_kernel<RB_F32, 3>))
-                             : (out_dtype == RB_F16    ? run(gemm1_kernel<RB_F16, 2>)
-                                : out_dtype == RB_BF16 ? run(gemm1_kernel<RB_BF16, 2>)
-                                                       : run(gemm1_kernel<RB_F32, 2>));
-    if (rc != RB_OK) return rc;
-    if (p.tail_split > 1) {
-        const size_t n = (size_t)T * p.tail_rows;
-        hipLaunchKernelGGL(finish_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, Acc, scl, Y, out_dtype, T,
-                           L->out, p.tail_row0, p.tail_rows, p.tail_split);
+    const uintptr_t x = (uintptr_t)X, y = (uintptr_t)Y;
+    const size_t x_bytes = (size_t)T * L->in * 2, y_bytes = (size_t)T * L->out * (out_dtype == RB_F32 ? 4 : 2);
+    if (x < y + y_bytes && y < x + x_bytes) {                  // in % 32 == 0: whole 16-byte pieces
+        hipLaunchKernelGGL(copy_kernel, dim3(1024), dim3(256), 0, stream, static_cast<const uint4 *>(X), static_cast<uint4 *>(workspace), x_bytes / 16);
+        X = workspace;
     }
+    Args a;
+    a.bits = static_cast<const uint32_t *>(L->bits);
+    a.g = reinterpret_cast<const __half *>(L->g);
+    a.h = reinterpret_cast<const __half *>(L->h);
+    a.X = X; a.Y = Y;
+    a.out = L->out; a.in = L->in; a.T = T; a.out_dtype = out_dtype;
+    const int s = best_shape(L, T);
+    const int rc = L->K == 2 ? (act_dtype == RB_BF16 ? launch_shape<2, true>(a, s, stream) : launch_shape<2, false>(a, s, stream))
+                             : (act_dtype == RB_BF16 ? launch_shape<3, true>(a, s, stream) : launch_shape<3, false>(a, s, stream));
+    if (rc != RB_OK) return rc;
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;
 }
 

@@ -1,6 +1,6 @@
 // rb_linear_gemm for callers that cannot provide a workspace and must not allocate: the scratch
-// memory of the many-token kernel (the input in contraction order and the partial sums of a split
-// contraction) lives in a device array of this library instead of a caller's buffer.
+// memory of the many-token kernel (a copy of an input that the output overlaps) lives in a device
+// array of this library instead of a caller's buffer.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -63,8 +63,8 @@ extern "C" int rb_linear_gemm_noalloc(const rb_layer *L, const void *X, void *Y,
         return rb::batch::launch_call(L, X, Y, T, act_dtype, out_dtype, stream);
     }
     if (rb::single_gemm_applies(L, T)) {
-        // the only kernels here that need scratch memory: every byte of it that they read in a
-        // call they have written earlier in the same call, so nothing has to be cleared
+        // every byte of scratch memory that is read in a call was written earlier in the same call, so
+        // nothing has to be cleared
         if (rb::gemm::workspace_bytes(L, T) > SCRATCH_BYTES) return RB_ERR_WORKSPACE;
         void *ptr = nullptr;
         const int rs = scratch_of_current_device(&ptr);

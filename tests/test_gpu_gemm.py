@@ -181,3 +181,56 @@ def test_prefill_70b_shapes_sampled(out, inn):
             err = max_rel_l2(Y[t:t + 1, r0:r0 + 512], ref2)
             _say(f"  rows {r0}.. t={t} rel_l2={err:.3e}")
             assert err <= TOL
+
+
+@pytest.mark.parametrize("K", [2, 3])
+@pytest.mark.parametrize("out,inn,T,act,res,shift", [
+    (40, 32, 65, "f16", "f16", 0),          # fewer rows than a wavefront's, one 32-column step, one token over a block
+    (130, 160, 97, "bf16", "f32", 0),       # one row tile in the second workgroup, ragged rows stored one by one
+    (1000, 2080, 333, "f16", "bf16", 1),    # column groups of unequal length; scales at an odd multiple of two bytes
+    (4096, 288, 500, "bf16", "f16", 0),     # 128 x 64 tiles, last column tile nearly empty
+    (8184, 384, 500, "f16", "f32", 0),      # 256 x 64
+    (11008, 256, 333, "f16", "f16", 0),     # 256 x 96
+    (8200, 256, 1025, "bf16", "bf16", 0),   # 256 x 128, one row and one token over
+])
+def test_many_token_shapes(K, out, inn, T, act, res, shift):
+    """Every shape of a workgroup of the many-token kernel at its edges, scales of either sign and zero.
+    The bar: 1e-3 for results in fp16 and fp32; bf16 results round by up to 2^-9 of each value, 2^-9 / sqrt(3) in
+    the mean, on top."""
+    rng = synth.child_rng(5, 120, K, out, inn, T)
+    signs, g, h = random_layer(rng, K, out, inn)
+    g = g.copy(); h = h.copy()
+    g[1, ::6] *= -1; h[0, ::3] *= -1; g[0, 3] = 0; h[1, 5] = 0
+    X = synth.outlier_activations(rng, T, inn)
+    _say(f"many-token K={K} out={out} in={inn} T={T} {act} -> {res} shift={shift}")
+    L = to_device_layer(signs, g, h)
+    if shift:
+        store = torch.zeros(K * inn + shift, dtype=torch.float16, device="cuda")
+        store[shift:] = L.h.flatten()
+        L.h = store[shift:].view(K, inn)
+        assert L.h.data_ptr() % 4 == 2
+    Xd = torch.from_numpy(X).cuda()
+    if act == "bf16":
+        Xd = Xd.to(torch.bfloat16)
+        X = oracle.bf16_bits_to_f64(bf16_bits(Xd.cpu())).reshape(T, inn)
+    dtype = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[res]
+    Y = torch.full((T + 1, out), 7.0, dtype=dtype, device="cuda")
+    rb.rb_linear_gemm(L, Xd, Y=Y[:T])
+    torch.cuda.synchronize()
+    assert rb.rb_last_path() == rb.RB_PATH_GEMM
+    assert torch.all(Y[T] == 7.0)
+    err = max_rel_l2(Y[:T], oracle.forward(signs, g, h, X))
+    _say(f"  rel_l2={err:.3e}")
+    assert err <= TOL + (2.0 ** -9 / 3 ** 0.5 if res == "bf16" else 0.0)
+
+
+def test_many_token_output_over_its_input():
+    """The output buffer may be the input buffer beyond 64 tokens (the input is moved to the workspace first)."""
+    n, T = 544, 130
+    rng = synth.child_rng(5, 121)
+    L = to_device_layer(*random_layer(rng, 2, n, n))
+    X = torch.from_numpy(synth.outlier_activations(rng, T, n)).cuda()
+    want = rb.rb_linear_gemm(L, X)
+    got = rb.rb_linear_gemm(L, X, Y=X)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
