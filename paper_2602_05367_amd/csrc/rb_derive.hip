@@ -11,10 +11,18 @@
 // ever materialised: a path is its packed signs and two vectors, and every pass recomputes R_i
 // from W (4 bytes per weight) and the other paths (a bit and two cached scale values each), so a
 // pass is bound by the HBM read of W.  The singular triplet comes from a power iteration from the
-// all-ones vector (the matrix is non-negative): two passes per iteration, a = |R| b by rows (one
-// wavefront per row) and b = |R|^T a by columns (slices of rows, partial sums added in slice
-// order); in both a lane takes four consecutive columns, one 16-byte load of W.  Every sum has a fixed order.  The iteration's stopping rule is
-// evaluated on the device; the host reads one flag every few iterations, so the call synchronises.
+// all-ones vector (the matrix is non-negative): two passes per iteration, a = |R| b by rows (four rows
+// per workgroup) and c = |R|^T a by columns (slices of rows, partial sums added in slice order); in both a lane takes
+// four consecutive columns, one 16-byte load of W.  a is left at its length: with b of length 1, sigma = ||c|| / ||a|| and
+// the next b is c / ||c||.  After the last iteration one more pass by rows gives the last |R| b, the
+// signs of R_i and ||R_i||^2, from which the error follows.  Every sum has a fixed order.  The
+// iteration's stopping rule is evaluated on the device; the host reads one flag per update when it expects the
+// iteration to have finished, so the call synchronises.
+//
+// Measured, 4096 x 11008, two paths, five sweeps (ten updates of four iterations): before (a row per wavefront, slices
+// of 64 rows on single wavefronts, a normalisation after each pass, separate passes for the last |R| b, the signs and
+// the error) 8.7 ms, now 4.9 ms: a row pass 38 us (4.8 TB/s of W),
+// a column pass 47 us, the sums and the normalisation 14 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -26,8 +34,9 @@
 namespace rb {
 namespace derive {
 
-constexpr int ROW_SLICE = 64;          // rows one workgroup of the column pass walks
-constexpr int CHECK_EVERY = 4;         // power iterations between two looks at the flag
+constexpr int ROW_SLICE = 32;          // rows one workgroup of the column pass walks (twice that where the workspace is the smaller)
+constexpr int ROWS = 4;                // rows one workgroup of the row pass takes
+constexpr int FIRST_LOOK = 4;          // power iterations before the first look at the flag
 constexpr int MAX_ITER = 200;
 constexpr double TOL_SIGMA = 1e-13, TOL_B = 1e-10;
 
@@ -67,29 +76,24 @@ __device__ __forceinline__ void residual4(const Problem &p, int r, int c, int sk
 }
 
 struct Scalars {
-    double sigma;       // the iteration's current estimate (norm of |R|^T a)
-    double na;          // norm of |R| b
+    double sigma;       // the iteration's current estimate
     double db;          // norm of the last change of b
     int done;           // the stopping rule held (or the matrix is zero)
-    int zero;           // |R| b = 0
+    int direct;         // the error is too small a difference: recompute it term by term
     int iters;
     int pad_;
 };
 
-// one workgroup: sum of squares of v[0..n) in a fixed order
-__device__ double block_sumsq(const double *v, int n, double *red)
+// sum over a workgroup of `waves` wavefronts in a fixed order, in every thread; red has a slot per wavefront
+__device__ __forceinline__ double group_sum(double v, double *red, int waves)
 {
+    for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
     double s = 0.0;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) s += v[i] * v[i];
-    red[threadIdx.x] = s;
+    for (int w = 0; w < waves; ++w) s += red[w];
     __syncthreads();
-    for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    const double total = red[0];
-    __syncthreads();
-    return total;
+    return s;
 }
 
 __global__ __launch_bounds__(256) void start_kernel(double *b, int in, Scalars *sc)
@@ -97,142 +101,237 @@ __global__ __launch_bounds__(256) void start_kernel(double *b, int in, Scalars *
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < in) b[i] = 1.0 / sqrt((double)in);
     if (i == 0) {
-        sc->sigma = 0.0; sc->na = 0.0; sc->db = 0.0; sc->done = 0; sc->zero = 0; sc->iters = 0; sc->pad_ = 0;
+        sc->sigma = 0.0; sc->db = 0.0; sc->done = 0; sc->direct = 0; sc->iters = 0; sc->pad_ = 0;
     }
 }
 
-// a_raw[r] = sum_c |R[r][c]| b[c]; one wavefront per row, a lane takes four consecutive columns at
-// a time (256 columns per step of the wavefront)
-__global__ __launch_bounds__(256) void rows_kernel(Problem p, int skip, const double *b, double *a_raw, const Scalars *sc,
-                                                   bool final_pass)
+// R[r][c .. c + 3] of ROWS rows for path `skip`: what the rows share of the columns (the factors, the other
+// paths' h) is read once for all of them, which is what the row pass is bound by (28 bytes through the caches for
+// the 4 bytes of a weight with one row at a time)
+template <int K, int R>
+__device__ __forceinline__ void residuals(const Problem &p, int r, int r_last, int c, int skip, const double (&g)[R][K], const double (&rows)[R], double (&v)[R][4])
 {
-    if (!final_pass && sc->done) return;
-    const int lane = threadIdx.x & 63;
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (r >= p.out) return;
-    double g_r[RB_MAX_K];
-    for (int j = 0; j < p.K; ++j) g_r[j] = p.g[(size_t)j * p.out + r];
-    const double rows_r = p.rows ? p.rows[r] : 1.0;
-    double s = 0.0;
-#pragma unroll 2
-    for (int c = 4 * lane; c < p.in; c += 256) {
-        double v[4];
-        residual4(p, r, c, skip, g_r, rows_r, v);
-        const double2 b01 = *reinterpret_cast<const double2 *>(b + c), b23 = *reinterpret_cast<const double2 *>(b + c + 2);
-        s += fabs(v[0]) * b01.x;
-        s += fabs(v[1]) * b01.y;
-        s += fabs(v[2]) * b23.x;
-        s += fabs(v[3]) * b23.y;
+    float4 w[R];
+    uint32_t bits[R][K];
+    const int W32 = p.in / 32;
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        w[u] = *reinterpret_cast<const float4 *>(p.W + (size_t)min(r + u, r_last) * p.in + c);
+#pragma unroll
+        for (int j = 0; j < K; ++j) bits[u][j] = j == skip ? 0u : p.packed[((size_t)j * p.out + min(r + u, r_last)) * W32 + (c >> 5)] >> (c & 31);
     }
-    for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m);
-    if (lane == 0) a_raw[r] = s;
+    double f[4] = {1.0, 1.0, 1.0, 1.0};
+    if (p.cols) {
+        const double2 c01 = *reinterpret_cast<const double2 *>(p.cols + c), c23 = *reinterpret_cast<const double2 *>(p.cols + c + 2);
+        f[0] = c01.x; f[1] = c01.y; f[2] = c23.x; f[3] = c23.y;
+    }
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        v[u][0] = (double)w[u].x; v[u][1] = (double)w[u].y; v[u][2] = (double)w[u].z; v[u][3] = (double)w[u].w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (p.rows) v[u][e] = rows[u] * v[u][e];
+            if (p.cols) v[u][e] = v[u][e] * f[e];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        if (j == skip) continue;
+        const double2 h01 = *reinterpret_cast<const double2 *>(p.h + (size_t)j * p.in + c);
+        const double2 h23 = *reinterpret_cast<const double2 *>(p.h + (size_t)j * p.in + c + 2);
+        const double hv[4] = {h01.x, h01.y, h23.x, h23.y};
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                // the sign of g_j B_j: bit e of the word to the top of the value
+                const unsigned long long flip = (unsigned long long)(bits[u][j] << (31 - e) & 0x80000000u) << 32;
+                v[u][e] -= __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, g[u][j]) ^ flip) * hv[e];
+            }
+    }
 }
 
-// a = a_raw / ||a_raw||  (one workgroup)
-__global__ __launch_bounds__(1024) void unit_a_kernel(const double *a_raw, double *a, int out, Scalars *sc, bool final_pass)
+// a[r] = sum_c |R[r][c]| b[c], its square by workgroup.  FINAL (after the iteration): also the signs of R (sign(0) = +1;
+// 32 columns per word, bit b = column 32 w + b, 1 means -1; nobody reads the path left out) and the sum of
+// the squares of R by workgroup.  ROWS rows per workgroup, 1024 columns per step
+template <int K, bool FINAL>
+__global__ __launch_bounds__(256) void rows_kernel(Problem p, int skip, const double *b, double *a, double *a_sq, double *r_sq,
+                                                   uint32_t *signs, const Scalars *sc)
 {
-    if (!final_pass && sc->done) return;
-    __shared__ double red[1024];
-    const double na = sqrt(block_sumsq(a_raw, out, red));
-    for (int i = threadIdx.x; i < out; i += 1024) a[i] = na > 0.0 ? a_raw[i] / na : 0.0;
-    if (threadIdx.x == 0) {
-        sc->na = na;
-        if (na == 0.0) { sc->zero = 1; sc->done = 1; }
+    if (FINAL ? !sc->done : sc->done) return;
+    __shared__ double red[4][ROWS], red1[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = blockIdx.x * ROWS, r_last = p.out - 1;
+    double g[ROWS][K], rows[ROWS];
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+        const int row = min(r + u, r_last);
+#pragma unroll
+        for (int j = 0; j < K; ++j) g[u][j] = p.g[(size_t)j * p.out + row];
+        rows[u] = p.rows ? p.rows[row] : 1.0;
     }
+    double dot[ROWS], sq = 0.0;
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) dot[u] = 0.0;
+    for (int c0 = 0; c0 < p.in; c0 += 1024) {
+        const int c = c0 + 4 * (int)threadIdx.x, cs = c < p.in ? c : 0;      // in % 32 == 0: all four columns or none
+        double2 b01 = *reinterpret_cast<const double2 *>(b + cs), b23 = *reinterpret_cast<const double2 *>(b + cs + 2);
+        if (c >= p.in) b01 = b23 = make_double2(0.0, 0.0);
+        double v[ROWS][4];
+        residuals<K, ROWS>(p, r, r_last, cs, skip, g, rows, v);
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            if (FINAL) {
+                // eight lanes hold the 32 columns of a word, four each
+                uint32_t four = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    four |= !(v[u][e] >= 0.0) ? 1u << e : 0u;
+                    if (c < p.in && r + u < p.out) sq += v[u][e] * v[u][e];
+                }
+                const uint32_t word = or_over_8(four << (4 * (lane & 7)));
+                if ((lane & 7) == 0 && c < p.in && r + u < p.out) signs[(size_t)(r + u) * (p.in / 32) + (c >> 5)] = word;
+            }
+            dot[u] += fabs(v[u][0]) * b01.x;
+            dot[u] += fabs(v[u][1]) * b01.y;
+            dot[u] += fabs(v[u][2]) * b23.x;
+            dot[u] += fabs(v[u][3]) * b23.y;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+        for (int m = 32; m > 0; m >>= 1) dot[u] += __shfl_xor(dot[u], m);
+        if (lane == 0) red[wave][u] = dot[u];
+    }
+    if (FINAL) sq = group_sum(sq, red1, 4);
+    else __syncthreads();
+    if (threadIdx.x != 0) return;
+    double s2 = 0.0;
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+        if (r + u >= p.out) break;
+        const double s = ((red[0][u] + red[1][u]) + red[2][u]) + red[3][u];
+        a[r + u] = s;
+        s2 += s * s;
+    }
+    a_sq[blockIdx.x] = s2;
+    if (FINAL) r_sq[blockIdx.x] = sq;
 }
 
 // partial[slice][c] = sum over the slice's rows of |R[r][c]| a[r]; a thread per four consecutive
-// columns, the rows of the slice in order
-__global__ __launch_bounds__(64) void cols_kernel(Problem p, int skip, const double *a, double *partial, const Scalars *sc)
+// columns, the rows of the slice in order, ROWS at a time
+template <int K>
+__global__ __launch_bounds__(256) void cols_kernel(Problem p, int skip, const double *a, double *partial, int slice_rows, const Scalars *sc)
 {
     if (sc->done) return;
-    const int c = (blockIdx.x * 64 + threadIdx.x) * 4;
-    const int r0 = blockIdx.y * ROW_SLICE, r1 = min(p.out, r0 + ROW_SLICE);
+    const int c = (blockIdx.x * 256 + threadIdx.x) * 4;
+    const int r0 = blockIdx.y * slice_rows, r1 = min(p.out, r0 + slice_rows);
     if (c >= p.in) return;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 8
-    for (int r = r0; r < r1; ++r) {
-        double g_r[RB_MAX_K];
-        for (int j = 0; j < p.K; ++j) g_r[j] = p.g[(size_t)j * p.out + r];
-        double v[4];
-        residual4(p, r, c, skip, g_r, p.rows ? p.rows[r] : 1.0, v);
-        const double a_r = a[r];
-        for (int e = 0; e < 4; ++e) s[e] += fabs(v[e]) * a_r;
+#pragma unroll 1
+    for (int r = r0; r < r1; r += ROWS) {
+        double g[ROWS][K], rows[ROWS], v[ROWS][4];
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            const int row = min(r + u, r1 - 1);
+#pragma unroll
+            for (int j = 0; j < K; ++j) g[u][j] = p.g[(size_t)j * p.out + row];
+            rows[u] = p.rows ? p.rows[row] : 1.0;
+        }
+        residuals<K, ROWS>(p, r, r1 - 1, c, skip, g, rows, v);
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+            const double a_r = r + u < r1 ? a[r + u] : 0.0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] += fabs(v[u][e]) * a_r;
+        }
     }
     double *dst = partial + (size_t)blockIdx.y * p.in + c;
     *reinterpret_cast<double2 *>(dst) = make_double2(s[0], s[1]);
     *reinterpret_cast<double2 *>(dst + 2) = make_double2(s[2], s[3]);
 }
 
-// sum[c] = the slices of partial[.][c] in order
-__global__ __launch_bounds__(256) void slices_kernel(const double *partial, int n_slices, int in, double *sum, const Scalars *sc)
+// sum[c] = the slices of partial[.][c], in eight runs of consecutive ones, and the squares by workgroup
+constexpr int SUMS_COLS = 64, SUMS_RUNS = 8;
+__global__ __launch_bounds__(SUMS_COLS * SUMS_RUNS) void slices_kernel(const double *partial, int n_slices, int in, double *sum, double *sum_sq, const Scalars *sc)
 {
     if (sc->done) return;
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= in) return;
+    __shared__ double part[SUMS_RUNS][SUMS_COLS];
+    const int x = threadIdx.x % SUMS_COLS, run = threadIdx.x / SUMS_COLS, c = blockIdx.x * SUMS_COLS + x, cs = min(c, in - 1);
     double s = 0.0;
 #pragma unroll 8
-    for (int k = 0; k < n_slices; ++k) s += partial[(size_t)k * in + c];
-    sum[c] = s;
+    for (int k = n_slices * run / SUMS_RUNS; k < n_slices * (run + 1) / SUMS_RUNS; ++k) s += partial[(size_t)k * in + cs];
+    part[run][x] = s;
+    __syncthreads();
+    if (threadIdx.x >= SUMS_COLS) return;
+    s = 0.0;
+#pragma unroll
+    for (int k = 0; k < SUMS_RUNS; ++k) s += part[k][x];
+    if (c < in) sum[c] = s;
+    double sq = c < in ? s * s : 0.0;
+    for (int m = SUMS_COLS / 2; m > 0; m >>= 1) sq += __shfl_xor(sq, m);
+    if (x == 0) sum_sq[blockIdx.x] = sq;
 }
 
-// b_new = scratch / its norm, the change of b, the stopping rule  (one workgroup; scratch is used up)
-__global__ __launch_bounds__(1024) void unit_b_kernel(double *b, double *scratch, int in, Scalars *sc)
+// b_new = sum / its norm, the change of b, the stopping rule  (one workgroup)
+__global__ __launch_bounds__(1024) void unit_kernel(double *b, const double *sum, const double *sum_sq, const double *a_sq, int n_a, int in, Scalars *sc)
 {
     if (sc->done) return;
-    __shared__ double red[1024];
-    const double s_new = sqrt(block_sumsq(scratch, in, red));
+    __shared__ double red[32];
+    double nc = 0.0, na = 0.0;
+    for (int i = threadIdx.x; i < (in + SUMS_COLS - 1) / SUMS_COLS; i += 1024) nc += sum_sq[i];
+    for (int i = threadIdx.x; i < n_a; i += 1024) na += a_sq[i];
+    for (int m = 32; m > 0; m >>= 1) { nc += __shfl_xor(nc, m); na += __shfl_xor(na, m); }
+    if ((threadIdx.x & 63) == 0) { red[threadIdx.x >> 6] = nc; red[16 + (threadIdx.x >> 6)] = na; }
+    __syncthreads();
+    nc = na = 0.0;
+    for (int w = 0; w < 16; ++w) { nc += red[w]; na += red[16 + w]; }
+    __syncthreads();
+    nc = sqrt(nc);
+    na = sqrt(na);
+    if (na == 0.0) {                                           // |R| b = 0: b stays
+        if (threadIdx.x == 0) sc->done = 1;
+        return;
+    }
+    double db = 0.0;
+#pragma unroll 4
     for (int c = threadIdx.x; c < in; c += 1024) {
-        const double bn = scratch[c] / s_new;
-        scratch[c] = bn - b[c];
+        const double bn = sum[c] / nc, d = bn - b[c];
+        db += d * d;
         b[c] = bn;
     }
-    __syncthreads();
-    const double db = sqrt(block_sumsq(scratch, in, red));
+    db = sqrt(group_sum(db, red, 16));
     if (threadIdx.x == 0) {
-        const bool done = fabs(s_new - sc->sigma) <= TOL_SIGMA * s_new && db <= TOL_B;
-        sc->sigma = s_new;
+        const double sigma = nc / na;
+        const bool done = fabs(sigma - sc->sigma) <= TOL_SIGMA * sigma && db <= TOL_B;
+        sc->sigma = sigma;
         sc->db = db;
         sc->iters += 1;
         if (done || sc->iters >= MAX_ITER) sc->done = 1;
     }
 }
 
-// after the final a = |R| b: g' = sqrt(sigma) a / sigma, h' = sqrt(sigma) b with sigma = ||a_raw||
-__global__ __launch_bounds__(1024) void scales_kernel(const double *a_raw, const double *b, double *g_i, double *h_i, int out, int in)
+// after the final a = |R| b: g' = sqrt(sigma) a / sigma, h' = sqrt(sigma) b with sigma = ||a||; the error from
+// ||R - What||^2 = ||R||^2 - sigma^2 (b has length 1), unless that is a difference of nearly equal numbers
+__global__ __launch_bounds__(256) void scales_kernel(const double *a, const double *b, const double *a_sq, const double *r_sq, int n_a, double *g_i,
+                                                     double *h_i, double *err, int out, int in, Scalars *sc)
 {
-    __shared__ double red[1024];
-    const double sigma = sqrt(block_sumsq(a_raw, out, red));
-    const double root = sqrt(sigma);
-    for (int i = threadIdx.x; i < out; i += 1024) g_i[i] = sigma > 0.0 ? root * (a_raw[i] / sigma) : 0.0;
-    for (int i = threadIdx.x; i < in; i += 1024) h_i[i] = root * b[i];
-}
-
-// B_i = sign(R_i) (sign(0) = +1), packed 32 columns per word, bit b = column 32 w + b, 1 means -1.
-// Written to a buffer of its own: the other kernels of this step still read path i's old signs
-// nowhere (it is the path left out), but a wavefront must not read words another has replaced.
-// Eight lanes hold the 32 columns of a word, four each: every lane shifts its four bits into place
-// and an OR over the eight gives the word.
-__global__ __launch_bounds__(256) void sign_kernel(Problem p, int skip, uint32_t *words)
-{
-    const int lane = threadIdx.x & 63;
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (r >= p.out) return;
-    double g_r[RB_MAX_K];
-    for (int j = 0; j < p.K; ++j) g_r[j] = p.g[(size_t)j * p.out + r];
-    const double rows_r = p.rows ? p.rows[r] : 1.0;
-    const int W32 = p.in / 32;
-    for (int c0 = 0; c0 < p.in; c0 += 256) {
-        const int c = c0 + 4 * lane;
-        uint32_t four = 0;
-        if (c < p.in) {                                        // in % 32 == 0: all four columns or none
-            double v[4];
-            residual4(p, r, c, skip, g_r, rows_r, v);
-            for (int e = 0; e < 4; ++e) four |= !(v[e] >= 0.0) ? 1u << e : 0u;
-        }
-        const uint32_t word = or_over_8(four << (4 * (lane & 7)));
-        const int w = (c0 >> 5) + (lane >> 3);
-        if ((lane & 7) == 0 && w < W32) words[(size_t)r * W32 + w] = word;
+    if (!sc->done) return;
+    __shared__ double red[4];
+    double a2 = 0.0;
+    for (int i = threadIdx.x; i < n_a; i += 256) a2 += a_sq[i];
+    a2 = group_sum(a2, red, 4);
+    const double sigma = sqrt(a2), root = sqrt(sigma);
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < out) g_i[i] = sigma > 0.0 ? root * (a[i] / sigma) : 0.0;
+    if (i < in) h_i[i] = root * b[i];
+    if (blockIdx.x != 0 || !err) return;
+    double r2 = 0.0;
+    for (int k = threadIdx.x; k < n_a; k += 256) r2 += r_sq[k];
+    r2 = group_sum(r2, red, 4);
+    if (threadIdx.x == 0) {
+        *err = sqrt(fmax(r2 - a2, 0.0));
+        // rounding leaves some 1e-15 of ||R||^2 in the difference; beyond a factor of 64 the terms are summed
+        sc->direct = !(r2 - a2 > r2 / 64.0);
     }
 }
 
@@ -288,24 +387,68 @@ __global__ __launch_bounds__(256) void unscale_kernel(double *g, double *h, cons
 }
 
 struct Layout {
-    size_t scalars, a_raw, a, b, scratch, partial, words, row_sq, total;
+    size_t scalars, a, a_sq, r_sq, b, sum, sum_sq, row_sq, partial, total;
 };
-static Layout make_layout(int out, int in)
+// the slices come last; `rows` of them each
+static Layout make_layout(int out, int in, int rows)
 {
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
-    const size_t slices = (size_t)(out + ROW_SLICE - 1) / ROW_SLICE;
+    const size_t slices = (size_t)(out + rows - 1) / rows, groups = (size_t)(out + ROWS - 1) / ROWS;
     Layout L;
     size_t o = 0;
     L.scalars = o; o += up(sizeof(Scalars));
-    L.a_raw = o; o += up(sizeof(double) * out);
     L.a = o; o += up(sizeof(double) * out);
+    L.a_sq = o; o += up(sizeof(double) * groups);
+    L.r_sq = o; o += up(sizeof(double) * groups);
     L.b = o; o += up(sizeof(double) * in);
-    L.scratch = o; o += up(sizeof(double) * in);
+    L.sum = o; o += up(sizeof(double) * in);
+    L.sum_sq = o; o += up(sizeof(double) * ((in + SUMS_COLS - 1) / SUMS_COLS));
+    L.row_sq = L.a;                                            // (the direct error is computed when a has been used up)
     L.partial = o; o += up(sizeof(double) * slices * in);
-    L.words = o; o += up(sizeof(uint32_t) * (size_t)out * (in / 32));
-    L.row_sq = o; o += up(sizeof(double) * out);
     L.total = o;
     return L;
+}
+
+struct Buffers {
+    Scalars *sc;
+    double *a, *a_sq, *r_sq, *b, *sum, *sum_sq, *row_sq, *partial;
+};
+
+template <int K>
+static int derive(const Problem &p, int T_max, double *g, double *h, uint32_t *packed, double *err, const Buffers &ws, int slice_rows, hipStream_t stream)
+{
+    const int out = p.out, in = p.in, n_slices = (out + slice_rows - 1) / slice_rows, n_a = (out + ROWS - 1) / ROWS;
+    const dim3 by_rows((unsigned)n_a), by_cols((in + 1023) / 1024, n_slices), wg(256);
+    int look = FIRST_LOOK;                         // iterations enqueued before the host looks: as many as the last update took
+    for (int t = 0; t < T_max; ++t) {
+        for (int i = 0; i < K; ++i) {
+            uint32_t *const signs = packed + (size_t)i * out * (in / 32);
+            double *const err_ti = err ? err + (size_t)t * K + i : nullptr;
+            hipLaunchKernelGGL(start_kernel, dim3((in + 255) / 256), wg, 0, stream, ws.b, in, ws.sc);
+            Scalars host;
+            for (int it = 1;; ++it) {
+                hipLaunchKernelGGL((rows_kernel<K, false>), by_rows, wg, 0, stream, p, i, ws.b, ws.a, ws.a_sq, ws.r_sq, signs, ws.sc);
+                hipLaunchKernelGGL((cols_kernel<K>), by_cols, wg, 0, stream, p, i, ws.a, ws.partial, slice_rows, ws.sc);
+                hipLaunchKernelGGL(slices_kernel, dim3((in + SUMS_COLS - 1) / SUMS_COLS), dim3(SUMS_COLS * SUMS_RUNS), 0, stream, ws.partial, n_slices, in, ws.sum, ws.sum_sq, ws.sc);
+                hipLaunchKernelGGL(unit_kernel, dim3(1), dim3(1024), 0, stream, ws.b, ws.sum, ws.sum_sq, ws.a_sq, n_a, in, ws.sc);
+                if (it < look) continue;
+                // |R| b and the signs for the converged b, the path's new scales: nothing happens unless the iteration has finished
+                hipLaunchKernelGGL((rows_kernel<K, true>), by_rows, wg, 0, stream, p, i, ws.b, ws.a, ws.a_sq, ws.r_sq, signs, ws.sc);
+                hipLaunchKernelGGL(scales_kernel, dim3((std::max(out, in) + 255) / 256), wg, 0, stream, ws.a, ws.b, ws.a_sq, ws.r_sq, n_a,
+                                   g + (size_t)i * out, h + (size_t)i * in, err_ti, out, in, ws.sc);
+                if (hipMemcpyAsync(&host, ws.sc, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess ||
+                    hipStreamSynchronize(stream) != hipSuccess)
+                    return RB_ERR_HIP;
+                if (host.done) break;
+            }
+            look = std::max(1, host.iters);
+            if (err && host.direct) {
+                hipLaunchKernelGGL(err_rows_kernel, dim3((out + 3) / 4), wg, 0, stream, p, ws.row_sq);
+                hipLaunchKernelGGL(err_sum_kernel, dim3(1), dim3(1024), 0, stream, ws.row_sq, out, err_ti);
+            }
+        }
+    }
+    return RB_OK;
 }
 
 }  // namespace derive
@@ -314,7 +457,7 @@ static Layout make_layout(int out, int in)
 extern "C" size_t rb_derive_workspace_bytes(int out, int in)
 {
     if (out < 1 || in < 32 || in % 32 != 0) return 0;
-    return rb::derive::make_layout(out, in).total;
+    return rb::derive::make_layout(out, in, rb::derive::ROW_SLICE).total;
 }
 
 extern "C" int rb_derive_iterative(const float *W, const double *row_factors, const double *col_factors, int K, int T_max,
@@ -327,19 +470,17 @@ extern "C" int rb_derive_iterative(const float *W, const double *row_factors, co
     if ((uintptr_t)packed & 3) return RB_ERR_ALIGN;
     if (((uintptr_t)g | (uintptr_t)row_factors | (uintptr_t)err) & 7) return RB_ERR_ALIGN;
     if (((uintptr_t)W | (uintptr_t)h | (uintptr_t)col_factors) & 15) return RB_ERR_ALIGN;      // read 16 bytes at a time
-    const Layout lay = make_layout(out, in);
+    // a smaller workspace (slices of twice the rows) does as well
+    const int slice_rows = workspace_bytes >= make_layout(out, in, ROW_SLICE).total ? ROW_SLICE : 2 * ROW_SLICE;
+    const Layout lay = make_layout(out, in, slice_rows);
     if (!workspace || workspace_bytes < lay.total) return RB_ERR_WORKSPACE;
     if ((uintptr_t)workspace & 15) return RB_ERR_ALIGN;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     uint8_t *ws = static_cast<uint8_t *>(workspace);
-    Scalars *sc = reinterpret_cast<Scalars *>(ws + lay.scalars);
-    double *a_raw = reinterpret_cast<double *>(ws + lay.a_raw), *a = reinterpret_cast<double *>(ws + lay.a);
-    double *b = reinterpret_cast<double *>(ws + lay.b), *scratch = reinterpret_cast<double *>(ws + lay.scratch);
-    double *partial = reinterpret_cast<double *>(ws + lay.partial), *row_sq = reinterpret_cast<double *>(ws + lay.row_sq);
-    uint32_t *words = reinterpret_cast<uint32_t *>(ws + lay.words);
+    auto at = [&](size_t offset) { return reinterpret_cast<double *>(ws + offset); };
+    const Buffers buf{reinterpret_cast<Scalars *>(ws + lay.scalars), at(lay.a), at(lay.a_sq), at(lay.r_sq), at(lay.b), at(lay.sum),
+                      at(lay.sum_sq), at(lay.row_sq), at(lay.partial)};
     const int W32 = in / 32;
-    const int n_slices = (out + ROW_SLICE - 1) / ROW_SLICE;
-    const dim3 by_rows((out + 3) / 4), by_cols((in + 255) / 256, n_slices);      // the column pass: 64 threads of 4 columns
 
     // What_i^(0) = 0: zero scales (and all-plus signs, which the zero scales make irrelevant)
     const size_t nv = (size_t)K * std::max(out, in), nw = (size_t)K * out * W32;
@@ -349,37 +490,10 @@ extern "C" int rb_derive_iterative(const float *W, const double *row_factors, co
                        static_cast<uint32_t *>(nullptr), (size_t)0);
     Problem p{W, row_factors, col_factors, packed, g, h, K, out, in};
 
-    for (int t = 0; t < T_max; ++t) {
-        for (int i = 0; i < K; ++i) {
-            hipLaunchKernelGGL(start_kernel, dim3((in + 255) / 256), dim3(256), 0, stream, b, in, sc);
-            for (int it = 0; it < MAX_ITER; it += CHECK_EVERY) {
-                for (int n = 0; n < CHECK_EVERY; ++n) {
-                    hipLaunchKernelGGL(rows_kernel, by_rows, dim3(256), 0, stream, p, i, b, a_raw, sc, false);
-                    hipLaunchKernelGGL(unit_a_kernel, dim3(1), dim3(1024), 0, stream, a_raw, a, out, sc, false);
-                    hipLaunchKernelGGL(cols_kernel, by_cols, dim3(64), 0, stream, p, i, a, partial, sc);
-                    hipLaunchKernelGGL(slices_kernel, dim3((in + 255) / 256), dim3(256), 0, stream, partial, n_slices, in, scratch, sc);
-                    hipLaunchKernelGGL(unit_b_kernel, dim3(1), dim3(1024), 0, stream, b, scratch, in, sc);
-                }
-                Scalars host;
-                if (hipMemcpyAsync(&host, sc, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess ||
-                    hipStreamSynchronize(stream) != hipSuccess)
-                    return RB_ERR_HIP;
-                if (host.done) break;
-            }
-            // sigma and a for the converged b, the signs of R_i, then the path's new scales
-            hipLaunchKernelGGL(rows_kernel, by_rows, dim3(256), 0, stream, p, i, b, a_raw, sc, true);
-            hipLaunchKernelGGL(sign_kernel, by_rows, dim3(256), 0, stream, p, i, words);
-            hipLaunchKernelGGL(scales_kernel, dim3(1), dim3(1024), 0, stream, a_raw, b, g + (size_t)i * out, h + (size_t)i * in, out,
-                               in);
-            if (hipMemcpyAsync(packed + (size_t)i * out * W32, words, sizeof(uint32_t) * (size_t)out * W32,
-                               hipMemcpyDeviceToDevice, stream) != hipSuccess)
-                return RB_ERR_HIP;
-            if (err) {
-                hipLaunchKernelGGL(err_rows_kernel, by_rows, dim3(256), 0, stream, p, row_sq);
-                hipLaunchKernelGGL(err_sum_kernel, dim3(1), dim3(1024), 0, stream, row_sq, out, err + (size_t)t * K + i);
-            }
-        }
-    }
+    const int rc = K == 1 ? derive<1>(p, T_max, g, h, packed, err, buf, slice_rows, stream)
+                 : K == 2 ? derive<2>(p, T_max, g, h, packed, err, buf, slice_rows, stream)
+                          : derive<3>(p, T_max, g, h, packed, err, buf, slice_rows, stream);
+    if (rc != RB_OK) return rc;
     if (row_factors || col_factors)
         hipLaunchKernelGGL(unscale_kernel, dim3((std::max(out, in) + 255) / 256), dim3(256), 0, stream, g, h, row_factors,
                            col_factors, K, out, in);

@@ -132,3 +132,29 @@ def test_full_size_layer_as_benchmarked_last_update_against_the_oracle():
     np.testing.assert_allclose(h[1], np.sqrt(sigma) * b, rtol=1e-8)
     left = np.linalg.norm(R - g[1][:, None] * B1 * h[1][None, :])
     np.testing.assert_allclose(flat[-1], left, rtol=1e-9)
+
+
+@pytest.mark.parametrize("K,out,inn,slices_of", [(2, 70, 1056, 32), (2, 70, 1056, 64), (1, 5, 32, 32), (3, 33, 2080, 64)])
+def test_slices_of_the_column_pass_and_their_workspace(K, out, inn, slices_of):
+    """Ragged rows and columns of both passes (four rows, 1024 columns, 64 columns of the sums); a workspace that holds
+    slices of 64 rows only is enough.  Same bars as above."""
+    rng = synth.child_rng(7, 705, K, out, slices_of)
+    W = synth.gaussian_weight(rng, out, inn, std=0.02).astype(np.float32)
+    signs, g, h, err = oracle.derive_iterative(W, K, 2)
+    need = rb.lib.rb_derive_workspace_bytes(out, inn)
+    if slices_of == 64:
+        need -= (-(-out // 32) - -(-out // 64)) * inn * 8 - 256          # (sizes are rounded to 256 bytes)
+    Wd = torch.from_numpy(W).cuda()
+    packed = torch.empty((K, out, inn // 32), dtype=torch.int32, device="cuda")
+    gd, hd = (torch.empty((K, n), dtype=torch.float64, device="cuda") for n in (out, inn))
+    ed = torch.empty((2, K), dtype=torch.float64, device="cuda")
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    print(f"derive K={K} {out}x{inn}, slices of {slices_of} rows", flush=True)
+    rc = rb.lib.rb_derive_iterative(Wd.data_ptr(), None, None, K, 2, out, inn, packed.data_ptr(), gd.data_ptr(), hd.data_ptr(),
+                                    ed.data_ptr(), ws.data_ptr(), need, None)
+    torch.cuda.synchronize()
+    assert rc == rb.RB_OK
+    assert np.array_equal(packed.cpu().numpy().view(np.uint32), oracle.pack(signs))
+    np.testing.assert_allclose(gd.cpu().numpy(), g, rtol=1e-8, atol=1e-14)
+    np.testing.assert_allclose(hd.cpu().numpy(), h, rtol=1e-8, atol=1e-14)
+    np.testing.assert_allclose(ed.cpu().numpy(), err, rtol=1e-9)
