@@ -8,11 +8,12 @@
 // input is prepared, and an op is one launch.  What bounds it:
 //   * a launch of a 4096-wide op moves 4 MB of signs, half a microsecond of HBM time, so it is a
 //     chain of latencies (launch, one trip to memory, the matrix instructions, the sum over the
-//     wavefronts): the compute units are filled and every wavefront asks for all it needs at once;
-//   * beyond that, vector instructions: three per two weights and path (a byte permute that brings
-//     two sign bits to bits 15 and 31, one three-input logic operation that puts them on the scales,
-//     and a share of the shifts), 0.7 to 0.9 k clocks per 16 x 256 tile and SIMD, where the matrix
-//     instructions of 16 tokens take 0.26 k.
+//     wavefronts): the compute units are filled and every wavefront asks for all it needs at once, the
+//     output scales of the end included;
+//   * the address unit, if activations are fetched in operand order (32 lines a load instruction: 11008
+//     columns for one row tile took 14.6 us, the transposition through LDS below takes 11);
+//   * beyond that, vector instructions: two per two weights and path (a shift and one three-input logic
+//     operation), where the matrix instructions of 16 tokens take a third of their time.
 // Shape: a workgroup owns P row tiles (16 rows) and all columns; its up to sixteen wavefronts share out the
 // column tiles, each takes all P row tiles of its columns, so an activation is read from memory by
 // one wavefront of the workgroup.  The partial outputs of the wavefronts meet in LDS and are added in
@@ -20,16 +21,17 @@
 // not depend on scheduling.  The ops of a stack that do not depend on each other (q/k/v, gate/up of
 // a transformer block) run in one launch; dependent ones are ordered by the stream.
 //
-// Measured (start: bf8 term expansions staged in LDS with a ring of copies, a set-up launch per input,
-// four launches for a single call): 7B-shaped dependent chain, 128 launches, 2.51 -> 1.42 ms at 8
-// tokens and 3.09 -> 1.61 ms at 16; a launch takes 7.5 us (4096 x 4096, one row tile per workgroup) to 17 us
+// Measured: 7B-shaped dependent chain, 128 launches, 1.30 ms at 8 tokens and 1.37 ms at 16 (activations in operand
+// order, the output scales fetched at the end: 1.42 and 1.61; bf8 term expansions of the activations in LDS, which
+// this kernel replaced: 2.51 and 3.09); a launch takes 6.3 us (4096 x 4096, one row tile per workgroup) to 16 us
 // (2 x 11008 x 4096, six), of which a dependent launch by itself is 4.7.  Single calls: 4096 x 11008
-// with three paths at 16 tokens 107 -> 17 us, 10999 x 4128 with two at 7 tokens 42 -> 13 us.
+// with three paths at 16 tokens 12.7 us, 10999 x 4128 with two at 7 tokens 11.4 us.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
 #include <atomic>
+#include <climits>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -52,10 +54,11 @@ constexpr int STACK_MAX_T = 16;        // tokens of a stack
 constexpr int MAX_STAGE_OPS = 8;       // independent ops that share a launch
 
 // Wavefronts of a workgroup at most, and row tiles per workgroup: accumulators take 4 P K G
-// registers and the activations of a column tile up to 32 G, of 128 with sixteen wavefronts per compute unit
-// and 256 with eight
-__host__ __device__ constexpr int max_waves(int G) { return G <= 2 ? 16 : 8; }
-__host__ __device__ constexpr bool p_available(int K, int G, int P) { return P == 1 || P * K <= (G == 1 ? 12 : 6); }
+// registers, sign words 2 P K, staged activations 16 G, of 128 with sixteen wavefronts per compute unit
+// and 256 with eight (two paths, six row tiles, 16 tokens: 28.6 us a launch of 2 x 11008 x 4096 with sixteen, which
+// spills, 16.2 with eight; four row tiles, 8 tokens, 7B chain: the same either way)
+__host__ __device__ constexpr int max_waves(int K, int G, int P) { return G == 1 && P * K <= 8 ? 16 : 8; }
+__host__ __device__ constexpr bool p_available(int K, int G, int P) { return P == 1 || P * K <= (G == 1 ? 12 : G == 2 ? 6 : 4); }
 
 struct Op {
     const uint32_t *bits;     // native sign tiles
@@ -64,49 +67,37 @@ struct Op {
     const void *x;            // [T][in]
     void *y;                  // [T][out]
     int out, in;
-    int wg0;                  // first workgroup of this op inside its launch
-    int h_even;               // h starts at a multiple of four bytes
+    int h_aligned;            // h starts at a multiple of 16 bytes (its rows then do too)
+    int pad_;
 };
-// everything a launch needs, passed by value: no table in memory to fetch before the work starts
+// everything a launch needs, passed by value: no table in memory to fetch before the work starts.  What
+// decides which op a workgroup belongs to comes first, in one piece: it costs one trip to the arguments, the op another
 struct Args {
+    int T, out_dtype, nops;
+    int wg0[MAX_STAGE_OPS];   // first workgroup of each op (past the last op: more than there are)
+    int pad_[5];
     Op op[MAX_STAGE_OPS];
-    int nops, T, out_dtype;
 };
 
 // ------------------------------------------------------------------- kernel ---
-// lane N of each row of 16 lanes, in all 16
-template <int N> __device__ __forceinline__ uint32_t row_lane(uint32_t v)
+// eight values in memory order as the pairs (e, e + 4), e = 0..3: the order in which one shift of a
+// native sign word serves both halves of a register
+__device__ __forceinline__ uint4 pair_order(uint4 v)
 {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + N, 0xf, 0xf, true);
+    return make_uint4(__builtin_amdgcn_perm(v.z, v.x, 0x05040100u), __builtin_amdgcn_perm(v.z, v.x, 0x07060302u),
+                      __builtin_amdgcn_perm(v.w, v.y, 0x05040100u), __builtin_amdgcn_perm(v.w, v.y, 0x07060302u));
 }
-__device__ __forceinline__ uint32_t row_lane(uint32_t v, int n)      // n: constant once the loop around the call is unrolled
+// the same of bf16 values as fp16, halved: a bf16 value up to 1.3e5 stays finite, and the result is doubled
+// again in fp32
+__device__ __forceinline__ uint32_t halved_low(uint32_t a, uint32_t b)
 {
-    switch (n) {
-    case 0: return row_lane<0>(v);
-    case 1: return row_lane<1>(v);
-    case 2: return row_lane<2>(v);
-    case 3: return row_lane<3>(v);
-    case 4: return row_lane<4>(v);
-    case 5: return row_lane<5>(v);
-    case 6: return row_lane<6>(v);
-    case 7: return row_lane<7>(v);
-    case 8: return row_lane<8>(v);
-    case 9: return row_lane<9>(v);
-    case 10: return row_lane<10>(v);
-    case 11: return row_lane<11>(v);
-    case 12: return row_lane<12>(v);
-    case 13: return row_lane<13>(v);
-    case 14: return row_lane<14>(v);
-    default: return row_lane<15>(v);
-    }
-}
-
-// two bf16 activations as a pair of fp16 values, halved: a bf16 value up to 1.3e5 stays finite, and the
-// result is doubled again in fp32
-__device__ __forceinline__ uint32_t half_of_bf16_pair(uint32_t v)
-{
-    const _Float16 lo = (_Float16)(0.5f * __uint_as_float(v << 16)), hi = (_Float16)(0.5f * __uint_as_float(v & 0xffff0000u));
+    const _Float16 lo = (_Float16)(0.5f * __uint_as_float(a << 16)), hi = (_Float16)(0.5f * __uint_as_float(b << 16));
     return (uint32_t)__builtin_bit_cast(unsigned short, lo) | ((uint32_t)__builtin_bit_cast(unsigned short, hi) << 16);
+}
+__device__ __forceinline__ uint32_t halved_high(uint32_t a, uint32_t b) { return halved_low(a >> 16, b >> 16); }
+__device__ __forceinline__ uint4 pair_order_of_bf16(uint4 v)
+{
+    return make_uint4(halved_low(v.x, v.z), halved_high(v.x, v.z), halved_low(v.y, v.w), halved_high(v.y, v.w));
 }
 
 // the 2 K words (word c * K + k: path k, columns 128 c + 32 (lane / 16) ..) of one lane of a sign tile
@@ -127,32 +118,85 @@ template <int K> __device__ __forceinline__ Words<K> load_words(const uint32_t *
     return r;
 }
 
+constexpr int UNIT_COLS = 128, ROW_BYTES = 256;      // columns a wavefront stages at a time; a token's fp16 values of them
+template <int K, int G> __host__ __device__ constexpr int slab_bytes() { return (16 * G + K) * ROW_BYTES; }
+
 // K paths, G groups of 16 tokens, P row tiles per workgroup, BF16: the activations are bfloat16
 template <int K, int G, int P, bool BF16>
-__global__ __launch_bounds__(max_waves(G) * 64, 1) void batch_kernel(const Args args)
+__global__ __launch_bounds__(max_waves(K, G, P) * 64, 1) void batch_kernel(const Args args)
 {
     constexpr bool AHEAD = P * K <= (G == 1 ? 6 : 4) && G <= 2;       // registers for the sign words of the next column tile
-    constexpr int XC = G == 1 && P * K <= 9 ? 2 : 1;                 // column halves whose activations are held at once
-    extern __shared__ __attribute__((aligned(16))) float part[];     // [wavefront][row tile][token][row]
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];    // a slab per wavefront; then [wavefront][row tile][token][row] sums
+    __shared__ __attribute__((aligned(16))) float g_lds[P * K * TILE_ROWS];      // [path][row tile][row]
     const int tid = threadIdx.x, lane = tid & 63, nw = (int)blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, q = lane >> 4;
-    int o = 0;
-    while (o + 1 < args.nops && (int)blockIdx.x >= args.op[o + 1].wg0) ++o;
+    int o = 0, first = 0;
+#pragma unroll
+    for (int i = 1; i < MAX_STAGE_OPS; ++i)
+        if ((int)blockIdx.x >= args.wg0[i]) { o = i; first = args.wg0[i]; }
     const Op &op = args.op[o];
     const int out = op.out, in = op.in, T = args.T;
     const int RT = row_tiles(out), CT = col_tiles(in);
-    const int rt0 = ((int)blockIdx.x - op.wg0) * P;
+    const int rt0 = ((int)blockIdx.x - first) * P;
 
     // the row tiles of this workgroup; one past the end of the matrix reads the last one (not stored)
-    const uint32_t *bits[P];
+    const uint32_t *bits[P];                                   // (uniform: the lane's offset is added at the load)
 #pragma unroll
-    for (int p = 0; p < P; ++p) bits[p] = op.bits + (size_t)min(rt0 + p, RT - 1) * CT * tile_words(K) + lane * 2 * K;
+    for (int p = 0; p < P; ++p) bits[p] = op.bits + (size_t)min(rt0 + p, RT - 1) * CT * tile_words(K);
+    const uint32_t lane_words = (uint32_t)lane * 2u * K;
 
     Words<K> w[P];
     if (wave < CT)
 #pragma unroll
-        for (int p = 0; p < P; ++p) w[p] = load_words<K>(bits[p] + (size_t)wave * tile_words(K));
+        for (int p = 0; p < P; ++p) w[p] = load_words<K>(bits[p] + (size_t)wave * tile_words(K) + lane_words);
+
+    // ---- staging.  A load instruction fetches 256 contiguous bytes of four tokens (a token per 16 lanes: 16
+    // chunks of eight columns), so it touches eight lines; fetched in operand order it would touch 32 and
+    // the address unit would bound the kernel.  Chunk 4 q + s (columns 32 q + 8 s ..) of a row goes to position
+    // (4 s + q) ^ (row % 16) of the wavefront's own slab: neither these writes nor the operand reads collide
+    const int ch = lane & 15, row4 = lane >> 4, pos = (ch & 3) * 4 + (ch >> 2);
+    uint8_t *const slab = lds + (size_t)wave * slab_bytes<K, G>();
+    uint32_t x_off[4 * G];
+#pragma unroll
+    for (int i = 0; i < 4 * G; ++i) x_off[i] = (uint32_t)min(4 * i + row4, T - 1) * (uint32_t)in + 8u * (uint32_t)ch;
+    uint4 xs[4 * G], hs;
+    auto request = [&](int j0) {
+        const bool real = j0 + 8 * ch < in;                    // in % 32 == 0: all eight columns or none
+        const uint16_t *const x = static_cast<const uint16_t *>(op.x) + j0;
+#pragma unroll
+        for (int i = 0; i < 4 * G; ++i) {
+            xs[i] = make_uint4(0u, 0u, 0u, 0u);
+            if (4 * i < T && real) xs[i] = *reinterpret_cast<const uint4 *>(x + x_off[i]);       // (rows of no token are not looked at)
+        }
+        hs = make_uint4(0u, 0u, 0u, 0u);
+        if (row4 < K && real) {
+            const uint16_t *const h = op.h + (size_t)row4 * in + j0 + 8 * ch;
+            if (op.h_aligned) hs = *reinterpret_cast<const uint4 *>(h);
+            else                                               // the scales need only be 2-byte aligned
+                hs = make_uint4((uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16,
+                                (uint32_t)h[4] | (uint32_t)h[5] << 16, (uint32_t)h[6] | (uint32_t)h[7] << 16);
+        }
+    };
+    auto put = [&]() {
+#pragma unroll
+        for (int i = 0; i < 4 * G; ++i) {
+            const int row = 4 * i + row4;
+            if (4 * i < T) *reinterpret_cast<uint4 *>(slab + row * ROW_BYTES + ((pos ^ (row & 15)) * 16)) = BF16 ? pair_order_of_bf16(xs[i]) : pair_order(xs[i]);
+        }
+        if (row4 < K) *reinterpret_cast<uint4 *>(slab + (16 * G + row4) * ROW_BYTES + pos * 16) = pair_order(hs);
+        __builtin_amdgcn_wave_barrier();
+    };
+    if (wave < CT) request(wave * TILE_COLS);
+    // output scales, asked for now, shared through LDS when the sums are there
+    constexpr int GV = (P * K * TILE_ROWS + 63) / 64;            // (a workgroup may have one wavefront only)
+    uint16_t gval[GV];
+#pragma unroll
+    for (int i = 0; i < GV; ++i) {
+        const int at = tid + i * (int)blockDim.x, row = min(rt0 * TILE_ROWS + at % (P * TILE_ROWS), out - 1), k = min(at / (P * TILE_ROWS), K - 1);
+        gval[i] = 0;
+        if ((int)blockDim.x * i < P * K * TILE_ROWS) gval[i] = op.g[(size_t)k * out + row];
+    }
     v4f acc[P][K][G];
 #pragma unroll
     for (int p = 0; p < P; ++p)
@@ -161,102 +205,66 @@ __global__ __launch_bounds__(max_waves(G) * 64, 1) void batch_kernel(const Args 
 #pragma unroll
             for (int g = 0; g < G; ++g) acc[p][k][g] = (v4f){0.f, 0.f, 0.f, 0.f};
 
-    // columns of this lane: 32 consecutive ones per half of a column tile, all of them inside the
-    // matrix or none (in % 32 == 0); lane r of a row of 16 feeds token r
-    const uint16_t *xrow[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-        xrow[g] = static_cast<const uint16_t *>(op.x) + (size_t)min(16 * g + r, T - 1) * in + 32 * q;
-
+    const int x_addr = r * ROW_BYTES + ((q ^ r) * 16), h_addr = 16 * G * ROW_BYTES + q * 16;
     for (int ct = wave; ct < CT; ct += nw) {
-        const int j0 = ct * TILE_COLS;
-        // scales: lane r of a row of 16 holds the pair of columns 2 r, 2 r + 1 of the row's 32
-        uint32_t hw[2][K];
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const bool real = j0 + 128 * c + 32 * q < in;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const uint16_t *hp = op.h + (size_t)k * in + (real ? j0 + 128 * c + 32 * q + 2 * r : 0);
-                uint32_t v;
-                if (op.h_even) v = *reinterpret_cast<const uint32_t *>(hp);
-                else v = (uint32_t)hp[0] | ((uint32_t)hp[1] << 16);      // the scales need only be 2-byte aligned
-                hw[c][k] = real ? v : 0u;
-            }
-        }
-        uint4 x[XC][4][G];
-        auto load_x = [&](int c) {
-            const bool real = j0 + 128 * c + 32 * q < in;
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    x[c % XC][s][g] = make_uint4(0u, 0u, 0u, 0u);
-                    if (real) x[c % XC][s][g] = *reinterpret_cast<const uint4 *>(xrow[g] + j0 + 128 * c + 8 * s);
-                }
-        };
-        load_x(0);
-        if constexpr (XC == 2) load_x(1);
         Words<K> next[P];
         if (AHEAD && ct + nw < CT)
 #pragma unroll
-            for (int p = 0; p < P; ++p) next[p] = load_words<K>(bits[p] + (size_t)(ct + nw) * tile_words(K));
+            for (int p = 0; p < P; ++p) next[p] = load_words<K>(bits[p] + (size_t)(ct + nw) * tile_words(K) + lane_words);
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            if (XC == 1 && c == 1) load_x(1);
+            put();
+            if (c == 0) request(ct * TILE_COLS + UNIT_COLS);
+            else if (ct + nw < CT) request((ct + nw) * TILE_COLS);
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 v8h b[G];
+                uint4 hv[K];
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    uint4 v = x[c % XC][s][g];
-                    if constexpr (BF16) v = make_uint4(half_of_bf16_pair(v.x), half_of_bf16_pair(v.y), half_of_bf16_pair(v.z), half_of_bf16_pair(v.w));
-                    b[g] = __builtin_bit_cast(v8h, v);
-                }
+                for (int k = 0; k < K; ++k) hv[k] = *reinterpret_cast<const uint4 *>(slab + h_addr + k * ROW_BYTES + s * 64);
 #pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    uint32_t hp[4];
+                for (int g = 0; g < G; ++g) b[g] = *reinterpret_cast<const v8h *>(slab + (x_addr ^ (s * 64)) + g * 16 * ROW_BYTES);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) hp[j] = row_lane(hw[c][k], 4 * s + j);
+                for (int k = 0; k < K; ++k)
 #pragma unroll
                     for (int p = 0; p < P; ++p) {
-                        // element e of the lane's eight is column 8 s + e: native bit 4 e + s.  Shifted by
-                        // 7 - s (3 - s) bit 8 j + s (8 j + 4 + s), of element 2 j (2 j + 1), is the
-                        // top of byte j; a permute brings the two bytes to the tops of the halves
-                        const uint32_t even = w[p].w[c * K + k] << (7 - s), odd = w[p].w[c * K + k] << (3 - s);
+                        // pair (e, e + 4) of the lane's eight columns 8 s ..: native bits 4 e + s and 16 more
                         uint4 a;
                         uint32_t *const av = reinterpret_cast<uint32_t *>(&a);
 #pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            av[j] = hp[j] ^ (__builtin_amdgcn_perm(odd, even, (uint32_t)((4 + j) << 24 | j << 8)) & 0x80008000u);
+                        for (int e = 0; e < 4; ++e)
+                            av[e] = reinterpret_cast<const uint32_t *>(&hv[k])[e] ^ ((w[p].w[c * K + k] << (15 - 4 * e - s)) & 0x80008000u);
                         const v8h av8 = __builtin_bit_cast(v8h, a);
 #pragma unroll
                         for (int g = 0; g < G; ++g) acc[p][k][g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av8, b[g], acc[p][k][g], 0, 0, 0);
                     }
-                }
+                if (P * K > 4) __builtin_amdgcn_sched_barrier(0);        // operands of one contraction at a time (registers)
             }
+            __builtin_amdgcn_wave_barrier();
         }
         if (AHEAD) {
 #pragma unroll
             for (int p = 0; p < P; ++p) w[p] = next[p];
         } else if (ct + nw < CT) {
 #pragma unroll
-            for (int p = 0; p < P; ++p) w[p] = load_words<K>(bits[p] + (size_t)(ct + nw) * tile_words(K));
+            for (int p = 0; p < P; ++p) w[p] = load_words<K>(bits[p] + (size_t)(ct + nw) * tile_words(K) + lane_words);
         }
     }
+#pragma unroll
+    for (int i = 0; i < GV; ++i) {
+        const int at = tid + i * (int)blockDim.x;
+        if (at < P * K * TILE_ROWS) g_lds[at] = __half2float(__ushort_as_half(gval[i])) * (BF16 ? 2.f : 1.f);
+    }
+    __syncthreads();                                           // the slabs have been read, too: the sums take their place
+    float *const part = reinterpret_cast<float *>(lds);
 
     // ---- partial outputs of this wavefront: path sum with the output scales (Section 4.1).  Lane
     // (r, q) holds token r, rows 4 q .. 4 q + 3 of the row tile.
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-        float gq[K][4];
+        v4f gq[K];
 #pragma unroll
-        for (int k = 0; k < K; ++k)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int row = min((rt0 + p) * TILE_ROWS + 4 * q + i, out - 1);
-                gq[k][i] = __half2float(__ushort_as_half(op.g[(size_t)k * out + row])) * (BF16 ? 2.f : 1.f);
-            }
+        for (int k = 0; k < K; ++k) gq[k] = *reinterpret_cast<const v4f *>(&g_lds[(k * P + p) * TILE_ROWS + 4 * q]);
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             v4f v = {0.f, 0.f, 0.f, 0.f};
@@ -301,8 +309,8 @@ static int row_tiles_per_wg(const int *RT, int nops, int K, int G)
 template <int K, int G, int P, bool BF16>
 static int launch_form(const Args &args, int groups, int nw, hipStream_t stream)
 {
-    constexpr int lds_max = max_waves(G) * P * G * 1024;
-    if (lds_max > 64 * 1024) {
+    constexpr int per_wave = std::max(slab_bytes<K, G>(), P * G * 1024), lds_max = max_waves(K, G, P) * per_wave;
+    if (lds_max + P * K * TILE_ROWS * (int)sizeof(float) > 64 * 1024) {
         static std::atomic<bool> allowed[64];
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return RB_ERR_HIP;
@@ -313,7 +321,7 @@ static int launch_form(const Args &args, int groups, int nw, hipStream_t stream)
             allowed[dev].store(true);
         }
     }
-    hipLaunchKernelGGL((batch_kernel<K, G, P, BF16>), dim3((unsigned)groups), dim3((unsigned)(nw * 64)), nw * P * G * 1024, stream, args);
+    hipLaunchKernelGGL((batch_kernel<K, G, P, BF16>), dim3((unsigned)groups), dim3((unsigned)(nw * 64)), nw * per_wave, stream, args);
     return RB_OK;
 }
 
@@ -340,18 +348,17 @@ static Shape shape_of(Args &args, int K)
     for (int i = 0; i < args.nops; ++i) {
         RT[i] = row_tiles(args.op[i].out);
         CT = std::max(CT, col_tiles(args.op[i].in));
-        args.op[i].h_even = ((uintptr_t)args.op[i].h & 3) == 0;
     }
     Shape s;
     s.K = K;
     const int G = token_groups(args.T);
     s.P = row_tiles_per_wg(RT, args.nops, K, G);
     s.groups = 0;
-    for (int i = 0; i < args.nops; ++i) {
-        args.op[i].wg0 = s.groups;
-        s.groups += (RT[i] + s.P - 1) / s.P;
+    for (int i = 0; i < MAX_STAGE_OPS; ++i) {
+        args.wg0[i] = i < args.nops ? s.groups : INT_MAX;
+        if (i < args.nops) s.groups += (RT[i] + s.P - 1) / s.P;
     }
-    s.nw = std::min(CT, max_waves(G));      // a wavefront takes whole column tiles
+    s.nw = std::min(CT, max_waves(K, G, s.P));      // a wavefront takes whole column tiles
     return s;
 }
 
@@ -374,7 +381,7 @@ static Op make_op(const rb_layer &L, const void *x, void *y)
     o.g = L.g; o.h = L.h;
     o.x = x; o.y = y;
     o.out = L.out; o.in = L.in;
-    o.wg0 = 0; o.h_even = 0;
+    o.h_aligned = ((uintptr_t)L.h & 15) == 0; o.pad_ = 0;
     return o;
 }
 
@@ -382,7 +389,7 @@ bool call_supported(const rb_layer *L, int T) { return (L->K == 2 || L->K == 3) 
 
 int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, hipStream_t stream)
 {
-    Args args;
+    Args args = {};
     args.nops = 1; args.T = T; args.out_dtype = out_dtype;
     args.op[0] = make_op(*L, X, Y);
     const Shape s = shape_of(args, L->K);
@@ -421,7 +428,7 @@ int prepare_plan(const rb_layer *layers, const rb_stack_op *sops, int n_ops, uin
     // launches: runs of consecutive ops of one K that neither read nor overwrite each other
     auto pr = std::make_shared<Prepared>();
     for (int op0 = 0; op0 < n_ops;) {
-        Args args;
+        Args args = {};
         args.nops = 0; args.T = T; args.out_dtype = RB_F16;
         const int K = layers[sops[op0].layer].K;
         for (int n = op0; n < n_ops && args.nops < MAX_STAGE_OPS; ++n) {

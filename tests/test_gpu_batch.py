@@ -8,7 +8,7 @@ import torch
 import oracle
 import synth
 import paper_2602_05367_amd as rb
-from helpers import TOL, to_device_layer, random_layer
+from helpers import TOL, to_device_layer, random_layer, bf16_bits, max_rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -294,3 +294,34 @@ def test_few_token_calls_element_by_element(K, out, inn, T, bf16):
         size += (np.abs(X.astype(np.float64)) @ np.abs(h[k].astype(np.float64)))[:, None] * np.abs(g[k].astype(np.float64))[None, :]
     err = np.abs(Y.cpu().numpy().astype(np.float64) - ref)
     assert np.all(err <= (K * inn + 8) * 2.0 ** -23 * size), float((err / size).max())
+
+
+@pytest.mark.parametrize("K", [2, 3])
+@pytest.mark.parametrize("out,inn,T,act,shift", [
+    (16, 32, 6, "f16", 0), (130, 160, 13, "bf16", 1), (1000, 2080, 17, "f16", 1), (4099, 288, 33, "bf16", 0), (70, 4128, 64, "f16", 0),
+    (9000, 544, 9, "f16", 0)])
+def test_few_token_staging_edges(K, out, inn, T, act, shift):
+    """Staged activations of the few-token kernel: token counts that are no multiple of the four a load takes, half
+    column tiles, one wavefront per workgroup, two and four token groups, several row tiles per workgroup, scales at an odd
+    multiple of two bytes.  Products are exact, so fp32 results are held to 1e-5."""
+    rng = synth.child_rng(5, 130, K, out, inn, T)
+    signs, g, h = random_layer(rng, K, out, inn)
+    g = g.copy(); h = h.copy()
+    g[1, ::6] *= -1; h[0, ::3] *= -1; h[1, 5] = 0
+    X = synth.outlier_activations(rng, T, inn)
+    print(f"few tokens K={K} out={out} in={inn} T={T} {act} shift={shift}", flush=True)
+    L = to_device_layer(signs, g, h)
+    if shift:
+        store = torch.zeros(K * inn + shift, dtype=torch.float16, device="cuda")
+        store[shift:] = L.h.flatten()
+        L.h = store[shift:].view(K, inn)
+    Xd = torch.from_numpy(X).cuda()
+    if act == "bf16":
+        Xd = Xd.to(torch.bfloat16)
+        X = oracle.bf16_bits_to_f64(bf16_bits(Xd.cpu())).reshape(T, inn)
+    Y = torch.full((T + 1, out), 7.0, dtype=torch.float32, device="cuda")
+    rb.rb_linear_gemm(L, Xd, Y=Y[:T])
+    torch.cuda.synchronize()
+    assert rb.rb_last_path() == rb.RB_PATH_GEMM
+    assert torch.all(Y[T] == 7.0)
+    assert max_rel_l2(Y[:T], oracle.forward(signs, g, h, X)) <= 1e-5
