@@ -27,16 +27,12 @@ namespace rb {
 namespace train {
 
 constexpr int ROW_SLICE = 64;          // rows one workgroup of the column reduction walks
-constexpr int COUPLE_CHUNK = 1024;     // columns one wavefront of the coupling kernel walks
+constexpr int COUPLE_CHUNK = 512, COUPLE_ROWS = 4;      // columns and rows one wavefront of the coupling kernel takes
 
 // ------------------------------------------------------------------ couple ---
-__global__ __launch_bounds__(256) void zero_kernel(uint32_t *p, size_t n)
-{
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = 0u;
-}
-
-// One wavefront per row and chunk of COUPLE_CHUNK columns.  A lane takes four consecutive columns
+// A workgroup takes one row tile (16 rows, four wavefronts of COUPLE_ROWS) and COUPLE_CHUNK columns: its native tiles are put
+// together in LDS and stored in whole lines, padding included (zero bits: +1).  What a wavefront's rows share of
+// the columns (h, converted to fp32) is fetched once.  A lane takes four consecutive columns
 // at a time (one 16-byte load of W; the chunk's loads are all requested before the first is used),
 // so a step of the wavefront covers 256 columns and eight lanes hold one sign word between them:
 // lane i of the eight has columns 4 i .. 4 i + 3 of the word, bits 4 i + j of the canonical word
@@ -44,34 +40,46 @@ __global__ __launch_bounds__(256) void zero_kernel(uint32_t *p, size_t n)
 // bit 4 e + s is column 8 s + e); each lane shifts its four bits into place in both and an OR over
 // the eight lanes gives the words.  The residual is fp32 with one rounding for g * h and one for
 // the subtraction, the arithmetic the definition fixes (the sign of the product is exact).
+// Bound by the read of W and, close behind, by vector instructions (some 35 per four weights and path).
+// 4096 x 11008, two paths: 55 us (74 with one row per wavefront, native words stored one by one
+// and zeroed before).
+template <int K>
 __global__ __launch_bounds__(256) void couple_kernel(const float *__restrict__ W, const __half *__restrict__ g,
-                                                     const __half *__restrict__ h, int K, int out, int in,
+                                                     const __half *__restrict__ h, int out, int in,
                                                      uint32_t *__restrict__ packed, uint32_t *__restrict__ native,
                                                      float *__restrict__ residual)
 {
+    constexpr int STEPS = COUPLE_CHUNK / 256, R = COUPLE_ROWS;
     const int lane = threadIdx.x & 63;
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= out) return;
+    const int tile_row0 = (int)(threadIdx.x >> 6) * R, row0 = blockIdx.x * TILE_ROWS + tile_row0;
+    static_assert(4 * R == TILE_ROWS && COUPLE_CHUNK % TILE_COLS == 0, "whole sign tiles per workgroup");
+    __shared__ __attribute__((aligned(16))) uint32_t tiles[STEPS * tile_words(K)];
     const int W32 = in / 32, CT = col_tiles(in);
-    float gr[RB_MAX_K];
-    for (int k = 0; k < K; ++k) gr[k] = __half2float(g[(size_t)k * out + row]);
+    float gr[R][K];
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+#pragma unroll
+        for (int k = 0; k < K; ++k) gr[u][k] = __half2float(g[(size_t)k * out + min(row0 + u, out - 1)]);
     const int chunk0 = blockIdx.y * COUPLE_CHUNK;
-    constexpr int STEPS = COUPLE_CHUNK / 256;
-    float4 wv[STEPS];
+    float4 wv[STEPS][R];
 #pragma unroll
     for (int i = 0; i < STEPS; ++i) {
         const int c = chunk0 + 256 * i + 4 * lane;
-        wv[i] = c < in ? *reinterpret_cast<const float4 *>(W + (size_t)row * in + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int u = 0; u < R; ++u)                            // rows past the end: the last one, not stored
+            wv[i][u] = c < in ? *reinterpret_cast<const float4 *>(W + (size_t)min(row0 + u, out - 1) * in + c) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
     for (int i = 0; i < STEPS; ++i) {
         const int c0 = chunk0 + 256 * i;
-        if (c0 >= in) break;
         const int c = c0 + 4 * lane;
         const bool real = c < in;                              // in % 32 == 0: all four columns or none
-        float r[4] = {wv[i].x, wv[i].y, wv[i].z, wv[i].w};
         const int i8 = lane & 7;
         const int w = (c0 >> 5) + (lane >> 3);                 // the word this group of eight lanes holds
+        float r[R][4];
+#pragma unroll
+        for (int u = 0; u < R; ++u) { r[u][0] = wv[i][u].x; r[u][1] = wv[i][u].y; r[u][2] = wv[i][u].z; r[u][3] = wv[i][u].w; }
+#pragma unroll
         for (int k = 0; k < K; ++k) {
             float hv[4] = {0.f, 0.f, 0.f, 0.f};
             if (real) {
@@ -81,27 +89,39 @@ __global__ __launch_bounds__(256) void couple_kernel(const float *__restrict__ W
                 hv[2] = __half2float(__ushort_as_half((unsigned short)(hb.y & 0xffffu)));
                 hv[3] = __half2float(__ushort_as_half((unsigned short)(hb.y >> 16)));
             }
-            uint32_t can = 0, nat = 0;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const bool neg = real && !(r[j] >= 0.f);       // sign(0) = +1; columns past the end read as +1
-                const float prod = __fmul_rn(gr[k], hv[j]);
-                r[j] = neg ? __fadd_rn(r[j], prod) : __fsub_rn(r[j], prod);
-                can |= neg ? 1u << j : 0u;
-                nat |= neg ? 1u << (4 * j) : 0u;
-            }
-            const uint32_t word = or_over_8(can << (4 * i8));
-            const uint32_t nword = or_over_8(nat << (16 * (i8 & 1) + (i8 >> 1)));
-            if (i8 == 0 && w < W32) {
-                if (packed) packed[((size_t)k * out + row) * W32 + w] = word;
-                if (native) {
-                    const int rt = row / TILE_ROWS, ct = w / 8, cc = (w % 8) / 4, q = w % 4;
-                    native[((size_t)rt * CT + ct) * tile_words(K) + lane_word((row % TILE_ROWS) + 16 * q, cc, k, K)] = nword;
+            for (int u = 0; u < R; ++u) {
+                uint32_t can = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    // sign(0) = +1; columns past the end (zero times h) read as +1 unless h is, which `real` settles below
+                    const bool neg = !(r[u][j] >= 0.f);
+                    const float prod = __fmul_rn(gr[u][k], hv[j]);
+                    r[u][j] = __fsub_rn(r[u][j], neg ? -prod : prod);
+                    can |= neg ? 1u << j : 0u;
+                }
+                const int row = row0 + u;
+                if (!real || row >= out) can = 0;
+                const uint32_t nat = (can | can << 3 | can << 6 | can << 9) & 0x1111u;
+                const uint32_t word = or_over_8(can << (4 * i8));
+                const uint32_t nword = or_over_8(nat << (16 * (i8 & 1) + (i8 >> 1)));
+                if (i8 == 0) {
+                    if (packed && w < W32 && row < out) packed[((size_t)k * out + row) * W32 + w] = word;
+                    const int cc = (w % 8) / 4, q = w % 4;
+                    tiles[i * tile_words(K) + lane_word(tile_row0 + u + 16 * q, cc, k, K)] = nword;
                 }
             }
         }
-        if (residual && real) *reinterpret_cast<float4 *>(residual + (size_t)row * in + c) = make_float4(r[0], r[1], r[2], r[3]);
+        if (residual && real)
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+                if (row0 + u < out) *reinterpret_cast<float4 *>(residual + (size_t)(row0 + u) * in + c) = make_float4(r[u][0], r[u][1], r[u][2], r[u][3]);
     }
+    if (!native) return;
+    __syncthreads();
+    const int ct0 = chunk0 / TILE_COLS, words = min(STEPS, CT - ct0) * tile_words(K);
+    uint32_t *const dst = native + ((size_t)blockIdx.x * CT + ct0) * tile_words(K);      // 4-byte aligned at least
+    for (int i = threadIdx.x; i < words; i += 256) dst[i] = tiles[i];
 }
 
 // --------------------------------------------------------------- gradients ---
@@ -350,16 +370,14 @@ extern "C" int rb_couple(const float *W, const uint16_t *g, const uint16_t *h, i
     if (((uintptr_t)W | (uintptr_t)residual) & 15) return RB_ERR_ALIGN;
     if ((uintptr_t)h & 7) return RB_ERR_ALIGN;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
-    if (native) {
-        // rows and columns of padding read as +1 (bit 0); a kernel, not a memset, so that a caller may capture the call
-        const size_t words = rb_native_bytes(K, out, in) / 4;
-        hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, stream,
-                           static_cast<uint32_t *>(native), words);
-    }
-    hipLaunchKernelGGL(couple_kernel, dim3((unsigned)((out + 3) / 4), (unsigned)((in + COUPLE_CHUNK - 1) / COUPLE_CHUNK)),
-                       dim3(256), 0, stream, W,
-                       reinterpret_cast<const __half *>(g), reinterpret_cast<const __half *>(h), K, out, in, packed,
-                       static_cast<uint32_t *>(native), residual);
+    const dim3 grid((unsigned)rb::row_tiles(out), (unsigned)((in + COUPLE_CHUNK - 1) / COUPLE_CHUNK));
+    auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, W, reinterpret_cast<const __half *>(g),
+                           reinterpret_cast<const __half *>(h), out, in, packed, static_cast<uint32_t *>(native), residual);
+    };
+    if (K == 1) run(couple_kernel<1>);
+    else if (K == 2) run(couple_kernel<2>);
+    else run(couple_kernel<3>);
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;
 }
 
