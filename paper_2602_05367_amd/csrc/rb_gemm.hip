@@ -50,6 +50,7 @@ namespace gemm {
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef float v2f __attribute__((ext_vector_type(2)));
 
 constexpr int WAVES = 8, MB = 2;                 // wavefronts of a workgroup, blocks of 32 rows of a wavefront
 constexpr int STEP_COLS = 128, ROW_BYTES = 256;  // columns of a step; a token's fp16 values of them
@@ -77,12 +78,18 @@ __device__ __forceinline__ uint4 pair_order(uint4 v)
     return make_uint4(__builtin_amdgcn_perm(v.z, v.x, 0x05040100u), __builtin_amdgcn_perm(v.z, v.x, 0x07060302u),
                       __builtin_amdgcn_perm(v.w, v.y, 0x05040100u), __builtin_amdgcn_perm(v.w, v.y, 0x07060302u));
 }
-__device__ __forceinline__ _Float16 low_bf16(uint32_t v) { return (_Float16)__uint_as_float(v << 16); }
-__device__ __forceinline__ _Float16 high_bf16(uint32_t v) { return (_Float16)__uint_as_float(v & 0xffff0000u); }
+// (as vectors of two: one conversion instruction per pair)
+__device__ __forceinline__ uint32_t low_bf16(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f){__uint_as_float(a << 16), __uint_as_float(b << 16)}, v2h));
+}
+__device__ __forceinline__ uint32_t high_bf16(uint32_t a, uint32_t b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f){__uint_as_float(a & 0xffff0000u), __uint_as_float(b & 0xffff0000u)}, v2h));
+}
 __device__ __forceinline__ uint4 pair_order_of_bf16(uint4 v)
 {
-    return make_uint4(pack_halves(low_bf16(v.x), low_bf16(v.z)), pack_halves(high_bf16(v.x), high_bf16(v.z)),
-                      pack_halves(low_bf16(v.y), low_bf16(v.w)), pack_halves(high_bf16(v.y), high_bf16(v.w)));
+    return make_uint4(low_bf16(v.x, v.z), high_bf16(v.x, v.z), low_bf16(v.y, v.w), high_bf16(v.y, v.w));
 }
 __device__ __forceinline__ float abs_max8(uint4 v)
 {
