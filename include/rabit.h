@@ -109,7 +109,9 @@ int rb_linear_gemv(const rb_layer *L, const uint16_t *x, uint16_t *y,
  * effective weight W_hat = sum_k g_k (.) B_k (.) h_k (the form Alg. 2 gives for
  * batched inputs), which the kernel builds in fp16 registers from the packed
  * signs (two roundings per weight, a few 1e-4 relative on the output; fp32
- * accumulation).  Beyond 64 tokens the workspace is used only when Y overlaps X.
+ * accumulation).  Y may overlap X from three tokens on (K = 3: from six; K = 1 and, beyond
+ * 64 tokens, in >= 2^22: never): the input is then moved to the workspace first, which
+ * is all that the workspace is used for at three tokens and more.
  */
 int rb_linear_gemm(const rb_layer *L, const void *X, void *Y, int T,
                    int act_dtype, int out_dtype,

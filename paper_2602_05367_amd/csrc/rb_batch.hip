@@ -387,8 +387,15 @@ static Op make_op(const rb_layer &L, const void *x, void *y)
 
 bool call_supported(const rb_layer *L, int T) { return (L->K == 2 || L->K == 3) && T >= 1 && T <= CALL_MAX_T && L->in % 32 == 0; }
 
-int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, hipStream_t stream)
+int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
+                size_t workspace_bytes, hipStream_t stream)
 {
+    // (one and two tokens: nothing is asked for, and the output must not overlap the input)
+    if (T > 2 && overlap(X, input_bytes(L, T), Y, output_bytes(L, T, out_dtype))) {
+        if (!workspace || workspace_bytes < aside_bytes(L, T)) return RB_ERR_WORKSPACE;
+        copy_aside(X, workspace, input_bytes(L, T), stream);
+        X = workspace;
+    }
     Args args = {};
     args.nops = 1; args.T = T; args.out_dtype = out_dtype;
     args.op[0] = make_op(*L, X, Y);

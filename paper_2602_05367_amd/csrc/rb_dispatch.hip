@@ -49,19 +49,33 @@ bool single_gemm_applies(const rb_layer *L, int T)
     return T > batch::CALL_MAX_T && gemm::supported(L, T);
 }
 
+__global__ __launch_bounds__(256) static void copy_kernel(const uint4 *__restrict__ from, uint4 *__restrict__ to, size_t n)
+{
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) to[i] = from[i];
+}
+void copy_aside(const void *X, void *to, size_t bytes, hipStream_t stream)
+{
+    const size_t n = bytes / 16;
+    hipLaunchKernelGGL(copy_kernel, dim3((unsigned)std::min<size_t>(1024, (n + 255) / 256)), dim3(256), 0, stream,
+                       static_cast<const uint4 *>(X), static_cast<uint4 *>(to), n);
+}
+
+// scratch memory of one call on this layer, whatever its element types
+static size_t call_bytes(const rb_layer *L, int T)
+{
+    if (single_gemm_applies(L, T)) return gemm::workspace_bytes(L, T);
+    return T > 2 && single_few_applies(L, T, RB_F16, RB_F16) ? aside_bytes(L, T) : 0;
+}
+
 size_t workspace_bytes(const rb_layer *layers, int n_layers, int n_ops, int T)
 {
     // one layer, one token: the single-call kernel keeps everything in LDS
     if (n_layers == 1 && n_ops == 1 && T == 1 && gemv1::supported(&layers[0], 1)) return 0;
     if (batch_applies(layers, n_layers, T) && n_ops > 1) return batch::plan_workspace_bytes();
-    if (T > FUSED_MAX_T) {
-        // ops run one after the other on the caller's stream and share the scratch of the GEMM path
-        size_t need = 0;
-        for (int l = 0; l < n_layers; ++l)
-            if (single_gemm_applies(&layers[l], T)) need = std::max(need, gemm::workspace_bytes(&layers[l], T));
-        return need;
-    }
-    return mx::plan_workspace_bytes(layers, n_layers, n_ops, T);
+    // a single call, or ops that run one after the other on the caller's stream and share its scratch
+    size_t need = T > FUSED_MAX_T ? 0 : mx::plan_workspace_bytes(layers, n_layers, n_ops, T);
+    for (int l = 0; l < n_layers; ++l) need = std::max(need, call_bytes(&layers[l], T));
+    return need;
 }
 
 int dispatch_linear(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype,
@@ -81,7 +95,7 @@ int dispatch_linear(const rb_layer *L, const void *X, void *Y, int T, int act_dt
     }
     if (single_few_applies(L, T, act_dtype, out_dtype)) {
         g_last_path = few_path(L, T, act_dtype, out_dtype);
-        return batch::launch_call(L, X, Y, T, act_dtype, out_dtype, stream);
+        return batch::launch_call(L, X, Y, T, act_dtype, out_dtype, workspace, workspace_bytes, stream);
     }
     if (single_gemm_applies(L, T) && workspace && workspace_bytes >= gemm::workspace_bytes(L, T)) {
         g_last_path = RB_PATH_GEMM;

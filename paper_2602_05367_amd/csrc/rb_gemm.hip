@@ -422,12 +422,6 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
     }
 }
 
-// X out of the way of an output that overlaps it
-__global__ __launch_bounds__(256) void copy_kernel(const uint4 *__restrict__ from, uint4 *__restrict__ to, size_t n)
-{
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) to[i] = from[i];
-}
-
 // ------------------------------------------------------------------ host ---
 // The shapes of a workgroup, and what a round of the device takes with each, in microseconds: `fixed` (launch,
 // scales, first loads, sums, stores) and `step` per step of 128 columns per group, for two and for three paths.
@@ -511,10 +505,8 @@ bool supported(const rb_layer *L, int T)
 int launch(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
            hipStream_t stream)
 {
-    const uintptr_t x = (uintptr_t)X, y = (uintptr_t)Y;
-    const size_t x_bytes = (size_t)T * L->in * 2, y_bytes = (size_t)T * L->out * (out_dtype == RB_F32 ? 4 : 2);
-    if (x < y + y_bytes && y < x + x_bytes) {                  // in % 32 == 0: whole 16-byte pieces
-        hipLaunchKernelGGL(copy_kernel, dim3(1024), dim3(256), 0, stream, static_cast<const uint4 *>(X), static_cast<uint4 *>(workspace), x_bytes / 16);
+    if (overlap(X, input_bytes(L, T), Y, output_bytes(L, T, out_dtype))) {
+        copy_aside(X, workspace, input_bytes(L, T), stream);
         X = workspace;
     }
     Args a;

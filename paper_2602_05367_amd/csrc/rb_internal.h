@@ -29,8 +29,19 @@ int dispatch_stack(const rb_layer *layers, int n_layers, const rb_stack_op *ops,
                    uint16_t *const *bufs, int n_bufs, int T, void *workspace, size_t workspace_bytes,
                    hipStream_t stream);
 
+// An output that overlaps its input: workgroups of the matrix-core kernels store rows of Y while others
+// still read X, so the input is moved to scratch memory first (in % 32 == 0: whole 16-byte pieces)
+inline bool overlap(const void *a, size_t na, const void *b, size_t nb)
+{
+    return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+inline size_t input_bytes(const rb_layer *L, int T) { return (size_t)T * L->in * 2; }
+inline size_t output_bytes(const rb_layer *L, int T, int out_dtype) { return (size_t)T * L->out * (out_dtype == RB_F32 ? 4 : 2); }
+inline size_t aside_bytes(const rb_layer *L, int T) { return (input_bytes(L, T) + 255) / 256 * 256; }
+void copy_aside(const void *X, void *to, size_t bytes, hipStream_t stream);
+
 namespace gemm {
-// many-token matrix-core GEMM (K = 2 or 3): workspace holds the input in contraction order
+// many-token matrix-core GEMM (K = 2 or 3): workspace holds the input when the output overlaps it
 bool supported(const rb_layer *L, int T);
 size_t workspace_bytes(const rb_layer *L, int T);
 int launch(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
@@ -50,7 +61,9 @@ namespace batch {
 // take up to CALL_MAX_T tokens, stacks up to 16.
 constexpr int CALL_MAX_T = 64;
 bool call_supported(const rb_layer *L, int T);
-int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, hipStream_t stream);
+// workspace: aside_bytes(L, T) from three tokens on, used when Y overlaps X
+int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
+                size_t workspace_bytes, hipStream_t stream);
 bool layer_supported(const rb_layer *L, int T);
 size_t plan_workspace_bytes();
 int prepare_plan(const rb_layer *layers, const rb_stack_op *ops, int n_ops, uint16_t *const *bufs, int T,

@@ -1,6 +1,6 @@
 // rb_linear_gemm for callers that cannot provide a workspace and must not allocate: the scratch
-// memory of the many-token kernel (a copy of an input that the output overlaps) lives in a device
-// array of this library instead of a caller's buffer.
+// memory (a copy of an input that the output overlaps) lives in a device array of this library instead
+// of a caller's buffer.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -57,10 +57,15 @@ extern "C" int rb_linear_gemm_noalloc(const rb_layer *L, const void *X, void *Y,
     // three paths at up to 32 tokens: the generic kernel serves whatever the many-token kernel's
     // scratch would not fit
     const bool generic_instead = L->K == 3 && T <= 32 && rb::gemm::workspace_bytes(L, T) > SCRATCH_BYTES;
-    // the few-token kernel needs no scratch memory
+    // the few-token kernel: scratch memory only for an input that the output overlaps
     if (rb::single_few_applies(L, T, act_dtype, out_dtype) && !generic_instead) {
+        void *ptr = nullptr;
+        if (T > 2 && rb::overlap(X, rb::input_bytes(L, T), Y, rb::output_bytes(L, T, out_dtype))) {
+            const int rs = scratch_of_current_device(&ptr);
+            if (rs != RB_OK) return rs;
+        }
         rb::set_last_path(RB_PATH_GEMM);
-        return rb::batch::launch_call(L, X, Y, T, act_dtype, out_dtype, stream);
+        return rb::batch::launch_call(L, X, Y, T, act_dtype, out_dtype, ptr, SCRATCH_BYTES, stream);
     }
     if (rb::single_gemm_applies(L, T)) {
         // every byte of scratch memory that is read in a call was written earlier in the same call, so

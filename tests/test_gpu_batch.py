@@ -325,3 +325,41 @@ def test_few_token_staging_edges(K, out, inn, T, act, shift):
     assert rb.rb_last_path() == rb.RB_PATH_GEMM
     assert torch.all(Y[T] == 7.0)
     assert max_rel_l2(Y[:T], oracle.forward(signs, g, h, X)) <= 1e-5
+
+
+def _device_layer(gen, K, out, inn):
+    """Random signs drawn on the device in native order, scales near those of a derived layer."""
+    bits = torch.randint(-2 ** 31, 2 ** 31 - 1, (rb.rb_native_bytes(K, out, inn) // 4,), dtype=torch.int32, device="cuda", generator=gen)
+    g = (torch.randn((K, out), device="cuda", generator=gen).abs() * 0.1 + 0.01).half()
+    h = (torch.randn((K, inn), device="cuda", generator=gen).abs() * 0.1 + 0.01).half()
+    return rb.Layer(bits, g, h, K, out, inn)
+
+
+@pytest.mark.parametrize("K,n,T", [(2, 8224, 3), (2, 8224, 16), (2, 12320, 7), (2, 4128, 33), (2, 8224, 64), (3, 8224, 6), (3, 4128, 16), (3, 4128, 64)])
+def test_few_token_output_over_its_input(K, n, T):
+    """From three tokens on (six with three paths) the output may overlap the input, with more row tiles than one
+    round of workgroups takes: the input is moved aside first, to the workspace or to the library's scratch
+    memory.  The results are those of separate buffers, bit for bit."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(100 * n + T)
+    L = _device_layer(gen, K, n, n)
+    X = torch.randn((T, n), device="cuda", generator=gen).half()
+    want = rb.rb_linear_gemm(L, X)
+    print(f"output over its input K={K} {n}x{n} T={T}", flush=True)
+    for call in (lambda x, y: rb.rb_linear_gemm(L, x, Y=y), lambda x, y: rb.rb_linear_gemm_noalloc(L, x, y)):
+        whole = torch.zeros((3, T, n), dtype=torch.float16, device="cuda")
+        # the same buffer, and an output that starts in the middle of the input
+        for at in (0, T // 2 * n):
+            x, y = whole.flatten()[:T * n].view(T, n), whole.flatten()[at:at + T * n].view(T, n)
+            x.copy_(X)
+            call(x, y)
+            torch.cuda.synchronize()
+            assert torch.equal(y, want)
+        # bfloat16 in, fp32 out, the input inside the output
+        store = torch.zeros(T * n * 4, dtype=torch.uint8, device="cuda")
+        y, x = store.view(torch.float32).view(T, n), store[T * n * 2:].view(torch.bfloat16).view(T, n)
+        x.copy_(X)
+        sep = rb.rb_linear_gemm(L, x.clone(), out_dtype=torch.float32)
+        call(x, y)
+        torch.cuda.synchronize()
+        assert torch.equal(y, sep)

@@ -196,3 +196,11 @@ def test_many_token_workspace_counts_the_shared_last_round():
     assert need(4096, 4096, T) == u(4096) + 2 * T * 4096 * 4
     # 43 x 8 = 344 tiles: one round, then 88 tiles (rows 8192..11007) shared by two
     assert need(11008, 4096, T) == u(4096) + 2 * T * (11008 - 8192) * 4
+
+
+@pytest.mark.parametrize("K,T", [(2, 3), (2, 4), (2, 5), (2, 16), (2, 33), (2, 64), (3, 6), (3, 16), (3, 64), (2, 65), (3, 65)])
+def test_single_calls_ask_for_room_to_move_their_input_aside(K, T):
+    """An output may overlap its input from three tokens on (six with three paths): the workspace holds the input."""
+    for out, inn in ((4096, 4096), (32, 96), (11008, 4128)):
+        L = rb.binding.rb_layer(out, inn, K, 0x1000, 0x2000, 0x3000)
+        assert rb.lib.rb_workspace_bytes(ctypes.byref(L), 1, 1, T) >= T * inn * 2
