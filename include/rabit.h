@@ -144,7 +144,8 @@ size_t rb_noalloc_scratch_bytes(void);
  * 3 <= T <= 16 a stack may run on another kernel or with another order of its
  * sums, and they agree to the accuracy all are held to).  An op may read any buffer written by an
  * earlier op (or never written: stack inputs); dst buffers must be distinct
- * from the op's src.  layers, ops and bufs are host arrays; bufs holds n_bufs
+ * from the op's src (on the few-token kernel buffers of different indices may
+ * overlap in memory: the results are those of the ops run one after the other).  layers, ops and bufs are host arrays; bufs holds n_bufs
  * device pointers.  Activations are expected to be finite: an infinity or NaN
  * in an op's input (an fp16 overflow upstream) makes that op's outputs NaN on
  * the fused kernels, where plain arithmetic could still give an infinity.

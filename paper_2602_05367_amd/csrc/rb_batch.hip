@@ -411,10 +411,16 @@ bool layer_supported(const rb_layer *L, int T)
 }
 
 // A plan lives on the host: the kernel needs nothing in device memory besides the buffers.  The
-// workspace is the name it is run by.
-size_t plan_workspace_bytes() { return 256; }
+// workspace is the name it is run by, and holds the input of an op whose output overlaps it.
+size_t plan_workspace_bytes(const rb_layer *layers, int n_layers, int T)
+{
+    size_t need = 256;
+    for (int l = 0; l < n_layers; ++l) need = std::max(need, aside_bytes(&layers[l], T));
+    return need;
+}
 
-struct Prepared { std::vector<std::pair<Args, Shape>> launches; };
+struct Launch { Args args; Shape shape; const void *aside; size_t aside_bytes; };     // aside: an input to be moved to the workspace first
+struct Prepared { std::vector<Launch> launches; size_t need = 256; };
 static std::mutex g_mutex;
 static std::map<const void *, std::shared_ptr<const Prepared>> g_prepared;
 
@@ -422,7 +428,9 @@ int prepare_plan(const rb_layer *layers, const rb_stack_op *sops, int n_ops, uin
                  void *workspace, size_t workspace_bytes_)
 {
     if (T < 1 || T > STACK_MAX_T) return RB_ERR_UNSUPPORTED;
-    if (!workspace || workspace_bytes_ < plan_workspace_bytes()) return RB_ERR_WORKSPACE;
+    auto pr = std::make_shared<Prepared>();
+    for (int n = 0; n < n_ops; ++n) pr->need = std::max(pr->need, plan_workspace_bytes(&layers[sops[n].layer], 1, T));
+    if (!workspace || workspace_bytes_ < pr->need) return RB_ERR_WORKSPACE;
     // an op that reads another one's output reads all of it
     std::map<int, int> width;
     for (int n = 0; n < n_ops; ++n) {
@@ -432,22 +440,33 @@ int prepare_plan(const rb_layer *layers, const rb_stack_op *sops, int n_ops, uin
         if (it != width.end() && it->second != L.in) return RB_ERR_SHAPE;
         width[sops[n].dst] = L.out;
     }
-    // launches: runs of consecutive ops of one K that neither read nor overwrite each other
-    auto pr = std::make_shared<Prepared>();
+    // launches: runs of consecutive ops of one K that neither read nor overwrite each other.  Memory
+    // decides, not the buffers' indices: two of them may overlap.  An op that overwrites its own input gets a launch of
+    // its own and reads a copy
+    struct Span { const void *at; size_t bytes; };
+    auto src = [&](int n) { return Span{bufs[sops[n].src], input_bytes(&layers[sops[n].layer], T)}; };
+    auto dst = [&](int n) { return Span{bufs[sops[n].dst], output_bytes(&layers[sops[n].layer], T, RB_F16)}; };
+    auto meet = [](Span a, Span b) { return overlap(a.at, a.bytes, b.at, b.bytes); };
     for (int op0 = 0; op0 < n_ops;) {
         Args args = {};
         args.nops = 0; args.T = T; args.out_dtype = RB_F16;
         const int K = layers[sops[op0].layer].K;
         for (int n = op0; n < n_ops && args.nops < MAX_STAGE_OPS; ++n) {
             const rb_layer &L = layers[sops[n].layer];
-            bool conflict = L.K != K;
+            bool conflict = L.K != K || (n > op0 && (meet(src(n), dst(n)) || meet(src(op0), dst(op0))));
             for (int m = op0; m < n; ++m)
-                if (sops[m].dst == sops[n].src || sops[m].dst == sops[n].dst || sops[m].src == sops[n].dst) conflict = true;
+                if (meet(dst(m), src(n)) || meet(dst(m), dst(n)) || meet(src(m), dst(n))) conflict = true;
             if (conflict) break;
             args.op[args.nops++] = make_op(L, bufs[sops[n].src], bufs[sops[n].dst]);
         }
-        const Shape s = shape_of(args, K);
-        pr->launches.emplace_back(args, s);
+        const Shape shape = shape_of(args, K);                 // (numbers the workgroups in args)
+        Launch l = {args, shape, nullptr, 0};
+        if (meet(src(op0), dst(op0))) {
+            l.aside = src(op0).at;
+            l.aside_bytes = src(op0).bytes;
+            l.args.op[0].x = workspace;
+        }
+        pr->launches.push_back(l);
         op0 += args.nops;
     }
     std::lock_guard<std::mutex> lock(g_mutex);
@@ -465,9 +484,10 @@ int launch_plan(void *workspace, size_t workspace_bytes_, hipStream_t stream)
         if (it == g_prepared.end()) return RB_ERR_UNSUPPORTED;
         pr = it->second;
     }
-    if (workspace_bytes_ < plan_workspace_bytes()) return RB_ERR_WORKSPACE;
-    for (const auto &l : pr->launches) {
-        const int rc = launch_shape<false>(l.first, l.second, stream);
+    if (workspace_bytes_ < pr->need) return RB_ERR_WORKSPACE;
+    for (const Launch &l : pr->launches) {
+        if (l.aside) copy_aside(l.aside, workspace, l.aside_bytes, stream);
+        const int rc = launch_shape<false>(l.args, l.shape, stream);
         if (rc != RB_OK) return rc;
     }
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;

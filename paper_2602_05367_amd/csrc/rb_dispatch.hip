@@ -71,7 +71,7 @@ size_t workspace_bytes(const rb_layer *layers, int n_layers, int n_ops, int T)
 {
     // one layer, one token: the single-call kernel keeps everything in LDS
     if (n_layers == 1 && n_ops == 1 && T == 1 && gemv1::supported(&layers[0], 1)) return 0;
-    if (batch_applies(layers, n_layers, T) && n_ops > 1) return batch::plan_workspace_bytes();
+    if (batch_applies(layers, n_layers, T) && n_ops > 1) return batch::plan_workspace_bytes(layers, n_layers, T);
     // a single call, or ops that run one after the other on the caller's stream and share its scratch
     size_t need = T > FUSED_MAX_T ? 0 : mx::plan_workspace_bytes(layers, n_layers, n_ops, T);
     for (int l = 0; l < n_layers; ++l) need = std::max(need, call_bytes(&layers[l], T));

@@ -65,7 +65,7 @@ bool call_supported(const rb_layer *L, int T);
 int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
                 size_t workspace_bytes, hipStream_t stream);
 bool layer_supported(const rb_layer *L, int T);
-size_t plan_workspace_bytes();
+size_t plan_workspace_bytes(const rb_layer *layers, int n_layers, int T);
 int prepare_plan(const rb_layer *layers, const rb_stack_op *ops, int n_ops, uint16_t *const *bufs, int T,
                  void *workspace, size_t workspace_bytes);
 int launch_plan(void *workspace, size_t workspace_bytes, hipStream_t stream);      // RB_ERR_UNSUPPORTED: no plan of this kind

@@ -363,3 +363,38 @@ def test_few_token_output_over_its_input(K, n, T):
         call(x, y)
         torch.cuda.synchronize()
         assert torch.equal(y, sep)
+
+
+@pytest.mark.parametrize("K,T,prepared", [(2, 5, True), (2, 16, False), (3, 2, False), (3, 8, True)])
+def test_stack_buffers_that_overlap_in_memory(K, T, prepared):
+    """Buffers of different indices in one piece of memory: an op over its own input (buffer 1 starts in the
+    middle of buffer 0), an op that reads what an earlier op of the list has written under another index (4 is
+    3's memory), one that overwrites what an earlier op has read (6 is 2's).  Each op's result is that of the
+    ops run one after the other on buffers of their own."""
+    n = 8224
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7 * K + T)
+    layers = [_device_layer(gen, K, n, n) for _ in range(4)]
+    for L in layers:                                           # outputs near RMS 1
+        L.g.mul_(1.0 / (0.0064 * (K * n) ** 0.5))
+    ops = [(0, 0, 1), (1, 2, 3), (2, 4, 5), (3, 5, 6)]
+    pool = torch.zeros((6, T, n), dtype=torch.float16, device="cuda").flatten()
+    at = lambda i: pool[i * T * n // 2:i * T * n // 2 + T * n].view(T, n)
+    bufs = [at(0), at(1), at(4), at(6), at(6), at(8), at(4)]
+    x0, x2 = (torch.randn((T, n), device="cuda", generator=gen).half() for _ in range(2))
+    print(f"overlapping buffers K={K} T={T} prepared={prepared}", flush=True)
+    stack = rb.Stack(layers, ops, bufs, T)
+    if prepared:
+        stack.prepare()
+    for _ in range(2):                                         # (a run leaves other contents behind)
+        bufs[0].copy_(x0)
+        bufs[2].copy_(x2)
+        stack.run_prepared() if prepared else stack.run()
+    torch.cuda.synchronize()
+    assert rb.rb_last_path() == rb.RB_PATH_BATCH
+    stack.forget()
+    y1, y3 = rb.rb_linear_gemm(layers[0], x0), rb.rb_linear_gemm(layers[1], x2)
+    y5 = rb.rb_linear_gemm(layers[2], bufs[3].clone())
+    y6 = rb.rb_linear_gemm(layers[3], bufs[5].clone())
+    for got, want in ((bufs[1], y1), (bufs[3], y3), (bufs[5], y5), (bufs[6], y6)):
+        assert max_rel_l2(got, want.double().cpu().numpy()) <= TOL

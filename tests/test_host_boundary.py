@@ -204,3 +204,11 @@ def test_single_calls_ask_for_room_to_move_their_input_aside(K, T):
     for out, inn in ((4096, 4096), (32, 96), (11008, 4128)):
         L = rb.binding.rb_layer(out, inn, K, 0x1000, 0x2000, 0x3000)
         assert rb.lib.rb_workspace_bytes(ctypes.byref(L), 1, 1, T) >= T * inn * 2
+
+
+@pytest.mark.parametrize("K,T", [(2, 5), (2, 16), (3, 2), (3, 16)])
+def test_few_token_stacks_ask_for_room_to_move_an_input_aside(K, T):
+    """Buffers of a stack may overlap in memory: room for the widest input that an op's output may overwrite."""
+    layers = (rb.binding.rb_layer * 2)(rb.binding.rb_layer(4096, 96, K, 0x1000, 0x2000, 0x3000),
+                                       rb.binding.rb_layer(96, 4128, K, 0x1000, 0x2000, 0x3000))
+    assert rb.lib.rb_workspace_bytes(layers, 2, 3, T) >= T * 4128 * 2
