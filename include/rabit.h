@@ -103,15 +103,19 @@ int rb_linear_gemv(const rb_layer *L, const uint16_t *x, uint16_t *y,
 /*
  * Batched form, T tokens: Y[t] = layer(X[t]).  X device [T][in] of act_dtype
  * (RB_F16 or RB_BF16), Y device [T][out] of out_dtype (RB_F16, RB_BF16, RB_F32).
- * Up to 64 tokens the weights are streamed once for all tokens and every product of
- * scale and activation is exact; larger T runs as a dense
+ * One and two fp16 tokens with fp16 results (K = 2) run on the decode kernels, which hold
+ * h_k (.) x as four 8-bit terms (to 2^-12).  Otherwise up to 64 tokens the weights are
+ * streamed once for all tokens and every product of scale and activation is exact, over
+ * the whole range of either activation type; larger T runs as a dense
  * contraction on the matrix cores, Y = W_hat X with the
  * effective weight W_hat = sum_k g_k (.) B_k (.) h_k (the form Alg. 2 gives for
  * batched inputs), which the kernel builds in fp16 registers from the packed
  * signs (two roundings per weight, a few 1e-4 relative on the output; fp32
- * accumulation).  Y may overlap X from three tokens on (K = 3: from six; K = 1 and, beyond
- * 64 tokens, in >= 2^22: never): the input is then moved to the workspace first, which
- * is all that the workspace is used for at three tokens and more.
+ * accumulation) and with the activations in fp16: bfloat16 ones are infinite there
+ * from 65520 on and lose bits below 2^-17.
+ * Y may overlap X from three tokens on (K = 3: from six; K = 1 and, beyond 64 tokens,
+ * in >= 2^22: never): the input is then moved to the workspace first, which is all that
+ * the workspace is used for at three tokens and more.
  */
 int rb_linear_gemm(const rb_layer *L, const void *X, void *Y, int T,
                    int act_dtype, int out_dtype,

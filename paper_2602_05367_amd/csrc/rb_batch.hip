@@ -5,7 +5,11 @@
 // signs: the left operand of v_mfma_f32_16x16x32_f16 is +-h_k[j] (the stored fp16 scale with the sign
 // bit of the weight put in), the right operand is the fp16 activation itself.  Both are exact, so are
 // their products, and only fp32 sums round; the activation is shared by the paths, nothing about the
-// input is prepared, and an op is one launch.  What bounds it:
+// input is prepared, and an op is one launch.  bfloat16 activations keep their whole range: they go into
+// v_mfma_f32_16x16x32_bf16 as they are, against two left operands, as an fp16 scale is the exact sum of two bf16
+// values (three vector instructions in place of two and twice the matrix instructions; 4096 x 4096 at 16
+// tokens 7.1 us where fp16 takes 5.8, 28672 x 8192 48 where halved fp16 copies of the activations, which
+// overflow from 1.3e5 and lose bits below 2^-16, took 38).  What bounds it:
 //   * a launch of a 4096-wide op moves 4 MB of signs, half a microsecond of HBM time, so it is a
 //     chain of latencies (launch, one trip to memory, the matrix instructions, the sum over the
 //     wavefronts): the compute units are filled and every wavefront asks for all it needs at once, the
@@ -25,7 +29,7 @@
 // order, the output scales fetched at the end: 1.42 and 1.61; bf8 term expansions of the activations in LDS, which
 // this kernel replaced: 2.51 and 3.09); a launch takes 6.3 us (4096 x 4096, one row tile per workgroup) to 16 us
 // (2 x 11008 x 4096, six), of which a dependent launch by itself is 4.7.  Single calls: 4096 x 11008
-// with three paths at 16 tokens 12.7 us, 10999 x 4128 with two at 7 tokens 11.4 us.
+// with three paths at 16 tokens 12.7 us, 10999 x 4128 with two at 7 tokens of bfloat16 13 us.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
@@ -49,6 +53,7 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
 
 constexpr int STACK_MAX_T = 16;        // tokens of a stack
 constexpr int MAX_STAGE_OPS = 8;       // independent ops that share a launch
@@ -56,8 +61,9 @@ constexpr int MAX_STAGE_OPS = 8;       // independent ops that share a launch
 // Wavefronts of a workgroup at most, and row tiles per workgroup: accumulators take 4 P K G
 // registers, sign words 2 P K, staged activations 16 G, of 128 with sixteen wavefronts per compute unit
 // and 256 with eight (two paths, six row tiles, 16 tokens: 28.6 us a launch of 2 x 11008 x 4096 with sixteen, which
-// spills, 16.2 with eight; four row tiles, 8 tokens, 7B chain: the same either way)
-__host__ __device__ constexpr int max_waves(int K, int G, int P) { return G == 1 && P * K <= 8 ? 16 : 8; }
+// spills, 16.2 with eight; four row tiles, 8 tokens, 7B chain: the same either way; bfloat16, two paths, four row
+// tiles, 12304 x 4096 at 5 tokens: 15.0 us with sixteen, which spills, 14.3 with eight)
+__host__ __device__ constexpr int max_waves(int K, int G, int P, bool bf16) { return G == 1 && P * K <= (bf16 ? 6 : 8) ? 16 : 8; }
 __host__ __device__ constexpr bool p_available(int K, int G, int P) { return P == 1 || P * K <= (G == 1 ? 12 : G == 2 ? 6 : 4); }
 
 struct Op {
@@ -87,17 +93,28 @@ __device__ __forceinline__ uint4 pair_order(uint4 v)
     return make_uint4(__builtin_amdgcn_perm(v.z, v.x, 0x05040100u), __builtin_amdgcn_perm(v.z, v.x, 0x07060302u),
                       __builtin_amdgcn_perm(v.w, v.y, 0x05040100u), __builtin_amdgcn_perm(v.w, v.y, 0x07060302u));
 }
-// the same of bf16 values as fp16, halved: a bf16 value up to 1.3e5 stays finite, and the result is doubled
-// again in fp32
-__device__ __forceinline__ uint32_t halved_low(uint32_t a, uint32_t b)
+// an fp16 scale as two bf16 values: the one below it in magnitude and what is left (at most eight bits of
+// eleven, then at most three; or one unit, where the scale itself is a bf16 value).  Their sum is exact,
+// both have the scale's sign, and neither is zero unless the scale is: an infinite activation gives
+// the infinity that its product with the scale is
+__device__ __forceinline__ void split_scale(unsigned short h, uint32_t &high, uint32_t &low)
 {
-    const _Float16 lo = (_Float16)(0.5f * __uint_as_float(a << 16)), hi = (_Float16)(0.5f * __uint_as_float(b << 16));
-    return (uint32_t)__builtin_bit_cast(unsigned short, lo) | ((uint32_t)__builtin_bit_cast(unsigned short, hi) << 16);
+    const float f = __half2float(__ushort_as_half(h));
+    const uint32_t u = __float_as_uint(f);
+    high = (u << 1) != 0u ? (u - 1u) & 0xffff0000u : u;
+    low = __float_as_uint(f - __uint_as_float(high));
 }
-__device__ __forceinline__ uint32_t halved_high(uint32_t a, uint32_t b) { return halved_low(a >> 16, b >> 16); }
-__device__ __forceinline__ uint4 pair_order_of_bf16(uint4 v)
+__device__ __forceinline__ void split_scales(uint4 h, uint4 &high, uint4 &low)
 {
-    return make_uint4(halved_low(v.x, v.z), halved_high(v.x, v.z), halved_low(v.y, v.w), halved_high(v.y, v.w));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t v = reinterpret_cast<const uint32_t *>(&h)[i];
+        uint32_t h0, l0, h1, l1;
+        split_scale((unsigned short)(v & 0xffffu), h0, l0);
+        split_scale((unsigned short)(v >> 16), h1, l1);
+        reinterpret_cast<uint32_t *>(&high)[i] = __builtin_amdgcn_perm(h1, h0, 0x07060302u);
+        reinterpret_cast<uint32_t *>(&low)[i] = __builtin_amdgcn_perm(l1, l0, 0x07060302u);
+    }
 }
 
 // the 2 K words (word c * K + k: path k, columns 128 c + 32 (lane / 16) ..) of one lane of a sign tile
@@ -119,13 +136,16 @@ template <int K> __device__ __forceinline__ Words<K> load_words(const uint32_t *
 }
 
 constexpr int UNIT_COLS = 128, ROW_BYTES = 256;      // columns a wavefront stages at a time; a token's fp16 values of them
-template <int K, int G> __host__ __device__ constexpr int slab_bytes() { return (16 * G + K) * ROW_BYTES; }
+template <bool BF16> constexpr int TERMS = BF16 ? 2 : 1;                           // values that an input scale is the sum of
+template <int K, int G, bool BF16> __host__ __device__ constexpr int slab_bytes() { return (16 * G + K * TERMS<BF16>) * ROW_BYTES; }
 
 // K paths, G groups of 16 tokens, P row tiles per workgroup, BF16: the activations are bfloat16
 template <int K, int G, int P, bool BF16>
-__global__ __launch_bounds__(max_waves(K, G, P) * 64, 1) void batch_kernel(const Args args)
+__global__ __launch_bounds__(max_waves(K, G, P, BF16) * 64, 1) void batch_kernel(const Args args)
 {
-    constexpr bool AHEAD = P * K <= (G == 1 ? 6 : 4) && G <= 2;       // registers for the sign words of the next column tile
+    // registers for the sign words of the next column tile (bf16, 10999 x 4128 at 7 tokens, three row tiles: 13.5 us with
+    // them, which spills, 12.9 without)
+    constexpr bool AHEAD = P * K <= (G == 1 && !BF16 ? 6 : 4) && G <= 2;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];    // a slab per wavefront; then [wavefront][row tile][token][row] sums
     __shared__ __attribute__((aligned(16))) float g_lds[P * K * TILE_ROWS];      // [path][row tile][row]
     const int tid = threadIdx.x, lane = tid & 63, nw = (int)blockDim.x >> 6;
@@ -156,7 +176,7 @@ __global__ __launch_bounds__(max_waves(K, G, P) * 64, 1) void batch_kernel(const
     // the address unit would bound the kernel.  Chunk 4 q + s (columns 32 q + 8 s ..) of a row goes to position
     // (4 s + q) ^ (row % 16) of the wavefront's own slab: neither these writes nor the operand reads collide
     const int ch = lane & 15, row4 = lane >> 4, pos = (ch & 3) * 4 + (ch >> 2);
-    uint8_t *const slab = lds + (size_t)wave * slab_bytes<K, G>();
+    uint8_t *const slab = lds + (size_t)wave * slab_bytes<K, G, BF16>();
     uint32_t x_off[4 * G];
 #pragma unroll
     for (int i = 0; i < 4 * G; ++i) x_off[i] = (uint32_t)min(4 * i + row4, T - 1) * (uint32_t)in + 8u * (uint32_t)ch;
@@ -182,9 +202,14 @@ __global__ __launch_bounds__(max_waves(K, G, P) * 64, 1) void batch_kernel(const
 #pragma unroll
         for (int i = 0; i < 4 * G; ++i) {
             const int row = 4 * i + row4;
-            if (4 * i < T) *reinterpret_cast<uint4 *>(slab + row * ROW_BYTES + ((pos ^ (row & 15)) * 16)) = BF16 ? pair_order_of_bf16(xs[i]) : pair_order(xs[i]);
+            if (4 * i < T) *reinterpret_cast<uint4 *>(slab + row * ROW_BYTES + ((pos ^ (row & 15)) * 16)) = pair_order(xs[i]);
         }
-        if (row4 < K) *reinterpret_cast<uint4 *>(slab + (16 * G + row4) * ROW_BYTES + pos * 16) = pair_order(hs);
+        if (row4 < K) {
+            uint4 v[TERMS<BF16>] = {hs};
+            if constexpr (BF16) split_scales(hs, v[0], v[1]);
+#pragma unroll
+            for (int m = 0; m < TERMS<BF16>; ++m) *reinterpret_cast<uint4 *>(slab + (16 * G + m * K + row4) * ROW_BYTES + pos * 16) = pair_order(v[m]);
+        }
         __builtin_amdgcn_wave_barrier();
     };
     if (wave < CT) request(wave * TILE_COLS);
@@ -218,25 +243,30 @@ __global__ __launch_bounds__(max_waves(K, G, P) * 64, 1) void batch_kernel(const
             else if (ct + nw < CT) request((ct + nw) * TILE_COLS);
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                v8h b[G];
-                uint4 hv[K];
+                v4u b[G];
+                uint4 hv[K][TERMS<BF16>];
 #pragma unroll
-                for (int k = 0; k < K; ++k) hv[k] = *reinterpret_cast<const uint4 *>(slab + h_addr + k * ROW_BYTES + s * 64);
+                for (int k = 0; k < K; ++k)
 #pragma unroll
-                for (int g = 0; g < G; ++g) b[g] = *reinterpret_cast<const v8h *>(slab + (x_addr ^ (s * 64)) + g * 16 * ROW_BYTES);
+                    for (int m = 0; m < TERMS<BF16>; ++m) hv[k][m] = *reinterpret_cast<const uint4 *>(slab + h_addr + (m * K + k) * ROW_BYTES + s * 64);
+#pragma unroll
+                for (int g = 0; g < G; ++g) b[g] = *reinterpret_cast<const v4u *>(slab + (x_addr ^ (s * 64)) + g * 16 * ROW_BYTES);
 #pragma unroll
                 for (int k = 0; k < K; ++k)
 #pragma unroll
                     for (int p = 0; p < P; ++p) {
                         // pair (e, e + 4) of the lane's eight columns 8 s ..: native bits 4 e + s and 16 more
-                        uint4 a;
-                        uint32_t *const av = reinterpret_cast<uint32_t *>(&a);
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            av[e] = reinterpret_cast<const uint32_t *>(&hv[k])[e] ^ ((w[p].w[c * K + k] << (15 - 4 * e - s)) & 0x80008000u);
-                        const v8h av8 = __builtin_bit_cast(v8h, a);
+                        for (int m = 0; m < TERMS<BF16>; ++m) {
+                            v4u a;
 #pragma unroll
-                        for (int g = 0; g < G; ++g) acc[p][k][g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av8, b[g], acc[p][k][g], 0, 0, 0);
+                            for (int e = 0; e < 4; ++e)
+                                a[e] = reinterpret_cast<const uint32_t *>(&hv[k][m])[e] ^ ((w[p].w[c * K + k] << (15 - 4 * e - s)) & 0x80008000u);
+#pragma unroll
+                            for (int g = 0; g < G; ++g)
+                                if constexpr (BF16) acc[p][k][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b[g]), acc[p][k][g], 0, 0, 0);
+                                else acc[p][k][g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b[g]), acc[p][k][g], 0, 0, 0);
+                        }
                     }
                 if (P * K > 4) __builtin_amdgcn_sched_barrier(0);        // operands of one contraction at a time (registers)
             }
@@ -253,7 +283,7 @@ __global__ __launch_bounds__(max_waves(K, G, P) * 64, 1) void batch_kernel(const
 #pragma unroll
     for (int i = 0; i < GV; ++i) {
         const int at = tid + i * (int)blockDim.x;
-        if (at < P * K * TILE_ROWS) g_lds[at] = __half2float(__ushort_as_half(gval[i])) * (BF16 ? 2.f : 1.f);
+        if (at < P * K * TILE_ROWS) g_lds[at] = __half2float(__ushort_as_half(gval[i]));
     }
     __syncthreads();                                           // the slabs have been read, too: the sums take their place
     float *const part = reinterpret_cast<float *>(lds);
@@ -309,7 +339,7 @@ static int row_tiles_per_wg(const int *RT, int nops, int K, int G)
 template <int K, int G, int P, bool BF16>
 static int launch_form(const Args &args, int groups, int nw, hipStream_t stream)
 {
-    constexpr int per_wave = std::max(slab_bytes<K, G>(), P * G * 1024), lds_max = max_waves(K, G, P) * per_wave;
+    constexpr int per_wave = std::max(slab_bytes<K, G, BF16>(), P * G * 1024), lds_max = max_waves(K, G, P, BF16) * per_wave;
     if (lds_max + P * K * TILE_ROWS * (int)sizeof(float) > 64 * 1024) {
         static std::atomic<bool> allowed[64];
         int dev = 0;
@@ -342,7 +372,7 @@ static int token_groups(int T) { return T <= 16 ? 1 : T <= 32 ? 2 : 4; }
 
 // one launch: the ops of `args` (wg0 is filled in here), all of K paths
 struct Shape { int K, P, groups, nw; };
-static Shape shape_of(Args &args, int K)
+static Shape shape_of(Args &args, int K, bool bf16)
 {
     int RT[MAX_STAGE_OPS], CT = 1;
     for (int i = 0; i < args.nops; ++i) {
@@ -358,7 +388,7 @@ static Shape shape_of(Args &args, int K)
         args.wg0[i] = i < args.nops ? s.groups : INT_MAX;
         if (i < args.nops) s.groups += (RT[i] + s.P - 1) / s.P;
     }
-    s.nw = std::min(CT, max_waves(K, G, s.P));      // a wavefront takes whole column tiles
+    s.nw = std::min(CT, max_waves(K, G, s.P, bf16));      // a wavefront takes whole column tiles
     return s;
 }
 
@@ -399,7 +429,7 @@ int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype,
     Args args = {};
     args.nops = 1; args.T = T; args.out_dtype = out_dtype;
     args.op[0] = make_op(*L, X, Y);
-    const Shape s = shape_of(args, L->K);
+    const Shape s = shape_of(args, L->K, act_dtype == RB_BF16);
     const int rc = act_dtype == RB_BF16 ? launch_shape<true>(args, s, stream) : launch_shape<false>(args, s, stream);
     if (rc != RB_OK) return rc;
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;
@@ -459,7 +489,7 @@ int prepare_plan(const rb_layer *layers, const rb_stack_op *sops, int n_ops, uin
             if (conflict) break;
             args.op[args.nops++] = make_op(L, bufs[sops[n].src], bufs[sops[n].dst]);
         }
-        const Shape shape = shape_of(args, K);                 // (numbers the workgroups in args)
+        const Shape shape = shape_of(args, K, false);                 // (numbers the workgroups in args)
         Launch l = {args, shape, nullptr, 0};
         if (meet(src(op0), dst(op0))) {
             l.aside = src(op0).at;

@@ -398,3 +398,50 @@ def test_stack_buffers_that_overlap_in_memory(K, T, prepared):
     y6 = rb.rb_linear_gemm(layers[3], bufs[5].clone())
     for got, want in ((bufs[1], y1), (bufs[3], y3), (bufs[5], y5), (bufs[6], y6)):
         assert max_rel_l2(got, want.double().cpu().numpy()) <= TOL
+
+
+@pytest.mark.parametrize("K,out,inn,T", [(2, 4112, 288, 1), (2, 300, 1056, 2), (2, 4112, 288, 7), (2, 8200, 160, 16), (2, 12304, 160, 5),
+                                         (2, 16390, 96, 9), (2, 300, 544, 18), (2, 4112, 96, 64), (3, 300, 288, 6), (3, 4112, 160, 16),
+                                         (3, 300, 96, 33)])
+@pytest.mark.parametrize("size", [3.0e5, 1.0e30, 2.0 ** -20, 2.0 ** -30, 2.0 ** -80])
+def test_few_token_bf16_over_its_whole_range(K, out, inn, T, size):
+    """bfloat16 activations far beyond fp16's range, every row tile count per workgroup and token group.  An input scale
+    is the exact sum of two bf16 values, so their products with a bf16 activation are exact and only the additions of the
+    2 K in terms, the output scale and the path sum round: |error| <= (2 K in + 8) 2^-23 sum |g h x| (twice the
+    half-ulp bound).  The scales are the ends of fp16's range too: subnormals, zeros, either sign."""
+    rng = synth.child_rng(3, 511, K, out, inn, T)
+    signs, g, h = random_layer(rng, K, out, inn)
+    g = g.copy(); h = h.copy()
+    g[0, ::5] *= -1; h[1, 1::3] *= -1; h[0, 4] = 0; h[1, 9] = -0.0; h[0, 6] = 1.0; h[1, 7] = 65504.0; h[0, 8] = 6.0e-8
+    h[:, ::8] = (h[:, ::8].astype(np.float64) * 1e-3).astype(np.float16)
+    Xd = torch.from_numpy(synth.gaussian_activations(rng, T, inn)).cuda().float().mul(size).to(torch.bfloat16)
+    X = Xd.double().cpu().numpy()
+    print(f"bf16 range K={K} {out}x{inn} T={T} size={size}", flush=True)
+    Y = rb.rb_linear_gemm(to_device_layer(signs, g, h), Xd, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    ref = oracle.forward(signs, g, h, X)
+    bound = np.zeros((T, out))
+    for k in range(K):
+        bound += (np.abs(X) @ np.abs(h[k].astype(np.float64)))[:, None] * np.abs(g[k].astype(np.float64))[None, :]
+    err = np.abs(Y.cpu().numpy().astype(np.float64) - ref)
+    assert np.all(err <= (2 * K * inn + 8) * 2.0 ** -23 * bound), float((err / bound).max())
+
+
+@pytest.mark.parametrize("K,T,act", [(2, 2, "bf16"), (2, 7, "bf16"), (3, 6, "bf16"), (2, 7, "f16")])
+def test_few_token_infinite_activations(K, T, act):
+    """An infinity in one token's input: that token's outputs are what plain arithmetic gives (infinities by the sign of
+    the weight, NaN where a scale is zero or the paths disagree), the other tokens' are finite."""
+    out, inn = 300, 544
+    rng = synth.child_rng(3, 512, K, T)
+    signs, g, h = random_layer(rng, K, out, inn)
+    g = np.abs(g) + np.float16(0.01); h = np.abs(h) + np.float16(0.01)
+    h[:, 40] = np.float16(0.5)                                 # a bf16 value
+    X = synth.gaussian_activations(rng, T, inn)
+    X[1, 40] = np.inf
+    print(f"infinite activation K={K} T={T} {act}", flush=True)
+    Xd = torch.from_numpy(X).cuda().to(torch.bfloat16 if act == "bf16" else torch.float16)
+    Y = rb.rb_linear_gemm(to_device_layer(signs, g, h), Xd, out_dtype=torch.float32).cpu().numpy()
+    paths = signs[:, :, 40].astype(np.float64) * np.inf
+    with np.errstate(invalid="ignore"):
+        np.testing.assert_array_equal(Y[1], paths.sum(axis=0))
+    assert np.all(np.isfinite(np.delete(Y, 1, axis=0)))
