@@ -245,17 +245,18 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
         if (lane == 0) { red[2 * k][wave] = mx_h[k]; red[2 * k + 1][wave] = mx_g[k]; }
     }
     __syncthreads();
-    float S = 0.f, sk[K];
+    // (a path without a scale in these rows adds nothing to them and has no say)
+    float S = INFINITY, sk[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         float a = 0.f, b = 0.f;
 #pragma unroll
         for (int v = 0; v < WAVES; ++v) { a = fmaxf(a, red[2 * k][v]); b = fmaxf(b, red[2 * k + 1][v]); }
         sk[k] = mx::input_scale(a);
-        const float cand = sk[k] * mx::input_scale(b);
-        S = k == 0 ? cand : fminf(S, cand);
+        if (b > 0.f) S = fminf(S, sk[k] * mx::input_scale(b));
         if (row0 == k) h_scale = sk[k];
     }
+    if (S == INFINITY) S = 1.f;
     v2h G[MB][K];
 #pragma unroll
     for (int b = 0; b < MB; ++b)

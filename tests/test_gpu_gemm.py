@@ -234,3 +234,25 @@ def test_many_token_output_over_its_input():
     got = rb.rb_linear_gemm(L, X, Y=X)
     torch.cuda.synchronize()
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("K,T", [(2, 70), (2, 500), (3, 70)])
+def test_gemm_small_scales_next_to_rows_without_a_path(K, T):
+    """Output scales around 2e-5 (fp16 subnormals) and, in the first 512 rows, none for the last path: the power
+    of two that lifts the other paths' scales into fp16's normal range must not come from the path that is zero there."""
+    out, inn = 1100, 544
+    rng = synth.child_rng(5, 122, K, T)
+    signs, g, h = random_layer(rng, K, out, inn)
+    g = (g.astype(np.float64) * 1e-3).astype(np.float16)
+    g[K - 1, :512] = 0
+    X = synth.outlier_activations(rng, T, inn)
+    Xd = torch.from_numpy(X).cuda()
+    _say(f"small scales, rows without a path, K={K} T={T}")
+    Y = rb.rb_linear_gemm(to_device_layer(signs, g, h), Xd, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    assert rb.rb_last_path() == rb.RB_PATH_GEMM
+    ref = oracle.forward(signs, g, h, X)
+    for rows in (slice(0, 512), slice(512, out)):
+        err = max_rel_l2(Y[:, rows], ref[:, rows])
+        _say(f"  rel_l2={err:.3e}")
+        assert err <= TOL
