@@ -14,14 +14,15 @@
 // all-ones vector (the matrix is non-negative): two passes per iteration, a = |R| b by rows (four rows
 // per workgroup) and c = |R|^T a by columns (slices of rows, partial sums added in slice order); in both a lane takes
 // four consecutive columns, one 16-byte load of W.  a is left at its length: with b of length 1, sigma = ||c|| / ||a|| and
-// the next b is c / ||c||.  After the last iteration one more pass by rows gives the last |R| b, the
-// signs of R_i and ||R_i||^2, from which the error follows.  Every sum has a fixed order.  The
+// the next b is c / ||c||.  After the last iteration one more pass by rows gives the last |R| b and the
+// signs of R_i, and another one the error, term by term (as ||R_i||^2 - sigma^2 it would come out of the same pass, but with
+// a digit less: 3.6e-15 off where the terms are 1e-16).  Every sum has a fixed order.  The
 // iteration's stopping rule is evaluated on the device; the host reads one flag per update when it expects the
 // iteration to have finished, so the call synchronises.
 //
 // Measured, 4096 x 11008, two paths, five sweeps (ten updates of four iterations): before (a row per wavefront, slices
 // of 64 rows on single wavefronts, a normalisation after each pass, separate passes for the last |R| b, the signs and
-// the error) 8.7 ms, now 4.9 ms: a row pass 38 us (4.8 TB/s of W),
+// the error) 8.7 ms, now 5.2 ms: a row pass 38 us (4.8 TB/s of W),
 // a column pass 47 us, the sums and the normalisation 14 us.
 #include <hip/hip_runtime.h>
 
@@ -48,40 +49,11 @@ struct Problem {
     int K, out, in;
 };
 
-// R_i[r][c .. c + 3] for path `skip` (skip < 0: the error of the whole approximation, no path left
-// out); c % 4 == 0.  One 16-byte load of W, four bits of one sign word per path.
-__device__ __forceinline__ void residual4(const Problem &p, int r, int c, int skip, const double *g_r, double rows_r,
-                                          double v[4])
-{
-    const float4 w = *reinterpret_cast<const float4 *>(p.W + (size_t)r * p.in + c);
-    v[0] = (double)w.x; v[1] = (double)w.y; v[2] = (double)w.z; v[3] = (double)w.w;
-    if (p.rows)
-        for (int e = 0; e < 4; ++e) v[e] = rows_r * v[e];
-    if (p.cols) {
-        const double2 c01 = *reinterpret_cast<const double2 *>(p.cols + c), c23 = *reinterpret_cast<const double2 *>(p.cols + c + 2);
-        v[0] = v[0] * c01.x; v[1] = v[1] * c01.y; v[2] = v[2] * c23.x; v[3] = v[3] * c23.y;
-    }
-    const int W32 = p.in / 32;
-    for (int j = 0; j < p.K; ++j) {
-        if (j == skip) continue;
-        const uint32_t bits4 = p.packed[((size_t)j * p.out + r) * W32 + (c >> 5)] >> (c & 31);
-        const double2 h01 = *reinterpret_cast<const double2 *>(p.h + (size_t)j * p.in + c);
-        const double2 h23 = *reinterpret_cast<const double2 *>(p.h + (size_t)j * p.in + c + 2);
-        const double hv[4] = {h01.x, h01.y, h23.x, h23.y};
-        for (int e = 0; e < 4; ++e) {
-            const double gs = (bits4 >> e) & 1u ? -g_r[j] : g_r[j];
-            v[e] -= gs * hv[e];
-        }
-    }
-}
-
 struct Scalars {
     double sigma;       // the iteration's current estimate
     double db;          // norm of the last change of b
     int done;           // the stopping rule held (or the matrix is zero)
-    int direct;         // the error is too small a difference: recompute it term by term
     int iters;
-    int pad_;
 };
 
 // sum over a workgroup of `waves` wavefronts in a fixed order, in every thread; red has a slot per wavefront
@@ -101,7 +73,7 @@ __global__ __launch_bounds__(256) void start_kernel(double *b, int in, Scalars *
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < in) b[i] = 1.0 / sqrt((double)in);
     if (i == 0) {
-        sc->sigma = 0.0; sc->db = 0.0; sc->done = 0; sc->direct = 0; sc->iters = 0; sc->pad_ = 0;
+        sc->sigma = 0.0; sc->db = 0.0; sc->done = 0; sc->iters = 0;
     }
 }
 
@@ -151,17 +123,8 @@ __device__ __forceinline__ void residuals(const Problem &p, int r, int r_last, i
     }
 }
 
-// a[r] = sum_c |R[r][c]| b[c], its square by workgroup.  FINAL (after the iteration): also the signs of R (sign(0) = +1;
-// 32 columns per word, bit b = column 32 w + b, 1 means -1; nobody reads the path left out) and the sum of
-// the squares of R by workgroup.  ROWS rows per workgroup, 1024 columns per step
-template <int K, bool FINAL>
-__global__ __launch_bounds__(256) void rows_kernel(Problem p, int skip, const double *b, double *a, double *a_sq, double *r_sq,
-                                                   uint32_t *signs, const Scalars *sc)
+template <int K> __device__ __forceinline__ void load_rows(const Problem &p, int r, int r_last, double (&g)[ROWS][K], double (&rows)[ROWS])
 {
-    if (FINAL ? !sc->done : sc->done) return;
-    __shared__ double red[4][ROWS], red1[4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = blockIdx.x * ROWS, r_last = p.out - 1;
-    double g[ROWS][K], rows[ROWS];
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
         const int row = min(r + u, r_last);
@@ -169,7 +132,20 @@ __global__ __launch_bounds__(256) void rows_kernel(Problem p, int skip, const do
         for (int j = 0; j < K; ++j) g[u][j] = p.g[(size_t)j * p.out + row];
         rows[u] = p.rows ? p.rows[row] : 1.0;
     }
-    double dot[ROWS], sq = 0.0;
+}
+
+// a[r] = sum_c |R[r][c]| b[c], its square by workgroup.  FINAL (after the iteration): also the signs of R (sign(0) = +1;
+// 32 columns per word, bit b = column 32 w + b, 1 means -1; nobody reads the path left out).
+// ROWS rows per workgroup, 1024 columns per step
+template <int K, bool FINAL>
+__global__ __launch_bounds__(256) void rows_kernel(Problem p, int skip, const double *b, double *a, double *a_sq, uint32_t *signs, const Scalars *sc)
+{
+    if (FINAL ? !sc->done : sc->done) return;
+    __shared__ double red[4][ROWS];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = blockIdx.x * ROWS, r_last = p.out - 1;
+    double g[ROWS][K], rows[ROWS];
+    load_rows<K>(p, r, r_last, g, rows);
+    double dot[ROWS];
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) dot[u] = 0.0;
     for (int c0 = 0; c0 < p.in; c0 += 1024) {
@@ -184,10 +160,7 @@ __global__ __launch_bounds__(256) void rows_kernel(Problem p, int skip, const do
                 // eight lanes hold the 32 columns of a word, four each
                 uint32_t four = 0;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    four |= !(v[u][e] >= 0.0) ? 1u << e : 0u;
-                    if (c < p.in && r + u < p.out) sq += v[u][e] * v[u][e];
-                }
+                for (int e = 0; e < 4; ++e) four |= !(v[u][e] >= 0.0) ? 1u << e : 0u;
                 const uint32_t word = or_over_8(four << (4 * (lane & 7)));
                 if ((lane & 7) == 0 && c < p.in && r + u < p.out) signs[(size_t)(r + u) * (p.in / 32) + (c >> 5)] = word;
             }
@@ -202,8 +175,7 @@ __global__ __launch_bounds__(256) void rows_kernel(Problem p, int skip, const do
         for (int m = 32; m > 0; m >>= 1) dot[u] += __shfl_xor(dot[u], m);
         if (lane == 0) red[wave][u] = dot[u];
     }
-    if (FINAL) sq = group_sum(sq, red1, 4);
-    else __syncthreads();
+    __syncthreads();
     if (threadIdx.x != 0) return;
     double s2 = 0.0;
 #pragma unroll
@@ -214,7 +186,6 @@ __global__ __launch_bounds__(256) void rows_kernel(Problem p, int skip, const do
         s2 += s * s;
     }
     a_sq[blockIdx.x] = s2;
-    if (FINAL) r_sq[blockIdx.x] = sq;
 }
 
 // partial[slice][c] = sum over the slice's rows of |R[r][c]| a[r]; a thread per four consecutive
@@ -230,13 +201,7 @@ __global__ __launch_bounds__(256) void cols_kernel(Problem p, int skip, const do
 #pragma unroll 1
     for (int r = r0; r < r1; r += ROWS) {
         double g[ROWS][K], rows[ROWS], v[ROWS][4];
-#pragma unroll
-        for (int u = 0; u < ROWS; ++u) {
-            const int row = min(r + u, r1 - 1);
-#pragma unroll
-            for (int j = 0; j < K; ++j) g[u][j] = p.g[(size_t)j * p.out + row];
-            rows[u] = p.rows ? p.rows[row] : 1.0;
-        }
+        load_rows<K>(p, r, r1 - 1, g, rows);
         residuals<K, ROWS>(p, r, r1 - 1, c, skip, g, rows, v);
 #pragma unroll
         for (int u = 0; u < ROWS; ++u) {
@@ -310,10 +275,9 @@ __global__ __launch_bounds__(1024) void unit_kernel(double *b, const double *sum
     }
 }
 
-// after the final a = |R| b: g' = sqrt(sigma) a / sigma, h' = sqrt(sigma) b with sigma = ||a||; the error from
-// ||R - What||^2 = ||R||^2 - sigma^2 (b has length 1), unless that is a difference of nearly equal numbers
-__global__ __launch_bounds__(256) void scales_kernel(const double *a, const double *b, const double *a_sq, const double *r_sq, int n_a, double *g_i,
-                                                     double *h_i, double *err, int out, int in, Scalars *sc)
+// after the final a = |R| b: g' = sqrt(sigma) a / sigma, h' = sqrt(sigma) b with sigma = ||a||
+__global__ __launch_bounds__(256) void scales_kernel(const double *a, const double *b, const double *a_sq, int n_a, double *g_i,
+                                                     double *h_i, int out, int in, const Scalars *sc)
 {
     if (!sc->done) return;
     __shared__ double red[4];
@@ -324,41 +288,34 @@ __global__ __launch_bounds__(256) void scales_kernel(const double *a, const doub
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < out) g_i[i] = sigma > 0.0 ? root * (a[i] / sigma) : 0.0;
     if (i < in) h_i[i] = root * b[i];
-    if (blockIdx.x != 0 || !err) return;
-    double r2 = 0.0;
-    for (int k = threadIdx.x; k < n_a; k += 256) r2 += r_sq[k];
-    r2 = group_sum(r2, red, 4);
-    if (threadIdx.x == 0) {
-        *err = sqrt(fmax(r2 - a2, 0.0));
-        // rounding leaves some 1e-15 of ||R||^2 in the difference; beyond a factor of 64 the terms are summed
-        sc->direct = !(r2 - a2 > r2 / 64.0);
-    }
 }
 
-// squared Frobenius norm of W' - sum_j What_j by rows, then one workgroup adds the rows up
-__global__ __launch_bounds__(256) void err_rows_kernel(Problem p, double *row_sq)
+// squared Frobenius norm of W' - sum_j What_j, ROWS rows per workgroup as above, then one workgroup adds them up
+template <int K>
+__global__ __launch_bounds__(256) void err_rows_kernel(Problem p, double *rows_sq)
 {
-    const int lane = threadIdx.x & 63;
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (r >= p.out) return;
-    double g_r[RB_MAX_K];
-    for (int j = 0; j < p.K; ++j) g_r[j] = p.g[(size_t)j * p.out + r];
-    const double rows_r = p.rows ? p.rows[r] : 1.0;
-    double s = 0.0;
-#pragma unroll 2
-    for (int c = 4 * lane; c < p.in; c += 256) {
-        double v[4];
-        residual4(p, r, c, -1, g_r, rows_r, v);
-        for (int e = 0; e < 4; ++e) s += v[e] * v[e];
+    __shared__ double red[4];
+    const int r = blockIdx.x * ROWS, r_last = p.out - 1;
+    double g[ROWS][K], rows[ROWS];
+    load_rows<K>(p, r, r_last, g, rows);
+    double sq = 0.0;
+    for (int c = 4 * (int)threadIdx.x; c < p.in; c += 1024) {
+        double v[ROWS][4];
+        residuals<K, ROWS>(p, r, r_last, c, -1, g, rows, v);
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (r + u < p.out) sq += v[u][e] * v[u][e];
     }
-    for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m);
-    if (lane == 0) row_sq[r] = s;
+    sq = group_sum(sq, red, 4);
+    if (threadIdx.x == 0) rows_sq[blockIdx.x] = sq;
 }
-__global__ __launch_bounds__(1024) void err_sum_kernel(const double *row_sq, int out, double *err)
+__global__ __launch_bounds__(1024) void err_sum_kernel(const double *rows_sq, int n, double *err)
 {
     __shared__ double red[1024];
     double s = 0.0;
-    for (int i = threadIdx.x; i < out; i += 1024) s += row_sq[i];
+    for (int i = threadIdx.x; i < n; i += 1024) s += rows_sq[i];
     red[threadIdx.x] = s;
     __syncthreads();
     for (int w = 512; w > 0; w >>= 1) {
@@ -387,7 +344,7 @@ __global__ __launch_bounds__(256) void unscale_kernel(double *g, double *h, cons
 }
 
 struct Layout {
-    size_t scalars, a, a_sq, r_sq, b, sum, sum_sq, row_sq, partial, total;
+    size_t scalars, a, a_sq, b, sum, sum_sq, partial, total;
 };
 // the slices come last; `rows` of them each
 static Layout make_layout(int out, int in, int rows)
@@ -399,11 +356,9 @@ static Layout make_layout(int out, int in, int rows)
     L.scalars = o; o += up(sizeof(Scalars));
     L.a = o; o += up(sizeof(double) * out);
     L.a_sq = o; o += up(sizeof(double) * groups);
-    L.r_sq = o; o += up(sizeof(double) * groups);
     L.b = o; o += up(sizeof(double) * in);
     L.sum = o; o += up(sizeof(double) * in);
     L.sum_sq = o; o += up(sizeof(double) * ((in + SUMS_COLS - 1) / SUMS_COLS));
-    L.row_sq = L.a;                                            // (the direct error is computed when a has been used up)
     L.partial = o; o += up(sizeof(double) * slices * in);
     L.total = o;
     return L;
@@ -411,7 +366,7 @@ static Layout make_layout(int out, int in, int rows)
 
 struct Buffers {
     Scalars *sc;
-    double *a, *a_sq, *r_sq, *b, *sum, *sum_sq, *row_sq, *partial;
+    double *a, *a_sq, *b, *sum, *sum_sq, *partial;
 };
 
 template <int K>
@@ -423,28 +378,27 @@ static int derive(const Problem &p, int T_max, double *g, double *h, uint32_t *p
     for (int t = 0; t < T_max; ++t) {
         for (int i = 0; i < K; ++i) {
             uint32_t *const signs = packed + (size_t)i * out * (in / 32);
-            double *const err_ti = err ? err + (size_t)t * K + i : nullptr;
             hipLaunchKernelGGL(start_kernel, dim3((in + 255) / 256), wg, 0, stream, ws.b, in, ws.sc);
             Scalars host;
             for (int it = 1;; ++it) {
-                hipLaunchKernelGGL((rows_kernel<K, false>), by_rows, wg, 0, stream, p, i, ws.b, ws.a, ws.a_sq, ws.r_sq, signs, ws.sc);
+                hipLaunchKernelGGL((rows_kernel<K, false>), by_rows, wg, 0, stream, p, i, ws.b, ws.a, ws.a_sq, signs, ws.sc);
                 hipLaunchKernelGGL((cols_kernel<K>), by_cols, wg, 0, stream, p, i, ws.a, ws.partial, slice_rows, ws.sc);
                 hipLaunchKernelGGL(slices_kernel, dim3((in + SUMS_COLS - 1) / SUMS_COLS), dim3(SUMS_COLS * SUMS_RUNS), 0, stream, ws.partial, n_slices, in, ws.sum, ws.sum_sq, ws.sc);
                 hipLaunchKernelGGL(unit_kernel, dim3(1), dim3(1024), 0, stream, ws.b, ws.sum, ws.sum_sq, ws.a_sq, n_a, in, ws.sc);
                 if (it < look) continue;
                 // |R| b and the signs for the converged b, the path's new scales: nothing happens unless the iteration has finished
-                hipLaunchKernelGGL((rows_kernel<K, true>), by_rows, wg, 0, stream, p, i, ws.b, ws.a, ws.a_sq, ws.r_sq, signs, ws.sc);
-                hipLaunchKernelGGL(scales_kernel, dim3((std::max(out, in) + 255) / 256), wg, 0, stream, ws.a, ws.b, ws.a_sq, ws.r_sq, n_a,
-                                   g + (size_t)i * out, h + (size_t)i * in, err_ti, out, in, ws.sc);
+                hipLaunchKernelGGL((rows_kernel<K, true>), by_rows, wg, 0, stream, p, i, ws.b, ws.a, ws.a_sq, signs, ws.sc);
+                hipLaunchKernelGGL(scales_kernel, dim3((std::max(out, in) + 255) / 256), wg, 0, stream, ws.a, ws.b, ws.a_sq, n_a,
+                                   g + (size_t)i * out, h + (size_t)i * in, out, in, ws.sc);
                 if (hipMemcpyAsync(&host, ws.sc, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess ||
                     hipStreamSynchronize(stream) != hipSuccess)
                     return RB_ERR_HIP;
                 if (host.done) break;
             }
             look = std::max(1, host.iters);
-            if (err && host.direct) {
-                hipLaunchKernelGGL(err_rows_kernel, dim3((out + 3) / 4), wg, 0, stream, p, ws.row_sq);
-                hipLaunchKernelGGL(err_sum_kernel, dim3(1), dim3(1024), 0, stream, ws.row_sq, out, err_ti);
+            if (err) {
+                hipLaunchKernelGGL((err_rows_kernel<K>), by_rows, wg, 0, stream, p, ws.a);       // (a has been used up)
+                hipLaunchKernelGGL(err_sum_kernel, dim3(1), dim3(1024), 0, stream, ws.a, n_a, err + (size_t)t * K + i);
             }
         }
     }
@@ -478,8 +432,8 @@ extern "C" int rb_derive_iterative(const float *W, const double *row_factors, co
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     uint8_t *ws = static_cast<uint8_t *>(workspace);
     auto at = [&](size_t offset) { return reinterpret_cast<double *>(ws + offset); };
-    const Buffers buf{reinterpret_cast<Scalars *>(ws + lay.scalars), at(lay.a), at(lay.a_sq), at(lay.r_sq), at(lay.b), at(lay.sum),
-                      at(lay.sum_sq), at(lay.row_sq), at(lay.partial)};
+    const Buffers buf{reinterpret_cast<Scalars *>(ws + lay.scalars), at(lay.a), at(lay.a_sq), at(lay.b), at(lay.sum),
+                      at(lay.sum_sq), at(lay.partial)};
     const int W32 = in / 32;
 
     // What_i^(0) = 0: zero scales (and all-plus signs, which the zero scales make irrelevant)

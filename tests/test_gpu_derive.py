@@ -158,3 +158,23 @@ def test_slices_of_the_column_pass_and_their_workspace(K, out, inn, slices_of):
     np.testing.assert_allclose(gd.cpu().numpy(), g, rtol=1e-8, atol=1e-14)
     np.testing.assert_allclose(hd.cpu().numpy(), h, rtol=1e-8, atol=1e-14)
     np.testing.assert_allclose(ed.cpu().numpy(), err, rtol=1e-9)
+
+
+@pytest.mark.parametrize("K,out,inn,noise", [(1, 300, 1056, 0.14), (1, 1024, 2048, 0.14), (2, 300, 544, 0.3), (3, 70, 4128, 1.0)])
+def test_error_of_the_last_update_term_by_term(K, out, inn, noise):
+    """The last entry of err against the residual of the returned paths, term by term in extended precision, where
+    the residual is a small part of the weight.  Each term W - sum_j What_j rounds K times (2^-53 of a few W each),
+    at random over out x in terms, which leaves nothing of it; a sum of squares goes through some 30 additions (in / 64
+    of a thread, then trees), 30 x 2^-53 if all round the same way, sqrt(30) x 2^-53 = 6e-16 at random, half of it after
+    the root."""
+    rng = synth.child_rng(7, 706, K, out)
+    W = (1.0 + noise * rng.standard_normal((out, inn))) * synth.uniform_signs(rng, 1, out, inn)[0]
+    W = W.astype(np.float32)
+    packed, g, h, err = _run(W, K, 1)
+    signs = oracle.unpack(packed)
+    left = W.astype(np.longdouble)
+    for k in range(K):
+        left = left - g[k].astype(np.longdouble)[:, None] * signs[k] * h[k].astype(np.longdouble)[None, :]
+    want = np.sqrt((left * left).sum())
+    print(f"error K={K} {out}x{inn}: off by {float(abs(err[-1, -1] / want - 1)):.2e}, {float((want / np.linalg.norm(W)) ** 2):.4f} of the weight", flush=True)
+    assert abs(err[-1, -1] / want - 1) <= 1e-15
