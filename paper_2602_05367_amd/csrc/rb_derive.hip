@@ -13,8 +13,8 @@
 // pass is bound by the HBM read of W.  The singular triplet comes from a power iteration from the
 // all-ones vector (the matrix is non-negative): two passes per iteration, a = |R| b by rows (four rows
 // per workgroup) and c = |R|^T a by columns (slices of rows, partial sums added in slice order); in both a lane takes
-// four consecutive columns, one 16-byte load of W.  a is left at its length: with b of length 1, sigma = ||c|| / ||a|| and
-// the next b is c / ||c||.  After the last iteration one more pass by rows gives the last |R| b and the
+// four consecutive columns, one 16-byte load of W.  a is left at its length and its norm taken
+// out of c: with b of length 1, sigma = ||c|| and the next b is c / ||c||.  After the last iteration one more pass by rows gives the last |R| b and the
 // signs of R_i, and another one the error, term by term (as ||R_i||^2 - sigma^2 it would come out of the same pass, but with
 // a digit less: 3.6e-15 off where the terms are 1e-16).  Every sum has a fixed order.  The
 // iteration's stopping rule is evaluated on the device; the host reads one flag per update when it expects the
@@ -51,6 +51,7 @@ struct Problem {
 
 struct Scalars {
     double sigma;       // the iteration's current estimate
+    double na;          // norm of |R| b
     double db;          // norm of the last change of b
     int done;           // the stopping rule held (or the matrix is zero)
     int iters;
@@ -73,7 +74,7 @@ __global__ __launch_bounds__(256) void start_kernel(double *b, int in, Scalars *
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < in) b[i] = 1.0 / sqrt((double)in);
     if (i == 0) {
-        sc->sigma = 0.0; sc->db = 0.0; sc->done = 0; sc->iters = 0;
+        sc->sigma = 0.0; sc->na = 0.0; sc->db = 0.0; sc->done = 0; sc->iters = 0;
     }
 }
 
@@ -215,22 +216,26 @@ __global__ __launch_bounds__(256) void cols_kernel(Problem p, int skip, const do
     *reinterpret_cast<double2 *>(dst + 2) = make_double2(s[2], s[3]);
 }
 
-// sum[c] = the slices of partial[.][c], in eight runs of consecutive ones, and the squares by workgroup
+// sum[c] = the slices of partial[.][c], in eight runs of consecutive ones, over the norm of a (every workgroup adds
+// that up: squares of sums left at their length would leave fp64's range with W'^4), and the squares by workgroup
 constexpr int SUMS_COLS = 64, SUMS_RUNS = 8;
-__global__ __launch_bounds__(SUMS_COLS * SUMS_RUNS) void slices_kernel(const double *partial, int n_slices, int in, double *sum, double *sum_sq, const Scalars *sc)
+__global__ __launch_bounds__(SUMS_COLS * SUMS_RUNS) void slices_kernel(const double *partial, int n_slices, const double *a_sq, int n_a, int in, double *sum, double *sum_sq, Scalars *sc)
 {
     if (sc->done) return;
-    __shared__ double part[SUMS_RUNS][SUMS_COLS];
+    __shared__ double part[SUMS_RUNS][SUMS_COLS], red[SUMS_RUNS];
     const int x = threadIdx.x % SUMS_COLS, run = threadIdx.x / SUMS_COLS, c = blockIdx.x * SUMS_COLS + x, cs = min(c, in - 1);
-    double s = 0.0;
+    double s = 0.0, na = 0.0;
+    for (int i = threadIdx.x; i < n_a; i += SUMS_COLS * SUMS_RUNS) na += a_sq[i];
 #pragma unroll 8
     for (int k = n_slices * run / SUMS_RUNS; k < n_slices * (run + 1) / SUMS_RUNS; ++k) s += partial[(size_t)k * in + cs];
     part[run][x] = s;
-    __syncthreads();
+    na = sqrt(group_sum(na, red, SUMS_RUNS));
+    if (blockIdx.x == 0 && threadIdx.x == 0) sc->na = na;
     if (threadIdx.x >= SUMS_COLS) return;
     s = 0.0;
 #pragma unroll
     for (int k = 0; k < SUMS_RUNS; ++k) s += part[k][x];
+    s /= na;                                                   // (a zero norm: the next kernel does not look at the sums)
     if (c < in) sum[c] = s;
     double sq = c < in ? s * s : 0.0;
     for (int m = SUMS_COLS / 2; m > 0; m >>= 1) sq += __shfl_xor(sq, m);
@@ -238,35 +243,26 @@ __global__ __launch_bounds__(SUMS_COLS * SUMS_RUNS) void slices_kernel(const dou
 }
 
 // b_new = sum / its norm, the change of b, the stopping rule  (one workgroup)
-__global__ __launch_bounds__(1024) void unit_kernel(double *b, const double *sum, const double *sum_sq, const double *a_sq, int n_a, int in, Scalars *sc)
+__global__ __launch_bounds__(1024) void unit_kernel(double *b, const double *sum, const double *sum_sq, int in, Scalars *sc)
 {
     if (sc->done) return;
-    __shared__ double red[32];
-    double nc = 0.0, na = 0.0;
-    for (int i = threadIdx.x; i < (in + SUMS_COLS - 1) / SUMS_COLS; i += 1024) nc += sum_sq[i];
-    for (int i = threadIdx.x; i < n_a; i += 1024) na += a_sq[i];
-    for (int m = 32; m > 0; m >>= 1) { nc += __shfl_xor(nc, m); na += __shfl_xor(na, m); }
-    if ((threadIdx.x & 63) == 0) { red[threadIdx.x >> 6] = nc; red[16 + (threadIdx.x >> 6)] = na; }
-    __syncthreads();
-    nc = na = 0.0;
-    for (int w = 0; w < 16; ++w) { nc += red[w]; na += red[16 + w]; }
-    __syncthreads();
-    nc = sqrt(nc);
-    na = sqrt(na);
-    if (na == 0.0) {                                           // |R| b = 0: b stays
+    __shared__ double red[16];
+    double sigma = 0.0;
+    for (int i = threadIdx.x; i < (in + SUMS_COLS - 1) / SUMS_COLS; i += 1024) sigma += sum_sq[i];
+    sigma = sqrt(group_sum(sigma, red, 16));
+    if (sc->na == 0.0) {                                       // |R| b = 0: b stays
         if (threadIdx.x == 0) sc->done = 1;
         return;
     }
     double db = 0.0;
 #pragma unroll 4
     for (int c = threadIdx.x; c < in; c += 1024) {
-        const double bn = sum[c] / nc, d = bn - b[c];
+        const double bn = sum[c] / sigma, d = bn - b[c];
         db += d * d;
         b[c] = bn;
     }
     db = sqrt(group_sum(db, red, 16));
     if (threadIdx.x == 0) {
-        const double sigma = nc / na;
         const bool done = fabs(sigma - sc->sigma) <= TOL_SIGMA * sigma && db <= TOL_B;
         sc->sigma = sigma;
         sc->db = db;
@@ -383,8 +379,8 @@ static int derive(const Problem &p, int T_max, double *g, double *h, uint32_t *p
             for (int it = 1;; ++it) {
                 hipLaunchKernelGGL((rows_kernel<K, false>), by_rows, wg, 0, stream, p, i, ws.b, ws.a, ws.a_sq, signs, ws.sc);
                 hipLaunchKernelGGL((cols_kernel<K>), by_cols, wg, 0, stream, p, i, ws.a, ws.partial, slice_rows, ws.sc);
-                hipLaunchKernelGGL(slices_kernel, dim3((in + SUMS_COLS - 1) / SUMS_COLS), dim3(SUMS_COLS * SUMS_RUNS), 0, stream, ws.partial, n_slices, in, ws.sum, ws.sum_sq, ws.sc);
-                hipLaunchKernelGGL(unit_kernel, dim3(1), dim3(1024), 0, stream, ws.b, ws.sum, ws.sum_sq, ws.a_sq, n_a, in, ws.sc);
+                hipLaunchKernelGGL(slices_kernel, dim3((in + SUMS_COLS - 1) / SUMS_COLS), dim3(SUMS_COLS * SUMS_RUNS), 0, stream, ws.partial, n_slices, ws.a_sq, n_a, in, ws.sum, ws.sum_sq, ws.sc);
+                hipLaunchKernelGGL(unit_kernel, dim3(1), dim3(1024), 0, stream, ws.b, ws.sum, ws.sum_sq, in, ws.sc);
                 if (it < look) continue;
                 // |R| b and the signs for the converged b, the path's new scales: nothing happens unless the iteration has finished
                 hipLaunchKernelGGL((rows_kernel<K, true>), by_rows, wg, 0, stream, p, i, ws.b, ws.a, ws.a_sq, signs, ws.sc);

@@ -178,3 +178,17 @@ def test_error_of_the_last_update_term_by_term(K, out, inn, noise):
     want = np.sqrt((left * left).sum())
     print(f"error K={K} {out}x{inn}: off by {float(abs(err[-1, -1] / want - 1)):.2e}, {float((want / np.linalg.norm(W)) ** 2):.4f} of the weight", flush=True)
     assert abs(err[-1, -1] / want - 1) <= 1e-15
+
+
+@pytest.mark.parametrize("K,out,inn,power", [(2, 70, 1056, -200), (2, 70, 1056, 200), (3, 300, 544, -230), (1, 1024, 2080, 230)])
+def test_preconditioned_weights_of_any_size(K, out, inn, power):
+    """Factors that are powers of two change nothing but the exponents, whatever their size: the same signs and, back in the
+    original domain, the same scales, bit for bit, and errors that are the factors times as large."""
+    rng = synth.child_rng(7, 707, K, out)
+    W = synth.gaussian_weight(rng, out, inn, std=0.02).astype(np.float32)
+    one = _run(W, K, 2)
+    print(f"derive K={K} {out}x{inn}, factors of 2^{power}", flush=True)
+    packed, g, h, err = _run(W, K, 2, np.full(out, 2.0 ** power), np.full(inn, 2.0 ** power))
+    assert np.array_equal(packed, one[0])
+    assert np.array_equal(g, one[1]) and np.array_equal(h, one[2])
+    assert np.array_equal(err, one[3] * 4.0 ** power)
