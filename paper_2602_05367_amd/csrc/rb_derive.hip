@@ -36,6 +36,7 @@ namespace rb {
 namespace derive {
 
 constexpr int ROW_SLICE = 32;          // rows one workgroup of the column pass walks (twice that where the workspace is the smaller)
+constexpr int MAX_SLICES = 65535;
 constexpr int ROWS = 4;                // rows one workgroup of the row pass takes
 constexpr int FIRST_LOOK = 4;          // power iterations before the first look at the flag
 constexpr int MAX_ITER = 200;
@@ -420,8 +421,10 @@ extern "C" int rb_derive_iterative(const float *W, const double *row_factors, co
     if ((uintptr_t)packed & 3) return RB_ERR_ALIGN;
     if (((uintptr_t)g | (uintptr_t)row_factors | (uintptr_t)err) & 7) return RB_ERR_ALIGN;
     if (((uintptr_t)W | (uintptr_t)h | (uintptr_t)col_factors) & 15) return RB_ERR_ALIGN;      // read 16 bytes at a time
-    // a smaller workspace (slices of twice the rows) does as well
-    const int slice_rows = workspace_bytes >= make_layout(out, in, ROW_SLICE).total ? ROW_SLICE : 2 * ROW_SLICE;
+    // a smaller workspace (slices of twice the rows) does as well; more slices than the second dimension of a grid
+    // may have: the same
+    const bool short_slices = workspace_bytes >= make_layout(out, in, ROW_SLICE).total && out <= MAX_SLICES * ROW_SLICE;
+    const int slice_rows = short_slices ? ROW_SLICE : 2 * ROW_SLICE;
     const Layout lay = make_layout(out, in, slice_rows);
     if (!workspace || workspace_bytes < lay.total) return RB_ERR_WORKSPACE;
     if ((uintptr_t)workspace & 15) return RB_ERR_ALIGN;

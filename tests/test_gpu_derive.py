@@ -192,3 +192,25 @@ def test_preconditioned_weights_of_any_size(K, out, inn, power):
     assert np.array_equal(packed, one[0])
     assert np.array_equal(g, one[1]) and np.array_equal(h, one[2])
     assert np.array_equal(err, one[3] * 4.0 ** power)
+
+
+def test_more_rows_than_slices_of_a_grid():
+    """More than 65535 slices of 32 rows (a grid's second dimension ends at 65536): one path of a tall matrix against the
+    leading eigenvector of |W|^T |W|."""
+    out, inn = 65536 * 32 + 37, 32
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(708)
+    W = torch.randn((out, inn), device="cuda", generator=gen) * 0.02
+    print(f"derive {out}x{inn}", flush=True)
+    packed, g, h, err = rb.rb_derive_iterative(W, 1, 1)
+    A = W.double().abs()
+    values, vectors = torch.linalg.eigh((A.T @ A).cpu())
+    b = vectors[:, -1].abs()
+    sigma = values[-1].sqrt()
+    assert torch.allclose(h[0].cpu(), sigma.sqrt() * b, rtol=1e-8, atol=0)
+    assert torch.allclose(g[0], (A @ b.cuda()) / sigma.sqrt(), rtol=1e-8, atol=1e-12)
+    weights = (1 << torch.arange(32, device="cuda")).long()
+    words = ((W < 0).long() * weights).sum(dim=1)
+    assert torch.equal(packed[0, :, 0].long() & 0xffffffff, words)
+    left = (A - g[0][:, None] * h[0][None, :]).norm()
+    assert abs(float(err[0, 0] / left) - 1) <= 1e-9
