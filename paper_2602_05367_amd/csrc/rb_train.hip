@@ -51,7 +51,9 @@ __global__ __launch_bounds__(256) void couple_kernel(const float *__restrict__ W
 {
     constexpr int STEPS = COUPLE_CHUNK / 256, R = COUPLE_ROWS;
     const int lane = threadIdx.x & 63;
-    const int tile_row0 = (int)(threadIdx.x >> 6) * R, row0 = blockIdx.x * TILE_ROWS + tile_row0;
+    // one-dimensional grid, row tiles fastest (a second dimension would end at 65536 chunks of columns)
+    const int RT = row_tiles(out), rt = (int)(blockIdx.x % (unsigned)RT);
+    const int tile_row0 = (int)(threadIdx.x >> 6) * R, row0 = rt * TILE_ROWS + tile_row0;
     static_assert(4 * R == TILE_ROWS && COUPLE_CHUNK % TILE_COLS == 0, "whole sign tiles per workgroup");
     __shared__ __attribute__((aligned(16))) uint32_t tiles[STEPS * tile_words(K)];
     const int W32 = in / 32, CT = col_tiles(in);
@@ -60,7 +62,7 @@ __global__ __launch_bounds__(256) void couple_kernel(const float *__restrict__ W
     for (int u = 0; u < R; ++u)
 #pragma unroll
         for (int k = 0; k < K; ++k) gr[u][k] = __half2float(g[(size_t)k * out + min(row0 + u, out - 1)]);
-    const int chunk0 = blockIdx.y * COUPLE_CHUNK;
+    const int chunk0 = (int)(blockIdx.x / (unsigned)RT) * COUPLE_CHUNK;
     float4 wv[STEPS][R];
 #pragma unroll
     for (int i = 0; i < STEPS; ++i) {
@@ -120,7 +122,7 @@ __global__ __launch_bounds__(256) void couple_kernel(const float *__restrict__ W
     if (!native) return;
     __syncthreads();
     const int ct0 = chunk0 / TILE_COLS, words = min(STEPS, CT - ct0) * tile_words(K);
-    uint32_t *const dst = native + ((size_t)blockIdx.x * CT + ct0) * tile_words(K);      // 4-byte aligned at least
+    uint32_t *const dst = native + ((size_t)rt * CT + ct0) * tile_words(K);      // 4-byte aligned at least
     for (int i = threadIdx.x; i < words; i += 256) dst[i] = tiles[i];
 }
 
@@ -370,7 +372,7 @@ extern "C" int rb_couple(const float *W, const uint16_t *g, const uint16_t *h, i
     if (((uintptr_t)W | (uintptr_t)residual) & 15) return RB_ERR_ALIGN;
     if ((uintptr_t)h & 7) return RB_ERR_ALIGN;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
-    const dim3 grid((unsigned)rb::row_tiles(out), (unsigned)((in + COUPLE_CHUNK - 1) / COUPLE_CHUNK));
+    const dim3 grid((unsigned)rb::row_tiles(out) * (((unsigned)in + COUPLE_CHUNK - 1) / COUPLE_CHUNK));
     auto run = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, W, reinterpret_cast<const __half *>(g),
                            reinterpret_cast<const __half *>(h), out, in, packed, static_cast<uint32_t *>(native), residual);

@@ -126,3 +126,18 @@ def test_training_entry_points_reject_bad_arguments():
     assert lib.rb_scale_grads(W.data_ptr(), out.data_ptr(), g.data_ptr(), h.data_ptr(), 2, 4, 32, W.data_ptr(), W.data_ptr(),
                               None, 0, None) == rb.RB_ERR_WORKSPACE
     assert lib.rb_scale_grads_workspace_bytes(2, 4, 31) == 0
+
+
+def test_coupling_of_very_long_rows():
+    """More chunks of 512 columns than a grid's second dimension may have (65536)."""
+    K, out, inn = 1, 3, 65536 * 512 + 4128
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(604)
+    W = torch.randn((out, inn), device="cuda", generator=gen) * 0.02
+    g, h = torch.full((K, out), 0.1, device="cuda").half(), torch.full((K, inn), 0.1, device="cuda").half()
+    print(f"couple {out}x{inn}", flush=True)
+    packed, native, _ = rb.rb_couple(W, g, h)
+    torch.cuda.synchronize()
+    packed = packed.cpu().numpy().view(np.uint32)
+    assert np.array_equal(packed[0], np.packbits((W < 0).cpu().numpy(), axis=1, bitorder="little").view(np.uint32))
+    assert np.array_equal(rb.rb_unpack_native(native.cpu().numpy().view(np.uint32), K, out, inn), packed)
