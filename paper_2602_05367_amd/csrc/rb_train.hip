@@ -221,8 +221,9 @@ __global__ __launch_bounds__(256, 2) void weight_grad_kernel(const __half *__res
     request(0);
     put(lds[0]);
     int cur = 0;
-    for (int n0 = 0; n0 < N; n0 += WG_N, cur ^= 1) {
-        const bool more = n0 + WG_N < N;
+    // (n0 + WG_N is a sample's number only while there are more; beyond 2^31 - 32 of them it would not be an int)
+    for (int n0 = 0, left = N; left > 0; n0 += left > WG_N ? WG_N : 0, left -= WG_N, cur ^= 1) {
+        const bool more = left > WG_N;
         if (more) request(n0 + WG_N);
         __syncthreads();                                   // this step's tile is complete, the other one free
         const uint8_t *const a = lds[cur] + (wr * 64 + (lane & 31)) * 16, *const b = lds[cur] + A_BYTES + (wc * 128 + (lane & 31)) * 16;
