@@ -113,9 +113,10 @@ int rb_linear_gemv(const rb_layer *L, const uint16_t *x, uint16_t *y,
  * signs (two roundings per weight, a few 1e-4 relative on the output; fp32
  * accumulation) and with the activations in fp16: bfloat16 ones are infinite there
  * from 65520 on and lose bits below 2^-17.
- * Y may overlap X from three tokens on (K = 3: from six; K = 1 and, beyond 64 tokens,
- * in >= 2^22: never): the input is then moved to the workspace first, which is all that
- * the workspace is used for at three tokens and more.
+ * Y may overlap X from three tokens on (K = 3: from six; never for K = 1 and for inputs
+ * too large for the matrix-core kernels, T * in >= 2^32 up to 64 tokens and in >= 2^22
+ * beyond): the input is then moved to the workspace first, which is all that the
+ * workspace is used for at three tokens and more.
  */
 int rb_linear_gemm(const rb_layer *L, const void *X, void *Y, int T,
                    int act_dtype, int out_dtype,

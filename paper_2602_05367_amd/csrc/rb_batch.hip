@@ -415,7 +415,13 @@ static Op make_op(const rb_layer &L, const void *x, void *y)
     return o;
 }
 
-bool call_supported(const rb_layer *L, int T) { return (L->K == 2 || L->K == 3) && T >= 1 && T <= CALL_MAX_T && L->in % 32 == 0; }
+// (the kernel keeps 32-bit offsets into the input)
+static bool supported(const rb_layer *L, int T, int max_T)
+{
+    return (L->K == 2 || L->K == 3) && T >= 1 && T <= max_T && L->in % 32 == 0 && (size_t)T * L->in < (size_t)1 << 32;
+}
+
+bool call_supported(const rb_layer *L, int T) { return supported(L, T, CALL_MAX_T); }
 
 int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
                 size_t workspace_bytes, hipStream_t stream)
@@ -435,10 +441,7 @@ int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype,
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;
 }
 
-bool layer_supported(const rb_layer *L, int T)
-{
-    return (L->K == 2 || L->K == 3) && T >= 1 && T <= STACK_MAX_T && L->in % 32 == 0;
-}
+bool layer_supported(const rb_layer *L, int T) { return supported(L, T, STACK_MAX_T); }
 
 // A plan lives on the host: the kernel needs nothing in device memory besides the buffers.  The
 // workspace is the name it is run by, and holds the input of an op whose output overlaps it.

@@ -212,3 +212,13 @@ def test_few_token_stacks_ask_for_room_to_move_an_input_aside(K, T):
     layers = (rb.binding.rb_layer * 2)(rb.binding.rb_layer(4096, 96, K, 0x1000, 0x2000, 0x3000),
                                        rb.binding.rb_layer(96, 4128, K, 0x1000, 0x2000, 0x3000))
     assert rb.lib.rb_workspace_bytes(layers, 2, 3, T) >= T * 4128 * 2
+
+
+def test_inputs_beyond_32_bit_offsets_are_not_for_the_few_token_kernel():
+    """It keeps 32-bit offsets into the input: from T * in = 2^32 elements on calls and stacks take the generic kernel, which
+    needs no workspace."""
+    def need(T, inn, n_ops=1):
+        L = rb.binding.rb_layer(16, inn, 2, 0x1000, 0x2000, 0x3000)
+        return rb.lib.rb_workspace_bytes(ctypes.byref(L), 1, n_ops, T)
+    assert need(64, 2 ** 26 - 32) == 64 * (2 ** 26 - 32) * 2 and need(64, 2 ** 26) == 0
+    assert need(16, 2 ** 28 - 32, 2) == 16 * (2 ** 28 - 32) * 2 and need(16, 2 ** 28, 2) == 0
