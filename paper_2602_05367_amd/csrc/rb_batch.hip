@@ -7,9 +7,10 @@
 // their products, and only fp32 sums round; the activation is shared by the paths, nothing about the
 // input is prepared, and an op is one launch.  bfloat16 activations keep their whole range: they go into
 // v_mfma_f32_16x16x32_bf16 as they are, against two left operands, as an fp16 scale is the exact sum of two bf16
-// values (three vector instructions in place of two and twice the matrix instructions; 4096 x 4096 at 16
-// tokens 7.1 us where fp16 takes 5.8, 28672 x 8192 48 where halved fp16 copies of the activations, which
-// overflow from 1.3e5 and lose bits below 2^-16, took 38).  What bounds it:
+// values (three vector instructions in place of two and twice the matrix instructions).  Up to 16 tokens only
+// where it must be: 128 columns whose values fp16 holds exactly (zeros, 2^-17 up to 65536, which is nearly all there is) are
+// multiplied as fp16, the others after them (28672 x 8192 at 5 tokens 36 us, 47 with two operands throughout, 33 with
+// unchecked fp16 copies).  What bounds it:
 //   * a launch of a 4096-wide op moves 4 MB of signs, half a microsecond of HBM time, so it is a
 //     chain of latencies (launch, one trip to memory, the matrix instructions, the sum over the
 //     wavefronts): the compute units are filled and every wavefront asks for all it needs at once, the
@@ -39,6 +40,7 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "rabit.h"
@@ -61,9 +63,9 @@ constexpr int MAX_STAGE_OPS = 8;       // independent ops that share a launch
 // Wavefronts of a workgroup at most, and row tiles per workgroup: accumulators take 4 P K G
 // registers, sign words 2 P K, staged activations 16 G, of 128 with sixteen wavefronts per compute unit
 // and 256 with eight (two paths, six row tiles, 16 tokens: 28.6 us a launch of 2 x 11008 x 4096 with sixteen, which
-// spills, 16.2 with eight; four row tiles, 8 tokens, 7B chain: the same either way; bfloat16, two paths, four row
-// tiles, 12304 x 4096 at 5 tokens: 15.0 us with sixteen, which spills, 14.3 with eight)
-__host__ __device__ constexpr int max_waves(int K, int G, int P, bool bf16) { return G == 1 && P * K <= (bf16 ? 6 : 8) ? 16 : 8; }
+// spills, 16.2 with eight; four row tiles, 8 tokens, 7B chain: the same either way).  Two paths, four token groups, two row
+// tiles spill 14 registers and are worth it: 8192 x 8192 at 64 tokens 30.4 us, 39.0 with one row tile
+__host__ __device__ constexpr int max_waves(int K, int G, int P) { return G == 1 && P * K <= 8 ? 16 : 8; }
 __host__ __device__ constexpr bool p_available(int K, int G, int P) { return P == 1 || P * K <= (G == 1 ? 12 : G == 2 ? 6 : 4); }
 
 struct Op {
@@ -135,17 +137,44 @@ template <int K> __device__ __forceinline__ Words<K> load_words(const uint32_t *
     return r;
 }
 
+// bfloat16 values whose fp16 values are the same, in pair order; the others are marked in `range`: below 2^-17 in magnitude
+// (but zero) or at 65536 and beyond, infinities and NaN
+typedef unsigned short v2us __attribute__((ext_vector_type(2)));
+struct Bf16Range {
+    v2us least = {0xffff, 0xffff}, most = {0, 0};              // of the magnitudes less one (a zero: the largest) and of the magnitudes
+    __device__ __forceinline__ void look_at(uint4 v)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const v2us m = __builtin_bit_cast(v2us, reinterpret_cast<const uint32_t *>(&v)[i] & 0x7fff7fffu);
+            least = __builtin_elementwise_min(least, (v2us)(m - (v2us){1, 1}));
+            most = __builtin_elementwise_max(most, m);
+        }
+    }
+    __device__ __forceinline__ bool beyond_fp16() const
+    {
+        return least.x < 0x36ff || least.y < 0x36ff || most.x >= 0x4780 || most.y >= 0x4780;
+    }
+};
+__device__ __forceinline__ uint4 pair_order_as_fp16(uint4 v)
+{
+    auto pair = [](uint32_t a, uint32_t b) { return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(__uint_as_float(a), __uint_as_float(b))); };
+    return make_uint4(pair(v.x << 16, v.z << 16), pair(v.x & 0xffff0000u, v.z & 0xffff0000u),
+                      pair(v.y << 16, v.w << 16), pair(v.y & 0xffff0000u, v.w & 0xffff0000u));
+}
+
 constexpr int UNIT_COLS = 128, ROW_BYTES = 256;      // columns a wavefront stages at a time; a token's fp16 values of them
-template <bool BF16> constexpr int TERMS = BF16 ? 2 : 1;                           // values that an input scale is the sum of
-template <int K, int G, bool BF16> __host__ __device__ constexpr int slab_bytes() { return (16 * G + K * TERMS<BF16>) * ROW_BYTES; }
+template <int K, int G, bool BF16> __host__ __device__ constexpr int slab_bytes() { return (16 * G + K * (BF16 ? 2 : 1)) * ROW_BYTES; }
 
 // K paths, G groups of 16 tokens, P row tiles per workgroup, BF16: the activations are bfloat16
 template <int K, int G, int P, bool BF16>
-__global__ __launch_bounds__(max_waves(K, G, P, BF16) * 64, 1) void batch_kernel(const Args args)
+__global__ __launch_bounds__(max_waves(K, G, P) * 64, 1) void batch_kernel(const Args args)
 {
-    // registers for the sign words of the next column tile (bf16, 10999 x 4128 at 7 tokens, three row tiles: 13.5 us with
-    // them, which spills, 12.9 without)
-    constexpr bool AHEAD = P * K <= (G == 1 && !BF16 ? 6 : 4) && G <= 2;
+    constexpr bool AHEAD = P * K <= (G == 1 ? 6 : 4) && G <= 2;       // registers for the sign words of the next column tile
+    // bfloat16: fp16 copies of the units that fp16 holds, the others after them as they are.  Beyond one token group looking at a
+    // unit costs what the copies save (4096 x 4096 at 24 tokens: 9.3 us with copies unlooked at, 11.5 with the look, 9.2
+    // without copies; at 64, 14.2 without copies)
+    constexpr bool EITHER = BF16 && G == 1;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];    // a slab per wavefront; then [wavefront][row tile][token][row] sums
     __shared__ __attribute__((aligned(16))) float g_lds[P * K * TILE_ROWS];      // [path][row tile][row]
     const int tid = threadIdx.x, lane = tid & 63, nw = (int)blockDim.x >> 6;
@@ -198,19 +227,37 @@ __global__ __launch_bounds__(max_waves(K, G, P, BF16) * 64, 1) void batch_kernel
                                 (uint32_t)h[4] | (uint32_t)h[5] << 16, (uint32_t)h[6] | (uint32_t)h[7] << 16);
         }
     };
-    auto put = [&]() {
+    auto put_x = [&](auto order) {
 #pragma unroll
         for (int i = 0; i < 4 * G; ++i) {
             const int row = 4 * i + row4;
-            if (4 * i < T) *reinterpret_cast<uint4 *>(slab + row * ROW_BYTES + ((pos ^ (row & 15)) * 16)) = pair_order(xs[i]);
+            if (4 * i < T) *reinterpret_cast<uint4 *>(slab + row * ROW_BYTES + ((pos ^ (row & 15)) * 16)) = order(xs[i]);
         }
+    };
+    auto put_h = [&](int m, uint4 v) { *reinterpret_cast<uint4 *>(slab + (16 * G + m * K + row4) * ROW_BYTES + pos * 16) = pair_order(v); };
+    // fp16 activations, or fp16 copies of bfloat16 ones
+    auto put = [&]() {
+        if constexpr (EITHER) put_x([](uint4 v) { return pair_order_as_fp16(v); });
+        else put_x([](uint4 v) { return pair_order(v); });
+        if (row4 < K) put_h(0, hs);
+        __builtin_amdgcn_wave_barrier();
+    };
+    auto put_wide = [&]() {
+        put_x([](uint4 v) { return pair_order(v); });
         if (row4 < K) {
-            uint4 v[TERMS<BF16>] = {hs};
-            if constexpr (BF16) split_scales(hs, v[0], v[1]);
-#pragma unroll
-            for (int m = 0; m < TERMS<BF16>; ++m) *reinterpret_cast<uint4 *>(slab + (16 * G + m * K + row4) * ROW_BYTES + pos * 16) = pair_order(v[m]);
+            uint4 high, low;
+            split_scales(hs, high, low);
+            put_h(0, high);
+            put_h(1, low);
         }
         __builtin_amdgcn_wave_barrier();
+    };
+    auto beyond_fp16 = [&]() {
+        Bf16Range range;
+#pragma unroll
+        for (int i = 0; i < 4 * G; ++i)
+            if (4 * i < T) range.look_at(xs[i]);
+        return (bool)__any(range.beyond_fp16());
     };
     if (wave < CT) request(wave * TILE_COLS);
     // output scales, asked for now, shared through LDS when the sums are there
@@ -231,6 +278,39 @@ __global__ __launch_bounds__(max_waves(K, G, P, BF16) * 64, 1) void batch_kernel
             for (int g = 0; g < G; ++g) acc[p][k][g] = (v4f){0.f, 0.f, 0.f, 0.f};
 
     const int x_addr = r * ROW_BYTES + ((q ^ r) * 16), h_addr = 16 * G * ROW_BYTES + q * 16;
+    // a unit: TERMS left operands per path and row tile
+    auto contract = [&](auto terms, int c) {
+        constexpr int TERMS = decltype(terms)::value, UNROLL = EITHER && TERMS == 2 ? 1 : 4;
+#pragma unroll UNROLL
+        for (int s = 0; s < 4; ++s) {
+            v4u b[G];
+            uint4 hv[K][TERMS];
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int m = 0; m < TERMS; ++m) hv[k][m] = *reinterpret_cast<const uint4 *>(slab + h_addr + (m * K + k) * ROW_BYTES + s * 64);
+#pragma unroll
+            for (int g = 0; g < G; ++g) b[g] = *reinterpret_cast<const v4u *>(slab + (x_addr ^ (s * 64)) + g * 16 * ROW_BYTES);
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int m = 0; m < TERMS; ++m) {
+                        // pair (e, e + 4) of the lane's eight columns 8 s ..: native bits 4 e + s and 16 more
+                        v4u a;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            a[e] = reinterpret_cast<const uint32_t *>(&hv[k][m])[e] ^ ((w[p].w[c * K + k] << (15 - 4 * e - s)) & 0x80008000u);
+#pragma unroll
+                        for (int g = 0; g < G; ++g)
+                            if constexpr (TERMS == 2) acc[p][k][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b[g]), acc[p][k][g], 0, 0, 0);
+                            else acc[p][k][g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b[g]), acc[p][k][g], 0, 0, 0);
+                    }
+            if (P * K > 4) __builtin_amdgcn_sched_barrier(0);            // operands of one contraction at a time (registers)
+        }
+    };
+    unsigned long long left = 0;                               // EITHER: the units put off, the last bit for all from number 63 on
     for (int ct = wave; ct < CT; ct += nw) {
         Words<K> next[P];
         if (AHEAD && ct + nw < CT)
@@ -238,38 +318,13 @@ __global__ __launch_bounds__(max_waves(K, G, P, BF16) * 64, 1) void batch_kernel
             for (int p = 0; p < P; ++p) next[p] = load_words<K>(bits[p] + (size_t)(ct + nw) * tile_words(K) + lane_words);
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            put();
+            const bool late = EITHER && beyond_fp16();
+            if (late) left |= 1ull << min(2 * (ct / nw) + c, 63);
+            else if (BF16 && !EITHER) put_wide();
+            else put();
             if (c == 0) request(ct * TILE_COLS + UNIT_COLS);
             else if (ct + nw < CT) request((ct + nw) * TILE_COLS);
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                v4u b[G];
-                uint4 hv[K][TERMS<BF16>];
-#pragma unroll
-                for (int k = 0; k < K; ++k)
-#pragma unroll
-                    for (int m = 0; m < TERMS<BF16>; ++m) hv[k][m] = *reinterpret_cast<const uint4 *>(slab + h_addr + (m * K + k) * ROW_BYTES + s * 64);
-#pragma unroll
-                for (int g = 0; g < G; ++g) b[g] = *reinterpret_cast<const v4u *>(slab + (x_addr ^ (s * 64)) + g * 16 * ROW_BYTES);
-#pragma unroll
-                for (int k = 0; k < K; ++k)
-#pragma unroll
-                    for (int p = 0; p < P; ++p) {
-                        // pair (e, e + 4) of the lane's eight columns 8 s ..: native bits 4 e + s and 16 more
-#pragma unroll
-                        for (int m = 0; m < TERMS<BF16>; ++m) {
-                            v4u a;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                a[e] = reinterpret_cast<const uint32_t *>(&hv[k][m])[e] ^ ((w[p].w[c * K + k] << (15 - 4 * e - s)) & 0x80008000u);
-#pragma unroll
-                            for (int g = 0; g < G; ++g)
-                                if constexpr (BF16) acc[p][k][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b[g]), acc[p][k][g], 0, 0, 0);
-                                else acc[p][k][g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b[g]), acc[p][k][g], 0, 0, 0);
-                        }
-                    }
-                if (P * K > 4) __builtin_amdgcn_sched_barrier(0);        // operands of one contraction at a time (registers)
-            }
+            if (!late) contract(std::integral_constant<int, BF16 && !EITHER ? 2 : 1>(), c);
             __builtin_amdgcn_wave_barrier();
         }
         if (AHEAD) {
@@ -280,6 +335,21 @@ __global__ __launch_bounds__(max_waves(K, G, P, BF16) * 64, 1) void batch_kernel
             for (int p = 0; p < P; ++p) w[p] = load_words<K>(bits[p] + (size_t)(ct + nw) * tile_words(K) + lane_words);
         }
     }
+    if (EITHER && left != 0)                                   // (a bit too many costs a second look)
+#pragma unroll 1
+        for (int ct = wave; ct < CT; ct += nw) {
+            if (!(left >> min(2 * (ct / nw), 62) & 3)) continue;
+#pragma unroll
+            for (int p = 0; p < P; ++p) w[p] = load_words<K>(bits[p] + (size_t)ct * tile_words(K) + lane_words);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                request(ct * TILE_COLS + c * UNIT_COLS);
+                if (!beyond_fp16()) continue;
+                put_wide();
+                contract(std::integral_constant<int, 2>(), c);
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
 #pragma unroll
     for (int i = 0; i < GV; ++i) {
         const int at = tid + i * (int)blockDim.x;
@@ -339,7 +409,7 @@ static int row_tiles_per_wg(const int *RT, int nops, int K, int G)
 template <int K, int G, int P, bool BF16>
 static int launch_form(const Args &args, int groups, int nw, hipStream_t stream)
 {
-    constexpr int per_wave = std::max(slab_bytes<K, G, BF16>(), P * G * 1024), lds_max = max_waves(K, G, P, BF16) * per_wave;
+    constexpr int per_wave = std::max(slab_bytes<K, G, BF16>(), P * G * 1024), lds_max = max_waves(K, G, P) * per_wave;
     if (lds_max + P * K * TILE_ROWS * (int)sizeof(float) > 64 * 1024) {
         static std::atomic<bool> allowed[64];
         int dev = 0;
@@ -372,7 +442,7 @@ static int token_groups(int T) { return T <= 16 ? 1 : T <= 32 ? 2 : 4; }
 
 // one launch: the ops of `args` (wg0 is filled in here), all of K paths
 struct Shape { int K, P, groups, nw; };
-static Shape shape_of(Args &args, int K, bool bf16)
+static Shape shape_of(Args &args, int K)
 {
     int RT[MAX_STAGE_OPS], CT = 1;
     for (int i = 0; i < args.nops; ++i) {
@@ -388,7 +458,7 @@ static Shape shape_of(Args &args, int K, bool bf16)
         args.wg0[i] = i < args.nops ? s.groups : INT_MAX;
         if (i < args.nops) s.groups += (RT[i] + s.P - 1) / s.P;
     }
-    s.nw = std::min(CT, max_waves(K, G, s.P, bf16));      // a wavefront takes whole column tiles
+    s.nw = std::min(CT, max_waves(K, G, s.P));      // a wavefront takes whole column tiles
     return s;
 }
 
@@ -435,7 +505,7 @@ int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype,
     Args args = {};
     args.nops = 1; args.T = T; args.out_dtype = out_dtype;
     args.op[0] = make_op(*L, X, Y);
-    const Shape s = shape_of(args, L->K, act_dtype == RB_BF16);
+    const Shape s = shape_of(args, L->K);
     const int rc = act_dtype == RB_BF16 ? launch_shape<true>(args, s, stream) : launch_shape<false>(args, s, stream);
     if (rc != RB_OK) return rc;
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;
@@ -492,7 +562,7 @@ int prepare_plan(const rb_layer *layers, const rb_stack_op *sops, int n_ops, uin
             if (conflict) break;
             args.op[args.nops++] = make_op(L, bufs[sops[n].src], bufs[sops[n].dst]);
         }
-        const Shape shape = shape_of(args, K, false);                 // (numbers the workgroups in args)
+        const Shape shape = shape_of(args, K);                 // (numbers the workgroups in args)
         Launch l = {args, shape, nullptr, 0};
         if (meet(src(op0), dst(op0))) {
             l.aside = src(op0).at;

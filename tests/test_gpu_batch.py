@@ -402,10 +402,11 @@ def test_stack_buffers_that_overlap_in_memory(K, T, prepared):
 
 @pytest.mark.parametrize("K,out,inn,T", [(2, 4112, 288, 1), (2, 300, 1056, 2), (2, 4112, 288, 7), (2, 8200, 160, 16), (2, 12304, 160, 5),
                                          (2, 16390, 96, 9), (2, 300, 544, 18), (2, 4112, 96, 64), (3, 300, 288, 6), (3, 4112, 160, 16),
-                                         (3, 300, 96, 33)])
-@pytest.mark.parametrize("size", [3.0e5, 1.0e30, 2.0 ** -20, 2.0 ** -30, 2.0 ** -80])
+                                         (3, 300, 96, 33), (2, 20, 135200, 2), (3, 16, 135200, 6)])
+@pytest.mark.parametrize("size", [3.0e5, 1.0e30, 2.0 ** -15, 2.0 ** -20, 2.0 ** -30, 2.0 ** -80, "mixed"])
 def test_few_token_bf16_over_its_whole_range(K, out, inn, T, size):
-    """bfloat16 activations far beyond fp16's range, every row tile count per workgroup and token group.  An input scale
+    """bfloat16 activations far beyond fp16's range, every row tile count per workgroup and token group, more than 64 pieces of
+    128 columns per wavefront.  An input scale
     is the exact sum of two bf16 values, so their products with a bf16 activation are exact and only the additions of the
     2 K in terms, the output scale and the path sum round: |error| <= (2 K in + 8) 2^-23 sum |g h x| (twice the
     half-ulp bound).  The scales are the ends of fp16's range too: subnormals, zeros, either sign."""
@@ -414,7 +415,12 @@ def test_few_token_bf16_over_its_whole_range(K, out, inn, T, size):
     g = g.copy(); h = h.copy()
     g[0, ::5] *= -1; h[1, 1::3] *= -1; h[0, 4] = 0; h[1, 9] = -0.0; h[0, 6] = 1.0; h[1, 7] = 65504.0; h[0, 8] = 6.0e-8
     h[:, ::8] = (h[:, ::8].astype(np.float64) * 1e-3).astype(np.float16)
-    Xd = torch.from_numpy(synth.gaussian_activations(rng, T, inn)).cuda().float().mul(size).to(torch.bfloat16)
+    # "mixed": every 128 columns in three of a size of their own, zeros and whole runs that fp16 holds among them
+    sizes = torch.from_numpy(2.0 ** rng.uniform(-24, 24, -(-inn // 128))).repeat_interleave(128)[:inn]
+    sizes[torch.arange(inn) // 128 % 3 != 0] = 1.0
+    Xd = torch.from_numpy(synth.gaussian_activations(rng, T, inn)).double() * (sizes if size == "mixed" else size)
+    Xd[:, ::11] = 0.0
+    Xd = Xd.cuda().to(torch.bfloat16)
     X = Xd.double().cpu().numpy()
     print(f"bf16 range K={K} {out}x{inn} T={T} size={size}", flush=True)
     Y = rb.rb_linear_gemm(to_device_layer(signs, g, h), Xd, out_dtype=torch.float32)
