@@ -116,7 +116,8 @@ int rb_linear_gemv(const rb_layer *L, const uint16_t *x, uint16_t *y,
  * Y may overlap X from three tokens on (K = 3: from six; never for K = 1 and for inputs
  * too large for the matrix-core kernels, T * in >= 2^32 up to 64 tokens and in >= 2^22
  * beyond): the input is then moved to the workspace first, which is all that the
- * workspace is used for at three tokens and more.
+ * workspace is used for at three tokens and more (and, beyond 64 tokens, for a copy of h
+ * where that does not start at a multiple of 16 bytes).
  */
 int rb_linear_gemm(const rb_layer *L, const void *X, void *Y, int T,
                    int act_dtype, int out_dtype,

@@ -114,21 +114,9 @@ __device__ __forceinline__ uint4 buffer_load(__amdgpu_buffer_rsrc_t rs, uint32_t
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)lane_offset, offset, 0));
 }
 
-// eight scales; without H16 they need only be 2-byte aligned
-template <bool H16> __device__ __forceinline__ uint4 load_h8(__amdgpu_buffer_rsrc_t rs, uint32_t lane_offset, int offset)
-{
-    if constexpr (H16) return buffer_load(rs, lane_offset, offset);
-    uint32_t v[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        v[i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)lane_offset + 4 * i, offset, 0) |
-               (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)lane_offset + 4 * i + 2, offset, 0) << 16;
-    return make_uint4(v[0], v[1], v[2], v[3]);
-}
-
 // K paths, NT groups of 32 tokens, WR wavefronts along the rows (the other WAVES / WR share out the columns);
-// BF16: X is bfloat16; H16: h starts at a multiple of 16 bytes (its rows then do too)
-template <int K, int NT, int WR, bool BF16, bool H16>
+// BF16: X is bfloat16.  h starts at a multiple of 16 bytes (its rows then do too)
+template <int K, int NT, int WR, bool BF16>
 __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
 {
     constexpr int WK = WAVES / WR, GT = 64 * WR;               // column groups; threads of one
@@ -175,7 +163,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
         const int at = min(s, n128 - 1) * ROW_BYTES;
 #pragma unroll
         for (int i = part * XP; i < part * XP + XP; ++i) xs[reg(i)] = buffer_load(x_rs, real ? x_off[i] : NOWHERE, at);
-        if (part == 0) hs = load_h8<H16>(h_rs, real ? h_off : NOWHERE, at);
+        if (part == 0) hs = buffer_load(h_rs, real ? h_off : NOWHERE, at);
     };
     float h_scale = 1.f;
     // a chunk sits at position chunk ^ (row % 16) of its row: neither these writes nor the operand reads collide on LDS banks
@@ -231,7 +219,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         mx_h[k] = 0.f;
-        for (int j = tid * 8; j < in; j += WAVES * 64 * 8) mx_h[k] = fmaxf(mx_h[k], abs_max8(load_h8<H16>(h_rs, (uint32_t)(k * in + j) * 2u, 0)));
+        for (int j = tid * 8; j < in; j += WAVES * 64 * 8) mx_h[k] = fmaxf(mx_h[k], abs_max8(buffer_load(h_rs, (uint32_t)(k * in + j) * 2u, 0)));
         mx_g[k] = 0.f;
 #pragma unroll
         for (int b = 0; b < MB; ++b) mx_g[k] = fmaxf(mx_g[k], fabsf(gv[b][k]));
@@ -423,6 +411,12 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
     }
 }
 
+// scales that start at an odd multiple of two bytes, to where 16-byte loads can have them
+__global__ __launch_bounds__(256) void align_kernel(const uint16_t *__restrict__ h, uint16_t *__restrict__ to, int n)
+{
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) to[i] = h[i];
+}
+
 // ------------------------------------------------------------------ host ---
 // The shapes of a workgroup, and what a round of the device takes with each, in microseconds: `fixed` (launch,
 // scales, first loads, sums, stores) and `step` per step of 128 columns per group, for two and for three paths.
@@ -451,39 +445,38 @@ static int best_shape(const rb_layer *L, int T)
     return best;
 }
 
-template <int K, int NT, int WR, bool BF16, bool H16> static int launch_form(const Args &a, hipStream_t stream)
+template <int K, int NT, int WR, bool BF16> static int launch_form(const Args &a, hipStream_t stream)
 {
     constexpr int lds = lds_bytes<K, NT, WR>();
     static std::atomic<bool> allowed[64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return RB_ERR_HIP;
     if (!allowed[dev].load()) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_kernel<K, NT, WR, BF16, H16>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_kernel<K, NT, WR, BF16>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
             return RB_ERR_HIP;
         allowed[dev].store(true);
     }
     const int tiles = tiles_of(Shape{NT, WR, 0.f, {0.f, 0.f}}, a.out, a.T);
-    hipLaunchKernelGGL((gemm_kernel<K, NT, WR, BF16, H16>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(WAVES * 64), lds, stream, a);
+    hipLaunchKernelGGL((gemm_kernel<K, NT, WR, BF16>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(WAVES * 64), lds, stream, a);
     return RB_OK;
 }
 
 template <int K, bool BF16> static int launch_shape(const Args &a, int shape, hipStream_t stream)
 {
-    // scales at an odd multiple of two bytes: one shape serves them, eight loads in place of one
-    if ((uintptr_t)a.h & 15) return launch_form<K, 2, 4, BF16, false>(a, stream);
     switch (shape) {
-    case 0: return launch_form<K, 1, 2, BF16, true>(a, stream);
-    case 1: return launch_form<K, 2, 2, BF16, true>(a, stream);
-    case 2: return launch_form<K, 2, 4, BF16, true>(a, stream);
-    case 3: return launch_form<K, 3, 4, BF16, true>(a, stream);
-    default: return launch_form<K, 4, 4, BF16, true>(a, stream);
+    case 0: return launch_form<K, 1, 2, BF16>(a, stream);
+    case 1: return launch_form<K, 2, 2, BF16>(a, stream);
+    case 2: return launch_form<K, 2, 4, BF16>(a, stream);
+    case 3: return launch_form<K, 3, 4, BF16>(a, stream);
+    default: return launch_form<K, 4, 4, BF16>(a, stream);
     }
 }
 
 // What a caller is asked for (rb_workspace_bytes): room for the input and, when 256 x 256 tiles
 // do not fill whole rounds of the device, for partial sums of the tiles of the last round.  This kernel uses
-// the room for the input alone, and that only when the output overlaps it; the size asked for stays what it was,
-// so that callers that keep one buffer for many layers need not change.
+// the room for the input when the output overlaps it, and the room for the scales when they are not aligned to
+// 16 bytes; the size asked for, and with it what rb_linear_gemm_noalloc turns down, is what it was with the
+// kernel before this one.
 constexpr int BLK = 256;
 constexpr size_t SCALES_BYTES = 256, HBLOCK_BYTES = 256;
 size_t workspace_bytes(const rb_layer *L, int T)
@@ -506,14 +499,24 @@ bool supported(const rb_layer *L, int T)
 int launch(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
            hipStream_t stream)
 {
+    uint8_t *const room_h = static_cast<uint8_t *>(workspace) + SCALES_BYTES, *const room_x = room_h + (size_t)col_tiles(L->in) * 8 * HBLOCK_BYTES;
     if (overlap(X, input_bytes(L, T), Y, output_bytes(L, T, out_dtype))) {
-        copy_aside(X, workspace, input_bytes(L, T), stream);
-        X = workspace;
+        copy_aside(X, room_x, input_bytes(L, T), stream);
+        X = room_x;
+    }
+    // (a launch, some 3 us; with eight 2-byte loads in place of one in the kernel 4096 x 4096 at 100 tokens took 43 us
+    // where aligned scales take 22, and 28672 x 8192 at 2048 tokens a third longer)
+    const uint16_t *h = L->h;
+    if ((uintptr_t)h & 15) {
+        static_assert(8 * HBLOCK_BYTES >= RB_MAX_K * TILE_COLS * sizeof(uint16_t), "the scales fit");
+        const int n = L->K * L->in;
+        hipLaunchKernelGGL(align_kernel, dim3((unsigned)std::min(256, (n + 255) / 256)), dim3(256), 0, stream, h, reinterpret_cast<uint16_t *>(room_h), n);
+        h = reinterpret_cast<const uint16_t *>(room_h);
     }
     Args a;
     a.bits = static_cast<const uint32_t *>(L->bits);
     a.g = reinterpret_cast<const __half *>(L->g);
-    a.h = reinterpret_cast<const __half *>(L->h);
+    a.h = reinterpret_cast<const __half *>(h);
     a.X = X; a.Y = Y;
     a.out = L->out; a.in = L->in; a.T = T; a.out_dtype = out_dtype;
     const int s = best_shape(L, T);

@@ -256,3 +256,22 @@ def test_gemm_small_scales_next_to_rows_without_a_path(K, T):
         err = max_rel_l2(Y[:, rows], ref[:, rows])
         _say(f"  rel_l2={err:.3e}")
         assert err <= TOL
+
+
+@pytest.mark.parametrize("K,n,T,shift", [(2, 544, 70, 1), (3, 544, 70, 3), (2, 1056, 333, 5), (3, 4128, 200, 7)])
+def test_many_token_scales_off_alignment(K, n, T, shift):
+    """Scales that start at an odd multiple of two bytes are moved to the workspace: the same results as aligned ones, bit for
+    bit, also when the output lies over the input and on the library's own scratch memory."""
+    rng = synth.child_rng(5, 123, K, n, T)
+    L = to_device_layer(*random_layer(rng, K, n, n))
+    X = torch.from_numpy(synth.outlier_activations(rng, T, n)).cuda()
+    want = rb.rb_linear_gemm(L, X)
+    store = torch.zeros(K * n + shift, dtype=torch.float16, device="cuda")
+    store[shift:] = L.h.flatten()
+    L.h = store[shift:].view(K, n)
+    _say(f"scales off alignment K={K} {n}x{n} T={T} shift={shift}")
+    assert torch.equal(rb.rb_linear_gemm(L, X), want)
+    Y = X.clone()
+    assert torch.equal(rb.rb_linear_gemm(L, Y, Y=Y), want)
+    Y = X.clone()
+    assert torch.equal(rb.rb_linear_gemm_noalloc(L, Y, Y), want)
