@@ -1,4 +1,4 @@
-"""The small-batch kernel (one pass over the weights for up to 16 tokens, two or three paths) and
+"""The few-token kernel (one pass over the weights, two or three paths: stacks of up to 16 tokens, calls of up to 64) and
 the three-path form of the fused decode kernel (one token) against the oracle: every op of a stack
 recomputed from the input the GPU run actually used."""
 import numpy as np
@@ -29,7 +29,7 @@ def _branching_stack(rng, K, widths):
 
 
 def _check_stack(layers, op_list, widths, x, T, label, prepared):
-    # one token and three paths in every layer: the fused decode kernel; everything else here: the small-batch kernel
+    # one token and three paths in every layer: the fused decode kernel; everything else here: the few-token kernel
     want_path = rb.RB_PATH_MX if (T == 1 and all(l[0].shape[0] == 3 for l in layers)) else rb.RB_PATH_BATCH
     dev_layers = [to_device_layer(*l) for l in layers]
     bufs = [torch.zeros((T, w), dtype=torch.float16, device="cuda") for w in widths]
@@ -74,7 +74,7 @@ def test_two_path_stack_small_batches(T):
     rng = synth.child_rng(3, 500, T)
     layers, op_list = _branching_stack(rng, 2, WIDTHS)
     x = synth.outlier_activations(rng, T, WIDTHS[0])
-    # prepared stacks take this kernel from 8 tokens on, rb_layer_stack from 5 on
+    # from 5 tokens on, rb_layer_stack and prepared stacks alike
     _check_stack(layers, op_list, WIDTHS, x, T, "two paths, branching stack", prepared=(T >= 8 and T % 2 == 0))
 
 
@@ -198,7 +198,7 @@ def test_many_independent_rows_take_larger_row_blocks(n_ops, T):
 def test_scales_that_are_only_two_byte_aligned(T):
     """g and h need no more than the alignment of their elements: a two-op chain whose scale
     vectors start two bytes past a 16-byte boundary, on the fused kernel (1 and 3 tokens) and on
-    the small-batch kernel (8 tokens; its input expansion reads h sixteen bytes at a time when it can)."""
+    the few-token kernel (8 tokens; it reads h sixteen bytes at a time when it can)."""
     rng = synth.child_rng(3, 507, T)
     shapes = [(320, 544), (288, 320)]
     layers = [random_layer(rng, 2, o, i, gain=30.0) for o, i in shapes]
@@ -273,8 +273,8 @@ def test_few_token_calls_element_by_element(K, out, inn, T, bf16):
     """Every form of the few-token kernel (token groups of 16, row tiles per workgroup, both element
     types) against fp64, fp32 results.  Products of a scale and an activation are exact, so only the
     additions of the K in terms, the output scale and the path sum round: |error| <= (K in + 8)
-    2^-23 sum |g h x| (twice the half-ulp bound).  One h in eight is an fp16 subnormal, scales have
-    either sign; bf16 activations are representable in fp16 after halving."""
+    2^-23 sum |g h x| (twice the half-ulp bound; a scale that meets bf16 activations as two terms adds twice as many, which
+    half of that bound covers).  One h in eight is an fp16 subnormal, scales have either sign."""
     rng = synth.child_rng(3, 510, K, out, inn, T)
     signs, g, h = random_layer(rng, K, out, inn)
     g = g.copy(); h = h.copy()

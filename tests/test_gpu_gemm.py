@@ -1,5 +1,6 @@
-"""Many-token matrix-core GEMM vs the fp64 oracle (Section 4.1, Eq. stacked binary
-weight), through the C ABI.  Sizes span several 256 x 256 workgroup tiles and ragged
+"""Matrix-core GEMM of single calls (the few-token kernel up to 64 tokens, the many-token kernel beyond; both
+report RB_PATH_GEMM here) vs the fp64 oracle (Section 4.1, Eq. stacked binary
+weight), through the C ABI.  Sizes span several workgroup tiles and ragged
 tails in every dimension; the 70B-shaped prefill matrices are checked on sampled
 outputs the oracle computes one by one."""
 import sys
@@ -22,14 +23,14 @@ def _say(msg):
 
 
 @pytest.mark.parametrize("out,inn,T", [
-    (256, 256, 256),        # exactly one workgroup tile, one column tile
-    (512, 1024, 300),       # two row blocks, ragged tokens
-    (272, 320, 33),         # ragged rows (17 row tiles), ragged columns (in % 256 != 0)
-    (1000, 2080, 517),      # everything ragged, three token blocks
-    (48, 32, 3),            # tiny: one row tile group, the smallest input width
-    (4096, 1024, 256),      # 16 output tiles on 256 compute units: every tile's contraction cut in four
-    (8400, 1024, 2048),     # 264 tiles: one full round, then 8 tiles (ragged last row block) cut in four
-    (2816, 512, 2048),      # 88 tiles: cut in two, as many slices as column tiles
+    (256, 256, 256),        # two blocks of 128 rows, one column tile
+    (512, 1024, 300),       # whole row blocks, ragged tokens
+    (272, 320, 33),         # few tokens: ragged rows (17 row tiles), ragged columns (in % 256 != 0)
+    (1000, 2080, 517),      # everything ragged
+    (48, 32, 3),            # few tokens, tiny: three row tiles, the smallest input width
+    (4096, 1024, 256),      # whole tiles in every direction
+    (8400, 1024, 2048),     # more than one round of the device's workgroups, ragged last row block
+    (2816, 512, 2048),      # as many column steps as column groups
 ])
 def test_gemm_matches_oracle(out, inn, T):
     rng = synth.child_rng(5, 100, out, inn, T)
@@ -47,8 +48,8 @@ def test_gemm_matches_oracle(out, inn, T):
 
 @pytest.mark.parametrize("out,inn,T", [(272, 320, 33), (1000, 2080, 517), (4096, 1024, 256), (8400, 1024, 300)])
 def test_three_path_gemm_matches_oracle(out, inn, T):
-    """The 3-bit variant beyond 32 tokens: the same one-contraction kernel with a third path in
-    the effective weight (ragged shapes, tiles cut along the contraction, scales of either sign)."""
+    """The 3-bit variant: a third path in the effective weight (ragged shapes, scales of either sign); at 33 tokens the
+    few-token kernel."""
     rng = synth.child_rng(5, 110, out, inn, T)
     signs, g, h = random_layer(rng, 3, out, inn)
     g = g.copy(); h = h.copy()
@@ -68,8 +69,8 @@ def test_three_path_gemm_matches_oracle(out, inn, T):
     (272, 544, 5, False, "generic"), (272, 544, 6, False, "batch"), (1000, 2080, 8, False, "batch"), (272, 544, 12, False, "batch"),
     (272, 544, 13, False, "gemm"), (1000, 2080, 32, False, "gemm"), (272, 544, 3, True, "generic"), (48, 32, 7, True, "gemm")])
 def test_three_path_single_calls_at_few_tokens(out, inn, T, bf16_in, path):
-    """One call on a three-path layer at 6..32 tokens reads the weights once: the small-batch kernel
-    as a plan of one op up to 12 fp16 tokens, the one-contraction kernel beyond that and for bf16."""
+    """One call on a three-path layer from 6 tokens on takes the few-token kernel, which reports itself as RB_PATH_BATCH up
+    to 12 fp16 tokens and as RB_PATH_GEMM beyond that and for bf16; fewer tokens take the generic kernel."""
     rng = synth.child_rng(5, 111, out, inn, T)
     signs, g, h = random_layer(rng, 3, out, inn)
     g = g.copy(); h = h.copy()
@@ -90,8 +91,7 @@ def test_three_path_single_calls_at_few_tokens(out, inn, T, bf16_in, path):
 
 
 def test_gemm_negative_and_zero_scales():
-    """Stored output scales of either sign and zero: the kernel folds the sign of g into the
-    sign bits and keeps |g| as the magnitude of its left operand."""
+    """Stored output scales of either sign and zero, 40 tokens."""
     out, inn, T = 96, 512, 40
     rng = synth.child_rng(5, 101)
     signs, g, h = random_layer(rng, 2, out, inn)
@@ -170,8 +170,7 @@ def test_prefill_70b_shapes_sampled(out, inn):
     scale = np.sqrt(np.mean(ref ** 2))
     assert np.max(np.abs(got - ref)) <= 4 * TOL * scale, (np.max(np.abs(got - ref)), scale)
     # two whole token rows over a 512-row slice: per-vector relative L2 as everywhere else
-    # (for 28672 rows also the last 512: the row blocks of the partly filled last round, whose
-    # contraction is shared by two workgroups)
+    # (for 28672 rows also the last 512)
     for r0 in ([3 * 512, out - 512] if out >= 2048 * 2 else [0]):
         rows2 = np.arange(r0, r0 + 512)
         S2 = signs_rows(rows2)

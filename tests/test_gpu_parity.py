@@ -56,7 +56,7 @@ def test_gemv_shapes_and_tails(K, out, inn):
 
 def test_three_paths_derived_and_batched():
     """K = 3 (the 3-bit variant of the paper's packing appendix): paths derived from a Gaussian
-    matrix, one token and a few on the generic kernel, a small batch on the small-batch kernel."""
+    matrix, one token and a few on the generic kernel, nine on the few-token kernel."""
     rng = synth.child_rng(0, 260)
     W = rng.standard_normal((160, 544)) * 0.02
     signs, g, h, norms = oracle.derive(W, 3)

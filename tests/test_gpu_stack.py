@@ -29,14 +29,14 @@ def _run_and_check(ops, widths, layers, bufs0, T, label, prepared=False):
         stack.prepare()
         stack.run_prepared()
         torch.cuda.synchronize()
-        assert rb.rb_last_path() == (rb.RB_PATH_MX if T < 8 else rb.RB_PATH_BATCH)
+        assert rb.rb_last_path() == (rb.RB_PATH_MX if T <= 4 else rb.RB_PATH_BATCH)
         assert stack.status() == rb.RB_OK, f"gave up: reason {stack.gave_up()}"
         stack.forget()
     else:
         rb.rb_layer_stack(dev_layers, op_list, dev_bufs, T)
     torch.cuda.synchronize()
-    # a stack of 3..16 tokens runs as token pairs on the fused kernel or on the small-batch kernel,
-    # a single call on the many-token kernel
+    # a stack of 3 or 4 tokens runs on the fused kernel where a single call takes the few-token kernel; from 5 to 16 tokens
+    # both take the few-token kernel, whose sums depend on the workgroups a launch has
     same_kernel = T <= 2 or T > 16
     got = [b.cpu().numpy() for b in dev_bufs]
     forced = [got[op.src] for op in ops]
@@ -82,12 +82,38 @@ def test_small_stack_batched_with_outliers(T):
 
 @pytest.mark.parametrize("T", [3, 8, 16])
 def test_prepared_small_batches(T):
-    """rb_stack_prepare / rb_stack_run at 3..16 tokens (token pairs on the fused kernel below 8
-    tokens, the small-batch kernel from 8 on), every op checked against the oracle."""
+    """rb_stack_prepare / rb_stack_run at 3..16 tokens (the fused kernel up to 4 tokens, the few-token
+    kernel from 5 on), every op checked against the oracle."""
     shrink = {4096: 512, 11008: 1376}
     ops, widths, layers, bufs = build_stack("7b", 2, 5, T, derived=False, shrink=shrink, outliers=True,
                                             gain=100.0)
     _run_and_check(ops, widths, layers, bufs, T, "prepared small batch", prepared=True)
+
+
+@pytest.mark.parametrize("T", [5, 6, 7])
+def test_prepared_stacks_of_five_to_seven_tokens(T):
+    """The first token counts of the few-token kernel, ragged rows (1370 is no multiple of 8): every op against the
+    oracle, and a second run of the plan repeats the first bit for bit."""
+    shrink = {4096: 512, 11008: 1376}
+    ops, widths, layers, bufs = build_stack("7b", 2, 5, T, derived=False, shrink=shrink, outliers=True, gain=100.0)
+    _run_and_check(ops, widths, layers, bufs, T, "prepared stack", prepared=True)
+    rng = synth.child_rng(3, 513, T)
+    layers = [random_layer(rng, 2, 1370, 512, gain=100.0), random_layer(rng, 2, 90, 512, gain=100.0)]
+    bufs = [torch.from_numpy(synth.outlier_activations(rng, T, 512)).cuda()]
+    bufs += [torch.zeros((T, w), dtype=torch.float16, device="cuda") for w in (1370, 90)]
+    stack = rb.Stack([to_device_layer(*l) for l in layers], [(0, 0, 1), (1, 0, 2)], bufs, T)
+    stack.prepare()
+    runs = []
+    for _ in range(2):
+        stack.run_prepared()
+        torch.cuda.synchronize()
+        runs.append([b.clone() for b in bufs])
+    assert rb.rb_last_path() == rb.RB_PATH_BATCH and stack.status() == rb.RB_OK
+    stack.forget()
+    for n in range(2):
+        assert torch.equal(runs[0][n + 1], runs[1][n + 1])
+        ref = oracle.forward(*layers[n], bufs[0].cpu().numpy())
+        assert oracle.relative_l2(bufs[n + 1].cpu().numpy().astype(np.float64), ref).max() <= TOL
 
 
 def test_one_13b_block_derived():
@@ -252,8 +278,7 @@ def test_full_7b_stack_as_benchmarked_sampled_outputs():
 
 
 def test_three_path_layers_in_a_stack():
-    """K = 3 layers in a stack of two tokens run on the small-batch matrix-core kernel (three right
-    operands per 128 columns), every op checked against the oracle."""
+    """K = 3 layers in a stack of two tokens run on the few-token kernel, every op checked against the oracle."""
     rng = synth.child_rng(3, 88)
     shapes = [(192, 256), (320, 192), (192, 320)]              # x -> a -> b -> c
     layers = []
@@ -560,8 +585,8 @@ def test_stack_decode_kernel_with_degenerate_scales_and_extreme_inputs(T):
 
 @pytest.mark.parametrize("T,n_chain", [(3, 2), (5, 2), (3, 8), (5, 8)])
 def test_prepared_odd_batches_on_pure_chains(T, n_chain):
-    """Odd T on a chain in which every op is a stage of its own: the last pass holds one token, and
-    the workspace that rb_workspace_bytes reports must be enough for it."""
+    """Odd T on a chain in which every op is a stage of its own: the workspace that rb_workspace_bytes reports
+    must be enough for it."""
     rng = synth.child_rng(3, 500 + 10 * T + n_chain)
     d = 4096
     layers = [random_layer(rng, 2, d, d, gain=100.0) for _ in range(n_chain)]

@@ -178,11 +178,11 @@ def test_storage_accounting_reproduces_effective_bits():
 
 
 def test_many_token_workspace_counts_the_shared_last_round():
-    """The many-token GEMM needs 256 bytes for the power-of-two scalings, 256 bytes per 32-column
-    group for the input scales in operand order, the input in fp16 in contraction order (T x in)
-    and, when the output tiles (256 rows x 256 tokens) do not fill whole rounds of the device's 256
+    """What a call of many tokens asks for, kept from a kernel that needed all of it: 256 bytes, 256 bytes
+    per 32-column group (the present kernel: scales off alignment), the input (an output that overlaps it)
+    and, when tiles of 256 rows x 256 tokens do not fill whole rounds of the device's 256
     compute units, fp32 partial sums for the row blocks of the last round, one copy per workgroup
-    that shares a tile."""
+    that shares a tile (not used any more)."""
     def need(out, inn, T):
         L = rb.binding.rb_layer(out, inn, 2, 0x1000, 0x2000, 0x3000)
         return rb.lib.rb_workspace_bytes(ctypes.byref(L), 1, 1, T)
