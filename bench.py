@@ -192,7 +192,7 @@ def main() -> int:
     ap.add_argument("--prefill-only", action="store_true",
                     help="only the prefill GEMM figures (for profiling that kernel)")
     ap.add_argument("--batch-only", type=int, default=0, metavar="T",
-                    help="only the dependent 7B-shaped chain at T tokens (8..16) on the small-batch kernel (for profiling it)")
+                    help="only the dependent 7B-shaped chain at T tokens (5..16) on the few-token kernel (for profiling it)")
     ap.add_argument("--block-only", type=int, default=0, metavar="T",
                     help="only the 7B-shaped decoder-block stack at T tokens (1..4) on the fused kernel (for profiling it)")
     ap.add_argument("--train-only", action="store_true",
@@ -376,7 +376,7 @@ def main() -> int:
         stack2.forget()
         del ops2, layers2, bufs2, stack2
         # three paths (the paper's 3-bit variant), the whole 7B-shaped chain: one token on the fused
-        # decode kernel (one launch), eight on the small-batch kernel (one launch per group of independent ops)
+        # decode kernel (one launch), eight on the few-token kernel (one launch per group of independent ops)
         three = {}
         for T3 in (1, 8):
             ops3, layers3, bufs3, op_list3, packed3 = build_stack(rb, synth, torch, "7b", T3, K=3)
@@ -461,9 +461,9 @@ def main() -> int:
         result["speedup_vs_dense_fp16"] = result["tokens_per_s"] / result["dense_fp16_gemv"]["tokens_per_s"]
         result["paper_context"] = "RTX 4090: 291.88 tok/s = 4.49x FP16, whole Llama2-7B model (inference table)"
         result["prefill_gemm_T2048"] = prefill_figures(rb, torch)
-        # small decode batches (configs[2]): the 7B-shaped stack, every op on its own input buffer.
+        # small decode batches: the 7B-shaped stack, every op on its own input buffer.
         # 2 and 4 tokens: the fused decode kernel, one launch (four tokens are two pairs that share the
-        # expanded signs).  8 and 16 tokens: the small-batch kernel,
+        # expanded signs).  8 and 16 tokens: the few-token kernel,
         # one pass over the weights, one launch per group of independent ops.
         skinny = {}
         for Ts in (2, 4, 8, 16):
@@ -482,7 +482,7 @@ def main() -> int:
                 "kernel": "small-batch kernel" if path == rb.RB_PATH_BATCH else "fused decode kernel",
                 "entry_point": "rb_stack_run"}
             del fbs, outs_s, st_s
-        # the dependent 7B-shaped chain at 8 and 16 tokens (the small-batch kernel)
+        # the dependent 7B-shaped chain at 8 and 16 tokens (the few-token kernel)
         for Ts in (8, 16):
             ops_b, layers_b, bufs_b, op_list_b, _ = build_stack(rb, synth, torch, "7b", Ts)
             st_b = rb.Stack(layers_b, op_list_b, bufs_b, Ts)

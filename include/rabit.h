@@ -129,9 +129,12 @@ int rb_linear_gemm(const rb_layer *L, const void *X, void *Y, int T,
  * status codes as rb_linear_gemm without the workspace pair; the scratch memory of the many-token
  * kernel is a device array inside the library (RB_NOALLOC_SCRATCH_BYTES per GPU that uses the
  * library, held until the process ends).  The call allocates nothing on host or device.  It returns
- * RB_ERR_WORKSPACE when rb_workspace_bytes(L, 1, 1, T) of the many-token kernel (more than 64
- * tokens) exceeds RB_NOALLOC_SCRATCH_BYTES (T_padded * in above 16 M elements; a three-path layer
- * that wide takes the generic kernel at up to 32 tokens).  Every call on one GPU
+ * RB_ERR_WORKSPACE when, beyond 64 tokens, rb_workspace_bytes(L, 1, 1, T) exceeds
+ * RB_NOALLOC_SCRATCH_BYTES (it counts 2 bytes per element of the input, padded to 256 tokens, and
+ * up to 16 bytes per output where tiles of 256 x 256 outputs leave part of the device's last round
+ * empty: 4096 x 4096 exceeds 32 MB at 512 tokens, 28672 x 8192 at 128 but not at 300), and at up
+ * to 64 tokens when Y overlaps an X larger than that.  A three-path layer of some 64 K columns or
+ * more, whose workspace would exceed it, takes the generic kernel at up to 32 tokens.  Every call on one GPU
  * shares that GPU's array: calls that may overlap in time on one GPU (different streams or
  * threads) race and must be ordered by the caller; calls on one stream are ordered already.
  * rb_noalloc_scratch_bytes returns RB_NOALLOC_SCRATCH_BYTES.
@@ -178,8 +181,9 @@ int rb_layer_stack(const rb_layer *layers, int n_layers,
  * layer: T = 1 as one launch, 2 <= T <= 16 on the few-token kernel, which
  * also takes stacks that mix two- and three-path layers.
  * rb_stack_prepare returns RB_ERR_UNSUPPORTED for stacks that only
- * rb_layer_stack's general path can run (K = 1, T > 16, an output read by more
- * than three ops, more than 1024 ops fed from outside the stack).
+ * rb_layer_stack's general path can run (K = 1, T > 16, a single op of more than four
+ * tokens and, where the stack would run as one launch, an output read by more
+ * than three ops or more than 1024 ops fed from outside the stack).
  */
 int rb_stack_prepare(const rb_layer *layers, int n_layers,
                      const rb_stack_op *ops, int n_ops,
@@ -294,13 +298,13 @@ int rb_stream_read_groups(void);
 
 /* Which kernel family the most recent compute call of this thread enqueued:
  * RB_PATH_NONE, RB_PATH_SIGNADD (generic sign-XOR + add kernel, one launch per
- * op), RB_PATH_GEMM (matrix-core GEMM of a single call: the few-token or the many-token kernel, one
- * launch per op),
+ * op), RB_PATH_GEMM (matrix-core GEMM of a single call: the few-token kernel up to
+ * 64 tokens, the many-token kernel beyond, one launch per op),
  * RB_PATH_MX (matrix-core decode kernels: one layer and token in one launch,
  * or all ops of a stack in one persistent launch) or RB_PATH_BATCH (few-token
  * kernel of a stack: one pass over the weights for up to 16 tokens, two or
- * three paths, one launch per group of independent ops; also a single three-path
- * call of 6 to 12 fp16 tokens).  For tests and
+ * three paths, one launch per group of independent ops; also rb_linear_gemm on a
+ * three-path layer with 6 to 12 fp16 tokens).  For tests and
  * benchmarks that must know what they measured. */
 #define RB_PATH_NONE    0
 #define RB_PATH_SIGNADD 1

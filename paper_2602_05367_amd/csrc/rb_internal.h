@@ -15,7 +15,7 @@ int launch_signadd(const rb_layer *L, const void *X, void *Y, int T, int act_dty
                    hipStream_t stream);
 
 size_t workspace_bytes(const rb_layer *layers, int n_layers, int n_ops, int T);
-// stacks that run on the small-batch kernel (see rb_dispatch.hip)
+// stacks that run on the few-token kernel (see rb_dispatch.hip)
 bool batch_applies(const rb_layer *layers, int n_layers, int T);
 // a single call takes the few-token kernel; of T tokens on this layer, the many-token kernel (given
 // the scratch memory it needs)
