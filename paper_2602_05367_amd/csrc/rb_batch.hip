@@ -9,7 +9,7 @@
 // v_mfma_f32_16x16x32_bf16 as they are, against two left operands, as an fp16 scale is the exact sum of two bf16
 // values (three vector instructions in place of two and twice the matrix instructions).  Up to 16 tokens only
 // where it must be: 128 columns whose values fp16 holds exactly (zeros, 2^-17 up to 65536, which is nearly all there is) are
-// multiplied as fp16, the others after them (28672 x 8192 at 5 tokens 36 us, 47 with two operands throughout, 33 with
+// multiplied as fp16, the others after them (28672 x 8192 at 5 tokens 34 us, 47 with two operands throughout, 33 with
 // unchecked fp16 copies).  What bounds it:
 //   * a launch of a 4096-wide op moves 4 MB of signs, half a microsecond of HBM time, so it is a
 //     chain of latencies (launch, one trip to memory, the matrix instructions, the sum over the
@@ -30,7 +30,7 @@
 // order, the output scales fetched at the end: 1.42 and 1.61; bf8 term expansions of the activations in LDS, which
 // this kernel replaced: 2.51 and 3.09); a launch takes 6.3 us (4096 x 4096, one row tile per workgroup) to 16 us
 // (2 x 11008 x 4096, six), of which a dependent launch by itself is 4.7.  Single calls: 4096 x 11008
-// with three paths at 16 tokens 12.7 us, 10999 x 4128 with two at 7 tokens of bfloat16 13 us.
+// with three paths at 16 tokens 12.7 us, 10999 x 4128 with two at 7 tokens 9.7 us, of bfloat16 10.7.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 

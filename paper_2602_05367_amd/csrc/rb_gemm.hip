@@ -29,10 +29,10 @@
 //   * the left operand of the next row block is built between the matrix instructions of this one.
 //
 // Measured (before: a 256 x 256 tile on four wavefronts behind four pre-pass launches and, for most
-// sizes, a launch that added partial sums; stores of single elements), fp16, two paths:
-// 4096 x 4096 at 333 tokens 85 -> 31 us, 11008 x 4096 116 -> 55 us, 4096 x 11008 124 -> 64 us, at 512
-// tokens 132 -> 79 us; 8192 x 8192 at 1024 tokens 198 -> 138 us (1.0 PFLOP/s), 28672 x 8192
-// at 2048 tokens of bfloat16 1.03 -> 0.99 ms.
+// sizes, a launch that added partial sums; stores of single elements), fp16, two paths, calls in a row in a graph:
+// 4096 x 4096 at 333 tokens 82 -> 28 us, 11008 x 4096 108 -> 51 us, 4096 x 11008 124 -> 63 us, at 512
+// tokens 125 -> 72 us; 8192 x 8192 at 1024 tokens 208 -> 150 us (0.92 PFLOP/s), 28672 x 8192
+// at 2048 tokens of bfloat16 1.02 -> 0.96 ms.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 

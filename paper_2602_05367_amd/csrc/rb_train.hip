@@ -41,8 +41,8 @@ constexpr int COUPLE_CHUNK = 512, COUPLE_ROWS = 4;      // columns and rows one 
 // the eight lanes gives the words.  The residual is fp32 with one rounding for g * h and one for
 // the subtraction, the arithmetic the definition fixes (the sign of the product is exact).
 // Bound by the read of W and, close behind, by vector instructions (some 35 per four weights and path).
-// 4096 x 11008, two paths: 55 us (74 with one row per wavefront, native words stored one by one
-// and zeroed before).
+// 4096 x 11008, two paths, under the profiler: 56 us (64 with one row per wavefront and native words stored one by one,
+// and 6 for zeroing them before).
 template <int K>
 __global__ __launch_bounds__(256) void couple_kernel(const float *__restrict__ W, const __half *__restrict__ g,
                                                      const __half *__restrict__ h, int out, int in,
