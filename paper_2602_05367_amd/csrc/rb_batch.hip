@@ -9,8 +9,8 @@
 // v_mfma_f32_16x16x32_bf16 as they are, against two left operands, as an fp16 scale is the exact sum of two bf16
 // values (three vector instructions in place of two and twice the matrix instructions).  Up to 16 tokens only
 // where it must be: 128 columns whose values fp16 holds exactly (zeros, 2^-17 up to 65536, which is nearly all there is) are
-// multiplied as fp16, the others after them (28672 x 8192 at 5 tokens 34 us, 47 with two operands throughout, 33 with
-// unchecked fp16 copies).  What bounds it:
+// multiplied as fp16, the others after them (28672 x 8192 at 5 tokens 28 us; in an earlier form of this kernel 34, 47 with two
+// operands throughout, 33 with unchecked fp16 copies).  What bounds it:
 //   * a launch of a 4096-wide op moves 4 MB of signs, half a microsecond of HBM time, so it is a
 //     chain of latencies (launch, one trip to memory, the matrix instructions, the sum over the
 //     wavefronts): the compute units are filled and every wavefront asks for all it needs at once, the
@@ -19,18 +19,22 @@
 //     columns for one row tile took 14.6 us, the transposition through LDS below takes 11);
 //   * beyond that, vector instructions: two per two weights and path (a shift and one three-input logic
 //     operation), where the matrix instructions of 16 tokens take a third of their time.
-// Shape: a workgroup owns P row tiles (16 rows) and all columns; its up to sixteen wavefronts share out the
-// column tiles, each takes all P row tiles of its columns, so an activation is read from memory by
-// one wavefront of the workgroup.  The partial outputs of the wavefronts meet in LDS and are added in
+//   * the number of load instructions: one that fetches nothing (past the end, or a second unit asked for ahead of
+//     time) takes its turn in the address unit all the same, and asking two units ahead made every launch slower (7B chain
+//     at 16 tokens 1.47 ms).
+// Shape: a workgroup owns P row tiles (16 rows) and all columns; its wavefronts share out the columns in runs of
+// 128 (so that 17 column tiles do not take twice as long as 16), each takes all P row tiles of its columns, so an activation is
+// read from memory by one wavefront of the workgroup.  The partial outputs of the wavefronts meet in LDS and are added in
 // a fixed order.  Nothing is exchanged between workgroups: no counters, no scratch memory, results do
 // not depend on scheduling.  The ops of a stack that do not depend on each other (q/k/v, gate/up of
 // a transformer block) run in one launch; dependent ones are ordered by the stream.
 //
-// Measured: 7B-shaped dependent chain, 128 launches, 1.30 ms at 8 tokens and 1.37 ms at 16 (activations in operand
-// order, the output scales fetched at the end: 1.42 and 1.61; bf8 term expansions of the activations in LDS, which
-// this kernel replaced: 2.51 and 3.09); a launch takes 6.3 us (4096 x 4096, one row tile per workgroup) to 16 us
-// (2 x 11008 x 4096, six), of which a dependent launch by itself is 4.7.  Single calls: 4096 x 11008
-// with three paths at 16 tokens 12.7 us, 10999 x 4128 with two at 7 tokens 9.7 us, of bfloat16 10.7.
+// Measured (in brackets the form before this one: whole column tiles per wavefront, loads in branches, which made the
+// waits coarse and took up to 60 registers more, one workgroup per compute unit): 7B-shaped dependent chain, 128 launches, 1.19 ms
+// at 5 tokens and 1.32 at 16 (1.26, 1.37); 13B-shaped, three paths, 32 launches, 6 tokens 0.57 ms (0.62).  Of a launch 1.4 us pass
+// between the last wavefront of one and the first of the next, and 1.2 until the first activations are there.  Single calls
+// in a graph: 28672 x 8192 at 16 tokens 28.5 us (33.5), 10999 x 4128 at 4 9.0 (9.9), 4096 x 4096 at 4 5.2 (5.5), 11008 x 4096 at 48
+// 16.8 (28.9), three paths 13824 x 5120 at 48 34.4 (53.8).
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
@@ -54,20 +58,26 @@ namespace batch {
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
+typedef unsigned v3u __attribute__((ext_vector_type(3)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef __bf16 v8b __attribute__((ext_vector_type(8)));
 
 constexpr int STACK_MAX_T = 16;        // tokens of a stack
 constexpr int MAX_STAGE_OPS = 8;       // independent ops that share a launch
 
-// Wavefronts of a workgroup at most, and row tiles per workgroup: accumulators take 4 P K G
-// registers, sign words 2 P K, staged activations 16 G, of 128 with sixteen wavefronts per compute unit
-// and 256 with eight (two paths, six row tiles, 16 tokens: 28.6 us a launch of 2 x 11008 x 4096 with sixteen, which
-// spills, 16.2 with eight; four row tiles, 8 tokens, 7B chain: the same either way).  Two paths, four token groups, two row
-// tiles spill 14 registers and are worth it: 8192 x 8192 at 64 tokens 30.4 us, 39.0 with one row tile
-__host__ __device__ constexpr int max_waves(int K, int G, int P) { return G == 1 && P * K <= 8 ? 16 : 8; }
-__host__ __device__ constexpr bool p_available(int K, int G, int P) { return P == 1 || P * K <= (G == 1 ? 12 : G == 2 ? 6 : 4); }
+// The forms of a workgroup.  Row tiles: as many as fit without spilling (accumulators take 4 P K G registers, sign words 2 P K, staged
+// activations 16 G); with four token groups three for two paths and two for three (11008 x 4096 at 64 tokens 18.9 us, 26.5
+// with two; 13824 x 5120, three paths, 39.0 and 54.5 with one), but not for bfloat16, whose two left operands would spill
+// 64 registers (28672 x 8192: 192 us, 125 with two).  Wavefronts: eight, of which two workgroups share a compute unit where 128
+// registers are enough, so that one multiplies while the other waits for memory and more workgroups than compute units
+// still run at once (28672 x 8192 at 16 tokens: 448 workgroups of four row tiles 28.9 us, with sixteen wavefronts each, in two
+// rounds, 32.2); sixteen for one or two row tiles in a launch that has no second workgroup for a compute unit (4096 x 11008
+// at 16 tokens 9.9 us, 11.7 with eight; for three and four row tiles it makes no difference).
+__host__ __device__ constexpr bool p_available(int K, int G, int P, bool bf16) { return P == 1 || P * K <= (G == 1 ? 12 : G == 2 ? 8 : bf16 ? 4 : 6); }
+__host__ __device__ constexpr bool two_share(int K, int G, int P) { return G == 1 ? P * K <= 9 : G == 2 && P == 1; }
+__host__ __device__ constexpr bool sixteen_available(int G, int P) { return (G == 1 && P <= 2) || (G == 2 && P == 1); }
 
+// One op of a launch, 64 bytes: everything a workgroup needs comes with one load of scalars
 struct Op {
     const uint32_t *bits;     // native sign tiles
     const uint16_t *g;        // fp16 [K][out]
@@ -75,17 +85,13 @@ struct Op {
     const void *x;            // [T][in]
     void *y;                  // [T][out]
     int out, in;
-    int h_aligned;            // h starts at a multiple of 16 bytes (its rows then do too)
-    int pad_;
+    int T, out_dtype;
+    uint16_t waves, rest;     // wavefronts of a workgroup; each takes `run` units, the first `rest` one more
+    int run;
 };
-// everything a launch needs, passed by value: no table in memory to fetch before the work starts.  What
-// decides which op a workgroup belongs to comes first, in one piece: it costs one trip to the arguments, the op another
-struct Args {
-    int T, out_dtype, nops;
-    int wg0[MAX_STAGE_OPS];   // first workgroup of each op (past the last op: more than there are)
-    int pad_[5];
-    Op op[MAX_STAGE_OPS];
-};
+// everything a launch needs, passed by value: no table in memory to fetch before the work starts.  The op
+// of a workgroup is its blockIdx.y
+struct Args { Op op[MAX_STAGE_OPS]; };
 
 // ------------------------------------------------------------------- kernel ---
 // eight values in memory order as the pairs (e, e + 4), e = 0..3: the order in which one shift of a
@@ -119,20 +125,24 @@ __device__ __forceinline__ void split_scales(uint4 h, uint4 &high, uint4 &low)
     }
 }
 
-// the 2 K words (word c * K + k: path k, columns 128 c + 32 (lane / 16) ..) of one lane of a sign tile
-template <int K> struct Words { uint32_t w[2 * K]; };
-template <int K> __device__ __forceinline__ Words<K> load_words(const uint32_t *p)
+// loads that return zero past the end of their buffer (NOWHERE always is): no branch around any of them, so that the
+// waits count exactly what came after
+constexpr uint32_t NOWHERE = 0x40000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void *p, size_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
+}
+// the K words of one lane for half a sign tile (path k, columns 32 (lane / 16) .. of the 128)
+template <int K> struct Words { uint32_t w[K]; };
+template <int K> __device__ __forceinline__ Words<K> load_words(__amdgpu_buffer_rsrc_t rs, uint32_t lane_offset, int offset)
 {
     Words<K> r;
     if constexpr (K == 2) {
-        const v4u v = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(p));
-        r.w[0] = v.x; r.w[1] = v.y; r.w[2] = v.z; r.w[3] = v.w;
+        const v2u v = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)lane_offset, offset, 0));
+        r.w[0] = v.x; r.w[1] = v.y;
     } else {
-#pragma unroll
-        for (int i = 0; i < K; ++i) {
-            const v2u v = __builtin_nontemporal_load(reinterpret_cast<const v2u *>(p) + i);
-            r.w[2 * i] = v.x; r.w[2 * i + 1] = v.y;
-        }
+        const v3u v = __builtin_bit_cast(v3u, __builtin_amdgcn_raw_buffer_load_b96(rs, (int)lane_offset, offset, 0));
+        r.w[0] = v.x; r.w[1] = v.y; r.w[2] = v.z;
     }
     return r;
 }
@@ -166,87 +176,78 @@ __device__ __forceinline__ uint4 pair_order_as_fp16(uint4 v)
 constexpr int UNIT_COLS = 128, ROW_BYTES = 256;      // columns a wavefront stages at a time; a token's fp16 values of them
 template <int K, int G, bool BF16> __host__ __device__ constexpr int slab_bytes() { return (16 * G + K * (BF16 ? 2 : 1)) * ROW_BYTES; }
 
-// K paths, G groups of 16 tokens, P row tiles per workgroup, BF16: the activations are bfloat16
-template <int K, int G, int P, bool BF16>
-__global__ __launch_bounds__(max_waves(K, G, P) * 64, 1) void batch_kernel(const Args args)
+// K paths, G groups of 16 tokens, P row tiles per workgroup of W wavefronts at most, BF16: the activations are bfloat16
+template <int K, int G, int P, int W, bool BF16>
+__global__ __launch_bounds__(W * 64, two_share(K, G, P) ? 4 : 2) void batch_kernel(const Args args)
 {
-    constexpr bool AHEAD = P * K <= (G == 1 ? 6 : 4) && G <= 2;       // registers for the sign words of the next column tile
     // bfloat16: fp16 copies of the units that fp16 holds, the others after them as they are.  Beyond one token group looking at a
     // unit costs what the copies save (4096 x 4096 at 24 tokens: 9.3 us with copies unlooked at, 11.5 with the look, 9.2
     // without copies; at 64, 14.2 without copies)
     constexpr bool EITHER = BF16 && G == 1;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];    // a slab per wavefront; then [wavefront][row tile][token][row] sums
     __shared__ __attribute__((aligned(16))) float g_lds[P * K * TILE_ROWS];      // [path][row tile][row]
-    const int tid = threadIdx.x, lane = tid & 63, nw = (int)blockDim.x >> 6;
+    const Op op = args.op[blockIdx.y];
+    // (all of it at once: left to itself the compiler fetches it in four trips, each where it is used first)
+    asm volatile("" :: "s"(op.bits), "s"(op.g), "s"(op.h), "s"(op.x), "s"(op.y), "s"(op.out), "s"(op.in), "s"(op.T), "s"(op.out_dtype), "s"((int)op.waves), "s"(op.run));
+    const int tid = threadIdx.x, lane = tid & 63, nw = op.waves, threads = nw * 64;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, q = lane >> 4;
-    int o = 0, first = 0;
-#pragma unroll
-    for (int i = 1; i < MAX_STAGE_OPS; ++i)
-        if ((int)blockIdx.x >= args.wg0[i]) { o = i; first = args.wg0[i]; }
-    const Op &op = args.op[o];
-    const int out = op.out, in = op.in, T = args.T;
-    const int RT = row_tiles(out), CT = col_tiles(in);
-    const int rt0 = ((int)blockIdx.x - first) * P;
+    const int out = op.out, in = op.in, T = op.T;
+    const int RT = row_tiles(out), CT = col_tiles(in), rt0 = (int)blockIdx.x * P;
+    if (rt0 >= RT) return;                                     // (an op with fewer row tiles than another one of the launch)
 
-    // the row tiles of this workgroup; one past the end of the matrix reads the last one (not stored)
-    const uint32_t *bits[P];                                   // (uniform: the lane's offset is added at the load)
-#pragma unroll
-    for (int p = 0; p < P; ++p) bits[p] = op.bits + (size_t)min(rt0 + p, RT - 1) * CT * tile_words(K);
-    const uint32_t lane_words = (uint32_t)lane * 2u * K;
-
-    Words<K> w[P];
-    if (wave < CT)
-#pragma unroll
-        for (int p = 0; p < P; ++p) w[p] = load_words<K>(bits[p] + (size_t)wave * tile_words(K) + lane_words);
-
+    // ---- a wavefront takes a run of units of 128 columns, half a sign tile wide
+    const int u0 = wave * op.run + min(wave, (int)op.rest), u1 = u0 + op.run + (wave < op.rest ? 1 : 0);
     // ---- staging.  A load instruction fetches 256 contiguous bytes of four tokens (a token per 16 lanes: 16
     // chunks of eight columns), so it touches eight lines; fetched in operand order it would touch 32 and
     // the address unit would bound the kernel.  Chunk 4 q + s (columns 32 q + 8 s ..) of a row goes to position
     // (4 s + q) ^ (row % 16) of the wavefront's own slab: neither these writes nor the operand reads collide
     const int ch = lane & 15, row4 = lane >> 4, pos = (ch & 3) * 4 + (ch >> 2);
     uint8_t *const slab = lds + (size_t)wave * slab_bytes<K, G, BF16>();
-    uint32_t x_off[4 * G];
+    const __amdgpu_buffer_rsrc_t x_rs = buffer(op.x, (size_t)T * in * 2);
+    const __amdgpu_buffer_rsrc_t w_rs = buffer(op.bits + (size_t)rt0 * CT * tile_words(K), (size_t)min(P, RT - rt0) * CT * tile_words(K) * 4);
+    uint32_t x_off[4 * G];                                     // (rows of no token are not fetched)
 #pragma unroll
-    for (int i = 0; i < 4 * G; ++i) x_off[i] = (uint32_t)min(4 * i + row4, T - 1) * (uint32_t)in + 8u * (uint32_t)ch;
+    for (int i = 0; i < 4 * G; ++i) x_off[i] = 4 * i + row4 < T ? ((uint32_t)(4 * i + row4) * (uint32_t)in + 8u * (uint32_t)ch) * 2u : NOWHERE;
+    const uint32_t h_row = (uint32_t)row4 * (uint32_t)in;
     uint4 xs[4 * G], hs;
-    auto request = [&](int j0) {
-        const bool real = j0 + 8 * ch < in;                    // in % 32 == 0: all eight columns or none
-        const uint16_t *const x = static_cast<const uint16_t *>(op.x) + j0;
+    Words<K> ws[P];
+    auto real = [&](int u) { return u * UNIT_COLS + 8 * ch < in; };              // in % 32 == 0: all eight columns or none
+    auto request = [&](int u) {
+        const bool some = real(u);
 #pragma unroll
-        for (int i = 0; i < 4 * G; ++i) {
-            xs[i] = make_uint4(0u, 0u, 0u, 0u);
-            if (4 * i < T && real) xs[i] = *reinterpret_cast<const uint4 *>(x + x_off[i]);       // (rows of no token are not looked at)
-        }
-        hs = make_uint4(0u, 0u, 0u, 0u);
-        if (row4 < K && real) {
-            const uint16_t *const h = op.h + (size_t)row4 * in + j0 + 8 * ch;
-            if (op.h_aligned) hs = *reinterpret_cast<const uint4 *>(h);
-            else                                               // the scales need only be 2-byte aligned
-                hs = make_uint4((uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16,
-                                (uint32_t)h[4] | (uint32_t)h[5] << 16, (uint32_t)h[6] | (uint32_t)h[7] << 16);
-        }
+        for (int i = 0; i < 4 * G; ++i)
+            if (4 * i < T) xs[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(x_rs, (int)(some ? x_off[i] : NOWHERE), u * ROW_BYTES, 0));
+        // (the scales need only be 2-byte aligned)
+        if (row4 < K) __builtin_memcpy(&hs, op.h + u * UNIT_COLS + (h_row + (some ? 8u * (uint32_t)ch : 0u)), 16);
+    };
+    auto request_words = [&](int u) {
+#pragma unroll
+        for (int p = 0; p < P; ++p)                            // a row tile past the end of the matrix reads as zero (not stored)
+            ws[p] = load_words<K>(w_rs, (rt0 + p < RT ? 0u : NOWHERE) + (uint32_t)lane * 8u * K, ((p * CT + (u >> 1)) * tile_words(K) + (u & 1) * K) * 4);
     };
     auto put_x = [&](auto order) {
 #pragma unroll
-        for (int i = 0; i < 4 * G; ++i) {
-            const int row = 4 * i + row4;
-            if (4 * i < T) *reinterpret_cast<uint4 *>(slab + row * ROW_BYTES + ((pos ^ (row & 15)) * 16)) = order(xs[i]);
-        }
+        for (int i = 0; i < 4 * G; ++i)
+            if (4 * i < T) *reinterpret_cast<uint4 *>(slab + (4 * i + row4) * ROW_BYTES + ((pos ^ ((4 * i + row4) & 15)) * 16)) = order(xs[i]);
     };
     auto put_h = [&](int m, uint4 v) { *reinterpret_cast<uint4 *>(slab + (16 * G + m * K + row4) * ROW_BYTES + pos * 16) = pair_order(v); };
+    auto scales = [&](int u) {
+        const uint32_t all = real(u) ? ~0u : 0u;
+        return make_uint4(hs.x & all, hs.y & all, hs.z & all, hs.w & all);
+    };
     // fp16 activations, or fp16 copies of bfloat16 ones
-    auto put = [&]() {
+    auto put = [&](int u) {
         if constexpr (EITHER) put_x([](uint4 v) { return pair_order_as_fp16(v); });
         else put_x([](uint4 v) { return pair_order(v); });
-        if (row4 < K) put_h(0, hs);
+        if (row4 < K) put_h(0, scales(u));
         __builtin_amdgcn_wave_barrier();
     };
-    auto put_wide = [&]() {
+    auto put_wide = [&](int u) {
         put_x([](uint4 v) { return pair_order(v); });
         if (row4 < K) {
             uint4 high, low;
-            split_scales(hs, high, low);
+            split_scales(scales(u), high, low);
             put_h(0, high);
             put_h(1, low);
         }
@@ -259,15 +260,15 @@ __global__ __launch_bounds__(max_waves(K, G, P) * 64, 1) void batch_kernel(const
             if (4 * i < T) range.look_at(xs[i]);
         return (bool)__any(range.beyond_fp16());
     };
-    if (wave < CT) request(wave * TILE_COLS);
+    request(u0);
+    request_words(u0);
     // output scales, asked for now, shared through LDS when the sums are there
     constexpr int GV = (P * K * TILE_ROWS + 63) / 64;            // (a workgroup may have one wavefront only)
     uint16_t gval[GV];
 #pragma unroll
     for (int i = 0; i < GV; ++i) {
-        const int at = tid + i * (int)blockDim.x, row = min(rt0 * TILE_ROWS + at % (P * TILE_ROWS), out - 1), k = min(at / (P * TILE_ROWS), K - 1);
-        gval[i] = 0;
-        if ((int)blockDim.x * i < P * K * TILE_ROWS) gval[i] = op.g[(size_t)k * out + row];
+        const int at = tid + i * threads, row = min(rt0 * TILE_ROWS + at % (P * TILE_ROWS), out - 1), k = min(at / (P * TILE_ROWS), K - 1);
+        gval[i] = op.g[(size_t)k * out + row];
     }
     v4f acc[P][K][G];
 #pragma unroll
@@ -279,7 +280,7 @@ __global__ __launch_bounds__(max_waves(K, G, P) * 64, 1) void batch_kernel(const
 
     const int x_addr = r * ROW_BYTES + ((q ^ r) * 16), h_addr = 16 * G * ROW_BYTES + q * 16;
     // a unit: TERMS left operands per path and row tile
-    auto contract = [&](auto terms, int c) {
+    auto contract = [&](auto terms, const Words<K> (&w)[P]) {
         constexpr int TERMS = decltype(terms)::value, UNROLL = EITHER && TERMS == 2 ? 1 : 4;
 #pragma unroll UNROLL
         for (int s = 0; s < 4; ++s) {
@@ -301,7 +302,7 @@ __global__ __launch_bounds__(max_waves(K, G, P) * 64, 1) void batch_kernel(const
                         v4u a;
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
-                            a[e] = reinterpret_cast<const uint32_t *>(&hv[k][m])[e] ^ ((w[p].w[c * K + k] << (15 - 4 * e - s)) & 0x80008000u);
+                            a[e] = reinterpret_cast<const uint32_t *>(&hv[k][m])[e] ^ ((w[p].w[k] << (15 - 4 * e - s)) & 0x80008000u);
 #pragma unroll
                         for (int g = 0; g < G; ++g)
                             if constexpr (TERMS == 2) acc[p][k][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b[g]), acc[p][k][g], 0, 0, 0);
@@ -311,48 +312,39 @@ __global__ __launch_bounds__(max_waves(K, G, P) * 64, 1) void batch_kernel(const
         }
     };
     unsigned long long left = 0;                               // EITHER: the units put off, the last bit for all from number 63 on
-    for (int ct = wave; ct < CT; ct += nw) {
-        Words<K> next[P];
-        if (AHEAD && ct + nw < CT)
+#pragma unroll 1
+    for (int u = u0; u < u1; ++u) {
+        const bool late = EITHER && beyond_fp16();
+        if (late) left |= 1ull << min(u - u0, 63);
+        else if (BF16 && !EITHER) put_wide(u);
+        else put(u);
+        Words<K> w[P];
 #pragma unroll
-            for (int p = 0; p < P; ++p) next[p] = load_words<K>(bits[p] + (size_t)(ct + nw) * tile_words(K) + lane_words);
+        for (int p = 0; p < P; ++p)
+            // a copy at this place: one that the compiler puts at the end of the loop would wait for the next words
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const bool late = EITHER && beyond_fp16();
-            if (late) left |= 1ull << min(2 * (ct / nw) + c, 63);
-            else if (BF16 && !EITHER) put_wide();
-            else put();
-            if (c == 0) request(ct * TILE_COLS + UNIT_COLS);
-            else if (ct + nw < CT) request((ct + nw) * TILE_COLS);
-            if (!late) contract(std::integral_constant<int, BF16 && !EITHER ? 2 : 1>(), c);
-            __builtin_amdgcn_wave_barrier();
+            for (int k = 0; k < K; ++k) asm volatile("v_mov_b32 %0, %1" : "=&v"(w[p].w[k]) : "v"(ws[p].w[k]));
+        if (u + 1 < u1) {
+            request(u + 1);
+            request_words(u + 1);
         }
-        if (AHEAD) {
-#pragma unroll
-            for (int p = 0; p < P; ++p) w[p] = next[p];
-        } else if (ct + nw < CT) {
-#pragma unroll
-            for (int p = 0; p < P; ++p) w[p] = load_words<K>(bits[p] + (size_t)(ct + nw) * tile_words(K) + lane_words);
-        }
+        if (!late) contract(std::integral_constant<int, BF16 && !EITHER ? 2 : 1>(), w);
+        __builtin_amdgcn_wave_barrier();
     }
     if (EITHER && left != 0)                                   // (a bit too many costs a second look)
 #pragma unroll 1
-        for (int ct = wave; ct < CT; ct += nw) {
-            if (!(left >> min(2 * (ct / nw), 62) & 3)) continue;
-#pragma unroll
-            for (int p = 0; p < P; ++p) w[p] = load_words<K>(bits[p] + (size_t)ct * tile_words(K) + lane_words);
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                request(ct * TILE_COLS + c * UNIT_COLS);
-                if (!beyond_fp16()) continue;
-                put_wide();
-                contract(std::integral_constant<int, 2>(), c);
-                __builtin_amdgcn_wave_barrier();
-            }
+        for (int u = u0; u < u1; ++u) {
+            if (!(left >> min(u - u0, 63) & 1)) continue;
+            request(u);
+            if (!beyond_fp16()) continue;
+            request_words(u);
+            put_wide(u);
+            contract(std::integral_constant<int, 2>(), ws);
+            __builtin_amdgcn_wave_barrier();
         }
 #pragma unroll
     for (int i = 0; i < GV; ++i) {
-        const int at = tid + i * (int)blockDim.x;
+        const int at = tid + i * threads;
         if (at < P * K * TILE_ROWS) g_lds[at] = __half2float(__ushort_as_half(gval[i]));
     }
     __syncthreads();                                           // the slabs have been read, too: the sums take their place
@@ -377,121 +369,139 @@ __global__ __launch_bounds__(max_waves(K, G, P) * 64, 1) void batch_kernel(const
     }
     __syncthreads();
     // ---- add the wavefronts in order, round, store
-    for (int idx = tid; idx < P * G * 256; idx += (int)blockDim.x) {
+    for (int idx = tid; idx < P * G * 256; idx += threads) {
         const int p = idx / (G * 256), t = idx / 16 % (G * 16), row = (rt0 + p) * TILE_ROWS + idx % 16;
         float s = 0.f;
         for (int v = 0; v < nw; ++v) s += part[v * (P * G * 256) + idx];
-        if (t < T && row < out) store_out(op.y, args.out_dtype, (size_t)t * out + row, s);
+        if (t < T && row < out) store_out(op.y, op.out_dtype, (size_t)t * out + row, s);
     }
 }
 
 // ------------------------------------------------------------------ host ---
 constexpr int ROW_TILES_PER_WG[] = {1, 2, 3, 4, 6};
 
-// Row tiles per workgroup: the device runs the workgroups in rounds of one per compute unit; a
-// round takes as long as its row tiles plus what every workgroup pays once (reading the
-// activations, the latencies, the sum), about one and a half row tiles' worth
-static int row_tiles_per_wg(const int *RT, int nops, int K, int G)
+// Row tiles per workgroup: the busiest compute unit gets `each` workgroups, in rounds of the one or two that run at
+// once.  In units of a row tile's work (0.1 us per column tile) a workgroup costs 0.6 more (its activations, the sum) and a round
+// 33 / column tiles (3.3 us: the latencies).  (16 tokens, two paths, us for 1, 2, 3, 4, 6 row tiles: 12288 x 4096 10.9 10.6 9.1 10.1 12.8;
+// 22016 x 4096 18.3 14.5 13.5 16.4 12.9; 28672 x 8192 39.4 32.6 32.7 28.9 41.5)
+static int row_tiles_per_wg(const int *RT, int nops, int CT, int K, int G, bool bf16)
 {
     const int cus = std::max(1, mx::device_groups());
     int best = 1;
     double best_cost = 0.0;
     for (int P : ROW_TILES_PER_WG) {
-        if (!p_available(K, G, P)) continue;
+        if (!p_available(K, G, P, bf16)) continue;
         int groups = 0;
         for (int i = 0; i < nops; ++i) groups += (RT[i] + P - 1) / P;
-        const double cost = (double)((groups + cus - 1) / cus) * (P + 1.5);
+        const int each = (groups + cus - 1) / cus, rounds = two_share(K, G, P) ? (each + 1) / 2 : each;
+        const double cost = each * (P + 0.6) + rounds * 33.0 / CT;
         if (P == 1 || cost < best_cost) { best = P; best_cost = cost; }
     }
     return best;
 }
 
-template <int K, int G, int P, bool BF16>
-static int launch_form(const Args &args, int groups, int nw, hipStream_t stream)
+template <int K, int G, int P, int W, bool BF16>
+static int launch_form(const Args &args, int nops, int groups, int nw, hipStream_t stream)
 {
-    constexpr int per_wave = std::max(slab_bytes<K, G, BF16>(), P * G * 1024), lds_max = max_waves(K, G, P) * per_wave;
+    constexpr int per_wave = std::max(slab_bytes<K, G, BF16>(), P * G * 1024), lds_max = W * per_wave;
     if (lds_max + P * K * TILE_ROWS * (int)sizeof(float) > 64 * 1024) {
         static std::atomic<bool> allowed[64];
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return RB_ERR_HIP;
         if (!allowed[dev].load()) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(batch_kernel<K, G, P, BF16>), hipFuncAttributeMaxDynamicSharedMemorySize,
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(batch_kernel<K, G, P, W, BF16>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     lds_max) != hipSuccess)
                 return RB_ERR_HIP;
             allowed[dev].store(true);
         }
     }
-    hipLaunchKernelGGL((batch_kernel<K, G, P, BF16>), dim3((unsigned)groups), dim3((unsigned)(nw * 64)), nw * per_wave, stream, args);
+    hipLaunchKernelGGL((batch_kernel<K, G, P, W, BF16>), dim3((unsigned)groups, (unsigned)nops), dim3((unsigned)(nw * 64)), nw * per_wave, stream, args);
     return RB_OK;
 }
 
+template <int K, int G, int P, bool BF16>
+static int launch_waves(const Args &args, int nops, int groups, int nw, hipStream_t stream)
+{
+    if constexpr (sixteen_available(G, P))
+        if (nw > 8) return launch_form<K, G, P, 16, BF16>(args, nops, groups, nw, stream);
+    return launch_form<K, G, P, 8, BF16>(args, nops, groups, nw, stream);
+}
+
 template <int K, int G, bool BF16>
-static int launch_p(const Args &args, int P, int groups, int nw, hipStream_t stream)
+static int launch_p(const Args &args, int nops, int P, int groups, int nw, hipStream_t stream)
 {
     switch (P) {
-    case 1: return launch_form<K, G, 1, BF16>(args, groups, nw, stream);
-    case 2: if constexpr (p_available(K, G, 2)) return launch_form<K, G, 2, BF16>(args, groups, nw, stream); break;
-    case 3: if constexpr (p_available(K, G, 3)) return launch_form<K, G, 3, BF16>(args, groups, nw, stream); break;
-    case 4: if constexpr (p_available(K, G, 4)) return launch_form<K, G, 4, BF16>(args, groups, nw, stream); break;
-    default: if constexpr (p_available(K, G, 6)) return launch_form<K, G, 6, BF16>(args, groups, nw, stream); break;
+    case 1: return launch_waves<K, G, 1, BF16>(args, nops, groups, nw, stream);
+    case 2: if constexpr (p_available(K, G, 2, BF16)) return launch_waves<K, G, 2, BF16>(args, nops, groups, nw, stream); break;
+    case 3: if constexpr (p_available(K, G, 3, BF16)) return launch_waves<K, G, 3, BF16>(args, nops, groups, nw, stream); break;
+    case 4: if constexpr (p_available(K, G, 4, BF16)) return launch_waves<K, G, 4, BF16>(args, nops, groups, nw, stream); break;
+    default: if constexpr (p_available(K, G, 6, BF16)) return launch_waves<K, G, 6, BF16>(args, nops, groups, nw, stream); break;
     }
     return RB_ERR_UNSUPPORTED;
 }
 
 static int token_groups(int T) { return T <= 16 ? 1 : T <= 32 ? 2 : 4; }
 
-// one launch: the ops of `args` (wg0 is filled in here), all of K paths
-struct Shape { int K, P, groups, nw; };
-static Shape shape_of(Args &args, int K)
+// one launch: the first nops ops of `args`, all of K paths and T tokens; P row tiles per workgroup, `groups` workgroups
+// for the op with the most row tiles
+struct Shape { int K, T, nops, P, groups, nw; };
+static Shape shape_of(Args &args, int nops, int K, bool bf16)
 {
-    int RT[MAX_STAGE_OPS], CT = 1;
-    for (int i = 0; i < args.nops; ++i) {
+    int RT[MAX_STAGE_OPS], units = 1;
+    Shape s = {K, args.op[0].T, nops, 0, 0, 0};
+    for (int i = 0; i < nops; ++i) {
         RT[i] = row_tiles(args.op[i].out);
-        CT = std::max(CT, col_tiles(args.op[i].in));
+        units = std::max(units, (args.op[i].in + UNIT_COLS - 1) / UNIT_COLS);
     }
-    Shape s;
-    s.K = K;
-    const int G = token_groups(args.T);
-    s.P = row_tiles_per_wg(RT, args.nops, K, G);
-    s.groups = 0;
-    for (int i = 0; i < MAX_STAGE_OPS; ++i) {
-        args.wg0[i] = i < args.nops ? s.groups : INT_MAX;
-        if (i < args.nops) s.groups += (RT[i] + s.P - 1) / s.P;
+    const int G = token_groups(s.T);
+    s.P = row_tiles_per_wg(RT, nops, (units + 1) / 2, K, G, bf16);
+    int all = 0;
+    for (int i = 0; i < nops; ++i) {
+        s.groups = std::max(s.groups, (RT[i] + s.P - 1) / s.P);
+        all += (RT[i] + s.P - 1) / s.P;
     }
-    s.nw = std::min(CT, max_waves(K, G, s.P));      // a wavefront takes whole column tiles
+    s.nw = std::min(units, sixteen_available(G, s.P) && all <= mx::device_groups() ? 16 : 8);
+    for (int i = 0; i < nops; ++i) {
+        const int n = (args.op[i].in + UNIT_COLS - 1) / UNIT_COLS;
+        args.op[i].waves = (uint16_t)s.nw;
+        args.op[i].run = n / s.nw;
+        args.op[i].rest = (uint16_t)(n % s.nw);
+    }
     return s;
 }
 
 template <bool BF16> static int launch_shape(const Args &args, const Shape &s, hipStream_t stream)
 {
-    const int G = token_groups(args.T);
+    const int G = token_groups(s.T);
     if (s.K == 2)
-        return G == 1 ? launch_p<2, 1, BF16>(args, s.P, s.groups, s.nw, stream)
-             : G == 2 ? launch_p<2, 2, BF16>(args, s.P, s.groups, s.nw, stream)
-                      : launch_p<2, 4, BF16>(args, s.P, s.groups, s.nw, stream);
-    return G == 1 ? launch_p<3, 1, BF16>(args, s.P, s.groups, s.nw, stream)
-         : G == 2 ? launch_p<3, 2, BF16>(args, s.P, s.groups, s.nw, stream)
-                  : launch_p<3, 4, BF16>(args, s.P, s.groups, s.nw, stream);
+        return G == 1 ? launch_p<2, 1, BF16>(args, s.nops, s.P, s.groups, s.nw, stream)
+             : G == 2 ? launch_p<2, 2, BF16>(args, s.nops, s.P, s.groups, s.nw, stream)
+                      : launch_p<2, 4, BF16>(args, s.nops, s.P, s.groups, s.nw, stream);
+    return G == 1 ? launch_p<3, 1, BF16>(args, s.nops, s.P, s.groups, s.nw, stream)
+         : G == 2 ? launch_p<3, 2, BF16>(args, s.nops, s.P, s.groups, s.nw, stream)
+                  : launch_p<3, 4, BF16>(args, s.nops, s.P, s.groups, s.nw, stream);
 }
 
-static Op make_op(const rb_layer &L, const void *x, void *y)
+static Op make_op(const rb_layer &L, const void *x, void *y, int T, int out_dtype)
 {
-    Op o;
+    Op o = {};
     o.bits = static_cast<const uint32_t *>(L.bits);
     o.g = L.g; o.h = L.h;
     o.x = x; o.y = y;
     o.out = L.out; o.in = L.in;
-    o.h_aligned = ((uintptr_t)L.h & 15) == 0; o.pad_ = 0;
+    o.T = T; o.out_dtype = out_dtype;
     return o;
 }
 
-// (the kernel keeps 32-bit offsets into the input)
-static bool supported(const rb_layer *L, int T, int max_T)
+// (calls and stacks of at most this size are this file's; the kernel itself keeps 32-bit offsets into the input and into the signs
+// of a workgroup's row tiles, both below NOWHERE, so wider layers than fit run on the generic kernel)
+static bool sized(const rb_layer *L, int T, int max_T)
 {
     return (L->K == 2 || L->K == 3) && T >= 1 && T <= max_T && L->in % 32 == 0 && (size_t)T * L->in < (size_t)1 << 32;
 }
+static bool kernel_takes(const rb_layer *L, int T) { return L->in < 1 << 24 && (size_t)T * L->in * 2 < NOWHERE; }
 
-bool call_supported(const rb_layer *L, int T) { return supported(L, T, CALL_MAX_T); }
+bool call_sized(const rb_layer *L, int T) { return sized(L, T, CALL_MAX_T); }
 
 int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
                 size_t workspace_bytes, hipStream_t stream)
@@ -502,16 +512,16 @@ int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype,
         copy_aside(X, workspace, input_bytes(L, T), stream);
         X = workspace;
     }
+    if (!kernel_takes(L, T)) return launch_signadd(L, X, Y, T, act_dtype, out_dtype, stream);
     Args args = {};
-    args.nops = 1; args.T = T; args.out_dtype = out_dtype;
-    args.op[0] = make_op(*L, X, Y);
-    const Shape s = shape_of(args, L->K);
+    args.op[0] = make_op(*L, X, Y, T, out_dtype);
+    const Shape s = shape_of(args, 1, L->K, act_dtype == RB_BF16);
     const int rc = act_dtype == RB_BF16 ? launch_shape<true>(args, s, stream) : launch_shape<false>(args, s, stream);
     if (rc != RB_OK) return rc;
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;
 }
 
-bool layer_supported(const rb_layer *L, int T) { return supported(L, T, STACK_MAX_T); }
+bool layer_supported(const rb_layer *L, int T) { return sized(L, T, STACK_MAX_T); }
 
 // A plan lives on the host: the kernel needs nothing in device memory besides the buffers.  The
 // workspace is the name it is run by, and holds the input of an op whose output overlaps it.
@@ -522,7 +532,8 @@ size_t plan_workspace_bytes(const rb_layer *layers, int n_layers, int T)
     return need;
 }
 
-struct Launch { Args args; Shape shape; const void *aside; size_t aside_bytes; };     // aside: an input to be moved to the workspace first
+// aside: an input to be moved to the workspace first; wide: a layer for the generic kernel, by itself
+struct Launch { Args args; Shape shape; const void *aside; size_t aside_bytes; bool is_wide; rb_layer wide; };
 struct Prepared { std::vector<Launch> launches; size_t need = 256; };
 static std::mutex g_mutex;
 static std::map<const void *, std::shared_ptr<const Prepared>> g_prepared;
@@ -552,25 +563,25 @@ int prepare_plan(const rb_layer *layers, const rb_stack_op *sops, int n_ops, uin
     auto meet = [](Span a, Span b) { return overlap(a.at, a.bytes, b.at, b.bytes); };
     for (int op0 = 0; op0 < n_ops;) {
         Args args = {};
-        args.nops = 0; args.T = T; args.out_dtype = RB_F16;
+        int nops = 0;
         const int K = layers[sops[op0].layer].K;
-        for (int n = op0; n < n_ops && args.nops < MAX_STAGE_OPS; ++n) {
+        for (int n = op0; n < n_ops && nops < MAX_STAGE_OPS; ++n) {
             const rb_layer &L = layers[sops[n].layer];
-            bool conflict = L.K != K || (n > op0 && (meet(src(n), dst(n)) || meet(src(op0), dst(op0))));
+            bool conflict = L.K != K || (n > op0 && !(kernel_takes(&L, T) && kernel_takes(&layers[sops[op0].layer], T))) || (n > op0 && (meet(src(n), dst(n)) || meet(src(op0), dst(op0))));
             for (int m = op0; m < n; ++m)
                 if (meet(dst(m), src(n)) || meet(dst(m), dst(n)) || meet(src(m), dst(n))) conflict = true;
             if (conflict) break;
-            args.op[args.nops++] = make_op(L, bufs[sops[n].src], bufs[sops[n].dst]);
+            args.op[nops++] = make_op(L, bufs[sops[n].src], bufs[sops[n].dst], T, RB_F16);
         }
-        const Shape shape = shape_of(args, K);                 // (numbers the workgroups in args)
-        Launch l = {args, shape, nullptr, 0};
+        const Shape shape = shape_of(args, nops, K, false);
+        Launch l = {args, shape, nullptr, 0, !kernel_takes(&layers[sops[op0].layer], T), layers[sops[op0].layer]};
         if (meet(src(op0), dst(op0))) {
             l.aside = src(op0).at;
             l.aside_bytes = src(op0).bytes;
             l.args.op[0].x = workspace;
         }
         pr->launches.push_back(l);
-        op0 += args.nops;
+        op0 += nops;
     }
     std::lock_guard<std::mutex> lock(g_mutex);
     g_prepared[workspace] = std::move(pr);
@@ -590,7 +601,8 @@ int launch_plan(void *workspace, size_t workspace_bytes_, hipStream_t stream)
     if (workspace_bytes_ < pr->need) return RB_ERR_WORKSPACE;
     for (const Launch &l : pr->launches) {
         if (l.aside) copy_aside(l.aside, workspace, l.aside_bytes, stream);
-        const int rc = launch_shape<false>(l.args, l.shape, stream);
+        const int rc = l.is_wide ? launch_signadd(&l.wide, l.args.op[0].x, l.args.op[0].y, l.shape.T, RB_F16, RB_F16, stream)
+                                 : launch_shape<false>(l.args, l.shape, stream);
         if (rc != RB_OK) return rc;
     }
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;

@@ -36,7 +36,7 @@ bool batch_applies(const rb_layer *layers, int n_layers, int T)
 constexpr int K3_ONE_PASS_MIN_T = 6, K3_BATCH_MAX_T = 12;
 bool single_few_applies(const rb_layer *L, int T, int act_dtype, int out_dtype)
 {
-    if (!batch::call_supported(L, T)) return false;
+    if (!batch::call_sized(L, T)) return false;
     if (L->K == 3) return T >= K3_ONE_PASS_MIN_T;
     return T > 2 || act_dtype != RB_F16 || out_dtype != RB_F16;
 }

@@ -60,7 +60,7 @@ namespace batch {
 // stack share a launch, dependent ones are ordered by the stream.  Single calls of any element type
 // take up to CALL_MAX_T tokens, stacks up to 16.
 constexpr int CALL_MAX_T = 64;
-bool call_supported(const rb_layer *L, int T);
+bool call_sized(const rb_layer *L, int T);
 // workspace: aside_bytes(L, T) from three tokens on, used when Y overlaps X
 int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
                 size_t workspace_bytes, hipStream_t stream);
