@@ -15,15 +15,16 @@
 // per workgroup) and c = |R|^T a by columns (slices of rows, partial sums added in slice order); in both a lane takes
 // four consecutive columns, one 16-byte load of W.  a is left at its length and its norm taken
 // out of c: with b of length 1, sigma = ||c|| and the next b is c / ||c||.  After the last iteration one more pass by rows gives the last |R| b and the
-// signs of R_i, and another one the error, term by term (as ||R_i||^2 - sigma^2 it would come out of the same pass, but with
-// a digit less: 3.6e-15 off where the terms are 1e-16).  Every sum has a fixed order.  The
+// signs of R_i.  The error after an update, term by term (as ||R_i||^2 - sigma^2 it would come out of the same pass, but with
+// a digit less: 3.6e-15 off where the terms are 1e-16), is found by the first pass of the next update on the way: its R less the
+// path that it leaves out.  Every sum has a fixed order.  The
 // iteration's stopping rule is evaluated on the device; the host reads one flag per update when it expects the
 // iteration to have finished, so the call synchronises.
 //
-// Measured, 4096 x 11008, two paths, five sweeps (ten updates of four iterations): before (a row per wavefront, slices
-// of 64 rows on single wavefronts, a normalisation after each pass, separate passes for the last |R| b, the signs and
-// the error) 8.7 ms, now 5.2 ms: a row pass 38 us (4.8 TB/s of W),
-// a column pass 47 us, the sums and the normalisation 14 us.
+// Measured, 4096 x 11008, two paths, five sweeps (ten updates of four iterations): 3.9 ms (5.1 with the path left out found at
+// run time, whose branches waited for every sign word by itself, nothing of the next step in flight, and passes of their own for the
+// errors): a row pass 31 us (37 before), a column pass 31 us (47), the sums and the normalisation 13 us.  180 MB of W in
+// 31 us are 5.8 TB/s, what a plain read of as much out of the memory-side cache reaches (6.0).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -42,12 +43,13 @@ constexpr int FIRST_LOOK = 4;          // power iterations before the first look
 constexpr int MAX_ITER = 200;
 constexpr double TOL_SIGMA = 1e-13, TOL_B = 1e-10;
 
-struct Problem {
+// W and the J paths that a pass subtracts
+template <int J> struct Problem {
     const float *W;
     const double *rows, *cols;         // preconditioning factors (nullptr: 1)
-    const uint32_t *packed;            // [K][out][in/32]
-    const double *g, *h;               // [K][out], [K][in]: g', h' of the preconditioned domain
-    int K, out, in;
+    const uint32_t *packed[J + 1];     // [out][in/32] each (the last one of a first pass: the path itself as the last sweep left it)
+    const double *g[J + 1], *h[J + 1]; // [out], [in]: g', h' of the preconditioned domain
+    int out, in;
 };
 
 struct Scalars {
@@ -79,86 +81,117 @@ __global__ __launch_bounds__(256) void start_kernel(double *b, int in, Scalars *
     }
 }
 
-// R[r][c .. c + 3] of ROWS rows for path `skip`: what the rows share of the columns (the factors, the other
-// paths' h) is read once for all of them, which is what the row pass is bound by (28 bytes through the caches for
-// the 4 bytes of a weight with one row at a time)
-template <int K, int R>
-__device__ __forceinline__ void residuals(const Problem &p, int r, int r_last, int c, int skip, const double (&g)[R][K], const double (&rows)[R], double (&v)[R][4])
+// What a step of a pass fetches: four consecutive columns of ROWS rows of W and the sign words they lie in, for N paths.
+// No branch around any of it (rows past the last one: the last one): with the path left out found at run time the
+// compiler put a branch and a full wait around every sign word, which took a quarter of the time of a pass
+template <int N> struct Piece {
+    float4 w[ROWS];
+    uint32_t bits[ROWS][N + 1];
+};
+template <int J, int N>
+__device__ __forceinline__ void fetch(const Problem<J> &p, int r, int r_last, int c, Piece<N> &to)
 {
-    float4 w[R];
-    uint32_t bits[R][K];
     const int W32 = p.in / 32;
 #pragma unroll
-    for (int u = 0; u < R; ++u) {
-        w[u] = *reinterpret_cast<const float4 *>(p.W + (size_t)min(r + u, r_last) * p.in + c);
+    for (int u = 0; u < ROWS; ++u) {
+        const int row = min(r + u, r_last);
+        to.w[u] = *reinterpret_cast<const float4 *>(p.W + (size_t)row * p.in + c);
 #pragma unroll
-        for (int j = 0; j < K; ++j) bits[u][j] = j == skip ? 0u : p.packed[((size_t)j * p.out + min(r + u, r_last)) * W32 + (c >> 5)] >> (c & 31);
-    }
-    double f[4] = {1.0, 1.0, 1.0, 1.0};
-    if (p.cols) {
-        const double2 c01 = *reinterpret_cast<const double2 *>(p.cols + c), c23 = *reinterpret_cast<const double2 *>(p.cols + c + 2);
-        f[0] = c01.x; f[1] = c01.y; f[2] = c23.x; f[3] = c23.y;
-    }
-#pragma unroll
-    for (int u = 0; u < R; ++u) {
-        v[u][0] = (double)w[u].x; v[u][1] = (double)w[u].y; v[u][2] = (double)w[u].z; v[u][3] = (double)w[u].w;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (p.rows) v[u][e] = rows[u] * v[u][e];
-            if (p.cols) v[u][e] = v[u][e] * f[e];
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-        if (j == skip) continue;
-        const double2 h01 = *reinterpret_cast<const double2 *>(p.h + (size_t)j * p.in + c);
-        const double2 h23 = *reinterpret_cast<const double2 *>(p.h + (size_t)j * p.in + c + 2);
-        const double hv[4] = {h01.x, h01.y, h23.x, h23.y};
-#pragma unroll
-        for (int u = 0; u < R; ++u)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                // the sign of g_j B_j: bit e of the word to the top of the value
-                const unsigned long long flip = (unsigned long long)(bits[u][j] << (31 - e) & 0x80000000u) << 32;
-                v[u][e] -= __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, g[u][j]) ^ flip) * hv[e];
-            }
+        for (int j = 0; j < N; ++j) to.bits[u][j] = p.packed[j][(size_t)row * W32 + (c >> 5)];
     }
 }
-
-template <int K> __device__ __forceinline__ void load_rows(const Problem &p, int r, int r_last, double (&g)[ROWS][K], double (&rows)[ROWS])
+// four consecutive values of a vector of doubles
+__device__ __forceinline__ void four(const double *v, int c, double (&to)[4])
+{
+    const double2 a = *reinterpret_cast<const double2 *>(v + c), b = *reinterpret_cast<const double2 *>(v + c + 2);
+    to[0] = a.x; to[1] = a.y; to[2] = b.x; to[3] = b.y;
+}
+// What a step shares of the columns, which is read once for ROWS rows (28 bytes through the caches for the 4 bytes of a weight
+// with one row at a time): the factors and the paths' h
+template <int N> struct Columns { double f[4], h[N + 1][4]; };
+template <int J, int N> __device__ __forceinline__ void fetch_columns(const Problem<J> &p, int c, Columns<N> &to)
+{
+    to.f[0] = to.f[1] = to.f[2] = to.f[3] = 1.0;
+    if (p.cols) four(p.cols, c, to.f);
+#pragma unroll
+    for (int j = 0; j < N; ++j) four(p.h[j], c, to.h[j]);
+}
+// and of the rows
+template <int N> struct Rows { double rows[ROWS], g[ROWS][N + 1]; };
+template <int J, int N> __device__ __forceinline__ void fetch_rows(const Problem<J> &p, int r, int r_last, Rows<N> &to)
 {
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
         const int row = min(r + u, r_last);
 #pragma unroll
-        for (int j = 0; j < K; ++j) g[u][j] = p.g[(size_t)j * p.out + row];
-        rows[u] = p.rows ? p.rows[row] : 1.0;
+        for (int j = 0; j < N; ++j) to.g[u][j] = p.g[j][row];
+        to.rows[u] = p.rows ? p.rows[row] : 1.0;
     }
 }
-
-// a[r] = sum_c |R[r][c]| b[c], its square by workgroup.  FINAL (after the iteration): also the signs of R (sign(0) = +1;
-// 32 columns per word, bit b = column 32 w + b, 1 means -1; nobody reads the path left out).
-// ROWS rows per workgroup, 1024 columns per step
-template <int K, bool FINAL>
-__global__ __launch_bounds__(256) void rows_kernel(Problem p, int skip, const double *b, double *a, double *a_sq, uint32_t *signs, const Scalars *sc)
+// v -= g B h for path j: the sign of g B is the bit of the column put on top of g
+template <int N>
+__device__ __forceinline__ void subtract(const Piece<N> &piece, const Columns<N> &cols, const Rows<N> &rows, int j, int c, double (&v)[ROWS][4])
 {
-    if (FINAL ? !sc->done : sc->done) return;
-    __shared__ double red[4][ROWS];
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+        const uint32_t bits = piece.bits[u][j] >> (c & 31);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const unsigned long long flip = (unsigned long long)(bits << (31 - e) & 0x80000000u) << 32;
+            v[u][e] -= __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, rows.g[u][j]) ^ flip) * cols.h[j][e];
+        }
+    }
+}
+// R[r ..][c .. c + 3] = rows W cols - the J paths
+template <int J, int N>
+__device__ __forceinline__ void residuals(const Problem<J> &p, const Piece<N> &piece, const Columns<N> &cols, const Rows<N> &rows, int c, double (&v)[ROWS][4])
+{
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+        v[u][0] = (double)piece.w[u].x; v[u][1] = (double)piece.w[u].y; v[u][2] = (double)piece.w[u].z; v[u][3] = (double)piece.w[u].w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[u][e] = rows.rows[u] * v[u][e] * cols.f[e];
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) subtract<N>(piece, cols, rows, j, c, v);
+}
+
+// a[r] = sum_c |R[r][c]| b[c], its square by workgroup; ROWS rows per workgroup, 1024 columns per step, the next step's
+// fetches in flight.  FINAL (after the iteration): also the signs of R (sign(0) = +1;
+// 32 columns per word, bit b = column 32 w + b, 1 means -1; nobody reads the path left out).
+// FIRST (of an update): also the squared Frobenius norm of R less the path as the last sweep left it, by workgroup: the error after the
+// update before this one
+enum Pass { ITERATE, FIRST, FINAL };
+template <int J, Pass PASS>
+__global__ __launch_bounds__(256, PASS == FIRST && J == 2 ? 3 : 4) void rows_kernel(Problem<J> p, const double *b, double *a, double *a_sq, uint32_t *signs, double *err_sq, const Scalars *sc)
+{
+    if (PASS == FINAL ? !sc->done : sc->done) return;
+    constexpr int N = PASS == FIRST ? J + 1 : J;
+    __shared__ double red[4][ROWS], red_err[4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = blockIdx.x * ROWS, r_last = p.out - 1;
-    double g[ROWS][K], rows[ROWS];
-    load_rows<K>(p, r, r_last, g, rows);
-    double dot[ROWS];
+    Rows<N> rows;
+    fetch_rows<J, N>(p, r, r_last, rows);
+    double dot[ROWS], sq = 0.0;
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) dot[u] = 0.0;
+    auto safe = [&](int c) { return c < p.in ? c : 0; };       // in % 32 == 0: all four columns or none
+    Piece<N> piece;
+    fetch<J, N>(p, r, r_last, safe(4 * (int)threadIdx.x), piece);
+#pragma unroll 1
     for (int c0 = 0; c0 < p.in; c0 += 1024) {
-        const int c = c0 + 4 * (int)threadIdx.x, cs = c < p.in ? c : 0;      // in % 32 == 0: all four columns or none
-        double2 b01 = *reinterpret_cast<const double2 *>(b + cs), b23 = *reinterpret_cast<const double2 *>(b + cs + 2);
-        if (c >= p.in) b01 = b23 = make_double2(0.0, 0.0);
-        double v[ROWS][4];
-        residuals<K, ROWS>(p, r, r_last, cs, skip, g, rows, v);
+        const int c = c0 + 4 * (int)threadIdx.x, cs = safe(c);
+        Columns<N> cols;
+        double bv[4], v[ROWS][4];
+        fetch_columns<J, N>(p, cs, cols);
+        four(b, cs, bv);
+        Piece<N> next;
+        fetch<J, N>(p, r, r_last, safe(c + 1024), next);
+        __builtin_amdgcn_sched_barrier(0);
+        if (c >= p.in) bv[0] = bv[1] = bv[2] = bv[3] = 0.0;
+        residuals<J, N>(p, piece, cols, rows, cs, v);
 #pragma unroll
         for (int u = 0; u < ROWS; ++u) {
-            if (FINAL) {
+            if (PASS == FINAL) {
                 // eight lanes hold the 32 columns of a word, four each
                 uint32_t four = 0;
 #pragma unroll
@@ -166,16 +199,27 @@ __global__ __launch_bounds__(256) void rows_kernel(Problem p, int skip, const do
                 const uint32_t word = or_over_8(four << (4 * (lane & 7)));
                 if ((lane & 7) == 0 && c < p.in && r + u < p.out) signs[(size_t)(r + u) * (p.in / 32) + (c >> 5)] = word;
             }
-            dot[u] += fabs(v[u][0]) * b01.x;
-            dot[u] += fabs(v[u][1]) * b01.y;
-            dot[u] += fabs(v[u][2]) * b23.x;
-            dot[u] += fabs(v[u][3]) * b23.y;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dot[u] += fabs(v[u][e]) * bv[e];
         }
+        if (PASS == FIRST) {
+            subtract<N>(piece, cols, rows, J, cs, v);
+#pragma unroll
+            for (int u = 0; u < ROWS; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (r + u < p.out && c < p.in) sq += v[u][e] * v[u][e];
+        }
+        piece = next;
     }
 #pragma unroll
     for (int u = 0; u < ROWS; ++u) {
         for (int m = 32; m > 0; m >>= 1) dot[u] += __shfl_xor(dot[u], m);
         if (lane == 0) red[wave][u] = dot[u];
+    }
+    if (PASS == FIRST) {
+        for (int m = 32; m > 0; m >>= 1) sq += __shfl_xor(sq, m);
+        if (lane == 0) red_err[wave] = sq;
     }
     __syncthreads();
     if (threadIdx.x != 0) return;
@@ -188,29 +232,39 @@ __global__ __launch_bounds__(256) void rows_kernel(Problem p, int skip, const do
         s2 += s * s;
     }
     a_sq[blockIdx.x] = s2;
+    if (PASS == FIRST) err_sq[blockIdx.x] = ((red_err[0] + red_err[1]) + red_err[2]) + red_err[3];
 }
 
 // partial[slice][c] = sum over the slice's rows of |R[r][c]| a[r]; a thread per four consecutive
-// columns, the rows of the slice in order, ROWS at a time
-template <int K>
-__global__ __launch_bounds__(256) void cols_kernel(Problem p, int skip, const double *a, double *partial, int slice_rows, const Scalars *sc)
+// columns, the rows of the slice in order, ROWS at a time, the next ones in flight
+template <int J>
+__global__ __launch_bounds__(256, 4) void cols_kernel(Problem<J> p, const double *a, double *partial, int slice_rows, const Scalars *sc)
 {
     if (sc->done) return;
     const int c = (blockIdx.x * 256 + threadIdx.x) * 4;
     const int r0 = blockIdx.y * slice_rows, r1 = min(p.out, r0 + slice_rows);
     if (c >= p.in) return;
+    Columns<J> cols;
+    fetch_columns<J, J>(p, c, cols);
+    Piece<J> piece;
+    fetch<J, J>(p, r0, r1 - 1, c, piece);
     double s[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
     for (int r = r0; r < r1; r += ROWS) {
-        double g[ROWS][K], rows[ROWS], v[ROWS][4];
-        load_rows<K>(p, r, r1 - 1, g, rows);
-        residuals<K, ROWS>(p, r, r1 - 1, c, skip, g, rows, v);
+        Piece<J> next;
+        fetch<J, J>(p, min(r + ROWS, r1 - 1), r1 - 1, c, next);
+        Rows<J> rows;
+        fetch_rows<J, J>(p, r, r1 - 1, rows);
+        double a_r[ROWS], v[ROWS][4];
 #pragma unroll
-        for (int u = 0; u < ROWS; ++u) {
-            const double a_r = r + u < r1 ? a[r + u] : 0.0;
+        for (int u = 0; u < ROWS; ++u) a_r[u] = r + u < r1 ? a[r + u] : 0.0;
+        __builtin_amdgcn_sched_barrier(0);
+        residuals<J, J>(p, piece, cols, rows, c, v);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) s[e] += fabs(v[u][e]) * a_r;
-        }
+        for (int u = 0; u < ROWS; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] += fabs(v[u][e]) * a_r[u];
+        piece = next;
     }
     double *dst = partial + (size_t)blockIdx.y * p.in + c;
     *reinterpret_cast<double2 *>(dst) = make_double2(s[0], s[1]);
@@ -287,18 +341,23 @@ __global__ __launch_bounds__(256) void scales_kernel(const double *a, const doub
     if (i < in) h_i[i] = root * b[i];
 }
 
-// squared Frobenius norm of W' - sum_j What_j, ROWS rows per workgroup as above, then one workgroup adds them up
-template <int K>
-__global__ __launch_bounds__(256) void err_rows_kernel(Problem p, double *rows_sq)
+// squared Frobenius norm of W' - sum_j What_j over all J paths (the last update: nothing follows that could find it on the
+// way), ROWS rows per workgroup as above, then one workgroup adds them up
+template <int J>
+__global__ __launch_bounds__(256, 4) void err_rows_kernel(Problem<J> p, double *rows_sq)
 {
     __shared__ double red[4];
     const int r = blockIdx.x * ROWS, r_last = p.out - 1;
-    double g[ROWS][K], rows[ROWS];
-    load_rows<K>(p, r, r_last, g, rows);
+    Rows<J> rows;
+    fetch_rows<J, J>(p, r, r_last, rows);
     double sq = 0.0;
     for (int c = 4 * (int)threadIdx.x; c < p.in; c += 1024) {
         double v[ROWS][4];
-        residuals<K, ROWS>(p, r, r_last, c, -1, g, rows, v);
+        Columns<J> cols;
+        Piece<J> piece;
+        fetch_columns<J, J>(p, c, cols);
+        fetch<J, J>(p, r, r_last, c, piece);
+        residuals<J, J>(p, piece, cols, rows, c, v);
 #pragma unroll
         for (int u = 0; u < ROWS; ++u)
 #pragma unroll
@@ -367,24 +426,41 @@ struct Buffers {
 };
 
 template <int K>
-static int derive(const Problem &p, int T_max, double *g, double *h, uint32_t *packed, double *err, const Buffers &ws, int slice_rows, hipStream_t stream)
+static int derive(const float *W, const double *row_factors, const double *col_factors, int out, int in, int T_max, double *g, double *h,
+                  uint32_t *packed, double *err, const Buffers &ws, int slice_rows, hipStream_t stream)
 {
-    const int out = p.out, in = p.in, n_slices = (out + slice_rows - 1) / slice_rows, n_a = (out + ROWS - 1) / ROWS;
+    const int n_slices = (out + slice_rows - 1) / slice_rows, n_a = (out + ROWS - 1) / ROWS;
+    const size_t words = (size_t)out * (in / 32);
     const dim3 by_rows((unsigned)n_a), by_cols((in + 1023) / 1024, n_slices), wg(256);
     int look = FIRST_LOOK;                         // iterations enqueued before the host looks: as many as the last update took
     for (int t = 0; t < T_max; ++t) {
         for (int i = 0; i < K; ++i) {
-            uint32_t *const signs = packed + (size_t)i * out * (in / 32);
+            // the paths but i, and i itself as the last sweep left it (nothing, in the first) at the end
+            Problem<K - 1> p{W, row_factors, col_factors, {}, {}, {}, out, in};
+            for (int j = 0, n = 0; j < K; ++j) {
+                const int at = j == i ? K - 1 : n++;
+                p.packed[at] = packed + j * words;
+                p.g[at] = g + (size_t)j * out;
+                p.h[at] = h + (size_t)j * in;
+            }
+            uint32_t *const signs = packed + i * words;
+            const bool err_before = err && t * K + i > 0;
             hipLaunchKernelGGL(start_kernel, dim3((in + 255) / 256), wg, 0, stream, ws.b, in, ws.sc);
             Scalars host;
             for (int it = 1;; ++it) {
-                hipLaunchKernelGGL((rows_kernel<K, false>), by_rows, wg, 0, stream, p, i, ws.b, ws.a, ws.a_sq, signs, ws.sc);
-                hipLaunchKernelGGL((cols_kernel<K>), by_cols, wg, 0, stream, p, i, ws.a, ws.partial, slice_rows, ws.sc);
+                if (it == 1 && err_before) {
+                    // (`partial` has room: out / 4 sums where the column pass has at least out)
+                    hipLaunchKernelGGL((rows_kernel<K - 1, FIRST>), by_rows, wg, 0, stream, p, ws.b, ws.a, ws.a_sq, signs, ws.partial, ws.sc);
+                    hipLaunchKernelGGL(err_sum_kernel, dim3(1), dim3(1024), 0, stream, ws.partial, n_a, err + (size_t)t * K + i - 1);
+                } else {
+                    hipLaunchKernelGGL((rows_kernel<K - 1, ITERATE>), by_rows, wg, 0, stream, p, ws.b, ws.a, ws.a_sq, signs, ws.partial, ws.sc);
+                }
+                hipLaunchKernelGGL((cols_kernel<K - 1>), by_cols, wg, 0, stream, p, ws.a, ws.partial, slice_rows, ws.sc);
                 hipLaunchKernelGGL(slices_kernel, dim3((in + SUMS_COLS - 1) / SUMS_COLS), dim3(SUMS_COLS * SUMS_RUNS), 0, stream, ws.partial, n_slices, ws.a_sq, n_a, in, ws.sum, ws.sum_sq, ws.sc);
                 hipLaunchKernelGGL(unit_kernel, dim3(1), dim3(1024), 0, stream, ws.b, ws.sum, ws.sum_sq, in, ws.sc);
                 if (it < look) continue;
                 // |R| b and the signs for the converged b, the path's new scales: nothing happens unless the iteration has finished
-                hipLaunchKernelGGL((rows_kernel<K, true>), by_rows, wg, 0, stream, p, i, ws.b, ws.a, ws.a_sq, signs, ws.sc);
+                hipLaunchKernelGGL((rows_kernel<K - 1, FINAL>), by_rows, wg, 0, stream, p, ws.b, ws.a, ws.a_sq, signs, ws.partial, ws.sc);
                 hipLaunchKernelGGL(scales_kernel, dim3((std::max(out, in) + 255) / 256), wg, 0, stream, ws.a, ws.b, ws.a_sq, n_a,
                                    g + (size_t)i * out, h + (size_t)i * in, out, in, ws.sc);
                 if (hipMemcpyAsync(&host, ws.sc, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess ||
@@ -393,11 +469,17 @@ static int derive(const Problem &p, int T_max, double *g, double *h, uint32_t *p
                 if (host.done) break;
             }
             look = std::max(1, host.iters);
-            if (err) {
-                hipLaunchKernelGGL((err_rows_kernel<K>), by_rows, wg, 0, stream, p, ws.a);       // (a has been used up)
-                hipLaunchKernelGGL(err_sum_kernel, dim3(1), dim3(1024), 0, stream, ws.a, n_a, err + (size_t)t * K + i);
-            }
         }
+    }
+    if (err) {
+        Problem<K> p{W, row_factors, col_factors, {}, {}, {}, out, in};
+        for (int j = 0; j < K; ++j) {
+            p.packed[j] = packed + j * words;
+            p.g[j] = g + (size_t)j * out;
+            p.h[j] = h + (size_t)j * in;
+        }
+        hipLaunchKernelGGL((err_rows_kernel<K>), by_rows, wg, 0, stream, p, ws.a);               // (a has been used up)
+        hipLaunchKernelGGL(err_sum_kernel, dim3(1), dim3(1024), 0, stream, ws.a, n_a, err + (size_t)T_max * K - 1);
     }
     return RB_OK;
 }
@@ -441,11 +523,8 @@ extern "C" int rb_derive_iterative(const float *W, const double *row_factors, co
                        (size_t)K * out, packed, nw);
     hipLaunchKernelGGL(clear_kernel, dim3((unsigned)(((size_t)K * in + 255) / 256)), dim3(256), 0, stream, h, (size_t)K * in,
                        static_cast<uint32_t *>(nullptr), (size_t)0);
-    Problem p{W, row_factors, col_factors, packed, g, h, K, out, in};
-
-    const int rc = K == 1 ? derive<1>(p, T_max, g, h, packed, err, buf, slice_rows, stream)
-                 : K == 2 ? derive<2>(p, T_max, g, h, packed, err, buf, slice_rows, stream)
-                          : derive<3>(p, T_max, g, h, packed, err, buf, slice_rows, stream);
+    auto run = [&](auto derive_k) { return derive_k(W, row_factors, col_factors, out, in, T_max, g, h, packed, err, buf, slice_rows, stream); };
+    const int rc = K == 1 ? run(derive<1>) : K == 2 ? run(derive<2>) : run(derive<3>);
     if (rc != RB_OK) return rc;
     if (row_factors || col_factors)
         hipLaunchKernelGGL(unscale_kernel, dim3((std::max(out, in) + 255) / 256), dim3(256), 0, stream, g, h, row_factors,
