@@ -5,11 +5,12 @@
 // W_hat = sum_k g_k (.) B_k (.) h_k (Alg. 2, "compute layer output") on v_mfma_f32_32x32x16_f16.  The left
 // operand is W_hat itself, built in registers from the packed signs on the way to the matrix
 // instruction and never stored.  Per pair of fp16 elements and path: a shift brings the two sign bits
-// to bits 15 and 31, one three-input logic operation puts them on the pair of h_k, and a packed multiply
-// (the other paths: fused multiply-add) with g_k: six vector instructions for two paths, two
-// roundings to fp16.  Powers of two (s_k that brings max|h_k| into [1/4, 1/2), S / s_k on g_k with one S
-// for the rows of a workgroup; the result is multiplied by 1 / S) keep the products in fp16's normal range
-// however the layer splits its magnitude.
+// to bits 15 and 31, one three-input logic operation puts them on the pair of h_k; a packed fused multiply-add per path but the
+// first adds them up as h_0 B_0 + rho_k h_k B_k: five vector instructions for two paths, one rounding of the sum and one of
+// rho_k = g_k / g_0, which a lane keeps for its row.  g_0 multiplies the fp32 sums at the end.  (With g_k on every path it
+// was a multiplication and a wait state for its result more: seven of eight issue slots per pair against five, and two more
+// roundings; 4096 x 11008 at 512 tokens 80.9 us, now 71.9, 28672 x 8192 at 100 91.6 and 81.0, at 2048 989 and 964.)  Powers of two
+// (s_k that brings max|h_k| into [1/4, 1/2)) keep the terms in fp16's normal range however the layer splits its magnitude.
 //
 // What bounds it: the vector instructions that build W_hat, until some 128 tokens share them, then the
 // matrix units (a wavefront hides about six vector instructions behind one 32x32x16 instruction,
@@ -28,11 +29,8 @@
 //   * the tile is brought to the output's type in LDS and stored as whole rows;
 //   * the left operand of the next row block is built between the matrix instructions of this one.
 //
-// Measured (before: a 256 x 256 tile on four wavefronts behind four pre-pass launches and, for most
-// sizes, a launch that added partial sums; stores of single elements), fp16, two paths, calls in a row in a graph:
-// 4096 x 4096 at 333 tokens 82 -> 28 us, 11008 x 4096 108 -> 51 us, 4096 x 11008 124 -> 63 us, at 512
-// tokens 125 -> 72 us; 8192 x 8192 at 1024 tokens 208 -> 150 us (0.92 PFLOP/s), 28672 x 8192
-// at 2048 tokens of bfloat16 1.02 -> 0.96 ms.
+// Measured, fp16, two paths, calls in a row in a graph: 4096 x 4096 at 333 tokens 32 us, 11008 x 4096 54 us, 4096 x 11008 66 us,
+// 8192 x 8192 at 1024 149 us (0.92 PFLOP/s), 28672 x 8192 at 2048 tokens 0.96 ms.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
@@ -125,7 +123,8 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
     static_assert(MB == 2 && TOK * 16 % GT == 0 && XL % 2 == 0, "whole loads per thread");
     static_assert(TOK * (64 * WR * 4 + 16) <= lds_bytes<K, NT, WR>() && 32768 * NT <= lds_bytes<K, NT, WR>(), "what reuses the slabs fits");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];       // [column group][2][SLAB]
-    __shared__ float red[2 * RB_MAX_K][WAVES];
+    __shared__ float red[RB_MAX_K][WAVES];
+    __shared__ __attribute__((aligned(16))) float row_scale[64 * WR];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -214,45 +213,46 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
 #pragma unroll
         for (int k = 0; k < K; ++k) gv[b][k] = __half2float(args.g[(size_t)k * out + min(rt0 * TILE_ROWS + 32 * b + r, out - 1)]);
 
-    // ---- powers of two that keep the effective weight in fp16's normal range
-    float mx_h[K], mx_g[K];
+    // ---- powers of two that bring the scales h of a path to [1/4, 1/2)
+    float mx_h[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         mx_h[k] = 0.f;
         for (int j = tid * 8; j < in; j += WAVES * 64 * 8) mx_h[k] = fmaxf(mx_h[k], abs_max8(buffer_load(h_rs, (uint32_t)(k * in + j) * 2u, 0)));
-        mx_g[k] = 0.f;
-#pragma unroll
-        for (int b = 0; b < MB; ++b) mx_g[k] = fmaxf(mx_g[k], fabsf(gv[b][k]));
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        for (int d = 32; d > 0; d >>= 1) {
-            mx_h[k] = fmaxf(mx_h[k], __shfl_xor(mx_h[k], d));
-            mx_g[k] = fmaxf(mx_g[k], __shfl_xor(mx_g[k], d));
-        }
-        if (lane == 0) { red[2 * k][wave] = mx_h[k]; red[2 * k + 1][wave] = mx_g[k]; }
+        for (int d = 32; d > 0; d >>= 1) mx_h[k] = fmaxf(mx_h[k], __shfl_xor(mx_h[k], d));
+        if (lane == 0) red[k][wave] = mx_h[k];
     }
     __syncthreads();
-    // (a path without a scale in these rows adds nothing to them and has no say)
-    float S = INFINITY, sk[K];
+    float sk[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        float a = 0.f, b = 0.f;
+        float a = 0.f;
 #pragma unroll
-        for (int v = 0; v < WAVES; ++v) { a = fmaxf(a, red[2 * k][v]); b = fmaxf(b, red[2 * k + 1][v]); }
+        for (int v = 0; v < WAVES; ++v) a = fmaxf(a, red[k][v]);
         sk[k] = mx::input_scale(a);
-        if (b > 0.f) S = fminf(S, sk[k] * mx::input_scale(b));
         if (row0 == k) h_scale = sk[k];
+#pragma unroll
+        for (int b = 0; b < MB; ++b) gv[b][k] = a > 0.f ? gv[b][k] / sk[k] : 0.f;       // (a path without a scale has no say)
     }
-    if (S == INFINITY) S = 1.f;
-    v2h G[MB][K];
+    // ---- a row of W_hat as base (h_0 B_0 + sum_k rho_k h_k B_k): the base is path 0's output scale, or 2^-15 of the largest one where
+    // path 0 has none or a smaller one (what it adds then is less than the last bit of the others)
+    v2h rho[MB][K - 1];
 #pragma unroll
-    for (int b = 0; b < MB; ++b)
+    for (int b = 0; b < MB; ++b) {
+        float most = fabsf(gv[b][0]), base = gv[b][0];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const _Float16 v = (_Float16)(gv[b][k] * (S / sk[k]));
-            G[b][k] = (v2h){v, v};
+        for (int k = 1; k < K; ++k) most = fmaxf(most, fabsf(gv[b][k]));
+        if (fabsf(base) < most * 0x1p-15f) base = most * 0x1p-15f;
+#pragma unroll
+        for (int k = 1; k < K; ++k) {
+            const _Float16 v = (_Float16)(base != 0.f ? gv[b][k] / base : 0.f);
+            rho[b][k - 1] = (v2h){v, v};
         }
+        if (grp == 0 && kg == 0) row_scale[64 * wr + 32 * b + r] = base;
+    }
     put(0, 0);
     if (SHORT) request(s_begin, 1); else request(s_begin + 1, 0);
     put(0, 1);
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
         for (int k = 0; k < K; ++k) {
             const uint32_t hw = reinterpret_cast<const uint32_t *>(&hv[from][k])[j];
             const v2h v = __builtin_bit_cast(v2h, hw ^ ((w[b][uc >> 2][k] << (15 - 4 * j - (uc & 3))) & 0x80008000u));
-            sum = k == 0 ? G[b][0] * v : __builtin_elementwise_fma(G[b][k], v, sum);
+            sum = k == 0 ? v : __builtin_elementwise_fma(rho[b][k - 1], v, sum);
         }
         reinterpret_cast<uint32_t *>(&a)[j] = __builtin_bit_cast(uint32_t, sum);
     };
@@ -371,17 +371,15 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
     constexpr int RW = 32 * MB * WR;                           // rows of the workgroup
     const int size = args.out_dtype == RB_F32 ? 4 : 2, pitch = RW * size + 16;
     if (grp == 0) {
-        const float inv = 1.f / S;
 #pragma unroll
-        for (int n = 0; n < NT; ++n)
+        for (int b = 0; b < MB; ++b)
 #pragma unroll
-            for (int b = 0; b < MB; ++b)
+            for (int e = 0; e < 4; ++e) {
+                const float4 base = *reinterpret_cast<const float4 *>(&row_scale[64 * wr + 32 * b + 8 * e + 4 * kg]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
+                for (int n = 0; n < NT; ++n) {
                     uint8_t *const dst = lds + (32 * n + r) * pitch + (32 * (MB * wr + b) + 8 * e + 4 * kg) * size;
-                    float v[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) v[i] = acc[b][n][4 * e + i] * inv;
+                    const float v[4] = {acc[b][n][4 * e] * base.x, acc[b][n][4 * e + 1] * base.y, acc[b][n][4 * e + 2] * base.z, acc[b][n][4 * e + 3] * base.w};
                     if (args.out_dtype == RB_F32) {
                         *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
                     } else {
@@ -391,6 +389,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
                         *reinterpret_cast<uint2 *>(dst) = make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
                     }
                 }
+            }
     }
     __syncthreads();
     const int first = id / TB * RW, rows = min(RW, out - first), tokens = min(TOK, T - t0), per16 = 16 / size;
@@ -423,7 +422,6 @@ __global__ __launch_bounds__(256) void align_kernel(const uint16_t *__restrict__
 // Measured on layers of 256 to 11008 columns (4096 x 11008, 22 or 43 steps, against 4096 x 4096, 8 or 16); a
 // round costs the same whether it fills the device or not (11008 x 4096 at 333 tokens, two paths: 172 workgroups of
 // 256 x 96 55 us, 129 of 256 x 128 63, 258 of 256 x 64 92, 516 of 128 x 64 91), so the shape with the least sum is taken.
-// (Three paths, 256 x 128 spills two registers and is worth it: 28672 x 8192 at 2048 tokens 1.14 ms, 1.34 without that shape.)
 struct Shape { int NT, WR; float fixed, step[2]; };
 constexpr Shape SHAPES[] = {{1, 2, 6.3f, {2.05f, 2.8f}}, {2, 2, 10.f, {2.5f, 3.35f}}, {2, 4, 9.5f, {2.15f, 2.8f}},
                             {3, 4, 11.5f, {2.4f, 3.15f}}, {4, 4, 12.5f, {2.85f, 3.65f}}};

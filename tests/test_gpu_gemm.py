@@ -274,3 +274,37 @@ def test_many_token_scales_off_alignment(K, n, T, shift):
     assert torch.equal(rb.rb_linear_gemm(L, Y, Y=Y), want)
     Y = X.clone()
     assert torch.equal(rb.rb_linear_gemm_noalloc(L, Y, Y), want)
+
+
+@pytest.mark.parametrize("K,T,case", [(2, 70, "none"), (2, 200, "small"), (3, 70, "none"), (3, 333, "small"), (2, 70, "inputs"), (3, 70, "outlier")])
+def test_gemm_rows_whose_first_path_is_small_or_missing(K, T, case):
+    """A row is built as path 0 plus multiples of it: rows where path 0 has no output scale or one 1e-3 to 1e-6 of the others', layers where it
+    has no input scales or one a thousand times the rest, either sign.  Each group of rows by itself against the oracle, fp32 results: two
+    roundings to fp16 per weight (2^-12 of it each) stay below 1e-3."""
+    out, inn = 650, 544
+    rng = synth.child_rng(5, 124, K, T)
+    signs, g, h = random_layer(rng, K, out, inn)
+    g = (g.astype(np.float64) * 20).astype(np.float16)
+    g[:, ::3] *= -1; h[1, ::5] *= -1
+    groups = [slice(0, 100), slice(100, 300), slice(300, out)]
+    if case == "none":
+        g[0, groups[0]] = 0
+        g[:, 640:] = 0
+    elif case == "small":
+        g[0, groups[0]] = (g[0, groups[0]].astype(np.float64) * 1e-6).astype(np.float16)
+        g[0, groups[1]] = (g[0, groups[1]].astype(np.float64) * 1e-3).astype(np.float16)
+    elif case == "inputs":
+        h[0] = 0
+    else:
+        h[0, 17] *= np.float16(1000)
+    X = synth.outlier_activations(rng, T, inn)
+    _say(f"first path {case}, K={K} T={T}")
+    Y = rb.rb_linear_gemm(to_device_layer(signs, g, h), torch.from_numpy(X).cuda(), out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    ref = oracle.forward(signs, g, h, X)
+    for rows in groups:
+        err = max_rel_l2(Y[:, rows], ref[:, rows])
+        _say(f"  rel_l2={err:.3e}")
+        assert err <= TOL
+    if case == "none":
+        assert torch.all(Y[:, 640:] == 0)
