@@ -106,8 +106,9 @@ int rb_linear_gemv(const rb_layer *L, const uint16_t *x, uint16_t *y,
  * One and two fp16 tokens with fp16 results (K = 2) run on the decode kernels, which hold
  * h_k (.) x as four 8-bit terms (to 2^-12).  Otherwise up to 64 tokens the weights are
  * streamed once for all tokens and every product of scale and activation is exact, over
- * the whole range of either activation type; larger T runs as a dense
- * contraction on the matrix cores, Y = W_hat X with the
+ * the whole range of either activation type; so do more tokens of layers with few rows
+ * (where 64 tokens to a workgroup fill the device at most once and are the faster way); larger
+ * T otherwise runs as a dense contraction on the matrix cores, Y = W_hat X with the
  * effective weight W_hat = sum_k g_k (.) B_k (.) h_k (the form Alg. 2 gives for
  * batched inputs), which the kernel builds in fp16 registers from the packed
  * signs (two roundings per weight, a few 1e-4 relative on the output; fp32

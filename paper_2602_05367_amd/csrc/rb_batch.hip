@@ -41,6 +41,7 @@
 #include <algorithm>
 #include <atomic>
 #include <climits>
+#include <cmath>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -192,7 +193,9 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) ? 4 : 2) void batch_kern
     const int tid = threadIdx.x, lane = tid & 63, nw = op.waves, threads = nw * 64;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, q = lane >> 4;
-    const int out = op.out, in = op.in, T = op.T;
+    // (calls of more than 64 tokens: blockIdx.z takes 64 of them)
+    const int t0 = G == 4 ? (int)blockIdx.z * 64 : 0;
+    const int out = op.out, in = op.in, T = G == 4 ? min(op.T - t0, 64) : op.T;
     const int RT = row_tiles(out), CT = col_tiles(in), rt0 = (int)blockIdx.x * P;
     if (rt0 >= RT) return;                                     // (an op with fewer row tiles than another one of the launch)
 
@@ -204,7 +207,7 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) ? 4 : 2) void batch_kern
     // (4 s + q) ^ (row % 16) of the wavefront's own slab: neither these writes nor the operand reads collide
     const int ch = lane & 15, row4 = lane >> 4, pos = (ch & 3) * 4 + (ch >> 2);
     uint8_t *const slab = lds + (size_t)wave * slab_bytes<K, G, BF16>();
-    const __amdgpu_buffer_rsrc_t x_rs = buffer(op.x, (size_t)T * in * 2);
+    const __amdgpu_buffer_rsrc_t x_rs = buffer(static_cast<const uint8_t *>(op.x) + (size_t)t0 * in * 2, (size_t)T * in * 2);
     const __amdgpu_buffer_rsrc_t w_rs = buffer(op.bits + (size_t)rt0 * CT * tile_words(K), (size_t)min(P, RT - rt0) * CT * tile_words(K) * 4);
     uint32_t x_off[4 * G];                                     // (rows of no token are not fetched)
 #pragma unroll
@@ -373,7 +376,7 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) ? 4 : 2) void batch_kern
         const int p = idx / (G * 256), t = idx / 16 % (G * 16), row = (rt0 + p) * TILE_ROWS + idx % 16;
         float s = 0.f;
         for (int v = 0; v < nw; ++v) s += part[v * (P * G * 256) + idx];
-        if (t < T && row < out) store_out(op.y, op.out_dtype, (size_t)t * out + row, s);
+        if (t < T && row < out) store_out(op.y, op.out_dtype, (size_t)(t0 + t) * out + row, s);
     }
 }
 
@@ -384,7 +387,7 @@ constexpr int ROW_TILES_PER_WG[] = {1, 2, 3, 4, 6};
 // once.  In units of a row tile's work (0.1 us per column tile) a workgroup costs 0.6 more (its activations, the sum) and a round
 // 33 / column tiles (3.3 us: the latencies).  (16 tokens, two paths, us for 1, 2, 3, 4, 6 row tiles: 12288 x 4096 10.9 10.6 9.1 10.1 12.8;
 // 22016 x 4096 18.3 14.5 13.5 16.4 12.9; 28672 x 8192 39.4 32.6 32.7 28.9 41.5)
-static int row_tiles_per_wg(const int *RT, int nops, int CT, int K, int G, bool bf16)
+static int row_tiles_per_wg(const int *RT, int nops, int CT, int K, int G, int blocks, bool bf16)
 {
     const int cus = std::max(1, mx::device_groups());
     int best = 1;
@@ -393,7 +396,7 @@ static int row_tiles_per_wg(const int *RT, int nops, int CT, int K, int G, bool 
         if (!p_available(K, G, P, bf16)) continue;
         int groups = 0;
         for (int i = 0; i < nops; ++i) groups += (RT[i] + P - 1) / P;
-        const int each = (groups + cus - 1) / cus, rounds = two_share(K, G, P) ? (each + 1) / 2 : each;
+        const int each = (groups * blocks + cus - 1) / cus, rounds = two_share(K, G, P) ? (each + 1) / 2 : each;
         const double cost = each * (P + 0.6) + rounds * 33.0 / CT;
         if (P == 1 || cost < best_cost) { best = P; best_cost = cost; }
     }
@@ -415,7 +418,7 @@ static int launch_form(const Args &args, int nops, int groups, int nw, hipStream
             allowed[dev].store(true);
         }
     }
-    hipLaunchKernelGGL((batch_kernel<K, G, P, W, BF16>), dim3((unsigned)groups, (unsigned)nops), dim3((unsigned)(nw * 64)), nw * per_wave, stream, args);
+    hipLaunchKernelGGL((batch_kernel<K, G, P, W, BF16>), dim3((unsigned)groups, (unsigned)nops, (unsigned)(G == 4 ? (args.op[0].T + 63) / 64 : 1)), dim3((unsigned)(nw * 64)), nw * per_wave, stream, args);
     return RB_OK;
 }
 
@@ -454,7 +457,7 @@ static Shape shape_of(Args &args, int nops, int K, bool bf16)
         units = std::max(units, (args.op[i].in + UNIT_COLS - 1) / UNIT_COLS);
     }
     const int G = token_groups(s.T);
-    s.P = row_tiles_per_wg(RT, nops, (units + 1) / 2, K, G, bf16);
+    s.P = row_tiles_per_wg(RT, nops, (units + 1) / 2, K, G, (s.T + 63) / 64, bf16);
     int all = 0;
     for (int i = 0; i < nops; ++i) {
         s.groups = std::max(s.groups, (RT[i] + s.P - 1) / s.P);
@@ -503,6 +506,19 @@ static bool kernel_takes(const rb_layer *L, int T) { return L->in < 1 << 24 && (
 
 bool call_sized(const rb_layer *L, int T) { return sized(L, T, CALL_MAX_T); }
 
+// More than CALL_MAX_T tokens: 64 of them per workgroup, where the workgroups of a call do not outnumber the compute units (in a second
+// round the many-token kernel is always the faster one).  Microseconds, launch included: 6.5 and so much per column tile, measured on
+// layers of 800 to 11008 columns
+float blocks_cost(const rb_layer *L, int T, int act_dtype)
+{
+    static constexpr float per_tile[2][2][3] = {{{0.46f, 0.69f, 0.8f}, {0.57f, 0.95f, 0.f}}, {{0.5f, 0.85f, 0.f}, {0.67f, 0.f, 0.f}}};
+    const bool bf16 = act_dtype == RB_BF16;
+    if (!sized(L, T, INT_MAX) || !kernel_takes(L, std::min(T, 64))) return INFINITY;
+    for (int P = 1; P <= 3 && p_available(L->K, 4, P, bf16); ++P)
+        if ((long long)((row_tiles(L->out) + P - 1) / P) * ((T + 63) / 64) <= mx::device_groups()) return 6.5f + per_tile[L->K - 2][bf16][P - 1] * (float)col_tiles(L->in);
+    return INFINITY;
+}
+
 int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
                 size_t workspace_bytes, hipStream_t stream)
 {
@@ -512,7 +528,7 @@ int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype,
         copy_aside(X, workspace, input_bytes(L, T), stream);
         X = workspace;
     }
-    if (!kernel_takes(L, T)) return launch_signadd(L, X, Y, T, act_dtype, out_dtype, stream);
+    if (!kernel_takes(L, std::min(T, 64))) return launch_signadd(L, X, Y, T, act_dtype, out_dtype, stream);
     Args args = {};
     args.op[0] = make_op(*L, X, Y, T, out_dtype);
     const Shape s = shape_of(args, 1, L->K, act_dtype == RB_BF16);

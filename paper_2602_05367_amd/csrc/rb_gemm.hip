@@ -421,27 +421,33 @@ __global__ __launch_bounds__(256) void align_kernel(const uint16_t *__restrict__
 // scales, first loads, sums, stores) and `step` per step of 128 columns per group, for two and for three paths.
 // Measured on layers of 256 to 11008 columns (4096 x 11008, 22 or 43 steps, against 4096 x 4096, 8 or 16); a
 // round costs the same whether it fills the device or not (11008 x 4096 at 333 tokens, two paths: 172 workgroups of
-// 256 x 96 55 us, 129 of 256 x 128 63, 258 of 256 x 64 92, 516 of 128 x 64 91), so the shape with the least sum is taken.
+// 256 x 96 55 us, 129 of 256 x 128 68, 258 of 256 x 64 86, 516 of 128 x 64 85), so the shape with the least sum is taken.
 struct Shape { int NT, WR; float fixed, step[2]; };
-constexpr Shape SHAPES[] = {{1, 2, 6.3f, {2.05f, 2.8f}}, {2, 2, 10.f, {2.5f, 3.35f}}, {2, 4, 9.5f, {2.15f, 2.8f}},
-                            {3, 4, 11.5f, {2.4f, 3.15f}}, {4, 4, 12.5f, {2.85f, 3.65f}}};
+constexpr Shape SHAPES[] = {{1, 2, 8.f, {1.8f, 2.5f}}, {2, 2, 10.5f, {2.3f, 2.95f}}, {2, 4, 10.f, {1.95f, 2.55f}},
+                            {3, 4, 11.5f, {2.25f, 2.9f}}, {4, 4, 13.f, {2.85f, 3.4f}}};
 constexpr int N_SHAPES = sizeof(SHAPES) / sizeof(SHAPES[0]);
 
 static int tiles_of(const Shape &s, int out, int T)
 {
     return (row_tiles(out) + 4 * s.WR - 1) / (4 * s.WR) * ((T + 32 * s.NT - 1) / (32 * s.NT));
 }
-static int best_shape(const rb_layer *L, int T)
+static int best_shape(const rb_layer *L, int T, float &least)
 {
     const int cus = std::max(1, mx::device_groups()), n128 = (L->in + STEP_COLS - 1) / STEP_COLS;
     int best = 0;
-    float least = 0.f;
     for (int i = 0; i < N_SHAPES; ++i) {
         const int groups = WAVES / SHAPES[i].WR, rounds = (tiles_of(SHAPES[i], L->out, T) + cus - 1) / cus;
-        const float cost = (float)rounds * (SHAPES[i].fixed + SHAPES[i].step[L->K - 2] * (float)((n128 + groups - 1) / groups));
-        if (i == 0 || cost < least) { best = i; least = cost; }
+        const float c = (float)rounds * (SHAPES[i].fixed + SHAPES[i].step[L->K - 2] * (float)((n128 + groups - 1) / groups));
+        if (i == 0 || c < least) { best = i; least = c; }
     }
     return best;
+}
+
+float cost(const rb_layer *L, int T)
+{
+    float least = 0.f;
+    best_shape(L, T, least);
+    return least;
 }
 
 template <int K, int NT, int WR, bool BF16> static int launch_form(const Args &a, hipStream_t stream)
@@ -518,7 +524,8 @@ int launch(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int 
     a.h = reinterpret_cast<const __half *>(h);
     a.X = X; a.Y = Y;
     a.out = L->out; a.in = L->in; a.T = T; a.out_dtype = out_dtype;
-    const int s = best_shape(L, T);
+    float cost;
+    const int s = best_shape(L, T, cost);
     const int rc = L->K == 2 ? (act_dtype == RB_BF16 ? launch_shape<2, true>(a, s, stream) : launch_shape<2, false>(a, s, stream))
                              : (act_dtype == RB_BF16 ? launch_shape<3, true>(a, s, stream) : launch_shape<3, false>(a, s, stream));
     if (rc != RB_OK) return rc;

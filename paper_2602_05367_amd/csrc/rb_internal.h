@@ -22,6 +22,9 @@ bool batch_applies(const rb_layer *layers, int n_layers, int T);
 bool single_few_applies(const rb_layer *L, int T, int act_dtype, int out_dtype);
 bool single_gemm_applies(const rb_layer *L, int T);
 
+// a call of more than 64 tokens, given gemm::workspace_bytes: the many-token kernel, or the few-token kernel 64 tokens at a time
+int launch_many(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace, size_t workspace_bytes, hipStream_t stream);
+
 int dispatch_linear(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype,
                     void *workspace, size_t workspace_bytes, hipStream_t stream);
 
@@ -44,6 +47,7 @@ namespace gemm {
 // many-token matrix-core GEMM (K = 2 or 3): workspace holds the input when the output overlaps it
 bool supported(const rb_layer *L, int T);
 size_t workspace_bytes(const rb_layer *L, int T);
+float cost(const rb_layer *L, int T);      // microseconds a call takes, by the rule that picks the workgroup's shape
 int launch(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
            hipStream_t stream);
 }  // namespace gemm
@@ -61,6 +65,7 @@ namespace batch {
 // take up to CALL_MAX_T tokens, stacks up to 16.
 constexpr int CALL_MAX_T = 64;
 bool call_sized(const rb_layer *L, int T);
+float blocks_cost(const rb_layer *L, int T, int act_dtype);      // of more tokens, 64 per workgroup; infinite where that is never the faster way
 // workspace: aside_bytes(L, T) from three tokens on, used when Y overlaps X
 int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
                 size_t workspace_bytes, hipStream_t stream);

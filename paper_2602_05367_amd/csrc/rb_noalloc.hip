@@ -75,7 +75,7 @@ extern "C" int rb_linear_gemm_noalloc(const rb_layer *L, const void *X, void *Y,
         const int rs = scratch_of_current_device(&ptr);
         if (rs != RB_OK) return rs;
         rb::set_last_path(RB_PATH_GEMM);
-        return rb::gemm::launch(L, X, Y, T, act_dtype, out_dtype, ptr, stream);
+        return rb::launch_many(L, X, Y, T, act_dtype, out_dtype, ptr, SCRATCH_BYTES, stream);
     }
     rb::set_last_path(RB_PATH_SIGNADD);
     return rb::launch_signadd(L, X, Y, T, act_dtype, out_dtype, stream);

@@ -276,20 +276,20 @@ def test_many_token_scales_off_alignment(K, n, T, shift):
     assert torch.equal(rb.rb_linear_gemm_noalloc(L, Y, Y), want)
 
 
-@pytest.mark.parametrize("K,T,case", [(2, 70, "none"), (2, 200, "small"), (3, 70, "none"), (3, 333, "small"), (2, 70, "inputs"), (3, 70, "outlier")])
+@pytest.mark.parametrize("K,T,case", [(2, 700, "none"), (2, 1100, "small"), (3, 700, "none"), (3, 900, "small"), (2, 700, "inputs"), (3, 700, "outlier")])
 def test_gemm_rows_whose_first_path_is_small_or_missing(K, T, case):
     """A row is built as path 0 plus multiples of it: rows where path 0 has no output scale or one 1e-3 to 1e-6 of the others', layers where it
     has no input scales or one a thousand times the rest, either sign.  Each group of rows by itself against the oracle, fp32 results: two
     roundings to fp16 per weight (2^-12 of it each) stay below 1e-3."""
-    out, inn = 650, 544
+    out, inn = 1300, 544                                       # (too many tiles of 64 tokens for the few-token kernel)
     rng = synth.child_rng(5, 124, K, T)
     signs, g, h = random_layer(rng, K, out, inn)
     g = (g.astype(np.float64) * 20).astype(np.float16)
     g[:, ::3] *= -1; h[1, ::5] *= -1
-    groups = [slice(0, 100), slice(100, 300), slice(300, out)]
+    groups = [slice(0, 200), slice(200, 600), slice(600, out)]
     if case == "none":
         g[0, groups[0]] = 0
-        g[:, 640:] = 0
+        g[:, 1290:] = 0
     elif case == "small":
         g[0, groups[0]] = (g[0, groups[0]].astype(np.float64) * 1e-6).astype(np.float16)
         g[0, groups[1]] = (g[0, groups[1]].astype(np.float64) * 1e-3).astype(np.float16)
@@ -307,4 +307,47 @@ def test_gemm_rows_whose_first_path_is_small_or_missing(K, T, case):
         _say(f"  rel_l2={err:.3e}")
         assert err <= TOL
     if case == "none":
-        assert torch.all(Y[:, 640:] == 0)
+        assert torch.all(Y[:, 1290:] == 0)
+
+
+@pytest.mark.parametrize("K,out,inn,T,bf16", [(2, 1290, 800, 700, False), (2, 2600, 96, 1025, True), (3, 1400, 1056, 800, True), (3, 1300, 544, 641, False),
+                                              (2, 4100, 2080, 333, False), (2, 5000, 288, 1000, False)])
+def test_many_token_kernel_at_ragged_sizes(K, out, inn, T, bf16):
+    """Sizes at which calls of more than 64 tokens do take the many-token kernel, whose weights are rounded to fp16 (two roundings, 2^-12 of
+    a weight each): within 1e-3 of the oracle, and not as close as exact products would be."""
+    rng = synth.child_rng(5, 125, K, out, inn, T)
+    host = random_layer(rng, K, out, inn)
+    X = synth.gaussian_activations(rng, T, inn)
+    Xd = torch.from_numpy(X).cuda()
+    if bf16:
+        Xd = Xd.to(torch.bfloat16)
+        X = oracle.bf16_bits_to_f64(bf16_bits(Xd.cpu())).reshape(T, inn)
+    _say(f"many-token kernel K={K} {out}x{inn} T={T} bf16={bf16}")
+    Y = rb.rb_linear_gemm(to_device_layer(*host), Xd, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    err = max_rel_l2(Y, oracle.forward(*host, X))
+    _say(f"  rel_l2={err:.3e}")
+    assert 2e-5 < err <= TOL
+
+
+@pytest.mark.parametrize("K,out,inn,T,bf16", [(2, 300, 800, 65, False), (2, 1000, 2080, 333, True), (3, 700, 1056, 200, False), (2, 33, 4128, 1000, False),
+                                              (3, 16, 96, 4097, True), (2, 4100, 544, 100, False)])
+def test_many_tokens_of_few_rows(K, out, inn, T, bf16):
+    """Few tiles: 64 tokens per workgroup on the few-token kernel.  Its products are exact (fp32 results within 1e-5 of the
+    oracle), and every 64 tokens are what a call of their own gives, bit for bit."""
+    rng = synth.child_rng(5, 126, K, out, inn, T)
+    host = random_layer(rng, K, out, inn)
+    L = to_device_layer(*host)
+    X = synth.outlier_activations(rng, T, inn)
+    Xd = torch.from_numpy(X).cuda()
+    if bf16:
+        Xd = Xd.to(torch.bfloat16)
+        X = oracle.bf16_bits_to_f64(bf16_bits(Xd.cpu())).reshape(T, inn)
+    _say(f"few rows K={K} {out}x{inn} T={T} bf16={bf16}")
+    Y = torch.full((T + 1, out), 7.0, dtype=torch.float32, device="cuda")
+    rb.rb_linear_gemm(L, Xd, Y=Y[:T])
+    torch.cuda.synchronize()
+    assert rb.rb_last_path() == rb.RB_PATH_GEMM and torch.all(Y[T] == 7.0)
+    assert max_rel_l2(Y[:T], oracle.forward(*host, X)) <= 1e-5
+    for t in range(0, T - 63, 64 * 7):
+        assert torch.equal(rb.rb_linear_gemm(L, Xd[t:t + 64].contiguous(), out_dtype=torch.float32), Y[t:t + 64])
