@@ -124,8 +124,9 @@ def _np_ptr(a: np.ndarray) -> ctypes.c_void_p:
     return a.ctypes.data_as(ctypes.c_void_p)
 
 
-def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    """The current stream of the current device (torch.cuda.current_stream() without its stream object, 2 us of a call)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 _DTYPE_CODE = {torch.float16: RB_F16, torch.bfloat16: RB_BF16, torch.float32: RB_F32}
@@ -217,15 +218,28 @@ def _workspace(layers: Sequence[Layer], T: int, device, n_ops: int = 1) -> Tuple
     return ws, n
 
 
+def _call_workspace(s: rb_layer, T: int, device):
+    """Scratch memory of one call on the layer of struct s: the tensor, which the caller holds until the call is enqueued, its
+    address and size; nothing is allocated where nothing is asked for."""
+    n = lib.rb_workspace_bytes(ctypes.byref(s), 1, 1, T)
+    if n == 0:
+        return None, 0, 0
+    ws = torch.empty(n, dtype=torch.uint8, device=device)
+    return ws, ws.data_ptr(), n
+
+
 def rb_linear_gemv(layer: Layer, x: torch.Tensor, y: torch.Tensor = None, workspace=None) -> torch.Tensor:
     """y = layer(x) for one fp16 token x [in]; returns fp16 [out]."""
     assert x.is_cuda and x.dtype == torch.float16 and x.is_contiguous() and x.numel() == layer.inn
     if y is None:
         y = torch.empty(layer.out, dtype=torch.float16, device=x.device)
-    ws, n = workspace if workspace is not None else _workspace([layer], 1, x.device)
     s = layer.struct()
-    _check("rb_linear_gemv", lib.rb_linear_gemv(ctypes.byref(s), x.data_ptr(), y.data_ptr(),
-                                                ws.data_ptr(), n, _stream()))
+    if workspace is None:
+        ws, at, n = _call_workspace(s, 1, x.device)
+    else:
+        ws, n = workspace
+        at = ws.data_ptr()
+    _check("rb_linear_gemv", lib.rb_linear_gemv(ctypes.byref(s), x.data_ptr(), y.data_ptr(), at, n, _stream()))
     return y
 
 
@@ -236,11 +250,14 @@ def rb_linear_gemm(layer: Layer, X: torch.Tensor, out_dtype=torch.float16, Y: to
     T = X.shape[0]
     if Y is None:
         Y = torch.empty((T, layer.out), dtype=out_dtype, device=X.device)
-    ws, n = workspace if workspace is not None else _workspace([layer], T, X.device)
     s = layer.struct()
+    if workspace is None:
+        ws, at, n = _call_workspace(s, T, X.device)
+    else:
+        ws, n = workspace
+        at = ws.data_ptr()
     _check("rb_linear_gemm", lib.rb_linear_gemm(ctypes.byref(s), X.data_ptr(), Y.data_ptr(), T,
-                                                _DTYPE_CODE[X.dtype], _DTYPE_CODE[Y.dtype],
-                                                ws.data_ptr(), n, _stream()))
+                                                _DTYPE_CODE[X.dtype], _DTYPE_CODE[Y.dtype], at, n, _stream()))
     return Y
 
 
