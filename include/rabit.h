@@ -45,9 +45,9 @@ extern "C" {
 
 /* K = 2 is the 2-bit layer every kernel here is built for.  K = 3 (the 3-bit variant of the
  * paper's packing appendix): stacks run on the matrix cores (one token on the fused decode kernel,
- * 2..16 tokens on the few-token kernel), single calls of 6 tokens or more too (the few-token kernel
- * up to 64 tokens, the many-token kernel beyond), shorter single calls on the generic sign-XOR + add
- * kernel, which also runs K = 1. */
+ * 2..16 tokens on the few-token kernel), single calls too (the few-token kernel
+ * up to 64 tokens, the many-token kernel beyond).  K = 1 runs on the generic sign-XOR + add
+ * kernel. */
 #define RB_MAX_K 3
 
 /* element types for rb_linear_gemm */
@@ -302,7 +302,8 @@ int rb_stream_read_groups(void);
 
 /* Which kernel family the most recent compute call of this thread enqueued:
  * RB_PATH_NONE, RB_PATH_SIGNADD (generic sign-XOR + add kernel, one launch per
- * op), RB_PATH_GEMM (matrix-core GEMM of a single call: the few-token kernel up to
+ * op; single calls on a three-path layer with up to 5 tokens report it as well, as they
+ * did before the few-token kernel served them), RB_PATH_GEMM (matrix-core GEMM of a single call: the few-token kernel up to
  * 64 tokens, the many-token kernel beyond, one launch per op),
  * RB_PATH_MX (matrix-core decode kernels: one layer and token in one launch,
  * or all ops of a stack in one persistent launch) or RB_PATH_BATCH (few-token

@@ -522,8 +522,8 @@ float blocks_cost(const rb_layer *L, int T, int act_dtype)
 int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
                 size_t workspace_bytes, hipStream_t stream)
 {
-    // (one and two tokens: nothing is asked for, and the output must not overlap the input)
-    if (T > 2 && overlap(X, input_bytes(L, T), Y, output_bytes(L, T, out_dtype))) {
+    // (where nothing is asked for the output must not overlap the input)
+    if (single_few_has_room(L, T) && overlap(X, input_bytes(L, T), Y, output_bytes(L, T, out_dtype))) {
         if (!workspace || workspace_bytes < aside_bytes(L, T)) return RB_ERR_WORKSPACE;
         copy_aside(X, workspace, input_bytes(L, T), stream);
         X = workspace;

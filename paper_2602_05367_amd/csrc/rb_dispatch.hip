@@ -29,21 +29,24 @@ bool batch_applies(const rb_layer *layers, int n_layers, int T)
     return any_three || T > FUSED_MAX_T;
 }
 
-// Which single calls take the few-token kernel (one launch): two paths beyond two tokens and whatever
+// Which single calls take the few-token kernel (one launch): three paths, and two paths beyond two tokens and whatever
 // element types the decode kernels do not take (one and two fp16 tokens with fp16 results stay there: the bits are those of
-// a stack), three paths from K3_ONE_PASS_MIN_T tokens on.  Fewer stay on the generic kernel, which is what rb_last_path has
-// always said of them; it is not the faster one (4096 x 11008: 63 us at five tokens, 12.7 at sixteen here).
-constexpr int K3_ONE_PASS_MIN_T = 6, K3_BATCH_MAX_T = 12;
+// a stack).  Three paths at up to five tokens took the generic kernel once, which reads the weights for every token (us in a graph, there
+// and here: 4096 x 4096 at one token 10.9 and 6.2, at three 17.0 and 6.1, 4096 x 11008 at one 32.1 and 9.5, 28672 x 8192 at three 168 and 39).
+// They still ask for no scratch memory (so their output must not overlap their input) and report what they have always reported.
+constexpr int K3_ROOM_MIN_T = 6, K3_BATCH_MAX_T = 12;
 bool single_few_applies(const rb_layer *L, int T, int act_dtype, int out_dtype)
 {
     if (!batch::call_sized(L, T)) return false;
-    if (L->K == 3) return T >= K3_ONE_PASS_MIN_T;
-    return T > 2 || act_dtype != RB_F16 || out_dtype != RB_F16;
+    return L->K == 3 || T > 2 || act_dtype != RB_F16 || out_dtype != RB_F16;
 }
+// an output over its input is provided for
+bool single_few_has_room(const rb_layer *L, int T) { return T >= (L->K == 3 ? K3_ROOM_MIN_T : 3); }
 // the kernel family a few-token call is reported as (rb_last_path): the families these calls have always been
 // reported as; the kernel is the same
-static int few_path(const rb_layer *L, int T, int act_dtype, int out_dtype)
+int single_few_path(const rb_layer *L, int T, int act_dtype, int out_dtype)
 {
+    if (L->K == 3 && T < K3_ROOM_MIN_T) return RB_PATH_SIGNADD;
     return L->K == 3 && T <= K3_BATCH_MAX_T && act_dtype == RB_F16 && out_dtype == RB_F16 ? RB_PATH_BATCH : RB_PATH_GEMM;
 }
 bool single_gemm_applies(const rb_layer *L, int T)
@@ -75,7 +78,7 @@ void copy_aside(const void *X, void *to, size_t bytes, hipStream_t stream)
 static size_t call_bytes(const rb_layer *L, int T)
 {
     if (single_gemm_applies(L, T)) return gemm::workspace_bytes(L, T);
-    return T > 2 && single_few_applies(L, T, RB_F16, RB_F16) ? aside_bytes(L, T) : 0;
+    return single_few_has_room(L, T) && single_few_applies(L, T, RB_F16, RB_F16) ? aside_bytes(L, T) : 0;
 }
 
 size_t workspace_bytes(const rb_layer *layers, int n_layers, int n_ops, int T)
@@ -105,7 +108,7 @@ int dispatch_linear(const rb_layer *L, const void *X, void *Y, int T, int act_dt
         if (rc != RB_ERR_UNSUPPORTED) { g_last_path = RB_PATH_MX; return rc; }
     }
     if (single_few_applies(L, T, act_dtype, out_dtype)) {
-        g_last_path = few_path(L, T, act_dtype, out_dtype);
+        g_last_path = single_few_path(L, T, act_dtype, out_dtype);
         return batch::launch_call(L, X, Y, T, act_dtype, out_dtype, workspace, workspace_bytes, stream);
     }
     if (single_gemm_applies(L, T) && workspace && workspace_bytes >= gemm::workspace_bytes(L, T)) {

@@ -20,6 +20,8 @@ bool batch_applies(const rb_layer *layers, int n_layers, int T);
 // a single call takes the few-token kernel; of T tokens on this layer, the many-token kernel (given
 // the scratch memory it needs)
 bool single_few_applies(const rb_layer *L, int T, int act_dtype, int out_dtype);
+bool single_few_has_room(const rb_layer *L, int T);      // a call that asks for scratch memory, where the output overlaps the input
+int single_few_path(const rb_layer *L, int T, int act_dtype, int out_dtype);
 bool single_gemm_applies(const rb_layer *L, int T);
 
 // a call of more than 64 tokens, given gemm::workspace_bytes: the many-token kernel, or the few-token kernel 64 tokens at a time
@@ -66,7 +68,7 @@ namespace batch {
 constexpr int CALL_MAX_T = 64;
 bool call_sized(const rb_layer *L, int T);
 float blocks_cost(const rb_layer *L, int T, int act_dtype);      // of more tokens, 64 per workgroup; infinite where that is never the faster way
-// workspace: aside_bytes(L, T) from three tokens on, used when Y overlaps X
+// workspace: aside_bytes(L, T) where single_few_has_room, used when Y overlaps X
 int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace,
                 size_t workspace_bytes, hipStream_t stream);
 bool layer_supported(const rb_layer *L, int T);

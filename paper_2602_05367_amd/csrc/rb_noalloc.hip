@@ -60,11 +60,12 @@ extern "C" int rb_linear_gemm_noalloc(const rb_layer *L, const void *X, void *Y,
     // the few-token kernel: scratch memory only for an input that the output overlaps
     if (rb::single_few_applies(L, T, act_dtype, out_dtype) && !generic_instead) {
         void *ptr = nullptr;
-        if (T > 2 && rb::overlap(X, rb::input_bytes(L, T), Y, rb::output_bytes(L, T, out_dtype))) {
+        if (rb::single_few_has_room(L, T) && rb::overlap(X, rb::input_bytes(L, T), Y, rb::output_bytes(L, T, out_dtype))) {
             const int rs = scratch_of_current_device(&ptr);
             if (rs != RB_OK) return rs;
         }
-        rb::set_last_path(RB_PATH_GEMM);
+        const int path = rb::single_few_path(L, T, act_dtype, out_dtype);
+        rb::set_last_path(path == RB_PATH_SIGNADD ? path : RB_PATH_GEMM);
         return rb::batch::launch_call(L, X, Y, T, act_dtype, out_dtype, ptr, SCRATCH_BYTES, stream);
     }
     if (rb::single_gemm_applies(L, T)) {

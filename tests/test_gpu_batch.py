@@ -300,7 +300,9 @@ def test_few_token_calls_element_by_element(K, out, inn, T, bf16):
     # sign tiles shared by two wavefronts (9, 17 and 33 units of 128 columns for 8 or 16 of them); two workgroups on a compute unit;
     # three row tiles and four token groups, two of them with three paths; four row tiles and two token groups
     (2, 300, 1056, 16, False), (2, 300, 4128, 3, True), (3, 60, 2112, 7, False), (2, 28672, 288, 9, False), (2, 22016, 544, 16, True),
-    (3, 13824, 544, 6, False), (2, 11008, 544, 64, False), (3, 8208, 288, 40, False), (2, 16400, 544, 24, False), (3, 300, 2080, 17, True)])
+    (3, 13824, 544, 6, False), (2, 11008, 544, 64, False), (3, 8208, 288, 40, False), (2, 16400, 544, 24, False), (3, 300, 2080, 17, True),
+    # three paths, one to five tokens
+    (3, 300, 1056, 1, False), (3, 12300, 288, 2, True), (3, 28672, 160, 5, False), (3, 4100, 2080, 3, True)])
 def test_few_token_forms_and_shared_tiles(K, out, inn, T, bf16):
     test_few_token_calls_element_by_element(K, out, inn, T, bf16)
 
