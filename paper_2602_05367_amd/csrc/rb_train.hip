@@ -18,6 +18,8 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
+#include <type_traits>
+
 #include "rabit.h"
 #include "rb_device.h"
 #include "rb_internal.h"
@@ -139,36 +141,43 @@ __global__ __launch_bounds__(256) void couple_kernel(const float *__restrict__ W
 // with the columns of a wavefront de-interleaved (slot 32 i + q holds column 4 q + i), so that
 //   * a write covers consecutive slots (no bank conflicts), and so does an operand read;
 //   * the four column accumulators of a lane are four consecutive columns of G: 16-byte stores.
-// 4096 x 11008, 512 samples: 0.090 ms (0.51 PFLOP/s, 2.0 TB/s of G stored), against 13.8 ms with one
-// thread per element and a scalar loop over the samples.
+// 4096 x 11008: 83 us at 512 samples (0.56 PFLOP/s, 2.2 TB/s of G stored), 223 at 2048, 32 at 33; with one step in flight, its loads in
+// branches and so every wait for all of them, 94, 261 and 33.  The store of a tile and the multiplications of the next do not overlap
+// much (32 us of the 83 are what 33 samples take): all workgroups run in step.
 constexpr int WG_ROWS = 128, WG_COLS = 256, WG_N = 32;      // tile of G, samples per step
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-// four columns of one sample (zero past the end of the samples or the columns); VEC: 8-byte loads
-template <bool VEC>
-__device__ __forceinline__ uint2 load_cols(const __half *p, int n, int N, int c, int width)
+// four columns of one sample (zero past the end of the samples or the columns), two bytes at a time
+__device__ __forceinline__ uint2 load_cols(const __half *p, size_t n, size_t N, int c, int width)
 {
     uint2 v = make_uint2(0u, 0u);
     if (n >= N) return v;
     const unsigned short *row = reinterpret_cast<const unsigned short *>(p) + (size_t)n * width;
-    if (VEC) {
-        if (c < width) v = *reinterpret_cast<const uint2 *>(row + c);
-    } else {
-        if (c < width) v.x = row[c];
-        if (c + 1 < width) v.x |= (uint32_t)row[c + 1] << 16;
-        if (c + 2 < width) v.y = row[c + 2];
-        if (c + 3 < width) v.y |= (uint32_t)row[c + 3] << 16;
-    }
+    if (c < width) v.x = row[c];
+    if (c + 1 < width) v.x |= (uint32_t)row[c + 1] << 16;
+    if (c + 2 < width) v.y = row[c + 2];
+    if (c + 3 < width) v.y |= (uint32_t)row[c + 3] << 16;
     return v;
+}
+// loads that return zero past the end of their buffer (NOWHERE always is)
+constexpr uint32_t NOWHERE = 0x40000000u;
+constexpr int WG_MAX_WIDTH = 1 << 23;                       // WG_N rows of that many columns stay below NOWHERE
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void *p, size_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
 }
 __device__ __forceinline__ uint32_t low_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
 __device__ __forceinline__ uint32_t high_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 
-template <bool VEC>
+// FORM: rows of Delta, X and G that start at multiples of 8 (G: 16) bytes (ALIGNED), of X and G only (DELTA_OFF: Delta's are read
+// as they lie; 4095 x 4096 with 512 samples 35 us, 115 two bytes at a time), neither (ANY: two bytes at a time)
+enum Form { ALIGNED, DELTA_OFF, ANY };
+template <Form FORM>
 __global__ __launch_bounds__(256, 2) void weight_grad_kernel(const __half *__restrict__ Delta, const __half *__restrict__ X,
                                                              int N, int out, int in, float *__restrict__ G)
 {
+    constexpr bool VEC = FORM != ANY;
     constexpr int A_BYTES = WG_ROWS * WG_N * 2, B_BYTES = WG_COLS * WG_N * 2;
     __shared__ __attribute__((aligned(16))) uint8_t lds[2][A_BYTES + B_BYTES];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -183,28 +192,59 @@ __global__ __launch_bounds__(256, 2) void weight_grad_kernel(const __half *__res
     // this thread's part of a step: 4 samples x 4 columns of Delta, 8 samples x 4 columns of X
     const int qa = tid & 31, na = tid >> 5, qb = tid & 63, nb = tid >> 6;
     const int slot_a = (qa >> 4) * 64 + (qa & 15), slot_b = (qb >> 5) * 128 + (qb & 31);
-    uint2 da[4], xb[8];
-    auto request = [&](int n0) {
+    // Two steps are in flight beside the one that is multiplied: a step is 0.5 us of matrix instructions, less than its loads take.  They
+    // sit in buffers of their own (set 0, 1), and no branch is around any of them
+    constexpr int SETS = VEC ? 2 : 1;
+    uint2 da[SETS][4], xb[SETS][8];
+    const uint32_t a_off = r0 + 4 * qa < out ? ((uint32_t)(4 * na) * (uint32_t)out + (uint32_t)(r0 + 4 * qa)) * 2u : NOWHERE;
+    // Delta off alignment: the four columns from a_at, moved down by a_shift bits where those are not the lane's own
+    const uint32_t a_at = (uint32_t)min(r0 + 4 * qa, out - 4), a_shift = 16u * (uint32_t)min(r0 + 4 * qa - (int)a_at, 4);
+    const uint32_t b_off = c0 + 4 * qb < in ? ((uint32_t)(8 * nb) * (uint32_t)in + (uint32_t)(c0 + 4 * qb)) * 2u : NOWHERE;
+    auto request = [&](size_t n0, auto set) {
+        if constexpr (VEC) {
+            const size_t rows = min((size_t)WG_N, (size_t)N - n0);
+            const __amdgpu_buffer_rsrc_t a_rs = buffer(Delta + n0 * out, rows * out * 2), b_rs = buffer(X + n0 * in, rows * in * 2);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) da[j] = load_cols<VEC>(Delta, n0 + 4 * na + j, N, r0 + 4 * qa, out);
+            for (int j = 0; j < 4; ++j) {
+                if (FORM == ALIGNED) da[set][j] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(a_rs, (int)(a_off + (uint32_t)j * (uint32_t)out * 2u), 0, 0));
+                // (samples past the end: the last one, whose X reads as zero and which `put` clears)
+                else __builtin_memcpy(&da[set][j], Delta + n0 * out + (size_t)((uint32_t)min(4 * na + j, (int)rows - 1) * (uint32_t)out + a_at), 8);
+            }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) xb[j] = load_cols<VEC>(X, n0 + 8 * nb + j, N, c0 + 4 * qb, in);
+            for (int j = 0; j < 8; ++j) xb[set][j] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(b_rs, (int)(b_off + (uint32_t)j * (uint32_t)in * 2u), 0, 0));
+            __builtin_amdgcn_sched_barrier(0);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) da[set][j] = load_cols(Delta, n0 + 4 * na + j, N, r0 + 4 * qa, out);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) xb[set][j] = load_cols(X, n0 + 8 * nb + j, N, c0 + 4 * qb, in);
+        }
     };
-    auto put = [&](uint8_t *buf) {
+    auto put = [&](uint8_t *buf, auto set, [[maybe_unused]] size_t n0) {
+        uint2 d[4];
+        const uint2 (&x)[8] = xb[set];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            d[j] = da[set][j];
+            if (FORM == DELTA_OFF) {
+                const unsigned long long v = __builtin_bit_cast(unsigned long long, d[j]);
+                d[j] = __builtin_bit_cast(uint2, a_shift < 64 && n0 + 4 * na + j < (size_t)N ? v >> a_shift : 0ull);
+            }
+        }
         uint8_t *const a = buf + (na >> 1) * (WG_ROWS * 16) + slot_a * 16 + (na & 1) * 8;
-        *reinterpret_cast<uint2 *>(a) = make_uint2(low_halves(da[0].x, da[1].x), low_halves(da[2].x, da[3].x));
-        *reinterpret_cast<uint2 *>(a + 16 * 16) = make_uint2(high_halves(da[0].x, da[1].x), high_halves(da[2].x, da[3].x));
-        *reinterpret_cast<uint2 *>(a + 32 * 16) = make_uint2(low_halves(da[0].y, da[1].y), low_halves(da[2].y, da[3].y));
-        *reinterpret_cast<uint2 *>(a + 48 * 16) = make_uint2(high_halves(da[0].y, da[1].y), high_halves(da[2].y, da[3].y));
+        *reinterpret_cast<uint2 *>(a) = make_uint2(low_halves(d[0].x, d[1].x), low_halves(d[2].x, d[3].x));
+        *reinterpret_cast<uint2 *>(a + 16 * 16) = make_uint2(high_halves(d[0].x, d[1].x), high_halves(d[2].x, d[3].x));
+        *reinterpret_cast<uint2 *>(a + 32 * 16) = make_uint2(low_halves(d[0].y, d[1].y), low_halves(d[2].y, d[3].y));
+        *reinterpret_cast<uint2 *>(a + 48 * 16) = make_uint2(high_halves(d[0].y, d[1].y), high_halves(d[2].y, d[3].y));
         uint8_t *const b = buf + A_BYTES + nb * (WG_COLS * 16) + slot_b * 16;
         uint4 v[4];
         uint32_t *const w = reinterpret_cast<uint32_t *>(v);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            w[j] = low_halves(xb[2 * j].x, xb[2 * j + 1].x);
-            w[4 + j] = high_halves(xb[2 * j].x, xb[2 * j + 1].x);
-            w[8 + j] = low_halves(xb[2 * j].y, xb[2 * j + 1].y);
-            w[12 + j] = high_halves(xb[2 * j].y, xb[2 * j + 1].y);
+            w[j] = low_halves(x[2 * j].x, x[2 * j + 1].x);
+            w[4 + j] = high_halves(x[2 * j].x, x[2 * j + 1].x);
+            w[8 + j] = low_halves(x[2 * j].y, x[2 * j + 1].y);
+            w[12 + j] = high_halves(x[2 * j].y, x[2 * j + 1].y);
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4 *>(b + i * 32 * 16) = v[i];
@@ -218,15 +258,8 @@ __global__ __launch_bounds__(256, 2) void weight_grad_kernel(const __half *__res
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[m][i][e] = 0.f;
 
-    request(0);
-    put(lds[0]);
-    int cur = 0;
-    // (n0 + WG_N is a sample's number only while there are more; beyond 2^31 - 32 of them it would not be an int)
-    for (int n0 = 0, left = N; left > 0; n0 += left > WG_N ? WG_N : 0, left -= WG_N, cur ^= 1) {
-        const bool more = left > WG_N;
-        if (more) request(n0 + WG_N);
-        __syncthreads();                                   // this step's tile is complete, the other one free
-        const uint8_t *const a = lds[cur] + (wr * 64 + (lane & 31)) * 16, *const b = lds[cur] + A_BYTES + (wc * 128 + (lane & 31)) * 16;
+    auto multiply = [&](const uint8_t *buf) {
+        const uint8_t *const a = buf + (wr * 64 + (lane & 31)) * 16, *const b = buf + A_BYTES + (wc * 128 + (lane & 31)) * 16;
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
             const int group = 2 * kk + (lane >> 5);
@@ -240,7 +273,57 @@ __global__ __launch_bounds__(256, 2) void weight_grad_kernel(const __half *__res
 #pragma unroll
                 for (int i = 0; i < 4; ++i) acc[m][i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[m], bv[i], acc[m][i], 0, 0, 0);
         }
-        if (more) put(lds[cur ^ 1]);
+    };
+    constexpr std::integral_constant<int, 0> S0;
+    constexpr std::integral_constant<int, SETS - 1> S1;
+    // (sample numbers in 64 bits: beyond 2^31 - 128 of them the next steps' would not be an int)
+    request(0, S0);
+    if constexpr (VEC) {
+        // (the last steps by themselves: a request that fetches nothing takes its turn all the same, and one in a branch would make
+        // every wait as long as the longest)
+        const size_t steps = ((size_t)N + WG_N - 1) / WG_N;
+        if (steps > 1) request(WG_N, S1);
+        put(lds[0], S0, 0);
+        if (steps > 2) request(2 * WG_N, S0);
+        size_t s = 0;
+        for (; s + 4 < steps; s += 2) {
+            __syncthreads();                               // this step's tile is complete, the other one free
+            multiply(lds[0]);
+            put(lds[1], S1, (s + 1) * WG_N);
+            request((s + 3) * WG_N, S1);
+            __syncthreads();
+            multiply(lds[1]);
+            put(lds[0], S0, (s + 2) * WG_N);
+            request((s + 4) * WG_N, S0);
+        }
+        __syncthreads();
+        multiply(lds[0]);
+        if (s + 1 < steps) {
+            put(lds[1], S1, (s + 1) * WG_N);
+            if (s + 3 < steps) request((s + 3) * WG_N, S1);
+            __syncthreads();
+            multiply(lds[1]);
+        }
+        if (s + 2 < steps) {
+            put(lds[0], S0, (s + 2) * WG_N);
+            __syncthreads();
+            multiply(lds[0]);
+        }
+        if (s + 3 < steps) {
+            put(lds[1], S1, (s + 3) * WG_N);
+            __syncthreads();
+            multiply(lds[1]);
+        }
+    } else {
+        put(lds[0], S0, 0);
+        int cur = 0;
+        for (size_t n0 = 0; n0 < (size_t)N; n0 += WG_N, cur ^= 1) {
+            const bool more = n0 + WG_N < (size_t)N;
+            if (more) request(n0 + WG_N, S0);
+            __syncthreads();
+            multiply(lds[cur]);
+            if (more) put(lds[cur ^ 1], S0, n0 + WG_N);
+        }
     }
 
     // accumulator element e of a lane: matrix row rho = 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32;
@@ -264,7 +347,8 @@ __global__ __launch_bounds__(256, 2) void weight_grad_kernel(const __half *__res
         }
 }
 
-// Both scale gradients from one pass over G.  A wavefront takes a slab of ROW_SLICE rows by 256
+// Both scale gradients from one pass over G (4096 x 11008, two paths: 36 us + 4.5 for the sums; 43 with the paths counted at run time, a
+// conversion of all three paths' h and loads in branches; with the next eight rows in flight as well, which spills, 51).  A wavefront takes a slab of ROW_SLICE rows by 256
 // columns, a lane four consecutive columns (one 16-byte load of G and four bits of a sign word per
 // row and path), eight rows in flight.  The column sums of grad h stay in the lane (rows in order);
 // the row sums of grad g need the whole wavefront: the eight rows of a group are summed together,
@@ -272,42 +356,56 @@ __global__ __launch_bounds__(256, 2) void weight_grad_kernel(const __half *__res
 // 4 (l & 1) + 2 (l >> 1 & 1) + (l >> 2 & 1) of the group, summed over its eight lanes) and three
 // more over the eight-lane groups.  Partial sums: [slice][K][in] and [column block][K][out]; the
 // second kernel adds them in order, so results repeat bit for bit.
-__global__ __launch_bounds__(64) void grad_slab_kernel(const float *__restrict__ G, const uint32_t *__restrict__ packed,
-                                                       const __half *__restrict__ g, const __half *__restrict__ h, int K,
-                                                       int out, int in, float *__restrict__ part_h,
-                                                       float *__restrict__ part_g)
+template <int K>
+__global__ __launch_bounds__(64, K < 3 ? 4 : 2) void grad_slab_kernel(const float *__restrict__ G, const uint32_t *__restrict__ packed,
+                                                          const __half *__restrict__ g, const __half *__restrict__ h,
+                                                          int out, int in, float *__restrict__ part_h,
+                                                          float *__restrict__ part_g)
 {
     const int lane = threadIdx.x;
     const int c = (blockIdx.x * 64 + lane) * 4, slice = blockIdx.y;
     const bool real = c < in;                                  // in % 32 == 0: all four columns or none
     const int cs = real ? c : 0;
     const int W32 = in / 32, r0 = slice * ROW_SLICE, r1 = min(out, r0 + ROW_SLICE);
-    float sh[RB_MAX_K][4], hv[RB_MAX_K][4];
-    for (int k = 0; k < RB_MAX_K; ++k)
-        for (int e = 0; e < 4; ++e) {
-            sh[k][e] = 0.f;
-            hv[k][e] = k < K && real ? __half2float(h[(size_t)k * in + c + e]) : 0.f;
+    // eight rows: no branch around their loads (rows past the end: the last one, whose values do not count)
+    struct Rows { float4 v[8]; uint32_t bits[K][8]; };
+    auto fetch = [&](int rb, Rows &to) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int r = min(rb + u, r1 - 1);
+            to.v[u] = *reinterpret_cast<const float4 *>(G + (size_t)r * in + cs);
+#pragma unroll
+            for (int k = 0; k < K; ++k) to.bits[k][u] = packed[((size_t)k * out + r) * W32 + (cs >> 5)];
         }
+    };
+    float sh[K][4], hv[K][4];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            hv[k][e] = __half2float(h[(size_t)k * in + cs + e]);
+            sh[k][e] = 0.f;
+        }
+    }
     const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
     const int my_row = 4 * (int)b0 + 2 * (int)b1 + (int)b2;
+#pragma unroll 1
     for (int rb = r0; rb < r1; rb += 8) {
-        float4 gv[8];
+        Rows now;
+        fetch(rb, now);
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-            gv[u] = real && rb + u < r1 ? *reinterpret_cast<const float4 *>(G + (size_t)(rb + u) * in + c)
-                                        : make_float4(0.f, 0.f, 0.f, 0.f);
         for (int k = 0; k < K; ++k) {
             float rp[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int r = min(rb + u, r1 - 1);             // rows past the end: G read as zero above
-                const float v[4] = {gv[u].x, gv[u].y, gv[u].z, gv[u].w};
-                const uint32_t bits4 = packed[((size_t)k * out + r) * W32 + (cs >> 5)] >> (cs & 31);
-                const float gk = __half2float(g[(size_t)k * out + r]);
+                const bool counts = real && rb + u < r1;
+                const float v[4] = {counts ? now.v[u].x : 0.f, counts ? now.v[u].y : 0.f, counts ? now.v[u].z : 0.f, counts ? now.v[u].w : 0.f};
+                const uint32_t bits4 = now.bits[k][u] >> (cs & 31);
+                const float gk = __half2float(g[(size_t)k * out + min(rb + u, r1 - 1)]);
                 float rs = 0.f;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float sv = (bits4 >> e) & 1u ? -v[e] : v[e];
+                    const float sv = __uint_as_float(__float_as_uint(v[e]) ^ (bits4 << (31 - e) & 0x80000000u));
                     sh[k][e] = __builtin_fmaf(gk, sv, sh[k][e]);
                     rs = __builtin_fmaf(hv[k][e], sv, rs);
                 }
@@ -326,6 +424,7 @@ __global__ __launch_bounds__(64) void grad_slab_kernel(const float *__restrict__
         }
     }
     if (real)
+#pragma unroll
         for (int k = 0; k < K; ++k)
             *reinterpret_cast<float4 *>(part_h + ((size_t)slice * K + k) * in + c) =
                 make_float4(sh[k][0], sh[k][1], sh[k][2], sh[k][3]);
@@ -390,13 +489,14 @@ extern "C" int rb_weight_grad(const uint16_t *Delta, const uint16_t *X, int N, i
     if (N < 1 || out < 1 || in < 1 || out > 65535) return RB_ERR_SHAPE;
     const int tiles = (out + WG_ROWS - 1) / WG_ROWS * ((in + WG_COLS - 1) / WG_COLS);
     const dim3 grid((unsigned)((tiles + 7) / 8 * 8));
-    const bool vec = out % 4 == 0 && in % 4 == 0 && (((uintptr_t)Delta | (uintptr_t)X) & 7) == 0 && ((uintptr_t)G & 15) == 0;
+    const bool x_aligned = in % 4 == 0 && in < WG_MAX_WIDTH && ((uintptr_t)X & 7) == 0 && ((uintptr_t)G & 15) == 0;
+    const bool d_aligned = out % 4 == 0 && ((uintptr_t)Delta & 7) == 0;
     const __half *d = reinterpret_cast<const __half *>(Delta), *x = reinterpret_cast<const __half *>(X);
     hipStream_t stream = static_cast<hipStream_t>(stream_);
-    if (vec)
-        hipLaunchKernelGGL(weight_grad_kernel<true>, grid, dim3(256), 0, stream, d, x, N, out, in, G);
-    else                                                       // rows that do not start at multiples of 8 bytes
-        hipLaunchKernelGGL(weight_grad_kernel<false>, grid, dim3(256), 0, stream, d, x, N, out, in, G);
+    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, d, x, N, out, in, G); };
+    if (x_aligned && d_aligned) run(weight_grad_kernel<ALIGNED>);
+    else if (x_aligned && out >= 4) run(weight_grad_kernel<DELTA_OFF>);
+    else run(weight_grad_kernel<ANY>);
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;
 }
 
@@ -421,8 +521,13 @@ extern "C" int rb_scale_grads(const float *G, const uint32_t *packed, const uint
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     const int col_blocks = (in + 255) / 256;
     float *part_h = static_cast<float *>(workspace), *part_g = part_h + (size_t)slices * K * in;
-    hipLaunchKernelGGL(grad_slab_kernel, dim3((unsigned)col_blocks, (unsigned)slices), dim3(64), 0, stream, G, packed,
-                       reinterpret_cast<const __half *>(g), reinterpret_cast<const __half *>(h), K, out, in, part_h, part_g);
+    auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)col_blocks, (unsigned)slices), dim3(64), 0, stream, G, packed,
+                           reinterpret_cast<const __half *>(g), reinterpret_cast<const __half *>(h), out, in, part_h, part_g);
+    };
+    if (K == 1) run(grad_slab_kernel<1>);
+    else if (K == 2) run(grad_slab_kernel<2>);
+    else run(grad_slab_kernel<3>);
     hipLaunchKernelGGL(grad_finish_kernel, dim3((unsigned)((K * (in + out) + 255) / 256)), dim3(256), 0, stream, part_h,
                        slices, part_g, col_blocks, K, out, in, grad_g, grad_h);
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;

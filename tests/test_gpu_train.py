@@ -110,6 +110,20 @@ def test_weight_gradient_tiles_and_tails(N, out, inn, shift):
     assert np.all(err <= N * 2.0 ** -23 * (np.abs(D64).T @ np.abs(X64)))
 
 
+@pytest.mark.parametrize("N,out,inn,shift", [
+    # one to seven steps of 32 samples, whole and part-filled; rows of Delta that start at multiples of 2 and 4 bytes, last rows of one to
+    # three columns, fewer rows than a tile
+    (1, 4, 32, 0), (32, 131, 288, 0), (65, 5, 64, 0), (96, 258, 64, 0), (97, 777, 96, 0), (128, 132, 96, 0), (129, 133, 96, 0),
+    (160, 256, 96, 0), (161, 257, 32, 4), (193, 6, 256, 0), (224, 384, 32, 0)])
+def test_weight_gradient_steps_and_unaligned_rows(N, out, inn, shift):
+    test_weight_gradient_tiles_and_tails(N, out, inn, shift)
+
+
+@pytest.mark.parametrize("K,out,inn", [(1, 200, 288), (2, 129, 544), (3, 65, 1056)])
+def test_scale_gradients_of_part_filled_slices(K, out, inn):
+    test_scale_gradients_against_the_oracle(K, out, inn, 3)
+
+
 def test_training_entry_points_reject_bad_arguments():
     W = torch.zeros((4, 32), dtype=torch.float32, device="cuda")
     g = torch.zeros((2, 4), dtype=torch.float16, device="cuda")
