@@ -349,3 +349,32 @@ def test_full_7b_block_stack_as_benchmarked_sampled_outputs():
             worst = max(worst, err)
             assert err <= TOL, (op.name, err)
     print(f"  worst sampled rel_l2={worst:.3e}", flush=True)
+
+
+@pytest.mark.parametrize("T,n,shift", [(1, 1, 0), (3, 7, 1), (2, 8, 0), (5, 2047, 1), (2, 2049, 0), (3, 8191, 3), (2, 8193, 0), (1, 20005, 1)])
+def test_elementwise_kernels_at_every_remainder(T, n, shift):
+    """Eight values per thread: sizes around eight, around one and four pieces of 2048, pointers at odd elements, in place and not,
+    nothing written past the end."""
+    rng = synth.child_rng(6, 900, T, n)
+    a, b = ((rng.standard_normal((T, n)) * 2).astype(np.float16) for _ in range(2))
+
+    def at(v, pad=16):
+        t = torch.full((v.size + shift + pad,), 7.0, dtype=torch.float16, device="cuda")
+        t[shift:shift + v.size] = torch.from_numpy(v.flatten()).cuda()
+        return t
+    print(f"elementwise T={T} n={n} shift={shift}", flush=True)
+    p = lambda t: t.data_ptr() + 2 * shift
+    a64, b64 = a.astype(np.float64), b.astype(np.float64)
+    calls = ((lambda x, w, y: rb.lib.rb_rmsnorm(p(x), p(w), p(y), T, n, EPS, None), oracle.rmsnorm(a, b[0], EPS)),
+             (lambda x, w, y: rb.lib.rb_silu_mul(p(x), p(w), p(y), T * n, None), oracle.silu(a64) * b64),
+             (lambda x, w, y: rb.lib.rb_add(p(x), p(w), p(y), T * n, None), a64 + b64))
+    for call, ref in calls:
+        for in_place in (False, True):
+            x, w = at(a), at(b)
+            y = x if in_place else at(np.zeros_like(a))
+            assert call(x, w, y) == rb.RB_OK
+            torch.cuda.synchronize()
+            assert torch.all(y[shift + T * n:] == 7.0) and torch.all(y[:shift] == 7.0)
+            got = y[shift:shift + T * n].cpu().numpy().astype(np.float64).reshape(T, n)
+            # one rounding to fp16 (2^-11 of the value, or half a subnormal) of an fp32 result a few 2^-22 off
+            assert np.all(np.abs(got - ref) <= np.abs(ref) * (2.0 ** -11 + 2.0 ** -19) + 2.0 ** -25)
