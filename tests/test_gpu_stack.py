@@ -540,6 +540,28 @@ def test_single_call_decode_kernel_with_degenerate_scales_and_extreme_inputs(zer
     assert dead.size > 0 and np.all(got[0, dead] == 0.0)
 
 
+@pytest.mark.parametrize("out,inn", [(1, 32), (16, 1024), (17, 1056), (257, 2048), (300, 2080), (4111, 4064), (4160, 4128),
+                                     (61, 8192), (4097, 8224), (61, 12288), (4113, 12288)])
+def test_single_call_decode_kernel_forms(out, inn):
+    """One token at the edges of what a thread keeps of the input (1024 columns each, 1, 2, 4, 8 or 12 of them), with one
+    sign tile for a wavefront and with several, rows short of a tile: against the oracle, and the bits of the same op in
+    a stack."""
+    rng = synth.child_rng(0, 401, out, inn)
+    signs, g, h = random_layer(rng, 2, out, inn)
+    x = synth.outlier_activations(rng, 1, inn)
+    L = to_device_layer(signs, g, h)
+    print(f"single call out={out} in={inn}", flush=True)
+    bufs = [torch.from_numpy(x).cuda(), torch.zeros((1, out), dtype=torch.float16, device="cuda")]
+    y = rb.rb_linear_gemv(L, bufs[0][0])
+    torch.cuda.synchronize()
+    assert rb.rb_last_path() == rb.RB_PATH_MX
+    err = float(oracle.relative_l2(y.cpu().numpy().astype(np.float64)[None], oracle.forward(signs, g, h, x))[0])
+    print(f"  rel_l2={err:.3e}", flush=True)
+    assert err <= TOL
+    rb.rb_layer_stack([L], [(0, 0, 1)], bufs, 1)
+    assert torch.equal(y, bufs[1][0])
+
+
 @pytest.mark.parametrize("T", [1, 2])
 def test_stack_decode_kernel_with_degenerate_scales_and_extreme_inputs(T):
     """Three dependent ops through the persistent kernel.  The first op is fed from outside with
