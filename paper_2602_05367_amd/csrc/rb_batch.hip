@@ -174,7 +174,7 @@ __device__ __forceinline__ uint4 pair_order_as_fp16(uint4 v)
                       pair(v.y << 16, v.w << 16), pair(v.y & 0xffff0000u, v.w & 0xffff0000u));
 }
 
-constexpr int UNIT_COLS = 128, ROW_BYTES = 256;      // columns a wavefront stages at a time; a token's fp16 values of them
+constexpr int ROW_BYTES = UNIT_COLS * 2;             // a token's fp16 values of the columns that a wavefront stages at a time
 template <int K, int G, bool BF16> __host__ __device__ constexpr int slab_bytes() { return (16 * G + K * (BF16 ? 2 : 1)) * ROW_BYTES; }
 
 // K paths, G groups of 16 tokens, P row tiles per workgroup of W wavefronts at most, BF16: the activations are bfloat16
@@ -199,8 +199,8 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) ? 4 : 2) void batch_kern
     const int RT = row_tiles(out), CT = col_tiles(in), rt0 = (int)blockIdx.x * P;
     if (rt0 >= RT) return;                                     // (an op with fewer row tiles than another one of the launch)
 
-    // ---- a wavefront takes a run of units of 128 columns, half a sign tile wide
-    const int u0 = wave * op.run + min(wave, (int)op.rest), u1 = u0 + op.run + (wave < op.rest ? 1 : 0);
+    const UnitRun units = unit_run(wave, op.run, op.rest);
+    const int u0 = units.begin, u1 = units.end;
     // ---- staging.  A load instruction fetches 256 contiguous bytes of four tokens (a token per 16 lanes: 16
     // chunks of eight columns), so it touches eight lines; fetched in operand order it would touch 32 and
     // the address unit would bound the kernel.  Chunk 4 q + s (columns 32 q + 8 s ..) of a row goes to position
@@ -215,19 +215,21 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) ? 4 : 2) void batch_kern
     const uint32_t h_row = (uint32_t)row4 * (uint32_t)in;
     uint4 xs[4 * G], hs;
     Words<K> ws[P];
-    auto real = [&](int u) { return u * UNIT_COLS + 8 * ch < in; };              // in % 32 == 0: all eight columns or none
+    auto real = [&](int u) { return chunk_exists(u, ch, in); };
+    // (of a unit that exists: the loads of the scales know no end)
     auto request = [&](int u) {
         const bool some = real(u);
 #pragma unroll
         for (int i = 0; i < 4 * G; ++i)
             if (4 * i < T) xs[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(x_rs, (int)(some ? x_off[i] : NOWHERE), u * ROW_BYTES, 0));
         // (the scales need only be 2-byte aligned)
-        if (row4 < K) __builtin_memcpy(&hs, op.h + u * UNIT_COLS + (h_row + (some ? 8u * (uint32_t)ch : 0u)), 16);
+        if (row4 < K) __builtin_memcpy(&hs, op.h + u * UNIT_COLS + (h_row + chunk_scales_at(u, ch, in)), 16);
     };
+    const int p_last = min(P, RT - rt0) - 1;
     auto request_words = [&](int u) {
 #pragma unroll
         for (int p = 0; p < P; ++p)                            // a row tile past the end of the matrix reads as zero (not stored)
-            ws[p] = load_words<K>(w_rs, (rt0 + p < RT ? 0u : NOWHERE) + (uint32_t)lane * 8u * K, ((p * CT + (u >> 1)) * tile_words(K) + (u & 1) * K) * 4);
+            ws[p] = load_words<K>(w_rs, (p <= p_last ? 0u : NOWHERE) + (uint32_t)lane * 8u * K, ((min(p, p_last) * CT + (u >> 1)) * tile_words(K) + (u & 1) * K) * 4);
     };
     auto put_x = [&](auto order) {
 #pragma unroll
@@ -263,8 +265,9 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) ? 4 : 2) void batch_kern
             if (4 * i < T) range.look_at(xs[i]);
         return (bool)__any(range.beyond_fp16());
     };
-    request(u0);
-    request_words(u0);
+    const int u_first = first_request(units, in);
+    request(u_first);
+    request_words(u_first);
     // output scales, asked for now, shared through LDS when the sums are there
     constexpr int GV = (P * K * TILE_ROWS + 63) / 64;            // (a workgroup may have one wavefront only)
     uint16_t gval[GV];
@@ -454,7 +457,7 @@ static Shape shape_of(Args &args, int nops, int K, bool bf16)
     Shape s = {K, args.op[0].T, nops, 0, 0, 0};
     for (int i = 0; i < nops; ++i) {
         RT[i] = row_tiles(args.op[i].out);
-        units = std::max(units, (args.op[i].in + UNIT_COLS - 1) / UNIT_COLS);
+        units = std::max(units, units_of(args.op[i].in));
     }
     const int G = token_groups(s.T);
     s.P = row_tiles_per_wg(RT, nops, (units + 1) / 2, K, G, (s.T + 63) / 64, bf16);
@@ -465,7 +468,7 @@ static Shape shape_of(Args &args, int nops, int K, bool bf16)
     }
     s.nw = std::min(units, sixteen_available(G, s.P) && all <= mx::device_groups() ? 16 : 8);
     for (int i = 0; i < nops; ++i) {
-        const int n = (args.op[i].in + UNIT_COLS - 1) / UNIT_COLS;
+        const int n = units_of(args.op[i].in);
         args.op[i].waves = (uint16_t)s.nw;
         args.op[i].run = n / s.nw;
         args.op[i].rest = (uint16_t)(n % s.nw);

@@ -51,4 +51,23 @@ RB_HD inline uint32_t to_canonical_word(uint32_t native)
     return w;
 }
 
+// Few-token kernel: a wavefront takes a run of units of 128 columns, half a sign tile wide; the first `rest` of a
+// workgroup's wavefronts one unit more than the others.  An op narrower than another one of its launch may
+// leave wavefronts without a unit.
+constexpr int UNIT_COLS = 128;
+RB_HD constexpr int units_of(int in) { return (in + UNIT_COLS - 1) / UNIT_COLS; }
+struct UnitRun { int begin, end; };
+RB_HD constexpr UnitRun unit_run(int wave, int run, int rest)
+{
+    const int begin = wave * run + (wave < rest ? wave : rest);
+    return {begin, begin + run + (wave < rest ? 1 : 0)};
+}
+// what a wavefront asks for before anything else: its first unit; without one the last unit there is, so that
+// no request lies past the end of a layer
+RB_HD constexpr int first_request(UnitRun r, int in) { return r.begin < units_of(in) ? r.begin : units_of(in) - 1; }
+// chunk ch (0..15) of unit u is columns 128 u + 8 ch ..: there are eight of them or none (in % 32 == 0)
+RB_HD constexpr bool chunk_exists(int u, int ch, int in) { return u * UNIT_COLS + 8 * ch < in; }
+// where in its unit the scales of a chunk are read: a chunk past the last column reads the unit's first (and is cleared)
+RB_HD constexpr uint32_t chunk_scales_at(int u, int ch, int in) { return chunk_exists(u, ch, in) ? 8u * (uint32_t)ch : 0u; }
+
 }  // namespace rb

@@ -194,6 +194,26 @@ def test_many_independent_rows_take_larger_row_blocks(n_ops, T):
     _check_stack(layers, op_list, (inn,) + (out,) * n_ops, x, T, f"{n_ops} independent ops of {out} rows", prepared=(T >= 8))
 
 
+@pytest.mark.parametrize("narrow,wide,T,K", [(1024, 4096, 16, 2), (32, 4128, 5, 2), (896, 2080, 9, 2), (32, 1056, 16, 3), (1920, 4096, 6, 3), (96, 11008, 8, 2)])
+def test_ops_of_different_widths_share_a_launch(narrow, wide, T, K):
+    """Two independent ops in one launch, whose workgroups have as many wavefronts as the wider one has use for: some have no columns
+    of the narrower op.  Its scales fill an allocation of their own."""
+    rng = synth.child_rng(3, 511, narrow, wide, T)
+    layers, dev, widths = [], [], (narrow, wide, 300, 130)
+    for o, i in ((300, narrow), (130, wide)):
+        signs, g, h = random_layer(rng, K, o, i, gain=1.0 / (np.sqrt(i * K) * (0.02 * 0.02)))
+        layers.append((signs, g, h))
+        dev.append(to_device_layer(signs, g, h))
+    xs = [synth.outlier_activations(rng, T, w) for w in (narrow, wide)]
+    bufs = [torch.from_numpy(x).cuda() for x in xs] + [torch.zeros((T, w), dtype=torch.float16, device="cuda") for w in widths[2:]]
+    print(f"ops of {narrow} and {wide} columns in one launch, T={T} K={K}", flush=True)
+    rb.rb_layer_stack(dev, [(0, 0, 2), (1, 1, 3)], bufs, T)
+    torch.cuda.synchronize()
+    assert rb.rb_last_path() == rb.RB_PATH_BATCH
+    for n in range(2):
+        assert max_rel_l2(bufs[2 + n], oracle.forward(*layers[n], xs[n])) <= TOL, n
+
+
 @pytest.mark.parametrize("T", [1, 3, 8])
 def test_scales_that_are_only_two_byte_aligned(T):
     """g and h need no more than the alignment of their elements: a two-op chain whose scale

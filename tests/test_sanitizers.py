@@ -25,3 +25,12 @@ def test_oracle_and_host_packing_under_asan_and_ubsan(tmp_path):
     assert res.returncode == 0, res.stdout
     assert "all shapes passed" in res.stdout
     assert "runtime error" not in res.stdout and "AddressSanitizer" not in res.stdout, res.stdout
+
+
+def test_requests_of_the_few_token_kernel_stay_inside_a_layer(tmp_path):
+    """Ops of different widths share a launch: a wavefront that has no columns of the narrower one reads nothing past its end."""
+    exe = str(tmp_path / "units_driver")
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-fsanitize=address,undefined", "-static-libasan", "-fno-sanitize-recover=all", "-g", "-O1",
+                           "-I", os.path.join(ROOT, "paper_2602_05367_amd", "csrc"), os.path.join(ROOT, "tests", "sanitize", "units.cpp"), "-o", exe])
+    res = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert res.returncode == 0 and "all in bounds" in res.stdout, res.stdout
