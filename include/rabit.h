@@ -111,7 +111,7 @@ int rb_linear_gemv(const rb_layer *L, const uint16_t *x, uint16_t *y,
  * T otherwise runs as a dense contraction on the matrix cores, Y = W_hat X with the
  * effective weight W_hat = sum_k g_k (.) B_k (.) h_k (the form Alg. 2 gives for
  * batched inputs), which the kernel builds in fp16 registers from the packed
- * signs (two roundings per weight, a few 1e-4 relative on the output; fp32
+ * signs (as many roundings per weight as paths, a few 1e-4 relative on the output; fp32
  * accumulation) and with the activations in fp16: bfloat16 ones are infinite there
  * from 65520 on and lose bits below 2^-17.
  * Y may overlap X from three tokens on (K = 3: from six; never for K = 1 and for inputs

@@ -5,12 +5,18 @@
 // W_hat = sum_k g_k (.) B_k (.) h_k (Alg. 2, "compute layer output") on v_mfma_f32_32x32x16_f16.  The left
 // operand is W_hat itself, built in registers from the packed signs on the way to the matrix
 // instruction and never stored.  Per pair of fp16 elements and path: a shift brings the two sign bits
-// to bits 15 and 31, one three-input logic operation puts them on the pair of h_k; a packed fused multiply-add per path but the
-// first adds them up as h_0 B_0 + rho_k h_k B_k: five vector instructions for two paths, one rounding of the sum and one of
-// rho_k = g_k / g_0, which a lane keeps for its row.  g_0 multiplies the fp32 sums at the end.  (With g_k on every path it
-// was a multiplication and a wait state for its result more: seven of eight issue slots per pair against five, and two more
-// roundings; 4096 x 11008 at 512 tokens 80.9 us, now 71.9, 28672 x 8192 at 100 91.6 and 81.0, at 2048 989 and 964.)  Powers of two
-// (s_k that brings max|h_k| into [1/4, 1/2)) keep the terms in fp16's normal range however the layer splits its magnitude.
+// to bits 15 and 31, one three-input logic operation puts them on the pair of h_k.  Two forms add the paths up:
+//   * h_0 B_0 + rho_k h_k B_k with rho_k = g_k / g_0 in fp16 and g_0 on the fp32 sums at the end, a packed fused multiply-add per
+//     path but the first: five vector instructions for two paths, one rounding of the sum and one of rho_k.  Taken by a workgroup in all of
+//     whose rows path 0 weighs (g_k^2 |h_k|^2) as much as the others together, as it does in a layer whose paths are residuals of one another:
+//     there the rounding of rho_k, relative to the row, is no larger than that of g_0 h_0 B_0 which it replaces;
+//   * G_k h_k B_k summed over all paths, G_k = g_k but for a power of two per row, exact: a multiplication more and a wait state for its
+//     result, seven of eight issue slots per pair against five, and a rounding per path.
+// Measured, first form and second: 4096 x 11008 at 512 tokens 77 and 82 us, 28672 x 8192 at 100 88 and 93, at 2048 954 and 989; three
+// paths, 11008 x 4096 at 2048 237 and 246.  Error against fp64, all rows and the worst of 256: even scales (residual paths) 2.0e-4 and 2.6e-4
+// (2.7e-4 and 4.6e-4 in the second form), scales spread by e^N(0,1) 2.8e-4 and 3.4e-4 in the second (2.3e-4 and 4.9e-4 in the first; and a
+// per cent where an uneven h_1 stands beside a row without g_0).  Powers of two (s_k that brings max|h_k| into [1/4, 1/2)) keep the
+// terms in fp16's normal range however the layer splits its magnitude.
 //
 // What bounds it: the vector instructions that build W_hat, until some 128 tokens share them, then the
 // matrix units (a wavefront hides about six vector instructions behind one 32x32x16 instruction,
@@ -29,13 +35,14 @@
 //   * the tile is brought to the output's type in LDS and stored as whole rows;
 //   * the left operand of the next row block is built between the matrix instructions of this one.
 //
-// Measured, fp16, two paths, calls in a row in a graph: 4096 x 4096 at 333 tokens 32 us, 11008 x 4096 54 us, 4096 x 11008 66 us,
-// 8192 x 8192 at 1024 149 us (0.92 PFLOP/s), 28672 x 8192 at 2048 tokens 0.96 ms.
+// Measured, fp16, two paths, first form, calls in a row in a graph: 4096 x 4096 at 333 tokens 30-32 us, 11008 x 4096 52-55 us,
+// 4096 x 11008 61-66 us, 8192 x 8192 at 1024 141 us (0.97 PFLOP/s), 28672 x 8192 at 2048 tokens 0.95-0.97 ms.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "rabit.h"
 #include "rb_device.h"
@@ -90,16 +97,16 @@ __device__ __forceinline__ uint4 pair_order_of_bf16(uint4 v)
 {
     return make_uint4(low_bf16(v.x, v.z), high_bf16(v.x, v.z), low_bf16(v.y, v.w), high_bf16(v.y, v.w));
 }
-__device__ __forceinline__ float abs_max8(uint4 v)
+// of eight fp16 values
+__device__ __forceinline__ void largest_and_squares(uint4 v, float &m, float &sq)
 {
-    float m = 0.f;
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        m = fmaxf(m, fabsf(__half2float(__ushort_as_half((unsigned short)(w[i] & 0xffffu)))));
-        m = fmaxf(m, fabsf(__half2float(__ushort_as_half((unsigned short)(w[i] >> 16)))));
+        const float a = __half2float(__ushort_as_half((unsigned short)(w[i] & 0xffffu))), b = __half2float(__ushort_as_half((unsigned short)(w[i] >> 16)));
+        m = fmaxf(m, fmaxf(fabsf(a), fabsf(b)));
+        sq = __builtin_fmaf(a, a, __builtin_fmaf(b, b, sq));
     }
-    return m;
 }
 // loads that return zero past the end of their buffer (NOWHERE always is)
 constexpr uint32_t NOWHERE = 0x40000000u;
@@ -123,8 +130,9 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
     static_assert(MB == 2 && TOK * 16 % GT == 0 && XL % 2 == 0, "whole loads per thread");
     static_assert(TOK * (64 * WR * 4 + 16) <= lds_bytes<K, NT, WR>() && 32768 * NT <= lds_bytes<K, NT, WR>(), "what reuses the slabs fits");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];       // [column group][2][SLAB]
-    __shared__ float red[RB_MAX_K][WAVES];
+    __shared__ float red[2 * RB_MAX_K][WAVES];
     __shared__ __attribute__((aligned(16))) float row_scale[64 * WR];
+    __shared__ int uneven[WR];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -213,51 +221,77 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
 #pragma unroll
         for (int k = 0; k < K; ++k) gv[b][k] = __half2float(args.g[(size_t)k * out + min(rt0 * TILE_ROWS + 32 * b + r, out - 1)]);
 
-    // ---- powers of two that bring the scales h of a path to [1/4, 1/2)
-    float mx_h[K];
+    // ---- powers of two that bring the scales h of a path to [1/4, 1/2), and the sum of their squares
+    float mx_h[K], sq_h[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        mx_h[k] = 0.f;
-        for (int j = tid * 8; j < in; j += WAVES * 64 * 8) mx_h[k] = fmaxf(mx_h[k], abs_max8(buffer_load(h_rs, (uint32_t)(k * in + j) * 2u, 0)));
+        mx_h[k] = sq_h[k] = 0.f;
+        for (int j = tid * 8; j < in; j += WAVES * 64 * 8) largest_and_squares(buffer_load(h_rs, (uint32_t)(k * in + j) * 2u, 0), mx_h[k], sq_h[k]);
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        for (int d = 32; d > 0; d >>= 1) mx_h[k] = fmaxf(mx_h[k], __shfl_xor(mx_h[k], d));
-        if (lane == 0) red[k][wave] = mx_h[k];
+        for (int d = 32; d > 0; d >>= 1) {
+            mx_h[k] = fmaxf(mx_h[k], __shfl_xor(mx_h[k], d));
+            sq_h[k] += __shfl_xor(sq_h[k], d);
+        }
+        if (lane == 0) { red[2 * k][wave] = mx_h[k]; red[2 * k + 1][wave] = sq_h[k]; }
     }
     __syncthreads();
-    float sk[K];
+    float sk[K], weight[MB][K];                                // weight: what path k adds to the squared norm of a row of W_hat
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        float a = 0.f;
+        float a = 0.f, sq = 0.f;
 #pragma unroll
-        for (int v = 0; v < WAVES; ++v) a = fmaxf(a, red[k][v]);
+        for (int v = 0; v < WAVES; ++v) { a = fmaxf(a, red[2 * k][v]); sq += red[2 * k + 1][v]; }
         sk[k] = mx::input_scale(a);
         if (row0 == k) h_scale = sk[k];
 #pragma unroll
-        for (int b = 0; b < MB; ++b) gv[b][k] = a > 0.f ? gv[b][k] / sk[k] : 0.f;       // (a path without a scale has no say)
+        for (int b = 0; b < MB; ++b) {
+            weight[b][k] = gv[b][k] * gv[b][k] * sq;
+            gv[b][k] = a > 0.f ? gv[b][k] / sk[k] : 0.f;       // (a path without a scale has no say)
+        }
     }
-    // ---- a row of W_hat as base (h_0 B_0 + sum_k rho_k h_k B_k): the base is path 0's output scale, or 2^-15 of the largest one where
-    // path 0 has none or a smaller one (what it adds then is less than the last bit of the others)
-    v2h rho[MB][K - 1];
+    // ---- may path 0 carry the others (the first form above)?  (a NaN compares false: no)
+    bool carries = true;
 #pragma unroll
     for (int b = 0; b < MB; ++b) {
-        float most = fabsf(gv[b][0]), base = gv[b][0];
+        float others = 0.f;
 #pragma unroll
-        for (int k = 1; k < K; ++k) most = fmaxf(most, fabsf(gv[b][k]));
-        if (fabsf(base) < most * 0x1p-15f) base = most * 0x1p-15f;
+        for (int k = 1; k < K; ++k) others += weight[b][k];
+        carries = carries && others <= weight[b][0];
+    }
+    const bool all_carry = __all(carries);
+    if (grp == 0 && lane == 0) uneven[wr] = !all_carry;
+    // ---- a row of W_hat as base (h_0 B_0 + sum_k rho_k h_k B_k), base = g_0, if so; else (further down) as base (sum_k G_k h_k B_k), base a
+    // power of two that leaves the row's largest G_k in [1/4, 1/2)
+    auto both = [](float f) { const _Float16 v = (_Float16)f; return (v2h){v, v}; };
+    v2h coef[MB][K];
 #pragma unroll
-        for (int k = 1; k < K; ++k) {
-            const _Float16 v = (_Float16)(base != 0.f ? gv[b][k] / base : 0.f);
-            rho[b][k - 1] = (v2h){v, v};
-        }
-        if (grp == 0 && kg == 0) row_scale[64 * wr + 32 * b + r] = base;
+    for (int b = 0; b < MB; ++b) {
+        coef[b][0] = both(1.f);
+#pragma unroll
+        for (int k = 1; k < K; ++k) coef[b][k] = both(gv[b][0] != 0.f ? gv[b][k] / gv[b][0] : 0.f);
+        if (grp == 0 && kg == 0) row_scale[64 * wr + 32 * b + r] = gv[b][0];
     }
     put(0, 0);
     if (SHORT) request(s_begin, 1); else request(s_begin + 1, 0);
     put(0, 1);
     if (!SHORT) request(s_begin + 1, 1);
     __syncthreads();
+    bool ratios = true;                                        // uniform over the workgroup
+#pragma unroll
+    for (int v = 0; v < WR; ++v) ratios = ratios && __builtin_amdgcn_readfirstlane(uneven[v]) == 0;
+    if (!ratios)
+#pragma unroll
+        for (int b = 0; b < MB; ++b) {
+            float most = fabsf(gv[b][0]);
+#pragma unroll
+            for (int k = 1; k < K; ++k) most = fmaxf(most, fabsf(gv[b][k]));
+            const float S = mx::input_scale(most);
+#pragma unroll
+            for (int k = 0; k < K; ++k) coef[b][k] = both(gv[b][k] * S);
+            if (grp == 0 && kg == 0) row_scale[64 * wr + 32 * b + r] = 1.f / S;
+        }
 
     v16f acc[MB][NT];
 #pragma unroll
@@ -281,64 +315,72 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
         for (int n = 0; n < NT; ++n) x[to][n] = *reinterpret_cast<const v8h *>(slab + (x_addr ^ (uc * 16)) + n * 32 * ROW_BYTES);
     };
     // register j of the left operand of row block b, columns of contraction uc: W_hat of a pair of columns
-    auto expand = [&](uint4 &a, int b, int uc, int from, int j) {
+    auto expand = [&](auto by_ratios, uint4 &a, int b, int uc, int from, int j) {
         v2h sum;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const uint32_t hw = reinterpret_cast<const uint32_t *>(&hv[from][k])[j];
             const v2h v = __builtin_bit_cast(v2h, hw ^ ((w[b][uc >> 2][k] << (15 - 4 * j - (uc & 3))) & 0x80008000u));
-            sum = k == 0 ? v : __builtin_elementwise_fma(rho[b][k - 1], v, sum);
+            if (k == 0) sum = decltype(by_ratios)::value ? v : coef[b][0] * v;
+            else sum = __builtin_elementwise_fma(coef[b][k], v, sum);
         }
         reinterpret_cast<uint32_t *>(&a)[j] = __builtin_bit_cast(uint32_t, sum);
     };
-    for (int i = 0; i < rounds; ++i) {
-        const int s = s_begin + i;
-        const uint8_t *const slab = slab0 + (i & 1) * SLAB;
-        fetch_h(slab, 0, 0);
-        fetch_x(slab, 0, 0);
-        uint4 a[2];
+    auto contract = [&](auto by_ratios, int from, int to) {
+        for (int i = from; i < to; ++i) {
+            const int s = s_begin + i;
+            const uint8_t *const slab = slab0 + (i & 1) * SLAB;
+            fetch_h(slab, 0, 0);
+            fetch_x(slab, 0, 0);
+            uint4 a[2];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) expand(a[0], 0, 0, 0, j);
+            for (int j = 0; j < 4; ++j) expand(by_ratios, a[0], 0, 0, 0, j);
 #pragma unroll
-        for (int uc = 0; uc < 8; ++uc) {
-            const int at = uc & 1;
-            // the next step's slab is written part by part.  Each part's registers are asked for again at once (a
-            // step later they are needed), or half a step before they are needed
-            if (SHORT) {
-                if (uc == 0) request(s + 1, 0);
-                if (uc == 4) { put((i + 1) & 1, 0); request(s + 1, 1); }
-            } else {
-                if (uc == 1) { put((i + 1) & 1, 0); request(s + 2, 0); }
-                if (uc == 5) { put((i + 1) & 1, 1); request(s + 2, 1); }
-            }
-            if (uc == 3) load_words(s + 1, wn);
-            if (uc < 7) fetch_h(slab, uc + 1, at ^ 1);
-            if (uc < 7 && XB == 2) fetch_x(slab, uc + 1, at ^ 1);
-            if (uc > 0 && XB == 1) fetch_x(slab, uc, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            // between the matrix instructions of one row block: the left operand of the next
+            for (int uc = 0; uc < 8; ++uc) {
+                const int at = uc & 1;
+                // the next step's slab is written part by part.  Each part's registers are asked for again at once (a
+                // step later they are needed), or half a step before they are needed
+                if (SHORT) {
+                    if (uc == 0) request(s + 1, 0);
+                    if (uc == 4) { put((i + 1) & 1, 0); request(s + 1, 1); }
+                } else {
+                    if (uc == 1) { put((i + 1) & 1, 0); request(s + 2, 0); }
+                    if (uc == 5) { put((i + 1) & 1, 1); request(s + 2, 1); }
+                }
+                if (uc == 3) load_words(s + 1, wn);
+                if (uc < 7) fetch_h(slab, uc + 1, at ^ 1);
+                if (uc < 7 && XB == 2) fetch_x(slab, uc + 1, at ^ 1);
+                if (uc > 0 && XB == 1) fetch_x(slab, uc, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                // between the matrix instructions of one row block: the left operand of the next
 #pragma unroll
-            for (int b = 0; b < MB; ++b) {
-                const int next_uc = b + 1 < MB ? uc : uc + 1, next_b = (b + 1) % MB;
+                for (int b = 0; b < MB; ++b) {
+                    const int next_uc = b + 1 < MB ? uc : uc + 1, next_b = (b + 1) % MB;
 #pragma unroll
-                for (int n = 0; n < NT; ++n) {
-                    acc[b][n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a[b & 1]), x[at % XB][n], acc[b][n], 0, 0, 0);
-                    if (next_uc < 8)
+                    for (int n = 0; n < NT; ++n) {
+                        acc[b][n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a[b & 1]), x[at % XB][n], acc[b][n], 0, 0, 0);
+                        if (next_uc < 8)
 #pragma unroll
-                        for (int j = 4 * n / NT; j < 4 * (n + 1) / NT; ++j) expand(a[(b + 1) & 1], next_b, next_uc, next_uc & 1, j);
-                    if (NT > 2) __builtin_amdgcn_sched_barrier(0);
+                            for (int j = 4 * n / NT; j < 4 * (n + 1) / NT; ++j) expand(by_ratios, a[(b + 1) & 1], next_b, next_uc, next_uc & 1, j);
+                        if (NT > 2) __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
             }
+            if (SHORT) put((i + 1) & 1, 1);
+#pragma unroll
+            for (int b = 0; b < MB; ++b)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int k = 0; k < K; ++k) w[b][u][k] = wn[b][u][k];
+            __syncthreads();
         }
-        if (SHORT) put((i + 1) & 1, 1);
-#pragma unroll
-        for (int b = 0; b < MB; ++b)
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int k = 0; k < K; ++k) w[b][u][k] = wn[b][u][k];
-        __syncthreads();
-    }
+    };
+    // (one after the other, so that the second takes over the registers of the first; as the two sides of a branch they were kept
+    // twice and spilled up to 21)
+    const int by_ratios = ratios ? rounds : 0;
+    contract(std::true_type(), 0, by_ratios);
+    contract(std::false_type(), by_ratios, rounds);
 
     // ---- sums of the column groups: the upper half hands its accumulators to the lower half
     float4 *const part = reinterpret_cast<float4 *>(lds);

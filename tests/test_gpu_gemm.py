@@ -310,6 +310,53 @@ def test_gemm_rows_whose_first_path_is_small_or_missing(K, T, case):
         assert torch.all(Y[:, 1290:] == 0)
 
 
+@pytest.mark.parametrize("K,inn,T,case", [(2, 2080, 700, "outlier"), (3, 2080, 700, "outlier"), (2, 11008, 700, "one column"), (2, 1056, 900, "infinite"),
+                                          (2, 544, 1100, "spread"), (3, 544, 900, "spread")])
+def test_gemm_rows_that_the_first_path_does_not_carry(K, inn, T, case):
+    """The second path's input scales are uneven where the first path has no output scale, one 1e-3 or 0.05 of the others', or a usual
+    one, in groups of rows that share workgroups: one scale a thousand times the rest where the activations are a thousandth, or one scale
+    only, which leaves the row a single product; scales spread over e^-3 .. e^3; an infinite scale, whose column alone is not finite.
+    fp32 results, each group of rows by itself: as many roundings to fp16 per weight as paths (2^-12 of it each, and the largest error of a row of
+    several hundred no more than twice the mean) stay below 1e-3."""
+    out = 1300                                                 # (too many tiles of 64 tokens for the few-token kernel)
+    rng = synth.child_rng(5, 127, K, inn, T)
+    signs, g, h = random_layer(rng, K, out, inn)
+    g = (np.sign(g.astype(np.float64)) * (0.2 + np.abs(g.astype(np.float64)) * 20)).astype(np.float16)
+    h = (0.02 + np.abs(h.astype(np.float64))).astype(np.float16)
+    g[:, ::3] *= -1; h[1, ::5] *= -1
+    groups = [slice(0, 100), slice(100, 200), slice(200, 230), slice(230, out)]
+    for rows, f in zip(groups, (0.0, 1e-3, 0.05, 1.0)):
+        g[0, rows] = (g[0, rows].astype(np.float64) * f).astype(np.float16)
+    X = synth.outlier_activations(rng, T, inn)
+    if case == "outlier":
+        h[1, 17] *= np.float16(1000)
+        X[:, 17] *= np.float16(1e-3)
+    elif case == "one column":
+        g[2:] = 0
+        g[0, 230:] = 0
+        h[1, :17] = 0; h[1, 18:] = 0
+    elif case == "spread":
+        g = (g.astype(np.float64) * np.exp(rng.standard_normal(g.shape))).astype(np.float16)
+        h = (h.astype(np.float64) * np.exp(rng.standard_normal(h.shape))).astype(np.float16)
+    else:
+        h[1, 17] = np.inf
+    _say(f"first path carries not every row, {case}, K={K} in={inn} T={T}")
+    Y = rb.rb_linear_gemm(to_device_layer(signs, g, h), torch.from_numpy(X).cuda(), out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    if case == "infinite":
+        assert not torch.any(torch.isfinite(Y[torch.from_numpy(X[:, 17] != 0).cuda()]))
+        return
+    ref = oracle.forward(signs, g, h, X)
+    for rows in groups:
+        if case == "one column" and not np.any(ref[:, rows]):
+            assert torch.all(Y[:, rows] == 0)
+            continue
+        got, want = Y[:, rows].cpu().numpy().astype(np.float64), ref[:, rows]
+        err = np.sqrt(((got - want) ** 2).sum(0) / (want ** 2).sum(0))         # row by row, over the tokens
+        _say(f"  rel_l2={np.sqrt(((got - want) ** 2).sum() / (want ** 2).sum()):.3e} worst row {err.max():.3e}")
+        assert err.max() <= TOL
+
+
 @pytest.mark.parametrize("K,out,inn,T,bf16", [(2, 1290, 800, 700, False), (2, 2600, 96, 1025, True), (3, 1400, 1056, 800, True), (3, 1300, 544, 641, False),
                                               (2, 4100, 2080, 333, False), (2, 5000, 288, 1000, False)])
 def test_many_token_kernel_at_ragged_sizes(K, out, inn, T, bf16):
