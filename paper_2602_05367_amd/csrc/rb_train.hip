@@ -383,7 +383,8 @@ __global__ __launch_bounds__(64, K < 3 ? 4 : 2) void grad_slab_kernel(const floa
     for (int k = 0; k < K; ++k) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            hv[k][e] = __half2float(h[(size_t)k * in + cs + e]);
+            const float f = __half2float(h[(size_t)k * in + cs + e]);
+            hv[k][e] = real ? f : 0.f;                         // (a lane past the end adds nothing, also where f is infinite)
             sh[k][e] = 0.f;
         }
     }

@@ -124,6 +124,25 @@ def test_scale_gradients_of_part_filled_slices(K, out, inn):
     test_scale_gradients_against_the_oracle(K, out, inn, 3)
 
 
+@pytest.mark.parametrize("K,out,inn", [(1, 9, 32), (2, 70, 288), (3, 129, 1056)])
+def test_scale_gradients_with_an_infinite_scale(K, out, inn):
+    """An infinite scale among the first four columns of the first path: its rows' sums are infinite, with the sign of their term, and every
+    other gradient is what it is without it.  Columns past the last one must not bring it in a second time."""
+    rng = synth.child_rng(5, 605, K, out, inn)
+    signs = synth.uniform_signs(rng, K, out, inn)
+    G = rng.standard_normal((out, inn)).astype(np.float32)
+    G[3] = -np.abs(G[3])
+    g, h = synth.halfnormal_scales(rng, K, out), synth.halfnormal_scales(rng, K, inn)
+    dev = [torch.from_numpy(a).cuda() for a in (G, rb.rb_pack(signs).view(np.int32), g, h)]
+    print(f"scale gradients with an infinite scale K={K} {out}x{inn}", flush=True)
+    want_g, want_h = rb.rb_scale_grads(*dev)
+    dev[3][0, 2] = float("inf")
+    got_g, got_h = rb.rb_scale_grads(*dev)
+    torch.cuda.synchronize()
+    assert torch.equal(got_h, want_h) and torch.equal(got_g[1:], want_g[1:])
+    assert np.array_equal(got_g[0].cpu().numpy(), np.inf * signs[0, :, 2] * np.sign(G[:, 2]))
+
+
 def test_training_entry_points_reject_bad_arguments():
     W = torch.zeros((4, 32), dtype=torch.float32, device="cuda")
     g = torch.zeros((2, 4), dtype=torch.float16, device="cuda")
