@@ -177,9 +177,10 @@ __device__ __forceinline__ uint4 pair_order_as_fp16(uint4 v)
 constexpr int ROW_BYTES = UNIT_COLS * 2;             // a token's fp16 values of the columns that a wavefront stages at a time
 template <int K, int G, bool BF16> __host__ __device__ constexpr int slab_bytes() { return (16 * G + K * (BF16 ? 2 : 1)) * ROW_BYTES; }
 
-// K paths, G groups of 16 tokens, P row tiles per workgroup of W wavefronts at most, BF16: the activations are bfloat16
-template <int K, int G, int P, int W, bool BF16>
-__global__ __launch_bounds__(W * 64, two_share(K, G, P) ? 4 : 2) void batch_kernel(const Args args)
+// K paths, G groups of 16 tokens, P row tiles per workgroup of W wavefronts at most, BF16: the activations are bfloat16, WIDE: offsets into
+// the input or into the signs of a row tile may reach NOWHERE (1 GiB): 64-bit addresses, loads in branches, one row tile per workgroup
+template <int K, int G, int P, int W, bool BF16, bool WIDE>
+__global__ __launch_bounds__(W * 64, two_share(K, G, P) && !WIDE ? 4 : 2) void batch_kernel(const Args args)
 {
     // bfloat16: fp16 copies of the units that fp16 holds, the others after them as they are.  Beyond one token group looking at a
     // unit costs what the copies save (4096 x 4096 at 24 tokens: 9.3 us with copies unlooked at, 11.5 with the look, 9.2
@@ -212,6 +213,7 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) ? 4 : 2) void batch_kern
     uint32_t x_off[4 * G];                                     // (rows of no token are not fetched)
 #pragma unroll
     for (int i = 0; i < 4 * G; ++i) x_off[i] = 4 * i + row4 < T ? ((uint32_t)(4 * i + row4) * (uint32_t)in + 8u * (uint32_t)ch) * 2u : NOWHERE;
+    const uint16_t *const x_wide = static_cast<const uint16_t *>(op.x) + (size_t)t0 * in;
     const uint32_t h_row = (uint32_t)row4 * (uint32_t)in;
     uint4 xs[4 * G], hs;
     Words<K> ws[P];
@@ -220,8 +222,14 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) ? 4 : 2) void batch_kern
     auto request = [&](int u) {
         const bool some = real(u);
 #pragma unroll
-        for (int i = 0; i < 4 * G; ++i)
-            if (4 * i < T) xs[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(x_rs, (int)(some ? x_off[i] : NOWHERE), u * ROW_BYTES, 0));
+        for (int i = 0; i < 4 * G; ++i) {
+            if constexpr (WIDE) {
+                xs[i] = make_uint4(0u, 0u, 0u, 0u);
+                if (4 * i + row4 < T && some) xs[i] = *reinterpret_cast<const uint4 *>(x_wide + (size_t)(4 * i + row4) * in + (size_t)u * UNIT_COLS + 8 * ch);
+            } else if (4 * i < T) {
+                xs[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(x_rs, (int)(some ? x_off[i] : NOWHERE), u * ROW_BYTES, 0));
+            }
+        }
         // (the scales need only be 2-byte aligned)
         if (row4 < K) __builtin_memcpy(&hs, op.h + u * UNIT_COLS + (h_row + chunk_scales_at(u, ch, in)), 16);
     };
@@ -229,7 +237,13 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) ? 4 : 2) void batch_kern
     auto request_words = [&](int u) {
 #pragma unroll
         for (int p = 0; p < P; ++p)                            // a row tile past the end of the matrix reads as zero (not stored)
-            ws[p] = load_words<K>(w_rs, (p <= p_last ? 0u : NOWHERE) + (uint32_t)lane * 8u * K, ((min(p, p_last) * CT + (u >> 1)) * tile_words(K) + (u & 1) * K) * 4);
+            if constexpr (WIDE) {
+                const uint32_t *const w = op.bits + ((size_t)(rt0 + min(p, p_last)) * CT + (u >> 1)) * tile_words(K) + lane * 2 * K + (u & 1) * K;
+#pragma unroll
+                for (int k = 0; k < K; ++k) ws[p].w[k] = w[k];
+            } else {
+                ws[p] = load_words<K>(w_rs, (p <= p_last ? 0u : NOWHERE) + (uint32_t)lane * 8u * K, ((min(p, p_last) * CT + (u >> 1)) * tile_words(K) + (u & 1) * K) * 4);
+            }
     };
     auto put_x = [&](auto order) {
 #pragma unroll
@@ -406,7 +420,7 @@ static int row_tiles_per_wg(const int *RT, int nops, int CT, int K, int G, int b
     return best;
 }
 
-template <int K, int G, int P, int W, bool BF16>
+template <int K, int G, int P, int W, bool BF16, bool WIDE = false>
 static int launch_form(const Args &args, int nops, int groups, int nw, hipStream_t stream)
 {
     constexpr int per_wave = std::max(slab_bytes<K, G, BF16>(), P * G * 1024), lds_max = W * per_wave;
@@ -415,13 +429,13 @@ static int launch_form(const Args &args, int nops, int groups, int nw, hipStream
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return RB_ERR_HIP;
         if (!allowed[dev].load()) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(batch_kernel<K, G, P, W, BF16>), hipFuncAttributeMaxDynamicSharedMemorySize,
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(batch_kernel<K, G, P, W, BF16, WIDE>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     lds_max) != hipSuccess)
                 return RB_ERR_HIP;
             allowed[dev].store(true);
         }
     }
-    hipLaunchKernelGGL((batch_kernel<K, G, P, W, BF16>), dim3((unsigned)groups, (unsigned)nops, (unsigned)(G == 4 ? (args.op[0].T + 63) / 64 : 1)), dim3((unsigned)(nw * 64)), nw * per_wave, stream, args);
+    hipLaunchKernelGGL((batch_kernel<K, G, P, W, BF16, WIDE>), dim3((unsigned)groups, (unsigned)nops, (unsigned)(G == 4 ? (args.op[0].T + 63) / 64 : 1)), dim3((unsigned)(nw * 64)), nw * per_wave, stream, args);
     return RB_OK;
 }
 
@@ -434,8 +448,9 @@ static int launch_waves(const Args &args, int nops, int groups, int nw, hipStrea
 }
 
 template <int K, int G, bool BF16>
-static int launch_p(const Args &args, int nops, int P, int groups, int nw, hipStream_t stream)
+static int launch_p(const Args &args, int nops, int P, int groups, int nw, bool wide, hipStream_t stream)
 {
+    if (wide) return launch_form<K, G, 1, G == 1 ? 16 : 8, BF16, true>(args, nops, groups, nw, stream);
     switch (P) {
     case 1: return launch_waves<K, G, 1, BF16>(args, nops, groups, nw, stream);
     case 2: if constexpr (p_available(K, G, 2, BF16)) return launch_waves<K, G, 2, BF16>(args, nops, groups, nw, stream); break;
@@ -448,25 +463,30 @@ static int launch_p(const Args &args, int nops, int P, int groups, int nw, hipSt
 
 static int token_groups(int T) { return T <= 16 ? 1 : T <= 32 ? 2 : 4; }
 
+// The kernel keeps 32-bit offsets into the input of up to 64 tokens and into the signs of a workgroup's row tiles, both below NOWHERE; where
+// they may not fit its WIDE form runs (256 x 2^24 at 3 tokens 7.6 ms, on the generic kernel 40; 64 x 2^24 at 16 13.2 and 39.8)
+static bool offsets_fit(int in, int T) { return in < 1 << 24 && (size_t)std::min(T, 64) * in * 2 < NOWHERE; }
+
 // one launch: the first nops ops of `args`, all of K paths and T tokens; P row tiles per workgroup, `groups` workgroups
 // for the op with the most row tiles
-struct Shape { int K, T, nops, P, groups, nw; };
+struct Shape { int K, T, nops, P, groups, nw; bool wide; };
 static Shape shape_of(Args &args, int nops, int K, bool bf16)
 {
     int RT[MAX_STAGE_OPS], units = 1;
-    Shape s = {K, args.op[0].T, nops, 0, 0, 0};
+    Shape s = {K, args.op[0].T, nops, 0, 0, 0, false};
     for (int i = 0; i < nops; ++i) {
         RT[i] = row_tiles(args.op[i].out);
         units = std::max(units, units_of(args.op[i].in));
+        s.wide = s.wide || !offsets_fit(args.op[i].in, s.T);
     }
     const int G = token_groups(s.T);
-    s.P = row_tiles_per_wg(RT, nops, (units + 1) / 2, K, G, (s.T + 63) / 64, bf16);
+    s.P = s.wide ? 1 : row_tiles_per_wg(RT, nops, (units + 1) / 2, K, G, (s.T + 63) / 64, bf16);
     int all = 0;
     for (int i = 0; i < nops; ++i) {
         s.groups = std::max(s.groups, (RT[i] + s.P - 1) / s.P);
         all += (RT[i] + s.P - 1) / s.P;
     }
-    s.nw = std::min(units, sixteen_available(G, s.P) && all <= mx::device_groups() ? 16 : 8);
+    s.nw = std::min(units, s.wide ? (G == 1 ? 16 : 8) : sixteen_available(G, s.P) && all <= mx::device_groups() ? 16 : 8);
     for (int i = 0; i < nops; ++i) {
         const int n = units_of(args.op[i].in);
         args.op[i].waves = (uint16_t)s.nw;
@@ -480,12 +500,12 @@ template <bool BF16> static int launch_shape(const Args &args, const Shape &s, h
 {
     const int G = token_groups(s.T);
     if (s.K == 2)
-        return G == 1 ? launch_p<2, 1, BF16>(args, s.nops, s.P, s.groups, s.nw, stream)
-             : G == 2 ? launch_p<2, 2, BF16>(args, s.nops, s.P, s.groups, s.nw, stream)
-                      : launch_p<2, 4, BF16>(args, s.nops, s.P, s.groups, s.nw, stream);
-    return G == 1 ? launch_p<3, 1, BF16>(args, s.nops, s.P, s.groups, s.nw, stream)
-         : G == 2 ? launch_p<3, 2, BF16>(args, s.nops, s.P, s.groups, s.nw, stream)
-                  : launch_p<3, 4, BF16>(args, s.nops, s.P, s.groups, s.nw, stream);
+        return G == 1 ? launch_p<2, 1, BF16>(args, s.nops, s.P, s.groups, s.nw, s.wide, stream)
+             : G == 2 ? launch_p<2, 2, BF16>(args, s.nops, s.P, s.groups, s.nw, s.wide, stream)
+                      : launch_p<2, 4, BF16>(args, s.nops, s.P, s.groups, s.nw, s.wide, stream);
+    return G == 1 ? launch_p<3, 1, BF16>(args, s.nops, s.P, s.groups, s.nw, s.wide, stream)
+         : G == 2 ? launch_p<3, 2, BF16>(args, s.nops, s.P, s.groups, s.nw, s.wide, stream)
+                  : launch_p<3, 4, BF16>(args, s.nops, s.P, s.groups, s.nw, s.wide, stream);
 }
 
 static Op make_op(const rb_layer &L, const void *x, void *y, int T, int out_dtype)
@@ -499,13 +519,11 @@ static Op make_op(const rb_layer &L, const void *x, void *y, int T, int out_dtyp
     return o;
 }
 
-// (calls and stacks of at most this size are this file's; the kernel itself keeps 32-bit offsets into the input and into the signs
-// of a workgroup's row tiles, both below NOWHERE, so wider layers than fit run on the generic kernel)
+// (calls and stacks of at most this size are this file's)
 static bool sized(const rb_layer *L, int T, int max_T)
 {
     return (L->K == 2 || L->K == 3) && T >= 1 && T <= max_T && L->in % 32 == 0 && (size_t)T * L->in < (size_t)1 << 32;
 }
-static bool kernel_takes(const rb_layer *L, int T) { return L->in < 1 << 24 && (size_t)T * L->in * 2 < NOWHERE; }
 
 bool call_sized(const rb_layer *L, int T) { return sized(L, T, CALL_MAX_T); }
 
@@ -516,7 +534,7 @@ float blocks_cost(const rb_layer *L, int T, int act_dtype)
 {
     static constexpr float per_tile[2][2][3] = {{{0.46f, 0.69f, 0.8f}, {0.57f, 0.95f, 0.f}}, {{0.5f, 0.85f, 0.f}, {0.67f, 0.f, 0.f}}};
     const bool bf16 = act_dtype == RB_BF16;
-    if (!sized(L, T, INT_MAX) || !kernel_takes(L, std::min(T, 64))) return INFINITY;
+    if (!sized(L, T, INT_MAX) || !offsets_fit(L->in, T)) return INFINITY;
     for (int P = 1; P <= 3 && p_available(L->K, 4, P, bf16); ++P)
         if ((long long)((row_tiles(L->out) + P - 1) / P) * ((T + 63) / 64) <= mx::device_groups()) return 6.5f + per_tile[L->K - 2][bf16][P - 1] * (float)col_tiles(L->in);
     return INFINITY;
@@ -531,7 +549,6 @@ int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype,
         copy_aside(X, workspace, input_bytes(L, T), stream);
         X = workspace;
     }
-    if (!kernel_takes(L, std::min(T, 64))) return launch_signadd(L, X, Y, T, act_dtype, out_dtype, stream);
     Args args = {};
     args.op[0] = make_op(*L, X, Y, T, out_dtype);
     const Shape s = shape_of(args, 1, L->K, act_dtype == RB_BF16);
@@ -551,8 +568,7 @@ size_t plan_workspace_bytes(const rb_layer *layers, int n_layers, int T)
     return need;
 }
 
-// aside: an input to be moved to the workspace first; wide: a layer for the generic kernel, by itself
-struct Launch { Args args; Shape shape; const void *aside; size_t aside_bytes; bool is_wide; rb_layer wide; };
+struct Launch { Args args; Shape shape; const void *aside; size_t aside_bytes; };     // aside: an input to be moved to the workspace first
 struct Prepared { std::vector<Launch> launches; size_t need = 256; };
 static std::mutex g_mutex;
 static std::map<const void *, std::shared_ptr<const Prepared>> g_prepared;
@@ -586,14 +602,14 @@ int prepare_plan(const rb_layer *layers, const rb_stack_op *sops, int n_ops, uin
         const int K = layers[sops[op0].layer].K;
         for (int n = op0; n < n_ops && nops < MAX_STAGE_OPS; ++n) {
             const rb_layer &L = layers[sops[n].layer];
-            bool conflict = L.K != K || (n > op0 && !(kernel_takes(&L, T) && kernel_takes(&layers[sops[op0].layer], T))) || (n > op0 && (meet(src(n), dst(n)) || meet(src(op0), dst(op0))));
+            bool conflict = L.K != K || (n > op0 && (meet(src(n), dst(n)) || meet(src(op0), dst(op0))));
             for (int m = op0; m < n; ++m)
                 if (meet(dst(m), src(n)) || meet(dst(m), dst(n)) || meet(src(m), dst(n))) conflict = true;
             if (conflict) break;
             args.op[nops++] = make_op(L, bufs[sops[n].src], bufs[sops[n].dst], T, RB_F16);
         }
         const Shape shape = shape_of(args, nops, K, false);
-        Launch l = {args, shape, nullptr, 0, !kernel_takes(&layers[sops[op0].layer], T), layers[sops[op0].layer]};
+        Launch l = {args, shape, nullptr, 0};
         if (meet(src(op0), dst(op0))) {
             l.aside = src(op0).at;
             l.aside_bytes = src(op0).bytes;
@@ -620,8 +636,7 @@ int launch_plan(void *workspace, size_t workspace_bytes_, hipStream_t stream)
     if (workspace_bytes_ < pr->need) return RB_ERR_WORKSPACE;
     for (const Launch &l : pr->launches) {
         if (l.aside) copy_aside(l.aside, workspace, l.aside_bytes, stream);
-        const int rc = l.is_wide ? launch_signadd(&l.wide, l.args.op[0].x, l.args.op[0].y, l.shape.T, RB_F16, RB_F16, stream)
-                                 : launch_shape<false>(l.args, l.shape, stream);
+        const int rc = launch_shape<false>(l.args, l.shape, stream);
         if (rc != RB_OK) return rc;
     }
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;

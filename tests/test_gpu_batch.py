@@ -366,6 +366,52 @@ def _device_layer(gen, K, out, inn):
     return rb.Layer(bits, g, h, K, out, inn)
 
 
+def _forward_on_device(L, X):
+    """fp64 on the device, a path at a time (plain torch; the signs unpacked by the host's unpacker)."""
+    signs = rb.rb_unpack(rb.rb_unpack_native(L.bits.cpu().numpy().view(np.uint32), L.K, L.out, L.inn))
+    Y = torch.zeros((X.shape[0], L.out), dtype=torch.float64, device="cuda")
+    for k in range(L.K):
+        Y += ((X.double() * L.h[k].double()) @ torch.from_numpy(signs[k]).cuda().double().t()) * L.g[k].double()
+    return Y
+
+
+@pytest.mark.parametrize("K,out,inn,T,bf16", [(2, 5, 2 ** 24, 3, False), (3, 17, 2 ** 24 + 96, 1, True), (2, 3, 2 ** 23 + 160, 64, False), (2, 2, 2 ** 25, 20, True)])
+def test_few_token_calls_with_offsets_beyond_a_gigabyte(K, out, inn, T, bf16):
+    """2^24 columns, or inputs of a gigabyte and more: the few-token kernel's form with 64-bit addresses.  A sum of 2^24 terms of either sign in
+    fp32, an eighth of them per wavefront and 32 at a time: 2^16 roundings, each up to 2^-24 of the sum so far, add up in
+    quadrature to 2^8 2^-24 = 1.5e-5 of the outputs' norm (of all outputs: a single sum may cancel and its own relative error be any
+    size); the bar is six times that, and the root of the number of roundings more for wider layers and for bf16, which takes two
+    instructions.  A unit of 128 columns read from the wrong place is 2e-3 of it and more."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(out + T)
+    L = _device_layer(gen, K, out, inn)
+    X = torch.randn((T, inn), device="cuda", generator=gen).to(torch.bfloat16 if bf16 else torch.float16)
+    print(f"wide few-token call K={K} {out}x{inn} T={T} bf16={bf16}", flush=True)
+    Y = rb.rb_linear_gemm(L, X, out_dtype=torch.float32)
+    ref = _forward_on_device(L, X)
+    err = float((Y.double() - ref).norm() / ref.norm())
+    print(f"  rel_l2={err:.3e}", flush=True)
+    assert err <= 1e-4 * (inn / 2 ** 24 * (2 if bf16 else 1)) ** 0.5
+
+
+def test_stack_with_a_wide_op():
+    """2^24 columns beside 288 in one launch of a stack, then an op that reads the wide one's output."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(77)
+    T, shapes = 5, ((64, 2 ** 24), (300, 288), (40, 64))
+    layers = [_device_layer(gen, 2, o, i) for o, i in shapes]
+    for L in layers:                                           # outputs near RMS 1
+        L.g.copy_((L.g.float() * (1.0 / (0.0064 * (2 * L.inn) ** 0.5))).half())
+    bufs = [torch.randn((T, w), device="cuda", generator=gen).half() for w in (2 ** 24, 288)] + \
+           [torch.zeros((T, w), dtype=torch.float16, device="cuda") for w in (64, 300, 40)]
+    print("stack with a wide op", flush=True)
+    rb.rb_layer_stack(layers, [(0, 0, 2), (1, 1, 3), (2, 2, 4)], bufs, T)
+    torch.cuda.synchronize()
+    assert rb.rb_last_path() == rb.RB_PATH_BATCH
+    for L, src, dst in zip(layers, (0, 1, 2), (2, 3, 4)):
+        assert max_rel_l2(bufs[dst], _forward_on_device(L, bufs[src]).cpu().numpy()) <= TOL
+
+
 @pytest.mark.parametrize("K,n,T", [(2, 8224, 3), (2, 8224, 16), (2, 12320, 7), (2, 4128, 33), (2, 8224, 64), (3, 8224, 6), (3, 4128, 16), (3, 4128, 64)])
 def test_few_token_output_over_its_input(K, n, T):
     """From three tokens on (six with three paths) the output may overlap the input, with more row tiles than one
