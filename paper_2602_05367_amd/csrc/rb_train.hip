@@ -148,12 +148,16 @@ constexpr int WG_ROWS = 128, WG_COLS = 256, WG_N = 32;      // tile of G, sample
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-// four columns of one sample (zero past the end of the samples or the columns), two bytes at a time
-__device__ __forceinline__ uint2 load_cols(const __half *p, size_t n, size_t N, int c, int width)
+// four columns of one sample (zero past the end of the samples or the columns), two bytes at a time or (EIGHT) all at once
+template <bool EIGHT> __device__ __forceinline__ uint2 load_cols(const __half *p, size_t n, size_t N, int c, int width)
 {
     uint2 v = make_uint2(0u, 0u);
     if (n >= N) return v;
     const unsigned short *row = reinterpret_cast<const unsigned short *>(p) + (size_t)n * width;
+    if (EIGHT) {
+        if (c < width) v = *reinterpret_cast<const uint2 *>(row + c);
+        return v;
+    }
     if (c < width) v.x = row[c];
     if (c + 1 < width) v.x |= (uint32_t)row[c + 1] << 16;
     if (c + 2 < width) v.y = row[c + 2];
@@ -171,13 +175,14 @@ __device__ __forceinline__ uint32_t low_halves(uint32_t a, uint32_t b) { return 
 __device__ __forceinline__ uint32_t high_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 
 // FORM: rows of Delta, X and G that start at multiples of 8 (G: 16) bytes (ALIGNED), of X and G only (DELTA_OFF: Delta's are read
-// as they lie; 4095 x 4096 with 512 samples 35 us, 115 two bytes at a time), neither (ANY: two bytes at a time)
-enum Form { ALIGNED, DELTA_OFF, ANY };
+// as they lie; 4095 x 4096 with 512 samples 35 us, 115 two bytes at a time), neither (ANY: two bytes at a time).  WIDE: ALIGNED, but from WG_MAX_WIDTH columns on, beyond the offsets of a buffer:
+// 8-byte loads in branches, one step in flight (132 x 2^23 with 96 samples 1.7 ms, 4.7 two bytes at a time)
+enum Form { ALIGNED, DELTA_OFF, WIDE, ANY };
 template <Form FORM>
 __global__ __launch_bounds__(256, 2) void weight_grad_kernel(const __half *__restrict__ Delta, const __half *__restrict__ X,
                                                              int N, int out, int in, float *__restrict__ G)
 {
-    constexpr bool VEC = FORM != ANY;
+    constexpr bool VEC = FORM == ALIGNED || FORM == DELTA_OFF;
     constexpr int A_BYTES = WG_ROWS * WG_N * 2, B_BYTES = WG_COLS * WG_N * 2;
     __shared__ __attribute__((aligned(16))) uint8_t lds[2][A_BYTES + B_BYTES];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -215,9 +220,9 @@ __global__ __launch_bounds__(256, 2) void weight_grad_kernel(const __half *__res
             __builtin_amdgcn_sched_barrier(0);
         } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) da[set][j] = load_cols(Delta, n0 + 4 * na + j, N, r0 + 4 * qa, out);
+            for (int j = 0; j < 4; ++j) da[set][j] = load_cols<FORM == WIDE>(Delta, n0 + 4 * na + j, N, r0 + 4 * qa, out);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) xb[set][j] = load_cols(X, n0 + 8 * nb + j, N, c0 + 4 * qb, in);
+            for (int j = 0; j < 8; ++j) xb[set][j] = load_cols<FORM == WIDE>(X, n0 + 8 * nb + j, N, c0 + 4 * qb, in);
         }
     };
     auto put = [&](uint8_t *buf, auto set, [[maybe_unused]] size_t n0) {
@@ -337,7 +342,7 @@ __global__ __launch_bounds__(256, 2) void weight_grad_kernel(const __half *__res
             const int r = r0 + wr * 64 + 4 * (rho & 15) + 2 * m + (rho >> 4);
             if (r >= out) continue;
             float *const dst = G + (size_t)r * in + c;
-            if (VEC) {
+            if (FORM != ANY) {
                 if (c < in) *reinterpret_cast<float4 *>(dst) = make_float4(acc[m][0][e], acc[m][1][e], acc[m][2][e], acc[m][3][e]);
             } else {
 #pragma unroll
@@ -490,13 +495,14 @@ extern "C" int rb_weight_grad(const uint16_t *Delta, const uint16_t *X, int N, i
     if (N < 1 || out < 1 || in < 1 || out > 65535) return RB_ERR_SHAPE;
     const int tiles = (out + WG_ROWS - 1) / WG_ROWS * ((in + WG_COLS - 1) / WG_COLS);
     const dim3 grid((unsigned)((tiles + 7) / 8 * 8));
-    const bool x_aligned = in % 4 == 0 && in < WG_MAX_WIDTH && ((uintptr_t)X & 7) == 0 && ((uintptr_t)G & 15) == 0;
+    const bool x_aligned = in % 4 == 0 && ((uintptr_t)X & 7) == 0 && ((uintptr_t)G & 15) == 0;
     const bool d_aligned = out % 4 == 0 && ((uintptr_t)Delta & 7) == 0;
     const __half *d = reinterpret_cast<const __half *>(Delta), *x = reinterpret_cast<const __half *>(X);
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, d, x, N, out, in, G); };
-    if (x_aligned && d_aligned) run(weight_grad_kernel<ALIGNED>);
-    else if (x_aligned && out >= 4) run(weight_grad_kernel<DELTA_OFF>);
+    const bool fits = in < WG_MAX_WIDTH;
+    if (x_aligned && d_aligned) fits ? run(weight_grad_kernel<ALIGNED>) : run(weight_grad_kernel<WIDE>);
+    else if (x_aligned && out >= 4 && fits) run(weight_grad_kernel<DELTA_OFF>);
     else run(weight_grad_kernel<ANY>);
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;
 }

@@ -119,6 +119,22 @@ def test_weight_gradient_steps_and_unaligned_rows(N, out, inn, shift):
     test_weight_gradient_tiles_and_tails(N, out, inn, shift)
 
 
+@pytest.mark.parametrize("N,out,inn", [(33, 4, 2 ** 23), (1, 5, 2 ** 23 + 4), (65, 12, 2 ** 23 + 260)])
+def test_weight_gradient_of_very_wide_layers(N, out, inn):
+    """From 2^23 columns on 32 rows of X are beyond the offsets of a buffer: loads of eight bytes where rows are aligned, of two
+    where those of Delta are not.  Bound as in test_weight_gradient_tiles_and_tails; the reference is fp64 on the device."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N)
+    X = torch.randn((N, inn), device="cuda", generator=gen).half()
+    D = (torch.randn((N, out), device="cuda", generator=gen) * 0.1).half()
+    print(f"weight gradient {out}x{inn} N={N}", flush=True)
+    G = rb.rb_weight_grad(D, X)
+    for c in range(0, inn, 2 ** 20):
+        x = X[:, c:c + 2 ** 20].double()
+        err = (G[:, c:c + 2 ** 20].double() - D.double().t() @ x).abs()
+        assert torch.all(err <= N * 2.0 ** -23 * (D.double().abs().t() @ x.abs())), c
+
+
 @pytest.mark.parametrize("K,out,inn", [(1, 200, 288), (2, 129, 544), (3, 65, 1056)])
 def test_scale_gradients_of_part_filled_slices(K, out, inn):
     test_scale_gradients_against_the_oracle(K, out, inn, 3)
