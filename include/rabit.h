@@ -160,8 +160,9 @@ size_t rb_noalloc_scratch_bytes(void);
  * in an op's input (an fp16 overflow upstream) makes that op's outputs NaN on
  * the fused kernels, where plain arithmetic could still give an infinity.
  * Every call makes its plan anew, on the fused kernels from host memory that the
- * next call on the workspace replaces: do not record it (nor rb_linear_gemm with two
- * fp16 tokens on a two-path layer) in a graph; prepare before and record rb_stack_run.
+ * next call on the workspace replaces: do not record it in a graph, nor rb_linear_gemm with two
+ * fp16 tokens and fp16 results on a two-path layer, or one of them where the layer has more than
+ * 12288 columns or 128 rows per compute unit; prepare before and record rb_stack_run.
  */
 typedef struct rb_stack_op { int layer; int src; int dst; } rb_stack_op;
 
