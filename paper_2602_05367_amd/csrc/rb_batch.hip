@@ -65,6 +65,7 @@ typedef __bf16 v8b __attribute__((ext_vector_type(8)));
 
 constexpr int STACK_MAX_T = 16;        // tokens of a stack
 constexpr int MAX_STAGE_OPS = 8;       // independent ops that share a launch
+constexpr int LDS_BYTES = 160 * 1024;  // of a compute unit
 
 // The forms of a workgroup.  Row tiles: as many as fit without spilling (accumulators take 4 P K G registers, sign words 2 P K, staged
 // activations 16 G); with four token groups three for two paths and two for three (11008 x 4096 at 64 tokens 18.9 us, 26.5
@@ -175,7 +176,9 @@ __device__ __forceinline__ uint4 pair_order_as_fp16(uint4 v)
 }
 
 constexpr int ROW_BYTES = UNIT_COLS * 2;             // a token's fp16 values of the columns that a wavefront stages at a time
-template <int K, int G, bool BF16> __host__ __device__ constexpr int slab_bytes() { return (16 * G + K * (BF16 ? 2 : 1)) * ROW_BYTES; }
+__host__ __device__ constexpr int slab_bytes(int K, int G, bool bf16) { return (16 * G + K * (bf16 ? 2 : 1)) * ROW_BYTES; }
+// of a wavefront: its slab, then its part of the sums
+__host__ __device__ constexpr int wave_bytes(int K, int G, int P, bool bf16) { return slab_bytes(K, G, bf16) > P * G * 1024 ? slab_bytes(K, G, bf16) : P * G * 1024; }
 
 // K paths, G groups of 16 tokens, P row tiles per workgroup of W wavefronts at most, BF16: the activations are bfloat16, WIDE: offsets into
 // the input or into the signs of a row tile may reach NOWHERE (1 GiB): 64-bit addresses, loads in branches, one row tile per workgroup
@@ -207,7 +210,7 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) && !WIDE ? 4 : 2) void b
     // the address unit would bound the kernel.  Chunk 4 q + s (columns 32 q + 8 s ..) of a row goes to position
     // (4 s + q) ^ (row % 16) of the wavefront's own slab: neither these writes nor the operand reads collide
     const int ch = lane & 15, row4 = lane >> 4, pos = (ch & 3) * 4 + (ch >> 2);
-    uint8_t *const slab = lds + (size_t)wave * slab_bytes<K, G, BF16>();
+    uint8_t *const slab = lds + (size_t)wave * slab_bytes(K, G, BF16);
     const __amdgpu_buffer_rsrc_t x_rs = buffer(static_cast<const uint8_t *>(op.x) + (size_t)t0 * in * 2, (size_t)T * in * 2);
     const __amdgpu_buffer_rsrc_t w_rs = buffer(op.bits + (size_t)rt0 * CT * tile_words(K), (size_t)min(P, RT - rt0) * CT * tile_words(K) * 4);
     uint32_t x_off[4 * G];                                     // (rows of no token are not fetched)
@@ -400,22 +403,41 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) && !WIDE ? 4 : 2) void b
 // ------------------------------------------------------------------ host ---
 constexpr int ROW_TILES_PER_WG[] = {1, 2, 3, 4, 6};
 
-// Row tiles per workgroup: the busiest compute unit gets `each` workgroups, in rounds of the one or two that run at
-// once.  In units of a row tile's work (0.1 us per column tile) a workgroup costs 0.6 more (its activations, the sum) and a round
-// 33 / column tiles (3.3 us: the latencies).  (16 tokens, two paths, us for 1, 2, 3, 4, 6 row tiles: 12288 x 4096 10.9 10.6 9.1 10.1 12.8;
-// 22016 x 4096 18.3 14.5 13.5 16.4 12.9; 28672 x 8192 39.4 32.6 32.7 28.9 41.5)
-static int row_tiles_per_wg(const int *RT, int nops, int CT, int K, int G, int blocks, bool bf16)
+// Row tiles per workgroup and its wavefronts.  Beyond NARROW_UNITS of 128 columns: eight wavefronts, row tiles by what the busiest compute
+// unit takes, `each` workgroups in rounds of the one or two that run at once.  In units of a row tile's work (0.1 us per column tile) a workgroup
+// costs 0.6 more (its activations, the sum) and a round 33 / column tiles (3.3 us: the latencies).  (16 tokens, two paths, us for 1, 2, 3, 4, 6
+// row tiles: 12288 x 4096 10.9 10.6 9.1 10.1 12.8; 22016 x 4096 18.3 14.5 13.5 16.4 12.9; 28672 x 8192 39.4 32.6 32.7 28.9 41.5.)  Sixteen
+// wavefronts see above; two row tiles of up to 16 units are better off with eight (8192 x 2048 at 9 tokens 5.4 us, 5.7).
+// Narrower layers leave room for several small workgroups on a compute unit, whose latencies then overlap, and what a workgroup pays for
+// its sums is shared by fewer wavefronts.  Microseconds of a round of them, for P row tiles and G token groups: 1.5, per unit of a
+// wavefront 0.7 + 0.1 P G, for the sums 0.5 P G / wavefronts.  (us by the rule above and by this one: 28672 x 512 at 33 tokens 16.9 and 10.9;
+// three paths, 28672 x 1024 at 24 21.2 and 16.6, 5000 x 32 at 64 11.3 and 7.2.  Of the forms measured for 32 to 1024 columns at 9, 24 and 48
+// tokens it picks one that is 1 % slower than the best in the mean.)
+constexpr int NARROW_UNITS = 8;
+struct Form { int P, nw; double cost; };
+static Form form_of(const int *RT, int nops, int units, int K, int G, int blocks, bool bf16)
 {
-    const int cus = std::max(1, mx::device_groups());
-    int best = 1;
-    double best_cost = 0.0;
+    const int cus = std::max(1, mx::device_groups()), CT = (units + 1) / 2;
+    auto groups = [&](int P) {
+        int n = 0;
+        for (int i = 0; i < nops; ++i) n += (RT[i] + P - 1) / P;
+        return n * blocks;
+    };
+    Form best = {0, 0, 0.0};
     for (int P : ROW_TILES_PER_WG) {
         if (!p_available(K, G, P, bf16)) continue;
-        int groups = 0;
-        for (int i = 0; i < nops; ++i) groups += (RT[i] + P - 1) / P;
-        const int each = (groups * blocks + cus - 1) / cus, rounds = two_share(K, G, P) ? (each + 1) / 2 : each;
-        const double cost = each * (P + 0.6) + rounds * 33.0 / CT;
-        if (P == 1 || cost < best_cost) { best = P; best_cost = cost; }
+        const int each = (groups(P) + cus - 1) / cus, at_once = two_share(K, G, P) ? 2 : 1;
+        if (units > NARROW_UNITS) {
+            const double cost = each * (P + 0.6) + (each + at_once - 1) / at_once * 33.0 / CT;
+            if (best.P == 0 || cost < best.cost) best = {P, sixteen_available(G, P) && each <= 1 && (P == 1 || units > 16) ? 16 : 8, cost};
+        } else {
+            for (int nw = 1; nw < 2 * units; nw *= 2) {
+                const int waves = std::min(nw, units);
+                const int resident = std::max(1, std::min(8 * at_once / waves, LDS_BYTES / (waves * wave_bytes(K, G, P, bf16) + P * K * TILE_ROWS * 4)));
+                const double cost = (each + resident - 1) / resident * (1.5 + (units + waves - 1) / waves * (0.7 + 0.1 * P * G) + 0.5 * P * G / waves);
+                if (best.P == 0 || cost < best.cost) best = {P, waves, cost};
+            }
+        }
     }
     return best;
 }
@@ -423,7 +445,7 @@ static int row_tiles_per_wg(const int *RT, int nops, int CT, int K, int G, int b
 template <int K, int G, int P, int W, bool BF16, bool WIDE = false>
 static int launch_form(const Args &args, int nops, int groups, int nw, hipStream_t stream)
 {
-    constexpr int per_wave = std::max(slab_bytes<K, G, BF16>(), P * G * 1024), lds_max = W * per_wave;
+    constexpr int per_wave = wave_bytes(K, G, P, BF16), lds_max = W * per_wave;
     if (lds_max + P * K * TILE_ROWS * (int)sizeof(float) > 64 * 1024) {
         static std::atomic<bool> allowed[64];
         int dev = 0;
@@ -480,13 +502,10 @@ static Shape shape_of(Args &args, int nops, int K, bool bf16)
         s.wide = s.wide || !offsets_fit(args.op[i].in, s.T);
     }
     const int G = token_groups(s.T);
-    s.P = s.wide ? 1 : row_tiles_per_wg(RT, nops, (units + 1) / 2, K, G, (s.T + 63) / 64, bf16);
-    int all = 0;
-    for (int i = 0; i < nops; ++i) {
-        s.groups = std::max(s.groups, (RT[i] + s.P - 1) / s.P);
-        all += (RT[i] + s.P - 1) / s.P;
-    }
-    s.nw = std::min(units, s.wide ? (G == 1 ? 16 : 8) : sixteen_available(G, s.P) && all <= mx::device_groups() ? 16 : 8);
+    const Form form = s.wide ? Form{1, G == 1 ? 16 : 8, 0.0} : form_of(RT, nops, units, K, G, (s.T + 63) / 64, bf16);
+    s.P = form.P;
+    s.nw = std::min(units, form.nw);
+    for (int i = 0; i < nops; ++i) s.groups = std::max(s.groups, (RT[i] + s.P - 1) / s.P);
     for (int i = 0; i < nops; ++i) {
         const int n = units_of(args.op[i].in);
         args.op[i].waves = (uint16_t)s.nw;

@@ -55,7 +55,7 @@ RB_HD inline uint32_t to_canonical_word(uint32_t native)
 // workgroup's wavefronts one unit more than the others.  An op narrower than another one of its launch may
 // leave wavefronts without a unit.
 constexpr int UNIT_COLS = 128;
-RB_HD constexpr int units_of(int in) { return (in + UNIT_COLS - 1) / UNIT_COLS; }
+RB_HD constexpr int units_of(int in) { return (int)(((uint32_t)in + UNIT_COLS - 1) / UNIT_COLS); }
 struct UnitRun { int begin, end; };
 RB_HD constexpr UnitRun unit_run(int wave, int run, int rest)
 {

@@ -327,6 +327,20 @@ def test_few_token_forms_and_shared_tiles(K, out, inn, T, bf16):
     test_few_token_calls_element_by_element(K, out, inn, T, bf16)
 
 
+@pytest.mark.parametrize("K,out,inn,T,bf16", [
+    # wide enough (more than 1024 columns) that the number of row tiles decides: 1, 2, 3, 4 and 6 per workgroup, each with one, two and four token
+    # groups where that form exists, both element types, eight and sixteen wavefronts
+    (2, 300, 1056, 9, False), (2, 4112, 1056, 9, True), (2, 4112, 2080, 15, False), (2, 8200, 1056, 9, False), (2, 12304, 1056, 16, True),
+    (2, 16390, 1056, 9, False), (2, 16390, 1056, 3, True), (2, 4112, 1056, 24, False), (2, 8200, 1056, 32, True), (2, 12304, 1056, 24, False),
+    (2, 4112, 1056, 48, True), (2, 8200, 1056, 48, False), (3, 4112, 1056, 9, False), (3, 8200, 1056, 9, True), (3, 12304, 1056, 9, False),
+    (3, 12304, 1056, 2, True), (3, 4112, 1056, 24, True), (3, 8200, 1056, 24, False), (3, 4112, 1056, 48, False), (3, 300, 1056, 48, True),
+    # narrow layers: one to eight wavefronts and several workgroups on a compute unit
+    (2, 28672, 32, 48, False), (2, 28672, 512, 33, True), (2, 22016, 1024, 24, False), (3, 28672, 1024, 48, True), (3, 5000, 640, 64, False),
+    (3, 22016, 512, 9, True), (2, 8200, 896, 17, False)])
+def test_few_token_row_tiles_and_narrow_layers(K, out, inn, T, bf16):
+    test_few_token_calls_element_by_element(K, out, inn, T, bf16)
+
+
 @pytest.mark.parametrize("K", [2, 3])
 @pytest.mark.parametrize("out,inn,T,act,shift", [
     (16, 32, 6, "f16", 0), (130, 160, 13, "bf16", 1), (1000, 2080, 17, "f16", 1), (4099, 288, 33, "bf16", 0), (70, 4128, 64, "f16", 0),
