@@ -548,14 +548,19 @@ bool call_sized(const rb_layer *L, int T) { return sized(L, T, CALL_MAX_T); }
 
 // More than CALL_MAX_T tokens: 64 of them per workgroup, where the workgroups of a call do not outnumber the compute units (in a second
 // round the many-token kernel is always the faster one).  Microseconds, launch included: 6.5 and so much per column tile, measured on
-// layers of 800 to 11008 columns
+// layers of 800 to 11008 columns; or 6.5 and the time in which the workgroups of different rows, on eight dies with caches of their own, fetch
+// the activations, 6.2 TB/s (300 rows at 2000 tokens: 2048 columns 17.4 us, 28672 columns 124; the many-token kernel 15.2 and 111)
 float blocks_cost(const rb_layer *L, int T, int act_dtype)
 {
     static constexpr float per_tile[2][2][3] = {{{0.46f, 0.69f, 0.8f}, {0.57f, 0.95f, 0.f}}, {{0.5f, 0.85f, 0.f}, {0.67f, 0.f, 0.f}}};
     const bool bf16 = act_dtype == RB_BF16;
     if (!sized(L, T, INT_MAX) || !offsets_fit(L->in, T)) return INFINITY;
-    for (int P = 1; P <= 3 && p_available(L->K, 4, P, bf16); ++P)
-        if ((long long)((row_tiles(L->out) + P - 1) / P) * ((T + 63) / 64) <= mx::device_groups()) return 6.5f + per_tile[L->K - 2][bf16][P - 1] * (float)col_tiles(L->in);
+    for (int P = 1; P <= 3 && p_available(L->K, 4, P, bf16); ++P) {
+        const int groups = (row_tiles(L->out) + P - 1) / P;
+        if ((long long)groups * ((T + 63) / 64) > mx::device_groups()) continue;
+        const float fetch = (float)std::min(groups, 8) * (float)input_bytes(L, T) * (1.f / 6.2e6f);
+        return 6.5f + std::max(per_tile[L->K - 2][bf16][P - 1] * (float)col_tiles(L->in), fetch);
+    }
     return INFINITY;
 }
 
