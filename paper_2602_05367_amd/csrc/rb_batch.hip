@@ -73,11 +73,12 @@ constexpr int LDS_BYTES = 160 * 1024;  // of a compute unit
 // 64 registers (28672 x 8192: 192 us, 125 with two).  Wavefronts: eight, of which two workgroups share a compute unit where 128
 // registers are enough, so that one multiplies while the other waits for memory and more workgroups than compute units
 // still run at once (28672 x 8192 at 16 tokens: 448 workgroups of four row tiles 28.9 us, with sixteen wavefronts each, in two
-// rounds, 32.2); sixteen for one or two row tiles in a launch that has no second workgroup for a compute unit (4096 x 11008
-// at 16 tokens 9.9 us, 11.7 with eight; for three and four row tiles it makes no difference).
+// rounds, 32.2); sixteen, where 128 registers are enough for them, in a launch that has no second workgroup for a compute unit, from 5120
+// columns on for two row tiles and more (time of sixteen over that of eight, 1 to 16 tokens: one row tile 4128 columns 0.98, 11008 0.88; two
+// to four 2080 1.06, 4128 1.02, 6144 0.97, 8192 0.95, 11008 0.93).
 __host__ __device__ constexpr bool p_available(int K, int G, int P, bool bf16) { return P == 1 || P * K <= (G == 1 ? 12 : G == 2 ? 8 : bf16 ? 4 : 6); }
 __host__ __device__ constexpr bool two_share(int K, int G, int P) { return G == 1 ? P * K <= 9 : G == 2 && P == 1; }
-__host__ __device__ constexpr bool sixteen_available(int G, int P) { return (G == 1 && P <= 2) || (G == 2 && P == 1); }
+__host__ __device__ constexpr bool sixteen_available(int K, int G, int P) { return (G == 1 && P * K <= 8) || (G == 2 && P == 1); }
 
 // One op of a launch, 64 bytes: everything a workgroup needs comes with one load of scalars
 struct Op {
@@ -407,7 +408,7 @@ constexpr int ROW_TILES_PER_WG[] = {1, 2, 3, 4, 6};
 // unit takes, `each` workgroups in rounds of the one or two that run at once.  In units of a row tile's work (0.1 us per column tile) a workgroup
 // costs 0.6 more (its activations, the sum) and a round 33 / column tiles (3.3 us: the latencies).  (16 tokens, two paths, us for 1, 2, 3, 4, 6
 // row tiles: 12288 x 4096 10.9 10.6 9.1 10.1 12.8; 22016 x 4096 18.3 14.5 13.5 16.4 12.9; 28672 x 8192 39.4 32.6 32.7 28.9 41.5.)  Sixteen
-// wavefronts see above; two row tiles of up to 16 units are better off with eight (8192 x 2048 at 9 tokens 5.4 us, 5.7).
+// wavefronts: see above.
 // Narrower layers leave room for several small workgroups on a compute unit, whose latencies then overlap, and what a workgroup pays for
 // its sums is shared by fewer wavefronts.  Microseconds of a round of them, for P row tiles and G token groups: 1.5, per unit of a
 // wavefront 0.7 + 0.1 P G, for the sums 0.5 P G / wavefronts.  (us by the rule above and by this one: 28672 x 512 at 33 tokens 16.9 and 10.9;
@@ -429,7 +430,7 @@ static Form form_of(const int *RT, int nops, int units, int K, int G, int blocks
         const int each = (groups(P) + cus - 1) / cus, at_once = two_share(K, G, P) ? 2 : 1;
         if (units > NARROW_UNITS) {
             const double cost = each * (P + 0.6) + (each + at_once - 1) / at_once * 33.0 / CT;
-            if (best.P == 0 || cost < best.cost) best = {P, sixteen_available(G, P) && each <= 1 && (P == 1 || units > 16) ? 16 : 8, cost};
+            if (best.P == 0 || cost < best.cost) best = {P, sixteen_available(K, G, P) && each <= 1 && (P == 1 || units >= 40) ? 16 : 8, cost};
         } else {
             for (int nw = 1; nw < 2 * units; nw *= 2) {
                 const int waves = std::min(nw, units);
@@ -464,7 +465,7 @@ static int launch_form(const Args &args, int nops, int groups, int nw, hipStream
 template <int K, int G, int P, bool BF16>
 static int launch_waves(const Args &args, int nops, int groups, int nw, hipStream_t stream)
 {
-    if constexpr (sixteen_available(G, P))
+    if constexpr (sixteen_available(K, G, P))
         if (nw > 8) return launch_form<K, G, P, 16, BF16>(args, nops, groups, nw, stream);
     return launch_form<K, G, P, 8, BF16>(args, nops, groups, nw, stream);
 }

@@ -334,6 +334,8 @@ def test_few_token_forms_and_shared_tiles(K, out, inn, T, bf16):
     (2, 16390, 1056, 9, False), (2, 16390, 1056, 3, True), (2, 4112, 1056, 24, False), (2, 8200, 1056, 32, True), (2, 12304, 1056, 24, False),
     (2, 4112, 1056, 48, True), (2, 8200, 1056, 48, False), (3, 4112, 1056, 9, False), (3, 8200, 1056, 9, True), (3, 12304, 1056, 9, False),
     (3, 12304, 1056, 2, True), (3, 4112, 1056, 24, True), (3, 8200, 1056, 24, False), (3, 4112, 1056, 48, False), (3, 300, 1056, 48, True),
+    # sixteen wavefronts for two, three and four row tiles
+    (2, 4112, 5120, 6, False), (2, 8200, 5152, 16, True), (2, 8200, 5152, 11, False), (2, 12304, 5152, 3, False), (2, 12304, 5152, 9, True), (3, 4112, 5152, 13, False),
     # narrow layers: one to eight wavefronts and several workgroups on a compute unit
     (2, 28672, 32, 48, False), (2, 28672, 512, 33, True), (2, 22016, 1024, 24, False), (3, 28672, 1024, 48, True), (3, 5000, 640, 64, False),
     (3, 22016, 512, 9, True), (2, 8200, 896, 17, False)])
