@@ -34,6 +34,13 @@ def max_rel_l2(y_gpu: torch.Tensor, ref: np.ndarray) -> float:
     return float(oracle.relative_l2(got, ref).max())
 
 
+def only_for_many_tokens(K, out, T, bf16=False):
+    """A call of these sizes takes the many-token kernel: the few-token kernel takes more than 64 tokens only where its workgroups of 64 tokens
+    and up to 3 row tiles (2 for three paths or bf16, 1 for both) do not outnumber the device's compute units (rb_batch.hip, blocks_cost)."""
+    row_tiles = 1 if K == 3 and bf16 else 2 if K == 3 or bf16 else 3
+    return T > 64 and -(-(-(-out // 16)) // row_tiles) * -(-T // 64) > torch.cuda.get_device_properties(0).multi_processor_count
+
+
 def build_stack(which, n_layers, config, T, derived, shrink=None, outliers=False, gain=1.0):
     """Host-side description of a Llama-shaped stack: per op (signs, g, h) and the
     buffer list.  `derived`: paths come from a Gaussian W through the oracle's

@@ -177,13 +177,13 @@ def test_full_width_7b_block_on_the_batch_kernel(T, K):
     print(f"  worst sampled rel_l2={worst:.3e}", flush=True)
 
 
-@pytest.mark.parametrize("n_ops,T", [(8, 16), (4, 9), (8, 5)])
-def test_many_independent_rows_take_larger_row_blocks(n_ops, T):
-    """A launch with rows enough lets a workgroup own 16 (eight ops of 8192 rows) or 8 (four such
-    ops) row tiles instead of 4, so that the staged inputs are shared by more rows: the same
+@pytest.mark.parametrize("n_ops,T,inn", [(8, 16, 288), (4, 9, 288), (8, 5, 288), (8, 16, 1056), (4, 9, 1056), (2, 5, 1056)])
+def test_many_independent_rows_take_larger_row_blocks(n_ops, T, inn):
+    """A launch with rows enough lets a workgroup of a layer of more than 1024 columns own up to six row tiles, so that the staged inputs are
+    shared by more rows; narrow layers keep to one or two.  The same
     results, other instantiations of the kernel.  Every op reads the one stack input."""
     rng = synth.child_rng(3, 506, n_ops, T)
-    out, inn = 8192 - 16 * 5 - 3, 288                 # part-filled last row tile and last row block
+    out = 8192 - 16 * 5 - 3                           # part-filled last row tile and last row block
     layers = []
     for _ in range(n_ops):
         signs, g, h = random_layer(rng, 2, out, inn)
@@ -286,12 +286,12 @@ def test_three_path_decode_kernel_early_reads_and_degenerate_scales():
 
 @pytest.mark.parametrize("K,out,inn,T,bf16", [
     (2, 20, 32, 3, False), (2, 4112, 288, 16, False), (2, 8200, 288, 5, True), (2, 12304, 160, 16, False), (2, 16390, 288, 7, False),
-    (3, 4112, 288, 6, False), (3, 8208, 160, 16, True), (3, 12300, 288, 9, False),       # 1, 2, 3, 4 and 6 row tiles per workgroup
+    (3, 4112, 288, 6, False), (3, 8208, 160, 16, True), (3, 12300, 288, 9, False),       # (several row tiles per workgroup: see below)
     (2, 300, 4384, 17, False), (2, 4112, 288, 32, True), (2, 8200, 96, 31, False), (3, 4100, 288, 18, False),
     (2, 300, 8256, 33, True), (2, 4112, 288, 64, False), (2, 8200, 96, 49, False), (3, 4100, 160, 64, False)])
 def test_few_token_calls_element_by_element(K, out, inn, T, bf16):
-    """Every form of the few-token kernel (token groups of 16, row tiles per workgroup, both element
-    types) against fp64, fp32 results.  Products of a scale and an activation are exact, so only the
+    """The few-token kernel (token groups of 16, both element
+    types; every form of a workgroup in the tests below, which call this one) against fp64, fp32 results.  Products of a scale and an activation are exact, so only the
     additions of the K in terms, the output scale and the path sum round: |error| <= (K in + 8)
     2^-23 sum |g h x| (twice the half-ulp bound; a scale that meets bf16 activations as two terms adds twice as many, which
     half of that bound covers).  One h in eight is an fp16 subnormal, scales have either sign."""
@@ -317,8 +317,8 @@ def test_few_token_calls_element_by_element(K, out, inn, T, bf16):
 
 
 @pytest.mark.parametrize("K,out,inn,T,bf16", [
-    # sign tiles shared by two wavefronts (9, 17 and 33 units of 128 columns for 8 or 16 of them); two workgroups on a compute unit;
-    # three row tiles and four token groups, two of them with three paths; four row tiles and two token groups
+    # sign tiles shared by two wavefronts (9, 17 and 33 units of 128 columns for 8 or 16 of them); several workgroups on a
+    # compute unit, many rows of narrow layers
     (2, 300, 1056, 16, False), (2, 300, 4128, 3, True), (3, 60, 2112, 7, False), (2, 28672, 288, 9, False), (2, 22016, 544, 16, True),
     (3, 13824, 544, 6, False), (2, 11008, 544, 64, False), (3, 8208, 288, 40, False), (2, 16400, 544, 24, False), (3, 300, 2080, 17, True),
     # three paths, one to five tokens
@@ -346,7 +346,7 @@ def test_few_token_row_tiles_and_narrow_layers(K, out, inn, T, bf16):
 @pytest.mark.parametrize("K", [2, 3])
 @pytest.mark.parametrize("out,inn,T,act,shift", [
     (16, 32, 6, "f16", 0), (130, 160, 13, "bf16", 1), (1000, 2080, 17, "f16", 1), (4099, 288, 33, "bf16", 0), (70, 4128, 64, "f16", 0),
-    (9000, 544, 9, "f16", 0)])
+    (9000, 544, 9, "f16", 0), (9000, 1184, 9, "f16", 1)])
 def test_few_token_staging_edges(K, out, inn, T, act, shift):
     """Staged activations of the few-token kernel: token counts that are no multiple of the four a load takes, half
     column tiles, one wavefront per workgroup, two and four token groups, several row tiles per workgroup, scales at an odd
@@ -494,7 +494,8 @@ def test_stack_buffers_that_overlap_in_memory(K, T, prepared):
 
 
 @pytest.mark.parametrize("K,out,inn,T", [(2, 4112, 288, 1), (2, 300, 1056, 2), (2, 4112, 288, 7), (2, 8200, 160, 16), (2, 12304, 160, 5),
-                                         (2, 16390, 96, 9), (2, 300, 544, 18), (2, 4112, 96, 64), (3, 300, 288, 6), (3, 4112, 160, 16),
+                                         (2, 16390, 96, 9), (2, 4112, 1056, 7), (2, 8200, 1056, 16), (2, 12304, 1056, 5), (2, 16390, 1056, 9), (3, 12304, 1056, 6),
+                                         (2, 8200, 5152, 3), (2, 300, 544, 18), (2, 4112, 96, 64), (2, 4112, 1056, 64), (3, 300, 288, 6), (3, 4112, 160, 16),
                                          (3, 300, 96, 33), (2, 20, 135200, 2), (3, 16, 135200, 6)])
 @pytest.mark.parametrize("size", [3.0e5, 1.0e30, 2.0 ** -15, 2.0 ** -20, 2.0 ** -30, 2.0 ** -80, "mixed"])
 def test_few_token_bf16_over_its_whole_range(K, out, inn, T, size):
