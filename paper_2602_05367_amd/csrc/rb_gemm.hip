@@ -103,10 +103,23 @@ __device__ __forceinline__ void largest_and_squares(uint4 v, float &m, float &sq
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float a = __half2float(__ushort_as_half((unsigned short)(w[i] & 0xffffu))), b = __half2float(__ushort_as_half((unsigned short)(w[i] >> 16)));
-        m = fmaxf(m, fmaxf(fabsf(a), fabsf(b)));
-        sq = __builtin_fmaf(a, a, __builtin_fmaf(b, b, sq));
+        const v2h p = __builtin_bit_cast(v2h, w[i]);
+        m = fmaxf(m, fmaxf(fabsf((float)p[0]), fabsf((float)p[1])));
+        sq = __builtin_amdgcn_fdot2(p, p, sq, false);
     }
+}
+// all lanes' values combined, left in every lane (every lane must be active): data-parallel moves inside a row of 16 lanes, register
+// swaps beyond; by lane exchanges through LDS the two reductions took 0.4 us of a call
+template <typename F> __device__ __forceinline__ float over_wave(float v, F op)
+{
+    v = op(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, false)));      // quad_perm [1,0,3,2]
+    v = op(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, false)));      // quad_perm [2,3,0,1]
+    v = op(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, false)));     // row_half_mirror
+    v = op(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xf, 0xf, false)));     // row_mirror
+    const auto rows = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = op(__uint_as_float(rows[0]), __uint_as_float(rows[1]));
+    const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return op(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
 }
 // loads that return zero past the end of their buffer (NOWHERE always is)
 constexpr uint32_t NOWHERE = 0x40000000u;
@@ -230,10 +243,8 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        for (int d = 32; d > 0; d >>= 1) {
-            mx_h[k] = fmaxf(mx_h[k], __shfl_xor(mx_h[k], d));
-            sq_h[k] += __shfl_xor(sq_h[k], d);
-        }
+        mx_h[k] = over_wave(mx_h[k], [](float a, float b) { return fmaxf(a, b); });
+        sq_h[k] = over_wave(sq_h[k], [](float a, float b) { return a + b; });
         if (lane == 0) { red[2 * k][wave] = mx_h[k]; red[2 * k + 1][wave] = sq_h[k]; }
     }
     __syncthreads();
