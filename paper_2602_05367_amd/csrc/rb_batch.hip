@@ -9,8 +9,8 @@
 // v_mfma_f32_16x16x32_bf16 as they are, against two left operands, as an fp16 scale is the exact sum of two bf16
 // values (three vector instructions in place of two and twice the matrix instructions).  Up to 16 tokens only
 // where it must be: 128 columns whose values fp16 holds exactly (zeros, 2^-17 up to 65536, which is nearly all there is) are
-// multiplied as fp16, the others after them (28672 x 8192 at 5 tokens 28 us; in an earlier form of this kernel 34, 47 with two
-// operands throughout, 33 with unchecked fp16 copies).  What bounds it:
+// multiplied as fp16, the others after them (28672 x 8192 at 5 tokens of bfloat16 28 to 33 us from card to card, of fp16 29; in an earlier
+// form of this kernel 34, 47 with two operands throughout, 33 with unchecked fp16 copies).  What bounds it:
 //   * a launch of a 4096-wide op moves 4 MB of signs, half a microsecond of HBM time, so it is a
 //     chain of latencies (launch, one trip to memory, the matrix instructions, the sum over the
 //     wavefronts): the compute units are filled and every wavefront asks for all it needs at once, the
@@ -30,8 +30,8 @@
 // a transformer block) run in one launch; dependent ones are ordered by the stream.
 //
 // Measured (in brackets the form before this one: whole column tiles per wavefront, loads in branches, which made the
-// waits coarse and took up to 60 registers more, one workgroup per compute unit): 7B-shaped dependent chain, 128 launches, 1.19 ms
-// at 5 tokens and 1.32 at 16 (1.26, 1.37); 13B-shaped, three paths, 32 launches, 6 tokens 0.57 ms (0.62).  Of a launch 1.4 us pass
+// waits coarse and took up to 60 registers more, one workgroup per compute unit): 7B-shaped dependent chain, 128 launches, 1.19 to 1.22 ms
+// at 5 tokens and 1.32 to 1.38 at 16 (1.26, 1.37 where the first of these was measured); 13B-shaped, three paths, 32 launches, 6 tokens 0.57 ms (0.62).  Of a launch 1.4 us pass
 // between the last wavefront of one and the first of the next, and 1.2 until the first activations are there.  Single calls
 // in a graph: 28672 x 8192 at 16 tokens 28.5 us (33.5), 10999 x 4128 at 4 9.0 (9.9), 4096 x 4096 at 4 5.2 (5.5), 11008 x 4096 at 48
 // 16.8 (28.9), three paths 13824 x 5120 at 48 34.4 (53.8).
@@ -74,8 +74,8 @@ constexpr int LDS_BYTES = 160 * 1024;  // of a compute unit
 // registers are enough, so that one multiplies while the other waits for memory and more workgroups than compute units
 // still run at once (28672 x 8192 at 16 tokens: 448 workgroups of four row tiles 28.9 us, with sixteen wavefronts each, in two
 // rounds, 32.2); sixteen, where 128 registers are enough for them, in a launch that has no second workgroup for a compute unit, from 5120
-// columns on for two row tiles and more (time of sixteen over that of eight, 1 to 16 tokens: one row tile 4128 columns 0.98, 11008 0.88; two
-// to four 2080 1.06, 4128 1.02, 6144 0.97, 8192 0.95, 11008 0.93).
+// columns on (4096 of bfloat16) for two row tiles and more (time of sixteen over that of eight, 1 to 16 tokens: one row tile 4128 columns
+// 0.98, 11008 0.88; two to four 2080 1.06, 4128 1.02, 0.98 to 1.02 of bfloat16, 6144 0.97, 8192 0.95, 11008 0.93).
 __host__ __device__ constexpr bool p_available(int K, int G, int P, bool bf16) { return P == 1 || P * K <= (G == 1 ? 12 : G == 2 ? 8 : bf16 ? 4 : 6); }
 __host__ __device__ constexpr bool two_share(int K, int G, int P) { return G == 1 ? P * K <= 9 : G == 2 && P == 1; }
 __host__ __device__ constexpr bool sixteen_available(int K, int G, int P) { return (G == 1 && P * K <= 8) || (G == 2 && P == 1); }
@@ -128,8 +128,9 @@ __device__ __forceinline__ void split_scales(uint4 h, uint4 &high, uint4 &low)
     }
 }
 
-// loads that return zero past the end of their buffer (NOWHERE always is): no branch around any of them, so that the
-// waits count exactly what came after
+// loads that return zero past the end of their buffer (NOWHERE always is), so that what is absent of a row, a unit or a row tile needs
+// no branch.  Two kinds of branch are left around loads: a uniform one per four tokens (none of which may be there) and the
+// lanes of the scales; the waits merge there
 constexpr uint32_t NOWHERE = 0x40000000u;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void *p, size_t bytes)
 {
@@ -430,7 +431,7 @@ static Form form_of(const int *RT, int nops, int units, int K, int G, int blocks
         const int each = (groups(P) + cus - 1) / cus, at_once = two_share(K, G, P) ? 2 : 1;
         if (units > NARROW_UNITS) {
             const double cost = each * (P + 0.6) + (each + at_once - 1) / at_once * 33.0 / CT;
-            if (best.P == 0 || cost < best.cost) best = {P, sixteen_available(K, G, P) && each <= 1 && (P == 1 || units >= 40) ? 16 : 8, cost};
+            if (best.P == 0 || cost < best.cost) best = {P, sixteen_available(K, G, P) && each <= 1 && (P == 1 || units >= (bf16 ? 32 : 40)) ? 16 : 8, cost};
         } else {
             for (int nw = 1; nw < 2 * units; nw *= 2) {
                 const int waves = std::min(nw, units);
