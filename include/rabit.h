@@ -305,7 +305,7 @@ int rb_stream_read_groups(void);
  * RB_PATH_NONE, RB_PATH_SIGNADD (generic sign-XOR + add kernel, one launch per
  * op; single calls on a three-path layer with up to 5 tokens report it as well, as they
  * did before the few-token kernel served them), RB_PATH_GEMM (matrix-core GEMM of a single call: the few-token kernel up to
- * 64 tokens, the many-token kernel beyond, one launch per op),
+ * 64 tokens and, on layers of few rows, beyond, the many-token kernel else, one launch per op),
  * RB_PATH_MX (matrix-core decode kernels: one layer and token in one launch,
  * or all ops of a stack in one persistent launch) or RB_PATH_BATCH (few-token
  * kernel of a stack: one pass over the weights for up to 16 tokens, two or

@@ -449,7 +449,7 @@ static int derive(const float *W, const double *row_factors, const double *col_f
             Scalars host;
             for (int it = 1;; ++it) {
                 if (it == 1 && err_before) {
-                    // (`partial` has room: out / 4 sums where the column pass has at least out)
+                    // (`partial` has room: out / 4 sums where the column pass has in >= 32 for every 32 rows, or 64 with the smaller workspace)
                     hipLaunchKernelGGL((rows_kernel<K - 1, FIRST>), by_rows, wg, 0, stream, p, ws.b, ws.a, ws.a_sq, signs, ws.partial, ws.sc);
                     hipLaunchKernelGGL(err_sum_kernel, dim3(1), dim3(1024), 0, stream, ws.partial, n_a, err + (size_t)t * K + i - 1);
                 } else {

@@ -14,9 +14,10 @@ void set_last_path(int path) { g_last_path = path; }
 constexpr int FUSED_MAX_T = 4;         // tokens of the fused decode kernel
 
 // Which stacks take the few-token kernel: every stack with a three-path layer, and two-path stacks
-// of more tokens than the fused decode kernel takes.  (At three or four tokens the fused kernel's one
-// launch is faster, 1.24 against 1.40 ms on the 7B-shaped dependent chain; at five tokens two passes of
-// it would take 1.87 ms where this kernel takes 1.43.)
+// of more tokens than the fused decode kernel takes.  (7B-shaped dependent chain at three and four tokens: one launch of the fused
+// kernel 1.25 ms, 128 of the few-token kernel 1.18 and 1.19; with the forms of the latter from which this line was drawn 1.40.  At
+// five tokens two passes of the fused kernel would take 1.87 ms, the few-token kernel 1.21.  The line stays: results of three and four
+// tokens are the fused kernel's, which serves their decoder blocks too.)
 bool batch_applies(const rb_layer *layers, int n_layers, int T)
 {
     bool any_three = false, all_three = true;

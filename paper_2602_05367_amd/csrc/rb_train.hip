@@ -141,9 +141,10 @@ __global__ __launch_bounds__(256) void couple_kernel(const float *__restrict__ W
 // with the columns of a wavefront de-interleaved (slot 32 i + q holds column 4 q + i), so that
 //   * a write covers consecutive slots (no bank conflicts), and so does an operand read;
 //   * the four column accumulators of a lane are four consecutive columns of G: 16-byte stores.
-// 4096 x 11008: 83 us at 512 samples (0.56 PFLOP/s, 2.2 TB/s of G stored), 223 at 2048, 32 at 33; with one step in flight, its loads in
-// branches and so every wait for all of them, 94, 261 and 33.  The store of a tile and the multiplications of the next do not overlap
-// much (32 us of the 83 are what 33 samples take): all workgroups run in step.
+// 4096 x 11008, calls in a row in a graph: 76 to 83 us from card to card at 512 samples (0.56 to 0.61 PFLOP/s, 2.2 TB/s of G stored), 223 to 229
+// at 2048, 33 at 33; with one step in flight, its loads in branches and so every wait for all of them, 86 to 94, 261 to 269 and 33 to 35.  In
+// a kernel trace 74.  The store of a tile and the multiplications of the next do not overlap
+// much (33 us of the 76 are what 33 samples take): all workgroups run in step.
 constexpr int WG_ROWS = 128, WG_COLS = 256, WG_N = 32;      // tile of G, samples per step
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
