@@ -17,8 +17,9 @@
 //     output scales of the end included;
 //   * the address unit, if activations are fetched in operand order (32 lines a load instruction: 11008
 //     columns for one row tile took 14.6 us, the transposition through LDS below takes 11);
-//   * beyond that, vector instructions: two per two weights and path (a shift and one three-input logic
-//     operation), where the matrix instructions of 16 tokens take a third of their time.
+//   * beyond that, vector instructions: three per four weights and path (a 64-bit shift for two words and a three-input logic
+//     operation for two weights).  A matrix instruction of 512 weights takes 6.7 ns of a SIMD, with the six of its left operand 14.5, of which
+//     16 to 17 are reached here; with a shift for each word, as before, 16.9 (28672 x 8192 at 16 tokens 27.6 us then, 25.8 now).
 //   * the number of load instructions: one that fetches nothing (past the end, or a second unit asked for ahead of
 //     time) takes its turn in the address unit all the same, and asking two units ahead made every launch slower (7B chain
 //     at 16 tokens 1.47 ms).
@@ -76,9 +77,15 @@ constexpr int LDS_BYTES = 160 * 1024;  // of a compute unit
 // rounds, 32.2); sixteen, where 128 registers are enough for them, in a launch that has no second workgroup for a compute unit, from 5120
 // columns on (4096 of bfloat16) for two row tiles and more (time of sixteen over that of eight, 1 to 16 tokens: one row tile 4128 columns
 // 0.98, 11008 0.88; two to four 2080 1.06, 4128 1.02, 0.98 to 1.02 of bfloat16, 6144 0.97, 8192 0.95, 11008 0.93).
-__host__ __device__ constexpr bool p_available(int K, int G, int P, bool bf16) { return P == 1 || P * K <= (G == 1 ? 12 : G == 2 ? 8 : bf16 ? 4 : 6); }
-__host__ __device__ constexpr bool two_share(int K, int G, int P) { return G == 1 ? P * K <= 9 : G == 2 && P == 1; }
+__host__ __device__ constexpr bool p_available(int K, int G, int P, bool bf16)
+{
+    return P == 1 || P * K <= (G == 1 ? 12 : G == 2 ? 8 : bf16 ? 4 : 6);
+}
+__host__ __device__ constexpr bool two_share(int K, int G, int P) { return G == 1 ? P * K <= 8 : G == 2 && P == 1; }
 __host__ __device__ constexpr bool sixteen_available(int K, int G, int P) { return (G == 1 && P * K <= 8) || (G == 2 && P == 1); }
+// Forms in which two left operands at a time, whose words share their shifts, would spill 16 registers (four token groups, where
+// matrix instructions are the larger part): 28672 x 8192 at 64 tokens 82 us, 92 so; three paths 105 and 117
+__host__ __device__ constexpr bool shifts_in_pairs(int K, int G, int P) { return G < 4 || P * K < 6; }
 
 // One op of a launch, 64 bytes: everything a workgroup needs comes with one load of scalars
 struct Op {
@@ -149,6 +156,42 @@ template <int K> __device__ __forceinline__ Words<K> load_words(__amdgpu_buffer_
         r.w[0] = v.x; r.w[1] = v.y; r.w[2] = v.z;
     }
     return r;
+}
+
+// the words of P row tiles two by two, the first of two in the lower half; the last of an odd number with itself, four bits further on
+template <int N> struct Pairs { unsigned long long pair[(N + 1) / 2]; };
+template <int K, int P> __device__ __forceinline__ Pairs<P * K> pairs_of(const Words<K> (&ws)[P])
+{
+    Pairs<P * K> r;
+#pragma unroll
+    for (int n = 0; n < P * K; n += 2) {
+        uint32_t lower, upper;
+        // copies at this place: ones that the compiler puts at the end of the loop would wait for the next words
+        asm volatile("v_mov_b32 %0, %1" : "=&v"(lower) : "v"(ws[n / K].w[n % K]));
+        if (n + 1 < P * K) asm volatile("v_mov_b32 %0, %1" : "=&v"(upper) : "v"(ws[(n + 1) / K].w[(n + 1) % K]));
+        else upper = lower >> 4;
+        r.pair[n / 2] = (unsigned long long)upper << 32 | lower;
+    }
+    return r;
+}
+// both words of a pair moved up by n < 16 bits; what the upper one takes over from the lower one lies in its lowest n bits.  In assembly:
+// the compiler would use one instruction per word, and the 64-bit shift takes as long as one of them (1.8 ns a wavefront)
+__device__ __forceinline__ void shift_left(unsigned long long pair, int n, uint32_t &lower, uint32_t &upper)
+{
+    unsigned long long r;
+    if (__builtin_constant_p(n)) {
+        switch (n) {
+#define RB_SHIFT(N) case N: asm("v_lshlrev_b64 %0, " #N ", %1" : "=v"(r) : "v"(pair)); break;
+            RB_SHIFT(1) RB_SHIFT(2) RB_SHIFT(3) RB_SHIFT(4) RB_SHIFT(5) RB_SHIFT(6) RB_SHIFT(7) RB_SHIFT(8) RB_SHIFT(9) RB_SHIFT(10)
+            RB_SHIFT(11) RB_SHIFT(12) RB_SHIFT(13) RB_SHIFT(14) RB_SHIFT(15)
+#undef RB_SHIFT
+        default: r = pair;
+        }
+    } else {
+        asm("v_lshlrev_b64 %0, %1, %2" : "=v"(r) : "s"(n), "v"(pair));
+    }
+    lower = (uint32_t)r;
+    upper = (uint32_t)(r >> 32);
 }
 
 // bfloat16 values whose fp16 values are the same, in pair order; the others are marked in `range`: below 2^-17 in magnitude
@@ -304,35 +347,55 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) && !WIDE ? 4 : 2) void b
             for (int g = 0; g < G; ++g) acc[p][k][g] = (v4f){0.f, 0.f, 0.f, 0.f};
 
     const int x_addr = r * ROW_BYTES + ((q ^ r) * 16), h_addr = 16 * G * ROW_BYTES + q * 16;
-    // a unit: TERMS left operands per path and row tile
-    auto contract = [&](auto terms, const Words<K> (&w)[P]) {
+    // a unit: TERMS left operands per path and row tile.  Pair (e, e + 4) of the lane's eight columns 8 s .. are the native bits 4 e + s and 16
+    // more: shifted to the tops of the two halves, they go into the pair of scales.  One 64-bit shift does it for two words, or
+    // for two pairs of one word where the number of words is odd.
+    auto contract = [&](auto terms, const Pairs<P * K> &w) {
         constexpr int TERMS = decltype(terms)::value, UNROLL = EITHER && TERMS == 2 ? 1 : 4;
 #pragma unroll UNROLL
         for (int s = 0; s < 4; ++s) {
-            v4u b[G];
             uint4 hv[K][TERMS];
+            v4u b[G];
 #pragma unroll
             for (int k = 0; k < K; ++k)
 #pragma unroll
                 for (int m = 0; m < TERMS; ++m) hv[k][m] = *reinterpret_cast<const uint4 *>(slab + h_addr + (m * K + k) * ROW_BYTES + s * 64);
 #pragma unroll
             for (int g = 0; g < G; ++g) b[g] = *reinterpret_cast<const v4u *>(slab + (x_addr ^ (s * 64)) + g * 16 * ROW_BYTES);
+            auto multiply = [&](int p, int k, const uint32_t (&at_top)[4]) {
 #pragma unroll
-            for (int k = 0; k < K; ++k)
+                for (int m = 0; m < TERMS; ++m) {
+                    v4u a;
 #pragma unroll
-                for (int p = 0; p < P; ++p)
+                    for (int e = 0; e < 4; ++e) a[e] = reinterpret_cast<const uint32_t *>(&hv[k][m])[e] ^ (at_top[e] & 0x80008000u);
 #pragma unroll
-                    for (int m = 0; m < TERMS; ++m) {
-                        // pair (e, e + 4) of the lane's eight columns 8 s ..: native bits 4 e + s and 16 more
-                        v4u a;
+                    for (int g = 0; g < G; ++g)
+                        if constexpr (TERMS == 2) acc[p][k][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b[g]), acc[p][k][g], 0, 0, 0);
+                        else acc[p][k][g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b[g]), acc[p][k][g], 0, 0, 0);
+                }
+            };
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            a[e] = reinterpret_cast<const uint32_t *>(&hv[k][m])[e] ^ ((w[p].w[k] << (15 - 4 * e - s)) & 0x80008000u);
+            for (int n = 0; n < P * K; n += 2) {
+                uint32_t first[4], second[4];
+                if constexpr (shifts_in_pairs(K, G, P)) {
+                    if (n + 1 < P * K) {
 #pragma unroll
-                        for (int g = 0; g < G; ++g)
-                            if constexpr (TERMS == 2) acc[p][k][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b[g]), acc[p][k][g], 0, 0, 0);
-                            else acc[p][k][g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b[g]), acc[p][k][g], 0, 0, 0);
+                        for (int e = 0; e < 4; ++e) shift_left(w.pair[n / 2], 15 - 4 * e - s, first[e], second[e]);
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; e += 2) shift_left(w.pair[n / 2], 15 - 4 * e - s, first[e], first[e + 1]);
                     }
+                    multiply(n / K, n % K, first);
+                    if (n + 1 < P * K) multiply((n + 1) / K, (n + 1) % K, second);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) first[e] = (uint32_t)w.pair[n / 2] << (15 - 4 * e - s);
+                    multiply(n / K, n % K, first);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) second[e] = (uint32_t)(w.pair[n / 2] >> 32) << (15 - 4 * e - s);
+                    if (n + 1 < P * K) multiply((n + 1) / K, (n + 1) % K, second);
+                }
+            }
             if (P * K > 4) __builtin_amdgcn_sched_barrier(0);            // operands of one contraction at a time (registers)
         }
     };
@@ -343,12 +406,7 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) && !WIDE ? 4 : 2) void b
         if (late) left |= 1ull << min(u - u0, 63);
         else if (BF16 && !EITHER) put_wide(u);
         else put(u);
-        Words<K> w[P];
-#pragma unroll
-        for (int p = 0; p < P; ++p)
-            // a copy at this place: one that the compiler puts at the end of the loop would wait for the next words
-#pragma unroll
-            for (int k = 0; k < K; ++k) asm volatile("v_mov_b32 %0, %1" : "=&v"(w[p].w[k]) : "v"(ws[p].w[k]));
+        const Pairs<P * K> w = pairs_of(ws);
         if (u + 1 < u1) {
             request(u + 1);
             request_words(u + 1);
@@ -364,7 +422,7 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) && !WIDE ? 4 : 2) void b
             if (!beyond_fp16()) continue;
             request_words(u);
             put_wide(u);
-            contract(std::integral_constant<int, 2>(), ws);
+            contract(std::integral_constant<int, 2>(), pairs_of(ws));
             __builtin_amdgcn_wave_barrier();
         }
 #pragma unroll
