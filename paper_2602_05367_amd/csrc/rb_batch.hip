@@ -74,12 +74,16 @@ constexpr int LDS_BYTES = 160 * 1024;  // of a compute unit
 // 64 registers (28672 x 8192: 192 us, 125 with two).  Wavefronts: eight, of which two workgroups share a compute unit where 128
 // registers are enough, so that one multiplies while the other waits for memory and more workgroups than compute units
 // still run at once (28672 x 8192 at 16 tokens: 448 workgroups of four row tiles 28.9 us, with sixteen wavefronts each, in two
-// rounds, 32.2); sixteen, where 128 registers are enough for them, in a launch that has no second workgroup for a compute unit, from 5120
+// rounds, 32.2); three paths go up to seven row tiles, so that a launch needs one round more often (28672 x 8192 at 16 tokens 38.5 us with four
+// in two rounds, 33.0 with seven in one; gate and up of 13824 x 5120 at 6 26.5, 22.5; for two paths, of which two workgroups of four run at
+// once, 25.6 and 26.2); sixteen, where 128 registers are enough for them, in a launch that has no second workgroup for a compute unit, from 5120
 // columns on (4096 of bfloat16) for two row tiles and more (time of sixteen over that of eight, 1 to 16 tokens: one row tile 4128 columns
 // 0.98, 11008 0.88; two to four 2080 1.06, 4128 1.02, 0.98 to 1.02 of bfloat16, 6144 0.97, 8192 0.95, 11008 0.93).
 __host__ __device__ constexpr bool p_available(int K, int G, int P, bool bf16)
 {
-    return P == 1 || P * K <= (G == 1 ? 12 : G == 2 ? 8 : bf16 ? 4 : 6);
+    if (P == 1) return true;
+    if (G == 1) return K == 2 ? P <= 4 || P == 6 : P <= 7;
+    return P * K <= (G == 2 ? 8 : bf16 ? 4 : 6);
 }
 __host__ __device__ constexpr bool two_share(int K, int G, int P) { return G == 1 ? P * K <= 8 : G == 2 && P == 1; }
 __host__ __device__ constexpr bool sixteen_available(int K, int G, int P) { return (G == 1 && P * K <= 8) || (G == 2 && P == 1); }
@@ -461,7 +465,7 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) && !WIDE ? 4 : 2) void b
 }
 
 // ------------------------------------------------------------------ host ---
-constexpr int ROW_TILES_PER_WG[] = {1, 2, 3, 4, 6};
+constexpr int ROW_TILES_PER_WG[] = {1, 2, 3, 4, 5, 6, 7};
 
 // Row tiles per workgroup and its wavefronts.  Beyond NARROW_UNITS of 128 columns: eight wavefronts, row tiles by what the busiest compute
 // unit takes, `each` workgroups in rounds of the one or two that run at once.  In units of a row tile's work (0.1 us per column tile) a workgroup
@@ -538,7 +542,9 @@ static int launch_p(const Args &args, int nops, int P, int groups, int nw, bool 
     case 2: if constexpr (p_available(K, G, 2, BF16)) return launch_waves<K, G, 2, BF16>(args, nops, groups, nw, stream); break;
     case 3: if constexpr (p_available(K, G, 3, BF16)) return launch_waves<K, G, 3, BF16>(args, nops, groups, nw, stream); break;
     case 4: if constexpr (p_available(K, G, 4, BF16)) return launch_waves<K, G, 4, BF16>(args, nops, groups, nw, stream); break;
-    default: if constexpr (p_available(K, G, 6, BF16)) return launch_waves<K, G, 6, BF16>(args, nops, groups, nw, stream); break;
+    case 5: if constexpr (p_available(K, G, 5, BF16)) return launch_waves<K, G, 5, BF16>(args, nops, groups, nw, stream); break;
+    case 6: if constexpr (p_available(K, G, 6, BF16)) return launch_waves<K, G, 6, BF16>(args, nops, groups, nw, stream); break;
+    default: if constexpr (p_available(K, G, 7, BF16)) return launch_waves<K, G, 7, BF16>(args, nops, groups, nw, stream); break;
     }
     return RB_ERR_UNSUPPORTED;
 }

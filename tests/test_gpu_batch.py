@@ -328,12 +328,13 @@ def test_few_token_forms_and_shared_tiles(K, out, inn, T, bf16):
 
 
 @pytest.mark.parametrize("K,out,inn,T,bf16", [
-    # wide enough (more than 1024 columns) that the number of row tiles decides: 1, 2, 3, 4 and 6 per workgroup, each with one, two and four token
+    # wide enough (more than 1024 columns) that the number of row tiles decides: 1, 2, 3, 4 and 6 per workgroup (three paths: 5 and 7 too), each with one, two and four token
     # groups where that form exists, both element types, eight and sixteen wavefronts
     (2, 300, 1056, 9, False), (2, 4112, 1056, 9, True), (2, 4112, 2080, 15, False), (2, 8200, 1056, 9, False), (2, 12304, 1056, 16, True),
     (2, 16390, 1056, 9, False), (2, 16390, 1056, 3, True), (2, 4112, 1056, 24, False), (2, 8200, 1056, 32, True), (2, 12304, 1056, 24, False),
     (2, 4112, 1056, 48, True), (2, 8200, 1056, 48, False), (3, 4112, 1056, 9, False), (3, 8200, 1056, 9, True), (3, 12304, 1056, 9, False),
-    (3, 12304, 1056, 2, True), (3, 4112, 1056, 24, True), (3, 8200, 1056, 24, False), (3, 4112, 1056, 48, False), (3, 300, 1056, 48, True),
+    (3, 12304, 1056, 2, True), (3, 16400, 1056, 9, False), (3, 16400, 1056, 16, True), (3, 20500, 1056, 3, False), (3, 20500, 1056, 9, True),
+    (3, 24600, 1056, 16, False), (3, 24600, 1056, 7, True), (3, 4112, 1056, 24, True), (3, 8200, 1056, 24, False), (3, 4112, 1056, 48, False), (3, 300, 1056, 48, True),
     # sixteen wavefronts for two, three and four row tiles
     (2, 4112, 5120, 6, False), (2, 8200, 5152, 16, True), (2, 8200, 5152, 11, False), (2, 12304, 5152, 3, False), (2, 12304, 5152, 9, True), (3, 4112, 5152, 13, False),
     # narrow layers: one to eight wavefronts and several workgroups on a compute unit
