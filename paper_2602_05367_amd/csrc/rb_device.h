@@ -34,6 +34,26 @@ __device__ __forceinline__ void store_out(void *Y, int out_dtype, size_t idx, fl
     }
 }
 
+// both words of a pair moved up by n < 16 bits; what the upper one takes over from the lower one lies in its lowest n bits.  In assembly:
+// the compiler would use one instruction per word, and the 64-bit shift takes as long as one of them (1.8 ns a wavefront)
+__device__ __forceinline__ void shift_left(unsigned long long pair, int n, uint32_t &lower, uint32_t &upper)
+{
+    unsigned long long r;
+    if (__builtin_constant_p(n)) {
+        switch (n) {
+#define RB_SHIFT(N) case N: asm("v_lshlrev_b64 %0, " #N ", %1" : "=v"(r) : "v"(pair)); break;
+            RB_SHIFT(1) RB_SHIFT(2) RB_SHIFT(3) RB_SHIFT(4) RB_SHIFT(5) RB_SHIFT(6) RB_SHIFT(7) RB_SHIFT(8) RB_SHIFT(9) RB_SHIFT(10)
+            RB_SHIFT(11) RB_SHIFT(12) RB_SHIFT(13) RB_SHIFT(14) RB_SHIFT(15)
+#undef RB_SHIFT
+        default: r = pair;
+        }
+    } else {
+        asm("v_lshlrev_b64 %0, %1, %2" : "=v"(r) : "s"(n), "v"(pair));
+    }
+    lower = (uint32_t)r;
+    upper = (uint32_t)(r >> 32);
+}
+
 // OR over each group of eight consecutive lanes, left in all eight: two exchanges inside the quad,
 // then one with the mirrored lane of the group (7 - i, which sits in the other quad).  Data-parallel
 // moves: every lane of the wavefront must be active.

@@ -4,16 +4,17 @@
 // With dozens of tokens per weight and more this is a dense contraction Y = W_hat X with
 // W_hat = sum_k g_k (.) B_k (.) h_k (Alg. 2, "compute layer output") on v_mfma_f32_32x32x16_f16.  The left
 // operand is W_hat itself, built in registers from the packed signs on the way to the matrix
-// instruction and never stored.  Per pair of fp16 elements and path: a shift brings the two sign bits
-// to bits 15 and 31, one three-input logic operation puts them on the pair of h_k.  Two forms add the paths up:
+// instruction and never stored.  Per pair of fp16 elements: a 64-bit shift brings the two sign bits of two paths
+// to bits 15 and 31 of their words (a shift per path before: 4096 x 4096 at 333 tokens 29.7 us, 28.5 now, three paths 28672 x 8192 at 512 288 and
+// 276), one three-input logic operation per path puts them on the pair of h_k.  Two forms add the paths up:
 //   * h_0 B_0 + rho_k h_k B_k with rho_k = g_k / g_0 in fp16 and g_0 on the fp32 sums at the end, a packed fused multiply-add per
-//     path but the first: five vector instructions for two paths, one rounding of the sum and one of rho_k.  Taken by a workgroup in all of
+//     path but the first: four vector instructions for two paths, one rounding of the sum and one of rho_k.  Taken by a workgroup in all of
 //     whose rows path 0 weighs (g_k^2 |h_k|^2) as much as the others together, as it does in a layer whose paths are residuals of one another:
 //     there the rounding of rho_k, relative to the row, is no larger than that of g_0 h_0 B_0 which it replaces;
 //   * G_k h_k B_k summed over all paths, G_k = g_k but for a power of two per row, exact: a multiplication more and a wait state for its
-//     result, seven of eight issue slots per pair against five, and a rounding per path.
-// Measured, first form and second: 4096 x 11008 at 512 tokens 77 and 82 us, 28672 x 8192 at 100 88 and 93, at 2048 954 and 989; three
-// paths, 11008 x 4096 at 2048 237 and 246.  Error against fp64, all rows and the worst of 256: even scales (residual paths) 2.0e-4 and 2.6e-4
+//     result, six issue slots per pair against four, and a rounding per path.
+// Measured, first form and second: 4096 x 11008 at 512 tokens 70 and 76 us, 28672 x 8192 at 100 79 and 82, at 2048 937 and 976; three
+// paths, 11008 x 4096 at 2048 224 and 235.  Error against fp64, all rows and the worst of 256: even scales (residual paths) 2.0e-4 and 2.6e-4
 // (2.7e-4 and 4.6e-4 in the second form), scales spread by e^N(0,1) 2.8e-4 and 3.4e-4 in the second (2.3e-4 and 4.9e-4 in the first; and a
 // per cent where an uneven h_1 stands beside a row without g_0).  Powers of two (s_k that brings max|h_k| into [1/4, 1/2)) keep the
 // terms in fp16's normal range however the layer splits its magnitude.
@@ -35,8 +36,9 @@
 //   * the tile is brought to the output's type in LDS and stored as whole rows;
 //   * the left operand of the next row block is built between the matrix instructions of this one.
 //
-// Measured, fp16, two paths, first form, calls in a row in a graph: 4096 x 4096 at 333 tokens 30-32 us, 11008 x 4096 52-55 us,
-// 4096 x 11008 61-66 us, 8192 x 8192 at 1024 141 us (0.97 PFLOP/s), 28672 x 8192 at 2048 tokens 0.95-0.97 ms.
+// Measured, fp16, two paths, first form, calls in a row in a graph: 4096 x 4096 at 333 tokens 28-30 us, 11008 x 4096 50-53 us,
+// 4096 x 11008 57-59 us, 8192 x 8192 at 1024 138 us (1.0 PFLOP/s), 28672 x 8192 at 2048 tokens 0.91-0.94 ms, where the power that the
+// matrix units may draw is the bound: the same call on activations of zero takes 0.71 ms (torch's product of fp16 matrices 0.82 and 0.66).
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
@@ -206,7 +208,9 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
         }
     };
     // sign words of row block b: lane (r, kg) holds, for row r of the 32, columns 64 kg + 32 u .. of the step
-    uint32_t w[MB][2][K], wn[MB][2][K];
+    // (the words of paths 0 and 1 in one register pair: they share their shifts)
+    struct Words { unsigned long long pair; uint32_t third; };
+    Words w[MB][2], wn[MB][2];
     uint32_t w_off[MB];
     const int rt_safe = min(rt0, RT - 1);
     const uint8_t *const tile_bits = reinterpret_cast<const uint8_t *>(args.bits + (size_t)rt_safe * CT * tile_words(K));
@@ -215,15 +219,20 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
         const uint32_t rt = (uint32_t)(min(rt0 + 2 * b + (r >> 4), RT - 1) - rt_safe);      // row tiles past the end: the last one, not stored
         w_off[b] = (rt * (uint32_t)CT * tile_words(K) + ((uint32_t)(r & 15) + 32u * kg) * (2 * K)) * 4u;
     }
-    auto load_words = [&](int s, uint32_t (&to)[MB][2][K]) {
+    auto load_words = [&](int s, Words (&to)[MB][2]) {
         const int sc = min(s, n128 - 1);
         const uint8_t *const p = tile_bits + (size_t)(sc >> 1) * (tile_words(K) * 4) + (sc & 1) * (4 * K);
 #pragma unroll
         for (int b = 0; b < MB; ++b)
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
+            for (int u = 0; u < 2; ++u) {
+                const uint8_t *const at = p + w_off[b] + u * (16 * 2 * K * 4);
+                uint32_t v[K];
 #pragma unroll
-                for (int k = 0; k < K; ++k) to[b][u][k] = *reinterpret_cast<const uint32_t *>(p + w_off[b] + u * (16 * 2 * K * 4) + k * 4);
+                for (int k = 0; k < K; ++k) v[k] = *reinterpret_cast<const uint32_t *>(at + k * 4);
+                to[b][u].pair = (unsigned long long)v[1] << 32 | v[0];
+                if (K == 3) to[b][u].third = v[K - 1];
+            }
     };
     request(s_begin, 0);
     if (!SHORT) request(s_begin, 1);
@@ -328,10 +337,13 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
     // register j of the left operand of row block b, columns of contraction uc: W_hat of a pair of columns
     auto expand = [&](auto by_ratios, uint4 &a, int b, int uc, int from, int j) {
         v2h sum;
+        uint32_t at_top[3];
+        shift_left(w[b][uc >> 2].pair, 15 - 4 * j - (uc & 3), at_top[0], at_top[1]);
+        if (K == 3) at_top[2] = w[b][uc >> 2].third << (15 - 4 * j - (uc & 3));
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const uint32_t hw = reinterpret_cast<const uint32_t *>(&hv[from][k])[j];
-            const v2h v = __builtin_bit_cast(v2h, hw ^ ((w[b][uc >> 2][k] << (15 - 4 * j - (uc & 3))) & 0x80008000u));
+            const v2h v = __builtin_bit_cast(v2h, hw ^ (at_top[k] & 0x80008000u));
             if (k == 0) sum = decltype(by_ratios)::value ? v : coef[b][0] * v;
             else sum = __builtin_elementwise_fma(coef[b][k], v, sum);
         }
@@ -381,9 +393,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
 #pragma unroll
             for (int b = 0; b < MB; ++b)
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int k = 0; k < K; ++k) w[b][u][k] = wn[b][u][k];
+                for (int u = 0; u < 2; ++u) w[b][u] = wn[b][u];
             __syncthreads();
         }
     };
