@@ -11,8 +11,9 @@
 // ever materialised: a path is its packed signs and two vectors, and every pass recomputes R_i
 // from W (4 bytes per weight) and the other paths (a bit and two cached scale values each), so a
 // pass is bound by the HBM read of W.  The singular triplet comes from a power iteration from the
-// all-ones vector (the matrix is non-negative): two passes per iteration, a = |R| b by rows (four rows
-// per workgroup) and c = |R|^T a by columns (slices of rows, partial sums added in slice order); in both a lane takes
+// all-ones vector (the matrix is non-negative): a = |R| b, c = |R|^T a.  One reading of W serves both where a row fits the registers
+// of a workgroup (one_pass_kernel); else, and in the first iteration of an update, there are two passes, by rows (four rows
+// per workgroup) and by columns (slices of rows, partial sums added in slice order).  In all of them a lane takes
 // four consecutive columns, one 16-byte load of W.  a is left at its length and its norm taken
 // out of c: with b of length 1, sigma = ||c|| and the next b is c / ||c||.  After the last iteration one more pass by rows gives the last |R| b and the
 // signs of R_i.  The error after an update, term by term (as ||R_i||^2 - sigma^2 it would come out of the same pass, but with
@@ -21,13 +22,14 @@
 // iteration's stopping rule is evaluated on the device; the host reads one flag per update when it expects the
 // iteration to have finished, so the call synchronises.
 //
-// Measured, 4096 x 11008, two paths, five sweeps (ten updates of four iterations): 3.9 ms (5.1 with the path left out found at
-// run time, whose branches waited for every sign word by itself, nothing of the next step in flight, and passes of their own for the
-// errors): a row pass 31 us (37 before), a column pass 31 us (47), the sums and the normalisation 13 us.  180 MB of W in
-// 31 us are 5.8 TB/s, what a plain read of as much out of the memory-side cache reaches (6.0).
+// Measured, 4096 x 11008, two paths, five sweeps (ten updates of four iterations): 3.1 to 3.2 ms (3.9 with two passes in every iteration; 5.1
+// before those): both passes in one 37 us, a row pass by itself 31 us, a column pass 31 us, the sums and the normalisation 12 us.  180 MB of W in
+// 31 us are 5.8 TB/s, what a plain read of as much out of the memory-side cache reaches (6.0); of the 37 us some 4 are the
+// columns' values at the start and 3 the 22 MB of sums at the end.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 
 #include "rabit.h"
 #include "rb_device.h"
@@ -41,6 +43,7 @@ constexpr int MAX_SLICES = 65535;
 constexpr int ROWS = 4;                // rows one workgroup of the row pass takes
 constexpr int FIRST_LOOK = 4;          // power iterations before the first look at the flag
 constexpr int MAX_ITER = 200;
+constexpr int ONE_PASS_MIN_ROWS = 1024, ONE_PASS_MIN_COLS = 2048;
 constexpr double TOL_SIGMA = 1e-13, TOL_B = 1e-10;
 
 // W and the J paths that a pass subtracts
@@ -60,10 +63,31 @@ struct Scalars {
     int iters;
 };
 
+// sum over the wavefront, in every lane (every lane must be active): data-parallel moves inside a row of 16 lanes, register swaps
+// beyond
+__device__ __forceinline__ double over_wave(double v)
+{
+    auto both = [](double v, auto move) {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+        return __builtin_bit_cast(double, (unsigned long long)move((uint32_t)(u >> 32)) << 32 | move((uint32_t)u));
+    };
+    v += both(v, [](uint32_t w) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xf, 0xf, false); });      // quad_perm [1,0,3,2]
+    v += both(v, [](uint32_t w) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x4E, 0xf, 0xf, false); });      // quad_perm [2,3,0,1]
+    v += both(v, [](uint32_t w) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x141, 0xf, 0xf, false); });     // row_half_mirror
+    v += both(v, [](uint32_t w) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x140, 0xf, 0xf, false); });     // row_mirror
+    auto swap_add = [](double v, auto swap) {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+        const auto low = swap((uint32_t)u), high = swap((uint32_t)(u >> 32));
+        return __builtin_bit_cast(double, (unsigned long long)high[0] << 32 | low[0]) + __builtin_bit_cast(double, (unsigned long long)high[1] << 32 | low[1]);
+    };
+    v = swap_add(v, [](uint32_t w) { return __builtin_amdgcn_permlane16_swap(w, w, false, false); });
+    return swap_add(v, [](uint32_t w) { return __builtin_amdgcn_permlane32_swap(w, w, false, false); });
+}
+
 // sum over a workgroup of `waves` wavefronts in a fixed order, in every thread; red has a slot per wavefront
 __device__ __forceinline__ double group_sum(double v, double *red, int waves)
 {
-    for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m);
+    v = over_wave(v);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     double s = 0.0;
@@ -271,6 +295,142 @@ __global__ __launch_bounds__(256, 4) void cols_kernel(Problem<J> p, const double
     *reinterpret_cast<double2 *>(dst + 2) = make_double2(s[2], s[3]);
 }
 
+// Both passes of an iteration in one reading of W: a workgroup per compute unit takes a run of whole rows, one after the other, and
+// keeps what it shares of the columns (the paths' h, the sums) in registers, four columns in each of CG groups of 2048 per
+// thread, and b in LDS.  A row's R stays in registers from its dot product with b to its part of the column sums; the next row is
+// on its way meanwhile (with two to four of them it was no faster).  The factor f of a column is taken out of it, R = f (rows W - g B h / f), and goes with b and with the column
+// sums (a column without a factor has no h).  partial[workgroup][c] = sum over its rows of |R[r][c]| a[r], a_sq[workgroup]
+// the sum of a[r]^2.
+// Bound: the reading of W; a row of 11008 columns costs a SIMD about 0.7 us of double precision and 0.3 us for the sum over the
+// workgroup, and has 1.9 us in which 256 compute units read a row each.
+constexpr int ONE_PASS_GROUPS = 256, ONE_PASS_THREADS = 512, GROUP_COLS = 4 * ONE_PASS_THREADS;
+template <int N> struct RowPiece {
+    float4 w;
+    uint32_t bits[N + 1];
+};
+template <int J, int CG>
+__global__ __launch_bounds__(ONE_PASS_THREADS, 2) void one_pass_kernel(Problem<J> p, const double *b, double *partial, double *a_sq, const Scalars *sc)
+{
+    constexpr int WAVES = ONE_PASS_THREADS / 64;
+    extern __shared__ __attribute__((aligned(16))) double2 b_lds[];      // [CG][2][thread]: f b of two columns, zero past the last column
+    __shared__ double red[2][WAVES];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, in = p.in, W32 = in / 32;
+    const int r0 = (int)((long long)p.out * blockIdx.x / gridDim.x), r1 = (int)((long long)p.out * (blockIdx.x + 1) / gridDim.x);
+    struct Row { RowPiece<J> piece[CG]; double factor, g[J + 1]; } row;
+    const int done = sc->done;                                 // (looked at when the first loads are on their way)
+    // (buffer loads: columns past the last one read as zero, and one register holds the thread's place in every group)
+    auto fetch_row = [&](int r) {
+        const __amdgpu_buffer_rsrc_t w_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.W + (size_t)r * in), 0, in * 4, 0x00020000);
+#pragma unroll
+        for (int k = 0; k < CG; ++k) row.piece[k].w = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(w_rs, tid * 16, k * GROUP_COLS * 4, 0));
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const __amdgpu_buffer_rsrc_t b_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.packed[j] + (size_t)r * W32), 0, W32 * 4, 0x00020000);
+#pragma unroll
+            for (int k = 0; k < CG; ++k) row.piece[k].bits[j] = __builtin_amdgcn_raw_buffer_load_b32(b_rs, tid / 8 * 4, k * (GROUP_COLS / 32) * 4, 0);
+            row.g[j] = p.g[j][r];
+        }
+        row.factor = p.rows ? p.rows[r] : 1.0;
+    };
+    fetch_row(min(r0, p.out - 1));
+    double h[CG][J + 1][4], sum[CG][4], squares = 0.0;
+#pragma unroll
+    for (int k = 0; k < CG; ++k) {
+        const int c = k * GROUP_COLS + 4 * tid, cs = c < in ? c : 0;     // in % 32 == 0: all four columns exist or none
+        double v[4];
+        Columns<J> cols;
+        fetch_columns<J, J>(p, cs, cols);
+        four(b, cs, v);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[e] = c < in ? v[e] * fabs(cols.f[e]) : 0.0;
+#pragma unroll
+            for (int j = 0; j < J; ++j) h[k][j][e] = cols.f[e] != 0.0 ? cols.h[j][e] / cols.f[e] : 0.0;
+            sum[k][e] = 0.0;
+        }
+        b_lds[2 * k * ONE_PASS_THREADS + tid] = make_double2(v[0], v[1]);
+        b_lds[(2 * k + 1) * ONE_PASS_THREADS + tid] = make_double2(v[2], v[3]);
+    }
+    // (a thread reads what it has written of b)
+    if (done) return;
+#pragma unroll 1
+    for (int r = r0; r < r1; ++r) {
+        double v[CG][4];
+#pragma unroll
+        for (int k = 0; k < CG; ++k) {
+            const float w[4] = {row.piece[k].w.x, row.piece[k].w.y, row.piece[k].w.z, row.piece[k].w.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[k][e] = row.factor * (double)w[e];
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const uint32_t bits = row.piece[k].bits[j] >> (4 * (tid & 7));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const unsigned long long flip = (unsigned long long)(bits << (31 - e) & 0x80000000u) << 32;
+                    v[k][e] -= __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, row.g[j]) ^ flip) * h[k][j][e];
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_row(min(r + 1, r1 - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        double dot[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < CG; ++k) {
+            const double2 low = b_lds[2 * k * ONE_PASS_THREADS + tid], high = b_lds[(2 * k + 1) * ONE_PASS_THREADS + tid];
+            dot[0] += fabs(v[k][0]) * low.x;
+            dot[1] += fabs(v[k][1]) * low.y;
+            dot[2] += fabs(v[k][2]) * high.x;
+            dot[3] += fabs(v[k][3]) * high.y;
+        }
+        const double d = over_wave((dot[0] + dot[1]) + (dot[2] + dot[3]));
+        if (lane == 0) red[r & 1][wave] = d;
+        __syncthreads();                                       // (the other half of `red` is written before anyone is a row further on)
+        double a = 0.0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) a += red[r & 1][w];
+        squares += a * a;
+#pragma unroll
+        for (int k = 0; k < CG; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[k][e] += fabs(v[k][e]) * a;
+    }
+#pragma unroll
+    for (int k = 0; k < CG; ++k) {
+        const int c = k * GROUP_COLS + 4 * tid;
+        if (c >= in) continue;
+        double f[4] = {1.0, 1.0, 1.0, 1.0};
+        if (p.cols) four(p.cols, c, f);
+        double *const to = partial + (size_t)blockIdx.x * in + c;
+        *reinterpret_cast<double2 *>(to) = make_double2(sum[k][0] * fabs(f[0]), sum[k][1] * fabs(f[1]));
+        *reinterpret_cast<double2 *>(to + 2) = make_double2(sum[k][2] * fabs(f[2]), sum[k][3] * fabs(f[3]));
+    }
+    if (tid == 0) a_sq[blockIdx.x] = squares;
+}
+// groups of columns of the one-pass form, 0 where it is not taken.  Wider rows do not fit the registers; below 1024 rows (four per workgroup) the sums
+// of 256 workgroups are as much to move as what a second pass reads, and rows of less than 2048 columns leave threads idle (time
+// of the call over that with two passes: 4096 x 11008 0.81, 5504 x 8192 0.75, 11008 x 4096 0.77, three paths 4096 x 11008, where 14 registers spill,
+// 0.90, 1024 x 11008 0.96 to 0.99, 1400 x 2048 0.87; 11008 x 1024 1.12)
+static int one_pass_groups(int out, int in)
+{
+    const int groups = (in + GROUP_COLS - 1) / GROUP_COLS;
+    if (out < ONE_PASS_MIN_ROWS || in < ONE_PASS_MIN_COLS || groups > 6) return 0;
+    return (groups + 1) / 2 * 2;
+}
+template <int J, int CG> static int launch_one_pass(const Problem<J> &p, const double *b, double *partial, double *a_sq, const Scalars *sc, hipStream_t stream)
+{
+    constexpr int lds = CG * GROUP_COLS * (int)sizeof(double);
+    static std::atomic<bool> allowed[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return RB_ERR_HIP;
+    if (lds > 48 * 1024 && !allowed[dev].load()) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(one_pass_kernel<J, CG>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return RB_ERR_HIP;
+        allowed[dev].store(true);
+    }
+    hipLaunchKernelGGL((one_pass_kernel<J, CG>), dim3(ONE_PASS_GROUPS), dim3(ONE_PASS_THREADS), lds, stream, p, b, partial, a_sq, sc);
+    return RB_OK;
+}
+
 // sum[c] = the slices of partial[.][c], in eight runs of consecutive ones, over the norm of a (every workgroup adds
 // that up: squares of sums left at their length would leave fp64's range with W'^4), and the squares by workgroup
 constexpr int SUMS_COLS = 64, SUMS_RUNS = 8;
@@ -297,11 +457,22 @@ __global__ __launch_bounds__(SUMS_COLS * SUMS_RUNS) void slices_kernel(const dou
     if (x == 0) sum_sq[blockIdx.x] = sq;
 }
 
+constexpr int UNIT_HELD = 12;           // columns of a thread that the next kernel asks for at its start
 // b_new = sum / its norm, the change of b, the stopping rule  (one workgroup)
 __global__ __launch_bounds__(1024) void unit_kernel(double *b, const double *sum, const double *sum_sq, int in, Scalars *sc)
 {
     if (sc->done) return;
     __shared__ double red[16];
+    // (the first UNIT_HELD x 1024 columns are asked for before the norm is known: one trip to memory instead of two, 7.5 -> 6.6 us)
+    double held_sum[UNIT_HELD], held_b[UNIT_HELD];
+#pragma unroll
+    for (int i = 0; i < UNIT_HELD; ++i) {
+        held_sum[i] = held_b[i] = 0.0;
+        if (1024 * i >= in) continue;
+        const int c = min((int)threadIdx.x + 1024 * i, in - 1);
+        held_sum[i] = sum[c];
+        held_b[i] = b[c];
+    }
     double sigma = 0.0;
     for (int i = threadIdx.x; i < (in + SUMS_COLS - 1) / SUMS_COLS; i += 1024) sigma += sum_sq[i];
     sigma = sqrt(group_sum(sigma, red, 16));
@@ -310,12 +481,15 @@ __global__ __launch_bounds__(1024) void unit_kernel(double *b, const double *sum
         return;
     }
     double db = 0.0;
-#pragma unroll 4
-    for (int c = threadIdx.x; c < in; c += 1024) {
-        const double bn = sum[c] / sigma, d = bn - b[c];
+    auto update = [&](int c, double s, double old) {
+        const double bn = s / sigma, d = bn - old;
         db += d * d;
         b[c] = bn;
-    }
+    };
+#pragma unroll
+    for (int i = 0; i < UNIT_HELD; ++i)
+        if ((int)threadIdx.x + 1024 * i < in) update(threadIdx.x + 1024 * i, held_sum[i], held_b[i]);
+    for (int c = threadIdx.x + 1024 * UNIT_HELD; c < in; c += 1024) update(c, sum[c], b[c]);
     db = sqrt(group_sum(db, red, 16));
     if (threadIdx.x == 0) {
         const bool done = fabs(sigma - sc->sigma) <= TOL_SIGMA * sigma && db <= TOL_B;
@@ -402,11 +576,11 @@ __global__ __launch_bounds__(256) void unscale_kernel(double *g, double *h, cons
 struct Layout {
     size_t scalars, a, a_sq, b, sum, sum_sq, partial, total;
 };
-// the slices come last; `rows` of them each
-static Layout make_layout(int out, int in, int rows)
+// the slices come last; `rows` of them each, or the workgroups of the one-pass form
+static Layout make_layout(int out, int in, int rows, bool one_pass)
 {
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
-    const size_t slices = (size_t)(out + rows - 1) / rows, groups = (size_t)(out + ROWS - 1) / ROWS;
+    const size_t slices = std::max<size_t>((size_t)(out + rows - 1) / rows, one_pass ? ONE_PASS_GROUPS : 0), groups = (size_t)(out + ROWS - 1) / ROWS;
     Layout L;
     size_t o = 0;
     L.scalars = o; o += up(sizeof(Scalars));
@@ -427,8 +601,9 @@ struct Buffers {
 
 template <int K>
 static int derive(const float *W, const double *row_factors, const double *col_factors, int out, int in, int T_max, double *g, double *h,
-                  uint32_t *packed, double *err, const Buffers &ws, int slice_rows, hipStream_t stream)
+                  uint32_t *packed, double *err, const Buffers &ws, int slice_rows, bool room, hipStream_t stream)
 {
+    const int one_pass = room ? one_pass_groups(out, in) : 0;
     const int n_slices = (out + slice_rows - 1) / slice_rows, n_a = (out + ROWS - 1) / ROWS;
     const size_t words = (size_t)out * (in / 32);
     const dim3 by_rows((unsigned)n_a), by_cols((in + 1023) / 1024, n_slices), wg(256);
@@ -453,10 +628,19 @@ static int derive(const float *W, const double *row_factors, const double *col_f
                     hipLaunchKernelGGL((rows_kernel<K - 1, FIRST>), by_rows, wg, 0, stream, p, ws.b, ws.a, ws.a_sq, signs, ws.partial, ws.sc);
                     hipLaunchKernelGGL(err_sum_kernel, dim3(1), dim3(1024), 0, stream, ws.partial, n_a, err + (size_t)t * K + i - 1);
                 } else {
-                    hipLaunchKernelGGL((rows_kernel<K - 1, ITERATE>), by_rows, wg, 0, stream, p, ws.b, ws.a, ws.a_sq, signs, ws.partial, ws.sc);
+                    if (!one_pass) hipLaunchKernelGGL((rows_kernel<K - 1, ITERATE>), by_rows, wg, 0, stream, p, ws.b, ws.a, ws.a_sq, signs, ws.partial, ws.sc);
                 }
-                hipLaunchKernelGGL((cols_kernel<K - 1>), by_cols, wg, 0, stream, p, ws.a, ws.partial, slice_rows, ws.sc);
-                hipLaunchKernelGGL(slices_kernel, dim3((in + SUMS_COLS - 1) / SUMS_COLS), dim3(SUMS_COLS * SUMS_RUNS), 0, stream, ws.partial, n_slices, ws.a_sq, n_a, in, ws.sum, ws.sum_sq, ws.sc);
+                const bool one = one_pass && !(it == 1 && err_before);
+                if (one) {
+                    int rc = RB_OK;
+                    if (one_pass == 2) rc = launch_one_pass<K - 1, 2>(p, ws.b, ws.partial, ws.a_sq, ws.sc, stream);
+                    else if (one_pass == 4) rc = launch_one_pass<K - 1, 4>(p, ws.b, ws.partial, ws.a_sq, ws.sc, stream);
+                    else rc = launch_one_pass<K - 1, 6>(p, ws.b, ws.partial, ws.a_sq, ws.sc, stream);
+                    if (rc != RB_OK) return rc;
+                } else {
+                    hipLaunchKernelGGL((cols_kernel<K - 1>), by_cols, wg, 0, stream, p, ws.a, ws.partial, slice_rows, ws.sc);
+                }
+                hipLaunchKernelGGL(slices_kernel, dim3((in + SUMS_COLS - 1) / SUMS_COLS), dim3(SUMS_COLS * SUMS_RUNS), 0, stream, ws.partial, one ? ONE_PASS_GROUPS : n_slices, ws.a_sq, one ? ONE_PASS_GROUPS : n_a, in, ws.sum, ws.sum_sq, ws.sc);
                 hipLaunchKernelGGL(unit_kernel, dim3(1), dim3(1024), 0, stream, ws.b, ws.sum, ws.sum_sq, in, ws.sc);
                 if (it < look) continue;
                 // |R| b and the signs for the converged b, the path's new scales: nothing happens unless the iteration has finished
@@ -490,7 +674,7 @@ static int derive(const float *W, const double *row_factors, const double *col_f
 extern "C" size_t rb_derive_workspace_bytes(int out, int in)
 {
     if (out < 1 || in < 32 || in % 32 != 0) return 0;
-    return rb::derive::make_layout(out, in, rb::derive::ROW_SLICE).total;
+    return rb::derive::make_layout(out, in, rb::derive::ROW_SLICE, rb::derive::one_pass_groups(out, in) != 0).total;
 }
 
 extern "C" int rb_derive_iterative(const float *W, const double *row_factors, const double *col_factors, int K, int T_max,
@@ -505,9 +689,11 @@ extern "C" int rb_derive_iterative(const float *W, const double *row_factors, co
     if (((uintptr_t)W | (uintptr_t)h | (uintptr_t)col_factors) & 15) return RB_ERR_ALIGN;      // read 16 bytes at a time
     // a smaller workspace (slices of twice the rows) does as well; more slices than the second dimension of a grid
     // may have: the same
-    const bool short_slices = workspace_bytes >= make_layout(out, in, ROW_SLICE).total && out <= MAX_SLICES * ROW_SLICE;
+    const bool short_slices = workspace_bytes >= make_layout(out, in, ROW_SLICE, false).total && out <= MAX_SLICES * ROW_SLICE;
     const int slice_rows = short_slices ? ROW_SLICE : 2 * ROW_SLICE;
-    const Layout lay = make_layout(out, in, slice_rows);
+    // (with less room than is asked for now: two passes)
+    const bool room = one_pass_groups(out, in) && workspace_bytes >= make_layout(out, in, slice_rows, true).total;
+    const Layout lay = make_layout(out, in, slice_rows, room);
     if (!workspace || workspace_bytes < lay.total) return RB_ERR_WORKSPACE;
     if ((uintptr_t)workspace & 15) return RB_ERR_ALIGN;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
@@ -523,7 +709,7 @@ extern "C" int rb_derive_iterative(const float *W, const double *row_factors, co
                        (size_t)K * out, packed, nw);
     hipLaunchKernelGGL(clear_kernel, dim3((unsigned)(((size_t)K * in + 255) / 256)), dim3(256), 0, stream, h, (size_t)K * in,
                        static_cast<uint32_t *>(nullptr), (size_t)0);
-    auto run = [&](auto derive_k) { return derive_k(W, row_factors, col_factors, out, in, T_max, g, h, packed, err, buf, slice_rows, stream); };
+    auto run = [&](auto derive_k) { return derive_k(W, row_factors, col_factors, out, in, T_max, g, h, packed, err, buf, slice_rows, room, stream); };
     const int rc = K == 1 ? run(derive<1>) : K == 2 ? run(derive<2>) : run(derive<3>);
     if (rc != RB_OK) return rc;
     if (row_factors || col_factors)

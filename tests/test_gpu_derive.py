@@ -160,6 +160,43 @@ def test_slices_of_the_column_pass_and_their_workspace(K, out, inn, slices_of):
     np.testing.assert_allclose(ed.cpu().numpy(), err, rtol=1e-9)
 
 
+@pytest.mark.parametrize("K,out,inn,calibrated", [
+    # one reading of W per iteration: from 1024 rows and 2048 columns to 12288 columns, 2, 4 and 6 groups of 2048; rows that 256 workgroups do
+    # not share evenly, groups that end inside a workgroup
+    (1, 1024, 2048, True), (2, 1030, 4096, False), (2, 1025, 4128, True), (3, 1024, 6176, True), (2, 1100, 8224, True), (1, 1027, 12288, False), (3, 1024, 8288, False)])
+def test_both_passes_in_one_reading(K, out, inn, calibrated):
+    """Same bars as above; and the workspace that two passes per iteration need is still enough, with the same signs and, but for
+    the order of the sums, the same scales."""
+    rng = synth.child_rng(7, 709, K, out)
+    W = synth.gaussian_weight(rng, out, inn, std=0.02).astype(np.float32)
+    W[0, :3] = 0.0
+    print(f"derive K={K} {out}x{inn} calibrated={calibrated}", flush=True)
+    s_in, s_out, rows, cols = _factors(rng, out, inn, 0.5, 0.25)
+    if not calibrated:
+        rows = cols = None
+    signs, g, h, err = oracle.derive_iterative(W, K, 2, **(dict(s_in=s_in, s_out=s_out, alpha_in=0.5, alpha_out=0.25) if calibrated else {}))
+    packed, g_d, h_d, err_d = _run(W, K, 2, rows, cols)
+    assert np.array_equal(packed, oracle.pack(signs))
+    np.testing.assert_allclose(g_d, g, rtol=1e-8, atol=1e-14)
+    np.testing.assert_allclose(h_d, h, rtol=1e-8, atol=1e-14)
+    np.testing.assert_allclose(err_d, err, rtol=1e-9)
+    need = rb.lib.rb_derive_workspace_bytes(out, inn) - (256 - -(-out // 32)) * inn * 8
+    Wd = torch.from_numpy(W).cuda()
+    rd, cd = (None if a is None else torch.from_numpy(a).cuda() for a in (rows, cols))
+    pd = torch.empty((K, out, inn // 32), dtype=torch.int32, device="cuda")
+    gd, hd = (torch.empty((K, n), dtype=torch.float64, device="cuda") for n in (out, inn))
+    ed = torch.empty((2, K), dtype=torch.float64, device="cuda")
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    at = lambda t: None if t is None else t.data_ptr()
+    rc = rb.lib.rb_derive_iterative(Wd.data_ptr(), at(rd), at(cd), K, 2, out, inn, pd.data_ptr(), gd.data_ptr(), hd.data_ptr(), ed.data_ptr(),
+                                    ws.data_ptr(), need, None)
+    torch.cuda.synchronize()
+    assert rc == rb.RB_OK and np.array_equal(pd.cpu().numpy().view(np.uint32), packed)
+    np.testing.assert_allclose(gd.cpu().numpy(), g_d, rtol=1e-9, atol=1e-14)
+    np.testing.assert_allclose(hd.cpu().numpy(), h_d, rtol=1e-9, atol=1e-14)
+    np.testing.assert_allclose(ed.cpu().numpy(), err_d, rtol=1e-12)
+
+
 @pytest.mark.parametrize("K,out,inn,noise", [(1, 300, 1056, 0.14), (1, 1024, 2048, 0.14), (2, 300, 544, 0.3), (3, 70, 4128, 1.0)])
 def test_error_of_the_last_update_term_by_term(K, out, inn, noise):
     """The last entry of err against the residual of the returned paths, term by term in extended precision, where
