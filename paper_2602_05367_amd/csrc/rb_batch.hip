@@ -31,8 +31,8 @@
 // a transformer block) run in one launch; dependent ones are ordered by the stream.
 //
 // Measured (in brackets the form before this one: whole column tiles per wavefront, loads in branches, which made the
-// waits coarse and took up to 60 registers more, one workgroup per compute unit): 7B-shaped dependent chain, 128 launches, 1.19 to 1.22 ms
-// at 5 tokens and 1.32 to 1.38 at 16 (1.26, 1.37 where the first of these was measured); 13B-shaped, three paths, 32 launches, 6 tokens 0.57 ms (0.62).  Of a launch 1.4 us pass
+// waits coarse and took up to 60 registers more, one workgroup per compute unit): 7B-shaped dependent chain, 128 launches, 1.26 to 1.28 ms
+// at 16 tokens (1.37); 13B-shaped, three paths, 32 launches, 6 tokens 0.49 to 0.52 ms (0.62).  Of a launch 1.4 us pass
 // between the last wavefront of one and the first of the next, and 1.2 until the first activations are there.  Single calls
 // in a graph: 28672 x 8192 at 16 tokens 28.5 us (33.5), 10999 x 4128 at 4 9.0 (9.9), 4096 x 4096 at 4 5.2 (5.5), 11008 x 4096 at 48
 // 16.8 (28.9), three paths 13824 x 5120 at 48 34.4 (53.8).
@@ -91,21 +91,28 @@ __host__ __device__ constexpr bool sixteen_available(int K, int G, int P) { retu
 // matrix instructions are the larger part): 28672 x 8192 at 64 tokens 82 us, 92 so; three paths 105 and 117
 __host__ __device__ constexpr bool shifts_in_pairs(int K, int G, int P) { return G < 4 || P * K < 6; }
 
-// One op of a launch, 64 bytes: everything a workgroup needs comes with one load of scalars
-struct Op {
+// One op of a launch: 14 words, which is what a workgroup can be given in registers at its start
+struct alignas(64) Op {
     const uint32_t *bits;     // native sign tiles
-    const uint16_t *g;        // fp16 [K][out]
-    const uint16_t *h;        // fp16 [K][in]
     const void *x;            // [T][in]
+    const uint16_t *h;        // fp16 [K][in]
+    const uint16_t *g;        // fp16 [K][out]
     void *y;                  // [T][out]
     int out, in;
-    int T, out_dtype;
-    uint16_t waves, rest;     // wavefronts of a workgroup; each takes `run` units, the first `rest` one more
-    int run;
+    uint32_t tokens;          // T, element type of y << 16
+    uint32_t cut;             // wavefronts of a workgroup, `rest` << 5, `run` << 9: each takes `run` units, the first `rest` one more
+    __host__ __device__ int T() const { return (int)(tokens & 0xffffu); }
+    __host__ __device__ int out_dtype() const { return (int)(tokens >> 16); }
+    __host__ __device__ int waves() const { return (int)(cut & 31u); }
+    __host__ __device__ int rest() const { return (int)(cut >> 5 & 15u); }
+    __host__ __device__ int run() const { return (int)(cut >> 9); }
 };
-// everything a launch needs, passed by value: no table in memory to fetch before the work starts.  The op
-// of a workgroup is its blockIdx.y
-struct Args { Op op[MAX_STAGE_OPS]; };
+// Everything a launch needs is passed by value: no table in memory to fetch before the work starts.  The op of a workgroup is its
+// blockIdx.y.  The first comes as single arguments, which the compiler has put into registers (build.py asks for it; 7B-shaped chain at 16
+// tokens, 128 launches, 1301 us with all in memory, 1273 so; 10999 x 4128 at 7 8.83 and 8.68).  The others are in memory, 64 bytes each, fetched in
+// one trip.
+struct Others { Op op[MAX_STAGE_OPS - 1]; };
+struct Args { Op first; Others others; Op &op(int i) { return i == 0 ? first : others.op[i - 1]; } };
 
 // ------------------------------------------------------------------- kernel ---
 // eight values in memory order as the pairs (e, e + 4), e = 0..3: the order in which one shift of a
@@ -212,7 +219,8 @@ __host__ __device__ constexpr int wave_bytes(int K, int G, int P, bool bf16) { r
 // K paths, G groups of 16 tokens, P row tiles per workgroup of W wavefronts at most, BF16: the activations are bfloat16, WIDE: offsets into
 // the input or into the signs of a row tile may reach NOWHERE (1 GiB): 64-bit addresses, loads in branches, one row tile per workgroup
 template <int K, int G, int P, int W, bool BF16, bool WIDE>
-__global__ __launch_bounds__(W * 64, two_share(K, G, P) && !WIDE ? 4 : 2) void batch_kernel(const Args args)
+__global__ __launch_bounds__(W * 64, two_share(K, G, P) && !WIDE ? 4 : 2) void batch_kernel(const uint32_t *bits, const void *x, const uint16_t *h, const uint16_t *g, void *y,
+                                                                                        int out, int in, uint32_t tokens, uint32_t cut, const Others others)
 {
     // bfloat16: fp16 copies of the units that fp16 holds, the others after them as they are.  Beyond one token group looking at a
     // unit costs what the copies save (4096 x 4096 at 24 tokens: 9.3 us with copies unlooked at, 11.5 with the look, 9.2
@@ -220,19 +228,24 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) && !WIDE ? 4 : 2) void b
     constexpr bool EITHER = BF16 && G == 1;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];    // a slab per wavefront; then [wavefront][row tile][token][row] sums
     __shared__ __attribute__((aligned(16))) float g_lds[P * K * TILE_ROWS];      // [path][row tile][row]
-    const Op op = args.op[blockIdx.y];
-    // (all of it at once: left to itself the compiler fetches it in four trips, each where it is used first)
-    asm volatile("" :: "s"(op.bits), "s"(op.g), "s"(op.h), "s"(op.x), "s"(op.y), "s"(op.out), "s"(op.in), "s"(op.T), "s"(op.out_dtype), "s"((int)op.waves), "s"(op.run));
-    const int tid = threadIdx.x, lane = tid & 63, nw = op.waves, threads = nw * 64;
+    Op op = {bits, x, h, g, y, out, in, tokens, cut};
+    if (blockIdx.y != 0) {
+        op = others.op[blockIdx.y - 1];
+        // (all of it at once: left to itself the compiler fetches it in four trips, each where it is used first)
+        asm volatile("" :: "s"(op.bits), "s"(op.g), "s"(op.h), "s"(op.x), "s"(op.y), "s"(op.out), "s"(op.in), "s"(op.tokens), "s"(op.cut));
+    }
+    out = op.out;
+    in = op.in;
+    const int tid = threadIdx.x, lane = tid & 63, nw = op.waves(), threads = nw * 64;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, q = lane >> 4;
     // (calls of more than 64 tokens: blockIdx.z takes 64 of them)
     const int t0 = G == 4 ? (int)blockIdx.z * 64 : 0;
-    const int out = op.out, in = op.in, T = G == 4 ? min(op.T - t0, 64) : op.T;
+    const int T = G == 4 ? min(op.T() - t0, 64) : op.T();
     const int RT = row_tiles(out), CT = col_tiles(in), rt0 = (int)blockIdx.x * P;
     if (rt0 >= RT) return;                                     // (an op with fewer row tiles than another one of the launch)
 
-    const UnitRun units = unit_run(wave, op.run, op.rest);
+    const UnitRun units = unit_run(wave, op.run(), op.rest());
     const int u0 = units.begin, u1 = units.end;
     // ---- staging.  A load instruction fetches 256 contiguous bytes of four tokens (a token per 16 lanes: 16
     // chunks of eight columns), so it touches eight lines; fetched in operand order it would touch 32 and
@@ -440,7 +453,7 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) && !WIDE ? 4 : 2) void b
         const int p = idx / (G * 256), t = idx / 16 % (G * 16), row = (rt0 + p) * TILE_ROWS + idx % 16;
         float s = 0.f;
         for (int v = 0; v < nw; ++v) s += part[v * (P * G * 256) + idx];
-        if (t < T && row < out) store_out(op.y, op.out_dtype, (size_t)(t0 + t) * out + row, s);
+        if (t < T && row < out) store_out(op.y, op.out_dtype(), (size_t)(t0 + t) * out + row, s);
     }
 }
 
@@ -501,7 +514,8 @@ static int launch_form(const Args &args, int nops, int groups, int nw, hipStream
             allowed[dev].store(true);
         }
     }
-    hipLaunchKernelGGL((batch_kernel<K, G, P, W, BF16, WIDE>), dim3((unsigned)groups, (unsigned)nops, (unsigned)(G == 4 ? (args.op[0].T + 63) / 64 : 1)), dim3((unsigned)(nw * 64)), nw * per_wave, stream, args);
+    hipLaunchKernelGGL((batch_kernel<K, G, P, W, BF16, WIDE>), dim3((unsigned)groups, (unsigned)nops, (unsigned)(G == 4 ? (args.first.T() + 63) / 64 : 1)), dim3((unsigned)(nw * 64)), nw * per_wave, stream,
+                       args.first.bits, args.first.x, args.first.h, args.first.g, args.first.y, args.first.out, args.first.in, args.first.tokens, args.first.cut, args.others);
     return RB_OK;
 }
 
@@ -541,11 +555,11 @@ struct Shape { int K, T, nops, P, groups, nw; bool wide; };
 static Shape shape_of(Args &args, int nops, int K, bool bf16)
 {
     int RT[MAX_STAGE_OPS], units = 1;
-    Shape s = {K, args.op[0].T, nops, 0, 0, 0, false};
+    Shape s = {K, args.first.T(), nops, 0, 0, 0, false};
     for (int i = 0; i < nops; ++i) {
-        RT[i] = row_tiles(args.op[i].out);
-        units = std::max(units, units_of(args.op[i].in));
-        s.wide = s.wide || !offsets_fit(args.op[i].in, s.T);
+        RT[i] = row_tiles(args.op(i).out);
+        units = std::max(units, units_of(args.op(i).in));
+        s.wide = s.wide || !offsets_fit(args.op(i).in, s.T);
     }
     const int G = token_groups(s.T);
     const Form form = s.wide ? Form{1, G == 1 ? 16 : 8, 0.0} : form_of(RT, nops, units, K, G, (s.T + 63) / 64, bf16);
@@ -553,10 +567,8 @@ static Shape shape_of(Args &args, int nops, int K, bool bf16)
     s.nw = std::min(units, form.nw);
     for (int i = 0; i < nops; ++i) s.groups = std::max(s.groups, (RT[i] + s.P - 1) / s.P);
     for (int i = 0; i < nops; ++i) {
-        const int n = units_of(args.op[i].in);
-        args.op[i].waves = (uint16_t)s.nw;
-        args.op[i].run = n / s.nw;
-        args.op[i].rest = (uint16_t)(n % s.nw);
+        const int n = units_of(args.op(i).in);
+        args.op(i).cut = (uint32_t)(n / s.nw) << 9 | (uint32_t)(n % s.nw) << 5 | (uint32_t)s.nw;
     }
     return s;
 }
@@ -580,7 +592,7 @@ static Op make_op(const rb_layer &L, const void *x, void *y, int T, int out_dtyp
     o.g = L.g; o.h = L.h;
     o.x = x; o.y = y;
     o.out = L.out; o.in = L.in;
-    o.T = T; o.out_dtype = out_dtype;
+    o.tokens = (uint32_t)T | (uint32_t)out_dtype << 16;
     return o;
 }
 
@@ -620,7 +632,7 @@ int launch_call(const rb_layer *L, const void *X, void *Y, int T, int act_dtype,
         X = workspace;
     }
     Args args = {};
-    args.op[0] = make_op(*L, X, Y, T, out_dtype);
+    args.first = make_op(*L, X, Y, T, out_dtype);
     const Shape s = shape_of(args, 1, L->K, act_dtype == RB_BF16);
     const int rc = act_dtype == RB_BF16 ? launch_shape<true>(args, s, stream) : launch_shape<false>(args, s, stream);
     if (rc != RB_OK) return rc;
@@ -676,14 +688,14 @@ int prepare_plan(const rb_layer *layers, const rb_stack_op *sops, int n_ops, uin
             for (int m = op0; m < n; ++m)
                 if (meet(dst(m), src(n)) || meet(dst(m), dst(n)) || meet(src(m), dst(n))) conflict = true;
             if (conflict) break;
-            args.op[nops++] = make_op(L, bufs[sops[n].src], bufs[sops[n].dst], T, RB_F16);
+            args.op(nops++) = make_op(L, bufs[sops[n].src], bufs[sops[n].dst], T, RB_F16);
         }
         const Shape shape = shape_of(args, nops, K, false);
         Launch l = {args, shape, nullptr, 0};
         if (meet(src(op0), dst(op0))) {
             l.aside = src(op0).at;
             l.aside_bytes = src(op0).bytes;
-            l.args.op[0].x = workspace;
+            l.args.first.x = workspace;
         }
         pr->launches.push_back(l);
         op0 += nops;

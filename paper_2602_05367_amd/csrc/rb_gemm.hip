@@ -135,9 +135,11 @@ __device__ __forceinline__ uint4 buffer_load(__amdgpu_buffer_rsrc_t rs, uint32_t
 }
 
 // K paths, NT groups of 32 tokens, WR wavefronts along the rows (the other WAVES / WR share out the columns);
-// BF16: X is bfloat16.  h starts at a multiple of 16 bytes (its rows then do too)
+// BF16: X is bfloat16.  h starts at a multiple of 16 bytes (its rows then do too).  14 words of single arguments, which the compiler has put
+// into registers at the start (build.py asks for it; two 7B-shaped blocks at 333 tokens 567 us with the arguments in memory, 560 so)
 template <int K, int NT, int WR, bool BF16>
-__global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
+__global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const uint32_t *bits, const __half *h, const void *X, const __half *g, void *Y, int out, int in,
+                                                              int T, int out_dtype)
 {
     constexpr int WK = WAVES / WR, GT = 64 * WR;               // column groups; threads of one
     constexpr int TOK = 32 * NT, XL = TOK * 16 / GT, XP = XL / 2;     // tokens of a tile; 16-byte loads of X per thread and step, in two parts
@@ -153,7 +155,6 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = wave / WR, wr = wave % WR;
     const int r = lane & 31, kg = lane >> 5;
-    const int out = args.out, in = args.in, T = args.T;
     const int RT = row_tiles(out), CT = col_tiles(in);
     const int TB = (T + TOK - 1) / TOK, RB = (RT + 2 * MB * WR - 1) / (2 * MB * WR);
     // workgroups go round the eight XCDs: each takes a run of tiles, token blocks fastest, so its L2 sees
@@ -170,12 +171,12 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
     // Everything a step advances is uniform over the wavefront; a lane keeps 32-bit offsets
     const int gid = tid - grp * GT, ch = gid & 15, row0 = gid >> 4;
     uint8_t *const slab0 = lds + (size_t)grp * 2 * SLAB;
-    const uint8_t *const Xt = static_cast<const uint8_t *>(args.X) + (size_t)t0 * in * 2;
+    const uint8_t *const Xt = static_cast<const uint8_t *>(X) + (size_t)t0 * in * 2;
     uint32_t x_off[XL];
 #pragma unroll
     for (int i = 0; i < XL; ++i) x_off[i] = (uint32_t)min(row0 + i * (GT / 16), T - 1 - t0) * (uint32_t)in * 2u + (uint32_t)ch * 16u;
     const uint32_t h_off = row0 < K ? ((uint32_t)row0 * (uint32_t)in + (uint32_t)ch * 8u) * 2u : NOWHERE;
-    const __amdgpu_buffer_rsrc_t x_rs = buffer(Xt, (size_t)min(TOK, T - t0) * in * 2), h_rs = buffer(args.h, (size_t)K * in * 2);
+    const __amdgpu_buffer_rsrc_t x_rs = buffer(Xt, (size_t)min(TOK, T - t0) * in * 2), h_rs = buffer(h, (size_t)K * in * 2);
     constexpr bool SHORT = NT == 4;                            // registers for half of a slab only
     uint4 xs[SHORT ? XP : XL], hs;
     auto reg = [&](int i) { return SHORT ? i % XP : i; };
@@ -213,7 +214,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
     Words w[MB][2], wn[MB][2];
     uint32_t w_off[MB];
     const int rt_safe = min(rt0, RT - 1);
-    const uint8_t *const tile_bits = reinterpret_cast<const uint8_t *>(args.bits + (size_t)rt_safe * CT * tile_words(K));
+    const uint8_t *const tile_bits = reinterpret_cast<const uint8_t *>(bits + (size_t)rt_safe * CT * tile_words(K));
 #pragma unroll
     for (int b = 0; b < MB; ++b) {
         const uint32_t rt = (uint32_t)(min(rt0 + 2 * b + (r >> 4), RT - 1) - rt_safe);      // row tiles past the end: the last one, not stored
@@ -241,7 +242,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
 #pragma unroll
     for (int b = 0; b < MB; ++b)
 #pragma unroll
-        for (int k = 0; k < K; ++k) gv[b][k] = __half2float(args.g[(size_t)k * out + min(rt0 * TILE_ROWS + 32 * b + r, out - 1)]);
+        for (int k = 0; k < K; ++k) gv[b][k] = __half2float(g[(size_t)k * out + min(rt0 * TILE_ROWS + 32 * b + r, out - 1)]);
 
     // ---- powers of two that bring the scales h of a path to [1/4, 1/2), and the sum of their squares
     float mx_h[K], sq_h[K];
@@ -432,7 +433,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
     // ---- the tile in the output's type through LDS, so that whole rows of it are stored.  Register 4 e + i
     // of lane (r, kg): token r, row 8 e + 4 kg + i of the 32
     constexpr int RW = 32 * MB * WR;                           // rows of the workgroup
-    const int size = args.out_dtype == RB_F32 ? 4 : 2, pitch = RW * size + 16;
+    const int size = out_dtype == RB_F32 ? 4 : 2, pitch = RW * size + 16;
     if (grp == 0) {
 #pragma unroll
         for (int b = 0; b < MB; ++b)
@@ -443,12 +444,12 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
                 for (int n = 0; n < NT; ++n) {
                     uint8_t *const dst = lds + (32 * n + r) * pitch + (32 * (MB * wr + b) + 8 * e + 4 * kg) * size;
                     const float v[4] = {acc[b][n][4 * e] * base.x, acc[b][n][4 * e + 1] * base.y, acc[b][n][4 * e + 2] * base.z, acc[b][n][4 * e + 3] * base.w};
-                    if (args.out_dtype == RB_F32) {
+                    if (out_dtype == RB_F32) {
                         *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
                     } else {
                         uint32_t o[4];
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) o[i] = args.out_dtype == RB_F16 ? __half_as_ushort(__float2half_rn(v[i])) : f32_to_bf16_rne(v[i]);
+                        for (int i = 0; i < 4; ++i) o[i] = out_dtype == RB_F16 ? __half_as_ushort(__float2half_rn(v[i])) : f32_to_bf16_rne(v[i]);
                         *reinterpret_cast<uint2 *>(dst) = make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
                     }
                 }
@@ -456,14 +457,14 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const Args args)
     }
     __syncthreads();
     const int first = id / TB * RW, rows = min(RW, out - first), tokens = min(TOK, T - t0), per16 = 16 / size;
-    uint8_t *const Y = static_cast<uint8_t *>(args.Y) + ((size_t)t0 * out + first) * size;
+    uint8_t *const Yt = static_cast<uint8_t *>(Y) + ((size_t)t0 * out + first) * size;
     // 16 bytes at a time whether rows of Y start at multiples of 16 bytes or not (10999 x 4128 at 2048 tokens: element by element 10 % of
     // the call), the end of a row that is no whole piece element by element
     constexpr int PIECES = RW / 8;                             // of two-byte elements; a power of two, as is the number of four-byte ones
     const int chunks = PIECES * 8 / per16;
     for (int i = tid; i < tokens * chunks; i += WAVES * 64) {
         const int t = i / chunks, c = i % chunks;
-        uint8_t *const to = Y + ((size_t)t * out + c * per16) * size;
+        uint8_t *const to = Yt + ((size_t)t * out + c * per16) * size;
         const uint8_t *const from = lds + t * pitch + c * 16;
         if ((c + 1) * per16 <= rows) {
             const uint4 v = *reinterpret_cast<const uint4 *>(from);
@@ -529,7 +530,8 @@ template <int K, int NT, int WR, bool BF16> static int launch_form(const Args &a
         allowed[dev].store(true);
     }
     const int tiles = tiles_of(Shape{NT, WR, 0.f, {0.f, 0.f}}, a.out, a.T);
-    hipLaunchKernelGGL((gemm_kernel<K, NT, WR, BF16>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(WAVES * 64), lds, stream, a);
+    hipLaunchKernelGGL((gemm_kernel<K, NT, WR, BF16>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(WAVES * 64), lds, stream,
+                       a.bits, a.h, a.X, a.g, a.Y, a.out, a.in, a.T, a.out_dtype);
     return RB_OK;
 }
 

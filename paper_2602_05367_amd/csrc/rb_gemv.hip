@@ -40,7 +40,7 @@ constexpr int PART_FLOATS = MAXSLOT * CW * 2 * 16;   // [slot][wavefront][path][
 template <int KEPT, int DEPTH>
 __global__ __launch_bounds__(THREADS, 1) void gemv1_kernel(const v4u *__restrict__ bits, const __half *__restrict__ g,
                                                            const __half *__restrict__ h, const __half *__restrict__ x,
-                                                           __half *__restrict__ y, int out, int in, int RT, int CT)
+                                                           __half *__restrict__ y, int out, int in, int groups)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int n_up = (int)up_bytes(in, 1);
@@ -65,10 +65,10 @@ __global__ __launch_bounds__(THREADS, 1) void gemv1_kernel(const v4u *__restrict
 #pragma unroll
     for (int i = 0; i < KEPT; ++i) xv[i] = x[min(tid + i * THREADS, in - 1)];
     uint32_t rt0, nrt;
-    group_rows((uint32_t)RT, blockIdx.x, gridDim.x, 0, rt0, nrt);
+    group_rows((uint32_t)row_tiles(out), blockIdx.x, (uint32_t)groups, 0, rt0, nrt);
     const int my_row = min((int)rt0 * 16 + min(tid, (int)nrt * 16), out - 1);
     const __half g0 = g[my_row], g1 = g[(size_t)out + my_row];
-    const uint32_t uCT = (uint32_t)CT;
+    const uint32_t uCT = (uint32_t)col_tiles(in);
     const uint32_t U = nrt * uCT, u0 = (uint32_t)min(wave, CW) * U / CW, u1 = (uint32_t)min(wave + 1, CW) * U / CW;
     // tiles of a share are consecutive in the native layout: tile u of the share is rt0 * CT + u; a tile past the
     // share's end reads as zeros and fetches nothing
@@ -210,8 +210,7 @@ static int launch_form(const rb_layer *L, const void *x, void *y, hipStream_t st
     }
     hipLaunchKernelGGL((gemv1_kernel<KEPT, DEPTH>), dim3(G), dim3(THREADS), lds, stream, static_cast<const v4u *>(L->bits),
                        reinterpret_cast<const __half *>(L->g), reinterpret_cast<const __half *>(L->h),
-                       static_cast<const __half *>(x), static_cast<__half *>(y), L->out, L->in, row_tiles(L->out),
-                       col_tiles(L->in));
+                       static_cast<const __half *>(x), static_cast<__half *>(y), L->out, L->in, G);
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;
 }
 
