@@ -12,19 +12,20 @@
 // from W (4 bytes per weight) and the other paths (a bit and two cached scale values each), so a
 // pass is bound by the HBM read of W.  The singular triplet comes from a power iteration from the
 // all-ones vector (the matrix is non-negative): a = |R| b, c = |R|^T a.  One reading of W serves both where a row fits the registers
-// of a workgroup (one_pass_kernel); else, and in the first iteration of an update, there are two passes, by rows (four rows
+// of a workgroup (one_pass_kernel); else there are two passes, by rows (four rows
 // per workgroup) and by columns (slices of rows, partial sums added in slice order).  In all of them a lane takes
 // four consecutive columns, one 16-byte load of W.  a is left at its length and its norm taken
 // out of c: with b of length 1, sigma = ||c|| and the next b is c / ||c||.  After the last iteration one more pass by rows gives the last |R| b and the
 // signs of R_i.  The error after an update, term by term (as ||R_i||^2 - sigma^2 it would come out of the same pass, but with
-// a digit less: 3.6e-15 off where the terms are 1e-16), is found by the first pass of the next update on the way: its R less the
-// path that it leaves out.  Every sum has a fixed order.  The
+// a digit less: 3.6e-15 off where the terms are 1e-16), is found by the pass after the iteration while it holds a row of R, or, by two passes, by
+// the first pass of the next update on the way: its R less the path that it leaves out.  Every sum has a fixed order.  The
 // iteration's stopping rule is evaluated on the device; the host reads one flag per update when it expects the
 // iteration to have finished, so the call synchronises.
 //
-// Measured, 4096 x 11008, two paths, five sweeps (ten updates of four iterations): 3.1 to 3.2 ms (3.9 with two passes in every iteration; 5.1
-// before those): both passes in one 37 us, a row pass by itself 31 us, a column pass 31 us, the sums and the normalisation 12 us.  180 MB of W in
-// 31 us are 5.8 TB/s, what a plain read of as much out of the memory-side cache reaches (6.0); of the 37 us some 4 are the
+// Measured, 4096 x 11008, two paths, five sweeps (ten updates of four iterations): 2.7 to 2.8 ms (3.1 to 3.2 with launches of their own for b and for the errors; 3.9 with
+// two passes in every iteration; 5.1 before those): an iteration is one pass of 38 to 42 us and 5.5 for the sums, the pass after it 45 to 47 (by rows, without the errors, 35).
+// By two passes: 31 us each, the sums and the normalisation 12.  180 MB of W in
+// 31 us are 5.8 TB/s, what a plain read of as much out of the memory-side cache reaches (6.0); of the 42 us some 7 are b and the
 // columns' values at the start and 3 the 22 MB of sums at the end.
 #include <hip/hip_runtime.h>
 
@@ -301,6 +302,13 @@ __global__ __launch_bounds__(256, 4) void cols_kernel(Problem<J> p, const double
 // on its way meanwhile (with two to four of them it was no faster).  The factor f of a column is taken out of it, R = f (rows W - g B h / f), and goes with b and with the column
 // sums (a column without a factor has no h).  partial[workgroup][c] = sum over its rows of |R[r][c]| a[r], a_sq[workgroup]
 // the sum of a[r]^2.
+// LAST (after the iteration): a, the signs of R as rows_kernel<., FINAL> gives them (R in the order of its products, so the factors are
+// in LDS and b in registers), and partial[workgroup] = the sum of (|R[r][c]| - a[r] b[c])^2, the error after this update: what the
+// path leaves of R, while R is still there.  With that no pass after it has to find the error (a first pass by rows for it and one by columns
+// took 68 us where an iteration is one of 38; the pass over all paths at the end 34).
+// Before the rows, every workgroup does for itself what unit_kernel does (`fold`): b from the sums of the iteration before, its
+// change, the stopping rule, all from the same values in the same order, so all come to the same end.  The first workgroup writes down b and
+// the scalars, where nobody reads them meanwhile.  A launch of its own, of one workgroup, took 7 us of an iteration's 50.
 // Bound: the reading of W; a row of 11008 columns costs a SIMD about 0.7 us of double precision and 0.3 us for the sum over the
 // workgroup, and has 1.9 us in which 256 compute units read a row each.
 constexpr int ONE_PASS_GROUPS = 256, ONE_PASS_THREADS = 512, GROUP_COLS = 4 * ONE_PASS_THREADS;
@@ -308,16 +316,24 @@ template <int N> struct RowPiece {
     float4 w;
     uint32_t bits[N + 1];
 };
-template <int J, int CG>
-__global__ __launch_bounds__(ONE_PASS_THREADS, 2) void one_pass_kernel(Problem<J> p, const double *b, double *partial, double *a_sq, const Scalars *sc)
+// what an iteration starts from and, if it has sums to fold in, leaves for the next one
+struct Step {
+    const double *b, *sum, *sum_sq;
+    double *b_new;
+    const Scalars *sc;
+    Scalars *sc_new;
+    int n_sq, fold;                    // values of sum_sq; whether there are sums
+};
+template <int J, int CG, bool LAST>
+__global__ __launch_bounds__(ONE_PASS_THREADS, 2) void one_pass_kernel(Problem<J> p, Step st, double *partial, double *a, double *a_sq, uint32_t *signs)
 {
     constexpr int WAVES = ONE_PASS_THREADS / 64;
-    extern __shared__ __attribute__((aligned(16))) double2 b_lds[];      // [CG][2][thread]: f b of two columns, zero past the last column
-    __shared__ double red[2][WAVES];
+    extern __shared__ __attribute__((aligned(16))) double2 lds[];      // [CG][2][thread]: f b (LAST: f) of two columns, zero past the last column
+    __shared__ double red[2][WAVES], red_group[WAVES];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, in = p.in, W32 = in / 32;
     const int r0 = (int)((long long)p.out * blockIdx.x / gridDim.x), r1 = (int)((long long)p.out * (blockIdx.x + 1) / gridDim.x);
     struct Row { RowPiece<J> piece[CG]; double factor, g[J + 1]; } row;
-    const int done = sc->done;                                 // (looked at when the first loads are on their way)
+    const Scalars before = *st.sc;                             // (looked at when the first loads are on their way)
     // (buffer loads: columns past the last one read as zero, and one register holds the thread's place in every group)
     auto fetch_row = [&](int r) {
         const __amdgpu_buffer_rsrc_t w_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.W + (size_t)r * in), 0, in * 4, 0x00020000);
@@ -332,27 +348,70 @@ __global__ __launch_bounds__(ONE_PASS_THREADS, 2) void one_pass_kernel(Problem<J
         }
         row.factor = p.rows ? p.rows[r] : 1.0;
     };
+    auto column = [&](int k) { return k * GROUP_COLS + 4 * tid; };
+    auto safe = [&](int c) { return c < in ? c : 0; };          // in % 32 == 0: all four columns exist or none
     fetch_row(min(r0, p.out - 1));
-    double h[CG][J + 1][4], sum[CG][4], squares = 0.0;
+    double b[CG][4];
+#pragma unroll
+    for (int k = 0; k < CG; ++k) four(st.b, safe(column(k)), b[k]);
+    bool done = before.done != 0;
+    if (st.fold) {
+        double sum[CG][4], sq = 0.0;
+#pragma unroll
+        for (int k = 0; k < CG; ++k) four(st.sum, safe(column(k)), sum[k]);
+        for (int i = tid; i < st.n_sq; i += ONE_PASS_THREADS) sq += st.sum_sq[i];
+        Scalars after = before;
+        if (!done && before.na == 0.0) {                       // |R| b = 0: b stays
+            done = true;
+        } else if (!done) {
+            after.sigma = sqrt(group_sum(sq, red_group, WAVES));
+            double change = 0.0;
+#pragma unroll
+            for (int k = 0; k < CG; ++k)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double bn = sum[k][e] / after.sigma, d = bn - b[k][e];
+                    change += column(k) < in ? d * d : 0.0;
+                    b[k][e] = bn;
+                }
+            after.db = sqrt(group_sum(change, red_group, WAVES));
+            after.iters += 1;
+            done = (fabs(after.sigma - before.sigma) <= TOL_SIGMA * after.sigma && after.db <= TOL_B) || after.iters >= MAX_ITER;
+        }
+        after.done = done;
+        if (blockIdx.x == 0) {
+#pragma unroll
+            for (int k = 0; k < CG; ++k)
+                if (column(k) < in) {
+                    *reinterpret_cast<double2 *>(st.b_new + column(k)) = make_double2(b[k][0], b[k][1]);
+                    *reinterpret_cast<double2 *>(st.b_new + column(k) + 2) = make_double2(b[k][2], b[k][3]);
+                }
+            if (tid == 0) *st.sc_new = after;
+        }
+    }
+    if (LAST ? !done : done) return;
+    double h[CG][J + 1][4], sum[CG][4], squares = 0.0, error = 0.0;
 #pragma unroll
     for (int k = 0; k < CG; ++k) {
-        const int c = k * GROUP_COLS + 4 * tid, cs = c < in ? c : 0;     // in % 32 == 0: all four columns exist or none
-        double v[4];
+        const bool there = column(k) < in;
         Columns<J> cols;
-        fetch_columns<J, J>(p, cs, cols);
-        four(b, cs, v);
+        fetch_columns<J, J>(p, safe(column(k)), cols);
+        double kept[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            v[e] = c < in ? v[e] * fabs(cols.f[e]) : 0.0;
+            b[k][e] = there ? b[k][e] : 0.0;
+            kept[e] = LAST ? (there ? cols.f[e] : 0.0) : b[k][e] * fabs(cols.f[e]);
 #pragma unroll
-            for (int j = 0; j < J; ++j) h[k][j][e] = cols.f[e] != 0.0 ? cols.h[j][e] / cols.f[e] : 0.0;
+            for (int j = 0; j < J; ++j) {
+                if (LAST) h[k][j][e] = there ? cols.h[j][e] : 0.0;
+                else h[k][j][e] = cols.f[e] != 0.0 ? cols.h[j][e] / cols.f[e] : 0.0;
+            }
             sum[k][e] = 0.0;
         }
-        b_lds[2 * k * ONE_PASS_THREADS + tid] = make_double2(v[0], v[1]);
-        b_lds[(2 * k + 1) * ONE_PASS_THREADS + tid] = make_double2(v[2], v[3]);
+        lds[2 * k * ONE_PASS_THREADS + tid] = make_double2(kept[0], kept[1]);
+        lds[(2 * k + 1) * ONE_PASS_THREADS + tid] = make_double2(kept[2], kept[3]);
     }
-    // (a thread reads what it has written of b)
-    if (done) return;
+    // (a thread reads what it has written there)
 #pragma unroll 1
     for (int r = r0; r < r1; ++r) {
         double v[CG][4];
@@ -361,6 +420,10 @@ __global__ __launch_bounds__(ONE_PASS_THREADS, 2) void one_pass_kernel(Problem<J
             const float w[4] = {row.piece[k].w.x, row.piece[k].w.y, row.piece[k].w.z, row.piece[k].w.w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[k][e] = row.factor * (double)w[e];
+            if (LAST) {
+                const double2 low = lds[2 * k * ONE_PASS_THREADS + tid], high = lds[(2 * k + 1) * ONE_PASS_THREADS + tid];
+                v[k][0] *= low.x; v[k][1] *= low.y; v[k][2] *= high.x; v[k][3] *= high.y;
+            }
 #pragma unroll
             for (int j = 0; j < J; ++j) {
                 const uint32_t bits = row.piece[k].bits[j] >> (4 * (tid & 7));
@@ -377,7 +440,20 @@ __global__ __launch_bounds__(ONE_PASS_THREADS, 2) void one_pass_kernel(Problem<J
         double dot[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int k = 0; k < CG; ++k) {
-            const double2 low = b_lds[2 * k * ONE_PASS_THREADS + tid], high = b_lds[(2 * k + 1) * ONE_PASS_THREADS + tid];
+            double2 low, high;
+            if (LAST) {
+                low = make_double2(b[k][0], b[k][1]);
+                high = make_double2(b[k][2], b[k][3]);
+                // eight lanes hold the 32 columns of a word, four each
+                uint32_t four = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) four |= !(v[k][e] >= 0.0) ? 1u << e : 0u;
+                const uint32_t word = or_over_8(four << (4 * (lane & 7)));
+                if ((lane & 7) == 0 && column(k) < in) signs[(size_t)r * W32 + (column(k) >> 5)] = word;
+            } else {
+                low = lds[2 * k * ONE_PASS_THREADS + tid];
+                high = lds[(2 * k + 1) * ONE_PASS_THREADS + tid];
+            }
             dot[0] += fabs(v[k][0]) * low.x;
             dot[1] += fabs(v[k][1]) * low.y;
             dot[2] += fabs(v[k][2]) * high.x;
@@ -386,49 +462,69 @@ __global__ __launch_bounds__(ONE_PASS_THREADS, 2) void one_pass_kernel(Problem<J
         const double d = over_wave((dot[0] + dot[1]) + (dot[2] + dot[3]));
         if (lane == 0) red[r & 1][wave] = d;
         __syncthreads();                                       // (the other half of `red` is written before anyone is a row further on)
-        double a = 0.0;
+        double ar = 0.0;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) a += red[r & 1][w];
-        squares += a * a;
+        for (int w = 0; w < WAVES; ++w) ar += red[r & 1][w];
+        squares += ar * ar;
+        if (LAST && tid == 0) a[r] = ar;
 #pragma unroll
         for (int k = 0; k < CG; ++k)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sum[k][e] += fabs(v[k][e]) * a;
+            for (int e = 0; e < 4; ++e) {
+                if (LAST) {
+                    const double left = fabs(v[k][e]) - ar * b[k][e];
+                    error += left * left;
+                } else {
+                    sum[k][e] += fabs(v[k][e]) * ar;
+                }
+            }
     }
+    if (LAST) {
+        error = group_sum(error, red_group, WAVES);
+        if (tid == 0) partial[blockIdx.x] = error;
+    } else {
 #pragma unroll
-    for (int k = 0; k < CG; ++k) {
-        const int c = k * GROUP_COLS + 4 * tid;
-        if (c >= in) continue;
-        double f[4] = {1.0, 1.0, 1.0, 1.0};
-        if (p.cols) four(p.cols, c, f);
-        double *const to = partial + (size_t)blockIdx.x * in + c;
-        *reinterpret_cast<double2 *>(to) = make_double2(sum[k][0] * fabs(f[0]), sum[k][1] * fabs(f[1]));
-        *reinterpret_cast<double2 *>(to + 2) = make_double2(sum[k][2] * fabs(f[2]), sum[k][3] * fabs(f[3]));
+        for (int k = 0; k < CG; ++k) {
+            const int c = column(k);
+            if (c >= in) continue;
+            double f[4] = {1.0, 1.0, 1.0, 1.0};
+            if (p.cols) four(p.cols, c, f);
+            double *const to = partial + (size_t)blockIdx.x * in + c;
+            *reinterpret_cast<double2 *>(to) = make_double2(sum[k][0] * fabs(f[0]), sum[k][1] * fabs(f[1]));
+            *reinterpret_cast<double2 *>(to + 2) = make_double2(sum[k][2] * fabs(f[2]), sum[k][3] * fabs(f[3]));
+        }
     }
     if (tid == 0) a_sq[blockIdx.x] = squares;
 }
 // groups of columns of the one-pass form, 0 where it is not taken.  Wider rows do not fit the registers; below 1024 rows (four per workgroup) the sums
 // of 256 workgroups are as much to move as what a second pass reads, and rows of less than 2048 columns leave threads idle (time
-// of the call over that with two passes: 4096 x 11008 0.81, 5504 x 8192 0.75, 11008 x 4096 0.77, three paths 4096 x 11008, where 14 registers spill,
-// 0.90, 1024 x 11008 0.96 to 0.99, 1400 x 2048 0.87; 11008 x 1024 1.12)
+// of the call over that with two passes: 4096 x 11008 0.70, 5504 x 8192 0.62, 11008 x 4096 0.68, three paths 4096 x 11008, where 12 registers spill,
+// 0.86, 1024 x 11008 0.85, 1400 x 2048 0.75)
 static int one_pass_groups(int out, int in)
 {
     const int groups = (in + GROUP_COLS - 1) / GROUP_COLS;
     if (out < ONE_PASS_MIN_ROWS || in < ONE_PASS_MIN_COLS || groups > 6) return 0;
     return (groups + 1) / 2 * 2;
 }
-template <int J, int CG> static int launch_one_pass(const Problem<J> &p, const double *b, double *partial, double *a_sq, const Scalars *sc, hipStream_t stream)
+template <int J, int CG, bool LAST> static int launch_groups(const Problem<J> &p, const Step &st, double *partial, double *a, double *a_sq, uint32_t *signs, hipStream_t stream)
 {
     constexpr int lds = CG * GROUP_COLS * (int)sizeof(double);
     static std::atomic<bool> allowed[64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return RB_ERR_HIP;
     if (lds > 48 * 1024 && !allowed[dev].load()) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(one_pass_kernel<J, CG>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return RB_ERR_HIP;
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(one_pass_kernel<J, CG, LAST>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return RB_ERR_HIP;
         allowed[dev].store(true);
     }
-    hipLaunchKernelGGL((one_pass_kernel<J, CG>), dim3(ONE_PASS_GROUPS), dim3(ONE_PASS_THREADS), lds, stream, p, b, partial, a_sq, sc);
+    hipLaunchKernelGGL((one_pass_kernel<J, CG, LAST>), dim3(ONE_PASS_GROUPS), dim3(ONE_PASS_THREADS), lds, stream, p, st, partial, a, a_sq, signs);
     return RB_OK;
+}
+template <bool LAST, int J> static int launch_one_pass(int groups, const Problem<J> &p, const Step &st, double *partial, double *a, double *a_sq, uint32_t *signs, hipStream_t stream)
+{
+    if (groups == 2) return launch_groups<J, 2, LAST>(p, st, partial, a, a_sq, signs, stream);
+    if (groups == 4) return launch_groups<J, 4, LAST>(p, st, partial, a, a_sq, signs, stream);
+    if constexpr (LAST && J == 2) return RB_ERR_UNSUPPORTED;   // (not asked for, see `whole`)
+    else return launch_groups<J, 6, LAST>(p, st, partial, a, a_sq, signs, stream);
 }
 
 // sum[c] = the slices of partial[.][c], in eight runs of consecutive ones, over the norm of a (every workgroup adds
@@ -436,13 +532,14 @@ template <int J, int CG> static int launch_one_pass(const Problem<J> &p, const d
 constexpr int SUMS_COLS = 64, SUMS_RUNS = 8;
 __global__ __launch_bounds__(SUMS_COLS * SUMS_RUNS) void slices_kernel(const double *partial, int n_slices, const double *a_sq, int n_a, int in, double *sum, double *sum_sq, Scalars *sc)
 {
-    if (sc->done) return;
+    const int done = sc->done;                                 // (looked at when the sums are there: no trip to memory before theirs)
     __shared__ double part[SUMS_RUNS][SUMS_COLS], red[SUMS_RUNS];
     const int x = threadIdx.x % SUMS_COLS, run = threadIdx.x / SUMS_COLS, c = blockIdx.x * SUMS_COLS + x, cs = min(c, in - 1);
     double s = 0.0, na = 0.0;
     for (int i = threadIdx.x; i < n_a; i += SUMS_COLS * SUMS_RUNS) na += a_sq[i];
 #pragma unroll 8
     for (int k = n_slices * run / SUMS_RUNS; k < n_slices * (run + 1) / SUMS_RUNS; ++k) s += partial[(size_t)k * in + cs];
+    if (done) return;
     part[run][x] = s;
     na = sqrt(group_sum(na, red, SUMS_RUNS));
     if (blockIdx.x == 0 && threadIdx.x == 0) sc->na = na;
@@ -500,9 +597,10 @@ __global__ __launch_bounds__(1024) void unit_kernel(double *b, const double *sum
     }
 }
 
-// after the final a = |R| b: g' = sqrt(sigma) a / sigma, h' = sqrt(sigma) b with sigma = ||a||
+// after the final a = |R| b: g' = sqrt(sigma) a / sigma, h' = sqrt(sigma) b with sigma = ||a||; and the root of the sum of err_sq, of
+// as many workgroups as a_sq, if there are any
 __global__ __launch_bounds__(256) void scales_kernel(const double *a, const double *b, const double *a_sq, int n_a, double *g_i,
-                                                     double *h_i, int out, int in, const Scalars *sc)
+                                                     double *h_i, int out, int in, const Scalars *sc, const double *err_sq, double *err)
 {
     if (!sc->done) return;
     __shared__ double red[4];
@@ -513,6 +611,12 @@ __global__ __launch_bounds__(256) void scales_kernel(const double *a, const doub
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < out) g_i[i] = sigma > 0.0 ? root * (a[i] / sigma) : 0.0;
     if (i < in) h_i[i] = root * b[i];
+    if (err && blockIdx.x == 0) {
+        double e2 = 0.0;
+        for (int n = threadIdx.x; n < n_a; n += 256) e2 += err_sq[n];
+        e2 = group_sum(e2, red, 4);
+        if (threadIdx.x == 0) *err = sqrt(e2);
+    }
 }
 
 // squared Frobenius norm of W' - sum_j What_j over all J paths (the last update: nothing follows that could find it on the
@@ -576,14 +680,14 @@ __global__ __launch_bounds__(256) void unscale_kernel(double *g, double *h, cons
 struct Layout {
     size_t scalars, a, a_sq, b, sum, sum_sq, partial, total;
 };
-// the slices come last; `rows` of them each, or the workgroups of the one-pass form
+// the slices come last; `rows` of them each, or the workgroups of the one-pass form and a second b
 static Layout make_layout(int out, int in, int rows, bool one_pass)
 {
     auto up = [](size_t v) { return (v + 255) / 256 * 256; };
-    const size_t slices = std::max<size_t>((size_t)(out + rows - 1) / rows, one_pass ? ONE_PASS_GROUPS : 0), groups = (size_t)(out + ROWS - 1) / ROWS;
+    const size_t slices = std::max<size_t>((size_t)(out + rows - 1) / rows, one_pass ? ONE_PASS_GROUPS + 1 : 0), groups = (size_t)(out + ROWS - 1) / ROWS;
     Layout L;
     size_t o = 0;
-    L.scalars = o; o += up(sizeof(Scalars));
+    L.scalars = o; o += up(2 * sizeof(Scalars));
     L.a = o; o += up(sizeof(double) * out);
     L.a_sq = o; o += up(sizeof(double) * groups);
     L.b = o; o += up(sizeof(double) * in);
@@ -604,6 +708,9 @@ static int derive(const float *W, const double *row_factors, const double *col_f
                   uint32_t *packed, double *err, const Buffers &ws, int slice_rows, bool room, hipStream_t stream)
 {
     const int one_pass = room ? one_pass_groups(out, in) : 0;
+    // Whether the one-pass form does all of an iteration and the pass after it.  Not for three paths of more than 8192 columns: LAST would spill 52 registers
+    // (169 us, where the pass by rows and a first iteration in two passes cost 66 more than an iteration; 4096 x 11008, three sweeps 4.10 and 3.42 ms)
+    const bool whole = one_pass && (K < 3 || one_pass < 6);
     const int n_slices = (out + slice_rows - 1) / slice_rows, n_a = (out + ROWS - 1) / ROWS;
     const size_t words = (size_t)out * (in / 32);
     const dim3 by_rows((unsigned)n_a), by_cols((in + 1023) / 1024, n_slices), wg(256);
@@ -621,33 +728,47 @@ static int derive(const float *W, const double *row_factors, const double *col_f
             uint32_t *const signs = packed + i * words;
             const bool err_before = err && t * K + i > 0;
             hipLaunchKernelGGL(start_kernel, dim3((in + 255) / 256), wg, 0, stream, ws.b, in, ws.sc);
+            double *const err_here = err ? err + (size_t)t * K + i : nullptr;
+            // one reading of W per iteration: b and the scalars change places whenever a kernel folds sums in
+            double *const bs[2] = {ws.b, ws.partial + (size_t)ONE_PASS_GROUPS * in};
+            int now = 0, fold = 0;
+            auto step = [&]() {
+                const Step st{bs[now], ws.sum, ws.sum_sq, bs[now ^ 1], ws.sc + now, ws.sc + (now ^ 1), (in + SUMS_COLS - 1) / SUMS_COLS, fold};
+                now ^= fold;
+                return st;
+            };
             Scalars host;
             for (int it = 1;; ++it) {
-                if (it == 1 && err_before) {
-                    // (`partial` has room: out / 4 sums where the column pass has in >= 32 for every 32 rows, or 64 with the smaller workspace)
-                    hipLaunchKernelGGL((rows_kernel<K - 1, FIRST>), by_rows, wg, 0, stream, p, ws.b, ws.a, ws.a_sq, signs, ws.partial, ws.sc);
-                    hipLaunchKernelGGL(err_sum_kernel, dim3(1), dim3(1024), 0, stream, ws.partial, n_a, err + (size_t)t * K + i - 1);
-                } else {
-                    if (!one_pass) hipLaunchKernelGGL((rows_kernel<K - 1, ITERATE>), by_rows, wg, 0, stream, p, ws.b, ws.a, ws.a_sq, signs, ws.partial, ws.sc);
-                }
-                const bool one = one_pass && !(it == 1 && err_before);
+                const bool one = one_pass && (whole || it > 1 || !err_before);
                 if (one) {
-                    int rc = RB_OK;
-                    if (one_pass == 2) rc = launch_one_pass<K - 1, 2>(p, ws.b, ws.partial, ws.a_sq, ws.sc, stream);
-                    else if (one_pass == 4) rc = launch_one_pass<K - 1, 4>(p, ws.b, ws.partial, ws.a_sq, ws.sc, stream);
-                    else rc = launch_one_pass<K - 1, 6>(p, ws.b, ws.partial, ws.a_sq, ws.sc, stream);
+                    const int rc = launch_one_pass<false>(one_pass, p, step(), ws.partial, ws.a, ws.a_sq, signs, stream);
                     if (rc != RB_OK) return rc;
                 } else {
+                    if (it == 1 && err_before) {
+                        // (`partial` has room: out / 4 sums where the column pass has in >= 32 for every 32 rows, or 64 with the smaller workspace)
+                        hipLaunchKernelGGL((rows_kernel<K - 1, FIRST>), by_rows, wg, 0, stream, p, ws.b, ws.a, ws.a_sq, signs, ws.partial, ws.sc);
+                        hipLaunchKernelGGL(err_sum_kernel, dim3(1), dim3(1024), 0, stream, ws.partial, n_a, err_here - 1);
+                    } else {
+                        hipLaunchKernelGGL((rows_kernel<K - 1, ITERATE>), by_rows, wg, 0, stream, p, ws.b, ws.a, ws.a_sq, signs, ws.partial, ws.sc);
+                    }
                     hipLaunchKernelGGL((cols_kernel<K - 1>), by_cols, wg, 0, stream, p, ws.a, ws.partial, slice_rows, ws.sc);
                 }
-                hipLaunchKernelGGL(slices_kernel, dim3((in + SUMS_COLS - 1) / SUMS_COLS), dim3(SUMS_COLS * SUMS_RUNS), 0, stream, ws.partial, one ? ONE_PASS_GROUPS : n_slices, ws.a_sq, one ? ONE_PASS_GROUPS : n_a, in, ws.sum, ws.sum_sq, ws.sc);
-                hipLaunchKernelGGL(unit_kernel, dim3(1), dim3(1024), 0, stream, ws.b, ws.sum, ws.sum_sq, in, ws.sc);
+                hipLaunchKernelGGL(slices_kernel, dim3((in + SUMS_COLS - 1) / SUMS_COLS), dim3(SUMS_COLS * SUMS_RUNS), 0, stream, ws.partial, one ? ONE_PASS_GROUPS : n_slices, ws.a_sq,
+                                   one ? ONE_PASS_GROUPS : n_a, in, ws.sum, ws.sum_sq, ws.sc + now);
+                if (!whole) hipLaunchKernelGGL(unit_kernel, dim3(1), dim3(1024), 0, stream, ws.b, ws.sum, ws.sum_sq, in, ws.sc);
+                fold = whole;
                 if (it < look) continue;
                 // |R| b and the signs for the converged b, the path's new scales: nothing happens unless the iteration has finished
-                hipLaunchKernelGGL((rows_kernel<K - 1, FINAL>), by_rows, wg, 0, stream, p, ws.b, ws.a, ws.a_sq, signs, ws.partial, ws.sc);
-                hipLaunchKernelGGL(scales_kernel, dim3((std::max(out, in) + 255) / 256), wg, 0, stream, ws.a, ws.b, ws.a_sq, n_a,
-                                   g + (size_t)i * out, h + (size_t)i * in, out, in, ws.sc);
-                if (hipMemcpyAsync(&host, ws.sc, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess ||
+                if (whole) {
+                    const int rc = launch_one_pass<true>(one_pass, p, step(), ws.partial, ws.a, ws.a_sq, signs, stream);
+                    if (rc != RB_OK) return rc;
+                    fold = 0;
+                } else {
+                    hipLaunchKernelGGL((rows_kernel<K - 1, FINAL>), by_rows, wg, 0, stream, p, ws.b, ws.a, ws.a_sq, signs, ws.partial, ws.sc);
+                }
+                hipLaunchKernelGGL(scales_kernel, dim3((std::max(out, in) + 255) / 256), wg, 0, stream, ws.a, bs[now], ws.a_sq, whole ? ONE_PASS_GROUPS : n_a,
+                                   g + (size_t)i * out, h + (size_t)i * in, out, in, ws.sc + now, ws.partial, whole ? err_here : nullptr);
+                if (hipMemcpyAsync(&host, ws.sc + now, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess ||
                     hipStreamSynchronize(stream) != hipSuccess)
                     return RB_ERR_HIP;
                 if (host.done) break;
@@ -655,7 +776,7 @@ static int derive(const float *W, const double *row_factors, const double *col_f
             look = std::max(1, host.iters);
         }
     }
-    if (err) {
+    if (err && !whole) {
         Problem<K> p{W, row_factors, col_factors, {}, {}, {}, out, in};
         for (int j = 0; j < K; ++j) {
             p.packed[j] = packed + j * words;
