@@ -404,57 +404,61 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const uint32_t *bit
     contract(std::true_type(), 0, by_ratios);
     contract(std::false_type(), by_ratios, rounds);
 
-    // ---- sums of the column groups: the upper half hands its accumulators to the lower half
+    // ---- sums of the column groups.  The tile is MB x NT x 4 pieces of four registers; each group adds up the pieces of an equal share
+    // of it and hands the others theirs, so all wavefronts write, read and (below) convert (the upper half handing everything to the lower, twice with four
+    // groups: 4096 x 4096 at 333 tokens 25.0 us)
+    constexpr int PIECES_ALL = MB * NT * 4, SHARE = PIECES_ALL / WK;
+    static_assert(PIECES_ALL % WK == 0 && (WK - 1) * WR * PIECES_ALL * 1024 <= lds_bytes<K, NT, WR>(), "equal shares, room for them");
     float4 *const part = reinterpret_cast<float4 *>(lds);
+    auto piece = [&](int f) { return acc[f / (NT * 4)][f / 4 % NT]; };
+    auto at = [&](int owner, int from, int f) { return part + ((((owner * (WK - 1) + (from < owner ? from : from - 1)) * WR + wr) * SHARE + f % SHARE) * 64 + lane); };
 #pragma unroll
-    for (int half = WK / 2; half > 0; half >>= 1) {
-        float4 *const mine = part + (size_t)((grp % half) * WR + wr) * (MB * NT * 4 * 64) + lane;
-        if (grp >= half && grp < 2 * half)
+    for (int o = 0; o < WK; ++o)
+        if (grp != o)
 #pragma unroll
-            for (int b = 0; b < MB; ++b)
+            for (int f = o * SHARE; f < (o + 1) * SHARE; ++f) {
+                const v16f v = piece(f);
+                *at(o, grp, f) = make_float4(v[f % 4 * 4], v[f % 4 * 4 + 1], v[f % 4 * 4 + 2], v[f % 4 * 4 + 3]);
+            }
+    __syncthreads();
 #pragma unroll
-                for (int n = 0; n < NT; ++n)
+    for (int o = 0; o < WK; ++o)
+        if (grp == o)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        mine[((b * NT + n) * 4 + e) * 64] = make_float4(acc[b][n][4 * e], acc[b][n][4 * e + 1], acc[b][n][4 * e + 2], acc[b][n][4 * e + 3]);
-        __syncthreads();
-        if (grp < half)
+            for (int f = o * SHARE; f < (o + 1) * SHARE; ++f) {
+                v16f &to = acc[f / (NT * 4)][f / 4 % NT];
+                float4 v[WK];
 #pragma unroll
-            for (int b = 0; b < MB; ++b)
-#pragma unroll
-                for (int n = 0; n < NT; ++n)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float4 v = mine[((b * NT + n) * 4 + e) * 64];
-                        acc[b][n][4 * e] += v.x; acc[b][n][4 * e + 1] += v.y; acc[b][n][4 * e + 2] += v.z; acc[b][n][4 * e + 3] += v.w;
-                    }
-        __syncthreads();
-    }
+                for (int n = 0; n < WK; ++n) v[n] = n == o ? make_float4(to[f % 4 * 4], to[f % 4 * 4 + 1], to[f % 4 * 4 + 2], to[f % 4 * 4 + 3]) : *at(o, n, f);
+                auto sum = [&](auto get) { return WK == 2 ? get(v[0]) + get(v[1]) : (get(v[0]) + get(v[2 % WK])) + (get(v[1]) + get(v[3 % WK])); };
+                to[f % 4 * 4] = sum([](float4 a) { return a.x; });
+                to[f % 4 * 4 + 1] = sum([](float4 a) { return a.y; });
+                to[f % 4 * 4 + 2] = sum([](float4 a) { return a.z; });
+                to[f % 4 * 4 + 3] = sum([](float4 a) { return a.w; });
+            }
+    __syncthreads();
     // ---- the tile in the output's type through LDS, so that whole rows of it are stored.  Register 4 e + i
     // of lane (r, kg): token r, row 8 e + 4 kg + i of the 32
     constexpr int RW = 32 * MB * WR;                           // rows of the workgroup
     const int size = out_dtype == RB_F32 ? 4 : 2, pitch = RW * size + 16;
-    if (grp == 0) {
 #pragma unroll
-        for (int b = 0; b < MB; ++b)
+    for (int o = 0; o < WK; ++o)
+        if (grp == o)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
+            for (int f = o * SHARE; f < (o + 1) * SHARE; ++f) {
+                const int b = f / (NT * 4), n = f / 4 % NT, e = f % 4;
                 const float4 base = *reinterpret_cast<const float4 *>(&row_scale[64 * wr + 32 * b + 8 * e + 4 * kg]);
+                uint8_t *const dst = lds + (32 * n + r) * pitch + (32 * (MB * wr + b) + 8 * e + 4 * kg) * size;
+                const float v[4] = {acc[b][n][4 * e] * base.x, acc[b][n][4 * e + 1] * base.y, acc[b][n][4 * e + 2] * base.z, acc[b][n][4 * e + 3] * base.w};
+                if (out_dtype == RB_F32) {
+                    *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+                } else {
+                    uint32_t to[4];
 #pragma unroll
-                for (int n = 0; n < NT; ++n) {
-                    uint8_t *const dst = lds + (32 * n + r) * pitch + (32 * (MB * wr + b) + 8 * e + 4 * kg) * size;
-                    const float v[4] = {acc[b][n][4 * e] * base.x, acc[b][n][4 * e + 1] * base.y, acc[b][n][4 * e + 2] * base.z, acc[b][n][4 * e + 3] * base.w};
-                    if (out_dtype == RB_F32) {
-                        *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
-                    } else {
-                        uint32_t o[4];
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) o[i] = out_dtype == RB_F16 ? __half_as_ushort(__float2half_rn(v[i])) : f32_to_bf16_rne(v[i]);
-                        *reinterpret_cast<uint2 *>(dst) = make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
-                    }
+                    for (int i = 0; i < 4; ++i) to[i] = out_dtype == RB_F16 ? __half_as_ushort(__float2half_rn(v[i])) : f32_to_bf16_rne(v[i]);
+                    *reinterpret_cast<uint2 *>(dst) = make_uint2(to[0] | (to[1] << 16), to[2] | (to[3] << 16));
                 }
             }
-    }
     __syncthreads();
     const int first = id / TB * RW, rows = min(RW, out - first), tokens = min(TOK, T - t0), per16 = 16 / size;
     uint8_t *const Yt = static_cast<uint8_t *>(Y) + ((size_t)t0 * out + first) * size;
