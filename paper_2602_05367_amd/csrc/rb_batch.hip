@@ -219,7 +219,7 @@ __host__ __device__ constexpr int wave_bytes(int K, int G, int P, bool bf16) { r
 // K paths, G groups of 16 tokens, P row tiles per workgroup of W wavefronts at most, BF16: the activations are bfloat16, WIDE: offsets into
 // the input or into the signs of a row tile may reach NOWHERE (1 GiB): 64-bit addresses, loads in branches, one row tile per workgroup
 template <int K, int G, int P, int W, bool BF16, bool WIDE>
-__global__ __launch_bounds__(W * 64, two_share(K, G, P) && !WIDE ? 4 : 2) void batch_kernel(const uint32_t *bits, const void *x, const uint16_t *h, const uint16_t *g, void *y,
+__global__ __launch_bounds__(W * 64, two_share(K, G, P) && !WIDE ? 4 : 2) void batch_kernel(Address bits, Address x, Address h, Address g, Address y,
                                                                                         int out, int in, uint32_t tokens, uint32_t cut, const Others others)
 {
     // bfloat16: fp16 copies of the units that fp16 holds, the others after them as they are.  Beyond one token group looking at a
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(W * 64, two_share(K, G, P) && !WIDE ? 4 : 2) void b
     constexpr bool EITHER = BF16 && G == 1;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];    // a slab per wavefront; then [wavefront][row tile][token][row] sums
     __shared__ __attribute__((aligned(16))) float g_lds[P * K * TILE_ROWS];      // [path][row tile][row]
-    Op op = {bits, x, h, g, y, out, in, tokens, cut};
+    Op op = {global_at<const uint32_t>(bits), global_at<const uint8_t>(x), global_at<const uint16_t>(h), global_at<const uint16_t>(g), global_at<uint8_t>(y), out, in, tokens, cut};
     if (blockIdx.y != 0) {
         op = others.op[blockIdx.y - 1];
         // (all of it at once: left to itself the compiler fetches it in four trips, each where it is used first)
@@ -515,7 +515,7 @@ static int launch_form(const Args &args, int nops, int groups, int nw, hipStream
         }
     }
     hipLaunchKernelGGL((batch_kernel<K, G, P, W, BF16, WIDE>), dim3((unsigned)groups, (unsigned)nops, (unsigned)(G == 4 ? (args.first.T() + 63) / 64 : 1)), dim3((unsigned)(nw * 64)), nw * per_wave, stream,
-                       args.first.bits, args.first.x, args.first.h, args.first.g, args.first.y, args.first.out, args.first.in, args.first.tokens, args.first.cut, args.others);
+                       address_of(args.first.bits), address_of(args.first.x), address_of(args.first.h), address_of(args.first.g), address_of(args.first.y), args.first.out, args.first.in, args.first.tokens, args.first.cut, args.others);
     return RB_OK;
 }
 

@@ -34,6 +34,15 @@ __device__ __forceinline__ void store_out(void *Y, int out_dtype, size_t idx, fl
     }
 }
 
+// A kernel's pointer as a number: for each pointer argument of a launch the runtime looks up which allocation it lies in, some 0.05 us of
+// host time, which is most of a small call
+typedef unsigned long long Address;
+inline Address address_of(const void *p) { return (Address)reinterpret_cast<uintptr_t>(p); }
+template <typename T> __device__ __forceinline__ T *global_at(Address a)
+{
+    return (T *)reinterpret_cast<__attribute__((address_space(1))) T *>(a);
+}
+
 // both words of a pair moved up by n < 16 bits; what the upper one takes over from the lower one lies in its lowest n bits.  In assembly:
 // the compiler would use one instruction per word, and the 64-bit shift takes as long as one of them (1.8 ns a wavefront)
 __device__ __forceinline__ void shift_left(unsigned long long pair, int n, uint32_t &lower, uint32_t &upper)

@@ -138,9 +138,12 @@ __device__ __forceinline__ uint4 buffer_load(__amdgpu_buffer_rsrc_t rs, uint32_t
 // BF16: X is bfloat16.  h starts at a multiple of 16 bytes (its rows then do too).  14 words of single arguments, which the compiler has put
 // into registers at the start (build.py asks for it; two 7B-shaped blocks at 333 tokens 567 us with the arguments in memory, 560 so)
 template <int K, int NT, int WR, bool BF16>
-__global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const uint32_t *bits, const __half *h, const void *X, const __half *g, void *Y, int out, int in,
-                                                              int T, int out_dtype)
+__global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(Address bits_, Address h_, Address X_, Address g_, Address Y_, int out, int in, int T, int out_dtype)
 {
+    const uint32_t *const bits = global_at<const uint32_t>(bits_);
+    const __half *const h = global_at<const __half>(h_), *const g = global_at<const __half>(g_);
+    const uint8_t *const X = global_at<const uint8_t>(X_);
+    uint8_t *const Y = global_at<uint8_t>(Y_);
     constexpr int WK = WAVES / WR, GT = 64 * WR;               // column groups; threads of one
     constexpr int TOK = 32 * NT, XL = TOK * 16 / GT, XP = XL / 2;     // tokens of a tile; 16-byte loads of X per thread and step, in two parts
     constexpr int SLAB = slab_bytes<K, NT>();
@@ -171,7 +174,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const uint32_t *bit
     // Everything a step advances is uniform over the wavefront; a lane keeps 32-bit offsets
     const int gid = tid - grp * GT, ch = gid & 15, row0 = gid >> 4;
     uint8_t *const slab0 = lds + (size_t)grp * 2 * SLAB;
-    const uint8_t *const Xt = static_cast<const uint8_t *>(X) + (size_t)t0 * in * 2;
+    const uint8_t *const Xt = X + (size_t)t0 * in * 2;
     uint32_t x_off[XL];
 #pragma unroll
     for (int i = 0; i < XL; ++i) x_off[i] = (uint32_t)min(row0 + i * (GT / 16), T - 1 - t0) * (uint32_t)in * 2u + (uint32_t)ch * 16u;
@@ -461,7 +464,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(const uint32_t *bit
             }
     __syncthreads();
     const int first = id / TB * RW, rows = min(RW, out - first), tokens = min(TOK, T - t0), per16 = 16 / size;
-    uint8_t *const Yt = static_cast<uint8_t *>(Y) + ((size_t)t0 * out + first) * size;
+    uint8_t *const Yt = Y + ((size_t)t0 * out + first) * size;
     // 16 bytes at a time whether rows of Y start at multiples of 16 bytes or not (10999 x 4128 at 2048 tokens: element by element 10 % of
     // the call), the end of a row that is no whole piece element by element
     constexpr int PIECES = RW / 8;                             // of two-byte elements; a power of two, as is the number of four-byte ones
@@ -535,7 +538,7 @@ template <int K, int NT, int WR, bool BF16> static int launch_form(const Args &a
     }
     const int tiles = tiles_of(Shape{NT, WR, 0.f, {0.f, 0.f}}, a.out, a.T);
     hipLaunchKernelGGL((gemm_kernel<K, NT, WR, BF16>), dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(WAVES * 64), lds, stream,
-                       a.bits, a.h, a.X, a.g, a.Y, a.out, a.in, a.T, a.out_dtype);
+                       address_of(a.bits), address_of(a.h), address_of(a.X), address_of(a.g), address_of(a.Y), a.out, a.in, a.T, a.out_dtype);
     return RB_OK;
 }
 

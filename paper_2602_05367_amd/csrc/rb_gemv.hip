@@ -17,6 +17,7 @@
 #include <hip/hip_fp16.h>
 
 #include "rabit.h"
+#include "rb_device.h"
 #include "rb_internal.h"
 #include "rb_layout.h"
 #include "rb_mx.h"
@@ -38,10 +39,11 @@ constexpr int PART_FLOATS = MAXSLOT * CW * 2 * 16;   // [slot][wavefront][path][
 // is unconditional: a load inside a branch makes the wait for an earlier one a wait for all of them.
 // DEPTH: sign tiles requested before the first is used.
 template <int KEPT, int DEPTH>
-__global__ __launch_bounds__(THREADS, 1) void gemv1_kernel(const v4u *__restrict__ bits, const __half *__restrict__ g,
-                                                           const __half *__restrict__ h, const __half *__restrict__ x,
-                                                           __half *__restrict__ y, int out, int in, int groups)
+__global__ __launch_bounds__(THREADS, 1) void gemv1_kernel(Address bits_, Address g_, Address h_, Address x_, Address y_, int out, int in, int groups)
 {
+    const v4u *const __restrict__ bits = global_at<const v4u>(bits_);
+    const __half *const __restrict__ g = global_at<const __half>(g_), *const __restrict__ h = global_at<const __half>(h_), *const __restrict__ x = global_at<const __half>(x_);
+    __half *const __restrict__ y = global_at<__half>(y_);
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int n_up = (int)up_bytes(in, 1);
     uint8_t *const up = lds;
@@ -208,9 +210,8 @@ static int launch_form(const rb_layer *L, const void *x, void *y, hipStream_t st
             return RB_ERR_HIP;
         allowed[dev] = true;
     }
-    hipLaunchKernelGGL((gemv1_kernel<KEPT, DEPTH>), dim3(G), dim3(THREADS), lds, stream, static_cast<const v4u *>(L->bits),
-                       reinterpret_cast<const __half *>(L->g), reinterpret_cast<const __half *>(L->h),
-                       static_cast<const __half *>(x), static_cast<__half *>(y), L->out, L->in, G);
+    hipLaunchKernelGGL((gemv1_kernel<KEPT, DEPTH>), dim3(G), dim3(THREADS), lds, stream, address_of(L->bits), address_of(L->g), address_of(L->h), address_of(x), address_of(y),
+                       L->out, L->in, G);
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;
 }
 
