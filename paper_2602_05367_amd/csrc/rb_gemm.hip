@@ -5,7 +5,7 @@
 // W_hat = sum_k g_k (.) B_k (.) h_k (Alg. 2, "compute layer output") on v_mfma_f32_32x32x16_f16.  The left
 // operand is W_hat itself, built in registers from the packed signs on the way to the matrix
 // instruction and never stored.  Per pair of fp16 elements: a 64-bit shift brings the two sign bits of two paths
-// to bits 15 and 31 of their words (a shift per path before: 4096 x 4096 at 333 tokens 29.7 us, 28.5 now, three paths 28672 x 8192 at 512 288 and
+// to bits 15 and 31 of their words (with a shift per path 4096 x 4096 at 333 tokens took 29.7 us where this took 28.5, three paths 28672 x 8192 at 512 288 and
 // 276), one three-input logic operation per path puts them on the pair of h_k.  Two forms add the paths up:
 //   * h_0 B_0 + rho_k h_k B_k with rho_k = g_k / g_0 in fp16 and g_0 on the fp32 sums at the end, a packed fused multiply-add per
 //     path but the first: four vector instructions for two paths, one rounding of the sum and one of rho_k.  Taken by a workgroup in all of
@@ -36,8 +36,8 @@
 //   * the tile is brought to the output's type in LDS and stored as whole rows;
 //   * the left operand of the next row block is built between the matrix instructions of this one.
 //
-// Measured, fp16, two paths, first form, calls in a row in a graph: 4096 x 4096 at 333 tokens 28-30 us, 11008 x 4096 50-53 us,
-// 4096 x 11008 57-59 us, 8192 x 8192 at 1024 138 us (1.0 PFLOP/s), 28672 x 8192 at 2048 tokens 0.91-0.94 ms, where the power that the
+// Measured, fp16, two paths, first form, calls in a row in a graph: 4096 x 4096 at 333 tokens 23-26 us, 11008 x 4096 45-46 us,
+// 4096 x 11008 54-56 us, 8192 x 8192 at 1024 134-139 us (1.0 PFLOP/s), 28672 x 8192 at 2048 tokens 0.93-0.94 ms, where the power that the
 // matrix units may draw is the bound: the same call on activations of zero takes 0.71 ms (torch's product of fp16 matrices 0.82 and 0.66).
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
