@@ -56,8 +56,9 @@ bool single_gemm_applies(const rb_layer *L, int T)
 }
 
 // Few rows and tokens leave most compute units without a tile of the many-token kernel: there 64 tokens per workgroup on the few-token
-// kernel are faster (us: 2048 x 2048 at 128 tokens 15.7 and 10.3, 4096 x 11008 at 128 50.7 and 36.8, 512 x 8192 at 512 38.6 and 24.4;
-// 11008 x 4096 at 128 30.3 and 36.9)
+// kernel are faster (us: 2048 x 2048 at 128 tokens 11.3 and 7.3, 4096 x 11008 at 128 41.0 and 30.5, 512 x 8192 at 512 31.1 and 19.1;
+// 11008 x 4096 at 128 23.1, where the few-token kernel took 36.9 in a form with a shift per sign word).  The estimates are those of earlier forms of
+// both kernels: with 1.7 us less for the many-token kernel, which it has become faster by, three of sixty sizes were 4 to 10 % slower, one 2 % faster
 int launch_many(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace, size_t workspace_bytes, hipStream_t stream)
 {
     if (batch::blocks_cost(L, T, act_dtype) < gemm::cost(L, T)) return batch::launch_call(L, X, Y, T, act_dtype, out_dtype, workspace, workspace_bytes, stream);
