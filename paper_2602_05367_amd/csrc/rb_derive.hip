@@ -334,16 +334,27 @@ __global__ __launch_bounds__(ONE_PASS_THREADS, 2) void one_pass_kernel(Problem<J
     const int r0 = (int)((long long)p.out * blockIdx.x / gridDim.x), r1 = (int)((long long)p.out * (blockIdx.x + 1) / gridDim.x);
     struct Row { RowPiece<J> piece[CG]; double factor, g[J + 1]; } row;
     const Scalars before = *st.sc;                             // (looked at when the first loads are on their way)
-    // (buffer loads: columns past the last one read as zero, and one register holds the thread's place in every group)
+    // (buffer loads: columns past the last one read as zero, and one register holds the thread's place in every group.  A scalar offset
+    // beside it is no part of the check, so only groups that the row fills have one; the last two, which it may not, are buffers of their own)
+    auto buffer = [](const void *row, int bytes, int at) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(static_cast<const uint8_t *>(row)) + min(at, bytes), 0, max(bytes - at, 0), 0x00020000);
+    };
     auto fetch_row = [&](int r) {
-        const __amdgpu_buffer_rsrc_t w_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p.W + (size_t)r * in), 0, in * 4, 0x00020000);
+        auto each_group = [&](const void *row, int bytes, int group_bytes, auto load) {
+            const __amdgpu_buffer_rsrc_t filled = buffer(row, bytes, 0);
 #pragma unroll
-        for (int k = 0; k < CG; ++k) row.piece[k].w = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(w_rs, tid * 16, k * GROUP_COLS * 4, 0));
+            for (int k = 0; k < CG - 2; ++k) load(k, filled, k * group_bytes);
+#pragma unroll
+            for (int k = CG - 2; k < CG; ++k) load(k, buffer(row, bytes, k * group_bytes), 0);
+        };
+        each_group(p.W + (size_t)r * in, in * 4, GROUP_COLS * 4, [&](int k, __amdgpu_buffer_rsrc_t rs, int at) {
+            row.piece[k].w = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, tid * 16, at, 0));
+        });
 #pragma unroll
         for (int j = 0; j < J; ++j) {
-            const __amdgpu_buffer_rsrc_t b_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.packed[j] + (size_t)r * W32), 0, W32 * 4, 0x00020000);
-#pragma unroll
-            for (int k = 0; k < CG; ++k) row.piece[k].bits[j] = __builtin_amdgcn_raw_buffer_load_b32(b_rs, tid / 8 * 4, k * (GROUP_COLS / 32) * 4, 0);
+            each_group(p.packed[j] + (size_t)r * W32, W32 * 4, GROUP_COLS / 8, [&](int k, __amdgpu_buffer_rsrc_t rs, int at) {
+                row.piece[k].bits[j] = __builtin_amdgcn_raw_buffer_load_b32(rs, tid / 8 * 4, at, 0);
+            });
             row.g[j] = p.g[j][r];
         }
         row.factor = p.rows ? p.rows[r] : 1.0;

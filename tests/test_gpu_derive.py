@@ -204,6 +204,37 @@ def test_both_passes_in_one_reading(K, out, inn, calibrated, slow):
     np.testing.assert_allclose(ed.cpu().numpy(), err_d, rtol=1e-12)
 
 
+@pytest.mark.parametrize("K,inn", [(1, 4128), (2, 2080), (2, 8224), (2, 10272), (3, 4128), (3, 8288)])
+def test_nothing_beside_the_weight_is_read(K, inn):
+    """Groups of 2048 columns that a row fills in part, or not at all (4128, 8224 and 8288 columns: three and five groups' worth in forms
+    of four and six): after the weight, the factors and the results lie NaN, as far as the widest form goes, and change nothing."""
+    out, beside = 1024, 12288
+    W = torch.from_numpy(synth.gaussian_weight(synth.child_rng(7, 710, K, inn), out, inn, std=0.02).astype(np.float32))
+    rows, cols = torch.linspace(0.5, 1.0, out, dtype=torch.float64), torch.linspace(0.5, 1.0, inn, dtype=torch.float64)
+
+    def call(fill):
+        sizes = {torch.float32: [W.numel()], torch.float64: [out, inn, K * out, K * inn, 2 * K], torch.int32: [K * out * (inn // 32)]}
+        held = [torch.full((n + beside,), fill, dtype=t, device="cuda") if t.is_floating_point else torch.full((n + beside,), -1, dtype=t, device="cuda")
+                for t, ns in sizes.items() for n in ns]
+        Wd, rd, cd, g, h, err, packed = held
+        for to, v in ((Wd, W.reshape(-1)), (rd, rows), (cd, cols)):
+            to[:v.numel()] = v.cuda()
+        need = rb.lib.rb_derive_workspace_bytes(out, inn)
+        ws = torch.full((need,), 255, dtype=torch.uint8, device="cuda")
+        print(f"derive K={K} {out}x{inn} beside {fill}", flush=True)
+        rc = rb.lib.rb_derive_iterative(Wd.data_ptr(), rd.data_ptr(), cd.data_ptr(), K, 2, out, inn, packed.data_ptr(), g.data_ptr(), h.data_ptr(),
+                                        err.data_ptr(), ws.data_ptr(), need, None)
+        torch.cuda.synchronize()
+        assert rc == rb.RB_OK
+        for t, n in ((g, K * out), (h, K * inn), (err, 2 * K)):
+            assert torch.isfinite(t[:n]).all() and (torch.isnan(t[n:]).all() if fill != fill else not t[n:].any())
+        assert (packed[K * out * (inn // 32):] == -1).all()
+        return [t[:n].cpu() for t, n in ((packed, K * out * (inn // 32)), (g, K * out), (h, K * inn), (err, 2 * K))]
+
+    for a, b in zip(call(0.0), call(float("nan"))):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("K,out,inn,noise", [(1, 300, 1056, 0.14), (1, 1024, 2048, 0.14), (2, 300, 544, 0.3), (3, 70, 4128, 1.0)])
 def test_error_of_the_last_update_term_by_term(K, out, inn, noise):
     """The last entry of err against the residual of the returned paths, term by term in extended precision, where
