@@ -411,6 +411,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void gemm_kernel(Address bits_, Addr
     // of it and hands the others theirs, so all wavefronts write, read and (below) convert (the upper half handing everything to the lower, twice with four
     // groups: 4096 x 4096 at 333 tokens 25.0 us)
     constexpr int PIECES_ALL = MB * NT * 4, SHARE = PIECES_ALL / WK;
+    static_assert(WK == 2 || WK == 4, "`sum` below adds two or four");
     static_assert(PIECES_ALL % WK == 0 && (WK - 1) * WR * PIECES_ALL * 1024 <= lds_bytes<K, NT, WR>(), "equal shares, room for them");
     float4 *const part = reinterpret_cast<float4 *>(lds);
     auto piece = [&](int f) { return acc[f / (NT * 4)][f / 4 % NT]; };
