@@ -68,16 +68,19 @@ def test_one_sweep_is_the_greedy_pass():
     assert abs(frac[0] - (1 - 2 / np.pi)) < 0.01 and abs(frac[1] - 0.130) < 0.01 and abs(frac[2] - 0.058) < 0.01
 
 
-def test_degenerate_weights():
+# (two passes per iteration; one reading of W; three paths of more columns than the pass after the iteration takes)
+@pytest.mark.parametrize("K,zero,out,inn", [(2, (20, 64), 48, 96), (2, (1024, 2080), 1030, 4128), (3, (1024, 8224), 1024, 8224)])
+def test_degenerate_weights(K, zero, out, inn):
     # all zero: no scale, every sign +1
-    packed, g, h, err = _run(np.zeros((20, 64), dtype=np.float32), 2, 2)
+    print(f"derive K={K} of zeros {zero}, of one path {out}x{inn}", flush=True)
+    packed, g, h, err = _run(np.zeros(zero, dtype=np.float32), K, 2)
     assert not packed.any() and not g.any() and not h.any() and not err.any()
     # a weight that is one path exactly: found in the first update, nothing left for the second
     rng = synth.child_rng(7, 702)
-    B = synth.uniform_signs(rng, 1, 48, 96)[0].astype(np.float64)
-    g0, h0 = np.abs(rng.standard_normal(48)) + 0.5, np.abs(rng.standard_normal(96)) + 0.5
+    B = synth.uniform_signs(rng, 1, out, inn)[0].astype(np.float64)
+    g0, h0 = np.abs(rng.standard_normal(out)) + 0.5, np.abs(rng.standard_normal(inn)) + 0.5
     W = (g0[:, None] * B * h0[None, :]).astype(np.float32)
-    packed, g, h, err = _run(W, 2, 1)
+    packed, g, h, err = _run(W, K, 1)
     assert np.array_equal(packed[0], oracle.pack(B[None].astype(np.int8))[0])
     np.testing.assert_allclose(g[0][:, None] * h[0][None, :], np.abs(W.astype(np.float64)), rtol=1e-6)
     assert err[0, 0] <= 1e-6 * np.linalg.norm(W) and err[0, 1] <= err[0, 0]
@@ -165,6 +168,7 @@ def test_slices_of_the_column_pass_and_their_workspace(K, out, inn, slices_of):
     # not share evenly, groups that end inside a workgroup
     (1, 1024, 2048, True, False), (2, 1030, 4096, False, False), (2, 1025, 4128, True, False), (3, 1024, 6176, True, False),
     (2, 1100, 8224, True, False), (1, 1027, 12288, False, False), (3, 1024, 8288, False, False),
+    (1, 1024, 4160, True, False), (3, 1027, 2080, True, False),
     # many more iterations than the host enqueues before it looks: it looks, and goes on, after each
     (1, 1026, 2080, False, True), (2, 1024, 4128, True, True)])
 def test_both_passes_in_one_reading(K, out, inn, calibrated, slow):
@@ -255,7 +259,8 @@ def test_error_of_the_last_update_term_by_term(K, out, inn, noise):
     assert abs(err[-1, -1] / want - 1) <= 1e-15
 
 
-@pytest.mark.parametrize("K,out,inn,power", [(2, 70, 1056, -200), (2, 70, 1056, 200), (3, 300, 544, -230), (1, 1024, 2080, 230)])
+@pytest.mark.parametrize("K,out,inn,power", [(2, 70, 1056, -200), (2, 70, 1056, 200), (3, 300, 544, -230), (1, 1024, 2080, 230),
+                                             (2, 1024, 4128, -200), (3, 1024, 2080, 200)])
 def test_preconditioned_weights_of_any_size(K, out, inn, power):
     """Factors that are powers of two change nothing but the exponents, whatever their size: the same signs and, back in the
     original domain, the same scales, bit for bit, and errors that are the factors times as large."""
