@@ -470,6 +470,9 @@ constexpr int ROW_TILES_PER_WG[] = {1, 2, 3, 4, 5, 6, 7};
 // wavefront 0.7 + 0.1 P G, for the sums 0.5 P G / wavefronts.  (us by the rule above and by this one: 28672 x 512 at 33 tokens 16.9 and 10.9;
 // three paths, 28672 x 1024 at 24 21.2 and 16.6, 5000 x 32 at 64 11.3 and 7.2.  Of the forms measured for 32 to 1024 columns at 9, 24 and 48
 // tokens it picks one that is 1 % slower than the best in the mean.)
+// Five to seven row tiles of three paths are no part of that: each row tile more costs such a workgroup 0.6 to 1.1 us, not the 0.1 to 0.2 per unit
+// that the rule counts (2048 x 640 at 5 tokens, one to seven: 3.1 4.0 4.9 5.4 6.2 7.2 8.2; 28672 x 704 at 6 with seven 8.5, with the two chosen
+// without them 6.6; of 48 sizes at which it chose them three were 6 to 14 % faster with them, most 5 to 25 % slower).
 constexpr int NARROW_UNITS = 8;
 struct Form { int P, nw; double cost; };
 static Form form_of(const int *RT, int nops, int units, int K, int G, int blocks, bool bf16)
@@ -487,7 +490,7 @@ static Form form_of(const int *RT, int nops, int units, int K, int G, int blocks
         if (units > NARROW_UNITS) {
             const double cost = each * (P + 0.6) + (each + at_once - 1) / at_once * 33.0 / CT;
             if (best.P == 0 || cost < best.cost) best = {P, sixteen_available(K, G, P) && each <= 1 && (P == 1 || units >= (bf16 ? 32 : 40)) ? 16 : 8, cost};
-        } else {
+        } else if (P * K <= 12) {
             for (int nw = 1; nw < 2 * units; nw *= 2) {
                 const int waves = std::min(nw, units);
                 const int resident = std::max(1, std::min(8 * at_once / waves, LDS_BYTES / (waves * wave_bytes(K, G, P, bf16) + P * K * TILE_ROWS * 4)));
