@@ -7,19 +7,20 @@
 // their products, and only fp32 sums round; the activation is shared by the paths, nothing about the
 // input is prepared, and an op is one launch.  bfloat16 activations keep their whole range: they go into
 // v_mfma_f32_16x16x32_bf16 as they are, against two left operands, as an fp16 scale is the exact sum of two bf16
-// values (three vector instructions in place of two and twice the matrix instructions).  Up to 16 tokens only
+// values (five vector instructions per four weights and path in place of three and twice the matrix instructions).  Up to 16 tokens only
 // where it must be: 128 columns whose values fp16 holds exactly (zeros, 2^-17 up to 65536, which is nearly all there is) are
-// multiplied as fp16, the others after them (28672 x 8192 at 5 tokens of bfloat16 28 to 33 us from card to card, of fp16 29; in an earlier
+// multiplied as fp16, the others after them (28672 x 8192 at 5 tokens of bfloat16 27 to 28 us, of fp16 24 to 26; in an earlier
 // form of this kernel 34, 47 with two operands throughout, 33 with unchecked fp16 copies).  What bounds it:
 //   * a launch of a 4096-wide op moves 4 MB of signs, half a microsecond of HBM time, so it is a
 //     chain of latencies (launch, one trip to memory, the matrix instructions, the sum over the
 //     wavefronts): the compute units are filled and every wavefront asks for all it needs at once, the
 //     output scales of the end included;
 //   * the address unit, if activations are fetched in operand order (32 lines a load instruction: 11008
-//     columns for one row tile took 14.6 us, the transposition through LDS below takes 11);
+//     columns for one row tile took 14.6 us where the transposition through LDS below took 11, 9.1 now);
 //   * beyond that, vector instructions: three per four weights and path (a 64-bit shift for two words and a three-input logic
 //     operation for two weights).  A matrix instruction of 512 weights takes 6.7 ns of a SIMD, with the six of its left operand 14.5, of which
-//     16 to 17 are reached here; with a shift for each word, as before, 16.9 (28672 x 8192 at 16 tokens 27.6 us then, 25.8 now).
+//     16 to 17 are reached here; with a shift for each word 16.9 (28672 x 8192 at 16 tokens 27.6 us then and 25.8 so on one card; so 26 to 28 from
+//     card to card).
 //   * the number of load instructions: one that fetches nothing (past the end, or a second unit asked for ahead of
 //     time) takes its turn in the address unit all the same, and asking two units ahead made every launch slower (7B chain
 //     at 16 tokens 1.47 ms).
@@ -34,8 +35,8 @@
 // waits coarse and took up to 60 registers more, one workgroup per compute unit): 7B-shaped dependent chain, 128 launches, 1.26 to 1.28 ms
 // at 16 tokens (1.37); 13B-shaped, three paths, 32 launches, 6 tokens 0.49 to 0.52 ms (0.62).  Of a launch 1.4 us pass
 // between the last wavefront of one and the first of the next, and 1.2 until the first activations are there.  Single calls
-// in a graph: 28672 x 8192 at 16 tokens 28.5 us (33.5), 10999 x 4128 at 4 9.0 (9.9), 4096 x 4096 at 4 5.2 (5.5), 11008 x 4096 at 48
-// 16.8 (28.9), three paths 13824 x 5120 at 48 34.4 (53.8).
+// in a graph: 28672 x 8192 at 16 tokens 26 to 28 us (33.5), 10999 x 4128 at 4 7.2 to 7.9 (9.9), 4096 x 4096 at 4 4.5 to 4.8 (5.5), 11008 x 4096 at 48
+// 16.3 to 16.9 (28.9), three paths 13824 x 5120 at 48 33.6 to 35.3 (53.8).
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
@@ -69,16 +70,16 @@ constexpr int MAX_STAGE_OPS = 8;       // independent ops that share a launch
 constexpr int LDS_BYTES = 160 * 1024;  // of a compute unit
 
 // The forms of a workgroup.  Row tiles: as many as fit without spilling (accumulators take 4 P K G registers, sign words 2 P K, staged
-// activations 16 G); with four token groups three for two paths and two for three (11008 x 4096 at 64 tokens 18.9 us, 26.5
-// with two; 13824 x 5120, three paths, 39.0 and 54.5 with one), but not for bfloat16, whose two left operands would spill
-// 64 registers (28672 x 8192: 192 us, 125 with two).  Wavefronts: eight, of which two workgroups share a compute unit where 128
+// activations 16 G); with four token groups three for two paths and two for three (with a shift per sign word 11008 x 4096 at 64 tokens 18.9 us,
+// 26.5 with two; 13824 x 5120, three paths, 39.0 and 54.5 with one; now 17.5 and 37), but not for bfloat16, whose two left operands would spill
+// 64 registers (28672 x 8192: 192 us, 124 with two).  Wavefronts: eight, of which two workgroups share a compute unit where 128
 // registers are enough, so that one multiplies while the other waits for memory and more workgroups than compute units
-// still run at once (28672 x 8192 at 16 tokens: 448 workgroups of four row tiles 28.9 us, with sixteen wavefronts each, in two
-// rounds, 32.2); three paths go up to seven row tiles, so that a launch needs one round more often (28672 x 8192 at 16 tokens 38.5 us with four
-// in two rounds, 33.0 with seven in one; gate and up of 13824 x 5120 at 6 26.5, 22.5; for two paths, of which two workgroups of four run at
+// still run at once (28672 x 8192 at 16 tokens: 448 workgroups of four row tiles 26.4 us, with sixteen wavefronts each, in two
+// rounds, 29.9); three paths go up to seven row tiles, so that a launch needs one round more often (28672 x 8192 at 16 tokens 38.6 us with four
+// in two rounds, 32.7 with seven in one; gate and up of 13824 x 5120 at 6 26.5, 22.5; for two paths, of which two workgroups of four run at
 // once, 25.6 and 26.2); sixteen, where 128 registers are enough for them, in a launch that has no second workgroup for a compute unit, from 5120
-// columns on (4096 of bfloat16) for two row tiles and more (time of sixteen over that of eight, 1 to 16 tokens: one row tile 4128 columns
-// 0.98, 11008 0.88; two to four 2080 1.06, 4128 1.02, 0.98 to 1.02 of bfloat16, 6144 0.97, 8192 0.95, 11008 0.93).
+// columns on (4096 of bfloat16) for two row tiles and more (time of sixteen over that of eight, 9 tokens: one row tile 4128 columns
+// 1.00, 11008 0.87; two and three 2080 1.09, 4128 1.01 to 1.04, 1.00 of bfloat16, 6144 0.99, 8192 0.96, 11008 0.98).
 __host__ __device__ constexpr bool p_available(int K, int G, int P, bool bf16)
 {
     if (P == 1) return true;
@@ -99,7 +100,7 @@ struct alignas(64) Op {
     const uint16_t *g;        // fp16 [K][out]
     void *y;                  // [T][out]
     int out, in;
-    uint32_t tokens;          // T, element type of y << 16
+    uint32_t tokens;          // T (every entry point turns down more than 65535), element type of y << 16
     uint32_t cut;             // wavefronts of a workgroup, `rest` << 5, `run` << 9: each takes `run` units, the first `rest` one more
     __host__ __device__ int T() const { return (int)(tokens & 0xffffu); }
     __host__ __device__ int out_dtype() const { return (int)(tokens >> 16); }
@@ -463,16 +464,18 @@ constexpr int ROW_TILES_PER_WG[] = {1, 2, 3, 4, 5, 6, 7};
 // Row tiles per workgroup and its wavefronts.  Beyond NARROW_UNITS of 128 columns: eight wavefronts, row tiles by what the busiest compute
 // unit takes, `each` workgroups in rounds of the one or two that run at once.  In units of a row tile's work (0.1 us per column tile) a workgroup
 // costs 0.6 more (its activations, the sum) and a round 33 / column tiles (3.3 us: the latencies).  (16 tokens, two paths, us for 1, 2, 3, 4, 6
-// row tiles: 12288 x 4096 10.9 10.6 9.1 10.1 12.8; 22016 x 4096 18.3 14.5 13.5 16.4 12.9; 28672 x 8192 39.4 32.6 32.7 28.9 41.5.)  Sixteen
-// wavefronts: see above.
+// row tiles: 12288 x 4096 9.7 9.2 7.8 8.6 11.6; 22016 x 4096 17.6 13.2 11.8 14.7 11.8; 28672 x 8192 39.3 30.8 30.1 26.3 37.9.)  The constants are
+// those of a form with a shift per sign word; of 48 three-path layers of 1056 to 10528 columns they still pick one within 3 % of the best in 46 (22016 x
+// 3616 at 2 tokens 14.5 us, with two row tiles 13.5).  Sixteen wavefronts: see above.
 // Narrower layers leave room for several small workgroups on a compute unit, whose latencies then overlap, and what a workgroup pays for
 // its sums is shared by fewer wavefronts.  Microseconds of a round of them, for P row tiles and G token groups: 1.5, per unit of a
-// wavefront 0.7 + 0.1 P G, for the sums 0.5 P G / wavefronts.  (us by the rule above and by this one: 28672 x 512 at 33 tokens 16.9 and 10.9;
-// three paths, 28672 x 1024 at 24 21.2 and 16.6, 5000 x 32 at 64 11.3 and 7.2.  Of the forms measured for 32 to 1024 columns at 9, 24 and 48
-// tokens it picks one that is 1 % slower than the best in the mean.)
+// wavefront 0.7 + 0.1 P G, for the sums 0.5 P G / wavefronts.  (us by the rule above and by this one, with a shift per sign word: 28672 x 512
+// at 33 tokens 16.9 and 10.9, by this one now 10.3; three paths, 28672 x 1024 at 24 21.2 and 16.6, now 11.6, 5000 x 32 at 64 11.3 and 7.2, now 6.7.
+// Of the forms measured for 32 to 1024 columns at 9, 24 and 48 tokens it picked one that was 1 % slower than the best in the mean; now, 108
+// three-path layers at 1 to 16 tokens, 3 %, 18 % at most.)
 // Five to seven row tiles of three paths are no part of that: each row tile more costs such a workgroup 0.6 to 1.1 us, not the 0.1 to 0.2 per unit
 // that the rule counts (2048 x 640 at 5 tokens, one to seven: 3.1 4.0 4.9 5.4 6.2 7.2 8.2; 28672 x 704 at 6 with seven 8.5, with the two chosen
-// without them 6.6; of 48 sizes at which it chose them three were 6 to 14 % faster with them, most 5 to 25 % slower).
+// without them 6.6; of 48 sizes at which it chose them four were 9 to 14 % faster with them, most 5 to 28 % slower).
 constexpr int NARROW_UNITS = 8;
 struct Form { int P, nw; double cost; };
 static Form form_of(const int *RT, int nops, int units, int K, int G, int blocks, bool bf16)
@@ -610,7 +613,8 @@ bool call_sized(const rb_layer *L, int T) { return sized(L, T, CALL_MAX_T); }
 // More than CALL_MAX_T tokens: 64 of them per workgroup, where the workgroups of a call do not outnumber the compute units (in a second
 // round the many-token kernel is always the faster one).  Microseconds, launch included: 6.5 and so much per column tile, measured on
 // layers of 800 to 11008 columns; or 6.5 and the time in which the workgroups of different rows, on eight dies with caches of their own, fetch
-// the activations, 6.2 TB/s (300 rows at 2000 tokens: 2048 columns 17.4 us, 28672 columns 124; the many-token kernel 15.2 and 111)
+// the activations, 6.2 TB/s (300 rows at 2000 tokens: 2048 columns 16.4 us, 28672 columns 123; the many-token kernel 12.4 and 101).  The
+// constants are those of a form with a shift per sign word: estimates are 1.1 to 1.4 times what it takes now (launch_many has the choice that results)
 float blocks_cost(const rb_layer *L, int T, int act_dtype)
 {
     static constexpr float per_tile[2][2][3] = {{{0.46f, 0.69f, 0.8f}, {0.57f, 0.95f, 0.f}}, {{0.5f, 0.85f, 0.f}, {0.67f, 0.f, 0.f}}};

@@ -15,8 +15,8 @@ constexpr int FUSED_MAX_T = 4;         // tokens of the fused decode kernel
 
 // Which stacks take the few-token kernel: every stack with a three-path layer, and two-path stacks
 // of more tokens than the fused decode kernel takes.  (7B-shaped dependent chain at three and four tokens: one launch of the fused
-// kernel 1.25 ms, 128 of the few-token kernel 1.18 and 1.19; with the forms of the latter from which this line was drawn 1.40.  At
-// five tokens two passes of the fused kernel would take 1.87 ms, the few-token kernel 1.21.  The line stays: results of three and four
+// kernel 1.24 to 1.25 ms, 128 of the few-token kernel 1.09 to 1.11; with the forms of the latter from which this line was drawn 1.40.  At
+// five tokens two passes of the fused kernel would take 1.87 ms, the few-token kernel 1.11.  The line stays: results of three and four
 // tokens are the fused kernel's, which serves their decoder blocks too.)
 bool batch_applies(const rb_layer *layers, int n_layers, int T)
 {
@@ -33,7 +33,7 @@ bool batch_applies(const rb_layer *layers, int n_layers, int T)
 // Which single calls take the few-token kernel (one launch): three paths, and two paths beyond two tokens and whatever
 // element types the decode kernels do not take (one and two fp16 tokens with fp16 results stay there: the bits are those of
 // a stack).  Three paths at up to five tokens took the generic kernel once, which reads the weights for every token (us in a graph, there
-// and here: 4096 x 4096 at one token 10.9 and 6.2, at three 17.0 and 6.1, 4096 x 11008 at one 32.1 and 9.5, 28672 x 8192 at three 168 and 39).
+// and here: 4096 x 4096 at one token 10.9 and 5.2, at three 17.0 and 5.2, 4096 x 11008 at one 32.1 and 9.2, 28672 x 8192 at three 168 and 31).
 // They still ask for no scratch memory (so their output must not overlap their input) and report what they have always reported.
 constexpr int K3_ROOM_MIN_T = 6, K3_BATCH_MAX_T = 12;
 bool single_few_applies(const rb_layer *L, int T, int act_dtype, int out_dtype)
@@ -56,9 +56,10 @@ bool single_gemm_applies(const rb_layer *L, int T)
 }
 
 // Few rows and tokens leave most compute units without a tile of the many-token kernel: there 64 tokens per workgroup on the few-token
-// kernel are faster (us: 2048 x 2048 at 128 tokens 11.3 and 7.3, 4096 x 11008 at 128 41.0 and 30.5, 512 x 8192 at 512 31.1 and 19.1;
-// 11008 x 4096 at 128 23.1, where the few-token kernel took 36.9 in a form with a shift per sign word).  The estimates are those of earlier forms of
-// both kernels: with 1.7 us less for the many-token kernel, which it has become faster by, three of sixty sizes were 4 to 10 % slower, one 2 % faster
+// kernel are faster (us, many-token and few-token kernel: 2048 x 2048 at 128 tokens 11.5 and 7.7, 4096 x 11008 at 128 41 and 33, 512 x 8192 at 512 31 and
+// 20; on the other side of the line 300 x 2048 at 2000 12.4 and 16.5, 300 x 28672 at 2000 101 and 123).  The estimates are those of earlier forms of
+// both kernels, which have become faster alike: of 40 layers near the line 38 went to the faster one within 1.2 %, two to one that took a quarter more (1020 x 352 at 573
+// tokens 7.2 and 8.8, 5465 x 288 at 125 7.1 and 9.0); with 1.7 us less for the many-token kernel three of sixty were 4 to 10 % slower, one 2 % faster
 int launch_many(const rb_layer *L, const void *X, void *Y, int T, int act_dtype, int out_dtype, void *workspace, size_t workspace_bytes, hipStream_t stream)
 {
     if (batch::blocks_cost(L, T, act_dtype) < gemm::cost(L, T)) return batch::launch_call(L, X, Y, T, act_dtype, out_dtype, workspace, workspace_bytes, stream);

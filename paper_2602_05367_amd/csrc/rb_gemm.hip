@@ -36,9 +36,9 @@
 //   * the tile is brought to the output's type in LDS and stored as whole rows;
 //   * the left operand of the next row block is built between the matrix instructions of this one.
 //
-// Measured, fp16, two paths, first form, calls in a row in a graph: 4096 x 4096 at 333 tokens 23-26 us, 11008 x 4096 45-46 us,
-// 4096 x 11008 54-56 us, 8192 x 8192 at 1024 134-139 us (1.0 PFLOP/s), 28672 x 8192 at 2048 tokens 0.93-0.94 ms, where the power that the
-// matrix units may draw is the bound: the same call on activations of zero takes 0.71 ms (torch's product of fp16 matrices 0.82 and 0.66).
+// Measured, fp16, two paths, first form, calls in a row in a graph, from card to card and with cold clocks: 4096 x 4096 at 333 tokens 23-28 us,
+// 11008 x 4096 45-52 us, 4096 x 11008 54-63 us, 8192 x 8192 at 1024 134-145 us (1.0 PFLOP/s), 28672 x 8192 at 2048 tokens 0.92-0.97 ms (1.07 among
+// other work), where the power that the matrix units may draw is the bound: the same call on activations of zero takes 0.71 ms (torch's product of fp16 matrices 0.82 and 0.66).
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
@@ -495,9 +495,11 @@ __global__ __launch_bounds__(256) void align_kernel(const uint16_t *__restrict__
 // ------------------------------------------------------------------ host ---
 // The shapes of a workgroup, and what a round of the device takes with each, in microseconds: `fixed` (launch,
 // scales, first loads, sums, stores) and `step` per step of 128 columns per group, for two and for three paths.
-// Measured on layers of 256 to 11008 columns (4096 x 11008, 22 or 43 steps, against 4096 x 4096, 8 or 16); a
+// Measured on layers of 256 to 11008 columns (4096 x 11008, 22 or 43 steps, against 4096 x 4096, 8 or 16) with an earlier form of the
+// kernel, which now takes 0.7 to 1.25 of the estimate; but all five shapes became faster alike: timed on 50 random layers (256 to 28672 rows, 256 to
+// 8128 columns, 71 to 1894 tokens, two and three paths, both types) the one that is picked was the fastest on every one.  A
 // round costs the same whether it fills the device or not (11008 x 4096 at 333 tokens, two paths: 172 workgroups of
-// 256 x 96 55 us, 129 of 256 x 128 68, 258 of 256 x 64 86, 516 of 128 x 64 85), so the shape with the least sum is taken.
+// 256 x 96 47 us, 129 of 256 x 128 55, 258 of 256 x 64 76, 516 of 128 x 64 75), so the shape with the least sum is taken.
 struct Shape { int NT, WR; float fixed, step[2]; };
 constexpr Shape SHAPES[] = {{1, 2, 8.f, {1.8f, 2.5f}}, {2, 2, 10.5f, {2.3f, 2.95f}}, {2, 4, 10.f, {1.95f, 2.55f}},
                             {3, 4, 11.5f, {2.25f, 2.9f}}, {4, 4, 13.f, {2.85f, 3.4f}}};
