@@ -14,10 +14,8 @@ void set_last_path(int path) { g_last_path = path; }
 constexpr int FUSED_MAX_T = 4;         // tokens of the fused decode kernel
 
 // Which stacks take the few-token kernel: every stack with a three-path layer, and two-path stacks
-// of more tokens than the fused decode kernel takes.  (7B-shaped dependent chain at three and four tokens: one launch of the fused
-// kernel 1.24 to 1.25 ms, 128 of the few-token kernel 1.09 to 1.11; with the forms of the latter from which this line was drawn 1.40.  At
-// five tokens two passes of the fused kernel would take 1.87 ms, the few-token kernel 1.11.  The line stays: results of three and four
-// tokens are the fused kernel's, which serves their decoder blocks too.)
+// of more tokens than the fused decode kernels take.  (7B-shaped dependent chain at three and four tokens: one launch of the persistent
+// kernel 0.90 to 0.94 ms, 128 of the few-token kernel 1.09 to 1.11.  At five tokens two passes of the former would take 1.6 ms, the latter 1.11.)
 bool batch_applies(const rb_layer *layers, int n_layers, int T)
 {
     bool any_three = false, all_three = true;

@@ -629,3 +629,48 @@ def test_prepared_odd_batches_on_pure_chains(T, n_chain):
         ref = oracle.forward(*layers[n], got[n])
         err = float(oracle.relative_l2(got[n + 1].astype(np.float64), ref).max())
         assert np.all(np.isfinite(got[n + 1])) and err <= TOL, (n, err)
+
+
+@pytest.mark.parametrize("T", [3, 4])
+@pytest.mark.parametrize("shapes", [
+    # (out, in, source): buffer 0 is the first input; source -1: an input of its own
+    # one to three resident column tiles per wavefront, then a streamed run; a ragged end
+    [(2080, 32, 0), (6144, 2080, 1), (8192, 6144, 2), (300, 8192, 3)],
+    # eight row tiles per workgroup; a row of sign tiles longer than the ring that holds them
+    [(32768, 64, 0), (48, 32768, 1)],
+    # shares that end in another op, ops shorter than a share, an output with three readers
+    [(4112, 1056, 0), (544, 1056, 0), (16, 1056, 0), (9000, 1056, 0), (1056, 544, 2), (704, 4128, -1), (544, 1056, 5), (512, 1056, 5), (80, 1056, 5)],
+    # a stage of more tiles than the ring: seven row tiles of seventeen column tiles
+    [(4128, 64, 0), (28000, 4128, 1), (96, 28000, 2)],
+])
+def test_three_and_four_token_stack_forms(T, shapes):
+    """Every op against the oracle on the input it read, and a second run bit for bit the first."""
+    rng = synth.child_rng(3, 500, T, len(shapes))
+    layers, bufs, op_list = [], [synth.gaussian_activations(rng, T, shapes[0][1])], []
+    for out, inn, src in shapes:
+        layers.append(random_layer(rng, 2, out, inn, gain=1.0 / (0.02 * 0.02 * np.sqrt(inn))))
+        if src < 0:
+            src = len(bufs)
+            bufs.append(synth.gaussian_activations(rng, T, inn))
+        op_list.append((len(layers) - 1, src, len(bufs)))
+        bufs.append(np.zeros((T, out), np.float16))
+    dev_layers = [to_device_layer(*l) for l in layers]
+    dev = [torch.from_numpy(b).cuda() for b in bufs]
+    stack = rb.Stack(dev_layers, op_list, dev, T)
+    stack.prepare()
+    runs = []
+    for _ in range(2):
+        for _, _, dst in op_list:
+            dev[dst].fill_(7.0)
+        print(f"forms of the kernel for three and four tokens, {shapes}", flush=True)
+        stack.run_prepared()
+        torch.cuda.synchronize()
+        assert rb.rb_last_path() == rb.RB_PATH_MX and stack.status() == rb.RB_OK, f"gave up: reason {stack.gave_up()}"
+        runs.append([b.clone() for b in dev])
+    stack.forget()
+    for a, b in zip(*runs):
+        assert torch.equal(a, b)
+    for n, src, dst in op_list:
+        ref = oracle.forward(*layers[n], dev[src].cpu().numpy())
+        got = dev[dst].cpu().numpy().astype(np.float64)
+        assert oracle.relative_l2(got, ref).max() <= TOL, (n, shapes[n])
