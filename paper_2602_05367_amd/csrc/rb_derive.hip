@@ -19,11 +19,12 @@
 // signs of R_i.  The error after an update, term by term (as ||R_i||^2 - sigma^2 it would come out of the same pass, but with
 // a digit less: 3.6e-15 off where the terms are 1e-16), is found by the pass after the iteration while it holds a row of R, or, by two passes, by
 // the first pass of the next update on the way: its R less the path that it leaves out.  Every sum has a fixed order.  The
-// iteration's stopping rule is evaluated on the device; the host reads one flag per update when it expects the
-// iteration to have finished, so the call synchronises.
+// iteration's stopping rule is evaluated on the device.  Where one reading serves both passes, the device goes on to the next update by itself and the host
+// looks a few times in all how far it has come; else it reads a flag per update when it expects the iteration to have finished.  So the call synchronises.
 //
-// Measured, 4096 x 11008, two paths, five sweeps (ten updates of four iterations): 2.7 to 2.8 ms (3.1 to 3.2 with launches of their own for b and for the errors; 3.9 with
-// two passes in every iteration; 5.1 before those): an iteration is one pass of 38 to 42 us and 5.5 for the sums, the pass after it 45 to 47 (by rows, without the errors, 35).
+// Measured, 4096 x 11008, two paths, five sweeps (ten updates of four iterations): 2.3 to 2.45 ms (2.6 to 2.8 with a look at the flag after every update and launches of its
+// start and end; 3.1 to 3.2 with launches of their own for b and for the errors; 3.9 with
+// two passes in every iteration; 5.1 before those): an iteration is one pass of 40 to 42 us and 5.7 for the sums, the pass after it 45 to 47 (by rows, without the errors, 35).
 // By two passes: 31 us each, the sums and the normalisation 12.  180 MB of W in
 // 31 us are 5.8 TB/s, what a plain read of as much out of the memory-side cache reaches (6.0); of the 42 us some 7 are b and the
 // columns' values at the start and 3 the 22 MB of sums at the end.
@@ -31,6 +32,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "rabit.h"
 #include "rb_device.h"
@@ -60,9 +62,11 @@ struct Scalars {
     double sigma;       // the iteration's current estimate
     double na;          // norm of |R| b
     double db;          // norm of the last change of b
-    int done;           // the stopping rule held (or the matrix is zero)
+    int done;           // the stopping rule held (or the matrix is zero); WALKED: nothing is left to do
     int iters;
+    int t, i;           // the update that this belongs to (one_pass_kernel)
 };
+constexpr int WALKED = 2;
 
 // sum over the wavefront, in every lane (every lane must be active): data-parallel moves inside a row of 16 lanes, register swaps
 // beyond
@@ -306,28 +310,41 @@ __global__ __launch_bounds__(256, 4) void cols_kernel(Problem<J> p, const double
 // in LDS and b in registers), and partial[workgroup] = the sum of (|R[r][c]| - a[r] b[c])^2, the error after this update: what the
 // path leaves of R, while R is still there.  With that no pass after it has to find the error (a first pass by rows for it and one by columns
 // took 68 us where an iteration is one of 38; the pass over all paths at the end 34).
-// Before the rows, every workgroup does for itself what unit_kernel does (`fold`): b from the sums of the iteration before, its
-// change, the stopping rule, all from the same values in the same order, so all come to the same end.  The first workgroup writes down b and
-// the scalars, where nobody reads them meanwhile.  A launch of its own, of one workgroup, took 7 us of an iteration's 50.
+// WALKS: the device goes through the updates by itself.  Before the rows, every workgroup does for itself what unit_kernel does: b from the sums
+// of the iteration before, its change, the stopping rule, all from the same values in the same order, so all come to the same end and
+// all take the same next step: an iteration, LAST, the first iteration of the next update (after a LAST; b is the all-ones vector then) or, after
+// the last update, nothing.  The first workgroup writes down b and the scalars, where nobody reads them meanwhile.  So the host only has to
+// ask for enough passes.  With a look after each update (27 us in which nothing runs, and launches for its start and end) ten updates of
+// 4096 x 11008 took 2.70 ms and take 2.44 (without factors 2.60 and 2.22), 1024 x 2048 1.33 and 0.92, three paths 4096 x 8192 (nine updates)
+// 2.17 and 1.94, one sweep of 4096 x 11008 0.57 and 0.54.  The columns' values are asked for before b is worked out, and the sums' factor is
+// left to walk_sums_kernel: 2.46 to 2.44.
+// Of a pass of 44 us over 4096 x 11008, 1.66 us are a row in each workgroup (6.9 TB/s) and 17 what it does once: 5 for a launch that has nothing to do,
+// the rest the trip to memory for b and the sums, 48 divisions, the columns' values and the writing of its sums.  (A launch of its own for b, of one workgroup, took 7 us of an iteration's 50.)
 // Bound: the reading of W; a row of 11008 columns costs a SIMD about 0.7 us of double precision and 0.3 us for the sum over the
 // workgroup, and has 1.9 us in which 256 compute units read a row each.
+constexpr int SUMS_COLS = 64, SUMS_RUNS = 8;       // (see slices_kernel)
 constexpr int ONE_PASS_GROUPS = 256, ONE_PASS_THREADS = 512, GROUP_COLS = 4 * ONE_PASS_THREADS;
 template <int N> struct RowPiece {
     float4 w;
     uint32_t bits[N + 1];
 };
-// what an iteration starts from and, if it has sums to fold in, leaves for the next one
+// Not for three paths of more than 8192 columns: LAST would spill 52 registers
+// (169 us, where the pass by rows and a first iteration in two passes cost 66 more than an iteration; 4096 x 11008, three sweeps 4.10 and 3.42 ms)
+constexpr bool walks(int J, int CG) { return J < 2 || CG < 6; }
+// what a pass starts from and, where it walks, leaves for the next one
 struct Step {
     const double *b, *sum, *sum_sq;
     double *b_new;
     const Scalars *sc;
     Scalars *sc_new;
-    int n_sq, fold;                    // values of sum_sq; whether there are sums
+    int n_sq, T_max;                   // values of sum_sq; sweeps
 };
-template <int J, int CG, bool LAST>
-__global__ __launch_bounds__(ONE_PASS_THREADS, 2) void one_pass_kernel(Problem<J> p, Step st, double *partial, double *a, double *a_sq, uint32_t *signs)
+// p: WALKS: the first of the J + 1 paths, which lie one after the other; else the J paths to subtract
+template <int J, int CG>
+__global__ __launch_bounds__(ONE_PASS_THREADS, 2) void one_pass_kernel(Problem<J> p, uint32_t *packed, Step st, double *partial, double *a, double *a_sq)
 {
     constexpr int WAVES = ONE_PASS_THREADS / 64;
+    constexpr bool WALKS = walks(J, CG);
     extern __shared__ __attribute__((aligned(16))) double2 lds[];      // [CG][2][thread]: f b (LAST: f) of two columns, zero past the last column
     __shared__ double red[2][WAVES], red_group[WAVES];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, in = p.in, W32 = in / 32;
@@ -339,43 +356,95 @@ __global__ __launch_bounds__(ONE_PASS_THREADS, 2) void one_pass_kernel(Problem<J
     auto buffer = [](const void *row, int bytes, int at) {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(static_cast<const uint8_t *>(row)) + min(at, bytes), 0, max(bytes - at, 0), 0x00020000);
     };
-    auto fetch_row = [&](int r) {
-        auto each_group = [&](const void *row, int bytes, int group_bytes, auto load) {
-            const __amdgpu_buffer_rsrc_t filled = buffer(row, bytes, 0);
+    auto each_group = [&](const void *row, int bytes, int group_bytes, auto load) {
+        const __amdgpu_buffer_rsrc_t filled = buffer(row, bytes, 0);
 #pragma unroll
-            for (int k = 0; k < CG - 2; ++k) load(k, filled, k * group_bytes);
+        for (int k = 0; k < CG - 2; ++k) load(k, filled, k * group_bytes);
 #pragma unroll
-            for (int k = CG - 2; k < CG; ++k) load(k, buffer(row, bytes, k * group_bytes), 0);
-        };
-        each_group(p.W + (size_t)r * in, in * 4, GROUP_COLS * 4, [&](int k, __amdgpu_buffer_rsrc_t rs, int at) {
-            row.piece[k].w = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, tid * 16, at, 0));
-        });
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            each_group(p.packed[j] + (size_t)r * W32, W32 * 4, GROUP_COLS / 8, [&](int k, __amdgpu_buffer_rsrc_t rs, int at) {
-                row.piece[k].bits[j] = __builtin_amdgcn_raw_buffer_load_b32(rs, tid / 8 * 4, at, 0);
-            });
-            row.g[j] = p.g[j][r];
-        }
-        row.factor = p.rows ? p.rows[r] : 1.0;
+        for (int k = CG - 2; k < CG; ++k) load(k, buffer(row, bytes, k * group_bytes), 0);
     };
     auto column = [&](int k) { return k * GROUP_COLS + 4 * tid; };
     auto safe = [&](int c) { return c < in ? c : 0; };          // in % 32 == 0: all four columns exist or none
-    fetch_row(min(r0, p.out - 1));
+    auto fetch_weights = [&](int r) {
+        each_group(p.W + (size_t)r * in, in * 4, GROUP_COLS * 4, [&](int k, __amdgpu_buffer_rsrc_t rs, int at) {
+            row.piece[k].w = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, tid * 16, at, 0));
+        });
+    };
+    // WALKS: path j of those that the update subtracts is j or, from the one left out on, j + 1.  (Made scalars where they are used: with
+    // pointers worked out at the start the compiler had a loop over the lanes around each load of a buffer, and a pass took 7 us more)
+    struct Paths { int n[J + 1]; };
+    auto paths_without = [](int left_out) {
+        const int i = __builtin_amdgcn_readfirstlane(left_out);
+        Paths to;
+#pragma unroll
+        for (int j = 0; j < J; ++j) to.n[j] = WALKS ? j + (j >= i) : 0;
+        return to;
+    };
+    auto fetch_paths = [&](int r, const Paths &paths) {
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int from = WALKS ? 0 : j;
+            const size_t line = (size_t)paths.n[j] * p.out + r;
+            each_group(p.packed[from] + line * W32, W32 * 4, GROUP_COLS / 8, [&](int k, __amdgpu_buffer_rsrc_t rs, int at) {
+                row.piece[k].bits[j] = __builtin_amdgcn_raw_buffer_load_b32(rs, tid / 8 * 4, at, 0);
+            });
+            row.g[j] = p.g[from][line];
+        }
+        row.factor = p.rows ? p.rows[r] : 1.0;                 // (a branch: what comes after it is asked for after the row before has been waited for)
+    };
+    // what the pass shares of the columns.  WALKS: on its way while b is worked out (three paths of 12288 columns have no registers for that:
+    // 13 instead of 11 spill, 2048 x 11008 5 % slower)
+    Columns<J> cols[CG];
+    auto fetch_shared = [&](int k, const Paths &paths) {
+        const int c = safe(column(k));
+        cols[k].f[0] = cols[k].f[1] = cols[k].f[2] = cols[k].f[3] = 1.0;
+        if (p.cols) four(p.cols, c, cols[k].f);
+#pragma unroll
+        for (int j = 0; j < J; ++j) four(WALKS ? p.h[0] + (size_t)paths.n[j] * in : p.h[j], c, cols[k].h[j]);
+    };
+    int left_out = 0;
+    fetch_weights(min(r0, p.out - 1));
+    if (!WALKS) fetch_paths(min(r0, p.out - 1), Paths{});
     double b[CG][4];
 #pragma unroll
     for (int k = 0; k < CG; ++k) four(st.b, safe(column(k)), b[k]);
     bool done = before.done != 0;
-    if (st.fold) {
-        double sum[CG][4], sq = 0.0;
+    if (WALKS) {
+        static_assert(CG * GROUP_COLS / SUMS_COLS <= ONE_PASS_THREADS, "a thread takes one of the squares");
+        double sum[CG][4], sq = st.sum_sq[min(tid, st.n_sq - 1)];
 #pragma unroll
         for (int k = 0; k < CG; ++k) four(st.sum, safe(column(k)), sum[k]);
-        for (int i = tid; i < st.n_sq; i += ONE_PASS_THREADS) sq += st.sum_sq[i];
+        // which update, and the paths that it subtracts
         Scalars after = before;
-        if (!done && before.na == 0.0) {                       // |R| b = 0: b stays
+        const bool fresh = __builtin_amdgcn_readfirstlane(before.done) != 0;
+        int t = __builtin_amdgcn_readfirstlane(before.t), i = __builtin_amdgcn_readfirstlane(before.i);
+        if (fresh && ++i > J) {
+            i = 0;
+            ++t;
+        }
+        if (t >= st.T_max) {
+            after.done = WALKED;
+            after.t = t;
+            after.i = -1;
+            if (blockIdx.x == 0 && tid == 0) *st.sc_new = after;
+            return;
+        }
+        left_out = i;
+        fetch_paths(min(r0, p.out - 1), paths_without(i));
+#pragma unroll
+        for (int k = 0; k < CG; ++k) fetch_shared(k, paths_without(i));
+        if (fresh) {
+            after = Scalars{0.0, 0.0, 0.0, 0, 0, t, i};
+            done = false;
+            const double one = 1.0 / sqrt((double)in);
+#pragma unroll
+            for (int k = 0; k < CG; ++k)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) b[k][e] = one;
+        } else if (before.na == 0.0) {                         // |R| b = 0: b stays
             done = true;
-        } else if (!done) {
-            after.sigma = sqrt(group_sum(sq, red_group, WAVES));
+        } else {
+            after.sigma = sqrt(group_sum(tid < st.n_sq ? sq : 0.0, red_group, WAVES));
             double change = 0.0;
 #pragma unroll
             for (int k = 0; k < CG; ++k)
@@ -389,6 +458,7 @@ __global__ __launch_bounds__(ONE_PASS_THREADS, 2) void one_pass_kernel(Problem<J
             after.iters += 1;
             done = (fabs(after.sigma - before.sigma) <= TOL_SIGMA * after.sigma && after.db <= TOL_B) || after.iters >= MAX_ITER;
         }
+        done = __builtin_amdgcn_readfirstlane(done);           // (the same everywhere)
         after.done = done;
         if (blockIdx.x == 0) {
 #pragma unroll
@@ -399,111 +469,124 @@ __global__ __launch_bounds__(ONE_PASS_THREADS, 2) void one_pass_kernel(Problem<J
                 }
             if (tid == 0) *st.sc_new = after;
         }
+    } else if (done) {
+        return;
     }
-    if (LAST ? !done : done) return;
-    double h[CG][J + 1][4], sum[CG][4], squares = 0.0, error = 0.0;
-#pragma unroll
-    for (int k = 0; k < CG; ++k) {
-        const bool there = column(k) < in;
-        Columns<J> cols;
-        fetch_columns<J, J>(p, safe(column(k)), cols);
-        double kept[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            b[k][e] = there ? b[k][e] : 0.0;
-            kept[e] = LAST ? (there ? cols.f[e] : 0.0) : b[k][e] * fabs(cols.f[e]);
-#pragma unroll
-            for (int j = 0; j < J; ++j) {
-                if (LAST) h[k][j][e] = there ? cols.h[j][e] : 0.0;
-                else h[k][j][e] = cols.f[e] != 0.0 ? cols.h[j][e] / cols.f[e] : 0.0;
-            }
-            sum[k][e] = 0.0;
-        }
-        lds[2 * k * ONE_PASS_THREADS + tid] = make_double2(kept[0], kept[1]);
-        lds[(2 * k + 1) * ONE_PASS_THREADS + tid] = make_double2(kept[2], kept[3]);
-    }
-    // (a thread reads what it has written there)
-#pragma unroll 1
-    for (int r = r0; r < r1; ++r) {
-        double v[CG][4];
+    double squares = 0.0;
+    auto over_rows = [&](auto last) {
+        constexpr bool LAST = decltype(last)::value;
+        double h[CG][J + 1][4], sum[CG][4], error = 0.0;
+        uint32_t *const signs = packed + (size_t)__builtin_amdgcn_readfirstlane(left_out) * p.out * W32;
+        const Paths paths = paths_without(left_out);
 #pragma unroll
         for (int k = 0; k < CG; ++k) {
-            const float w[4] = {row.piece[k].w.x, row.piece[k].w.y, row.piece[k].w.z, row.piece[k].w.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[k][e] = row.factor * (double)w[e];
-            if (LAST) {
-                const double2 low = lds[2 * k * ONE_PASS_THREADS + tid], high = lds[(2 * k + 1) * ONE_PASS_THREADS + tid];
-                v[k][0] *= low.x; v[k][1] *= low.y; v[k][2] *= high.x; v[k][3] *= high.y;
-            }
-#pragma unroll
-            for (int j = 0; j < J; ++j) {
-                const uint32_t bits = row.piece[k].bits[j] >> (4 * (tid & 7));
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const unsigned long long flip = (unsigned long long)(bits << (31 - e) & 0x80000000u) << 32;
-                    v[k][e] -= __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, row.g[j]) ^ flip) * h[k][j][e];
-                }
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        fetch_row(min(r + 1, r1 - 1));
-        __builtin_amdgcn_sched_barrier(0);
-        double dot[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int k = 0; k < CG; ++k) {
-            double2 low, high;
-            if (LAST) {
-                low = make_double2(b[k][0], b[k][1]);
-                high = make_double2(b[k][2], b[k][3]);
-                // eight lanes hold the 32 columns of a word, four each
-                uint32_t four = 0;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) four |= !(v[k][e] >= 0.0) ? 1u << e : 0u;
-                const uint32_t word = or_over_8(four << (4 * (lane & 7)));
-                if ((lane & 7) == 0 && column(k) < in) signs[(size_t)r * W32 + (column(k) >> 5)] = word;
-            } else {
-                low = lds[2 * k * ONE_PASS_THREADS + tid];
-                high = lds[(2 * k + 1) * ONE_PASS_THREADS + tid];
-            }
-            dot[0] += fabs(v[k][0]) * low.x;
-            dot[1] += fabs(v[k][1]) * low.y;
-            dot[2] += fabs(v[k][2]) * high.x;
-            dot[3] += fabs(v[k][3]) * high.y;
-        }
-        const double d = over_wave((dot[0] + dot[1]) + (dot[2] + dot[3]));
-        if (lane == 0) red[r & 1][wave] = d;
-        __syncthreads();                                       // (the other half of `red` is written before anyone is a row further on)
-        double ar = 0.0;
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) ar += red[r & 1][w];
-        squares += ar * ar;
-        if (LAST && tid == 0) a[r] = ar;
-#pragma unroll
-        for (int k = 0; k < CG; ++k)
+            const bool there = column(k) < in;
+            if (!WALKS) fetch_shared(k, Paths{});
+            double kept[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
+                b[k][e] = there ? b[k][e] : 0.0;
+                kept[e] = LAST ? (there ? cols[k].f[e] : 0.0) : b[k][e] * fabs(cols[k].f[e]);
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    if (LAST) h[k][j][e] = there ? cols[k].h[j][e] : 0.0;
+                    else h[k][j][e] = cols[k].f[e] != 0.0 ? cols[k].h[j][e] / cols[k].f[e] : 0.0;
+                }
+                sum[k][e] = 0.0;
+            }
+            lds[2 * k * ONE_PASS_THREADS + tid] = make_double2(kept[0], kept[1]);
+            lds[(2 * k + 1) * ONE_PASS_THREADS + tid] = make_double2(kept[2], kept[3]);
+        }
+        // (a thread reads what it has written there)
+#pragma unroll 1
+        for (int r = r0; r < r1; ++r) {
+            double v[CG][4];
+#pragma unroll
+            for (int k = 0; k < CG; ++k) {
+                const float w[4] = {row.piece[k].w.x, row.piece[k].w.y, row.piece[k].w.z, row.piece[k].w.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[k][e] = row.factor * (double)w[e];
                 if (LAST) {
-                    const double left = fabs(v[k][e]) - ar * b[k][e];
-                    error += left * left;
-                } else {
-                    sum[k][e] += fabs(v[k][e]) * ar;
+                    const double2 low = lds[2 * k * ONE_PASS_THREADS + tid], high = lds[(2 * k + 1) * ONE_PASS_THREADS + tid];
+                    v[k][0] *= low.x; v[k][1] *= low.y; v[k][2] *= high.x; v[k][3] *= high.y;
+                }
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    const uint32_t bits = row.piece[k].bits[j] >> (4 * (tid & 7));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const unsigned long long flip = (unsigned long long)(bits << (31 - e) & 0x80000000u) << 32;
+                        v[k][e] -= __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, row.g[j]) ^ flip) * h[k][j][e];
+                    }
                 }
             }
-    }
-    if (LAST) {
-        error = group_sum(error, red_group, WAVES);
-        if (tid == 0) partial[blockIdx.x] = error;
-    } else {
+            __builtin_amdgcn_sched_barrier(0);
+            fetch_weights(min(r + 1, r1 - 1));
+            fetch_paths(min(r + 1, r1 - 1), paths);
+            __builtin_amdgcn_sched_barrier(0);
+            double dot[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int k = 0; k < CG; ++k) {
-            const int c = column(k);
-            if (c >= in) continue;
-            double f[4] = {1.0, 1.0, 1.0, 1.0};
-            if (p.cols) four(p.cols, c, f);
-            double *const to = partial + (size_t)blockIdx.x * in + c;
-            *reinterpret_cast<double2 *>(to) = make_double2(sum[k][0] * fabs(f[0]), sum[k][1] * fabs(f[1]));
-            *reinterpret_cast<double2 *>(to + 2) = make_double2(sum[k][2] * fabs(f[2]), sum[k][3] * fabs(f[3]));
+            for (int k = 0; k < CG; ++k) {
+                double2 low, high;
+                if (LAST) {
+                    low = make_double2(b[k][0], b[k][1]);
+                    high = make_double2(b[k][2], b[k][3]);
+                    // eight lanes hold the 32 columns of a word, four each
+                    uint32_t four = 0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) four |= !(v[k][e] >= 0.0) ? 1u << e : 0u;
+                    const uint32_t word = or_over_8(four << (4 * (lane & 7)));
+                    if ((lane & 7) == 0 && column(k) < in) signs[(size_t)r * W32 + (column(k) >> 5)] = word;
+                } else {
+                    low = lds[2 * k * ONE_PASS_THREADS + tid];
+                    high = lds[(2 * k + 1) * ONE_PASS_THREADS + tid];
+                }
+                dot[0] += fabs(v[k][0]) * low.x;
+                dot[1] += fabs(v[k][1]) * low.y;
+                dot[2] += fabs(v[k][2]) * high.x;
+                dot[3] += fabs(v[k][3]) * high.y;
+            }
+            const double d = over_wave((dot[0] + dot[1]) + (dot[2] + dot[3]));
+            if (lane == 0) red[r & 1][wave] = d;
+            __syncthreads();                                       // (the other half of `red` is written before anyone is a row further on)
+            double ar = 0.0;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) ar += red[r & 1][w];
+            squares += ar * ar;
+            if (LAST && tid == 0) a[r] = ar;
+#pragma unroll
+            for (int k = 0; k < CG; ++k)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (LAST) {
+                        const double left = fabs(v[k][e]) - ar * b[k][e];
+                        error += left * left;
+                    } else {
+                        sum[k][e] += fabs(v[k][e]) * ar;
+                    }
+                }
         }
+        if (LAST) {
+            error = group_sum(error, red_group, WAVES);
+            if (tid == 0) partial[blockIdx.x] = error;
+        } else {
+#pragma unroll
+            for (int k = 0; k < CG; ++k) {
+                const int c = column(k);
+                if (c >= in) continue;
+                double f[4] = {1.0, 1.0, 1.0, 1.0};
+                if (!WALKS && p.cols) four(p.cols, c, f);        // (WALKS: by walk_sums_kernel, once for all workgroups)
+                double *const to = partial + (size_t)blockIdx.x * in + c;
+                *reinterpret_cast<double2 *>(to) = make_double2(sum[k][0] * fabs(f[0]), sum[k][1] * fabs(f[1]));
+                *reinterpret_cast<double2 *>(to + 2) = make_double2(sum[k][2] * fabs(f[2]), sum[k][3] * fabs(f[3]));
+            }
+        }
+    };
+    if constexpr (WALKS) {
+        if (done) over_rows(std::true_type{});
+        else over_rows(std::false_type{});
+    } else {
+        over_rows(std::false_type{});
     }
     if (tid == 0) a_sq[blockIdx.x] = squares;
 }
@@ -517,30 +600,28 @@ static int one_pass_groups(int out, int in)
     if (out < ONE_PASS_MIN_ROWS || in < ONE_PASS_MIN_COLS || groups > 6) return 0;
     return (groups + 1) / 2 * 2;
 }
-template <int J, int CG, bool LAST> static int launch_groups(const Problem<J> &p, const Step &st, double *partial, double *a, double *a_sq, uint32_t *signs, hipStream_t stream)
+template <int J, int CG> static int launch_groups(const Problem<J> &p, uint32_t *packed, const Step &st, double *partial, double *a, double *a_sq, hipStream_t stream)
 {
     constexpr int lds = CG * GROUP_COLS * (int)sizeof(double);
     static std::atomic<bool> allowed[64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return RB_ERR_HIP;
     if (lds > 48 * 1024 && !allowed[dev].load()) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(one_pass_kernel<J, CG, LAST>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return RB_ERR_HIP;
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(one_pass_kernel<J, CG>), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return RB_ERR_HIP;
         allowed[dev].store(true);
     }
-    hipLaunchKernelGGL((one_pass_kernel<J, CG, LAST>), dim3(ONE_PASS_GROUPS), dim3(ONE_PASS_THREADS), lds, stream, p, st, partial, a, a_sq, signs);
+    hipLaunchKernelGGL((one_pass_kernel<J, CG>), dim3(ONE_PASS_GROUPS), dim3(ONE_PASS_THREADS), lds, stream, p, packed, st, partial, a, a_sq);
     return RB_OK;
 }
-template <bool LAST, int J> static int launch_one_pass(int groups, const Problem<J> &p, const Step &st, double *partial, double *a, double *a_sq, uint32_t *signs, hipStream_t stream)
+template <int J> static int launch_one_pass(int groups, const Problem<J> &p, uint32_t *packed, const Step &st, double *partial, double *a, double *a_sq, hipStream_t stream)
 {
-    if (groups == 2) return launch_groups<J, 2, LAST>(p, st, partial, a, a_sq, signs, stream);
-    if (groups == 4) return launch_groups<J, 4, LAST>(p, st, partial, a, a_sq, signs, stream);
-    if constexpr (LAST && J == 2) return RB_ERR_UNSUPPORTED;   // (not asked for, see `whole`)
-    else return launch_groups<J, 6, LAST>(p, st, partial, a, a_sq, signs, stream);
+    if (groups == 2) return launch_groups<J, 2>(p, packed, st, partial, a, a_sq, stream);
+    if (groups == 4) return launch_groups<J, 4>(p, packed, st, partial, a, a_sq, stream);
+    return launch_groups<J, 6>(p, packed, st, partial, a, a_sq, stream);
 }
 
 // sum[c] = the slices of partial[.][c], in eight runs of consecutive ones, over the norm of a (every workgroup adds
 // that up: squares of sums left at their length would leave fp64's range with W'^4), and the squares by workgroup
-constexpr int SUMS_COLS = 64, SUMS_RUNS = 8;
 __global__ __launch_bounds__(SUMS_COLS * SUMS_RUNS) void slices_kernel(const double *partial, int n_slices, const double *a_sq, int n_a, int in, double *sum, double *sum_sq, Scalars *sc)
 {
     const int done = sc->done;                                 // (looked at when the sums are there: no trip to memory before theirs)
@@ -564,6 +645,59 @@ __global__ __launch_bounds__(SUMS_COLS * SUMS_RUNS) void slices_kernel(const dou
     for (int m = SUMS_COLS / 2; m > 0; m >>= 1) sq += __shfl_xor(sq, m);
     if (x == 0) sum_sq[blockIdx.x] = sq;
 }
+
+// g' and h' of path i as scales_kernel gives them, and the error after the update
+struct Ends {
+    const double *a, *b;
+    double *g, *h, *err;               // [K][out], [K][in], [T_max][K] (or nullptr)
+};
+// What follows a pass of the walking form: the sums as slices_kernel makes them or, after a LAST, the path's scales as scales_kernel makes
+// them.  (The first eight slices are asked for before it is known which: one trip to memory less)
+__global__ __launch_bounds__(SUMS_COLS * SUMS_RUNS) void walk_sums_kernel(const double *partial, const double *a_sq, const double *cols, int K, int out, int in, double *sum, double *sum_sq, Ends to, Scalars *sc)
+{
+    constexpr int THREADS = SUMS_COLS * SUMS_RUNS, OF_RUN = ONE_PASS_GROUPS / SUMS_RUNS, FIRST = 8;
+    static_assert(ONE_PASS_GROUPS <= THREADS && OF_RUN % FIRST == 0, "a thread takes one square; whole batches of slices");
+    const int done = sc->done, t = sc->t, i = sc->i;
+    __shared__ double part[SUMS_RUNS][SUMS_COLS], red[SUMS_RUNS];
+    const int tid = threadIdx.x, x = tid % SUMS_COLS, run = tid / SUMS_COLS, c = blockIdx.x * SUMS_COLS + x;
+    const double *from = partial + (size_t)(OF_RUN * run) * in + min(c, in - 1);
+    const double factor = cols ? fabs(cols[min(c, in - 1)]) : 1.0;
+    double na = tid < ONE_PASS_GROUPS ? a_sq[tid] : 0.0, held[FIRST];
+#pragma unroll
+    for (int k = 0; k < FIRST; ++k) held[k] = from[(size_t)k * in];
+    if (done == WALKED) return;
+    if (done) {
+        const double sigma = sqrt(group_sum(na, red, SUMS_RUNS)), root = sqrt(sigma);
+        for (int n = blockIdx.x * THREADS + tid; n < max(out, in); n += gridDim.x * THREADS) {
+            if (n < out) to.g[(size_t)i * out + n] = sigma > 0.0 ? root * (to.a[n] / sigma) : 0.0;
+            if (n < in) to.h[(size_t)i * in + n] = root * to.b[n];
+        }
+        if (to.err && blockIdx.x == 0) {
+            const double e2 = group_sum(tid < ONE_PASS_GROUPS ? partial[tid] : 0.0, red, SUMS_RUNS);
+            if (tid == 0) to.err[(size_t)t * K + i] = sqrt(e2);
+        }
+        return;
+    }
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < FIRST; ++k) s += held[k];
+#pragma unroll
+    for (int k = FIRST; k < OF_RUN; ++k) s += from[(size_t)k * in];
+    part[run][x] = s;
+    na = sqrt(group_sum(na, red, SUMS_RUNS));
+    if (blockIdx.x == 0 && tid == 0) sc->na = na;
+    if (tid >= SUMS_COLS) return;
+    s = 0.0;
+#pragma unroll
+    for (int k = 0; k < SUMS_RUNS; ++k) s += part[k][x];
+    s = s * factor / na;                                                   // (a zero norm: the next pass does not look at the sums)
+    if (c < in) sum[c] = s;
+    double sq = c < in ? s * s : 0.0;
+    for (int m = SUMS_COLS / 2; m > 0; m >>= 1) sq += __shfl_xor(sq, m);
+    if (x == 0) sum_sq[blockIdx.x] = sq;
+}
+// as after a LAST: the first pass begins the first update
+__global__ void walk_start_kernel(Scalars *sc) { *sc = Scalars{0.0, 0.0, 0.0, 1, 0, 0, -1}; }
 
 constexpr int UNIT_HELD = 12;           // columns of a thread that the next kernel asks for at its start
 // b_new = sum / its norm, the change of b, the stopping rule  (one workgroup)
@@ -608,10 +742,9 @@ __global__ __launch_bounds__(1024) void unit_kernel(double *b, const double *sum
     }
 }
 
-// after the final a = |R| b: g' = sqrt(sigma) a / sigma, h' = sqrt(sigma) b with sigma = ||a||; and the root of the sum of err_sq, of
-// as many workgroups as a_sq, if there are any
+// after the final a = |R| b: g' = sqrt(sigma) a / sigma, h' = sqrt(sigma) b with sigma = ||a||
 __global__ __launch_bounds__(256) void scales_kernel(const double *a, const double *b, const double *a_sq, int n_a, double *g_i,
-                                                     double *h_i, int out, int in, const Scalars *sc, const double *err_sq, double *err)
+                                                     double *h_i, int out, int in, const Scalars *sc)
 {
     if (!sc->done) return;
     __shared__ double red[4];
@@ -622,12 +755,6 @@ __global__ __launch_bounds__(256) void scales_kernel(const double *a, const doub
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < out) g_i[i] = sigma > 0.0 ? root * (a[i] / sigma) : 0.0;
     if (i < in) h_i[i] = root * b[i];
-    if (err && blockIdx.x == 0) {
-        double e2 = 0.0;
-        for (int n = threadIdx.x; n < n_a; n += 256) e2 += err_sq[n];
-        e2 = group_sum(e2, red, 4);
-        if (threadIdx.x == 0) *err = sqrt(e2);
-    }
 }
 
 // squared Frobenius norm of W' - sum_j What_j over all J paths (the last update: nothing follows that could find it on the
@@ -714,16 +841,51 @@ struct Buffers {
     double *a, *a_sq, *b, *sum, *sum_sq, *partial;
 };
 
+// All updates by one_pass_kernel where it walks.  The host asks for a first sweep's passes and looks how far they came; then for as many as the
+// rest would take at that rate, and looks again.  Two passes over (some 6 us each) are less than another look (27 us).
+template <int K>
+static int walk(const Problem<K - 1> &p, uint32_t *packed, double *g, double *h, double *err, int T_max, int groups, const Buffers &ws, hipStream_t stream)
+{
+    constexpr int MOST = 1024;             // passes asked for without a look
+    const int in = p.in, n_sq = (in + SUMS_COLS - 1) / SUMS_COLS;
+    double *const bs[2] = {ws.b, ws.partial + (size_t)ONE_PASS_GROUPS * in};
+    hipLaunchKernelGGL(walk_start_kernel, dim3(1), dim3(1), 0, stream, ws.sc);
+    double passes = 0.0, wanted = (double)K * (FIRST_LOOK + 1);
+    for (int now = 0;;) {
+        const int n = (int)std::min<double>(MOST, wanted);
+        for (int k = 0; k < n; ++k, now ^= 1) {
+            const Step st{bs[now], ws.sum, ws.sum_sq, bs[now ^ 1], ws.sc + now, ws.sc + (now ^ 1), n_sq, T_max};
+            const int rc = launch_one_pass(groups, p, packed, st, ws.partial, ws.a, ws.a_sq, stream);
+            if (rc != RB_OK) return rc;
+            hipLaunchKernelGGL(walk_sums_kernel, dim3(n_sq), dim3(SUMS_COLS * SUMS_RUNS), 0, stream, ws.partial, ws.a_sq, p.cols, K, p.out, in, ws.sum, ws.sum_sq,
+                               Ends{ws.a, bs[now ^ 1], g, h, err}, ws.sc + (now ^ 1));
+        }
+        Scalars host;
+        if (hipMemcpyAsync(&host, ws.sc + now, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess || hipStreamSynchronize(stream) != hipSuccess)
+            return RB_ERR_HIP;
+        passes += n;
+        const double spent = host.done ? 0.0 : host.iters + 1.0, finished = (double)K * host.t + host.i + (host.done ? 1.0 : 0.0), left = (double)K * T_max - finished;
+        if (host.done == WALKED || left <= 0.0) return RB_OK;
+        wanted = finished > 0.0 ? std::max(0.0, (passes - spent) / finished * left - spent) + 2.0 : FIRST_LOOK;
+    }
+}
+
 template <int K>
 static int derive(const float *W, const double *row_factors, const double *col_factors, int out, int in, int T_max, double *g, double *h,
                   uint32_t *packed, double *err, const Buffers &ws, int slice_rows, bool room, hipStream_t stream)
 {
     const int one_pass = room ? one_pass_groups(out, in) : 0;
-    // Whether the one-pass form does all of an iteration and the pass after it.  Not for three paths of more than 8192 columns: LAST would spill 52 registers
-    // (169 us, where the pass by rows and a first iteration in two passes cost 66 more than an iteration; 4096 x 11008, three sweeps 4.10 and 3.42 ms)
-    const bool whole = one_pass && (K < 3 || one_pass < 6);
-    const int n_slices = (out + slice_rows - 1) / slice_rows, n_a = (out + ROWS - 1) / ROWS;
     const size_t words = (size_t)out * (in / 32);
+    if (one_pass && walks(K - 1, one_pass)) {
+        Problem<K - 1> all{W, row_factors, col_factors, {}, {}, {}, out, in};
+        for (int j = 0; j < K; ++j) {
+            all.packed[j] = packed + j * words;
+            all.g[j] = g + (size_t)j * out;
+            all.h[j] = h + (size_t)j * in;
+        }
+        return walk<K>(all, packed, g, h, err, T_max, one_pass, ws, stream);
+    }
+    const int n_slices = (out + slice_rows - 1) / slice_rows, n_a = (out + ROWS - 1) / ROWS;
     const dim3 by_rows((unsigned)n_a), by_cols((in + 1023) / 1024, n_slices), wg(256);
     int look = FIRST_LOOK;                         // iterations enqueued before the host looks: as many as the last update took
     for (int t = 0; t < T_max; ++t) {
@@ -740,19 +902,11 @@ static int derive(const float *W, const double *row_factors, const double *col_f
             const bool err_before = err && t * K + i > 0;
             hipLaunchKernelGGL(start_kernel, dim3((in + 255) / 256), wg, 0, stream, ws.b, in, ws.sc);
             double *const err_here = err ? err + (size_t)t * K + i : nullptr;
-            // one reading of W per iteration: b and the scalars change places whenever a kernel folds sums in
-            double *const bs[2] = {ws.b, ws.partial + (size_t)ONE_PASS_GROUPS * in};
-            int now = 0, fold = 0;
-            auto step = [&]() {
-                const Step st{bs[now], ws.sum, ws.sum_sq, bs[now ^ 1], ws.sc + now, ws.sc + (now ^ 1), (in + SUMS_COLS - 1) / SUMS_COLS, fold};
-                now ^= fold;
-                return st;
-            };
             Scalars host;
             for (int it = 1;; ++it) {
-                const bool one = one_pass && (whole || it > 1 || !err_before);
+                const bool one = one_pass && (it > 1 || !err_before);
                 if (one) {
-                    const int rc = launch_one_pass<false>(one_pass, p, step(), ws.partial, ws.a, ws.a_sq, signs, stream);
+                    const int rc = launch_one_pass(one_pass, p, packed, Step{ws.b, nullptr, nullptr, nullptr, ws.sc, nullptr, 0, 0}, ws.partial, ws.a, ws.a_sq, stream);
                     if (rc != RB_OK) return rc;
                 } else {
                     if (it == 1 && err_before) {
@@ -765,21 +919,14 @@ static int derive(const float *W, const double *row_factors, const double *col_f
                     hipLaunchKernelGGL((cols_kernel<K - 1>), by_cols, wg, 0, stream, p, ws.a, ws.partial, slice_rows, ws.sc);
                 }
                 hipLaunchKernelGGL(slices_kernel, dim3((in + SUMS_COLS - 1) / SUMS_COLS), dim3(SUMS_COLS * SUMS_RUNS), 0, stream, ws.partial, one ? ONE_PASS_GROUPS : n_slices, ws.a_sq,
-                                   one ? ONE_PASS_GROUPS : n_a, in, ws.sum, ws.sum_sq, ws.sc + now);
-                if (!whole) hipLaunchKernelGGL(unit_kernel, dim3(1), dim3(1024), 0, stream, ws.b, ws.sum, ws.sum_sq, in, ws.sc);
-                fold = whole;
+                                   one ? ONE_PASS_GROUPS : n_a, in, ws.sum, ws.sum_sq, ws.sc);
+                hipLaunchKernelGGL(unit_kernel, dim3(1), dim3(1024), 0, stream, ws.b, ws.sum, ws.sum_sq, in, ws.sc);
                 if (it < look) continue;
                 // |R| b and the signs for the converged b, the path's new scales: nothing happens unless the iteration has finished
-                if (whole) {
-                    const int rc = launch_one_pass<true>(one_pass, p, step(), ws.partial, ws.a, ws.a_sq, signs, stream);
-                    if (rc != RB_OK) return rc;
-                    fold = 0;
-                } else {
-                    hipLaunchKernelGGL((rows_kernel<K - 1, FINAL>), by_rows, wg, 0, stream, p, ws.b, ws.a, ws.a_sq, signs, ws.partial, ws.sc);
-                }
-                hipLaunchKernelGGL(scales_kernel, dim3((std::max(out, in) + 255) / 256), wg, 0, stream, ws.a, bs[now], ws.a_sq, whole ? ONE_PASS_GROUPS : n_a,
-                                   g + (size_t)i * out, h + (size_t)i * in, out, in, ws.sc + now, ws.partial, whole ? err_here : nullptr);
-                if (hipMemcpyAsync(&host, ws.sc + now, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess ||
+                hipLaunchKernelGGL((rows_kernel<K - 1, FINAL>), by_rows, wg, 0, stream, p, ws.b, ws.a, ws.a_sq, signs, ws.partial, ws.sc);
+                hipLaunchKernelGGL(scales_kernel, dim3((std::max(out, in) + 255) / 256), wg, 0, stream, ws.a, ws.b, ws.a_sq, n_a,
+                                   g + (size_t)i * out, h + (size_t)i * in, out, in, ws.sc);
+                if (hipMemcpyAsync(&host, ws.sc, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess ||
                     hipStreamSynchronize(stream) != hipSuccess)
                     return RB_ERR_HIP;
                 if (host.done) break;
@@ -787,7 +934,7 @@ static int derive(const float *W, const double *row_factors, const double *col_f
             look = std::max(1, host.iters);
         }
     }
-    if (err && !whole) {
+    if (err) {
         Problem<K> p{W, row_factors, col_factors, {}, {}, {}, out, in};
         for (int j = 0; j < K; ++j) {
             p.packed[j] = packed + j * words;

@@ -208,6 +208,44 @@ def test_both_passes_in_one_reading(K, out, inn, calibrated, slow):
     np.testing.assert_allclose(ed.cpu().numpy(), err_d, rtol=1e-12)
 
 
+@pytest.mark.parametrize("K,out,inn,kind", [(1, 1024, 2048, "gaussian"), (2, 1030, 8224, "gaussian"), (3, 1024, 4160, "gaussian"), (2, 1024, 4128, "slow"),
+                                            (2, 1024, 2080, "zero"), (3, 1024, 2048, "signs")])
+def test_updates_one_after_the_other_without_the_host(K, out, inn, kind):
+    """However many passes the host has asked for when it looks (one sweep of four iterations each; a sweep of many more; updates that end at
+    once: |R| zero or of equal entries, after which all further residuals are zero), the updates are the same: T sweeps begin with what
+    one sweep gives, bit for bit, and the last scales are those of T sweeps with no errors asked for."""
+    W = synth.gaussian_weight(synth.child_rng(7, 713, K, out), out, inn, std=0.02).astype(np.float32)
+    if kind == "slow":
+        W[:out // 2, inn // 2:] *= 1e-3
+        W[out // 2:, :inn // 2] *= 1e-3
+        W[out // 2:, inn // 2:] *= 1.5
+    elif kind == "zero":
+        W[:] = 0.0
+    elif kind == "signs":
+        W = np.where(W >= 0, np.float32(0.25), np.float32(-0.25))
+    print(f"derive K={K} {out}x{inn} {kind}", flush=True)
+    one = _run(W, K, 1)
+    packed, g, h, err = _run(W, K, 7)
+    assert np.array_equal(err[:1], one[3]) and np.isfinite(err).all()
+    assert np.all(np.diff(err.reshape(-1)) <= 1e-12 * np.linalg.norm(W.astype(np.float64)))
+    Wd = torch.from_numpy(W).cuda()
+    for T, want in ((1, one), (7, (packed, g, h))):
+        pd = torch.empty((K, out, inn // 32), dtype=torch.int32, device="cuda")
+        gd, hd = (torch.empty((K, n), dtype=torch.float64, device="cuda") for n in (out, inn))
+        need = rb.lib.rb_derive_workspace_bytes(out, inn)
+        ws = torch.full((need,), 255, dtype=torch.uint8, device="cuda")
+        assert rb.lib.rb_derive_iterative(Wd.data_ptr(), None, None, K, T, out, inn, pd.data_ptr(), gd.data_ptr(), hd.data_ptr(), None, ws.data_ptr(), need, None) == rb.RB_OK
+        torch.cuda.synchronize()
+        assert np.array_equal(pd.cpu().numpy().view(np.uint32), want[0])
+        assert np.array_equal(gd.cpu().numpy(), want[1]) and np.array_equal(hd.cpu().numpy(), want[2])
+    if kind == "signs":                                        # the first path is the weight, the others are nothing
+        assert np.array_equal(np.unpackbits(packed[0].view(np.uint8), bitorder="little").reshape(out, inn) == 1, W < 0)
+        np.testing.assert_allclose(np.outer(g[0], h[0]), 0.25, rtol=1e-12)
+        assert err.max() < 1e-11 * 0.25 * np.sqrt(out * inn)
+    if kind == "zero":
+        assert not err.any() and not g.any() and not h.any()
+
+
 @pytest.mark.parametrize("K,inn", [(1, 4128), (2, 2080), (2, 8224), (2, 10272), (3, 4128), (3, 8288)])
 def test_nothing_beside_the_weight_is_read(K, inn):
     """Groups of 2048 columns that a row fills in part, or not at all (4128, 8224 and 8288 columns: three and five groups' worth in forms
