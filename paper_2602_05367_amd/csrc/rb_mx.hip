@@ -1310,15 +1310,18 @@ static int prepare_any(const rb_layer *layers, const PlanOp *sops, int n_ops, ui
     const int G = device_groups();
     if (G <= 0) return RB_ERR_HIP;
     if (tokens > 2) {
-        forget_plan(workspace);
-        return flow::prepare(layers, sops, n_ops, bufs, norm_w, eps, block, tokens, workspace, workspace_bytes_, stream);
+        const int rc = flow::prepare(layers, sops, n_ops, bufs, norm_w, eps, block, tokens, workspace, workspace_bytes_, stream);
+        if (rc == RB_OK || rc == RB_ERR_HIP) {                 // (what was refused leaves the plan that was there)
+            std::lock_guard<std::mutex> lock(g_mutex);
+            g_prepared.erase(workspace);
+        }
+        return rc;
     }
     // one kernel form per plan: every op has the same number of paths
     const int K = layers[sops[0].layer].K;
     for (int n = 0; n < n_ops; ++n)
         if (layers[sops[n].layer].K != K || !form_supported(&layers[sops[n].layer], tokens)) return RB_ERR_UNSUPPORTED;
     if (block && K == 3 && tokens != 1) return RB_ERR_UNSUPPORTED;
-    flow::forget(workspace);
     const int T = layout_tokens(tokens, K);            // tokens of the operand layout
 
     // ---- ops, consumers, stages
@@ -1493,6 +1496,7 @@ static int prepare_any(const rb_layer *layers, const PlanOp *sops, int n_ops, ui
         hipMemcpyAsync(ws + lay.which, which, sizeof(int) * expand_list.size(), hipMemcpyHostToDevice, stream) !=
             hipSuccess)
         return RB_ERR_HIP;
+    flow::forget(workspace);
     {
         std::lock_guard<std::mutex> lock(g_mutex);
         g_prepared[workspace] = pr;
@@ -1543,14 +1547,18 @@ int prepare_block(const rb_layer *layers, const uint16_t *const *norm_w, float e
 int launch_plan(void *workspace, size_t workspace_bytes_, hipStream_t stream)
 {
     Prepared pr;
+    bool here = false;
     {
         std::lock_guard<std::mutex> lock(g_mutex);
         const auto it = g_prepared.find(workspace);
-        if (it == g_prepared.end()) {
-            const int rc = flow::launch(workspace, workspace_bytes_, g_pause_clks.load(), stream);
-            return rc == RB_ERR_UNSUPPORTED ? RB_ERR_WORKSPACE : rc;
+        if (it != g_prepared.end()) {
+            pr = it->second;
+            here = true;
         }
-        pr = it->second;
+    }
+    if (!here) {
+        const int rc = flow::launch(workspace, workspace_bytes_, g_pause_clks.load(), stream);
+        return rc == RB_ERR_UNSUPPORTED ? RB_ERR_WORKSPACE : rc;
     }
     if (workspace_bytes_ < pr.lay.total) return RB_ERR_WORKSPACE;
     uint8_t *ws = static_cast<uint8_t *>(workspace);

@@ -674,3 +674,42 @@ def test_three_and_four_token_stack_forms(T, shapes):
         ref = oracle.forward(*layers[n], dev[src].cpu().numpy())
         got = dev[dst].cpu().numpy().astype(np.float64)
         assert oracle.relative_l2(got, ref).max() <= TOL, (n, shapes[n])
+
+
+@pytest.mark.parametrize("first,second", [(1, 3), (3, 1), (2, 4), (4, 3)])
+def test_one_workspace_for_plans_of_the_two_few_token_kernels(first, second):
+    """A plan that is refused for want of room leaves the one that was there; one that is accepted takes its place."""
+    rng = synth.child_rng(3, 501, first, second)
+    layers = [random_layer(rng, 2, 512, 512, gain=1.0 / (0.02 * 0.02 * np.sqrt(512))) for _ in range(2)]
+    dev_layers = [to_device_layer(*l) for l in layers]
+    stacks = []
+    for T in (first, second):
+        bufs = [torch.from_numpy(synth.gaussian_activations(rng, T, 512)).cuda()] + [torch.zeros((T, 512), dtype=torch.float16, device="cuda") for _ in range(2)]
+        stacks.append(rb.Stack(dev_layers, [(0, 0, 1), (1, 1, 2)], bufs, T))
+    size = max(s.ws_bytes for s in stacks)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    for s in stacks:
+        s.ws, s.ws_bytes = ws, size
+
+    def check(s):
+        s.bufs[2].fill_(7.0)
+        print(f"stack of {s.T} tokens on a shared workspace", flush=True)
+        s.run_prepared()
+        torch.cuda.synchronize()
+        assert s.status() == rb.RB_OK
+        ref = oracle.forward(*layers[1], s.bufs[1].cpu().numpy())
+        assert oracle.relative_l2(s.bufs[2].cpu().numpy().astype(np.float64), ref).max() <= TOL
+
+    one, two = stacks
+    one.prepare()
+    check(one)
+    two.ws_bytes = 1024
+    with pytest.raises(RuntimeError):
+        two.prepare()
+    check(one)
+    two.ws_bytes = size
+    two.prepare()
+    check(two)
+    one.prepare()
+    check(one)
+    one.forget()
