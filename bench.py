@@ -462,8 +462,7 @@ def main() -> int:
         result["paper_context"] = "RTX 4090: 291.88 tok/s = 4.49x FP16, whole Llama2-7B model (inference table)"
         result["prefill_gemm_T2048"] = prefill_figures(rb, torch)
         # small decode batches: the 7B-shaped stack, every op on its own input buffer.
-        # 2 and 4 tokens: the fused decode kernel, one launch (four tokens are two pairs that share the
-        # expanded signs).  8 and 16 tokens: the few-token kernel,
+        # 2 and 4 tokens: the fused decode kernels, one launch.  8 and 16 tokens: the few-token kernel,
         # one pass over the weights, one launch per group of independent ops.
         skinny = {}
         for Ts in (2, 4, 8, 16):
