@@ -36,15 +36,27 @@ constexpr int COUPLE_CHUNK = 512, COUPLE_ROWS = 4;      // columns and rows one 
 // together in LDS and stored in whole lines, padding included (zero bits: +1).  What a wavefront's rows share of
 // the columns (h, converted to fp32) is fetched once.  A lane takes four consecutive columns
 // at a time (one 16-byte load of W; the chunk's loads are all requested before the first is used),
-// so a step of the wavefront covers 256 columns and eight lanes hold one sign word between them:
-// lane i of the eight has columns 4 i .. 4 i + 3 of the word, bits 4 i + j of the canonical word
-// (bit b = column 32 w + b, 1 means -1) and bits 16 (i % 2) + 4 j + i / 2 of the native one (native
-// bit 4 e + s is column 8 s + e); each lane shifts its four bits into place in both and an OR over
-// the eight lanes gives the words.  The residual is fp32 with one rounding for g * h and one for
+// so a step of the wavefront covers 256 columns.  The comparison of column j of the lanes is a 64-bit
+// mask in scalar registers whose bits 8 w .. 8 w + 7 belong to sign word w of the step; its halves
+// are filed in lanes of a register of their own for each j, and at the end 64 lanes put 64 words
+// together at once: lane (step, row, w) fetches its byte of the four masks (bit 8 j + i is column 4 i + j)
+// and moves the bits to where the canonical word (bit 4 i + j) and the native one (native bit 4 e + s is
+// column 8 s + e: bit 16 (i % 2) + 4 j + i / 2) have them.
+// The residual is fp32 with one rounding for g * h and one for
 // the subtraction, the arithmetic the definition fixes (the sign of the product is exact).
-// Bound by the read of W and, close behind, by vector instructions (some 35 per four weights and path).
-// 4096 x 11008, two paths, under the profiler: 56 us (64 with one row per wavefront and native words stored one by one,
-// and 6 for zeroing them before).
+// Bound by the read of W and, behind it, by vector instructions.
+// Vector instructions of a wavefront at two paths 500, with an OR over eight lanes per word and form and h fetched where it was used
+// 877; a training step of 4096 x 11008 (512 samples) 228.6 -> 223.3 us by this alone.  (The words by themselves before that, one row per
+// wavefront and native words stored one by one: 8 us more, and 6 for zeroing them before.)
+extern "C" __device__ uint32_t rb_writelane(uint32_t value, uint32_t lane, uint32_t old) __asm("llvm.amdgcn.writelane.i32");      // has no builtin
+template <int A, int B> __device__ __forceinline__ uint32_t swap_index_bits(uint32_t x)      // bit i of a word goes where bits A > B of i are exchanged
+{
+    constexpr int D = (1 << A) - (1 << B);
+    constexpr uint32_t b[5] = {0xaaaaaaaau, 0xccccccccu, 0xf0f0f0f0u, 0xff00ff00u, 0xffff0000u}, mask = b[B] & ~b[A];
+    const uint32_t t = (x ^ x >> D) & mask;
+    return x ^ t ^ t << D;
+}
+
 template <int K>
 __global__ __launch_bounds__(256) void couple_kernel(const float *__restrict__ W, const __half *__restrict__ g,
                                                      const __half *__restrict__ h, int out, int in,
@@ -52,74 +64,80 @@ __global__ __launch_bounds__(256) void couple_kernel(const float *__restrict__ W
                                                      float *__restrict__ residual)
 {
     constexpr int STEPS = COUPLE_CHUNK / 256, R = COUPLE_ROWS;
+    static_assert(STEPS * R * 8 == 64 && STEPS * K * R * 2 <= 64, "a path's words are a wavefront's lanes, the masks' halves fit them");
     const int lane = threadIdx.x & 63;
     // one-dimensional grid, row tiles fastest (a second dimension would end at 65536 chunks of columns)
     const int RT = row_tiles(out), rt = (int)(blockIdx.x % (unsigned)RT);
-    const int tile_row0 = (int)(threadIdx.x >> 6) * R, row0 = rt * TILE_ROWS + tile_row0;
+    const int tile_row0 = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6) * R), row0 = rt * TILE_ROWS + tile_row0;
     static_assert(4 * R == TILE_ROWS && COUPLE_CHUNK % TILE_COLS == 0, "whole sign tiles per workgroup");
     __shared__ __attribute__((aligned(16))) uint32_t tiles[STEPS * tile_words(K)];
     const int W32 = in / 32, CT = col_tiles(in);
+    const int chunk0 = (int)(blockIdx.x / (unsigned)RT) * COUPLE_CHUNK;
+    float4 wv[STEPS][R];
+    uint2 hb[STEPS][K];
+#pragma unroll
+    for (int i = 0; i < STEPS; ++i) {
+        const int c = chunk0 + 256 * i + 4 * lane;             // in % 32 == 0: all four columns or none
+#pragma unroll
+        for (int k = 0; k < K; ++k) hb[i][k] = *reinterpret_cast<const uint2 *>(h + (size_t)k * in + (c < in ? c : 0));
+#pragma unroll
+        for (int u = 0; u < R; ++u)                            // rows and columns past the end: others, whose signs `real` clears
+            wv[i][u] = *reinterpret_cast<const float4 *>(W + (size_t)min(row0 + u, out - 1) * in + (c < in ? c : 0));
+    }
     float gr[R][K];
 #pragma unroll
     for (int u = 0; u < R; ++u)
 #pragma unroll
         for (int k = 0; k < K; ++k) gr[u][k] = __half2float(g[(size_t)k * out + min(row0 + u, out - 1)]);
-    const int chunk0 = (int)(blockIdx.x / (unsigned)RT) * COUPLE_CHUNK;
-    float4 wv[STEPS][R];
+    uint32_t masks[4] = {0u, 0u, 0u, 0u};                      // column j: half v of (step i, path k, row u) in lane ((i K + k) R + u) 2 + v
 #pragma unroll
     for (int i = 0; i < STEPS; ++i) {
         const int c = chunk0 + 256 * i + 4 * lane;
-#pragma unroll
-        for (int u = 0; u < R; ++u)                            // rows past the end: the last one, not stored
-            wv[i][u] = c < in ? *reinterpret_cast<const float4 *>(W + (size_t)min(row0 + u, out - 1) * in + c) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int i = 0; i < STEPS; ++i) {
-        const int c0 = chunk0 + 256 * i;
-        const int c = c0 + 4 * lane;
-        const bool real = c < in;                              // in % 32 == 0: all four columns or none
-        const int i8 = lane & 7;
-        const int w = (c0 >> 5) + (lane >> 3);                 // the word this group of eight lanes holds
+        const uint64_t real = __builtin_amdgcn_ballot_w64(c < in);
         float r[R][4];
 #pragma unroll
         for (int u = 0; u < R; ++u) { r[u][0] = wv[i][u].x; r[u][1] = wv[i][u].y; r[u][2] = wv[i][u].z; r[u][3] = wv[i][u].w; }
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            float hv[4] = {0.f, 0.f, 0.f, 0.f};
-            if (real) {
-                const uint2 hb = *reinterpret_cast<const uint2 *>(h + (size_t)k * in + c);
-                hv[0] = __half2float(__ushort_as_half((unsigned short)(hb.x & 0xffffu)));
-                hv[1] = __half2float(__ushort_as_half((unsigned short)(hb.x >> 16)));
-                hv[2] = __half2float(__ushort_as_half((unsigned short)(hb.y & 0xffffu)));
-                hv[3] = __half2float(__ushort_as_half((unsigned short)(hb.y >> 16)));
-            }
+            const float hv[4] = {__half2float(__ushort_as_half((unsigned short)(hb[i][k].x & 0xffffu))),
+                                 __half2float(__ushort_as_half((unsigned short)(hb[i][k].x >> 16))),
+                                 __half2float(__ushort_as_half((unsigned short)(hb[i][k].y & 0xffffu))),
+                                 __half2float(__ushort_as_half((unsigned short)(hb[i][k].y >> 16)))};
 #pragma unroll
             for (int u = 0; u < R; ++u) {
-                uint32_t can = 0;
+                const uint64_t counts = row0 + u < out ? real : 0u;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    // sign(0) = +1; columns past the end (zero times h) read as +1 unless h is, which `real` settles below
-                    const bool neg = !(r[u][j] >= 0.f);
+                    const bool neg = !(r[u][j] >= 0.f);        // sign(0) = +1
                     const float prod = __fmul_rn(gr[u][k], hv[j]);
                     r[u][j] = __fsub_rn(r[u][j], neg ? -prod : prod);
-                    can |= neg ? 1u << j : 0u;
-                }
-                const int row = row0 + u;
-                if (!real || row >= out) can = 0;
-                const uint32_t nat = (can | can << 3 | can << 6 | can << 9) & 0x1111u;
-                const uint32_t word = or_over_8(can << (4 * i8));
-                const uint32_t nword = or_over_8(nat << (16 * (i8 & 1) + (i8 >> 1)));
-                if (i8 == 0) {
-                    if (packed && w < W32 && row < out) packed[((size_t)k * out + row) * W32 + w] = word;
-                    const int cc = (w % 8) / 4, q = w % 4;
-                    tiles[i * tile_words(K) + lane_word(tile_row0 + u + 16 * q, cc, k, K)] = nword;
+                    const uint64_t m = __builtin_amdgcn_ballot_w64(neg) & counts;
+                    const int at = ((i * K + k) * R + u) * 2;
+                    masks[j] = rb_writelane((uint32_t)m, at, masks[j]);
+                    masks[j] = rb_writelane((uint32_t)(m >> 32), at + 1, masks[j]);
                 }
             }
         }
-        if (residual && real)
+        if (residual && c < in)
 #pragma unroll
             for (int u = 0; u < R; ++u)
                 if (row0 + u < out) *reinterpret_cast<float4 *>(residual + (size_t)(row0 + u) * in + c) = make_float4(r[u][0], r[u][1], r[u][2], r[u][3]);
+    }
+    // this lane's word of each path: step, row, word of the step
+    const int i = lane >> 5, u = lane >> 3 & 3, w = lane & 7;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int from = ((i * K + k) * R + u) * 2 + (w >> 2);
+        uint32_t x = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            x |= ((uint32_t)__builtin_amdgcn_ds_bpermute(4 * from, (int)masks[j]) >> 8 * (w & 3) & 0xffu) << 8 * j;
+        const int word = (chunk0 >> 5) + 8 * i + w;
+        if (packed && word < W32 && row0 + u < out)            // index bits j j i i i -> i i i j j
+            packed[((size_t)k * out + row0 + u) * W32 + word] =
+                swap_index_bits<1, 0>(swap_index_bits<2, 0>(swap_index_bits<3, 1>(swap_index_bits<4, 2>(x))));
+        tiles[i * tile_words(K) + lane_word(tile_row0 + u + 16 * (w & 3), w >> 2, k, K)] =      // j j i i i0 -> i0 j j i i
+            swap_index_bits<1, 0>(swap_index_bits<2, 0>(swap_index_bits<3, 0>(swap_index_bits<4, 0>(x))));
     }
     if (!native) return;
     __syncthreads();
