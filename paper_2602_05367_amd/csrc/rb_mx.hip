@@ -461,7 +461,7 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
     static_assert(KK == 2 || (KK == 3 && TT == 2), "three paths use the two-token layout");
     constexpr int CW = cwaves_of(TT), THREADS = threads_of(TT);
     constexpr int TILE_BYTES = 512 * KK, SL = sign_loads_of(KK);
-    using Lds = LdsMap<CW, KK>;
+    using Lds = LdsMap<CW, KK, pairs_of(TT)>;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     float *part = reinterpret_cast<float *>(lds + Lds::PART_OFF);
 
@@ -469,7 +469,7 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int grp = blockIdx.x;
     const int n_stages = hdr_p->n_stages;
-    constexpr int NB = nb_of(TT), KOP = kop_of(TT);
+    constexpr int T = TT, NB = nb_of(TT), KOP = kop_of(TT);
 
     // ---- LDS set-up: clear the partial sums
     for (int i = threadIdx.x; i < Lds::PART_BYTES / 4; i += THREADS) part[i] = 0.f;
@@ -638,7 +638,7 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
                                  : "+v"(dst.r[0]), "+v"(dst.r[1])
                                  : "v"(lane_off), "s"(rsrc)
                                  : "memory");
-                else
+                else if constexpr (TT == 2)
                     asm volatile("s_nop 4\n\t"
                                  "buffer_load_dwordx4 %0, %4, %5, 0 offen\n\t"
                                  "buffer_load_dwordx4 %1, %4, %5, 0 offen offset:1024\n\t"
@@ -647,6 +647,22 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
                                  : "+v"(dst.r[0]), "+v"(dst.r[1]), "+v"(dst.r[2]), "+v"(dst.r[3])
                                  : "v"(lane_off), "s"(rsrc)
                                  : "memory");
+                else {
+                    // eight KB: the offset field holds 12 bits, the second half goes through a second address
+                    asm volatile("s_nop 4\n\t"
+                                 "buffer_load_dwordx4 %0, %8, %10, 0 offen\n\t"
+                                 "buffer_load_dwordx4 %1, %8, %10, 0 offen offset:1024\n\t"
+                                 "buffer_load_dwordx4 %2, %8, %10, 0 offen offset:2048\n\t"
+                                 "buffer_load_dwordx4 %3, %8, %10, 0 offen offset:3072\n\t"
+                                 "buffer_load_dwordx4 %4, %9, %10, 0 offen\n\t"
+                                 "buffer_load_dwordx4 %5, %9, %10, 0 offen offset:1024\n\t"
+                                 "buffer_load_dwordx4 %6, %9, %10, 0 offen offset:2048\n\t"
+                                 "buffer_load_dwordx4 %7, %9, %10, 0 offen offset:3072"
+                                 : "+v"(dst.r[0]), "+v"(dst.r[1]), "+v"(dst.r[2 % KOP]), "+v"(dst.r[3 % KOP]), "+v"(dst.r[4 % KOP]),
+                                   "+v"(dst.r[5 % KOP]), "+v"(dst.r[6 % KOP]), "+v"(dst.r[7 % KOP])
+                                 : "v"(lane_off), "v"(lane_off + 4096u), "s"(rsrc)
+                                 : "memory");
+                }
             };
             // Hand-over: a finishing wavefront of this workgroup announces, with one word in LDS per
             // stage parity, that the inputs of this stage have probably been written.
@@ -687,14 +703,16 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
                 load_operand(dst, rsrc);
             };
 
-            v4f acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0}, acc2 = {0, 0, 0, 0};   // acc2: the third path
+            v4f acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0}, acc2 = {0, 0, 0, 0};   // acc2: the third path, or path 0 of tokens 2, 3
+            [[maybe_unused]] v4f acc3 = {0, 0, 0, 0};                             // path 1 of tokens 2, 3
             const int parity = st & 1;
             // a quad of lanes holds the four terms of (path = quad & 1, token = quad >> 1); its
             // first lane writes rows 4*qd .. 4*qd+3 of that path and token
             const int quad = col >> 2;
             const uint32_t part_lane = lds_addr(part) + (uint32_t)(parity * MAXSLOT) * Lds::PART_SLOT_BYTES +
                                        (uint32_t)(((quad & 1) * 2 + (quad >> 1)) * 16 + 4 * qd) * 4;
-            auto flush = [&](uint32_t part_index) {       // slot * CW + run: 256 bytes each
+            constexpr int PAIRS = pairs_of(TT);
+            auto flush = [&](uint32_t part_index) {       // slot * CW + run: 256 bytes per token pair each
                 v4f v;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {     // the four lanes of a quad hold terms of the same path
@@ -706,8 +724,18 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
                 if ((col & 3) == 0)
                     asm volatile("ds_write_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)"
                                  :
-                                 : "v"(part_lane + part_index * 256u), "v"(v)
+                                 : "v"(part_lane + part_index * (256u * PAIRS)), "v"(v)
                                  : "memory");
+                if constexpr (TT == 4) {          // tokens 2, 3
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] = quad_sum((quad & 1) ? acc3[r] : acc2[r]);
+                    if ((col & 3) == 0)
+                        asm volatile("ds_write_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)"
+                                     :
+                                     : "v"(part_lane + part_index * (256u * PAIRS) + 256u), "v"(v)
+                                     : "memory");
+                    acc3 = (v4f){0, 0, 0, 0};
+                }
                 acc0 = (v4f){0, 0, 0, 0};
                 acc1 = (v4f){0, 0, 0, 0};
                 acc2 = (v4f){0, 0, 0, 0};
@@ -805,6 +833,64 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
                                                [un] "=&s"(unwritten), [left] "=&s"(left)
                                              : [off] "v"(lane_off), [rs] "s"(rsrc), [cnt] "v"(waited_lds)
                                              : "vcc", "scc", "memory");
+                            } else if constexpr (TT == 4) {
+                                // Four tokens: the looks read first words only, and further and further
+                                // apart; the tile follows once they all show data.  (A look that fetched
+                                // the 8 KB tile as well, from every wavefront that waits, kept the
+                                // producers' second store of a row tile from landing for as long as the
+                                // looks went on.)
+                                int c0, c1, c2, c3, c4, c5, c6, c7;
+                                asm volatile("s_mov_b32 %[left], 0x40000\n"
+                                             "1:\n\t"
+                                             "s_nop 4\n\t"
+                                             "buffer_load_dword %[c0], %[off], %[rs], 0 offen sc1\n\t"
+                                             "buffer_load_dword %[c1], %[off], %[rs], 0 offen offset:1024 sc1\n\t"
+                                             "buffer_load_dword %[c2], %[off], %[rs], 0 offen offset:2048 sc1\n\t"
+                                             "buffer_load_dword %[c3], %[off], %[rs], 0 offen offset:3072 sc1\n\t"
+                                             "buffer_load_dword %[c4], %[off2], %[rs], 0 offen sc1\n\t"
+                                             "buffer_load_dword %[c5], %[off2], %[rs], 0 offen offset:1024 sc1\n\t"
+                                             "buffer_load_dword %[c6], %[off2], %[rs], 0 offen offset:2048 sc1\n\t"
+                                             "buffer_load_dword %[c7], %[off2], %[rs], 0 offen offset:3072 sc1\n\t"
+                                             "s_waitcnt vmcnt(0)\n\t"
+                                             "v_and_b32 %[c0], 0xff, %[c0]\n\t"
+                                             "v_and_b32 %[c1], 0xff, %[c1]\n\t"
+                                             "v_and_b32 %[c2], 0xff, %[c2]\n\t"
+                                             "v_and_b32 %[c3], 0xff, %[c3]\n\t"
+                                             "v_and_b32 %[c4], 0xff, %[c4]\n\t"
+                                             "v_and_b32 %[c5], 0xff, %[c5]\n\t"
+                                             "v_and_b32 %[c6], 0xff, %[c6]\n\t"
+                                             "v_and_b32 %[c7], 0xff, %[c7]\n\t"
+                                             "v_max3_u32 %[c0], %[c0], %[c1], %[c2]\n\t"
+                                             "v_max3_u32 %[c3], %[c3], %[c4], %[c5]\n\t"
+                                             "v_max3_u32 %[c0], %[c0], %[c3], %[c6]\n\t"
+                                             "v_max_u32 %[c0], %[c0], %[c7]\n\t"
+                                             "v_cmp_eq_u32 vcc, 0xff, %[c0]\n\t"
+                                             "s_mov_b64 %[un], vcc\n\t"
+                                             "s_cmp_eq_u64 %[un], 0\n\t"
+                                             "s_cbranch_scc1 2f\n\t"
+                                             RB_REPOLL_PAUSE
+                                             "s_sub_u32 %[left], %[left], 1\n\t"
+                                             "s_cmp_lg_u32 %[left], 0\n\t"
+                                             "s_cbranch_scc1 1b\n"
+                                             "2:\n\t"
+                                             "buffer_load_dwordx4 %[b0], %[off], %[rs], 0 offen sc1\n\t"
+                                             "buffer_load_dwordx4 %[b1], %[off], %[rs], 0 offen offset:1024 sc1\n\t"
+                                             "buffer_load_dwordx4 %[b2], %[off], %[rs], 0 offen offset:2048 sc1\n\t"
+                                             "buffer_load_dwordx4 %[b3], %[off], %[rs], 0 offen offset:3072 sc1\n\t"
+                                             "buffer_load_dwordx4 %[b4], %[off2], %[rs], 0 offen sc1\n\t"
+                                             "buffer_load_dwordx4 %[b5], %[off2], %[rs], 0 offen offset:1024 sc1\n\t"
+                                             "buffer_load_dwordx4 %[b6], %[off2], %[rs], 0 offen offset:2048 sc1\n\t"
+                                             "buffer_load_dwordx4 %[b7], %[off2], %[rs], 0 offen offset:3072 sc1\n\t"
+                                             "s_waitcnt vmcnt(0)\n\t"
+                                             "v_mov_b32 %[c0], 1\n\t"
+                                             "ds_add_u32 %[cnt], %[c0]"
+                                             : [b0] "+v"(B[s].r[0]), [b1] "+v"(B[s].r[1]), [b2] "+v"(B[s].r[2 % KOP]),
+                                               [b3] "+v"(B[s].r[3 % KOP]), [b4] "+v"(B[s].r[4 % KOP]), [b5] "+v"(B[s].r[5 % KOP]),
+                                               [b6] "+v"(B[s].r[6 % KOP]), [b7] "+v"(B[s].r[7 % KOP]), [c0] "=&v"(c0), [c1] "=&v"(c1),
+                                               [c2] "=&v"(c2), [c3] "=&v"(c3), [c4] "=&v"(c4), [c5] "=&v"(c5), [c6] "=&v"(c6),
+                                               [c7] "=&v"(c7), [un] "=&s"(unwritten), [left] "=&s"(left)
+                                             : [off] "v"(lane_off), [off2] "v"(lane_off + 4096u), [rs] "s"(rsrc), [cnt] "v"(waited_lds)
+                                             : "vcc", "scc", "memory");
                             } else {
                                 int c0, c1, c2, c3;
                                 asm volatile("s_mov_b32 %[left], 0x40000\n"
@@ -866,6 +952,7 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
                     if (c_slot_ptr == ring_end) c_slot_ptr = ring;
                     const BTile<TT> bt = B[s];
                     v8i b0, b1;
+                    [[maybe_unused]] v8i c0, c1;                  // four tokens: the operands of tokens 2, 3
                     if constexpr (TT == 1) {
                         // lanes 0..7 of a row of 16 hold the first four registers of their column; the
                         // other four sit eight lanes further on (row_shl:8).  Lanes 8..15 end up with
@@ -876,6 +963,15 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
                             b0[4 + i] = __builtin_amdgcn_update_dpp(0, bt.r[0][i], 0x108, 0xf, 0xf, true);
                             b1[i] = bt.r[1][i];
                             b1[4 + i] = __builtin_amdgcn_update_dpp(0, bt.r[1][i], 0x108, 0xf, 0xf, true);
+                        }
+                    } else if constexpr (TT == 4) {
+                        // per 128-column block: the image of tokens 0, 1 (two loads), then that of tokens 2, 3
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            b0[i] = bt.r[0][i]; b0[4 + i] = bt.r[1][i];
+                            c0[i] = bt.r[2 % KOP][i]; c0[4 + i] = bt.r[3 % KOP][i];
+                            b1[i] = bt.r[4 % KOP][i]; b1[4 + i] = bt.r[5 % KOP][i];
+                            c1[i] = bt.r[6 % KOP][i]; c1[4 + i] = bt.r[7 % KOP][i];
                         }
                     } else {
 #pragma unroll
@@ -890,6 +986,12 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
                         acc1 = mfma_signs(w.y, b0, acc1, c22, scale_b);
                         acc0 = mfma_signs(w.z, b1, acc0, c22, scale_b);
                         acc1 = mfma_signs(w.w, b1, acc1, c22, scale_b);
+                        if constexpr (TT == 4) {
+                            acc2 = mfma_signs(w.x, c0, acc2, c22, scale_b);
+                            acc3 = mfma_signs(w.y, c0, acc3, c22, scale_b);
+                            acc2 = mfma_signs(w.z, c1, acc2, c22, scale_b);
+                            acc3 = mfma_signs(w.w, c1, acc3, c22, scale_b);
+                        }
                     } else {
                         // (columns 0..127: paths 0, 1, 2), (columns 128..255: paths 0, 1, 2)
                         acc0 = mfma_signs(w.x, b0, acc0, c22, scale_b);
@@ -921,7 +1023,7 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
         const int half = lane >> 5;
         const int my_slot = ew + EWAVES * half;
         const int row = lane & 15, tok = (lane >> 4) & 1;
-        const int tokens = hdr_p->tokens;                 // of the activations
+        const int tokens = hdr_p->tokens;                 // of the activations (three use the layout of four)
 
         // Everything a stage's epilogue needs from memory sits in two flat tables indexed by
         // (stage, workgroup, slot) and is requested one stage ahead, while the compute wavefronts
@@ -962,9 +1064,11 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
             // ---- decoder blocks: what the epilogue takes from other workgroups' finishing
             // wavefronts is fetched while the compute wavefronts work.  Both are marked "not yet
             // written" (all ones) before the launch and looked at until they are not.
-            [[maybe_unused]] float rinv = 1.f, radd = 0.f;
+            [[maybe_unused]] float rinv[pairs_of(TT)], radd[pairs_of(TT)];
+#pragma unroll
+            for (int pr = 0; pr < pairs_of(TT); ++pr) { rinv[pr] = 1.f; radd[pr] = 0.f; }
             if constexpr (BLK) {
-                const int tk = (TT == 1 || KK == 3) ? 0 : tok;                // three paths: both lanes of a row hold token 0
+                const int tok_in_pair = (TT == 1 || KK == 3) ? 0 : tok;       // three paths: both lanes of a row hold token 0
                 // 1 / root mean square of the input, per token: the sums of squares of 16 columns
                 // each, added up by the 32 lanes of this slot's half in a fixed order
                 const int n_part = have_slot ? cur.x.n_part : 0;
@@ -982,15 +1086,15 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
                             __builtin_amdgcn_s_sleep(2);
                         }
                     }
-                    float tot[2];
+                    v4f tot;
                     // sums of squares come two at a time (their number is even: in % 32 == 0), four
                     // loads per lane in flight
                     const int n2 = n_part >> 1;
                     for (uint32_t left = BLOCK_POLLS;;) {
-                        tot[0] = tot[1] = 0.f;
+                        tot = (v4f){0.f, 0.f, 0.f, 0.f};
                         bool unwritten = false;
 #pragma unroll
-                        for (int t = 0; t < 2; ++t) {
+                        for (int t = 0; t < 4; ++t) {
                             if (t < tokens) {
                                 const auto *row_t = RB_GLOBAL(const uint64_t, cur.x.ssq_in) + (size_t)t * n2;
                                 for (int base = 0; base < n2; base += 128) {
@@ -1009,13 +1113,17 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
                                 }
                             }
                         }
-                        const size_t e = (size_t)tk * cur.r.out + grow;
-                        if (kind == RESID_CALLER && tk < tokens) radd = (float)RB_GLOBAL(_Float16, cur.x.resid)[e];
-                        if (kind == RESID_COPY && tk < tokens) {
-                            const uint32_t word = __hip_atomic_load(RB_GLOBAL(const uint32_t, cur.x.resid) + e, __ATOMIC_RELAXED,
-                                                                    __HIP_MEMORY_SCOPE_AGENT);
-                            unwritten |= word == 0xffffffffu;
-                            radd = (float)__builtin_bit_cast(_Float16, (uint16_t)word);
+#pragma unroll
+                        for (int pr = 0; pr < pairs_of(TT); ++pr) {
+                            const int tk = 2 * pr + tok_in_pair;
+                            const size_t e = (size_t)tk * cur.r.out + grow;
+                            if (kind == RESID_CALLER && tk < tokens) radd[pr] = (float)RB_GLOBAL(_Float16, cur.x.resid)[e];
+                            if (kind == RESID_COPY && tk < tokens) {
+                                const uint32_t word = __hip_atomic_load(RB_GLOBAL(const uint32_t, cur.x.resid) + e, __ATOMIC_RELAXED,
+                                                                        __HIP_MEMORY_SCOPE_AGENT);
+                                unwritten |= word == 0xffffffffu;
+                                radd[pr] = (float)__builtin_bit_cast(_Float16, (uint16_t)word);
+                            }
                         }
                         if (!__any(unwritten)) break;
                         if (--left == 0) {
@@ -1032,16 +1140,20 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
 #pragma unroll
                         for (int m = 1; m < 32; m <<= 1)
 #pragma unroll
-                            for (int t = 0; t < 2; ++t) tot[t] += __shfl_xor(tot[t], m);
-                        const float sum = tk == 0 ? tot[0] : tot[1];
-                        if (n_part > 0 && tk < tokens) rinv = rsqrtf(sum * cur.x.inv_n + cur.x.eps);
+                            for (int t = 0; t < 4; ++t) tot[t] += __shfl_xor(tot[t], m);
+#pragma unroll
+                        for (int pr = 0; pr < pairs_of(TT); ++pr) {
+                            const int tk = 2 * pr + tok_in_pair;
+                            const float sum = tk == 0 ? tot[0] : tk == 1 ? tot[1] : tk == 2 ? tot[2] : tot[3];
+                            if (n_part > 0 && tk < tokens) rinv[pr] = rsqrtf(sum * cur.x.inv_n + cur.x.eps);
+                        }
                     }
                 }
             }
             const int n_cons = have_slot ? cur.r.n_cons : 0;
             // where this lane's partial sums are, worked out before the barrier (what follows it is
             // on the path from the last matrix instruction of the stage to the stores)
-            uint32_t p_off = (uint32_t)(((st & 1) * MAXSLOT + my_slot) * CW * 64 + (TT == 1 ? 0 : tok * 16) + row);
+            uint32_t p_off = (uint32_t)(((st & 1) * MAXSLOT + my_slot) * CW * (64 * pairs_of(TT)) + (TT == 1 ? 0 : tok * 16) + row);
             asm volatile("" : "+v"(p_off));
             lds_barrier();                                    // partial sums complete
             // One token: the lanes of a row's second-token position are free, so the two lanes of a
@@ -1059,43 +1171,47 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
             // this lane's path of each reader's scales (selected value by value: an indexed array
             // would live in scratch memory)
             const float hsub[MAX_CONS] = {sub ? cur.a[3] : cur.a[2], sub ? cur.b[1] : cur.b[0], sub ? cur.b[3] : cur.b[2]};
-            const bool active = have_slot && (SPLIT || KK == 3 || tok < tokens) && grow < cur.r.out;
+            // four tokens: the pair of tokens 0, 1, then the pair 2, 3 (this lane's token is 2 * pair + tok)
+            constexpr int PAIRS = pairs_of(TT);
+#pragma unroll
+            for (int pair = 0; pair < PAIRS; ++pair) {
+            const bool active = have_slot && (SPLIT || KK == 3 || 2 * pair + tok < tokens) && grow < cur.r.out;
             float yf = 0.f, ysum = 0.f;
-            // partial sums of this lane's row: [run][path][token][row]
-            float *P = part + p_off;
+            // partial sums of this lane's row: [run][token pair][path][token][row]
+            float *P = part + p_off + pair * 64;
             if (active) {
                 // sum the partial sums of the runs in run order
                 float s0 = 0.f, s1 = 0.f;
                 if constexpr (SPLIT) {
                     float mine = 0.f;
 #pragma unroll
-                    for (int w = 0; w < CW; ++w) mine += P[w * 64 + sub * 32];
+                    for (int w = 0; w < CW; ++w) mine += P[w * (64 * PAIRS) + sub * 32];
                     const float other = xor16(mine);                // the lane with the same row and the other path
                     s0 = sub ? other : mine;
                     s1 = sub ? mine : other;
                 } else {
 #pragma unroll
                     for (int w = 0; w < CW; ++w) {
-                        s0 += P[w * 64];
-                        s1 += P[w * 64 + 32];
+                        s0 += P[w * (64 * PAIRS)];
+                        s1 += P[w * (64 * PAIRS) + 32];
                     }
                 }
                 ysum = path_sum(g_a, s0, g_b, s1);
                 if constexpr (KK == 3) ysum += xor16(ysum);                // paths 0 and 1 in one lane of the row, path 2 in the other
             }
             if constexpr (BLK) {
-                ysum *= rinv;                                          // the input was x / rms(x) (.) w
+                ysum *= rinv[pair];                                          // the input was x / rms(x) (.) w
                 const int role = have_slot ? cur.x.role : ROLE_PLAIN;
                 if (__any(role != ROLE_PLAIN)) {
                     // the same rows of the up projection sit in the other half of the wavefront
                     const float other = xor32(ysum);
                     if (role == ROLE_GATE) ysum = ysum / (1.f + __expf(-ysum)) * other;
                 }
-                ysum += radd;
+                ysum += radd[pair];
             }
             _Float16 y16 = (_Float16)0.f;
             const bool writes = active && (KK == 3 ? tok == 0 : (!SPLIT || sub == 0)) && (!BLK || cur.x.role != ROLE_UP);
-            const size_t y_at = (size_t)((SPLIT || KK == 3) ? 0 : tok) * cur.r.out + grow;
+            const size_t y_at = (size_t)((SPLIT || KK == 3) ? 0 : 2 * pair + tok) * cur.r.out + grow;
             if (active) {
                 y16 = (_Float16)ysum;                                        // round to nearest even
                 yf = (float)y16;
@@ -1108,7 +1224,7 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
                 const bool files = have_slot && cur.x.ssq_out != 0;
                 if (__any(files)) {
                     const float sq = row_sum(yf * yf);
-                    const int tk = (SPLIT || KK == 3) ? 0 : tok;
+                    const int tk = (SPLIT || KK == 3) ? 0 : 2 * pair + tok;
                     if (files && row == 0 && ((SPLIT || KK == 3) ? tok == 0 : true) && tk < tokens)
                         store_sc1_u32(cur.x.ssq_out + (uint64_t)tk * (uint32_t)cur.x.ssq_stride * 4u, __float_as_uint(sq));
                 }
@@ -1121,7 +1237,7 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
 #pragma unroll
                 for (int c = 0; c < MAX_CONS; ++c) {
                     if (c < n_cons) {                               // the same in all lanes of the half (two whole rows)
-                        uint8_t *const base = reinterpret_cast<uint8_t *>(cur.r.up[c]);
+                        uint8_t *const base = reinterpret_cast<uint8_t *>(cur.r.up[c]) + pair * 2048;
                         if constexpr (SPLIT) {
                             const v4i bytes = transpose_16x4_bytes(active ? expand4(hsub[c] * yf) : 0u);
                             uint8_t *dst = base + (4 * sub + row) * 16;
@@ -1143,15 +1259,16 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
             if (active) {
                 if constexpr (SPLIT) {
 #pragma unroll
-                    for (int w = 0; w < CW; ++w) P[w * 64 + sub * 32] = 0.f;
+                    for (int w = 0; w < CW; ++w) P[w * (64 * PAIRS) + sub * 32] = 0.f;
                 } else {
 #pragma unroll
                     for (int w = 0; w < CW; ++w) {
-                        P[w * 64] = 0.f;
-                        P[w * 64 + 32] = 0.f;
+                        P[w * (64 * PAIRS)] = 0.f;
+                        P[w * (64 * PAIRS) + 32] = 0.f;
                     }
                 }
             }
+            }   // token pairs
             // ---- tell the compute wavefronts, which may already be in the next stage, when that
             // stage's inputs have probably been written (one wavefront per workgroup)
             if (ew == 0 && st + 1 < n_stages) {
@@ -1223,12 +1340,11 @@ int device_groups()
     return cus;
 }
 
-static bool form_supported(const rb_layer *L, int T)
+bool layer_supported(const rb_layer *L, int T)
 {
     // three paths: one token (its three paths take the place of two tokens' two paths in the operand)
-    return ((L->K == 2 && T >= 1 && T <= 2) || (L->K == 3 && T == 1)) && L->in % 32 == 0 && L->in <= 65536;
+    return ((L->K == 2 && T >= 1 && T <= MAX_T) || (L->K == 3 && T == 1)) && L->in % 32 == 0 && L->in <= 65536;
 }
-bool layer_supported(const rb_layer *L, int T) { return form_supported(L, T) || flow::layer_supported(L, T); }
 
 // per op of a decoder block, at most: sums of squares of its output and of an input from outside,
 // and the copy of its output that a later op adds
@@ -1241,9 +1357,28 @@ static size_t block_aux_bound(const rb_layer *layers, int n_layers, int tokens)
     return most;
 }
 
+// Three and four tokens: plans with a wide layer take the kernel of rb_flow.hip, narrower ones the one here.  The other one saves
+// with the operands that a stage fetches and costs 4 us more once a launch and, in decoder blocks, more per stage.  Line by the weights
+// of the widest layer, us here and there: decoder blocks (d x f, number, tokens) 1024 x 2048 8 4 157 and 167, 1600 x 4800 8 4 219 and 224,
+// 2496 x 4992 4 4 126 and 133, 2048 x 5504 8 4 215 and 201, 2048 x 6144 8 4 205 and 207; from the line on 2048 x 8192 8 4 222 and 214,
+// 2624 x 6784 4 4 144 and 136, 3072 x 6144 4 4 130 and 116, 4992 x 9984 2 4 121 and 110.  Chains 1024 x 2048 2 3 37 and 41,
+// 1024 x 4096 8 4 141 and 136; from the line on 1920 x 3840 4 4 98 and 87, 1600 x 4800 8 4 196 and 162, 4096 x 11008 2 4 86 and 73.
+constexpr size_t FLOW_BLOCK_WEIGHTS = (size_t)16 << 20, FLOW_CHAIN_WEIGHTS = (size_t)6 << 20;
+static size_t weights_of(const rb_layer &L) { return (size_t)L.out * L.in; }
+static bool takes_flow(size_t widest, int tokens, bool block) { return tokens > 2 && widest >= (block ? FLOW_BLOCK_WEIGHTS : FLOW_CHAIN_WEIGHTS); }
+
 size_t plan_workspace_bytes(const rb_layer *layers, int n_layers, int n_ops, int T_in, bool block)
 {
-    if (T_in > 2) return flow::plan_workspace_bytes(layers, n_layers, n_ops, T_in, block);
+    // (the ops may leave the widest layers out: with layers on both sides of the line, room for either)
+    size_t widest = 0, narrowest = ~(size_t)0, other = 0;
+    for (int l = 0; l < n_layers; ++l) {
+        widest = std::max(widest, weights_of(layers[l]));
+        narrowest = std::min(narrowest, weights_of(layers[l]));
+    }
+    if (takes_flow(widest, T_in, block)) {
+        other = flow::plan_workspace_bytes(layers, n_layers, n_ops, T_in, block);
+        if (takes_flow(narrowest, T_in, block)) return other;
+    }
     int T = T_in;
     for (int l = 0; l < n_layers; ++l) T = std::max(T, layout_tokens(T_in, layers[l].K));
     // upper bound: every op could use the widest layer
@@ -1269,10 +1404,10 @@ size_t plan_workspace_bytes(const rb_layer *layers, int n_layers, int n_ops, int
     slots_per_op = std::min(slots_per_op, MAXSLOT);
     int K = 2;
     for (int l = 0; l < n_layers; ++l) K = std::max(K, layers[l].K);
-    return make_layout(n_ops, n_ops, (size_t)n_ops * (size_t)G * (size_t)slots_per_op, G, (int)CW, K, align_up(up_max, 256) * (size_t)n_ops,
-                       desc_blocks((uint32_t)(steps + RING_D)), desc_blocks((uint32_t)(steps + (size_t)nb_of(T) * n_ops)),
-                       block, block ? block_aux_bound(layers, n_layers, T_in) * (size_t)n_ops : 0, 0)
-        .total;
+    return std::max(other, make_layout(n_ops, n_ops, (size_t)n_ops * (size_t)G * (size_t)slots_per_op, G, (int)CW, K, align_up(up_max, 256) * (size_t)n_ops,
+                                       desc_blocks((uint32_t)(steps + RING_D)), desc_blocks((uint32_t)(steps + (size_t)nb_of(T) * n_ops)),
+                                       block, block ? block_aux_bound(layers, n_layers, T_in) * (size_t)n_ops : 0, 0)
+                               .total);
 }
 size_t plan_workspace_bytes(const rb_layer *layers, int n_layers, int n_ops, int T)
 {
@@ -1309,7 +1444,10 @@ static int prepare_any(const rb_layer *layers, const PlanOp *sops, int n_ops, ui
 {
     const int G = device_groups();
     if (G <= 0) return RB_ERR_HIP;
-    if (tokens > 2) {
+    if (block && tokens > MAX_T) return RB_ERR_UNSUPPORTED;
+    size_t widest = 0;
+    for (int n = 0; n < n_ops; ++n) widest = std::max(widest, weights_of(layers[sops[n].layer]));
+    if (takes_flow(widest, tokens, block)) {
         const int rc = flow::prepare(layers, sops, n_ops, bufs, norm_w, eps, block, tokens, workspace, workspace_bytes_, stream);
         if (rc == RB_OK || rc == RB_ERR_HIP) {                 // (what was refused leaves the plan that was there)
             std::lock_guard<std::mutex> lock(g_mutex);
@@ -1320,7 +1458,7 @@ static int prepare_any(const rb_layer *layers, const PlanOp *sops, int n_ops, ui
     // one kernel form per plan: every op has the same number of paths
     const int K = layers[sops[0].layer].K;
     for (int n = 0; n < n_ops; ++n)
-        if (layers[sops[n].layer].K != K || !form_supported(&layers[sops[n].layer], tokens)) return RB_ERR_UNSUPPORTED;
+        if (layers[sops[n].layer].K != K || !layer_supported(&layers[sops[n].layer], tokens)) return RB_ERR_UNSUPPORTED;
     if (block && K == 3 && tokens != 1) return RB_ERR_UNSUPPORTED;
     const int T = layout_tokens(tokens, K);            // tokens of the operand layout
 
@@ -1511,7 +1649,8 @@ static int prepare_any(const rb_layer *layers, const PlanOp *sops, int n_ops, ui
                            pr.oblocks);
     };
     if (T == 1) lists(desc_kernel<1>);
-    else lists(desc_kernel<2>);
+    else if (T == 2) lists(desc_kernel<2>);
+    else lists(desc_kernel<4>);
     hipLaunchKernelGGL(link_kernel, dim3(pr.n_stages, (G + LINK_GROUPS - 1) / LINK_GROUPS), dim3(256), 0, stream,
                        reinterpret_cast<const Header *>(ws), reinterpret_cast<const Op *>(ws + lay.ops),
                        reinterpret_cast<const Stage *>(ws + lay.stages), reinterpret_cast<SlotRec *>(ws + lay.slots),
@@ -1588,12 +1727,14 @@ int launch_plan(void *workspace, size_t workspace_bytes_, hipStream_t stream)
                            go_pause, pr.block ? reinterpret_cast<const SlotExt *>(ws + lay.ext) : nullptr);
         return RB_OK;
     };
-    const int rc = pr.block    ? (pr.K == 3 ? launch(stack_kernel<2, 3, true>, threads_of(2), LdsMap<cwaves_of(2), 3>::BYTES)
+    const int rc = pr.block    ? (pr.K == 3   ? launch(stack_kernel<2, 3, true>, threads_of(2), LdsMap<cwaves_of(2), 3>::BYTES)
                                   : pr.T == 1 ? launch(stack_kernel<1, 2, true>, threads_of(1), LdsMap<cwaves_of(1)>::BYTES)
-                                              : launch(stack_kernel<2, 2, true>, threads_of(2), LdsMap<cwaves_of(2)>::BYTES))
+                                  : pr.T == 2 ? launch(stack_kernel<2, 2, true>, threads_of(2), LdsMap<cwaves_of(2)>::BYTES)
+                                              : launch(stack_kernel<4, 2, true>, threads_of(4), LdsMap<cwaves_of(4), 2, 2>::BYTES))
                    : pr.K == 3 ? launch(stack_kernel<2, 3>, threads_of(2), LdsMap<cwaves_of(2), 3>::BYTES)
                    : pr.T == 1 ? launch(stack_kernel<1>, threads_of(1), LdsMap<cwaves_of(1)>::BYTES)
-                               : launch(stack_kernel<2>, threads_of(2), LdsMap<cwaves_of(2)>::BYTES);
+                   : pr.T == 2 ? launch(stack_kernel<2>, threads_of(2), LdsMap<cwaves_of(2)>::BYTES)
+                               : launch(stack_kernel<4>, threads_of(4), LdsMap<cwaves_of(4), 2, 2>::BYTES);
     if (rc != RB_OK) return rc;
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;
 }

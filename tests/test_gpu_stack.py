@@ -633,11 +633,14 @@ def test_prepared_odd_batches_on_pure_chains(T, n_chain):
 
 @pytest.mark.parametrize("T", [3, 4])
 @pytest.mark.parametrize("shapes", [
+    # narrow layers, which keep the step lists; the last one on either side of the line between the two kernels
+    [(1056, 544, 0), (96, 1056, 1), (3072, 96, 2), (2032, 3072, 3)],
+    [(1056, 544, 0), (96, 1056, 1), (3072, 96, 2), (2048, 3072, 3)],
     # (out, in, source): buffer 0 is the first input; source -1: an input of its own
     # one to three resident column tiles per wavefront, then a streamed run; a ragged end
     [(2080, 32, 0), (6144, 2080, 1), (8192, 6144, 2), (300, 8192, 3)],
     # eight row tiles per workgroup; a row of sign tiles longer than the ring that holds them
-    [(32768, 64, 0), (48, 32768, 1)],
+    [(32768, 64, 0), (208, 32768, 1)],
     # shares that end in another op, ops shorter than a share, an output with three readers
     [(4112, 1056, 0), (544, 1056, 0), (16, 1056, 0), (9000, 1056, 0), (1056, 544, 2), (704, 4128, -1), (544, 1056, 5), (512, 1056, 5), (80, 1056, 5)],
     # a stage of more tiles than the ring: seven row tiles of seventeen column tiles
@@ -680,11 +683,11 @@ def test_three_and_four_token_stack_forms(T, shapes):
 def test_one_workspace_for_plans_of_the_two_few_token_kernels(first, second):
     """A plan that is refused for want of room leaves the one that was there; one that is accepted takes its place."""
     rng = synth.child_rng(3, 501, first, second)
-    layers = [random_layer(rng, 2, 512, 512, gain=1.0 / (0.02 * 0.02 * np.sqrt(512))) for _ in range(2)]
+    layers = [random_layer(rng, 2, 2560, 2560, gain=1.0 / (0.02 * 0.02 * np.sqrt(2560))) for _ in range(2)]
     dev_layers = [to_device_layer(*l) for l in layers]
     stacks = []
     for T in (first, second):
-        bufs = [torch.from_numpy(synth.gaussian_activations(rng, T, 512)).cuda()] + [torch.zeros((T, 512), dtype=torch.float16, device="cuda") for _ in range(2)]
+        bufs = [torch.from_numpy(synth.gaussian_activations(rng, T, 2560)).cuda()] + [torch.zeros((T, 2560), dtype=torch.float16, device="cuda") for _ in range(2)]
         stacks.append(rb.Stack(dev_layers, [(0, 0, 1), (1, 1, 2)], bufs, T))
     size = max(s.ws_bytes for s in stacks)
     ws = torch.empty(size, dtype=torch.uint8, device="cuda")
