@@ -39,6 +39,11 @@ __host__ __device__ constexpr int run_begin(int wave, int CT) { return wave * CT
 // column tiles whose operands a wavefront holds in registers, 32 registers each; of a longer run they are fetched for every row tile
 constexpr int RESIDENT = 3;
 
+// The loading wavefront counts the sign tiles it has asked for, the others the first tile that each of them still needs; the counts may wrap.
+// Whether `more` tiles beyond the first `issued` fit a ring of `tiles`, with `used` the least of what is still needed.  Wavefronts that gave up a wait no
+// longer wait for tiles to arrive: what they still need may lie ahead of what has been asked for, and there is room then.
+__host__ __device__ constexpr bool ring_has_room(uint32_t issued, uint32_t more, uint32_t used, int tiles) { return (int32_t)(issued + more - used) <= tiles; }
+
 // Expanded input ("right operand") of one op, stored as the register image the MFMA wants.
 // The 8-bit right operand of v_mfma_scale_f32_16x16x128_f8f6f4 keeps, in lane col + 16 * q
 // (col = operand column, q = 0..3), contraction indices 16q..16q+15 in its first four registers and

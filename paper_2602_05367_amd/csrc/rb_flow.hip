@@ -409,7 +409,7 @@ __global__ __launch_bounds__(THREADS, 3) void flow_kernel(const Work *__restrict
                         told = issued - FLIGHT;
                         if (lane == 0) lds_write(lds_at(Lds::LANDED_OFF), told);
                     }
-                    if (issued + (uint32_t)m - used > (uint32_t)TILES) {
+                    if (!ring_has_room(issued, (uint32_t)m, used, TILES)) {
                         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                         told = issued;
                         if (lane == 0) lds_write(lds_at(Lds::LANDED_OFF), told);
@@ -420,7 +420,7 @@ __global__ __launch_bounds__(THREADS, 3) void flow_kernel(const Work *__restrict
 #pragma unroll
                             for (int i = 1; i < CWAVES; i <<= 1) u = (uint32_t)min((int)u, __shfl_xor((int)u, i));
                             used = issued + (uint32_t)__builtin_amdgcn_readfirstlane((int)u);
-                            if (issued + (uint32_t)m - used <= (uint32_t)TILES) break;
+                            if (ring_has_room(issued, (uint32_t)m, used, TILES)) break;
                             __builtin_amdgcn_s_sleep(1);
                         }
                     }

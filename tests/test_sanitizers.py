@@ -34,3 +34,13 @@ def test_requests_of_the_few_token_kernel_stay_inside_a_layer(tmp_path):
                            "-I", os.path.join(ROOT, "paper_2602_05367_amd", "csrc"), os.path.join(ROOT, "tests", "sanitize", "units.cpp"), "-o", exe])
     res = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert res.returncode == 0 and "all in bounds" in res.stdout, res.stdout
+
+
+def test_the_ring_of_sign_tiles_lets_everyone_come_to_the_end(tmp_path):
+    """Also a loading wavefront whose readers have given up and run ahead of it: a wait without an end would hang the GPU."""
+    exe = str(tmp_path / "ring_driver")
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-fsanitize=address,undefined", "-static-libasan", "-fno-sanitize-recover=all", "-g", "-O1", "-D__host__=", "-D__device__=",
+                           "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2602_05367_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "sanitize", "ring.cpp"), "-o", exe])
+    res = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert res.returncode == 0 and "everyone came to the end" in res.stdout, res.stdout
