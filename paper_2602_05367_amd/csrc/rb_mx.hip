@@ -1369,16 +1369,11 @@ static bool takes_flow(size_t widest, int tokens, bool block) { return tokens > 
 
 size_t plan_workspace_bytes(const rb_layer *layers, int n_layers, int n_ops, int T_in, bool block)
 {
-    // (the ops may leave the widest layers out: with layers on both sides of the line, room for either)
-    size_t widest = 0, narrowest = ~(size_t)0, other = 0;
-    for (int l = 0; l < n_layers; ++l) {
-        widest = std::max(widest, weights_of(layers[l]));
-        narrowest = std::min(narrowest, weights_of(layers[l]));
-    }
-    if (takes_flow(widest, T_in, block)) {
-        other = flow::plan_workspace_bytes(layers, n_layers, n_ops, T_in, block);
-        if (takes_flow(narrowest, T_in, block)) return other;
-    }
+    // (room for the step lists also where the plan takes the other kernel, which needs less: a workspace sized for the most
+    // tokens has served calls of fewer always, and the ops of a call may leave the widest layers out)
+    size_t widest = 0;
+    for (int l = 0; l < n_layers; ++l) widest = std::max(widest, weights_of(layers[l]));
+    const size_t other = takes_flow(widest, T_in, block) ? flow::plan_workspace_bytes(layers, n_layers, n_ops, T_in, block) : 0;
     int T = T_in;
     for (int l = 0; l < n_layers; ++l) T = std::max(T, layout_tokens(T_in, layers[l].K));
     // upper bound: every op could use the widest layer

@@ -2,6 +2,7 @@
 ops the two implementations drift apart by rounding alone, so parity is
 teacher-forced: the oracle recomputes every op from the input the GPU run
 actually used, and that op's output must agree to the usual tolerance."""
+import ctypes
 import sys
 
 import numpy as np
@@ -716,3 +717,34 @@ def test_one_workspace_for_plans_of_the_two_few_token_kernels(first, second):
     one.prepare()
     check(one)
     one.forget()
+
+
+@pytest.mark.parametrize("T", [1, 2])
+def test_a_workspace_sized_for_four_tokens_serves_one_and_two(T):
+    """A prepared chain of 64 wide layers, the same in one call, and a single call, all on the matrix-core kernels."""
+    n = 64
+    rng = synth.child_rng(3, 502, T)
+    wide = [to_device_layer(*random_layer(rng, 2, out, inn, gain=1.0 / (0.02 * 0.02 * np.sqrt(inn)))) for out, inn in ((11008, 4096), (4096, 11008))]
+    bufs = [torch.from_numpy(synth.gaussian_activations(rng, T, 4096)).cuda()]
+    bufs += [torch.zeros((T, wide[i % 2].out), dtype=torch.float16, device="cuda") for i in range(n)]
+    stack = rb.Stack(wide, [(i % 2, i, i + 1) for i in range(n)], bufs, T)
+    stack.ws_bytes = rb.rb_workspace_bytes(wide, n, 4)
+    stack.ws = torch.empty(stack.ws_bytes, dtype=torch.uint8, device="cuda")
+    print(f"chain of {n} layers, T={T}, workspace for four tokens", flush=True)
+    stack.prepare()
+    stack.run_prepared()
+    torch.cuda.synchronize()
+    assert stack.status() == rb.RB_OK and rb.rb_last_path() == rb.RB_PATH_MX
+    prepared = bufs[n].clone()
+    stack.forget()
+    bufs[n].zero_()
+    stack.run()
+    torch.cuda.synchronize()
+    assert rb.rb_last_path() == rb.RB_PATH_MX and torch.equal(bufs[n], prepared)
+    for layer, x in zip(wide, bufs):
+        size = rb.rb_workspace_bytes([layer], 1, 4)
+        ws, y = torch.empty(size, dtype=torch.uint8, device="cuda"), torch.zeros((T, layer.out), dtype=torch.float16, device="cuda")
+        L = layer.struct()
+        assert rb.lib.rb_linear_gemm(ctypes.byref(L), x.data_ptr(), y.data_ptr(), T, rb.RB_F16, rb.RB_F16, ws.data_ptr(), size, None) == rb.RB_OK
+        torch.cuda.synchronize()
+        assert rb.rb_last_path() == rb.RB_PATH_MX and torch.equal(y, bufs[1 + wide.index(layer)])

@@ -222,3 +222,13 @@ def test_inputs_beyond_32_bit_offsets_are_not_for_the_few_token_kernel():
         return rb.lib.rb_workspace_bytes(ctypes.byref(L), 1, n_ops, T)
     assert need(64, 2 ** 26 - 32) == 64 * (2 ** 26 - 32) * 2 and need(64, 2 ** 26) == 0
     assert need(16, 2 ** 28 - 32, 2) == 16 * (2 ** 28 - 32) * 2 and need(16, 2 ** 28, 2) == 0
+
+
+@pytest.mark.parametrize("shapes,n_ops", [([(4096, 4096)], 1), ([(28672, 8192)], 1), ([(4096, 4096), (11008, 4096), (4096, 11008)], 21), ([(96, 64), (4096, 4096)], 2),
+                                          ([(512, 1376), (1376, 512)], 6)])
+def test_a_workspace_for_four_tokens_serves_fewer(shapes, n_ops):
+    """Three and four tokens of wide layers run on a kernel that needs less than that of two; programs size a workspace once, for the most tokens."""
+    layers = (rb.binding.rb_layer * len(shapes))(*[rb.binding.rb_layer(o, i, 2, 0x1000, 0x2000, 0x3000) for o, i in shapes])
+    for need in (rb.lib.rb_workspace_bytes, rb.lib.rb_block_workspace_bytes):
+        two, three, four = (need(layers, len(shapes), n_ops, T) for T in (2, 3, 4))
+        assert two <= three <= four
