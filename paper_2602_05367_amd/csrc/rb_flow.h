@@ -80,7 +80,8 @@ struct alignas(64) Op {
     const float *ssq_in;      // [4][n_part]: per token, sums of squares of 16 input rows each
     float *ssq_out;           // [4][RT]: the same of this op's output, for readers that normalise it
     uint32_t *rcopy;          // [T][out]: the fp16 output once more, one word each, for an op that adds it later
-    const void *resid;        // what is added to the result: fp16 [T][out] of the caller or another op's rcopy
+    const void *resid;        // what is added to the result: fp16 [T][out] of the caller, the same put aside, or another op's rcopy
+    const uint16_t *resid_src;   // the caller's buffer that is put aside (null: none)
     int resid_kind;           // RESID_*
     int role;                 // ROLE_*
     int n_part;

@@ -42,6 +42,7 @@
 #include "rb_layout.h"
 #include "rb_flow.h"
 #include "rb_mx_device.h"
+#include "rb_plan.h"
 
 namespace rb {
 namespace flow {
@@ -60,14 +61,6 @@ constexpr int GO_PAUSE = 48;
 // between two looks at a tile that was not yet written (units of 64 clocks): the first 64 come quickly, the rest far
 // apart (wavefronts that look too often keep the stores they wait for from landing)
 constexpr uint32_t MAX_LOOKS = 0x40000, QUICK_LOOKS = 64;
-
-// ---------------------------------------------------------------- helpers ---
-// weight of the normalisation in front of the op at input column j (1 where there is none): it is
-// folded into the op's input scales
-__device__ __forceinline__ float norm_weight(const Op &op, int j)
-{
-    return op.norm_w ? __half2float(reinterpret_cast<const __half *>(op.norm_w)[j]) : 1.f;
-}
 
 // ------------------------------------------------------------ prep kernel ---
 // One workgroup per op: power-of-two scale of each path's input scales and the zero fill of the
@@ -226,23 +219,6 @@ __device__ __forceinline__ void expand_part(const Op *ops, const int *which, int
             make_uint4(out[t][0], out[t][1], out[t][2], out[t][3]);
 }
 
-// Sums of squares of an input from outside that an op normalises: 16 columns per entry, [token][entry], as the
-// finishing wavefronts file them for inputs written inside a launch.  One workgroup per (op, token).
-__device__ __forceinline__ void ssq_part(const Op *ops, const int *which, int bx, int tok)
-{
-    const Op &op = ops[which[bx]];
-    if (!op.norm_w || op.dep >= 0) return;
-    float *out = const_cast<float *>(op.ssq_in);
-    for (int e = threadIdx.x; e < op.n_part; e += 256) {
-        float sum = 0.f;
-        for (int j = 16 * e; j < min(16 * e + 16, op.in); ++j) {
-            const float x = __half2float(reinterpret_cast<const __half *>(op.x)[(size_t)tok * op.in + j]);
-            sum += x * x;
-        }
-        out[(size_t)tok * op.n_part + e] = sum;
-    }
-}
-
 // Before every launch: the expanded input of every op that a producer of this
 // launch will write is set to "not written yet" (0xff in every byte of the 16-byte groups of real
 // columns: no bf8 term of a finite value is 0xff; padding columns read as zero).  POISON_SPLIT
@@ -272,10 +248,10 @@ __device__ __forceinline__ void poison_part(const Op *ops, int n_ops, uint4 *aux
 // What goes before the flow kernel in every run, as one launch: the first n_poison workgroups mark
 // inputs (they write the expanded inputs of ops fed from inside the launch), the next n_expand
 // expand the inputs from outside (ex x ey x ez workgroups; they write those of the other ops), and
-// in a decoder block the rest add up the squares of the inputs from outside that an op normalises
-// (one workgroup per such input and token).
+// in a decoder block the next n_ssq add up the squares of the inputs from outside that an op normalises
+// (one workgroup per such input and token) and the rest put aside what ops add of the caller's.
 __global__ __launch_bounds__(256) void before_kernel(const Op *ops, int n_ops, const int *which, int n_poison,
-                                                     int n_expand, int ex, int ey, uint4 *aux, size_t aux16)
+                                                     int n_expand, int ex, int ey, int n_ssq, uint4 *aux, size_t aux16)
 {
     const int b = (int)blockIdx.x;
     if (b < n_poison) {
@@ -288,7 +264,11 @@ __global__ __launch_bounds__(256) void before_kernel(const Op *ops, int n_ops, c
         return;
     }
     const int q = e - n_expand;
-    ssq_part(ops, which, q / ey, q % ey);
+    if (q < n_ssq) {
+        ssq_part(ops, which, q / ey, q % ey);
+        return;
+    }
+    aside_part(ops, ey, (q - n_ssq) / ASIDE_SPLIT, (q - n_ssq) % ASIDE_SPLIT);
 }
 
 // ---------------------------------------------------------- flow kernel ---
@@ -901,11 +881,6 @@ static Layout make_layout(int n_ops, int n_stages, int G, size_t n_records, size
     return L;
 }
 
-bool layer_supported(const rb_layer *L, int tokens)
-{
-    return L->K == K && tokens >= 3 && tokens <= MAX_T && L->in % 32 == 0 && L->in <= 65536;
-}
-
 // per op of a decoder block, at most: sums of squares of its output and of an input from outside,
 // and the copy of its output that a later op adds
 static size_t block_aux_bound(const rb_layer *layers, int n_layers, int tokens)
@@ -940,6 +915,7 @@ struct Prepared {
     bool chained = false;                   // some op reads what another op of the launch writes
     bool block = false;                     // a decoder block: the kernel form with the epilogues
     bool ext_norm = false;                  // some op normalises an input from outside
+    bool aside = false;                     // some op adds what has to be put aside before the launch
     float eps = 0.f;
     // host memory the plan's tables are copied from: pageable, so it must outlive the queued copies
     std::shared_ptr<std::vector<uint8_t>> blob;
@@ -948,22 +924,18 @@ struct Prepared {
 static std::mutex g_mutex;
 static std::map<const void *, Prepared> g_prepared;
 
-int prepare(const rb_layer *layers, const PlanOp *sops, int n_ops, uint16_t *const *bufs,
+int prepare(const rb_layer *layers, const PlanOp *sops, const OpLinks *links, int n_ops, uint16_t *const *bufs,
                        const uint16_t *const *norm_w, float eps, bool block, int tokens, void *workspace,
                        size_t workspace_bytes_, hipStream_t stream)
 {
     const int G = device_groups();
     if (G <= 0) return RB_ERR_HIP;
-    for (int n = 0; n < n_ops; ++n)
-        if (!layer_supported(&layers[sops[n].layer], tokens)) return RB_ERR_UNSUPPORTED;
 
     // ---- ops, consumers, stages
     std::vector<Op> ops((size_t)n_ops);
     std::vector<int> expand_list;
     size_t up_total = 0;
     std::vector<size_t> up_off((size_t)n_ops);
-    std::vector<bool> need_ssq((size_t)n_ops, false), need_rcopy((size_t)n_ops, false);
-    std::vector<int> resid_from((size_t)n_ops, -1);
     for (int n = 0; n < n_ops; ++n) {
         const rb_layer &L = layers[sops[n].layer];
         Op &o = ops[(size_t)n];
@@ -979,40 +951,18 @@ int prepare(const rb_layer *layers, const PlanOp *sops, int n_ops, uint16_t *con
         o.RT = row_tiles(L.out); o.CT = col_tiles(L.in);
         up_off[(size_t)n] = up_total;
         up_total += align_up(up_bytes(L.in), 256);
-        // producer of this op's input: the last earlier op that writes the same buffer
-        int producer = -1;
-        for (int m = n - 1; m >= 0; --m)
-            if (sops[m].dst == sops[n].src) { producer = m; break; }
-        o.dep = producer;
-        if (o.norm_w) {
-            o.n_part = (L.in + 15) / 16;
-            if (producer >= 0) need_ssq[(size_t)producer] = true;
-        }
-        // what is added: the caller's buffer as it was before the launch, or what an earlier op wrote there
+        const OpLinks &l = links[n];
+        o.dep = l.producer;
+        if (o.norm_w) o.n_part = (L.in + 15) / 16;
         if (sops[n].add >= 0) {
-            int writer = -1;
-            for (int m = n - 1; m >= 0; --m)
-                if (sops[m].dst == sops[n].add) { writer = m; break; }
-            if (writer >= 0) {
-                if (ops[(size_t)writer].out != L.out) return RB_ERR_SHAPE;
-                need_rcopy[(size_t)writer] = true;
-                resid_from[(size_t)n] = writer;
-                o.resid_kind = RESID_COPY;
-            } else {
-                o.resid = bufs[sops[n].add];
-                o.resid_kind = RESID_CALLER;
-            }
+            o.resid_kind = l.addend >= 0 ? RESID_COPY : RESID_CALLER;
+            if (l.aside) o.resid_src = bufs[sops[n].add];
+            else if (l.addend < 0) o.resid = bufs[sops[n].add];
         }
-        if (producer < 0) {
-            expand_list.push_back(n);
-        } else {
-            Op &pr = ops[(size_t)producer];
-            if (pr.n_cons >= MAX_CONS) return RB_ERR_UNSUPPORTED;
-            if (pr.out != o.in) return RB_ERR_SHAPE;
-            pr.cons[pr.n_cons++] = n;
-        }
+        o.n_cons = l.n_cons;
+        std::copy(l.cons, l.cons + l.n_cons, o.cons);
+        if (l.producer < 0) expand_list.push_back(n);
     }
-    if (expand_list.size() > MAX_EXPAND || n_ops > MAX_OPS) return RB_ERR_UNSUPPORTED;
     std::vector<Stage> stages;
     size_t n_records = 0;
     for (int op0 = 0; op0 < n_ops;) {
@@ -1065,18 +1015,23 @@ int prepare(const rb_layer *layers, const PlanOp *sops, int n_ops, uint16_t *con
     pr.n_ops = n_ops; pr.n_stages = (int)stages.size(); pr.G = G; pr.tokens = tokens;
     pr.n_expand = (int)expand_list.size();
     for (int n : expand_list) pr.max_expand_in = std::max(pr.max_expand_in, ops[(size_t)n].in);
-    for (int n = 0; n < n_ops; ++n) pr.chained = pr.chained || ops[(size_t)n].dep >= 0 || resid_from[(size_t)n] >= 0;
+    for (int n = 0; n < n_ops; ++n) pr.chained = pr.chained || ops[(size_t)n].dep >= 0 || links[n].addend >= 0;
     // decoder blocks: what finishing wavefronts hand to each other (marked unwritten before every
-    // launch), then the sums of squares of inputs from outside
-    std::vector<size_t> ssq_off((size_t)n_ops, 0), rcopy_off((size_t)n_ops, 0), ext_off((size_t)n_ops, 0);
+    // launch), then the sums of squares of inputs from outside and what is put aside
+    std::vector<size_t> ssq_off((size_t)n_ops, 0), rcopy_off((size_t)n_ops, 0), ext_off((size_t)n_ops, 0), aside_off((size_t)n_ops, 0);
     size_t aux_poison = 0, aux_rest = 0;
     for (int n = 0; n < n_ops && block; ++n) {
-        if (need_ssq[(size_t)n]) { ssq_off[(size_t)n] = aux_poison; aux_poison += align_up((size_t)ops[(size_t)n].RT * 16, 256); }
-        if (need_rcopy[(size_t)n]) { rcopy_off[(size_t)n] = aux_poison; aux_poison += align_up((size_t)tokens * ops[(size_t)n].out * 4, 256); }
+        if (links[n].squares) { ssq_off[(size_t)n] = aux_poison; aux_poison += align_up((size_t)ops[(size_t)n].RT * 16, 256); }
+        if (links[n].copied) { rcopy_off[(size_t)n] = aux_poison; aux_poison += align_up((size_t)tokens * ops[(size_t)n].out * 4, 256); }
         if (ops[(size_t)n].norm_w && ops[(size_t)n].dep < 0) {
             ext_off[(size_t)n] = aux_rest;
             aux_rest += align_up((size_t)ops[(size_t)n].n_part * 16, 256);
             pr.ext_norm = true;
+        }
+        if (links[n].aside) {
+            aside_off[(size_t)n] = aux_rest;
+            aux_rest += align_up((size_t)tokens * ops[(size_t)n].out * 2, 256);
+            pr.aside = true;
         }
     }
     pr.block = block;
@@ -1090,15 +1045,16 @@ int prepare(const rb_layer *layers, const PlanOp *sops, int n_ops, uint16_t *con
     for (int n = 0; n < n_ops; ++n) ops[(size_t)n].up = ws + lay.up + up_off[(size_t)n];
     for (int n = 0; n < n_ops && block; ++n) {
         Op &o = ops[(size_t)n];
-        if (need_ssq[(size_t)n]) o.ssq_out = reinterpret_cast<float *>(ws + lay.aux + ssq_off[(size_t)n]);
-        if (need_rcopy[(size_t)n]) o.rcopy = reinterpret_cast<uint32_t *>(ws + lay.aux + rcopy_off[(size_t)n]);
+        if (links[n].squares) o.ssq_out = reinterpret_cast<float *>(ws + lay.aux + ssq_off[(size_t)n]);
+        if (links[n].copied) o.rcopy = reinterpret_cast<uint32_t *>(ws + lay.aux + rcopy_off[(size_t)n]);
     }
     for (int n = 0; n < n_ops && block; ++n) {
         Op &o = ops[(size_t)n];
         if (o.norm_w)
             o.ssq_in = o.dep >= 0 ? ops[(size_t)o.dep].ssq_out
                                   : reinterpret_cast<const float *>(ws + lay.aux + lay.aux_poison + ext_off[(size_t)n]);
-        if (resid_from[(size_t)n] >= 0) o.resid = ops[(size_t)resid_from[(size_t)n]].rcopy;
+        if (links[n].addend >= 0) o.resid = ops[(size_t)links[n].addend].rcopy;
+        if (links[n].aside) o.resid = ws + lay.aux + lay.aux_poison + aside_off[(size_t)n];
     }
 
     // ---- upload: stream-ordered copies out of host memory that the plan's record keeps alive
@@ -1143,10 +1099,10 @@ int launch(void *workspace, size_t workspace_bytes_, int pause, hipStream_t stre
     const int n_poison = pr.chained ? (pr.n_ops + (lay.aux_poison ? 1 : 0)) * POISON_SPLIT : 0;
     const int ex = (pr.max_expand_in / 16 * K + 255) / 256, ey = pr.tokens;
     const int n_expand_groups = pr.n_expand > 0 ? ex * ey * pr.n_expand : 0;
-    const int n_ssq_groups = pr.ext_norm ? pr.n_expand * ey : 0;
-    if (n_poison + n_expand_groups + n_ssq_groups > 0)
-        hipLaunchKernelGGL(before_kernel, dim3((unsigned)(n_poison + n_expand_groups + n_ssq_groups)), dim3(256), 0, stream, d_ops,
-                           pr.n_ops, reinterpret_cast<const int *>(ws + lay.which), n_poison, n_expand_groups, ex, ey,
+    const int n_ssq_groups = pr.ext_norm ? pr.n_expand * ey : 0, n_aside_groups = pr.aside ? pr.n_ops * ASIDE_SPLIT : 0;
+    if (n_poison + n_expand_groups + n_ssq_groups + n_aside_groups > 0)
+        hipLaunchKernelGGL(before_kernel, dim3((unsigned)(n_poison + n_expand_groups + n_ssq_groups + n_aside_groups)), dim3(256), 0, stream, d_ops,
+                           pr.n_ops, reinterpret_cast<const int *>(ws + lay.which), n_poison, n_expand_groups, ex, ey, n_ssq_groups,
                            reinterpret_cast<uint4 *>(ws + lay.aux), lay.aux_poison / 16);
     const int go_pause = pause < 0 ? GO_PAUSE : pause / 64;          // s_sleep units
     auto launch_form = [&](auto kernel) -> int {

@@ -81,20 +81,14 @@ void forget_plan(const void *workspace);
 }  // namespace batch
 
 namespace mx {
-// one op of a plan: a layer between two buffers and, in a decoder block, what surrounds it
-struct PlanOp {
-    int layer, src, dst;      // dst < 0: the result leaves through another op (ROLE_UP)
-    int norm;                 // >= 0: which weight vector normalises the input
-    int add;                  // >= 0: the buffer added to the result
-    int role;
-};
+struct PlanOp;
+struct OpLinks;
 }  // namespace mx
 
 namespace flow {
 // the persistent kernel for three and four tokens of two-path layers; its plans are prepared, run, checked and forgotten through namespace mx
-bool layer_supported(const rb_layer *L, int T);
 size_t plan_workspace_bytes(const rb_layer *layers, int n_layers, int n_ops, int tokens, bool block);
-int prepare(const rb_layer *layers, const mx::PlanOp *sops, int n_ops, uint16_t *const *bufs, const uint16_t *const *norm_w, float eps, bool block,
+int prepare(const rb_layer *layers, const mx::PlanOp *sops, const mx::OpLinks *links, int n_ops, uint16_t *const *bufs, const uint16_t *const *norm_w, float eps, bool block,
             int tokens, void *workspace, size_t workspace_bytes, hipStream_t stream);
 int launch(void *workspace, size_t workspace_bytes, int pause, hipStream_t stream);      // RB_ERR_UNSUPPORTED: no plan of this kind
 const void *marks(const void *workspace);

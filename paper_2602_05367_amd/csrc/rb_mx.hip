@@ -42,6 +42,7 @@
 #include "rb_layout.h"
 #include "rb_mx.h"
 #include "rb_mx_device.h"
+#include "rb_plan.h"
 
 namespace rb {
 namespace mx {
@@ -72,13 +73,6 @@ constexpr int TILE_PAUSE_2 = 44;    // ... two tokens
 __device__ __forceinline__ uint32_t lds_addr(const void *p)
 {
     return (uint32_t)(size_t)RB_LDS(p);
-}
-
-// weight of the normalisation in front of the op at input column j (1 where there is none): it is
-// folded into the op's input scales
-__device__ __forceinline__ float norm_weight(const Op &op, int j)
-{
-    return op.norm_w ? __half2float(reinterpret_cast<const __half *>(op.norm_w)[j]) : 1.f;
 }
 
 // ------------------------------------------------------------ prep kernel ---
@@ -341,23 +335,6 @@ __device__ __forceinline__ void expand_part(const Header *hdr, const Op *ops, co
             make_uint4(out[t][0], out[t][1], out[t][2], out[t][3]);
 }
 
-// Sums of squares of an input from outside that an op normalises: 16 columns per entry, [token][entry], as the
-// finishing wavefronts file them for inputs written inside a launch.  One workgroup per (op, token).
-__device__ __forceinline__ void ssq_part(const Op *ops, const int *which, int bx, int tok)
-{
-    const Op &op = ops[which[bx]];
-    if (!op.norm_w || op.dep >= 0) return;
-    float *out = const_cast<float *>(op.ssq_in);
-    for (int e = threadIdx.x; e < op.n_part; e += 256) {
-        float sum = 0.f;
-        for (int j = 16 * e; j < min(16 * e + 16, op.in); ++j) {
-            const float x = __half2float(reinterpret_cast<const __half *>(op.x)[(size_t)tok * op.in + j]);
-            sum += x * x;
-        }
-        out[(size_t)tok * op.n_part + e] = sum;
-    }
-}
-
 // Before every launch: the expanded input of every op that a producer of this
 // launch will write is set to "not written yet" (0xff in every byte of the 16-byte groups of real
 // columns: no bf8 term of a finite value is 0xff; padding columns read as zero).  POISON_SPLIT
@@ -391,10 +368,10 @@ __device__ __forceinline__ void poison_part(const Op *ops, int T, int n_ops, uin
 // What goes before the stack kernel in every run, as one launch: the first n_poison workgroups mark
 // inputs (they write the expanded inputs of ops fed from inside the launch), the next n_expand
 // expand the inputs from outside (ex x ey x ez workgroups; they write those of the other ops), and
-// in a decoder block the rest add up the squares of the inputs from outside that an op normalises
-// (one workgroup per such input and token).
+// in a decoder block the next n_ssq add up the squares of the inputs from outside that an op normalises
+// (one workgroup per such input and token) and the rest put aside what ops add of the caller's.
 __global__ __launch_bounds__(256) void before_kernel(const Header *hdr, const Op *ops, const int *which, int n_poison,
-                                                     int n_expand, int ex, int ey, uint4 *aux, size_t aux16)
+                                                     int n_expand, int ex, int ey, int n_ssq, uint4 *aux, size_t aux16)
 {
     const int b = (int)blockIdx.x;
     if (b < n_poison) {
@@ -407,7 +384,11 @@ __global__ __launch_bounds__(256) void before_kernel(const Header *hdr, const Op
         return;
     }
     const int q = e - n_expand;
-    ssq_part(ops, which, q / ey, q % ey);
+    if (q < n_ssq) {
+        ssq_part(ops, which, q / ey, q % ey);
+        return;
+    }
+    aside_part(ops, ey, (q - n_ssq) / ASIDE_SPLIT, (q - n_ssq) % ASIDE_SPLIT);
 }
 
 // ---------------------------------------------------------- stack kernel ---
@@ -1422,6 +1403,7 @@ struct Prepared {
     bool chained = false;                   // some op reads what another op of the launch writes
     bool block = false;                     // a decoder block: the kernel form with the epilogues
     bool ext_norm = false;                  // some op normalises an input from outside
+    bool aside = false;                     // some op adds what has to be put aside before the launch
     // host memory the plan's tables are copied from: pageable, so it must outlive the queued copies
     std::shared_ptr<std::vector<uint8_t>> blob;
     std::shared_ptr<std::vector<int>> which;
@@ -1440,30 +1422,31 @@ static int prepare_any(const rb_layer *layers, const PlanOp *sops, int n_ops, ui
     const int G = device_groups();
     if (G <= 0) return RB_ERR_HIP;
     if (block && tokens > MAX_T) return RB_ERR_UNSUPPORTED;
-    size_t widest = 0;
-    for (int n = 0; n < n_ops; ++n) widest = std::max(widest, weights_of(layers[sops[n].layer]));
-    if (takes_flow(widest, tokens, block)) {
-        const int rc = flow::prepare(layers, sops, n_ops, bufs, norm_w, eps, block, tokens, workspace, workspace_bytes_, stream);
-        if (rc == RB_OK || rc == RB_ERR_HIP) {                 // (what was refused leaves the plan that was there)
-            std::lock_guard<std::mutex> lock(g_mutex);
-            g_prepared.erase(workspace);
-        }
-        return rc;
-    }
     // one kernel form per plan: every op has the same number of paths
     const int K = layers[sops[0].layer].K;
     for (int n = 0; n < n_ops; ++n)
         if (layers[sops[n].layer].K != K || !layer_supported(&layers[sops[n].layer], tokens)) return RB_ERR_UNSUPPORTED;
     if (block && K == 3 && tokens != 1) return RB_ERR_UNSUPPORTED;
     const int T = layout_tokens(tokens, K);            // tokens of the operand layout
+    std::vector<OpLinks> all_links;
+    if (const int rc = link_ops(layers, sops, n_ops, all_links); rc != RB_OK) return rc;
+    const OpLinks *const links = all_links.data();
+    size_t widest = 0;
+    for (int n = 0; n < n_ops; ++n) widest = std::max(widest, weights_of(layers[sops[n].layer]));
+    if (takes_flow(widest, tokens, block)) {
+        const int rc = flow::prepare(layers, sops, links, n_ops, bufs, norm_w, eps, block, tokens, workspace, workspace_bytes_, stream);
+        if (rc == RB_OK || rc == RB_ERR_HIP) {                 // (what was refused leaves the plan that was there)
+            std::lock_guard<std::mutex> lock(g_mutex);
+            g_prepared.erase(workspace);
+        }
+        return rc;
+    }
 
     // ---- ops, consumers, stages
     std::vector<Op> ops((size_t)n_ops);
     std::vector<int> expand_list;
     size_t up_total = 0;
     std::vector<size_t> up_off((size_t)n_ops);
-    std::vector<bool> need_ssq((size_t)n_ops, false), need_rcopy((size_t)n_ops, false);
-    std::vector<int> resid_from((size_t)n_ops, -1);
     for (int n = 0; n < n_ops; ++n) {
         const rb_layer &L = layers[sops[n].layer];
         Op &o = ops[(size_t)n];
@@ -1480,41 +1463,21 @@ static int prepare_any(const rb_layer *layers, const PlanOp *sops, int n_ops, ui
         o.RT = row_tiles(L.out); o.CT = col_tiles(L.in);
         up_off[(size_t)n] = up_total;
         up_total += align_up(up_bytes(L.in, T), 256);
-        // producer of this op's input: the last earlier op that writes the same buffer
-        int producer = -1;
-        for (int m = n - 1; m >= 0; --m)
-            if (sops[m].dst == sops[n].src) { producer = m; break; }
-        o.dep = producer;
-        if (o.norm_w) {
-            o.n_part = (L.in + 15) / 16;
-            if (producer >= 0) need_ssq[(size_t)producer] = true;
-        }
-        // what is added: the caller's buffer as it was before the launch, or what an earlier op wrote there
+        const OpLinks &l = links[n];
+        o.dep = l.producer;
+        if (o.norm_w) o.n_part = (L.in + 15) / 16;
         if (sops[n].add >= 0) {
-            int writer = -1;
-            for (int m = n - 1; m >= 0; --m)
-                if (sops[m].dst == sops[n].add) { writer = m; break; }
-            if (writer >= 0) {
-                if (ops[(size_t)writer].out != L.out) return RB_ERR_SHAPE;
-                need_rcopy[(size_t)writer] = true;
-                resid_from[(size_t)n] = writer;
-                o.resid_kind = RESID_COPY;
-            } else {
-                o.resid = bufs[sops[n].add];
-                o.resid_kind = RESID_CALLER;
-            }
+            o.resid_kind = l.addend >= 0 ? RESID_COPY : RESID_CALLER;
+            if (l.aside) o.resid_src = bufs[sops[n].add];
+            else if (l.addend < 0) o.resid = bufs[sops[n].add];
         }
-        if (producer < 0) {
+        o.n_cons = l.n_cons;
+        std::copy(l.cons, l.cons + l.n_cons, o.cons);
+        if (l.producer < 0) {
             o.expand_x = 1;
             expand_list.push_back(n);
-        } else {
-            Op &pr = ops[(size_t)producer];
-            if (pr.n_cons >= MAX_CONS) return RB_ERR_UNSUPPORTED;
-            if (pr.out != o.in) return RB_ERR_SHAPE;
-            pr.cons[pr.n_cons++] = n;
         }
     }
-    if (expand_list.size() > MAX_EXPAND || n_ops > MAX_OPS) return RB_ERR_UNSUPPORTED;
     std::vector<Stage> stages;
     size_t n_records = 0;
     {
@@ -1564,7 +1527,7 @@ static int prepare_any(const rb_layer *layers, const PlanOp *sops, int n_ops, ui
     pr.n_ops = n_ops; pr.n_stages = (int)stages.size(); pr.G = G; pr.T = T; pr.K = K; pr.tokens = tokens;
     pr.n_expand = (int)expand_list.size();
     for (int n : expand_list) pr.max_expand_in = std::max(pr.max_expand_in, ops[(size_t)n].in);
-    for (int n = 0; n < n_ops; ++n) pr.chained = pr.chained || ops[(size_t)n].dep >= 0 || resid_from[(size_t)n] >= 0;
+    for (int n = 0; n < n_ops; ++n) pr.chained = pr.chained || ops[(size_t)n].dep >= 0 || links[n].addend >= 0;
     // an upper bound on the step list of a compute wavefront: the largest share of every op, cut in
     // CW runs, rounded up (the exact maximum over workgroups and wavefronts costs more host time than
     // the few blocks it saves)
@@ -1580,16 +1543,21 @@ static int prepare_any(const rb_layer *layers, const PlanOp *sops, int n_ops, ui
         pr.oblocks = desc_blocks((uint32_t)(longest + (size_t)nb_of(T) * (size_t)pr.n_stages));
     }
     // decoder blocks: what finishing wavefronts hand to each other (marked unwritten before every
-    // launch), then the sums of squares of inputs from outside
-    std::vector<size_t> ssq_off((size_t)n_ops, 0), rcopy_off((size_t)n_ops, 0), ext_off((size_t)n_ops, 0);
+    // launch), then the sums of squares of inputs from outside and what is put aside
+    std::vector<size_t> ssq_off((size_t)n_ops, 0), rcopy_off((size_t)n_ops, 0), ext_off((size_t)n_ops, 0), aside_off((size_t)n_ops, 0);
     size_t aux_poison = 0, aux_rest = 0;
     for (int n = 0; n < n_ops && block; ++n) {
-        if (need_ssq[(size_t)n]) { ssq_off[(size_t)n] = aux_poison; aux_poison += align_up((size_t)ops[(size_t)n].RT * 16, 256); }
-        if (need_rcopy[(size_t)n]) { rcopy_off[(size_t)n] = aux_poison; aux_poison += align_up((size_t)tokens * ops[(size_t)n].out * 4, 256); }
+        if (links[n].squares) { ssq_off[(size_t)n] = aux_poison; aux_poison += align_up((size_t)ops[(size_t)n].RT * 16, 256); }
+        if (links[n].copied) { rcopy_off[(size_t)n] = aux_poison; aux_poison += align_up((size_t)tokens * ops[(size_t)n].out * 4, 256); }
         if (ops[(size_t)n].norm_w && ops[(size_t)n].dep < 0) {
             ext_off[(size_t)n] = aux_rest;
             aux_rest += align_up((size_t)ops[(size_t)n].n_part * 16, 256);
             pr.ext_norm = true;
+        }
+        if (links[n].aside) {
+            aside_off[(size_t)n] = aux_rest;
+            aux_rest += align_up((size_t)tokens * ops[(size_t)n].out * 2, 256);
+            pr.aside = true;
         }
     }
     pr.block = block;
@@ -1602,15 +1570,16 @@ static int prepare_any(const rb_layer *layers, const PlanOp *sops, int n_ops, ui
     for (int n = 0; n < n_ops; ++n) ops[(size_t)n].up = ws + lay.up + up_off[(size_t)n];
     for (int n = 0; n < n_ops && block; ++n) {
         Op &o = ops[(size_t)n];
-        if (need_ssq[(size_t)n]) o.ssq_out = reinterpret_cast<float *>(ws + lay.aux + ssq_off[(size_t)n]);
-        if (need_rcopy[(size_t)n]) o.rcopy = reinterpret_cast<uint32_t *>(ws + lay.aux + rcopy_off[(size_t)n]);
+        if (links[n].squares) o.ssq_out = reinterpret_cast<float *>(ws + lay.aux + ssq_off[(size_t)n]);
+        if (links[n].copied) o.rcopy = reinterpret_cast<uint32_t *>(ws + lay.aux + rcopy_off[(size_t)n]);
     }
     for (int n = 0; n < n_ops && block; ++n) {
         Op &o = ops[(size_t)n];
         if (o.norm_w)
             o.ssq_in = o.dep >= 0 ? ops[(size_t)o.dep].ssq_out
                                   : reinterpret_cast<const float *>(ws + lay.aux + lay.aux_poison + ext_off[(size_t)n]);
-        if (resid_from[(size_t)n] >= 0) o.resid = ops[(size_t)resid_from[(size_t)n]].rcopy;
+        if (links[n].addend >= 0) o.resid = ops[(size_t)links[n].addend].rcopy;
+        if (links[n].aside) o.resid = ws + lay.aux + lay.aux_poison + aside_off[(size_t)n];
     }
 
     Header hdr{};
@@ -1702,10 +1671,10 @@ int launch_plan(void *workspace, size_t workspace_bytes_, hipStream_t stream)
     const int n_poison = pr.chained ? (pr.n_ops + (lay.aux_poison ? 1 : 0)) * POISON_SPLIT : 0;
     const int ex = (pr.max_expand_in / 16 * RB_MAX_K + 255) / 256, ey = pr.tokens;
     const int n_expand_groups = pr.n_expand > 0 ? ex * ey * pr.n_expand : 0;
-    const int n_ssq_groups = pr.ext_norm ? pr.n_expand * ey : 0;
-    if (n_poison + n_expand_groups + n_ssq_groups > 0)
-        hipLaunchKernelGGL(before_kernel, dim3((unsigned)(n_poison + n_expand_groups + n_ssq_groups)), dim3(256), 0, stream, d_hdr,
-                           d_ops, reinterpret_cast<const int *>(ws + lay.which), n_poison, n_expand_groups, ex, ey,
+    const int n_ssq_groups = pr.ext_norm ? pr.n_expand * ey : 0, n_aside_groups = pr.aside ? pr.n_ops * ASIDE_SPLIT : 0;
+    if (n_poison + n_expand_groups + n_ssq_groups + n_aside_groups > 0)
+        hipLaunchKernelGGL(before_kernel, dim3((unsigned)(n_poison + n_expand_groups + n_ssq_groups + n_aside_groups)), dim3(256), 0, stream, d_hdr,
+                           d_ops, reinterpret_cast<const int *>(ws + lay.which), n_poison, n_expand_groups, ex, ey, n_ssq_groups,
                            reinterpret_cast<uint4 *>(ws + lay.aux), lay.aux_poison / 16);
     const int pause_clks = g_pause_clks.load();
     const int go_pause = pause_clks < 0 ? -1 : pause_clks / 64;      // s_sleep units

@@ -158,5 +158,46 @@ __device__ __forceinline__ float path_sum(float a0, float s0, float a1, float s1
     return __builtin_fmaf(a0, s0, a1 * s1);
 }
 
+// Weight of the normalisation in front of an op at input column j (1 where there is none): it is
+// folded into the op's input scales
+template <class Op> __device__ __forceinline__ float norm_weight(const Op &op, int j)
+{
+    return op.norm_w ? __half2float(reinterpret_cast<const __half *>(op.norm_w)[j]) : 1.f;
+}
+
+// ---- what goes before a launch in both persistent kernels, 256 threads to a workgroup
+// Sums of squares of an input from outside that an op normalises: 16 columns per entry, [token][entry], as the
+// finishing wavefronts file them for inputs written inside a launch.  One workgroup per (op, token).
+template <class Op> __device__ __forceinline__ void ssq_part(const Op *ops, const int *which, int bx, int tok)
+{
+    const Op &op = ops[which[bx]];
+    if (!op.norm_w || op.dep >= 0) return;
+    float *out = const_cast<float *>(op.ssq_in);
+    for (int e = threadIdx.x; e < op.n_part; e += 256) {
+        float sum = 0.f;
+        for (int j = 16 * e; j < min(16 * e + 16, op.in); ++j) {
+            const float x = __half2float(reinterpret_cast<const __half *>(op.x)[(size_t)tok * op.in + j]);
+            sum += x * x;
+        }
+        out[(size_t)tok * op.n_part + e] = sum;
+    }
+}
+
+// What an op adds of the caller's, put aside before an op of the launch may store over it.  ASIDE_SPLIT workgroups per op.
+constexpr int ASIDE_SPLIT = 4;
+template <class Op> __device__ __forceinline__ void aside_part(const Op *ops, int tokens, int bx, int by)
+{
+    const Op &op = ops[bx];
+    if (!op.resid_src) return;
+    const size_t n = (size_t)tokens * op.out;
+    const uint16_t *from = op.resid_src;                     // (both 16-byte aligned)
+    uint16_t *to = const_cast<uint16_t *>(static_cast<const uint16_t *>(op.resid));
+    for (size_t i = ((size_t)by * 256 + threadIdx.x) * 8; i < n; i += 8 * 256 * ASIDE_SPLIT) {
+        if (i + 8 <= n) *reinterpret_cast<uint4 *>(to + i) = *reinterpret_cast<const uint4 *>(from + i);
+        else
+            for (size_t j = i; j < n; ++j) to[j] = from[j];
+    }
+}
+
 }  // namespace mx
 }  // namespace rb

@@ -189,6 +189,40 @@ def test_ragged_rows_and_plain_ops_in_a_block():
     _check(ops, layers, norm_w, got, "mixed block list")
 
 
+@pytest.mark.parametrize("T", [1, 2, 3, 4])
+@pytest.mark.parametrize("wide", [False, True])
+def test_an_addend_is_what_its_buffer_held_before_later_ops_wrote_it(T, wide):
+    """Two ops that share nothing but a buffer: one adds what the caller left there, a later one, which reads neither of them,
+    stores over it; what a third adds is the later one's."""
+    d, f = (4096, 11008) if wide else (544, 2080)
+    rng = synth.child_rng(81, T, d)
+    shapes = [(7 * d, d), (d, f), (d, 96), (d, 96)] if wide else [(d, f), (d, f), (d, 96), (d, 96)]
+    layers = [random_layer(synth.child_rng(81, 1, n, d), 2, o, i, gain=1.0 / (0.02 * 0.02 * np.sqrt(i))) for n, (o, i) in enumerate(shapes)]
+    norm_w = [(1.0 + 0.1 * rng.standard_normal(shapes[0][1])).astype(np.float16)]
+    E = (rb.RB_EPI_NONE, rb.RB_EPI_ADD, rb.RB_EPI_SILU_MUL)
+    # buffers: 0, 1, 2 inputs; 3 what is added and stored over
+    widths = [shapes[0][1], f, 96, d, shapes[0][0], d, d]
+    ops = [(0, 0, 4, 0, E[0], -1), (1, 1, 5, -1, E[1], 3), (2, 2, 3, -1, E[0], -1), (3, 2, 6, -1, E[1], 3)]
+    dev = [torch.from_numpy(synth.gaussian_activations(synth.child_rng(81, 2, n), T, w)).cuda() for n, w in enumerate(widths)]
+    held = dev[3].clone()
+    block = rb.Block([to_device_layer(*l) for l in layers], [torch.from_numpy(w).cuda() for w in norm_w], EPS, ops, dev, T)
+    print(f"an addend stored over, T={T}, d={d}", flush=True)
+    block.prepare()
+    for run in range(3):
+        dev[3].copy_(held)
+        block.run_prepared()
+        torch.cuda.synchronize()
+        assert block.status() == rb.RB_OK, f"gave up: reason {block.gave_up()}"
+        host = [b.cpu().numpy() for b in dev]
+        host[3] = held.cpu().numpy()
+        got = {n: dev[ops[n][2]].cpu().numpy().astype(np.float64) for n in range(4)}
+        refs = {1: oracle.forward(*layers[1], host[1]) + host[3].astype(np.float64), 2: oracle.forward(*layers[2], host[2])}
+        refs[3] = oracle.forward(*layers[3], host[2]) + got[2]
+        for n, ref in refs.items():
+            assert float(oracle.relative_l2(got[n], ref).max()) <= TOL, (run, n)
+    block.forget()
+
+
 def test_degenerate_inputs():
     """An all-zero token (its normalised input is zero, not NaN) next to an ordinary one; large
     activations (sums of squares beyond fp16's range stay in fp32)."""

@@ -36,11 +36,21 @@ def test_requests_of_the_few_token_kernel_stay_inside_a_layer(tmp_path):
     assert res.returncode == 0 and "all in bounds" in res.stdout, res.stdout
 
 
-def test_the_ring_of_sign_tiles_lets_everyone_come_to_the_end(tmp_path):
-    """Also a loading wavefront whose readers have given up and run ahead of it: a wait without an end would hang the GPU."""
-    exe = str(tmp_path / "ring_driver")
+def _host_build_of_kernel_headers(tmp_path, name):
+    exe = str(tmp_path / name)
     subprocess.check_call(["g++", "-std=c++17", "-Wall", "-fsanitize=address,undefined", "-static-libasan", "-fno-sanitize-recover=all", "-g", "-O1", "-D__host__=", "-D__device__=",
                            "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2602_05367_amd", "csrc"),
-                           os.path.join(ROOT, "tests", "sanitize", "ring.cpp"), "-o", exe])
-    res = subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+                           os.path.join(ROOT, "tests", "sanitize", name + ".cpp"), "-o", exe])
+    return subprocess.run([exe], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+
+
+def test_the_ring_of_sign_tiles_lets_everyone_come_to_the_end(tmp_path):
+    """Also a loading wavefront whose readers have given up and run ahead of it: a wait without an end would hang the GPU."""
+    res = _host_build_of_kernel_headers(tmp_path, "ring")
     assert res.returncode == 0 and "everyone came to the end" in res.stdout, res.stdout
+
+
+def test_ops_of_a_plan_hang_together_as_defined(tmp_path):
+    """Among them: an addend of the caller's that an op which need not come later stores over is put aside."""
+    res = _host_build_of_kernel_headers(tmp_path, "plan")
+    assert res.returncode == 0 and "as defined" in res.stdout, res.stdout
