@@ -943,7 +943,7 @@ int prepare(const rb_layer *layers, const PlanOp *sops, const OpLinks *links, in
         o.bits = static_cast<const uint32_t *>(L.bits);
         o.g = L.g; o.h = L.h;
         o.x = bufs[sops[n].src];
-        o.y = sops[n].dst >= 0 ? bufs[sops[n].dst] : nullptr;
+        o.y = sops[n].dst >= 0 && links[n].stores ? bufs[sops[n].dst] : nullptr;
         o.role = sops[n].role;
         o.norm_w = sops[n].norm >= 0 ? norm_w[sops[n].norm] : nullptr;
         o.eps = eps;
@@ -1006,11 +1006,6 @@ int prepare(const rb_layer *layers, const PlanOp *sops, const OpLinks *links, in
         stages.push_back(s);
         op0 += s.nops;
     }
-    // What the caller sees of a buffer after a run is its last writer's; readers inside the launch take what they read from the
-    // expanded inputs and copies of its writer.  So only the last one stores it, and no two stages' stores can race
-    for (int n = 0; n < n_ops; ++n)
-        for (int m = n + 1; m < n_ops && sops[n].dst >= 0; ++m)
-            if (sops[m].dst == sops[n].dst) { ops[(size_t)n].y = nullptr; break; }
     Prepared pr;
     pr.n_ops = n_ops; pr.n_stages = (int)stages.size(); pr.G = G; pr.tokens = tokens;
     pr.n_expand = (int)expand_list.size();

@@ -105,7 +105,7 @@ struct Op {
     const uint16_t *g;        // fp16 [K][out]
     const uint16_t *h;        // fp16 [K][in]
     const uint16_t *x;        // fp16 [T][in]  input buffer (read by the expansion kernel only)
-    uint16_t *y;              // fp16 [T][out] output buffer
+    uint16_t *y;              // fp16 [T][out] output buffer (null: a later op of the launch overwrites it)
     uint8_t *up;              // expanded input of this op (see up_group_offset)
     int out, in, K;
     int RT, CT;               // row tiles (16 rows), column tiles (256 columns)
@@ -162,7 +162,7 @@ __host__ __device__ constexpr uint32_t desc_blocks(uint32_t n) { return n / DESC
 // so that its address follows from the stage's entry and (grp, slot) alone and nothing on the path
 // from the partial sums to the stores waits for a chain of dependent loads.
 struct SlotRec {
-    uint64_t y;               // fp16 output: row 0 of token 0
+    uint64_t y;               // fp16 output: row 0 of token 0 (0: not stored)
     uint64_t pad64_;
     uint64_t up[MAX_CONS];    // per reading op: the 16-byte group of operand column 0 these rows fill
     int out, n_cons;          // rows of the op; ops that read its output

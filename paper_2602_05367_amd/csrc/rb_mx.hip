@@ -1234,7 +1234,7 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
                     }
                 }
             }
-            if (writes) RB_GLOBAL(_Float16, cur.r.y)[y_at] = y16;
+            if (writes && cur.r.y != 0) RB_GLOBAL(_Float16, cur.r.y)[y_at] = y16;
             // clear the partial sums for the stage after next (a run without tiles writes nothing);
             // off the path from the barrier to the stores
             if (active) {
@@ -1454,7 +1454,7 @@ static int prepare_any(const rb_layer *layers, const PlanOp *sops, int n_ops, ui
         o.bits = static_cast<const uint32_t *>(L.bits);
         o.g = L.g; o.h = L.h;
         o.x = bufs[sops[n].src];
-        o.y = sops[n].dst >= 0 ? bufs[sops[n].dst] : nullptr;
+        o.y = sops[n].dst >= 0 && links[n].stores ? bufs[sops[n].dst] : nullptr;
         o.slot0 = -1;
         o.role = sops[n].role;
         o.norm_w = sops[n].norm >= 0 ? norm_w[sops[n].norm] : nullptr;

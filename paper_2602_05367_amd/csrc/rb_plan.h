@@ -23,6 +23,7 @@ struct OpLinks {
     int n_cons = 0, cons[MAX_CONS] = {};   // ops that read the result
     bool squares = false;     // an op that normalises its input reads the result
     bool copied = false;      // a later op adds the result
+    bool stores = true;       // no later op writes the same buffer: what the caller finds there is this one's
     bool aside = false;       // what the caller's buffer held is added, and an op that need not come after this one writes that buffer
 };
 
@@ -71,6 +72,10 @@ inline int link_ops(const rb_layer *layers, const PlanOp *ops, int n_ops, std::v
         }
     }
     if (from_outside > MAX_EXPAND || n_ops > MAX_OPS) return RB_ERR_UNSUPPORTED;
+    // Readers inside the launch take what they read and add from the expanded inputs and copies of its writer, so only the last writer of a
+    // buffer needs to store it; the stores of two, from compute units whose caches are not coherent, could land in either order
+    for (int n = 0; n < n_ops; ++n)
+        for (int m = n + 1; m < n_ops && links[(size_t)n].stores; ++m) links[(size_t)n].stores = ops[n].dst < 0 || ops[m].dst != ops[n].dst;
     for (int n = 0; n < n_ops; ++n)
         if (ops[n].add >= 0 && links[(size_t)n].addend < 0) links[(size_t)n].aside = !adds_before_anyone_stores(ops, links, n_ops, n);
     return RB_OK;

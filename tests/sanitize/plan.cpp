@@ -59,15 +59,17 @@ int main()
             if (l.producer != producer[n] || l.addend != addend[n] || l.n_cons != readers[n]) return fail("producer, addend or readers", trial, n);
             for (int c = 0; c < l.n_cons; ++c)
                 if (producer[l.cons[c]] != n) return fail("a reader", trial, n);
-            bool squares = false, copied = false, aside = false, stored_over = false;
+            bool squares = false, copied = false, aside = false, stored_over = false, last = true;
             for (int m = 0; m < n_ops; ++m) {
                 squares = squares || (producer[m] == n && ops[m].norm >= 0);
                 copied = copied || addend[m] == n;
+                last = last && !(m > n && ops[m].dst == ops[n].dst);
                 if (m == n || ops[n].add < 0 || addend[n] >= 0 || ops[m].dst != ops[n].add) continue;
                 stored_over = true;
                 aside = aside || !before[n][m];
             }
             if (l.squares != squares || l.copied != copied) return fail("squares or copy", trial, n);
+            if (l.stores != last) return fail("stores", trial, n);
             if (l.aside != aside) return fail("aside", trial, n);
             asides += aside;
             in_order += stored_over && !aside;

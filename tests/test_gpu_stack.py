@@ -748,3 +748,29 @@ def test_a_workspace_sized_for_four_tokens_serves_one_and_two(T):
         assert rb.lib.rb_linear_gemm(ctypes.byref(L), x.data_ptr(), y.data_ptr(), T, rb.RB_F16, rb.RB_F16, ws.data_ptr(), size, None) == rb.RB_OK
         torch.cuda.synchronize()
         assert rb.rb_last_path() == rb.RB_PATH_MX and torch.equal(y, bufs[1 + wide.index(layer)])
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 4])
+@pytest.mark.parametrize("d,f", [(544, 2080), (4096, 11008)])
+def test_a_buffer_written_twice_holds_the_later_result(T, d, f):
+    """Two ops write one buffer, the second without waiting for the first (and with far less to do); an op between them reads the first
+    result."""
+    rng = synth.child_rng(3, 503, T, d)
+    shapes = [(f, d, 0, 1), (96, d, 0, 2), (d, f, 1, 3), (f, d, 3, 4), (d, 96, 2, 3)]      # out, in, from, to
+    layers = [random_layer(rng, 2, o, i, gain=1.0 / (0.02 * 0.02 * np.sqrt(i))) for o, i, _, _ in shapes]
+    bufs = [torch.from_numpy(synth.gaussian_activations(rng, T, d)).cuda()] + [torch.zeros((T, w), dtype=torch.float16, device="cuda") for w in (f, 96, d, f)]
+    stack = rb.Stack([to_device_layer(*l) for l in layers], [(n, src, dst) for n, (_, _, src, dst) in enumerate(shapes)], bufs, T)
+    print(f"a buffer written twice, T={T}, d={d}", flush=True)
+    stack.prepare()
+    for run in range(3):
+        for b in bufs[1:]:
+            b.fill_(7.0)
+        stack.run_prepared()
+        torch.cuda.synchronize()
+        assert stack.status() == rb.RB_OK, f"gave up: reason {stack.gave_up()}"
+        host = [b.cpu().numpy() for b in bufs]
+        first = oracle.forward(*layers[2], host[1]).astype(np.float16)         # (seen by the op between them alone)
+        for n, x in ((0, host[0]), (1, host[0]), (4, host[2]), (3, first)):
+            got = host[shapes[n][3]].astype(np.float64)
+            assert oracle.relative_l2(got, oracle.forward(*layers[n], x)).max() <= TOL, (run, n)
+    stack.forget()
