@@ -359,8 +359,10 @@ __global__ __launch_bounds__(THREADS, 3) void flow_kernel(const Work *__restrict
     auto second_of = [&](const Work &w) { return Segment{w.bits[1], w.up[1], w.P[1], w.CT[1], w.slot1, (w.flags & WORK_DEP1) != 0}; };
     uint8_t *const signs = lds + Lds::SIGNS_OFF;
     auto columns_of = [&](const Segment &s) { return run_begin(wave + 1, s.CT) - run_begin(wave, s.CT); };
-    // LDS set-up
+    // LDS set-up.  (The compiler does not count stores made in assembly: it need not wait for them at the barrier, and a zero that came
+    // late could undo an arrival, for which the others would wait without an end)
     if (threadIdx.x < 16) lds_write(lds_at(Lds::USED_OFF) + threadIdx.x * 4, 0u);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __syncthreads();
 
     if (wave == CWAVES) {
