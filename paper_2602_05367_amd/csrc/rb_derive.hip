@@ -37,6 +37,7 @@
 #include "rabit.h"
 #include "rb_device.h"
 #include "rb_internal.h"
+#include "rb_walk.h"
 
 namespace rb {
 namespace derive {
@@ -44,7 +45,6 @@ namespace derive {
 constexpr int ROW_SLICE = 32;          // rows one workgroup of the column pass walks (twice that where the workspace is the smaller)
 constexpr int MAX_SLICES = 65535;
 constexpr int ROWS = 4;                // rows one workgroup of the row pass takes
-constexpr int FIRST_LOOK = 4;          // power iterations before the first look at the flag
 constexpr int MAX_ITER = 200;
 constexpr int ONE_PASS_MIN_ROWS = 1024, ONE_PASS_MIN_COLS = 2048;
 constexpr double TOL_SIGMA = 1e-13, TOL_B = 1e-10;
@@ -841,18 +841,16 @@ struct Buffers {
     double *a, *a_sq, *b, *sum, *sum_sq, *partial;
 };
 
-// All updates by one_pass_kernel where it walks.  The host asks for a first sweep's passes and looks how far they came; then for as many as the
-// rest would take at that rate, and looks again.  Two passes over (some 6 us each) are less than another look (27 us).
+// All updates by one_pass_kernel where it walks.  The host asks for a first sweep's passes and looks how far they came; then for as many as
+// passes_to_ask says, and looks again.
 template <int K>
 static int walk(const Problem<K - 1> &p, uint32_t *packed, double *g, double *h, double *err, int T_max, int groups, const Buffers &ws, hipStream_t stream)
 {
-    constexpr int MOST = 1024;             // passes asked for without a look
     const int in = p.in, n_sq = (in + SUMS_COLS - 1) / SUMS_COLS;
     double *const bs[2] = {ws.b, ws.partial + (size_t)ONE_PASS_GROUPS * in};
     hipLaunchKernelGGL(walk_start_kernel, dim3(1), dim3(1), 0, stream, ws.sc);
-    double passes = 0.0, wanted = (double)K * (FIRST_LOOK + 1);
-    for (int now = 0;;) {
-        const int n = (int)std::min<double>(MOST, wanted);
+    double passes = 0.0;
+    for (int now = 0, n = K * (FIRST_LOOK + 1);;) {
         for (int k = 0; k < n; ++k, now ^= 1) {
             const Step st{bs[now], ws.sum, ws.sum_sq, bs[now ^ 1], ws.sc + now, ws.sc + (now ^ 1), n_sq, T_max};
             const int rc = launch_one_pass(groups, p, packed, st, ws.partial, ws.a, ws.a_sq, stream);
@@ -864,9 +862,9 @@ static int walk(const Problem<K - 1> &p, uint32_t *packed, double *g, double *h,
         if (hipMemcpyAsync(&host, ws.sc + now, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess || hipStreamSynchronize(stream) != hipSuccess)
             return RB_ERR_HIP;
         passes += n;
-        const double spent = host.done ? 0.0 : host.iters + 1.0, finished = (double)K * host.t + host.i + (host.done ? 1.0 : 0.0), left = (double)K * T_max - finished;
+        const double under_way = host.done ? 0.0 : host.iters + 1.0, finished = (double)K * host.t + host.i + (host.done ? 1.0 : 0.0), left = (double)K * T_max - finished;
         if (host.done == WALKED || left <= 0.0) return RB_OK;
-        wanted = finished > 0.0 ? std::max(0.0, (passes - spent) / finished * left - spent) + 2.0 : FIRST_LOOK;
+        n = passes_to_ask(passes, under_way, finished, left);
     }
 }
 

@@ -54,3 +54,9 @@ def test_ops_of_a_plan_hang_together_as_defined(tmp_path):
     """Among them: an addend of the caller's that an op which need not come later stores over is put aside."""
     res = _host_build_of_kernel_headers(tmp_path, "plan")
     assert res.returncode == 0 and "as defined" in res.stdout, res.stdout
+
+
+def test_passes_of_the_initialisation_are_asked_for_in_measure(tmp_path):
+    """A slow update says little of the others: neither many passes with nothing to do nor a look after every few."""
+    res = _host_build_of_kernel_headers(tmp_path, "walk")
+    assert res.returncode == 0 and "in measure" in res.stdout, res.stdout
