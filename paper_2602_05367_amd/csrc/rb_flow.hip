@@ -782,7 +782,10 @@ __global__ __launch_bounds__(THREADS, 3) void flow_kernel(const Work *__restrict
             }
             if (looks == MAX_LOOKS) give_up(GAVE_UP_BLOCK);
         }
-        // ---- the partial sums of the stage are in LDS when all have got here (the loading wavefront takes no part)
+        // ---- the partial sums of the stage are in LDS when all have got here (the loading wavefront takes no part).  In place one of the wavefronts
+        // that finish the same rows stores over what all of them add: it has arrived with each before any comes by here (the compiler waits for
+        // a loaded value that a statement takes)
+        if constexpr (BLK) asm volatile("" : "+v"(added) : : "memory");
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (lane == 0) lds_add(lds_at(Lds::ARRIVED_OFF), 1u);
         while ((int)(lds_read(lds_at(Lds::ARRIVED_OFF)) - (uint32_t)(CWAVES * (st + 1))) < 0) {}

@@ -1,4 +1,6 @@
 """Shared by the GPU parity tests: build a device layer and its oracle inputs."""
+import ctypes
+
 import numpy as np
 import torch
 
@@ -67,3 +69,11 @@ def build_stack(which, n_layers, config, T, derived, shrink=None, outliers=False
         layers.append((signs, g, h))
         bufs[op.dst] = oracle.forward(signs, g, h, bufs[op.src]).astype(np.float16)
     return ops, widths, layers, bufs
+
+
+def on_kernel_for_three_and_four_tokens(stack):
+    """Which of the two persistent kernels a prepared stack or block runs on: wide two-path layers of three and four tokens have one of
+    their own, and rb_last_path does not tell them apart.  (rb::flow::marks(workspace): where such a plan's marks are, null for others)"""
+    marks = rb.lib._ZN2rb4flow5marksEPKv
+    marks.argtypes, marks.restype = [ctypes.c_void_p], ctypes.c_void_p
+    return bool(marks(stack.ws.data_ptr()))

@@ -8,7 +8,7 @@ import torch
 import oracle
 import synth
 import paper_2602_05367_amd as rb
-from helpers import TOL, random_layer, to_device_layer
+from helpers import TOL, on_kernel_for_three_and_four_tokens, random_layer, to_device_layer
 
 pytestmark = pytest.mark.gpu
 
@@ -45,13 +45,15 @@ def _op_tuples(ops):
     return [(o.layer, o.src, o.dst, o.norm, o.epilogue, o.aux) for o in ops]
 
 
-def _run(ops, widths, layers, norm_w, x0, T, pause=-1, runs=1):
+def _run(ops, widths, layers, norm_w, x0, T, pause=-1, runs=1, wide=None):
     dev_layers = [to_device_layer(*l) for l in layers]
     dev_norms = [torch.from_numpy(w).cuda() for w in norm_w]
     dev_bufs = [torch.zeros((T, w), dtype=torch.float16, device="cuda") for w in widths]
     dev_bufs[0].copy_(torch.from_numpy(x0))
     block = rb.Block(dev_layers, dev_norms, EPS, _op_tuples(ops), dev_bufs, T)
     block.prepare()
+    if wide is not None:
+        assert on_kernel_for_three_and_four_tokens(block) == wide
     rb.rb_stack_set_option(rb.RB_OPT_HANDOVER_PAUSE, pause)
     try:
         for _ in range(runs):
@@ -93,13 +95,13 @@ def test_small_block_stack(T):
     assert 0.3 < float(np.sqrt((got[ops[-1].dst].astype(np.float64) ** 2).mean())) < 30.0
 
 
-@pytest.mark.parametrize("T", [1, 4])
+@pytest.mark.parametrize("T", [1, 3, 4])
 def test_full_width_7b_blocks(T):
     """Two blocks at the real 7B widths (688 row tiles of gate and of up: two or three per
     workgroup, meeting in the halves of the finishing wavefronts)."""
     ops, widths, layers, norm_w, x0 = build_block("7b", 2, 50 + T, T, outliers=True)
     print(f"two full-width 7B blocks, T={T}", flush=True)
-    got, _, _ = _run(ops, widths, layers, norm_w, x0, T)
+    got, _, _ = _run(ops, widths, layers, norm_w, x0, T, wide=T > 2)
     _check(ops, layers, norm_w, got, f"full-width 7B blocks T={T}")
 
 
@@ -162,12 +164,11 @@ def test_residual_stream_in_place():
             assert np.array_equal(got[a.dst], got_ip[b.dst]), a.name
 
 
-def test_ragged_rows_and_plain_ops_in_a_block():
+@pytest.mark.parametrize("T,d,f", [(2, 544, 1056), (3, 2080, 8224), (4, 2080, 8224)])
+def test_ragged_rows_and_plain_ops_in_a_block(T, d, f):
     """A block list that mixes plain ops with the fused ones; a dead-end op whose rows are not a
     multiple of 16; an op that adds a buffer written by an op it does not read."""
-    T = 2
     rng = synth.child_rng(80, 0)
-    d, f = 544, 1056
     shapes = [(300, d), (d, d), (d, d), (f, d), (f, d), (d, f), (d, d)]
     gains = [1.0 / (0.02 * 0.02 * np.sqrt(i)) for _, i in shapes]
     layers = [random_layer(synth.child_rng(80, 1, n), 2, o, i, gain=gn) for n, ((o, i), gn) in enumerate(zip(shapes, gains))]
@@ -185,8 +186,70 @@ def test_ragged_rows_and_plain_ops_in_a_block():
            O("down", 5, 4, 5, -1, E[1], 3),
            O("add_far", 6, 5, 6, 0, E[1], 2)]          # normalised input, adds what "plain" wrote
     x0 = synth.gaussian_activations(rng, T, d)
-    got, _, _ = _run(ops, widths, layers, norm_w, x0, T)
+    print(f"mixed block list, T={T}, d={d}", flush=True)
+    got, _, _ = _run(ops, widths, layers, norm_w, x0, T, wide=T > 2)
     _check(ops, layers, norm_w, got, "mixed block list")
+
+
+# Blocks whose widest layers (17 M weights) are just wide enough for the kernel for three and four tokens: 130 row tiles, which eight
+# wavefronts finish together, and 514, one or two to a workgroup of gate and of up; columns that end inside a column tile
+WIDE = {4096: 2080, 11008: 8224}
+
+
+@pytest.mark.parametrize("T", [3, 4])
+def test_13b_block_at_three_and_four_tokens(T):
+    """Four row tiles of gate and of up per workgroup, all finishing slots in use; 320 sums of squares per token, more than one wavefront asks for at once."""
+    ops, widths, layers, norm_w, x0 = build_block("13b", 1, 57 + T, T)
+    print(f"one full-width 13B block, T={T}", flush=True)
+    got, _, _ = _run(ops, widths, layers, norm_w, x0, T, wide=True)
+    _check(ops, layers, norm_w, got, f"13B block T={T}")
+
+
+@pytest.mark.parametrize("T", [3, 4])
+def test_wide_block_stack(T):
+    """Paced, without pause, and in place: against the oracle and the same bits."""
+    ops, widths, layers, norm_w, x0 = build_block("7b", 2, 62 + T, T, shrink=WIDE, outliers=True)
+    print(f"two wide blocks, T={T}", flush=True)
+    got, _, _ = _run(ops, widths, layers, norm_w, x0, T, wide=True)
+    _check(ops, layers, norm_w, got, f"two wide blocks T={T}")
+    print("  without pause", flush=True)
+    again, waited, _ = _run(ops, widths, layers, norm_w, x0, T, pause=0, runs=3, wide=True)
+    assert waited > 0
+    for a, b in zip(got, again):
+        assert np.array_equal(a, b)
+    print("  in place", flush=True)
+    ops_ip, widths_ip, _, _, _ = build_block("7b", 2, 62 + T, T, shrink=WIDE, outliers=True, in_place=True)
+    in_place, _, _ = _run(ops_ip, widths_ip, layers, norm_w, x0, T, wide=True)
+    assert np.array_equal(in_place[0], got[ops[-1].dst])
+    for a, b in zip(ops, ops_ip):
+        if b.dst != 0:
+            assert np.array_equal(got[a.dst], in_place[b.dst]), a.name
+
+
+@pytest.mark.parametrize("T", [3, 4])
+def test_wide_block_with_zero_large_and_non_finite_tokens(T):
+    """A zero token, a large one and ordinary ones against the oracle; then a token with an infinity and a NaN, which ends at once, in nothing finite, and leaves
+    the others' bits as they were."""
+    ops, widths, layers, norm_w, x0 = build_block("7b", 1, 92, T, shrink=WIDE)
+    x0 = x0.copy()
+    x0[0, :] = 0.0
+    x0[1, :] = (x0[1, :].astype(np.float64) * 300.0).astype(np.float16)
+    print(f"zero and large tokens through a wide block, T={T}", flush=True)
+    got, _, _ = _run(ops, widths, layers, norm_w, x0, T, wide=True)
+    refs = oracle.block_forward(layers, norm_w, EPS, _op_tuples(ops), got, write_back=False)
+    for n, op in enumerate(ops):
+        assert np.all(np.isfinite(got[op.dst])), op.name
+        if op.src == 0:
+            assert np.all(got[op.dst][0] == 0), op.name          # q, k, v of the zero token
+        err = oracle.relative_l2(got[op.dst].astype(np.float64), refs[n])
+        assert float(err[1:].max()) <= TOL, (op.name, err)
+        assert float(err[0]) <= TOL or np.abs(refs[n][0]).max() == 0.0, (op.name, err)
+    x0[0, 5], x0[0, 77] = np.inf, np.nan
+    print("  a non-finite token", flush=True)
+    worse, _, _ = _run(ops, widths, layers, norm_w, x0, T, wide=True)
+    for op in ops:
+        assert not np.isfinite(worse[op.dst][0]).any(), op.name
+        assert np.array_equal(worse[op.dst][1:], got[op.dst][1:]), op.name
 
 
 @pytest.mark.parametrize("T", [1, 2, 3, 4])
@@ -208,6 +271,7 @@ def test_an_addend_is_what_its_buffer_held_before_later_ops_wrote_it(T, wide):
     block = rb.Block([to_device_layer(*l) for l in layers], [torch.from_numpy(w).cuda() for w in norm_w], EPS, ops, dev, T)
     print(f"an addend stored over, T={T}, d={d}", flush=True)
     block.prepare()
+    assert on_kernel_for_three_and_four_tokens(block) == (wide and T > 2)
     for run in range(3):
         dev[3].copy_(held)
         block.run_prepared()
