@@ -12,7 +12,7 @@ import torch
 import oracle
 import synth
 import paper_2602_05367_amd as rb
-from helpers import TOL, build_stack, to_device_layer, random_layer
+from helpers import TOL, build_stack, on_kernel_for_three_and_four_tokens, random_layer, to_device_layer
 
 pytestmark = pytest.mark.gpu
 
@@ -155,23 +155,48 @@ def test_non_finite_activation_propagates_and_ends():
     """An infinity in the input must come out as non-finite outputs of every dependent op, at once:
     the flag-free hand-over tells "not written yet" from data by a byte pattern that a NaN term
     could otherwise take, and a wait on it would only end at its (long) bound with RB_ERR_HANDOVER."""
-    shrink = {4096: 512, 11008: 1376}
-    ops, widths, layers, bufs = build_stack("7b", 1, 7, 1, derived=False, shrink=shrink, gain=100.0)
+    _non_finite({4096: 512, 11008: 1376}, 1)
+
+
+@pytest.mark.parametrize("T", [3, 4])
+def test_non_finite_activation_propagates_and_ends_in_wide_layers(T):
+    """The same on the kernel for three and four tokens, where the other tokens are what they were."""
+    _non_finite(WIDE, T)
+
+
+# just wide enough for the kernel for three and four tokens (6.5 M weights in the widest layers)
+WIDE = {4096: 1568, 11008: 4128}
+
+
+def _non_finite(shrink, T):
+    ops, widths, layers, bufs = build_stack("7b", 1, 7, T, derived=False, shrink=shrink, gain=100.0)
     dev_layers = [to_device_layer(*l) for l in layers]
     op_list = [(n, op.src, op.dst) for n, op in enumerate(ops)]
-    dev_bufs = [torch.zeros((1, w), dtype=torch.float16, device="cuda") for w in widths]
+    dev_bufs = [torch.zeros((T, w), dtype=torch.float16, device="cuda") for w in widths]
     x = torch.from_numpy(bufs[0]).clone()
+    dev_bufs[0].copy_(x)
+    stack = rb.Stack(dev_layers, op_list, dev_bufs, T)
+    stack.prepare()
+    assert on_kernel_for_three_and_four_tokens(stack) == (shrink is WIDE)
+    stack.run_prepared()
+    assert stack.status() == rb.RB_OK, f"gave up: reason {stack.gave_up()}"
+    finite = [b.clone() for b in dev_bufs]
     x[0, 5] = float("inf")
     x[0, 77] = float("nan")
     dev_bufs[0].copy_(x)
-    stack = rb.Stack(dev_layers, op_list, dev_bufs, 1)
-    stack.prepare()
-    print("non-finite input through a dependent stack", flush=True)
+    print(f"non-finite input through a dependent stack, T={T}", flush=True)
     stack.run_prepared()
     assert stack.status() == rb.RB_OK, f"gave up: reason {stack.gave_up()}"
     stack.forget()
     for op in ops:
-        assert not torch.isfinite(dev_bufs[op.dst]).any(), op.name
+        assert not torch.isfinite(dev_bufs[op.dst][0]).any(), op.name
+        assert torch.equal(dev_bufs[op.dst][1:], finite[op.dst][1:]), op.name
+
+
+@pytest.mark.parametrize("T", [3, 4])
+def test_requests_ahead_of_the_writes_are_caught_in_wide_layers(T):
+    """The same on the kernel for three and four tokens."""
+    _requests_ahead(WIDE, T)
 
 
 @pytest.mark.parametrize("T", [1, 2, 3, 4])
@@ -181,7 +206,10 @@ def test_requests_ahead_of_the_writes_are_caught(T):
     them.  The consumer must notice every such tile (the 'not written yet' pattern), wait for it
     and read it again: same bits as the normally paced run, clean status, every kernel ends by
     itself."""
-    shrink = {4096: 1024, 11008: 2752}
+    _requests_ahead({4096: 1024, 11008: 2752}, T)
+
+
+def _requests_ahead(shrink, T):
     ops, widths, layers, bufs = build_stack("7b", 2, 8, T, derived=False, shrink=shrink, gain=100.0)
     dev_layers = [to_device_layer(*l) for l in layers]
     op_list = [(n, op.src, op.dst) for n, op in enumerate(ops)]
@@ -194,6 +222,7 @@ def test_requests_ahead_of_the_writes_are_caught(T):
             print(f"hand-over pause {pause}, T={T}", flush=True)
             stack = rb.Stack(dev_layers, op_list, dev_bufs, T)
             stack.prepare()
+            assert on_kernel_for_three_and_four_tokens(stack) == (shrink is WIDE)
             runs = []
             for token in range(6):
                 x = synth.gaussian_activations(synth.child_rng(2, 61, token), T, widths[0])
@@ -662,6 +691,7 @@ def test_three_and_four_token_stack_forms(T, shapes):
     dev = [torch.from_numpy(b).cuda() for b in bufs]
     stack = rb.Stack(dev_layers, op_list, dev, T)
     stack.prepare()
+    assert on_kernel_for_three_and_four_tokens(stack) == (shapes[-1][0] != 2032)
     runs = []
     for _ in range(2):
         for _, _, dst in op_list:
@@ -696,6 +726,7 @@ def test_one_workspace_for_plans_of_the_two_few_token_kernels(first, second):
         s.ws, s.ws_bytes = ws, size
 
     def check(s):
+        assert on_kernel_for_three_and_four_tokens(s) == (s.T > 2)
         s.bufs[2].fill_(7.0)
         print(f"stack of {s.T} tokens on a shared workspace", flush=True)
         s.run_prepared()
@@ -762,6 +793,7 @@ def test_a_buffer_written_twice_holds_the_later_result(T, d, f):
     stack = rb.Stack([to_device_layer(*l) for l in layers], [(n, src, dst) for n, (_, _, src, dst) in enumerate(shapes)], bufs, T)
     print(f"a buffer written twice, T={T}, d={d}", flush=True)
     stack.prepare()
+    assert on_kernel_for_three_and_four_tokens(stack) == (T > 2 and d == 4096)
     for run in range(3):
         for b in bufs[1:]:
             b.fill_(7.0)
