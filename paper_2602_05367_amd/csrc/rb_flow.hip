@@ -702,9 +702,12 @@ __global__ __launch_bounds__(THREADS, 3) void flow_kernel(const Work *__restrict
     for (int st = 0; st < n_stages; ++st) {
         const int parity = st & 1;
         const bool have = fin_slot < now.n_fin, gated = BLK && (now.flags & WORK_GATED) != 0, norm = BLK && (now.flags & WORK_NORM) != 0;
-        // ---- the time the slowest producer's stores need to land
-        if (st > 0 && (now.flags & (WORK_DEP0 | WORK_DEP1)) != 0)
-            for (int i = 0; i < go_pause; ++i) __builtin_amdgcn_s_sleep(1);
+        // ---- the time the slowest producer's stores need to land.  A workgroup without a part in the stage waits for twice that: the others take longer, and
+        // what it asks for before they are done is stale in the L2 that it shares with some of them (one block of layers at three tokens, us without and with:
+        // chains 2048 x 8192 35.9 and 28.1, 1280 x 5056 30.6 and 23.6, 3072 x 6144 31.1 and 28.1, a decoder block of 2048 x 8192 40.2 and 33.6; 64, 96 and 128
+        // units for the built-in pause of 48 are the same within 2 %)
+        const int pauses = now.P[0] == 0 ? (st + 1 < n_stages ? 2 : 0) : st > 0 && (now.flags & (WORK_DEP0 | WORK_DEP1)) != 0 ? 1 : 0;
+        for (int i = 0; i < pauses * go_pause; ++i) __builtin_amdgcn_s_sleep(1);
         // ---- decoder blocks: what comes from other workgroups' finishing wavefronts besides the operands.  Both kinds are marked "not yet
         // written" (all ones) before the launch and looked at until they are not.  The sums of squares of token `wave`:
         constexpr int SSQ = 4;

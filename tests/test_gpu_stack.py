@@ -750,6 +750,31 @@ def test_one_workspace_for_plans_of_the_two_few_token_kernels(first, second):
     one.forget()
 
 
+@pytest.mark.parametrize("T", [3, 4])
+def test_workgroups_without_a_part_in_a_stage_do_not_run_ahead(T):
+    """Layers of 128 row tiles leave half of the workgroups (of 256) out of o and down.  Those used to ask for the next stage's inputs while the others
+    still worked: each of their 128 x 8 tiles of gate and up was waited for in every run."""
+    groups = torch.cuda.get_device_properties(0).multi_processor_count
+    d, f = 8 * groups, 32 * groups
+    rng = synth.child_rng(3, 504, T)
+    shapes = [(d, d, 0), (d, d, 1), (f, d, 2), (f, d, 2), (d, f, 3)]
+    layers = [to_device_layer(*random_layer(rng, 2, o, i, gain=1.0 / (0.02 * 0.02 * np.sqrt(i)))) for o, i, _ in shapes]
+    bufs = [torch.from_numpy(synth.gaussian_activations(rng, T, d)).cuda()] + [torch.zeros((T, o), dtype=torch.float16, device="cuda") for o, _, _ in shapes]
+    stack = rb.Stack(layers, [(n, src, n + 1) for n, (_, _, src) in enumerate(shapes)], bufs, T)
+    print(f"layers of {d} rows, T={T}", flush=True)
+    stack.prepare()
+    assert on_kernel_for_three_and_four_tokens(stack)
+    runs = 20
+    for _ in range(runs):
+        stack.run_prepared()
+    torch.cuda.synchronize()
+    assert stack.status() == rb.RB_OK
+    waited = stack.waited() / runs
+    stack.forget()
+    print(f"  tiles waited for in a run: {waited}", flush=True)
+    assert waited < groups // 2 * 8 / 2
+
+
 @pytest.mark.parametrize("T", [1, 2])
 def test_a_workspace_sized_for_four_tokens_serves_one_and_two(T):
     """A prepared chain of 64 wide layers, the same in one call, and a single call, all on the matrix-core kernels."""
