@@ -1338,23 +1338,13 @@ static size_t block_aux_bound(const rb_layer *layers, int n_layers, int tokens)
     return most;
 }
 
-// Three and four tokens: plans with a wide layer take the kernel of rb_flow.hip, narrower ones the one here.  The other one saves
-// with the operands that a stage fetches and costs 4 us more once a launch and, in decoder blocks, more per stage.  Line by the weights
-// of the widest layer, us here and there: decoder blocks (d x f, number, tokens) 1024 x 2048 8 4 157 and 167, 1600 x 4800 8 4 219 and 224,
-// 2496 x 4992 4 4 126 and 133, 2048 x 5504 8 4 215 and 201, 2048 x 6144 8 4 205 and 207; from the line on 2048 x 8192 8 4 222 and 214,
-// 2624 x 6784 4 4 144 and 136, 3072 x 6144 4 4 130 and 116, 4992 x 9984 2 4 121 and 110.  Chains 1024 x 2048 2 3 37 and 41,
-// 1024 x 4096 8 4 141 and 136; from the line on 1920 x 3840 4 4 98 and 87, 1600 x 4800 8 4 196 and 162, 4096 x 11008 2 4 86 and 73.
-constexpr size_t FLOW_BLOCK_WEIGHTS = (size_t)16 << 20, FLOW_CHAIN_WEIGHTS = (size_t)6 << 20;
-static size_t weights_of(const rb_layer &L) { return (size_t)L.out * L.in; }
-static bool takes_flow(size_t widest, int tokens, bool block) { return tokens > 2 && widest >= (block ? FLOW_BLOCK_WEIGHTS : FLOW_CHAIN_WEIGHTS); }
-
 size_t plan_workspace_bytes(const rb_layer *layers, int n_layers, int n_ops, int T_in, bool block)
 {
     // (room for the step lists also where the plan takes the other kernel, which needs less: a workspace sized for the most
     // tokens has served calls of fewer always, and the ops of a call may leave the widest layers out)
-    size_t widest = 0;
-    for (int l = 0; l < n_layers; ++l) widest = std::max(widest, weights_of(layers[l]));
-    const size_t other = takes_flow(widest, T_in, block) ? flow::plan_workspace_bytes(layers, n_layers, n_ops, T_in, block) : 0;
+    bool any_wide = false;
+    for (int l = 0; l < n_layers; ++l) any_wide = any_wide || weights_of(layers[l]) >= flow_weights(block);
+    const size_t other = T_in > 2 && any_wide ? flow::plan_workspace_bytes(layers, n_layers, n_ops, T_in, block) : 0;
     int T = T_in;
     for (int l = 0; l < n_layers; ++l) T = std::max(T, layout_tokens(T_in, layers[l].K));
     // upper bound: every op could use the widest layer
@@ -1431,9 +1421,7 @@ static int prepare_any(const rb_layer *layers, const PlanOp *sops, int n_ops, ui
     std::vector<OpLinks> all_links;
     if (const int rc = link_ops(layers, sops, n_ops, all_links); rc != RB_OK) return rc;
     const OpLinks *const links = all_links.data();
-    size_t widest = 0;
-    for (int n = 0; n < n_ops; ++n) widest = std::max(widest, weights_of(layers[sops[n].layer]));
-    if (takes_flow(widest, tokens, block)) {
+    if (takes_flow(layers, sops, n_ops, tokens, block, G)) {
         const int rc = flow::prepare(layers, sops, links, n_ops, bufs, norm_w, eps, block, tokens, workspace, workspace_bytes_, stream);
         if (rc == RB_OK || rc == RB_ERR_HIP) {                 // (what was refused leaves the plan that was there)
             std::lock_guard<std::mutex> lock(g_mutex);

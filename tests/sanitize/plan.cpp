@@ -14,8 +14,49 @@ static int fail(const char *what, int trial, int n)
     return 1;
 }
 
+// Which plans of three and four tokens take the kernel of rb_flow.hip, on 256 compute units
+static int which_kernel()
+{
+    struct Shape { int out, in; };
+    auto takes = [](const std::vector<Shape> &shapes, int tokens, bool block) {
+        std::vector<rb_layer> layers;
+        std::vector<PlanOp> ops;
+        for (const Shape &s : shapes) {
+            layers.push_back(rb_layer{s.out, s.in, 2, nullptr, nullptr, nullptr});
+            ops.push_back(PlanOp{(int)ops.size(), 0, 1, -1, -1, ROLE_PLAIN});
+        }
+        return takes_flow(layers.data(), ops.data(), (int)ops.size(), tokens, block, 256);
+    };
+    auto blocks = [](int d, int f, int n, int head) {
+        std::vector<Shape> s;
+        for (int i = 0; i < n; ++i)
+            for (Shape o : {Shape{d, d}, {d, d}, {d, d}, {d, d}, {f, d}, {f, d}, {d, f}}) s.push_back(o);
+        if (head) s.push_back(Shape{head, d});
+        return s;
+    };
+    struct { std::vector<Shape> shapes; bool block, flow; } const cases[] = {
+        {blocks(4096, 11008, 32, 0), true, true},  {blocks(4096, 11008, 1, 0), false, true}, {blocks(1024, 2048, 8, 0), false, false},
+        {blocks(1216, 3328, 20, 0), false, true},  {blocks(2048, 7168, 3, 0), true, false},  {blocks(2496, 4992, 4, 0), true, true},
+        {blocks(2048, 8192, 3, 0), true, false},   {blocks(2048, 8192, 16, 0), true, true},
+        // narrow layers before a head, which alone is wide
+        {blocks(1024, 2048, 8, 32000), true, false}, {blocks(512, 2048, 16, 32000), false, false}, {blocks(2560, 6592, 4, 32000), true, true},
+        // long rows, many of them
+        {{{28672, 8192}}, false, false}, {{{32768, 6144}}, false, true}, {{{8192, 28672}}, false, true}, {blocks(8192, 28672, 1, 0), false, true},
+        // either side of a line, by one row of the smaller layer
+        {{{2500, 1024}, {2383, 1024}}, false, true}, {{{2500, 1024}, {2382, 1024}}, false, false},
+    };
+    int i = 0;
+    for (const auto &c : cases) {
+        for (int tokens = 1; tokens <= 4; ++tokens)
+            if (takes(c.shapes, tokens, c.block) != (c.flow && tokens > 2)) return fail("the wrong kernel", i, tokens);
+        ++i;
+    }
+    return 0;
+}
+
 int main()
 {
+    if (which_kernel()) return 1;
     std::mt19937 rng(3);
     auto pick = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
     int asides = 0, in_order = 0;

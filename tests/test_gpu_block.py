@@ -191,7 +191,7 @@ def test_ragged_rows_and_plain_ops_in_a_block(T, d, f):
     _check(ops, layers, norm_w, got, "mixed block list")
 
 
-# Blocks whose widest layers (17 M weights) are just wide enough for the kernel for three and four tokens: 130 row tiles, which eight
+# Blocks just wide enough for the kernel for three and four tokens (9.8 M weights in an op on the mean): 130 row tiles, which eight
 # wavefronts finish together, and 514, one or two to a workgroup of gate and of up; columns that end inside a column tile
 WIDE = {4096: 2080, 11008: 8224}
 
