@@ -83,9 +83,7 @@ struct alignas(64) Op {
     const void *resid;        // what is added to the result: fp16 [T][out] of the caller, the same put aside, or another op's rcopy
     const uint16_t *resid_src;   // the caller's buffer that is put aside (null: none)
     int resid_kind;           // RESID_*
-    int role;                 // ROLE_*
     int n_part;
-    float eps;
 };
 // The gate and the up projection of a feed-forward part run as two ops of a stage whose row tiles are dealt alike; the
 // wavefront that finishes a row tile of the gate takes the same rows of the up projection from LDS:
@@ -96,7 +94,6 @@ struct alignas(64) Op {
 struct alignas(64) Stage {
     int op0, nops, tiles, gated;
     int rt[MAX_STAGE_OPS];    // row tiles of each op
-    int n_deps;               // ops whose input an earlier stage of the launch writes
     int norm;                 // the ops normalise their input, which is the same for all of them
     int n_slots;              // finishing slots a workgroup may use
     uint32_t rec0;            // index of the stage's first finishing record

@@ -931,6 +931,7 @@ struct Prepared {
 };
 static std::mutex g_mutex;
 static std::map<const void *, Prepared> g_prepared;
+constexpr int STAGE_TILES = 96;             // sign tiles that a workgroup multiplies in the time that a stage takes besides
 
 int prepare(const rb_layer *layers, const PlanOp *sops, const OpLinks *links, int n_ops, uint16_t *const *bufs,
                        const uint16_t *const *norm_w, float eps, bool block, int tokens, void *workspace,
@@ -952,9 +953,7 @@ int prepare(const rb_layer *layers, const PlanOp *sops, const OpLinks *links, in
         o.g = L.g; o.h = L.h;
         o.x = bufs[sops[n].src];
         o.y = sops[n].dst >= 0 && links[n].stores ? bufs[sops[n].dst] : nullptr;
-        o.role = sops[n].role;
         o.norm_w = sops[n].norm >= 0 ? norm_w[sops[n].norm] : nullptr;
-        o.eps = eps;
         o.out = L.out; o.in = L.in;
         o.RT = row_tiles(L.out); o.CT = col_tiles(L.in);
         up_off[(size_t)n] = up_total;
@@ -977,6 +976,7 @@ int prepare(const rb_layer *layers, const PlanOp *sops, const OpLinks *links, in
         Stage s{};
         s.op0 = op0;
         s.norm = ops[(size_t)op0].norm_w != nullptr;
+        int ct_max = 0;
         for (int n = op0; n < n_ops && s.nops < MAX_STAGE_OPS; ++n) {
             bool conflict = false;
             for (int m = op0; m < n; ++m) {
@@ -987,11 +987,10 @@ int prepare(const rb_layer *layers, const PlanOp *sops, const OpLinks *links, in
             }
             const Op &o = ops[(size_t)n];
             if ((o.RT + G - 1) / G > MAXSLOT) return RB_ERR_UNSUPPORTED;
-            if (o.role == ROLE_GATE) {
+            if (sops[n].role == ROLE_GATE) {
                 // gate and up: a stage of their own; the row tiles of the two are dealt alike
                 if (n > op0) break;
                 if ((o.RT + G - 1) / G > GATED_SLOTS) return RB_ERR_UNSUPPORTED;
-                if (o.dep >= 0) s.n_deps = 2;
                 s.nops = 2;
                 s.gated = 1;
                 s.tiles = s.rt[0] = s.rt[1] = o.RT;
@@ -1000,13 +999,32 @@ int prepare(const rb_layer *layers, const PlanOp *sops, const OpLinks *links, in
             // one root mean square per token and stage: normalised ops share one only if they read the same
             if ((o.norm_w != nullptr) != (s.norm != 0) || (s.norm && (sops[n].src != sops[op0].src || o.dep != ops[(size_t)op0].dep))) conflict = true;
             // a workgroup's share lies in at most two ops: those between the first and the last are no shorter than a share
-            const int share = (s.tiles + o.RT + G - 1) / G;
+            const int share = (s.tiles + o.RT + G - 1) / G, longest = std::max(ct_max, o.CT);
             for (int i = 1; i < s.nops; ++i)
                 if (s.rt[i] < share) conflict = true;
             if (conflict || share > MAXSLOT) break;
-            if (o.dep >= 0) ++s.n_deps;
+            // Row tiles are dealt by number, so longer rows among shorter ones make some workgroups late: ops of other widths come along only where that is no
+            // more than a stage for each width would take (us of ops that read what the caller has, three tokens, together and apart: 4096 x 4096, two
+            // 11008 x 4096 and 4096 x 11008 49.5 and 23.8; 56 ops of 2048 x 5504 blocks, which leave half of the workgroups out, 62 and 98).  With a row tile or less for each
+            // workgroup neither is good: such plans are for the step lists, which deal each op by itself (14 pairs of 11008 x 4096 and 4096 x 11008 213 there, 307 and 228
+            // here, 28 ops of 2304 x 9216 blocks 66, 144 and 72; not 28 of 3584 x 9472, 100, 89 and 93)
+            int by_width = -STAGE_TILES;
+            bool uneven = false;
+            for (int i = 0; i <= s.nops; ++i) {
+                const Op &first = ops[(size_t)(op0 + i)];
+                int rt = 0, before = 0;
+                for (int j = 0; j <= s.nops; ++j)
+                    if (ops[(size_t)(op0 + j)].CT == first.CT) { rt += ops[(size_t)(op0 + j)].RT; before += j < i; }
+                if (before == 0) by_width += STAGE_TILES + (rt + G - 1) / G * first.CT;
+                if (first.CT != o.CT && 2 * first.RT > G && 2 * o.RT > G) {
+                    if (std::min(first.RT, o.RT) <= G) return RB_ERR_UNSUPPORTED;
+                    uneven = true;
+                }
+            }
+            if (uneven || share * longest > by_width) break;
             s.rt[s.nops++] = o.RT;
             s.tiles += o.RT;
+            ct_max = longest;
         }
         s.n_slots = (s.tiles + G - 1) / G + (s.gated ? GATED_SLOTS : 0);
         s.rec0 = (uint32_t)n_records;

@@ -450,7 +450,7 @@ __global__ __launch_bounds__(threads_of(TT), 1) void stack_kernel(const Header *
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int grp = blockIdx.x;
     const int n_stages = hdr_p->n_stages;
-    constexpr int T = TT, NB = nb_of(TT), KOP = kop_of(TT);
+    constexpr int NB = nb_of(TT), KOP = kop_of(TT);
 
     // ---- LDS set-up: clear the partial sums
     for (int i = threadIdx.x; i < Lds::PART_BYTES / 4; i += THREADS) part[i] = 0.f;
@@ -1427,7 +1427,7 @@ static int prepare_any(const rb_layer *layers, const PlanOp *sops, int n_ops, ui
             std::lock_guard<std::mutex> lock(g_mutex);
             g_prepared.erase(workspace);
         }
-        return rc;
+        if (rc != RB_ERR_UNSUPPORTED) return rc;               // (else for the step lists: independent ops of several widths)
     }
 
     // ---- ops, consumers, stages

@@ -678,6 +678,18 @@ def test_prepared_odd_batches_on_pure_chains(T, n_chain):
 ])
 def test_three_and_four_token_stack_forms(T, shapes):
     """Every op against the oracle on the input it read, and a second run bit for bit the first."""
+    _forms(T, shapes, shapes[-1][0] != 2928)
+
+
+@pytest.mark.parametrize("T", [3, 4])
+@pytest.mark.parametrize("rows,there", [(1600, True), (4000, False), (4112, True)])
+def test_independent_ops_of_two_widths_at_three_and_four_tokens(T, rows, there):
+    """Together in a stage where they leave half of the (256) workgroups out, on the step lists where they leave fewer out, else in stages of their
+    own."""
+    _forms(T, [(rows, 2080, -1), (rows, 4128, -1), (rows, 2080, -1), (rows, 4128, -1)], there)
+
+
+def _forms(T, shapes, there):
     rng = synth.child_rng(3, 500, T, len(shapes))
     layers, bufs, op_list = [], [synth.gaussian_activations(rng, T, shapes[0][1])], []
     for out, inn, src in shapes:
@@ -691,7 +703,7 @@ def test_three_and_four_token_stack_forms(T, shapes):
     dev = [torch.from_numpy(b).cuda() for b in bufs]
     stack = rb.Stack(dev_layers, op_list, dev, T)
     stack.prepare()
-    assert on_kernel_for_three_and_four_tokens(stack) == (shapes[-1][0] != 2928)
+    assert on_kernel_for_three_and_four_tokens(stack) == there
     runs = []
     for _ in range(2):
         for _, _, dst in op_list:
