@@ -328,8 +328,9 @@ __device__ __forceinline__ void lds_add(uint32_t at, uint32_t v) { asm volatile(
 // What a producer stores carries its own validity (a 16-byte group of an expanded input is all 0xff
 // until it is written), so a producer neither waits for its stores to be acknowledged nor raises a
 // flag, and nobody polls memory for flags.
-// BLK: the form that runs decoder blocks (normalised inputs, gate times up, residual additions when rows are finished).
-template <bool BLK>
+// BLK: the form that runs decoder blocks (normalised inputs, gate times up, residual additions when rows are finished).  LEFT_OUT: a stage has fewer row
+// tiles than there are workgroups.  (Of two forms: with the longer pause in it the other one of decoder blocks takes 1 % longer)
+template <bool BLK, bool LEFT_OUT>
 __global__ __launch_bounds__(THREADS, 3) void flow_kernel(const Work *__restrict__ work,
                                                            const SlotRec *__restrict__ slots, const float *__restrict__ vals,
                                                            const SlotExt *__restrict__ ext, uint8_t *up0, uint32_t *__restrict__ error,
@@ -706,8 +707,12 @@ __global__ __launch_bounds__(THREADS, 3) void flow_kernel(const Work *__restrict
         // what it asks for before they are done is stale in the L2 that it shares with some of them (one block of layers at three tokens, us without and with:
         // chains 2048 x 8192 35.9 and 28.1, 1280 x 5056 30.6 and 23.6, 3072 x 6144 31.1 and 28.1, a decoder block of 2048 x 8192 40.2 and 33.6; 64, 96 and 128
         // units for the built-in pause of 48 are the same within 2 %)
-        const int pauses = now.P[0] == 0 ? (st + 1 < n_stages ? 2 : 0) : st > 0 && (now.flags & (WORK_DEP0 | WORK_DEP1)) != 0 ? 1 : 0;
-        for (int i = 0; i < pauses * go_pause; ++i) __builtin_amdgcn_s_sleep(1);
+        if constexpr (LEFT_OUT) {
+            const int pauses = now.P[0] == 0 ? (st + 1 < n_stages ? 2 : 0) : st > 0 && (now.flags & (WORK_DEP0 | WORK_DEP1)) != 0 ? 1 : 0;
+            for (int i = 0; i < pauses * go_pause; ++i) __builtin_amdgcn_s_sleep(1);
+        } else if (st > 0 && (now.flags & (WORK_DEP0 | WORK_DEP1)) != 0) {
+            for (int i = 0; i < go_pause; ++i) __builtin_amdgcn_s_sleep(1);
+        }
         // ---- decoder blocks: what comes from other workgroups' finishing wavefronts besides the operands.  Both kinds are marked "not yet
         // written" (all ones) before the launch and looked at until they are not.  The sums of squares of token `wave`:
         constexpr int SSQ = 4;
@@ -924,6 +929,7 @@ struct Prepared {
     bool block = false;                     // a decoder block: the kernel form with the epilogues
     bool ext_norm = false;                  // some op normalises an input from outside
     bool aside = false;                     // some op adds what has to be put aside before the launch
+    bool left_out = false;                  // some stage has fewer row tiles than there are workgroups
     float eps = 0.f;
     // host memory the plan's tables are copied from: pageable, so it must outlive the queued copies
     std::shared_ptr<std::vector<uint8_t>> blob;
@@ -1035,6 +1041,7 @@ int prepare(const rb_layer *layers, const PlanOp *sops, const OpLinks *links, in
     Prepared pr;
     pr.n_ops = n_ops; pr.n_stages = (int)stages.size(); pr.G = G; pr.tokens = tokens;
     pr.n_expand = (int)expand_list.size();
+    for (const Stage &s : stages) pr.left_out = pr.left_out || s.tiles < G;
     for (int n : expand_list) pr.max_expand_in = std::max(pr.max_expand_in, ops[(size_t)n].in);
     for (int n = 0; n < n_ops; ++n) pr.chained = pr.chained || ops[(size_t)n].dep >= 0 || links[n].addend >= 0;
     // decoder blocks: what finishing wavefronts hand to each other (marked unwritten before every
@@ -1134,7 +1141,8 @@ int launch(void *workspace, size_t workspace_bytes_, int pause, hipStream_t stre
                            reinterpret_cast<uint32_t *>(ws + lay.error), pr.n_stages, pr.tokens, go_pause, pr.eps);
         return RB_OK;
     };
-    const int rc = pr.block ? launch_form(flow_kernel<true>) : launch_form(flow_kernel<false>);
+    const int rc = pr.block ? (pr.left_out ? launch_form(flow_kernel<true, true>) : launch_form(flow_kernel<true, false>))
+                            : (pr.left_out ? launch_form(flow_kernel<false, true>) : launch_form(flow_kernel<false, false>));
     if (rc != RB_OK) return rc;
     return hipGetLastError() == hipSuccess ? RB_OK : RB_ERR_HIP;
 }
