@@ -1,5 +1,5 @@
-// Three and four tokens of two-path layers: set-up kernels, the persistent kernel, and its host planner.  See rb_flow.h for the
-// layout of the operands and rb_mx.h for the arithmetic.
+// Three and four tokens of two-path layers whose ops have much to do (takes_flow in rb_plan.h; the others keep the step lists of rb_mx.hip): set-up
+// kernels, the persistent kernel, and its host planner.  See rb_flow.h for the layout of the operands and rb_mx.h for the arithmetic.
 //
 // The persistent kernel runs one workgroup per compute unit through the stages of the plan:
 //   * the row tiles of a stage's ops, one op after the other, are dealt to the workgroups in contiguous shares, so that a
@@ -19,11 +19,12 @@
 //     word that still reads 0xffffffff are waited for and read again past the L2.  The pause is a
 //     matter of speed, not of correctness.
 //
-// What bounds it: latencies and instruction issue.  A stage of a 7B-shaped stack takes 7.1 us at three and four tokens: 0.4 the pause, 1.3 the operands'
-// trip, 1 to 3 the products (two matrix instructions and 16 vector instructions per 1 KB of signs and path, 25 per row tile for the sums over terms), 0.7
-// until the slowest wavefront has filed its sums, 0.8 to finish rows, 0.8 tables and loop.  Measured, 7B-shaped, in dependency order (before: the
-// step-list kernel): three tokens 1242 -> 900 us, decoder blocks at three 1312 -> 980; 13B-shaped at four, 16 blocks 957 -> 685, with norms and residuals
-// 1030 -> 794; 16 blocks of 2048 columns at three 402 -> 321, 8 decoder blocks of 1024 at four 174 -> 172.  Fewer tokens stay on the step-list kernel: this form
+// What bounds it: latencies and instruction issue.  A stage of the 7B-shaped chain takes 7.1 us at three and four tokens, one of its decoder blocks 7.9: by time
+// stamps of all wavefronts, on the mean, the pause 1.5 and 1.4, operands 1.5 and 2.2 (5 and 3 % of the tiles late), products 1.9 and 1.6 (two matrix
+// instructions and 16 vector instructions per 1 KB of signs and path, 25 per row tile for the sums over terms), sums of squares and what is added 0 and 0.4, until the
+// slowest wavefront has filed its sums 1.0 and 1.3, finishing rows 0.4 and 0.6, tables 0.7 and 0.6.
+// Measured, 7B-shaped, in dependency order (before: the step-list kernel): three tokens 1235 -> 920 us, decoder blocks at three 1306 -> 1020; 13B-shaped at four, 16
+// blocks 969 -> 687, with norms and residuals 1037 -> 795; 16 blocks of 2048 x 5504 at three 397 -> 318.  Fewer tokens stay on the step-list kernel: this form
 // takes 770 us at one (641 there), at two 795 (839), but 930 for decoder blocks (852) and 355 for 16 blocks of 2048 columns (253).
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
@@ -53,7 +54,7 @@ using namespace rb::mx;
 // which also count as LDS traffic: every LDS wait would then wait for global stores to be acknowledged.
 #define RB_GLOBAL(T, p) ((__attribute__((address_space(1))) T *)(p))
 
-// Hand-over timing (a matter of speed only: a consuming wavefront checks what it gets), in units of 64 clocks: between a wavefront's own stores of a
+// Hand-over timing (a matter of speed only: a consuming wavefront checks what it gets), in units of 64 clocks, 27 ns: between a wavefront's own stores of a
 // stage and its first request of the next one's operands.  (us without it, with 24, 32, 40, 48, 64 units: 7B-shaped chain at three tokens
 // 1007 924 913 904 899 928, decoder blocks at three 1025 1012 1005 991 981 1019, of 13B at four, 16 of them, 802 803 801 800 794 775, 2048-wide chain at three
 // 335 318 316 316 321 343)
