@@ -23,8 +23,8 @@ static int play(const char *what, int K, const std::vector<int> &iterations)
         if (n < 1 || n > MOST_PASSES) { std::printf("%s: %d passes asked for\n", what, n); return 1; }
     }
     // Looks: one for every two passes or more (two over the mean) until an eighth of all is more, from 24 passes on one for every ninth that they grow, and
-    // one for every MOST_PASSES less an eighth.  Passes too many are all of the last request: an eighth, or for each update left FIRST_LOOK + 2 where it takes two.
-    const int n_updates = (int)iterations.size(), extra_allowed = needed / 8 + FIRST_LOOK * n_updates;
+    // one for every MOST_PASSES less an eighth.  Passes too many are all of the last request: a quarter, or for each update left FIRST_LOOK + 2 where it takes two.
+    const int n_updates = (int)iterations.size(), extra_allowed = needed / 4 + FIRST_LOOK * n_updates;
     const int looks_allowed = 12 + (int)std::ceil(std::log(std::max(1.0, needed / 24.0)) / std::log(9.0 / 8.0)) + needed / (MOST_PASSES - MOST_PASSES / 8);
     std::printf("%s: %d passes needed, %d asked for, %d looks\n", what, needed, asked, looks);
     if (looks > looks_allowed || asked - needed > extra_allowed) { std::printf("%s: too many\n", what); return 1; }
