@@ -895,17 +895,6 @@ static Layout make_layout(int n_ops, int n_stages, int G, size_t n_records, size
     return L;
 }
 
-// per op of a decoder block, at most: sums of squares of its output and of an input from outside,
-// and the copy of its output that a later op adds
-static size_t block_aux_bound(const rb_layer *layers, int n_layers, int tokens)
-{
-    size_t most = 0;
-    for (int l = 0; l < n_layers; ++l)
-        most = std::max(most, align_up((size_t)row_tiles(layers[l].out) * 16, 256) + align_up((size_t)tokens * layers[l].out * 4, 256) +
-                                  align_up((size_t)((layers[l].in + 15) / 16) * 16, 256));
-    return most;
-}
-
 size_t plan_workspace_bytes(const rb_layer *layers, int n_layers, int n_ops, int tokens, bool block)
 {
     // upper bound: every op could use the widest layer

@@ -1327,17 +1327,6 @@ bool layer_supported(const rb_layer *L, int T)
     return ((L->K == 2 && T >= 1 && T <= MAX_T) || (L->K == 3 && T == 1)) && L->in % 32 == 0 && L->in <= 65536;
 }
 
-// per op of a decoder block, at most: sums of squares of its output and of an input from outside,
-// and the copy of its output that a later op adds
-static size_t block_aux_bound(const rb_layer *layers, int n_layers, int tokens)
-{
-    size_t most = 0;
-    for (int l = 0; l < n_layers; ++l)
-        most = std::max(most, align_up((size_t)row_tiles(layers[l].out) * 16, 256) + align_up((size_t)tokens * layers[l].out * 4, 256) +
-                                  align_up((size_t)((layers[l].in + 15) / 16) * 16, 256));
-    return most;
-}
-
 size_t plan_workspace_bytes(const rb_layer *layers, int n_layers, int n_ops, int T_in, bool block)
 {
     // (room for the step lists also where the plan takes the other kernel, which needs less: a workspace sized for the most

@@ -1,6 +1,7 @@
 // How the ops of a plan hang together, for both persistent decode kernels (host only): who writes what an op reads and adds, and where a
-// launch, which has no barriers between ops, needs more than that to give what the ops give one after the other.
+// launch, which has no barriers between ops, needs more than that to give what the ops give one after the other; and which of the two takes a plan.
 #pragma once
+#include <algorithm>
 #include <vector>
 
 #include "rabit.h"
@@ -47,6 +48,17 @@ inline bool takes_flow(const rb_layer *layers, const PlanOp *ops, int n_ops, int
     }
     if (block && 2 * narrow > n_ops && n_ops < FLOW_NARROW_BLOCK_OPS) return false;
     return tokens > 2 && all >= flow_weights(block) * (size_t)n_ops && 2 * beyond <= all;
+}
+
+// Per op of a decoder block, at most: sums of squares of its output and of an input from outside, and the copy of its output that a later op adds.  (What is put
+// aside of the caller's is 2 bytes where the copy is 4: a plan is sized for two ops for each of the caller's, and only one of the two adds)
+inline size_t block_aux_bound(const rb_layer *layers, int n_layers, int tokens)
+{
+    size_t most = 0;
+    for (int l = 0; l < n_layers; ++l)
+        most = std::max(most, align_up((size_t)row_tiles(layers[l].out) * 16, 256) + align_up((size_t)tokens * layers[l].out * 4, 256) +
+                                  align_up((size_t)((layers[l].in + 15) / 16) * 16, 256));
+    return most;
 }
 
 struct OpLinks {
